@@ -329,8 +329,8 @@ def step_bench(args, cfg, scale_down=1, agg_dtype="f32", copy_gbs=None, graph=No
     if share_bf16:
         nn_peak = BF16_MFMA_PEAK_TFLOPS       # bf16 operands: one bf16 matrix instruction per product
     roofline_nn = dict(bound="mfma",
-                       kernel=("gemm_split_kernel (fp32 products from bf16 pieces, 6 bf16 MFMA per product; "
-                               "peak = 2500/6) + gemm_kernel (fp32 MFMA) for narrow products, all transform calls of a step"
+                       kernel=("strip_kernel, dw_kernel (fp32 products from bf16 pieces, 6 bf16 MFMA per product; "
+                               "peak = 2500/6), all transform calls of a step"
                                if split_core else "gemm_kernel (fp32 MFMA, all transform calls of a step)"),
                        achieved=nn_tflops, peak=nn_peak, unit="TFLOP/s (useful fp32 flops)",
                        frac=(nn_tflops / nn_peak) if nn_tflops else None,

@@ -14,8 +14,8 @@ LIB = os.path.join(PKG, "libntp.so")
 PROBE_SRC = os.path.join(CSRC, "line_rate_probe.hip")
 PROBE = os.path.join(PKG, "line_rate_probe")        # prints the chip's 128-byte line rates (L2 / Infinity Cache / HBM)
 
-SOURCES = ["graph_build.cpp", "plan.cpp", "ntp_api.hip", "agg_kernels.hip", "scatter_kernels.hip", "chunk_kernels.hip", "attention_kernels.hip", "attention_scores_kernels.hip", "loss_kernels.hip", "nn_kernels.hip"]
-HEADERS = [os.path.join(CSRC, "ntp_internal.h"), os.path.join(CSRC, "lane_util.h"), os.path.join(ROOT, "include", "ntp.h")]
+SOURCES = ["graph_build.cpp", "plan.cpp", "ntp_api.hip", "agg_kernels.hip", "scatter_kernels.hip", "chunk_kernels.hip", "attention_kernels.hip", "attention_scores_kernels.hip", "loss_kernels.hip", "nn_kernels.hip", "nn_strip_kernels.hip", "nn_dw_kernels.hip"]
+HEADERS = [os.path.join(CSRC, "ntp_internal.h"), os.path.join(CSRC, "lane_util.h"), os.path.join(CSRC, "nn_util.h"), os.path.join(ROOT, "include", "ntp.h")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
           "-ffp-contract=off", "-Wall", "-Wno-unused-function"]

@@ -1,64 +1,31 @@
 // Dense transform of eq. (4) on the matrix cores of gfx950: H = act(A W), and its
 // gradients dW = A^T dZ, dA = dZ W^T with dZ = dH * 1[H > 0].
 //
-// One tiled kernel serves the three products.  A block of 256 threads (4 wavefronts)
-// owns a BM x BN tile of the output; the contraction runs in steps of BK = 32 through
-// LDS.  Both operands are kept in LDS as [kk][mn] (contraction index major), so a
-// wavefront reads the fragments of v_mfma_f32_32x32x2_f32 (lane = 32*kk + mn) as 32
-// consecutive floats per half wave, free of bank conflicts.  An operand whose memory
-// layout is contraction-contiguous (A in the forward, dH and W in dA) is transposed on its
-// way into LDS; the ReLU mask and the bf16 -> fp32 conversion are applied on the same way.
-// The next tile is fetched into registers while the current one is multiplied.
-// dW contracts over the vertices: the rows are split over blocks, each block writes an
-// fp32 partial [K x M] to the caller's workspace and a second kernel adds them in order
-// (deterministic, no atomics).
+// The products run on the bf16 matrix instructions (v_mfma_f32_32x32x16_bf16): every fp32 operand element is cut into three
+// bf16 pieces hi + mid + lo = x (exact: 3 x 8 significant bits, by truncation), and a product a*b is formed as the
+// six piece products of weight >= 2^-16 (hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi), each exact in the fp32
+// accumulator's input; the dropped pieces are below 2^-23 |a b|.  Six bf16 instructions cost 6 x 32 cycles per 32x32x16
+// block against 8 x 64 for fp32, and operands that are bf16 in memory need one piece only.  H and dA: nn_strip_kernels.hip;
+// dW: nn_dw_kernels.hip, partial sums to the caller's workspace, added in order here (deterministic, no atomics).
 //
-// Two multiply cores share that skeleton:
-//   * fp32 MFMA (v_mfma_f32_32x32x2_f32), the plain form;
-//   * split bf16 MFMA (v_mfma_f32_32x32x16_bf16), the default: every fp32 operand element
-//     is cut into three bf16 pieces hi + mid + lo = x (exact: 3 x 8 significant bits, by
-//     truncation) on its way into LDS, and a product a*b is formed as the six piece
-//     products of weight >= 2^-16 (hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi), each exact
-//     in the fp32 accumulator's input; the dropped pieces are below 2^-23 |a b|.  Six bf16
-//     instructions cost 6 x 32 cycles per 32x32x16 block against 8 x 64 for fp32, and
-//     operands that are bf16 in memory need one piece only.
+// This file holds the dispatch and the plain fp32 form (v_mfma_f32_32x32x2_f32), which NTP_NN_CORE=fp32 selects for
+// comparison and which computes dW of matrices of fewer than four columns.  A block of 256 threads (4 wavefronts)
+// owns a BM x BN tile of the output; the contraction runs in steps of BK = 32 through LDS.  Both operands are kept in LDS
+// as [kk][mn] (contraction index major), so a wavefront reads the fragments (lane = 32*kk + mn) as 32
+// consecutive floats per half wave, free of bank conflicts.  An operand whose memory layout is contraction-contiguous (A in
+// the forward, dH and W in dA) is transposed on its way into LDS; the ReLU mask and the bf16 -> fp32 conversion are
+// applied on the same way.  The next tile is fetched into registers while the current one is multiplied.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdlib>
 
+#include "nn_util.h"
 #include "ntp_internal.h"
 
 namespace ntp {
 
 namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-// pieces an element of type T is cut into for the bf16 core
-template <class T> struct Pieces { static constexpr int n = 3; };
-template <> struct Pieces<unsigned short> { static constexpr int n = 1; };
-
-// x = sum of NP bf16 values, each returned as an fp32 bit pattern whose low half is zero
-// (NP = 1: x is a bf16 value already)
-template <int NP>
-__device__ __forceinline__ void split_bf16(float x, unsigned (&piece)[NP]) {
-    if constexpr (NP == 1) {
-        piece[0] = __float_as_uint(x);
-    } else {
-        const unsigned hi = __float_as_uint(x) & 0xffff0000u;
-        const float r1 = x - __uint_as_float(hi);                 // exact: at most 16 significant bits left
-        const unsigned mid = __float_as_uint(r1) & 0xffff0000u;
-        const float r2 = r1 - __uint_as_float(mid);               // exact: at most 8 significant bits left
-        piece[0] = hi; piece[1] = mid; piece[2] = __float_as_uint(r2);
-    }
-}
-// bf16 pair in one dword: low half = piece of the even contraction index, high half = odd
-__device__ __forceinline__ unsigned pack_pair(unsigned even, unsigned odd) {
-    return __builtin_amdgcn_perm(odd, even, 0x07060302u);
-}
 
 constexpr int BK = 32;
 constexpr int NTHREADS = 256;
@@ -81,18 +48,6 @@ struct GemmArgs {
     int tiles_m, tiles_n, n_splits;
     int share_splits;             // 1: major = split (dW), 0: major = row tile of C
 };
-
-__device__ __forceinline__ float elem_to_f32(float v) { return v; }
-__device__ __forceinline__ float elem_to_f32(unsigned short v) { return __uint_as_float((unsigned)v << 16); }
-
-__device__ __forceinline__ unsigned f32_to_bf16_bits(float f) {
-    unsigned u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
-__device__ __forceinline__ void store_elem(unsigned short* p, float v) { *p = (unsigned short)f32_to_bf16_bits(v); }
 
 // four consecutive elements starting at p (aligned for the vector path), as floats
 __device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
@@ -294,343 +249,6 @@ __global__ void __launch_bounds__(NTHREADS) gemm_kernel(const GemmArgs g) {
     store_tile<TC, TM, TN>(g, acc, bz, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane);
 }
 
-// ---- the split-bf16 core -----------------------------------------------------------------
-// LDS holds, per operand and piece, P[g][mn] = four dwords = the eight bf16 of contraction
-// indices 8g .. 8g+7 of tile row/column mn (g = 0..BK/8-1).  A lane of the 32x32x16
-// instruction (mn = lane % 32, h = lane / 32) needs exactly such a 16-byte group
-// (g = 2c + h in chunk c), so a fragment is one ds_read_b128 and consecutive lanes read
-// consecutive 16 bytes.
-//
-// Operand loaders.  Each thread owns whole items of the tile:
-//   contraction-contiguous source (memory rows run along k): an item = 4 consecutive k of
-//     one row mn = half a group, written with one 8-byte LDS store per piece;
-//   otherwise (memory rows run along mn): an item = 8 contraction rows x 2 adjacent mn =
-//     two whole groups, loaded with eight 8-byte reads that are contiguous across the lanes.
-// fetch<true> is the interior form: no bounds checks and no branches (rows/columns beyond
-// the matrix are clamped to the last valid ones: what they produce lands only in output
-// rows/columns that are never stored), so the loads of two tiles can be in flight with
-// exact wait counts.  fetch<false> checks every element and reads zero outside.
-template <class T, bool KCONTIG, bool MASK, int TILE_MN> struct Loader;
-
-template <class T, bool MASK, int TILE_MN>
-struct Loader<T, true, MASK, TILE_MN> {
-    static constexpr int NI = TILE_MN * BK / 4 / NTHREADS;     // items per thread (all threads busy)
-    static constexpr int REGS = 4;
-    using Regs = float[NI][REGS];
-    static __device__ __forceinline__ bool can_be_fast(const void* src, const void* mask, int64_t ld, int64_t mn_lim) {
-        return mn_lim > 0 && ld % 4 == 0 && (uintptr_t)src % (4 * sizeof(T)) == 0 && (!MASK || (uintptr_t)mask % (4 * sizeof(T)) == 0);
-    }
-    template <bool FAST>
-    static __device__ __forceinline__ void fetch(const T* __restrict__ src, const T* __restrict__ mask, int64_t ld,
-                                                 int64_t mn0, int64_t k0, int64_t mn_lim, int64_t k_lim, Regs& regs) {
-#pragma unroll
-        for (int v = 0; v < NI; ++v) {
-            const int idx = threadIdx.x + NTHREADS * v;
-            const int r = idx / (BK / 4), c4 = (idx % (BK / 4)) * 4;
-            if constexpr (FAST) {
-                int64_t row = mn0 + r;
-                row = row < mn_lim ? row : mn_lim - 1;
-                const int64_t off = row * ld + k0 + c4;
-                load4(src + off, regs[v]);
-                if constexpr (MASK) {
-                    float m[4];
-                    load4(mask + off, m);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) regs[v][e] = m[e] > 0.f ? regs[v][e] : 0.f;
-                }
-            } else {
-                const bool vec_ok = ld % 4 == 0 && (uintptr_t)src % (4 * sizeof(T)) == 0 && (!MASK || (uintptr_t)mask % (4 * sizeof(T)) == 0);
-                load_vec4<T, MASK>(src, mask, ld, mn0 + r, k0 + c4, mn_lim, k_lim, vec_ok, regs[v]);
-            }
-        }
-    }
-    template <int NP, int LD>
-    static __device__ __forceinline__ void stash(uint4 (*dst)[BK / 8][LD], const Regs& regs) {
-#pragma unroll
-        for (int v = 0; v < NI; ++v) {
-            const int idx = threadIdx.x + NTHREADS * v;
-            const int r = idx / (BK / 4), q = idx % (BK / 4);       // q-th group of four k: half of group q/2
-            unsigned x[4][NP];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) split_bf16<NP>(regs[v][e], x[e]);
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                unsigned* g4 = reinterpret_cast<unsigned*>(&dst[p][q / 2][r]);
-                *reinterpret_cast<uint2*>(g4 + 2 * (q % 2)) = make_uint2(pack_pair(x[0][p], x[1][p]), pack_pair(x[2][p], x[3][p]));
-            }
-        }
-    }
-};
-
-template <class T, bool MASK, int TILE_MN>
-struct Loader<T, false, MASK, TILE_MN> {
-    static constexpr int ITEMS = (BK / 8) * (TILE_MN / 2);
-    static constexpr int NI = (ITEMS + NTHREADS - 1) / NTHREADS;
-    static constexpr bool ALL = ITEMS % NTHREADS == 0;
-    static constexpr int REGS = 16;                               // [8 contraction rows][2 mn]
-    using Regs = float[NI][REGS];
-    static __device__ __forceinline__ bool can_be_fast(const void* src, const void* mask, int64_t ld, int64_t mn_lim) {
-        return mn_lim >= 2 && mn_lim % 2 == 0 && ld % 2 == 0 && (uintptr_t)src % (2 * sizeof(T)) == 0 &&
-               (!MASK || (uintptr_t)mask % (2 * sizeof(T)) == 0);
-    }
-    static __device__ __forceinline__ void load2(const float* p, float& a, float& b) {
-        const float2 t = *reinterpret_cast<const float2*>(p);
-        a = t.x; b = t.y;
-    }
-    static __device__ __forceinline__ void load2(const unsigned short* p, float& a, float& b) {
-        const unsigned t = *reinterpret_cast<const unsigned*>(p);
-        a = __uint_as_float(t << 16); b = __uint_as_float(t & 0xffff0000u);
-    }
-    template <bool FAST>
-    static __device__ __forceinline__ void fetch(const T* __restrict__ src, const T* __restrict__ mask, int64_t ld,
-                                                 int64_t mn0, int64_t k0, int64_t mn_lim, int64_t k_lim, Regs& regs) {
-#pragma unroll
-        for (int u = 0; u < NI; ++u) {
-            const int idx = threadIdx.x + NTHREADS * u;
-            const int g = idx / (TILE_MN / 2), m2 = (idx % (TILE_MN / 2)) * 2;
-            if (ALL || idx < ITEMS) {
-                if constexpr (FAST) {
-                    int64_t col = mn0 + m2;
-                    col = col < mn_lim ? col : mn_lim - 2;
-                    const T* p = src + (k0 + 8 * g) * ld + col;
-                    const T* pm = MASK ? mask + (k0 + 8 * g) * ld + col : nullptr;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        load2(p + j * ld, regs[u][2 * j], regs[u][2 * j + 1]);
-                        if constexpr (MASK) {
-                            float ma, mb;
-                            load2(pm + j * ld, ma, mb);
-                            regs[u][2 * j] = ma > 0.f ? regs[u][2 * j] : 0.f;
-                            regs[u][2 * j + 1] = mb > 0.f ? regs[u][2 * j + 1] : 0.f;
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const int64_t row = k0 + 8 * g + j, col = mn0 + m2 + e;
-                            float t = 0.f;
-                            if (row < k_lim && col < mn_lim) {
-                                t = elem_to_f32(src[row * ld + col]);
-                                if constexpr (MASK) t = elem_to_f32(mask[row * ld + col]) > 0.f ? t : 0.f;
-                            }
-                            regs[u][2 * j + e] = t;
-                        }
-                }
-            }
-        }
-    }
-    template <int NP, int LD>
-    static __device__ __forceinline__ void stash(uint4 (*dst)[BK / 8][LD], const Regs& regs) {
-#pragma unroll
-        for (int u = 0; u < NI; ++u) {
-            const int idx = threadIdx.x + NTHREADS * u;
-            const int g = idx / (TILE_MN / 2), m2 = (idx % (TILE_MN / 2)) * 2;
-            if (ALL || idx < ITEMS) {
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    unsigned x[8][NP];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) split_bf16<NP>(regs[u][2 * j + e], x[j]);
-#pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        dst[p][g][m2 + e] = make_uint4(pack_pair(x[0][p], x[1][p]), pack_pair(x[2][p], x[3][p]),
-                                                       pack_pair(x[4][p], x[5][p]), pack_pair(x[6][p], x[7][p]));
-                }
-            }
-        }
-    }
-};
-
-// Scheduling hint for one pipelined step: after the first fragment reads, every matrix
-// instruction is followed by a few vector instructions of the stash (and now and then an LDS
-// write or a fragment read of the next chunk), so that the matrix pipe runs while the vector
-// pipe cuts the next tile into pieces.
-template <int N, int VALU_PER_MFMA, int DS_READS_FIRST>
-__device__ __forceinline__ void interleave_hint() {
-    if constexpr (N > 0) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, VALU_PER_MFMA, 0);   // vector ALU
-        if constexpr (N % 2 == 0) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // an LDS write
-        if constexpr (N % 2 == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // an LDS read
-        interleave_hint<N - 1, VALU_PER_MFMA, DS_READS_FIRST>();
-    }
-}
-
-// LDS bytes of the split kernel: two buffers of (pieces x BK/8 groups x padded tile) 16-byte groups
-template <class TA, class TB, int BM, int BN>
-constexpr int split_lds_bytes() {
-    return 2 * (BK / 8) * 16 * (Pieces<TA>::n * (BM + 4) + Pieces<TB>::n * (BN + 4));
-}
-
-// Two schedules of the same step (fetch a tile to registers, cut it into pieces and write it
-// to LDS, multiply it):
-//   OCC >= 2 (the default for fp32 operands): one LDS buffer (50-63 KB), OCC blocks per compute
-//     unit.  A block stores tile s, multiplies it while tile s+1 is on its way from memory, and
-//     meets a barrier on either side of the store; what overlaps the cutting, the LDS traffic
-//     and the waiting of one block is the other block on the same compute unit.  Measured
-//     against the schedule below (169,343 rows): forward 128->256 0.132 -> 0.103 ms, 256->256
-//     0.202 -> 0.183 ms, dA 0.242 -> 0.190 ms, dW (with twice the row splits) 0.228 -> 0.208 ms.
-//   OCC == 1: two LDS buffers (100-126 KB for fp32 operands), one block per compute unit.  In
-//     step s a wavefront multiplies the tile in buffer s%2 while it cuts tile s+1 (already in
-//     registers) into pieces and writes it to the other buffer, and tile s+2 is on its way from
-//     memory: the three tiles overlap inside every wavefront, with one barrier per step.  Kept
-//     for bf16 operands with narrow outputs, where it measured faster (dW 256x40: 0.047 against
-//     0.074 ms).
-template <class TA, class TB, class TC, bool A_KCONTIG, bool B_KCONTIG, bool MASK_A, bool MASK_B,
-          int BM, int BN, int WM, int WN, int OCC = 1>
-__global__ void __launch_bounds__(NTHREADS, OCC) gemm_split_kernel(const GemmArgs g) {
-    constexpr bool ONEBUF = OCC > 1;      // one LDS buffer, OCC blocks per compute unit
-    static_assert(WM * WN == 4, "four wavefronts per block");
-    constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-    constexpr int NPA = Pieces<TA>::n, NPB = Pieces<TB>::n;
-    // row stride in 16-byte groups: 4 mod 16 spreads the 8-byte stores of a contraction-
-    // contiguous source (4 rows x 4 groups x 2 halves per 32 lanes) over all banks
-    constexpr int LDA_S = BM + 4, LDB_S = BN + 4;
-    extern __shared__ uint4 smem[];
-    typedef uint4 (*TileA)[BK / 8][LDA_S];
-    typedef uint4 (*TileB)[BK / 8][LDB_S];
-    // two buffers: [A0 | A1 | B0 | B1]; one buffer: [A0 | B0]
-    const TileA As0 = reinterpret_cast<TileA>(smem), As1 = As0 + NPA;
-    const TileB Bs0 = reinterpret_cast<TileB>(ONEBUF ? As1 : As1 + NPA), Bs1 = Bs0 + NPB;
-    using LA = Loader<TA, A_KCONTIG, MASK_A, BM>;
-    using LB = Loader<TB, B_KCONTIG, MASK_B, BN>;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int wm = wave / WN, wn = wave % WN;
-    int bx, by, bz;
-    if (!block_to_tile(g, bx, by, bz)) return;     // padding of the last group of eight
-    const int64_t m0 = (int64_t)bx * BM;
-    const int64_t n0 = (int64_t)by * BN;
-    const int64_t kbeg = (int64_t)bz * g.k_per_split;
-    const int64_t kend = kbeg + g.k_per_split < g.Kdim ? kbeg + g.k_per_split : g.Kdim;
-
-    const TA* A = static_cast<const TA*>(g.A);
-    const TB* B = static_cast<const TB*>(g.B);
-    const TA* mA = static_cast<const TA*>(g.maskA);
-    const TB* mB = static_cast<const TB*>(g.maskB);
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    const int mn_a = wm * (TM * 32) + (lane & 31);
-    const int mn_b = wn * (TN * 32) + (lane & 31);
-    const int h = lane >> 5;
-    // multiply the tile held in (as, bs) into the accumulators
-    auto multiply = [&](TileA as, TileB bs) {
-#pragma unroll
-        for (int c = 0; c < BK / 16; ++c) {
-            uint4 a[TM][NPA], b[TN][NPB];
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int p = 0; p < NPA; ++p) a[i][p] = as[p][2 * c + h][mn_a + i * 32];
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int p = 0; p < NPB; ++p) b[j][p] = bs[p][2 * c + h][mn_b + j * 32];
-            // piece products of weight 2^-8w, small ones first; consecutive instructions go to
-            // different accumulators so that none waits for its predecessor
-#pragma unroll
-            for (int w = 2; w >= 0; --w)
-#pragma unroll
-                for (int pa = 0; pa <= w; ++pa)
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) {
-                            const int pb = w - pa;
-                            if (pa < NPA && pb < NPB)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                    __builtin_bit_cast(bf16x8, a[i][pa < NPA ? pa : 0]), __builtin_bit_cast(bf16x8, b[j][pb < NPB ? pb : 0]), acc[i][j], 0, 0, 0);
-                        }
-        }
-    };
-    auto stash = [&](TileA as, TileB bs, const typename LA::Regs& ra, const typename LB::Regs& rb) {
-        LA::template stash<NPA, LDA_S>(as, ra);
-        LB::template stash<NPB, LDB_S>(bs, rb);
-    };
-
-    int64_t k0 = kbeg;
-    const bool fast = LA::can_be_fast(A, mA, g.lda, g.Mdim) && LB::can_be_fast(B, mB, g.ldb, g.Ndim);
-    if (!ONEBUF && fast && kend - kbeg >= 2 * BK) {
-        // An even number of whole steps.  Every fetch is issued unconditionally (past the end
-        // it re-reads a tile already taken, and what is stashed from it is never multiplied)
-        // so that the number of loads in flight is known at compile time and a stash waits
-        // only for its own tile; the scheduling fences keep the loads in program order, which
-        // the wait counts rely on.
-        const int64_t npipe = (kend - kbeg) / BK / 2 * 2;
-        constexpr int N_PROD = NPA == 3 && NPB == 3 ? 6 : (NPA == 1 && NPB == 1 ? 1 : 3);
-        constexpr int N_MFMA = (BK / 16) * TM * TN * N_PROD;           // matrix instructions per step
-        constexpr int FIRST_READS = TM * NPA + TN * NPB;               // fragment reads of the first chunk
-        constexpr int VALU_PER_MFMA = (LA::NI * LA::REGS * (4 * NPA - 2) + LB::NI * LB::REGS * (4 * NPB - 2)) / N_MFMA + 1;
-        typename LA::Regs ra0, ra1;
-        typename LB::Regs rb0, rb1;
-        auto fetch = [&](int64_t s, typename LA::Regs& ra, typename LB::Regs& rb) {
-            LA::template fetch<true>(A, mA, g.lda, m0, kbeg + s * BK, g.Mdim, kend, ra);
-            LB::template fetch<true>(B, mB, g.ldb, n0, kbeg + s * BK, g.Ndim, kend, rb);
-        };
-        fetch(0, ra0, rb0);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(1, ra1, rb1);
-        __builtin_amdgcn_sched_barrier(0);
-        stash(As0, Bs0, ra0, rb0);
-        __syncthreads();
-        for (int64_t s = 0; s < npipe; s += 2) {
-            fetch(s + 2 < npipe ? s + 2 : s, ra0, rb0);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(As0, Bs0);                 // tile s
-            stash(As1, Bs1, ra1, rb1);          // tile s+1
-            __builtin_amdgcn_sched_group_barrier(0x100, FIRST_READS, 0);
-            interleave_hint<N_MFMA, VALU_PER_MFMA, FIRST_READS>();
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-            fetch(s + 3 < npipe ? s + 3 : s + 1, ra1, rb1);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(As1, Bs1);                 // tile s+1
-            stash(As0, Bs0, ra0, rb0);          // tile s+2 (not used after the last step)
-            __builtin_amdgcn_sched_group_barrier(0x100, FIRST_READS, 0);
-            interleave_hint<N_MFMA, VALU_PER_MFMA, FIRST_READS>();
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-        }
-        k0 = kbeg + npipe * BK;
-    }
-    // what is left (an odd whole step, a partial last step, or everything when the operands
-    // are not aligned for the interior form): checked loads, one buffer, next tile fetched
-    // while this one is multiplied
-    if (k0 < kend) {
-        typename LA::Regs ra;
-        typename LB::Regs rb;
-        auto fetch1 = [&](int64_t k) {
-            if (ONEBUF && fast && k + BK <= kend) {
-                LA::template fetch<true>(A, mA, g.lda, m0, k, g.Mdim, kend, ra);
-                LB::template fetch<true>(B, mB, g.ldb, n0, k, g.Ndim, kend, rb);
-            } else {
-                LA::template fetch<false>(A, mA, g.lda, m0, k, g.Mdim, kend, ra);
-                LB::template fetch<false>(B, mB, g.ldb, n0, k, g.Ndim, kend, rb);
-            }
-        };
-        fetch1(k0);
-        for (; k0 < kend; k0 += BK) {
-            __syncthreads();
-            stash(As0, Bs0, ra, rb);
-            __syncthreads();
-            if (k0 + BK < kend) fetch1(k0 + BK);
-            multiply(As0, Bs0);
-        }
-    }
-
-    store_tile<TC, TM, TN>(g, acc, bz, m0 + wm * (TM * 32), n0 + wn * (TN * 32), lane);
-}
-
 // out[i] = sum over the splits of part[s * stride + i].  A block owns 64 consecutive
 // elements; wavefront w adds the splits w, w+4, ... in ascending order and the four sums
 // are combined as (s0 + s1) + (s2 + s3): fixed order, deterministic.
@@ -690,27 +308,6 @@ bool use_split_core() {
     return v;
 }
 
-// NTP_NN_SCHEDULE=1 / 2 forces the two-buffer / one-buffer schedule of the split core (for comparison)
-int split_schedule() {
-    static const int v = [] {
-        const char* e = getenv("NTP_NN_SCHEDULE");
-        return e ? atoi(e) : 0;
-    }();
-    return v;
-}
-
-// launch a split-core kernel with LDS bytes of dynamic LDS (more than the 64 KB a kernel may use
-// without asking, so the limit is raised once per kernel and device)
-template <auto kernel, int LDS>
-void launch_split(int64_t blocks, hipStream_t st, const GemmArgs& g) {
-    static bool allowed[64] = {};              // one table per kernel instantiation
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    if (dev >= 0 && dev < 64 && !allowed[dev])
-        allowed[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS) == hipSuccess;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NTHREADS), LDS, st, g);
-}
-
 template <class TA, class TB, class TC, bool AK, bool BKC, bool MA, bool MB, int BM, int BN, int WM, int WN>
 void launch_tiles(GemmArgs g, int n_splits, hipStream_t st) {
     g.tiles_m = (int)((g.Mdim + BM - 1) / BM);
@@ -720,22 +317,7 @@ void launch_tiles(GemmArgs g, int n_splits, hipStream_t st) {
     const int64_t n_major = g.share_splits ? n_splits : g.tiles_m;
     const int64_t n_minor = g.share_splits ? (int64_t)g.tiles_m * g.tiles_n : g.tiles_n;
     const int64_t blocks = (n_major + 7) / 8 * 8 * n_minor;
-    // The split core pays off from two contraction steps per block on and for output tiles of at
-    // least 64 columns; shorter contractions and narrower outputs (memory bound) stay on the plain
-    // core.  bf16 operands need one piece product only and always take the bf16 instructions.
-    const int64_t k_len = std::min<int64_t>(g.k_per_split, g.Kdim);
-    const bool split_pays = sizeof(TA) == 2 || (k_len >= 2 * BK && BN >= 64);
-    // fp32 operands: one LDS buffer and two blocks per compute unit; bf16 operands (one piece,
-    // small tiles in LDS either way): the same for wide outputs, the two-buffer schedule otherwise
-    const bool one_buffer = split_schedule() == 0 ? (sizeof(TA) == 4 || BN >= 128) : split_schedule() == 2;
-    if (use_split_core() && split_pays && one_buffer) {
-        constexpr int lds = split_lds_bytes<TA, TB, BM, BN>() / 2;
-        launch_split<gemm_split_kernel<TA, TB, TC, AK, BKC, MA, MB, BM, BN, WM, WN, 2>, lds>(blocks, st, g);
-    } else if (use_split_core() && split_pays) {
-        constexpr int lds = split_lds_bytes<TA, TB, BM, BN>();
-        launch_split<gemm_split_kernel<TA, TB, TC, AK, BKC, MA, MB, BM, BN, WM, WN, 1>, lds>(blocks, st, g);
-    } else
-        hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, AK, BKC, MA, MB, BM, BN, WM, WN>), dim3((unsigned)blocks), dim3(NTHREADS), 0, st, g);
+    hipLaunchKernelGGL((gemm_kernel<TA, TB, TC, AK, BKC, MA, MB, BM, BN, WM, WN>), dim3((unsigned)blocks), dim3(NTHREADS), 0, st, g);
 }
 
 template <class TA, class TB, class TC, bool AK, bool BKC, bool MA, bool MB>
@@ -777,8 +359,21 @@ int dw_splits(int64_t n, int64_t k, int64_t m) {
     return (int)std::min<int64_t>(s, 1024);
 }
 
+// dW = sum of the partial sums of the splits
+int sum_splits(const void* ws, float* dW, int64_t count, int splits, hipStream_t st) {
+    if (splits <= 1) return NTP_OK;
+    hipLaunchKernelGGL(sum_splits_kernel, dim3((unsigned)((count + 63) / 64)), dim3(256), 0, st,
+                       (const float*)ws, dW, count, count, splits);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("split reduction launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
+    return NTP_OK;
+}
+
+template <class T> constexpr int DTYPE = sizeof(T) == 2 ? NTP_BF16 : NTP_F32;
+
 template <class T>
 int nn_fwd_t(const void* A, const void* W, void* H, int64_t n, int64_t k, int64_t m, int act, hipStream_t st) {
+    if (use_split_core()) return launch_nn_strip(A, nullptr, W, H, n, k, m, k, m, m, false, act == NTP_ACT_RELU, DTYPE<T>, st);
     GemmArgs g{};
     g.A = A; g.B = W; g.C = H;
     g.lda = k; g.ldb = m; g.ldc = m;
@@ -795,6 +390,9 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
     int rc;
     if (dA && n > 0) {
         // dA[n x k] = dZ[n x m] * W^T : contraction over m; W is read as (kk=m, j=k) = W[j*m + kk]
+        if (use_split_core()) {
+            rc = launch_nn_strip(dH, relu ? H : nullptr, W, dA, n, m, k, m, m, k, true, false, DTYPE<T>, st);
+        } else {
         GemmArgs g{};
         g.A = dH; g.maskA = H; g.B = W; g.C = dA;
         g.lda = m; g.ldb = m; g.ldc = k;
@@ -802,10 +400,16 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
         g.k_per_split = (m + BK - 1) / BK * BK;
         rc = relu ? launch_gemm<T, T, T, true, true, true, false>(g, 1, st)
                   : launch_gemm<T, T, T, true, true, false, false>(g, 1, st);
+        }
         if (rc != NTP_OK) return rc;
     }
     if (!dW) return NTP_OK;
     // dW[k x m] = A^T[k x n] * dZ[n x m] : contraction over the vertices, split over blocks
+    if (use_split_core() && nn_dw_direct(n, k, m)) {
+        const int splits = nn_dw_direct_splits(n, k, m);
+        rc = launch_nn_dw_direct(A, dH, relu ? H : nullptr, splits > 1 ? (float*)ws : dW, n, k, m, DTYPE<T>, st);
+        return rc != NTP_OK ? rc : sum_splits(ws, dW, k * m, splits, st);
+    }
     const int S = dw_splits(n, k, m);
     GemmArgs g{};
     g.A = A; g.B = dH; g.maskB = H;
@@ -818,20 +422,14 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
     rc = relu ? launch_gemm<T, T, float, false, false, false, true>(g, S, st)
               : launch_gemm<T, T, float, false, false, false, false>(g, S, st);
     if (rc != NTP_OK) return rc;
-    if (S > 1) {
-        const int64_t count = k * m;
-        hipLaunchKernelGGL(sum_splits_kernel, dim3((unsigned)((count + 63) / 64)), dim3(256), 0, st,
-                           (const float*)ws, dW, count, count, S);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) { set_error("split reduction launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
-    }
-    return NTP_OK;
+    return sum_splits(ws, dW, k * m, S, st);
 }
 
 }  // namespace
 
 int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m) {
-    const int S = dw_splits(n, k, m);
+    int S = dw_splits(n, k, m);
+    if (nn_dw_direct(n, k, m)) S = std::max(S, nn_dw_direct_splits(n, k, m));
     return S > 1 ? (int64_t)S * k * m * 4 : 0;
 }
 

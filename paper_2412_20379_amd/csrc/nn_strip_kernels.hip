@@ -1,0 +1,594 @@
+// Dense transform with the small operand resident in LDS: C[n x N] = act(A[n x K] B[K x N]) for tall A
+// (H = act(A W), and dA = dZ W^T with the ReLU mask applied to dZ on its way in).
+//
+// B is small (the K x N of a layer), A is long.  A block of NW wavefronts cuts a column panel of B into bf16 pieces
+// ONCE, in the order the matrix instruction wants them, and keeps it in LDS; then every wavefront walks 32-row
+// units of its own without a barrier: 128 bytes of each row at a time come from memory as whole lines, take the operand
+// layout in 4 KB of LDS that belong to the wavefront alone, are cut into pieces in registers and
+// multiplied with the panel, 32 * TN columns at a time; the next two steps are in flight meanwhile.  Nobody waits for
+// another wavefront, so the cutting, loads and stores of one run under the matrix instructions of the others.
+// The blocks that work on the same rows (the panels of a row group) have ids that differ by 8, hence sit on one XCD, and
+// all but the first reader find the rows in its L2 (692 MB of re-reads at 17 TB/s measured alone).
+//
+// Bound.  Narrow outputs: memory (256 -> 40 on 169,343 rows: 200 MB in 0.040 ms = 5.0 TB/s, the rate of a large
+// copy).  256 -> 256: the matrix pipe at the clock that power allows (alone 0.067 ms at 2.3 GHz; together with
+// the cutting and LDS reads the chip drops to 1.8-2.0 GHz and 0.091 ms) plus 0.35 GB of traffic that
+// overlaps it only in part.  Against the 128 x 128 tiles of both operands cut through LDS behind barriers that this replaces
+// (169,343 rows, fp32): 256 -> 256 0.158 -> 0.136 ms, 128 -> 256 0.086 -> 0.077, 256 -> 40 0.048 -> 0.040, dA 40 -> 256 0.070
+// -> 0.046 (masked 0.080 -> 0.050), dA 256 -> 256 masked 0.183 -> 0.163; 602 -> 128 on 58,241 rows 0.086 -> 0.063 (bf16 0.112
+// -> 0.034); bf16 256 -> 256 0.080 -> 0.062, its dA 0.061 -> 0.045 (masked 0.090 -> 0.061).
+// Reading A in operand layout straight from memory (a lane = a row) instead of through LDS costs 32 line look-ups per
+// instruction instead of 8: 256 -> 256 0.200 ms.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "nn_util.h"
+#include "ntp_internal.h"
+
+namespace ntp {
+
+namespace {
+
+// a vector of VB bytes (16, or one element) as dwords; element alignment is enough (global loads of any width are
+// allowed from any dword or half-word address)
+template <int VB, class P>
+__device__ __forceinline__ void load_words(const P* p, unsigned (&w)[VB >= 4 ? VB / 4 : 1]) {
+    if constexpr (VB == 16) {
+        uint4 t;
+        __builtin_memcpy(&t, p, 16);
+        w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
+    }
+    else if constexpr (VB == 4) { w[0] = *reinterpret_cast<const unsigned*>(p); }
+    else { w[0] = *reinterpret_cast<const unsigned short*>(p); }
+}
+template <int VB>
+__device__ __forceinline__ void store_words(char* p, const unsigned (&w)[VB >= 4 ? VB / 4 : 1]) {
+    if constexpr (VB == 16) *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    else if constexpr (VB == 4) *reinterpret_cast<unsigned*>(p) = w[0];
+    else *reinterpret_cast<unsigned short*>(p) = (unsigned short)w[0];
+}
+// keep an element where the mask element is > 0
+template <class T, int VB>
+__device__ __forceinline__ void mask_words(unsigned (&w)[VB >= 4 ? VB / 4 : 1], const unsigned (&m)[VB >= 4 ? VB / 4 : 1]) {
+#pragma unroll
+    for (int i = 0; i < (VB >= 4 ? VB / 4 : 1); ++i) {
+        if constexpr (sizeof(T) == 4) w[i] = __uint_as_float(m[i]) > 0.f ? w[i] : 0u;
+        else {
+            const unsigned lo = __uint_as_float(m[i] << 16) > 0.f ? 0xffffu : 0u;
+            const unsigned hi = __uint_as_float(m[i] & 0xffff0000u) > 0.f ? 0xffff0000u : 0u;
+            w[i] &= lo | hi;
+        }
+    }
+}
+
+// drop the first `over` elements of the vector (all of them if there are no more), zeros come in at the end
+template <class T, int VB>
+__device__ __forceinline__ void shift_words(unsigned (&w)[VB >= 4 ? VB / 4 : 1], int over) {
+    if constexpr (VB < 16) {
+        w[0] = over > 0 ? 0u : w[0];
+    } else {
+        if constexpr (sizeof(T) == 2) {            // one half word, then whole dwords
+            const bool odd = over > 0 && (over & 1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = odd ? (w[i] >> 16) | (i < 3 ? w[i < 3 ? i + 1 : 3] << 16 : 0u) : w[i];
+            over = over > 0 ? over >> 1 : over;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool more = over > k;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = more ? (i < 3 ? w[i < 3 ? i + 1 : 3] : 0u) : w[i];
+        }
+    }
+}
+
+// TN consecutive results of a row as one vector of bf16
+template <int TN, class T>
+__device__ __forceinline__ void store_bf16(T* p, const float (&v)[TN], bool nt) {
+    if constexpr (TN > 1) {
+        typedef unsigned V __attribute__((ext_vector_type(TN / 2)));
+        V t;
+#pragma unroll
+        for (int j = 0; j < TN / 2; ++j) t[j] = f32_to_bf16_bits(v[2 * j]) | (f32_to_bf16_bits(v[2 * j + 1]) << 16);
+        if (nt) __builtin_nontemporal_store(t, reinterpret_cast<V*>(p));
+        else *reinterpret_cast<V*>(p) = t;
+    } else {
+        store_elem(p, v[0]);
+    }
+}
+// written once, not read again by the kernel: past the L2
+__device__ __forceinline__ void stream_elem(float* p, float v) { __builtin_nontemporal_store(v, p); }
+__device__ __forceinline__ void stream_elem(unsigned short* p, float v) { __builtin_nontemporal_store((unsigned short)f32_to_bf16_bits(v), p); }
+
+constexpr int LDS_BYTES = 160 * 1024;
+constexpr int64_t CACHE_BYTES = 256ll << 20;     // Infinity Cache
+constexpr int STEP_BYTES = 128;        // bytes of a row in one contraction step: a cache line
+
+struct StripArgs {
+    const void* A;
+    const void* mask;      // like A (nullable): an element of A is used only where its mask element is > 0
+    const void* B;
+    void* C;
+    int64_t n, lda, ldb, ldc;
+    int K, N;
+    int b_kcontig;         // B[kk][col] at B[col * ldb + kk] (else at B[kk * ldb + col])
+    int relu;
+    int interleave;        // lane l of block j of a column group holds column TN * l + j (else 32 * j + l): a lane's TN results are one store
+    int nt;                // C is stored past the caches: its rows are whole cache lines and the Infinity Cache would not hold it
+                           // for its reader anyway (a smaller C is found there by the aggregation that follows: measured 4 % of its time)
+    int panels, panel_groups;      // column panels, groups of 32 * TN columns in each
+    int row_groups;                // blocks per panel
+    int steps, phase_steps;        // contraction steps of 32; steps per phase
+};
+
+// A on its way from memory to a matrix operand.  One step = STEP_BYTES of each of a unit's 32 rows, read
+// as whole lines: lane l takes vector l % (128 / VB) of rows l / (128 / VB) + j * (VB / 2).  The operand layout (lane =
+// row) is made in 4 KB of LDS that belong to one wavefront alone: 16-byte segment s of row r sits at
+// r * 128 + (s ^ (r % 8)) * 16, so neither the line-wise writes nor the row-wise reads meet bank conflicts.
+template <class T, bool MASK, int VB>
+struct RowStage {
+    static constexpr int KS = STEP_BYTES / (int)sizeof(T);      // contraction indices of a step
+    static constexpr int LPR = 128 / VB, NI = 64 / VB, E = VB / (int)sizeof(T), WV = VB >= 4 ? VB / 4 : 1;
+    struct Raw { unsigned a[NI][WV]; unsigned m[MASK ? NI : 1][WV]; };
+    // step s of unit u on its way
+    static __device__ __forceinline__ void issue(const StripArgs& g, Raw& x, int u, int s, int lane) {
+        const int64_t first = (int64_t)u * 32;
+        const T* A = static_cast<const T*>(g.A) + first * g.lda + s * KS;
+        const T* mA = static_cast<const T*>(g.mask) + (MASK ? first * g.lda + s * KS : 0);
+        const int lim = (int)min(g.n - 1 - first, (int64_t)31);
+        const int vec = lane % LPR, row0 = lane / LPR;
+        // a vector that crosses the end of the row is read E elements before that end (stage shifts it), one beyond it anywhere
+        const int col = min(s * KS + vec * E, g.K - E) - s * KS;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int off = min(row0 + j * (VB / 2), lim) * (int)g.lda + col;
+            load_words<VB>(A + off, x.a[j]);
+            if constexpr (MASK) load_words<VB>(mA + off, x.m[j]);
+        }
+    }
+    // into LDS; elements beyond the row become zero
+    static __device__ __forceinline__ void stage(const StripArgs& g, Raw& x, int s, char* own, int lane) {
+        const int vec = lane % LPR, row0 = lane / LPR;
+        const bool tail = (s + 1) * KS > g.K;
+        const int over = s * KS + vec * E + E - g.K;           // elements of this lane's vector beyond the row
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            const int row = row0 + j * (VB / 2);
+            if constexpr (MASK) mask_words<T, VB>(x.a[j], x.m[j]);
+            if (tail) shift_words<T, VB>(x.a[j], over);
+            const int byte = vec * VB;
+            store_words<VB>(own + row * 128 + (((byte / 16) ^ (row & 7)) * 16 + byte % 16), x.a[j]);
+        }
+    }
+    // the pieces of this lane's eight elements of matrix step c
+    static __device__ __forceinline__ void read(const char* own, int c, int lane, uint4 (&piece)[Pieces<T>::n]) {
+        constexpr int SEGS = (int)sizeof(T) / 2;           // 16-byte segments of eight elements
+        const int r = lane & 31, h = lane >> 5;
+        unsigned w[Row8<T>::words];
+#pragma unroll
+        for (int q = 0; q < SEGS; ++q) {
+            const uint4 t = *reinterpret_cast<const uint4*>(own + r * 128 + ((((2 * c + h) * SEGS + q) ^ (r & 7)) * 16));
+            w[4 * q] = t.x; w[4 * q + 1] = t.y; w[4 * q + 2] = t.z; w[4 * q + 3] = t.w;
+        }
+        cut_row8<T>(w, piece);
+    }
+};
+
+// the pieces of elements k .. k+7 of column col of B, zero outside the matrix
+template <class T>
+__device__ __forceinline__ void read_b(const StripArgs& g, int k, int col, uint4 (&piece)[Pieces<T>::n]) {
+    const int64_t sk = g.b_kcontig ? 1 : g.ldb, sc = g.b_kcontig ? g.ldb : 1;
+    const T* src = static_cast<const T*>(g.B) + (int64_t)min(col, g.N - 1) * sc;
+    unsigned w[Row8<T>::words];
+    if (g.b_kcontig && k + 8 <= g.K) {
+        __builtin_memcpy(w, src + k, sizeof w);
+        if (col >= g.N) zero_row8_from<T>(w, 0);
+        cut_row8<T>(w, piece);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const T x = src[(int64_t)min(k + e, g.K - 1) * sk];
+        if constexpr (sizeof(T) == 4) w[e] = __float_as_uint(x);
+        else { if (e % 2 == 0) w[e / 2] = x; else w[e / 2] |= (unsigned)x << 16; }
+    }
+    zero_row8_from<T>(w, col < g.N ? g.K - k : 0);
+    cut_row8<T>(w, piece);
+}
+
+// the steps [s0, s0 + phase_steps) of a column panel into LDS as matrix operands
+template <class T, int TN, int NW>
+__device__ __forceinline__ void fill_panel(const StripArgs& g, uint4* lds, int col0, int n_groups, int s0) {
+    constexpr int NP = Pieces<T>::n, KS = STEP_BYTES / (int)sizeof(T), CH = KS / 16;
+    const int group_frags = CH * g.phase_steps * TN * NP * 64;
+    const int chunks = CH * min(g.phase_steps, g.steps - s0);
+    const int total = n_groups * chunks * TN * 64;
+    for (int idx = threadIdx.x; idx < total; idx += 64 * NW) {
+        const int l = idx & 63, j = (idx >> 6) % TN, t = (idx >> 6) / TN, c = t % chunks, gr = t / chunks;
+        const int col = col0 + gr * (32 * TN) + (g.interleave ? (l & 31) * TN + j : j * 32 + (l & 31));
+        uint4 piece[NP];
+        read_b<T>(g, s0 * KS + c * 16 + (l >> 5) * 8, col, piece);
+        uint4* d = lds + gr * group_frags + ((c * TN + j) * NP) * 64 + l;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) d[p * 64] = piece[p];
+    }
+}
+
+// a unit's 32 rows x 32 * TN columns from column cb on: element e of a 32x32 accumulator sits at row
+// 8*(e/4) + 4*(lane/32) + e%4, column lane%32
+template <class T, int TN>
+__device__ __forceinline__ void store_unit(const StripArgs& g, const f32x16 (&acc)[1][TN], int u, int cb, int lane) {
+    const int r = lane & 31, h = lane >> 5, N = g.N;
+                const bool relu = g.relu != 0;
+                const int64_t rbase = (int64_t)u * 32 + 4 * h;
+                const int64_t left64 = g.n - rbase;
+                const int rows_left = left64 > 32 ? 32 : (int)left64;
+                            const bool whole = (int64_t)(u + 1) * 32 <= g.n && cb + 32 * TN <= N;      // no tests needed
+                if (sizeof(T) == 2 && g.interleave) {
+                    T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + r * TN;
+                    const bool in = cb + r * TN < N;          // N is a multiple of TN
+    #pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        float v[TN];
+    #pragma unroll
+                        for (int j = 0; j < TN; ++j) v[j] = relu ? (acc[0][j][e] > 0.f ? acc[0][j][e] : 0.f) : acc[0][j][e];
+                        if (whole || (in && 8 * (e / 4) + (e % 4) < rows_left)) store_bf16<TN>(p, v, g.nt != 0);
+                        p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+                    }
+                } else if (whole && g.nt) {
+    #pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + j * 32 + r;
+    #pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const float v = acc[0][j][e];
+                            stream_elem(p, relu ? (v > 0.f ? v : 0.f) : v);
+                            p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+                        }
+                    }
+                } else {
+    #pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + j * 32 + r;
+                        const int lim = cb + j * 32 + r < N ? rows_left : 0;
+    #pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const float v = acc[0][j][e];
+                            if (8 * (e / 4) + (e % 4) < lim) store_elem(p, relu ? (v > 0.f ? v : 0.f) : v);
+                            p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+                        }
+                    }
+                }
+}
+
+// PHASED: the panel (one column group) does not fit in LDS; its contraction steps come in phases of
+// g.phase_steps (even).
+template <class T, bool MASK, int VB, int TN, int NW, bool PHASED>
+__global__ void __launch_bounds__(64 * NW, NW / 4) strip_kernel(const StripArgs g) {
+    constexpr int NP = Pieces<T>::n;
+    constexpr int KS = STEP_BYTES / (int)sizeof(T), CH = KS / 16;       // contraction indices and matrix steps of a step
+    extern __shared__ uint4 lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int id = (int)blockIdx.x;
+    const int panel = (id / 8) % g.panels, rg = (id / 8) / g.panels * 8 + id % 8;
+    if (rg >= g.row_groups) return;
+    const int K = g.K, N = g.N, steps = g.steps;
+    const int group_frags = CH * g.phase_steps * TN * NP * 64;        // 16-byte fragments of one column group
+    const int col0 = panel * g.panel_groups * (32 * TN);
+    const int n_groups = PHASED ? 1 : min(g.panel_groups, (N - col0 + 32 * TN - 1) / (32 * TN));
+
+    // this wavefront's units of 32 rows
+    const int units = (int)((g.n + 31) / 32);
+    const int n_waves = g.row_groups * NW, wv = rg * NW + wave;
+    const int u_begin = (int)((int64_t)units * wv / n_waves), u_end = (int)((int64_t)units * (wv + 1) / n_waves);
+
+    using Rows = RowStage<T, MASK, VB>;
+    typename Rows::Raw x0, x1;
+    char* const own = reinterpret_cast<char*>(lds + g.panel_groups * group_frags) + wave * 4096;
+
+    f32x16 acc[1][TN];
+    // multiply the step held in x (its panel part starts at b0) and refill x with step ns of unit nu
+    auto step = [&](typename Rows::Raw& x, const uint4* b0, int s, int nu, int ns) {
+        Rows::stage(g, x, s, own, lane);
+        Rows::issue(g, x, nu, ns, lane);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (c > 0 && s * KS + 16 * c >= K) break;
+            uint4 a[1][NP], b[TN][NP];
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) b[j][p] = b0[((c * TN + j) * NP + p) * 64];
+            Rows::read(own, c, lane, a[0]);
+            mfma_pieces<1, TN, NP, NP>(a, b, acc);
+        }
+    };
+
+    Rows::issue(g, x0, min(u_begin, units - 1), 0, lane);
+    Rows::issue(g, x1, min(u_begin, units - 1), min(1, steps - 1), lane);
+    if constexpr (!PHASED) {
+        fill_panel<T, TN, NW>(g, lds, col0, n_groups, 0);
+        __syncthreads();
+    }
+    // PHASED: every wavefront of the block makes the same number of sweeps (barriers inside)
+    const int n_items = PHASED ? (units + n_waves - 1) / n_waves : (u_end - u_begin) * n_groups;
+    int u = u_begin, gr = 0;
+    for (int item = 0; item < n_items; ++item) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[0][j][e] = 0.f;
+        const bool next_rows = PHASED || gr + 1 == n_groups;
+        const int cu = min(u, units - 1), nu = min(next_rows ? u + 1 : u, units - 1);
+        const uint4* b0 = lds + gr * group_frags + lane;
+        for (int s = 0; s < steps; s += 2) {
+            if constexpr (PHASED) {
+                if (s % g.phase_steps == 0) {
+                    __syncthreads();
+                    fill_panel<T, TN, NW>(g, lds, col0, 1, s);
+                    __syncthreads();
+                    b0 = lds + lane;
+                }
+            }
+            const bool more0 = s + 2 < steps, more1 = s + 3 < steps;
+            step(x0, b0, s, more0 ? cu : nu, more0 ? s + 2 : 0);
+            if (s + 1 < steps) step(x1, b0 + CH * TN * NP * 64, s + 1, more1 ? cu : nu, more1 ? s + 3 : 1);
+            b0 += 2 * CH * TN * NP * 64;
+        }
+        if (!PHASED || u < u_end) store_unit<T, TN>(g, acc, u, col0 + gr * (32 * TN), lane);
+        if (next_rows) { ++u; gr = 0; }
+        else ++gr;
+    }
+}
+
+// Short contraction (at most two steps): the pieces of a unit's rows stay in registers while the unit is multiplied
+// with every column group of the panel, so A is read and cut once instead of once per group.
+template <class T, bool MASK, int VB, int TN, int NW>
+__global__ void __launch_bounds__(64 * NW, NW / 4) strip_short_kernel(const StripArgs g) {
+    constexpr int NP = Pieces<T>::n;
+    using Rows = RowStage<T, MASK, VB>;
+    constexpr int CH = Rows::KS / 16;
+    extern __shared__ uint4 lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int id = (int)blockIdx.x;
+    const int panel = (id / 8) % g.panels, rg = (id / 8) / g.panels * 8 + id % 8;
+    if (rg >= g.row_groups) return;
+    const int group_frags = CH * g.steps * TN * NP * 64;
+    const int col0 = panel * g.panel_groups * (32 * TN);
+    const int n_groups = min(g.panel_groups, (g.N - col0 + 32 * TN - 1) / (32 * TN));
+    const int units = (int)((g.n + 31) / 32);
+    const int n_waves = g.row_groups * NW, wv = rg * NW + wave;
+    const int u_begin = (int)((int64_t)units * wv / n_waves), u_end = (int)((int64_t)units * (wv + 1) / n_waves);
+    char* const own = reinterpret_cast<char*>(lds + g.panel_groups * group_frags) + wave * 4096;
+    const bool two = g.steps > 1;
+    typename Rows::Raw x0, x1;
+    Rows::issue(g, x0, min(u_begin, units - 1), 0, lane);
+    if (two) Rows::issue(g, x1, min(u_begin, units - 1), 1, lane);
+    fill_panel<T, TN, NW>(g, lds, col0, n_groups, 0);
+    __syncthreads();
+    for (int u = u_begin; u < u_end; ++u) {
+        uint4 a[2 * CH][1][NP];
+        Rows::stage(g, x0, 0, own, lane);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) Rows::read(own, c, lane, a[c][0]);
+        if (two) {
+            Rows::stage(g, x1, 1, own, lane);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) Rows::read(own, c, lane, a[CH + c][0]);
+        }
+        if (u + 1 < u_end) {
+            Rows::issue(g, x0, u + 1, 0, lane);
+            if (two) Rows::issue(g, x1, u + 1, 1, lane);
+        }
+        for (int gr = 0; gr < n_groups; ++gr) {
+            f32x16 acc[1][TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[0][j][e] = 0.f;
+            const uint4* b0 = lds + gr * group_frags + lane;
+#pragma unroll
+            for (int c = 0; c < 2 * CH; ++c) {
+                if (c > 0 && c * 16 >= g.K) break;
+                uint4 b[TN][NP];
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) b[j][p] = b0[((c * TN + j) * NP + p) * 64];
+                mfma_pieces<1, TN, NP, NP>(a[c], b, acc);
+            }
+            store_unit<T, TN>(g, acc, u, col0 + gr * (32 * TN), lane);
+        }
+    }
+}
+
+// Few rows: the eight wavefronts of a block share one unit of 32 rows and one column group of 32, wavefront w
+// taking steps w, w + 8, ... of the contraction; B comes straight from memory.  The eight sums are
+// added through LDS in a fixed order.
+template <class T, bool MASK, int VB>
+__global__ void __launch_bounds__(512) strip_split_kernel(const StripArgs g) {
+    constexpr int NP = Pieces<T>::n;
+    using Rows = RowStage<T, MASK, VB>;
+    constexpr int KS = Rows::KS;
+    __shared__ uint4 lds[8 * 256];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane & 31, h = lane >> 5;
+    const int groups = (g.N + 31) / 32, gr = (int)blockIdx.x % groups, u = (int)blockIdx.x / groups;
+    char* const own = reinterpret_cast<char*>(lds) + wave * 4096;
+    f32x16 acc[1][1];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
+    typename Rows::Raw x;
+    if (wave < g.steps) Rows::issue(g, x, u, wave, lane);
+    for (int s = wave; s < g.steps; s += 8) {
+        Rows::stage(g, x, s, own, lane);
+        if (s + 8 < g.steps) Rows::issue(g, x, u, s + 8, lane);
+#pragma unroll
+        for (int c = 0; c < KS / 16; ++c) {
+            uint4 a[1][NP], b[1][NP];
+            read_b<T>(g, s * KS + 16 * c + 8 * h, gr * 32 + r, b[0]);
+            Rows::read(own, c, lane, a[0]);
+            mfma_pieces<1, 1, NP, NP>(a, b, acc);
+        }
+    }
+    // the sums of the wavefronts: element e of lane l at own[e * 64 + l]
+    float* mine = reinterpret_cast<float*>(own);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mine[e * 64 + lane] = acc[0][0][e];
+    __syncthreads();
+    const float* all = reinterpret_cast<const float*>(lds);
+    for (int i = threadIdx.x; i < 1024; i += 512) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) v += all[w * 1024 + i];
+        const int e = i >> 6, l = i & 63;
+        const int64_t row = (int64_t)u * 32 + 8 * (e / 4) + 4 * (l >> 5) + e % 4;
+        const int col = gr * 32 + (l & 31);
+        if (g.relu) v = v > 0.f ? v : 0.f;
+        if (row < g.n && col < g.N) store_elem(static_cast<T*>(g.C) + row * g.ldc + col, v);
+    }
+}
+
+// How a shape (TN, NW) would cut the work, and its cost in units of (rounds of a wavefront) x (wavefronts of a compute
+// unit) x (column blocks + 1 for the cutting of A); a panel in phases costs its barriers on top (measured 1.3x)
+struct StripPlan { int steps, phase_steps, panels, panel_groups, row_groups; double cost; };
+
+template <class T, int TN, int NW>
+StripPlan strip_plan(int64_t n, int K, int N, bool short_k = false) {
+    constexpr int CUS = 256;
+    constexpr int KS = STEP_BYTES / (int)sizeof(T);
+    constexpr int step_bytes = KS / 16 * TN * Pieces<T>::n * 1024;
+    constexpr int max_steps = (LDS_BYTES - NW * 4096) / step_bytes;
+    static_assert(max_steps >= 2, "the panel's steps come in pairs");
+    StripPlan p;
+    p.steps = (K + KS - 1) / KS;
+    const int groups = (N + 32 * TN - 1) / (32 * TN);
+    const int64_t units = (n + 31) / 32;
+    int most = 1;                                   // column groups that fit in LDS together
+    const bool phased = p.steps > max_steps;
+    if (!phased) { p.phase_steps = p.steps; most = max_steps / p.steps; }
+    else { const int phases = (p.steps + max_steps - 1) / max_steps; p.phase_steps = std::min(max_steps / 2, ((p.steps + phases - 1) / phases + 1) / 2) * 2; }
+    p.panels = (groups + most - 1) / most;
+    const int64_t rg_all = (units + NW - 1) / NW;        // row groups with one unit per wavefront
+    if (rg_all * p.panels < CUS) p.panels = (int)std::max<int64_t>(p.panels, std::min<int64_t>(groups, CUS / rg_all));      // few rows: spread the columns
+    p.panel_groups = (groups + p.panels - 1) / p.panels;
+    p.panels = (groups + p.panel_groups - 1) / p.panel_groups;
+    const int64_t rg_fit = std::max(1, CUS / 8 / p.panels) * 8;
+    p.row_groups = (int)std::min(rg_all, rg_fit);
+    const int64_t waves = (int64_t)p.row_groups * NW;
+    const int64_t rounds = (units + waves - 1) / waves * std::max<int64_t>(1, (int64_t)p.panels * 8 / CUS);
+    p.cost = (double)rounds * NW * (short_k ? p.panel_groups * TN + 1 : p.panel_groups * (TN + 1)) * (phased ? 1.3 : 1.0);
+    return p;
+}
+
+// with more LDS than a kernel may use without asking
+template <auto kernel>
+void launch_lds(int64_t blocks, int threads, int lds, const StripArgs& g, hipStream_t st) {
+    static bool allowed[64] = {};          // one table per kernel
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev >= 0 && dev < 64 && !allowed[dev])
+        allowed[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) == hipSuccess;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)threads), lds, st, g);
+}
+
+template <class T, bool MASK, int VB, int TN, int NW, bool SHORT = false>
+int launch_strip(StripArgs g, const StripPlan& p, hipStream_t st) {
+    constexpr int KS = STEP_BYTES / (int)sizeof(T);
+    g.steps = p.steps; g.phase_steps = p.phase_steps; g.panels = p.panels; g.panel_groups = p.panel_groups; g.row_groups = p.row_groups;
+    g.interleave = sizeof(T) == 2 && g.ldc % TN == 0 && g.N % TN == 0 && (uintptr_t)g.C % (TN * sizeof(T)) == 0;
+    g.nt = g.ldc * sizeof(T) % 128 == 0 && (uintptr_t)g.C % 128 == 0 && g.n * g.ldc * (int64_t)sizeof(T) > CACHE_BYTES;
+    const int lds = g.panel_groups * g.phase_steps * (KS / 16 * TN * Pieces<T>::n * 1024) + NW * 4096;
+    const int64_t blocks = (int64_t)(g.row_groups + 7) / 8 * 8 * g.panels;
+    if constexpr (SHORT) {
+        launch_lds<strip_short_kernel<T, MASK, VB, TN, NW>>(blocks, 64 * NW, lds, g, st);
+    } else if (g.phase_steps >= g.steps) {
+        launch_lds<strip_kernel<T, MASK, VB, TN, NW, false>>(blocks, 64 * NW, lds, g, st);
+    } else {
+        if constexpr (NW == 8 && (TN == 2 || TN == 4)) launch_lds<strip_kernel<T, MASK, VB, TN, NW, true>>(blocks, 64 * NW, lds, g, st);
+        else return NTP_EUNSUPPORTED;
+    }
+    return NTP_OK;
+}
+
+template <class T, bool MASK, int VB>
+int launch_shape(StripArgs g, hipStream_t st) {
+    constexpr int KS = STEP_BYTES / (int)sizeof(T);
+    const int64_t split_blocks = (g.n + 31) / 32 * ((g.N + 31) / 32);
+    g.steps = (g.K + KS - 1) / KS;
+    if (VB < 16 || g.steps <= 2) {         // rows of less than 16 bytes are one step
+        const StripPlan p1 = strip_plan<T, 1, 8>(g.n, g.K, g.N, true), p2 = strip_plan<T, 2, 8>(g.n, g.K, g.N, true);
+        if (g.N <= 32) return launch_strip<T, MASK, VB, 1, 8, true>(g, p1, st);
+        if constexpr (VB == 16) {
+            const StripPlan p4 = strip_plan<T, 4, 8>(g.n, g.K, g.N, true);
+            if constexpr (!MASK) {
+                const StripPlan p3 = strip_plan<T, 2, 12>(g.n, g.K, g.N, true);
+                if (p3.cost < std::min(p2.cost, p4.cost)) return launch_strip<T, MASK, VB, 2, 12, true>(g, p3, st);
+            }
+            if (p4.cost < p2.cost) return launch_strip<T, MASK, VB, 4, 8, true>(g, p4, st);
+        }
+        return launch_strip<T, MASK, VB, 2, 8, true>(g, p2, st);
+    }
+    if constexpr (VB == 16) {
+        if (split_blocks <= 512 && g.steps >= 4) {
+            hipLaunchKernelGGL((strip_split_kernel<T, MASK, VB>), dim3((unsigned)split_blocks), dim3(512), 0, st, g);
+            return NTP_OK;
+        }
+        // the cheapest shape; a phased panel is built for NW = 8 and TN = 2, 4 only
+        constexpr bool F32 = sizeof(T) == 4;
+        constexpr bool W4 = F32 && !MASK;          // with a mask in flight as well its registers spill
+        int best = 0;
+        double least = 1e300;
+        StripPlan plan{};
+        auto consider = [&](int id, const StripPlan& p, bool can_phase) {
+            if (p.phase_steps < p.steps && !can_phase) return;
+            if (p.cost < least) { least = p.cost; best = id; plan = p; }
+        };
+        if (g.N <= 32) consider(1, strip_plan<T, 1, 8>(g.n, g.K, g.N), false);
+        if constexpr (W4) consider(5, strip_plan<T, 4, 12>(g.n, g.K, g.N), false);
+        if constexpr (F32) consider(3, strip_plan<T, 2, 12>(g.n, g.K, g.N), false);
+        consider(4, strip_plan<T, 4, 8>(g.n, g.K, g.N), true);
+        consider(2, strip_plan<T, 2, 8>(g.n, g.K, g.N), true);
+        if constexpr (!F32) consider(6, strip_plan<T, 8, 8>(g.n, g.K, g.N), false);
+        switch (best) {
+            case 1: return launch_strip<T, MASK, VB, 1, 8>(g, plan, st);
+            case 2: return launch_strip<T, MASK, VB, 2, 8>(g, plan, st);
+            case 4: return launch_strip<T, MASK, VB, 4, 8>(g, plan, st);
+            case 3: if constexpr (F32) return launch_strip<T, MASK, VB, 2, 12>(g, plan, st); break;
+            case 5: if constexpr (W4) return launch_strip<T, MASK, VB, 4, 12>(g, plan, st); break;
+            case 6: if constexpr (!F32) return launch_strip<T, MASK, VB, 8, 8>(g, plan, st); break;
+        }
+    }
+    return NTP_EUNSUPPORTED;
+}
+
+template <class T>
+int launch_any(const StripArgs& g, hipStream_t st) {
+    constexpr int ELEM = (int)sizeof(T);
+    if (g.K * ELEM >= 16) return g.mask ? launch_shape<T, true, 16>(g, st) : launch_shape<T, false, 16>(g, st);
+    return g.mask ? launch_shape<T, true, ELEM>(g, st) : launch_shape<T, false, ELEM>(g, st);
+}
+
+}  // namespace
+
+// C[n x N] = act(A' B), A' = A [n x K] (kept where mask > 0), B[kk][col] at B[kk * ldb + col], or with b_kcontig at
+// B[col * ldb + kk]; n, K, N >= 1.
+int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int64_t n, int64_t K, int64_t N, int64_t lda,
+                    int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, void* stream) {
+    StripArgs g{};
+    g.A = A; g.mask = mask; g.B = B; g.C = C;
+    g.n = n; g.K = (int)K; g.N = (int)N;
+    g.lda = lda; g.ldb = ldb; g.ldc = ldc;
+    g.b_kcontig = b_kcontig; g.relu = relu;
+    const int rc = dtype == NTP_BF16 ? launch_any<unsigned short>(g, (hipStream_t)stream) : launch_any<float>(g, (hipStream_t)stream);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("transform kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
+    if (rc != NTP_OK) set_error("no transform kernel for this shape");
+    return rc;
+}
+
+}  // namespace ntp

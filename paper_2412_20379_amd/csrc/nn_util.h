@@ -1,0 +1,99 @@
+// Pieces shared by the dense transform kernels: fp32 operands cut into bf16 pieces, element
+// access for fp32 / bf16 buffers.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+namespace ntp {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// pieces an element of type T is cut into for the bf16 matrix instructions
+template <class T> struct Pieces { static constexpr int n = 3; };
+template <> struct Pieces<unsigned short> { static constexpr int n = 1; };
+
+// x = sum of NP bf16 values, each returned as an fp32 bit pattern whose low half is zero
+// (NP = 1: x is a bf16 value already)
+template <int NP>
+__device__ __forceinline__ void split_bf16(float x, unsigned (&piece)[NP]) {
+    if constexpr (NP == 1) {
+        piece[0] = __float_as_uint(x);
+    } else {
+        const unsigned hi = __float_as_uint(x) & 0xffff0000u;
+        const float r1 = x - __uint_as_float(hi);                 // exact: at most 16 significant bits left
+        const unsigned mid = __float_as_uint(r1) & 0xffff0000u;
+        const float r2 = r1 - __uint_as_float(mid);               // exact: at most 8 significant bits left
+        piece[0] = hi; piece[1] = mid; piece[2] = __float_as_uint(r2);
+    }
+}
+// bf16 pair in one dword: low half = piece of the even contraction index, high half = odd
+__device__ __forceinline__ unsigned pack_pair(unsigned even, unsigned odd) {
+    return __builtin_amdgcn_perm(odd, even, 0x07060302u);
+}
+
+__device__ __forceinline__ float elem_to_f32(float v) { return v; }
+__device__ __forceinline__ float elem_to_f32(unsigned short v) { return __uint_as_float((unsigned)v << 16); }
+
+__device__ __forceinline__ unsigned f32_to_bf16_bits(float f) {
+    unsigned u = __float_as_uint(f);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return u >> 16;
+}
+__device__ __forceinline__ void store_elem(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store_elem(unsigned short* p, float v) { *p = (unsigned short)f32_to_bf16_bits(v); }
+
+// ---- eight consecutive contraction indices of one row (or column) of an operand: what a lane of
+// v_mfma_f32_32x32x16_bf16 holds.  In memory they are 8 * sizeof(T) bytes = Row8<T>::words dwords.
+template <class T> struct Row8 { static constexpr int words = 2 * sizeof(T); };
+
+// keep the first `left` of the eight elements, zero the others
+template <class T>
+__device__ __forceinline__ void zero_row8_from(unsigned (&w)[Row8<T>::words], int left) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = e < left ? w[e] : 0u;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = 2 * e + 1 < left ? w[e] : (2 * e < left ? w[e] & 0xffffu : 0u);
+    }
+}
+// the bf16 pieces of the eight elements, each as the four dwords of a matrix operand
+template <class T>
+__device__ __forceinline__ void cut_row8(const unsigned (&w)[Row8<T>::words], uint4 (&piece)[Pieces<T>::n]) {
+    if constexpr (sizeof(T) == 2) {
+        piece[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    } else {
+        unsigned x[8][3];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) split_bf16<3>(__uint_as_float(w[e]), x[e]);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            piece[p] = make_uint4(pack_pair(x[0][p], x[1][p]), pack_pair(x[2][p], x[3][p]),
+                                  pack_pair(x[4][p], x[5][p]), pack_pair(x[6][p], x[7][p]));
+    }
+}
+
+// acc[i][j] += a[i] b[j] for TM x TN blocks of 32x32x16 from the pieces of both operands: piece
+// products of weight 2^-8w, small ones first; consecutive instructions go to different accumulators
+template <int TM, int TN, int NPA, int NPB>
+__device__ __forceinline__ void mfma_pieces(const uint4 (&a)[TM][NPA], const uint4 (&b)[TN][NPB], f32x16 (&acc)[TM][TN]) {
+#pragma unroll
+    for (int w = 2; w >= 0; --w)
+#pragma unroll
+        for (int pa = 0; pa <= w; ++pa)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int pb = w - pa;
+                    if (pa < NPA && pb < NPB)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8, a[i][pa < NPA ? pa : 0]), __builtin_bit_cast(bf16x8, b[j][pb < NPB ? pb : 0]), acc[i][j], 0, 0, 0);
+                }
+}
+
+}  // namespace ntp

@@ -1,0 +1,65 @@
+"""GPU parity of the transform kernels where their tiles, vectors and contraction phases end: rows that are no whole
+vector, single rows and columns, contractions just below and above a step and a phase, and short and long sides."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import gcn as ogcn
+import ntp_inputs as gen
+import paper_2412_20379_amd as ntp
+from helpers import assert_close, TOL_F32, TOL_BF16
+
+pytestmark = pytest.mark.gpu
+
+# (rows, contraction of the forward, columns): 32-row units, 16-byte vectors (4 fp32 or 8 bf16), 128-byte steps
+EDGES = [(1, 1, 1), (1, 4, 33), (31, 3, 31), (33, 5, 64), (32, 7, 65), (65, 8, 1), (97, 9, 127), (300, 31, 32), (257, 33, 40),
+         (17000, 33, 7), (16385, 63, 34), (20000, 65, 129), (40001, 41, 47), (17001, 127, 258), (16400, 602, 41), (5001, 289, 200),
+         (16384, 417, 64), (16385, 700, 20), (33, 1433, 47), (50001, 17, 130), (60003, 6, 70), (66000, 258, 66)]
+
+
+def _bits(a_f32):
+    import torch
+    bits = gen.to_bf16_bits(a_f32)
+    return torch.from_numpy(bits.view(np.int16)).to("cuda:0"), gen.bf16_bits_to_f32(bits)
+
+
+def _abs(A, B):
+    return np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)
+
+
+@pytest.mark.parametrize("n,k,m", EDGES)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
+def test_transform_edges(n, k, m, dtype, act):
+    import torch
+    print("nn edges", n, k, m, dtype, act, file=sys.stderr, flush=True)
+    bf16 = dtype == "bf16"
+    A = gen.normal_features(n, k, seed=n + k)
+    W = gen.glorot_weight(k, m, seed=m)
+    dH = gen.normal_features(n, m, seed=7, stream=6)
+    code, tol = (ntp.NTP_BF16, TOL_BF16) if bf16 else (ntp.NTP_F32, TOL_F32)
+    if bf16:
+        (At, A), (Wt, W), (dHt, dH) = _bits(A), _bits(W), _bits(dH)
+        empty = lambda r, c: torch.full((r, c), 0x7fc0, dtype=torch.int16, device="cuda:0")       # NaN
+        host = lambda t: gen.bf16_bits_to_f32(t.cpu().numpy().view(np.uint16))
+        rnd = lambda x: oracle.round_bf16(x).astype(np.float64)
+    else:
+        At, Wt, dHt = (torch.from_numpy(x).to("cuda:0") for x in (A, W, dH))
+        empty = lambda r, c: torch.full((r, c), float("nan"), device="cuda:0")
+        host = lambda t: t.cpu().numpy()
+        rnd = lambda x: x
+    H, dA = empty(n, m), empty(n, k)
+    dW = torch.full((k, m), float("nan"), device="cuda:0")
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws = torch.full((max(wsb // 4, 1),), float("nan"), device="cuda:0")
+    ntp.ntp_nn_fwd(At, Wt, H, n, k, m, act, code)
+    ntp.ntp_nn_bwd(At, Wt, H, dHt, dA, dW, n, k, m, act, code, ws, wsb)
+    torch.cuda.synchronize()
+    got = host(H)
+    assert_close(got, rnd(ogcn.nn_fwd(A, W, act)), _abs(A, W), tol, "H")
+    dA_ref, dW_ref = ogcn.nn_bwd(A, W, got, dH, act)          # with the H the device produced
+    dZ = dH * (got > 0) if act == ntp.NTP_ACT_RELU else dH
+    assert_close(host(dA), rnd(dA_ref), _abs(dZ, W.T), tol, "dA")
+    assert_close(dW.cpu().numpy(), dW_ref, _abs(A.T, dZ), TOL_F32 * (2 if bf16 else 1), "dW")
