@@ -24,17 +24,6 @@ namespace {
 
 __device__ __forceinline__ float lrelu(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-template <int L> __device__ __forceinline__ float group_max(float v, int lane) {
-#pragma unroll
-    for (int off = 1; off < L; off <<= 1) v = fmaxf(v, bperm_f(lane ^ off, v));
-    return v;
-}
-template <int L> __device__ __forceinline__ float group_sum(float v, int lane) {
-#pragma unroll
-    for (int off = 1; off < L; off <<= 1) v += bperm_f(lane ^ off, v);
-    return v;
-}
-
 // Per destination v the by-destination pass leaves st[v] = (q[v], row maximum, 1 / row sum, 0):
 // one 16-byte gather gives the by-source pass everything it needs about v.
 //
@@ -48,11 +37,11 @@ __device__ __forceinline__ float weight_of(float e, float mx, float rs) { return
 // than 4 L entries parks its scores in the output array after the first sweep, so the random
 // gathers of p happen once and the later sweeps read consecutive memory.
 template <int L, bool TRANSPOSED>
-__global__ void __launch_bounds__(256) attention_rows_kernel(const AttArgs a, int first, int n_rows) {
+__device__ __forceinline__ void attention_rows(const AttArgs& a, int block, int first, int n_rows) {
     constexpr int R = 64 / L;
     const int lane = threadIdx.x & 63;
     const int g = lane / L, l = lane % L;
-    const int64_t idx = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R + g;
+    const int64_t idx = ((int64_t)block * 4 + (threadIdx.x >> 6)) * R + g;
     const bool valid = idx < n_rows;
     int row = 0;
     int64_t beg = 0;
@@ -123,10 +112,9 @@ __global__ void __launch_bounds__(256) attention_rows_kernel(const AttArgs a, in
 // ---- rows beyond the split threshold: one block per segment (the pieces the aggregation
 // cuts such rows into), so that a hub row of 10^5 entries is spread over many blocks ---------
 // pass 1: scores parked in the output array; per segment maximum and sum of exp(score - maximum)
-__global__ void __launch_bounds__(256) attention_segment_stats_kernel(const AttArgs a, const Segment* segs, float2* seg_stats) {
+__device__ __forceinline__ void attention_segment_stats(const AttArgs& a, const Segment& sg, float2* seg_stats) {
     __shared__ float red[4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const Segment sg = segs[blockIdx.x];
     const int32_t* ci = a.colidx + sg.e_begin;
     float* out = a.alpha + sg.e_begin;
     const float qv = a.q[sg.row];
@@ -164,21 +152,45 @@ __global__ void __launch_bounds__(64) attention_combine_kernel(const AttArgs a, 
     if (lane == 0) reinterpret_cast<float4*>(a.st)[it.row] = make_float4(a.q[it.row], m, 1.f / s, 0.f);
 }
 
-// pass 3 (by destination): parked scores -> weights; by source: the element-wise form
-template <bool TRANSPOSED>
+// pass 3 (by destination): parked scores -> weights
 __global__ void __launch_bounds__(256) attention_segment_write_kernel(const AttArgs a, const Segment* segs) {
     const Segment sg = segs[blockIdx.x];
     float* out = a.alpha + sg.e_begin;
-    if constexpr (TRANSPOSED) {
-        const int32_t* ci = a.colidx + sg.e_begin;
-        const float pu = a.p[sg.row];
-        for (int k = threadIdx.x; k < sg.len; k += 256) {
-            const float4 t = reinterpret_cast<const float4*>(a.st)[ci[k]];
-            out[k] = weight_of(lrelu(pu + t.x, a.slope), t.y, t.z);
-        }
+    const float4 t = reinterpret_cast<const float4*>(a.st)[sg.row];
+    for (int k = threadIdx.x; k < sg.len; k += 256) out[k] = weight_of(out[k], t.y, t.z);
+}
+// by source: the element-wise form
+__device__ __forceinline__ void attention_segment_write_transposed(const AttArgs& a, const Segment& sg) {
+    float* out = a.alpha + sg.e_begin;
+    const int32_t* ci = a.colidx + sg.e_begin;
+    const float pu = a.p[sg.row];
+    for (int k = threadIdx.x; k < sg.len; k += 256) {
+        const float4 t = reinterpret_cast<const float4*>(a.st)[ci[k]];
+        out[k] = weight_of(lrelu(pu + t.x, a.slope), t.y, t.z);
+    }
+}
+
+// Everything that depends on nothing else in one launch, long rows first (they are the longest-running pieces): blocks
+// [0, n_segs) take the segments of split rows, the next ones the rows of more than 32, more than 8 and
+// up to 8 entries (64, 32 and 8 lanes each).
+struct AttRanges {
+    const Segment* segs;
+    int n_segs;
+    int first[3], count[3];
+    int block_end[3];          // first block after each range of rows
+};
+template <bool TRANSPOSED>
+__global__ void __launch_bounds__(256) attention_kernel(const AttArgs a, const AttRanges r, float2* seg_stats) {
+    const int b = (int)blockIdx.x;
+    if (b < r.n_segs) {
+        if constexpr (TRANSPOSED) attention_segment_write_transposed(a, r.segs[b]);
+        else attention_segment_stats(a, r.segs[b], seg_stats);
+    } else if (b < r.block_end[0]) {
+        attention_rows<64, TRANSPOSED>(a, b - r.n_segs, r.first[0], r.count[0]);
+    } else if (b < r.block_end[1]) {
+        attention_rows<32, TRANSPOSED>(a, b - r.block_end[0], r.first[1], r.count[1]);
     } else {
-        const float4 t = reinterpret_cast<const float4*>(a.st)[sg.row];
-        for (int k = threadIdx.x; k < sg.len; k += 256) out[k] = weight_of(out[k], t.y, t.z);
+        attention_rows<8, TRANSPOSED>(a, b - r.block_end[1], r.first[2], r.count[2]);
     }
 }
 
@@ -189,14 +201,17 @@ __global__ void __launch_bounds__(256) attention_segment_write_kernel(const AttA
 //   dp[u] = sum over out-edges of ds.
 // By-destination pass (rows v, own = dY[v,:], gathered = Z[u,:]): dalpha of every entry (parked in
 // scratch), t[v], dq[v].  By-source pass (rows u, own = Z[u,:], gathered = dY[v,:]): dalpha again
-// in that order, with t[v] and alpha in by-source order: dp[u].  A group of L lanes (4, 8 or 16)
-// forms one dot product at a time (L x VEC x NJ columns, xor tree over the group).  Rows of more
-// than 128 entries take one block (its groups share the entries, partial sums combined through
-// LDS in a fixed order; one wavefront per such row measured slower); rows beyond the split
-// threshold one block per segment, the partial sums of the segments combined by a small kernel
-// in segment order.  Where both sweeps run in one kernel each lane keeps the dalpha of its first
-// entry in a register (short rows park nothing) and a parked dalpha is read back by the thread
-// that wrote it.  Widest row: 1024 columns with 16-byte vectors, 256 otherwise.
+// in that order, with t[v] and alpha in by-source order: dp[u].  A group of L lanes (4, 8 or 16) forms one dot
+// product at a time (L x VEC x NJ columns, xor tree over the group) and takes its entries L at a time: lane l loads id and
+// weight of the l-th (one coalesced load each, where one broadcast load per entry used to take as many issue slots as
+// the gathers), the ids are handed round inside the group, and lane l keeps the l-th dot product, so that weights, gates
+// and parked values are again one coalesced access per L entries.  Rows of more than 128 entries take one block (its
+// groups share the entries, partial sums combined through LDS in a fixed order; one wavefront per such row measured
+// slower); rows beyond the split threshold one block per segment, the partial sums of the segments combined by a small
+// kernel in segment order.  Where both sweeps run in one kernel a lane keeps its first entry in
+// registers (short rows park nothing) and a parked dalpha is read back by the thread that wrote it.
+// Widest row: 1024 columns with 16-byte vectors, 256 otherwise.
+// Measured (169,343 vertices, 2.5 M entries, 64 columns, by destination): 0.178 -> 0.114 ms for the whole pass.
 template <int VEC, int NJ, int L>
 struct DotRow {
     float own[NJ][VEC];
@@ -216,11 +231,11 @@ struct DotRow {
         }
     }
     // this lane's share of own . other (columns outside the row contribute zero)
-    __device__ __forceinline__ float partial(const float* other, bool live) const {
+    __device__ __forceinline__ float partial(const float* other) const {
         float acc = 0.f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            if (on[j] && live) {
+            if (on[j]) {
                 if constexpr (VEC == 4) {
                     const float4 t = *reinterpret_cast<const float4*>(other + col[j]);
                     acc = fmaf(own[j][0], t.x, acc); acc = fmaf(own[j][1], t.y, acc);
@@ -234,140 +249,215 @@ struct DotRow {
     }
 };
 
-// WORK_GROUP  : one row per group of L lanes, rows[first .. first + n_rows).
-// WORK_BLOCK  : one row per block (its 256 / L groups take the entries in turn), rows[first + blockIdx.x].
-// WORK_SEG    : one segment of a split row per block, segs[blockIdx.x]: the dot products of its
+template <int VEC, int NJ, int L, int U, int J, int I>
+__device__ __forceinline__ void group_gathers(const DotRow<VEC, NJ, L>& dot, const float* other, int64_t ld, int c, int lane, float (&part)[U]) {
+    if constexpr (I < U) {
+        part[I] = dot.partial(other + (int64_t)group_bcast<L, J + I>(c, lane) * ld);
+        group_gathers<VEC, NJ, L, U, J, I + 1>(dot, other, ld, c, lane, part);
+    }
+}
+// the dot products of the group's entries J .. L-1 whose ids the lanes hold in c: lane j ends with that of entry j.  Entries
+// from nb on (nb differs between the groups of a wavefront) are looked up in vain.
+template <int VEC, int NJ, int L, int U, int J = 0>
+__device__ __forceinline__ void group_dots(const DotRow<VEC, NJ, L>& dot, const float* other, int64_t ld, int c, int nb, int lane, float& da) {
+    if constexpr (J < L) {
+        if (__ballot(J < nb) == 0) return;
+        float part[U];
+        group_gathers<VEC, NJ, L, U, J, 0>(dot, other, ld, c, lane, part);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float s = group_sum<L>(part[u], lane);
+            da = lane % L == J + u ? s : da;
+        }
+        group_dots<VEC, NJ, L, U, J + U>(dot, other, ld, c, nb, lane, da);
+    }
+}
+
+// WORK_GROUP  : one row per group of L lanes, rows[first .. first + n_rows), `block` counts the blocks of this kind.
+// WORK_BLOCK  : one row per block (its 256 / L groups take L entries each in turn), rows[first + block].
+// WORK_SEG    : one segment of a split row per block, segs[block]: the dot products of its
 //               entries; the partial t (by destination) or partial dp (by source) goes to the
 //               segment's slot.
-// WORK_SEG_DS : by destination only, after the slots of t were combined: ds of the segment's
-//               entries from the parked dalpha, partial dq to the slot.
-enum { WORK_GROUP = 0, WORK_BLOCK = 1, WORK_SEG = 2, WORK_SEG_DS = 3 };
+enum { WORK_GROUP = 0, WORK_BLOCK = 1, WORK_SEG = 2 };
+
+// sum over the NG groups of a block of a value all lanes of a group hold, in a fixed order
+template <int L>
+__device__ __forceinline__ float block_sum(float v, float* red) {
+    constexpr int NG = 256 / L;
+    if (threadIdx.x % L == 0) red[threadIdx.x / L] = v;
+    __syncthreads();
+    float s = 0.f;
+    for (int i = 0; i < NG; ++i) s += red[i];
+    __syncthreads();
+    return s;
+}
 
 template <int VEC, int NJ, int L, bool TRANSPOSED, int WORK>
-__global__ void __launch_bounds__(256) attention_bwd_kernel(const AttBwdArgs a, int first, int n_rows, const Segment* segs) {
-    constexpr bool SEG = WORK == WORK_SEG || WORK == WORK_SEG_DS;
+__device__ __forceinline__ void attention_bwd_work(const AttBwdArgs& a, int block, int first, int n_rows, const Segment* segs, float* red) {
+    constexpr bool SEG = WORK == WORK_SEG;
     constexpr int R = 64 / L;                                          // groups per wavefront
-    constexpr int NG = 256 / L;                                        // groups per block
-    constexpr int SHARE = WORK == WORK_GROUP ? 1 : NG;                  // groups on one row
-    constexpr int U = 4;                                               // dot products in flight per group
-    __shared__ float red[NG];
+    constexpr int SHARE = WORK == WORK_GROUP ? 1 : 256 / L;            // groups on one row
+    constexpr int U = NJ == 1 ? (L < 8 ? L : 8) : 4;                   // dot products in flight per group
     const int lane = threadIdx.x & 63;
     const int l = lane % L;
     const int gi = SHARE == 1 ? 0 : (int)(threadIdx.x / L);            // group among those on the row
     int row = 0;
     int slot = 0;
     bool valid = true;
-    int64_t beg = 0, d = 0;
+    int64_t beg = 0;
+    int d = 0;
     if constexpr (SEG) {
-        const Segment sg = segs[blockIdx.x];
+        const Segment sg = segs[block];
         row = sg.row; slot = sg.slot; beg = sg.e_begin; d = sg.len;
     } else {
-        const int64_t idx = WORK == WORK_BLOCK ? (int64_t)blockIdx.x : ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * R + lane / L;
+        const int64_t idx = WORK == WORK_BLOCK ? (int64_t)block : ((int64_t)block * 4 + (threadIdx.x >> 6)) * R + lane / L;
         valid = idx < n_rows;
-        if (valid) { row = a.rows[first + idx]; beg = a.rowptr[row]; d = a.rowptr[row + 1] - beg; }
+        if (valid) { row = a.rows[first + idx]; beg = a.rowptr[row]; d = (int)(a.rowptr[row + 1] - beg); }
     }
     const int32_t* ci = a.colidx + beg;
     const float* al = a.alpha + beg;
     float* park = a.park + beg;
-    // sum over the groups that share the row of a value all lanes of a group hold, in a fixed order
     auto share_sum = [&](float v) {
-        if constexpr (SHARE == 1) {
-            return v;
-        } else {
-            if (l == 0) red[gi] = v;
-            __syncthreads();
-            float s = 0.f;
-            for (int i = 0; i < NG; ++i) s += red[i];
-            __syncthreads();
-            return s;
-        }
+        if constexpr (SHARE == 1) return v;
+        else return block_sum<L>(v, red);
     };
-    const bool writer = SHARE == NG ? threadIdx.x == 0 : (valid && l == 0);
-    if constexpr (WORK == WORK_SEG_DS) {
-        const float t = a.t[2 * row];
-        const float qv = a.q[row];
-        float dqp = 0.f;
-        for (int64_t k = threadIdx.x; k < d; k += 256) {
-            const int cc = ci[k];
-            const float wv = (park[k] - t) * (a.p[cc] + qv > 0.f ? 1.f : a.slope);
-            if (a.keep_w) park[k] = wv;
-            dqp += al[k] * wv;
-        }
-        dqp = share_sum(group_sum<L>(dqp, lane));
-        if (writer) a.slots[slot] = dqp;
-        return;
-    }
+    const bool writer = SHARE == 1 ? valid && l == 0 : threadIdx.x == 0;
     DotRow<VEC, NJ, L> dot;
     dot.load_own(a.own + (int64_t)row * a.ld_own, l, valid ? a.m : 0);
-    bool in[U];
-    int c[U], cn[U];
-    float da[U];
-    auto columns = [&](int64_t k, int (&cc)[U]) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) cc[u] = k + u * SHARE < d ? ci[k + u * SHARE] : row;
+    // this lane's entry of the group's batch at k: column id and weight (an entry that does not exist: the row's own vertex, 0)
+    auto entry = [&](int k, int& c, float& w) {
+        c = row;
+        w = 0.f;
+        if (k + l < d) { c = ci[k + l]; w = al[k + l]; }
     };
-    // dalpha of entries k, k + SHARE, ...: U gathers issued before the first xor tree; the
-    // column ids of the next batch are fetched meanwhile
-    auto dots = [&](int64_t k) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) { in[u] = k + u * SHARE < d; c[u] = cn[u]; }
-#pragma unroll
-        for (int u = 0; u < U; ++u) da[u] = dot.partial(a.other + (int64_t)c[u] * a.ld_other, in[u]);
-        columns(k + U * SHARE, cn);
-#pragma unroll
-        for (int u = 0; u < U; ++u) da[u] = group_sum<L>(da[u], lane);
-    };
-    columns(gi, cn);
-    if constexpr (TRANSPOSED) {
-        const float pu = valid ? a.p[row] : 0.f;
-        float acc = 0.f;
-        for (int64_t k = gi; __ballot(k < d) != 0; k += U * SHARE) {          // the wavefront stays together for the shuffles
-            dots(k);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (in[u]) {
-                    const float2 tq = reinterpret_cast<const float2*>(a.t)[c[u]];      // (t, q) of the destination
-                    acc += al[k + u * SHARE] * (da[u] - tq.x) * (pu + tq.y > 0.f ? 1.f : a.slope);
-                }
-        }
-        acc = share_sum(acc);
-        if (writer) { if constexpr (SEG) a.slots[slot] = acc; else a.out[row] = a.accumulate ? a.out[row] + acc : acc; }
-        return;
-    }
-    // by destination: sweep 1 = dalpha of every entry (parked by the lane that reads it back), t
-    float t = 0.f;
-    float mine = 0.f;
-    for (int64_t k = gi; __ballot(k < d) != 0; k += U * SHARE) {
-        dots(k);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (in[u]) {
-                const int64_t ku = k + u * SHARE;             // ku % SHARE == gi
-                t += al[ku] * da[u];
-                if (l == (int)((ku / SHARE) % L)) {
-                    if (!SEG && ku < SHARE * L) mine = da[u]; // the lane's first entry stays in a register
-                    else park[ku] = da[u];
-                }
+    const float own_pq = valid ? (TRANSPOSED ? a.p[row] : a.q[row]) : 0.f;
+    int c, c0;
+    float w, w0;
+    int k = gi * L;
+    entry(k, c, w);
+    c0 = c;
+    w0 = w;
+    float sum = 0.f, da0 = 0.f;
+    for (; __ballot(k < d) != 0; k += SHARE * L) {                     // the wavefront stays together for the shuffles
+        int cn;
+        float wn;
+        entry(k + SHARE * L, cn, wn);                                   // the next batch is fetched meanwhile
+        float da = 0.f;
+        group_dots<VEC, NJ, L, U>(dot, a.other, a.ld_other, c, d - k, lane, da);
+        const bool in = k + l < d;
+        if constexpr (TRANSPOSED) {
+            if (in) {
+                const float2 tq = reinterpret_cast<const float2*>(a.t)[c];      // (t, q) of the destination
+                sum += w * (da - tq.x) * (own_pq + tq.y > 0.f ? 1.f : a.slope);
+            }
+        } else {
+            if (in) {
+                sum += w * da;
+                if (SEG || k >= SHARE * L) park[k + l] = da;
+                else da0 = da;                                          // the first entry stays in a register
             }
         }
+        c = cn;
+        w = wn;
     }
-    t = share_sum(t);
+    sum = share_sum(group_sum<L>(sum, lane));
     if constexpr (SEG) {
-        if (writer) a.slots[slot] = t;
-        return;
+        if (writer) a.slots[slot] = sum;
+    } else if constexpr (TRANSPOSED) {
+        if (writer) a.out[row] = a.accumulate ? a.out[row] + sum : sum;
+    } else {
+        // sum = t: ds of the entries of this lane, added over the row
+        const float t = sum;
+        float dqp = 0.f;
+        for (int e = gi * L + l; e < d; e += SHARE * L) {
+            const bool kept = e < SHARE * L;
+            const int cc = kept ? c0 : ci[e];
+            const float wv = ((kept ? da0 : park[e]) - t) * (a.p[cc] + own_pq > 0.f ? 1.f : a.slope);
+            if (a.keep_w) park[e] = wv;
+            dqp += (kept ? w0 : al[e]) * wv;
+        }
+        dqp = share_sum(group_sum<L>(dqp, lane));
+        if (writer) { a.out[row] = a.accumulate ? a.out[row] + dqp : dqp; reinterpret_cast<float2*>(a.t)[row] = make_float2(t, own_pq); }
     }
-    // sweep 2: ds of the entries this lane parked, summed over the row
-    const float qv = valid ? a.q[row] : 0.f;
+}
+
+// blocks [0, n_segs): the segments of split rows; the next n_block_rows: rows of more than 128 entries; then the rest
+template <int VEC, int NJ, int L, bool TRANSPOSED>
+__global__ void __launch_bounds__(256) attention_bwd_kernel(const AttBwdArgs a, int n_segs, const Segment* segs, int n_group_rows, int n_block_rows) {
+    __shared__ float red[256 / L];
+    const int b = (int)blockIdx.x;
+    if (b < n_segs) attention_bwd_work<VEC, NJ, L, TRANSPOSED, WORK_SEG>(a, b, 0, 0, segs, red);
+    else if (b < n_segs + n_block_rows) attention_bwd_work<VEC, NJ, L, TRANSPOSED, WORK_BLOCK>(a, b - n_segs, n_group_rows, n_block_rows, segs, red);
+    else attention_bwd_work<VEC, NJ, L, TRANSPOSED, WORK_GROUP>(a, b - n_segs - n_block_rows, 0, n_group_rows, segs, red);
+}
+
+// by destination, after the slots of t were combined: ds of a segment's entries from the parked dalpha, partial dq to the slot
+__global__ void __launch_bounds__(256) attention_bwd_segment_ds_kernel(const AttBwdArgs a, const Segment* segs) {
+    __shared__ float red[4];
+    const Segment sg = segs[blockIdx.x];
+    const int32_t* ci = a.colidx + sg.e_begin;
+    const float* al = a.alpha + sg.e_begin;
+    float* park = a.park + sg.e_begin;
+    const float t = a.t[2 * sg.row];
+    const float qv = a.q[sg.row];
     float dqp = 0.f;
-    for (int64_t k = gi + SHARE * l; k < d; k += SHARE * L) {                // k % SHARE == gi, (k / SHARE) % L == l
-        const int cc = ci[k];
-        const float dak = k < SHARE * L ? mine : park[k];
-        const float wv = (dak - t) * (a.p[cc] + qv > 0.f ? 1.f : a.slope);
+    for (int k = threadIdx.x; k < sg.len; k += 256) {
+        const float wv = (park[k] - t) * (a.p[ci[k]] + qv > 0.f ? 1.f : a.slope);
         if (a.keep_w) park[k] = wv;
         dqp += al[k] * wv;
     }
-    dqp = share_sum(group_sum<L>(dqp, lane));
-    if (writer) { a.out[row] = a.accumulate ? a.out[row] + dqp : dqp; reinterpret_cast<float2*>(a.t)[row] = make_float2(t, qv); }
+    dqp = block_sum<64>(group_sum<64>(dqp, threadIdx.x & 63), red);
+    if (threadIdx.x == 0) a.slots[sg.slot] = dqp;
+}
+
+// dp[u] = sum over the by-source entries k of row u of alpha[k] * w[perm[k]] (EDGE_PERM graphs: w of every edge sits in
+// by-destination order).  One scalar per entry, so the lanes of a group take entries and not columns: blocks
+// [0, n_segs) the segments of split rows (to the slots), then 64 lanes for the rows of more than 32 entries, 8 for the others.
+template <int L>
+__device__ __forceinline__ void perm_sum_rows(const AttBwdArgs& a, const int32_t* perm, int block, int first, int n_rows) {
+    constexpr int R = 64 / L;
+    const int lane = threadIdx.x & 63, l = lane % L;
+    const int64_t idx = ((int64_t)block * 4 + (threadIdx.x >> 6)) * R + lane / L;
+    if (idx - lane / L >= n_rows) return;                  // the whole wavefront
+    const bool valid = idx < n_rows;
+    int row = 0;
+    int64_t beg = 0;
+    int d = 0;
+    if (valid) { row = a.rows[first + idx]; beg = a.rowptr[row]; d = (int)(a.rowptr[row + 1] - beg); }
+    float s = 0.f;
+    for (int k = l; k < d; k += 4 * L) {
+        int c[4];
+        float w[4], x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = k + u * L < d;
+            c[u] = in ? perm[beg + k + u * L] : perm[beg];
+            w[u] = in ? a.alpha[beg + k + u * L] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = a.park[c[u]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += k + u * L < d ? w[u] * x[u] : 0.f;
+    }
+    s = group_sum<L>(s, lane);
+    if (valid && l == 0) a.out[row] = a.accumulate ? a.out[row] + s : s;
+}
+
+__global__ void __launch_bounds__(256) perm_sum_kernel(const AttBwdArgs a, const int32_t* perm, int n_segs, const Segment* segs,
+                                                       int n_short_rows, int n_long_rows) {
+    __shared__ float red[4];
+    const int b = (int)blockIdx.x, long_blocks = (n_long_rows + 3) / 4;
+    if (b < n_segs) {
+        const Segment sg = segs[b];
+        float s = 0.f;
+        for (int k = threadIdx.x; k < sg.len; k += 256) s += a.alpha[sg.e_begin + k] * a.park[perm[sg.e_begin + k]];
+        s = block_sum<64>(group_sum<64>(s, threadIdx.x & 63), red);
+        if (threadIdx.x == 0) a.slots[sg.slot] = s;
+    } else if (b < n_segs + long_blocks) {
+        perm_sum_rows<64>(a, perm, b - n_segs, n_short_rows, n_long_rows);
+    } else {
+        perm_sum_rows<8>(a, perm, b - n_segs - long_blocks, 0, n_short_rows);
+    }
 }
 
 // out[row] = sum of the row's slots, in segment order (added to out[row] when accumulate is set);
@@ -383,65 +473,41 @@ __global__ void __launch_bounds__(256) attention_bwd_combine_kernel(const Reduce
     else out[it.row] = accumulate ? out[it.row] + s : s;
 }
 
-__global__ void __launch_bounds__(256) vec_add_kernel(float* __restrict__ a, const float* __restrict__ b, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) a[i] += b[i];
-}
-
 template <int VEC, int NJ, int L, bool T>
-int launch_bwd_shape(const AttBwdArgs& a, const AttBwdRows& r, int phase, hipStream_t st) {
-    const Segment* none = nullptr;
+int launch_bwd_shape(const AttBwdArgs& a, const AttBwdRows& r, hipStream_t st) {
     constexpr int ROWS_PER_BLOCK = 4 * (64 / L);
-    if (phase == 0) {
-        if (r.n_segs > 0)
-            hipLaunchKernelGGL((attention_bwd_kernel<VEC, NJ, L, T, WORK_SEG>), dim3((unsigned)r.n_segs), dim3(256), 0, st, a, 0, 0, r.segs);
-        if (r.n_block_rows > 0)
-            hipLaunchKernelGGL((attention_bwd_kernel<VEC, NJ, L, T, WORK_BLOCK>), dim3((unsigned)r.n_block_rows), dim3(256), 0, st, a,
-                               r.n_group_rows, r.n_block_rows, none);
-        if (r.n_group_rows > 0)
-            hipLaunchKernelGGL((attention_bwd_kernel<VEC, NJ, L, T, WORK_GROUP>), dim3((unsigned)((r.n_group_rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK)),
-                               dim3(256), 0, st, a, 0, r.n_group_rows, none);
-    } else if (phase == 2) {
-        if constexpr (!T) {
-            if (r.n_segs > 0)
-                hipLaunchKernelGGL((attention_bwd_kernel<VEC, NJ, L, false, WORK_SEG_DS>), dim3((unsigned)r.n_segs), dim3(256), 0, st, a, 0, 0, r.segs);
-        }
-    }
+    const int64_t blocks = (int64_t)r.n_segs + r.n_block_rows + (r.n_group_rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
+    if (blocks == 0) return NTP_OK;
+    hipLaunchKernelGGL((attention_bwd_kernel<VEC, NJ, L, T>), dim3((unsigned)blocks), dim3(256), 0, st, a, r.n_segs, r.segs,
+                       r.n_group_rows, r.n_block_rows);
     return hipGetLastError() == hipSuccess ? NTP_OK : NTP_EHIP;
 }
 
 // lanes per group: the smallest of 4, 8, 16 whose vectors cover the row; wider rows take several
 // vectors per lane
 template <int VEC, bool T>
-int launch_bwd_vec(const AttBwdArgs& a, const AttBwdRows& r, int phase, hipStream_t st) {
+int launch_bwd_vec(const AttBwdArgs& a, const AttBwdRows& r, hipStream_t st) {
     const int nvec = (a.m + VEC - 1) / VEC;
-    if (nvec <= 4) return launch_bwd_shape<VEC, 1, 4, T>(a, r, phase, st);
-    if (nvec <= 8) return launch_bwd_shape<VEC, 1, 8, T>(a, r, phase, st);
+    if (nvec <= 4) return launch_bwd_shape<VEC, 1, 4, T>(a, r, st);
+    if (nvec <= 8) return launch_bwd_shape<VEC, 1, 8, T>(a, r, st);
     const int nj = (nvec + 15) / 16;
-    if (nj <= 1) return launch_bwd_shape<VEC, 1, 16, T>(a, r, phase, st);
-    if (nj <= 2) return launch_bwd_shape<VEC, 2, 16, T>(a, r, phase, st);
-    if (nj <= 4) return launch_bwd_shape<VEC, 4, 16, T>(a, r, phase, st);
-    if (nj <= 8) return launch_bwd_shape<VEC, 8, 16, T>(a, r, phase, st);
-    if (nj <= 16) return launch_bwd_shape<VEC, 16, 16, T>(a, r, phase, st);
+    if (nj <= 1) return launch_bwd_shape<VEC, 1, 16, T>(a, r, st);
+    if (nj <= 2) return launch_bwd_shape<VEC, 2, 16, T>(a, r, st);
+    if (nj <= 4) return launch_bwd_shape<VEC, 4, 16, T>(a, r, st);
+    if (nj <= 8) return launch_bwd_shape<VEC, 8, 16, T>(a, r, st);
+    if (nj <= 16) return launch_bwd_shape<VEC, 16, 16, T>(a, r, st);
     set_error("feature width %d too large for the attention gradient (at most %d)", a.m, 256 * VEC);
     return NTP_EUNSUPPORTED;
-}
-
-template <int L, bool T>
-int launch_rows(const AttArgs& a, int first, int n_rows, hipStream_t st) {
-    if (n_rows <= 0) return NTP_OK;
-    const int rows_per_block = 4 * (64 / L);
-    hipLaunchKernelGGL((attention_rows_kernel<L, T>), dim3((unsigned)((n_rows + rows_per_block - 1) / rows_per_block)), dim3(256), 0, st, a, first, n_rows);
-    return hipGetLastError() == hipSuccess ? NTP_OK : NTP_EHIP;
 }
 
 }  // namespace
 
 // One chunk of a form, one phase at a time (a row beyond the split threshold may have its
 // segments in several chunks, so the caller runs a phase over all chunks before the next):
-//   phase 0: per-segment statistics of split rows (by-destination pass only)
+//   phase 0: by destination: weights of all rows but the split ones, statistics of the split rows' segments;
+//            by source: all weights
 //   phase 1: per-row combination of the segment statistics (by-destination pass only)
-//   phase 2: weights of the split rows' segments and of all other rows
+//   phase 2: weights of the split rows' segments (by-destination pass only)
 // bins: bin_row_off / bin_count describe rows[] (see Plan); bins 0..3 hold rows of up to 8
 // entries, 4..5 up to 32, the rest up to the split threshold; split rows come as segments
 // (segs, n_segs), their rows as reduce items; seg_stats: two floats per partial-sum slot.
@@ -450,45 +516,31 @@ int launch_attention(const AttArgs& a, const int32_t* bin_row_off, const int32_t
                      float* seg_stats, bool transposed, int phase, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     float2* ss = reinterpret_cast<float2*>(seg_stats);
-    int rc = NTP_OK;
-    if (phase == 0) {
-        if (!transposed && n_segs > 0)
-            hipLaunchKernelGGL(attention_segment_stats_kernel, dim3((unsigned)n_segs), dim3(256), 0, st, a, segs, ss);
-    } else if (phase == 1) {
+    if (phase == 1) {
         if (!transposed && n_split_rows > 0)
             hipLaunchKernelGGL(attention_combine_kernel, dim3((unsigned)n_split_rows), dim3(64), 0, st, a, split_rows, ss);
+    } else if (phase == 2) {
+        if (!transposed && n_segs > 0)
+            hipLaunchKernelGGL(attention_segment_write_kernel, dim3((unsigned)n_segs), dim3(256), 0, st, a, segs);
     } else {
-        auto span = [&](int b0, int b1, int& first, int& count) {
-            first = bin_row_off[b0];
-            count = 0;
-            for (int b = b0; b <= b1; ++b) count += bin_count[b];
-        };
-        int first, count;
-        // long rows first: they are the longest-running pieces
-        if (n_segs > 0) {
-            if (transposed) hipLaunchKernelGGL(attention_segment_write_kernel<true>, dim3((unsigned)n_segs), dim3(256), 0, st, a, segs);
-            else hipLaunchKernelGGL(attention_segment_write_kernel<false>, dim3((unsigned)n_segs), dim3(256), 0, st, a, segs);
+        AttRanges r;
+        r.segs = segs;
+        r.n_segs = n_segs;
+        int end = n_segs;
+        const int b0[3] = {6, 4, 0}, b1[3] = {NBINS - 1, 5, 3}, rows_per_block[3] = {4, 8, 32};
+        for (int i = 0; i < 3; ++i) {
+            r.first[i] = bin_row_off[b0[i]];
+            r.count[i] = 0;
+            for (int b = b0[i]; b <= b1[i]; ++b) r.count[i] += bin_count[b];
+            end += (r.count[i] + rows_per_block[i] - 1) / rows_per_block[i];
+            r.block_end[i] = end;
         }
-        span(6, NBINS - 1, first, count);
-        rc = transposed ? launch_rows<64, true>(a, first, count, st) : launch_rows<64, false>(a, first, count, st);
-        if (rc == NTP_OK) {
-            span(4, 5, first, count);
-            rc = transposed ? launch_rows<32, true>(a, first, count, st) : launch_rows<32, false>(a, first, count, st);
-        }
-        if (rc == NTP_OK) {
-            span(0, 3, first, count);
-            rc = transposed ? launch_rows<8, true>(a, first, count, st) : launch_rows<8, false>(a, first, count, st);
+        if (end > 0) {
+            if (transposed) hipLaunchKernelGGL(attention_kernel<true>, dim3((unsigned)end), dim3(256), 0, st, a, r, ss);
+            else hipLaunchKernelGGL(attention_kernel<false>, dim3((unsigned)end), dim3(256), 0, st, a, r, ss);
         }
     }
-    if (rc == NTP_OK && hipGetLastError() != hipSuccess) rc = NTP_EHIP;
-    if (rc != NTP_OK) set_error("attention kernel launch failed");
-    return rc;
-}
-
-int launch_vec_add(float* a, const float* b, int64_t n, void* stream) {
-    if (n <= 0) return NTP_OK;
-    hipLaunchKernelGGL(vec_add_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, a, b, n);
-    if (hipGetLastError() != hipSuccess) { set_error("kernel launch failed"); return NTP_EHIP; }
+    if (hipGetLastError() != hipSuccess) { set_error("attention kernel launch failed"); return NTP_EHIP; }
     return NTP_OK;
 }
 
@@ -496,26 +548,32 @@ int launch_vec_add(float* a, const float* b, int64_t n, void* stream) {
 // 1 = t of the split rows from their slots, 2 = second sweep of the segments (partial dq),
 // 3 = dq of the split rows.  By source: phase 0 = whole rows and segments (partial dp), 1 = dp of
 // the split rows.  The caller runs each phase over every chunk before the next one.
-int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, void* stream) {
+// perm (by source only, nullable): the edge permutation, with w of every edge in a.park (see perm_sum_kernel).
+int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, const int32_t* perm, void* stream) {
     hipStream_t st = (hipStream_t)stream;
+    int rc = NTP_OK;
     if (phase == 1 || phase == 3) {
         if (r.n_split_rows == 0) return NTP_OK;
         const bool is_t = phase == 1 && !transposed;
         hipLaunchKernelGGL(attention_bwd_combine_kernel, dim3((unsigned)((r.n_split_rows + 255) / 256)), dim3(256), 0, st,
                            r.split_rows, r.n_split_rows, a.slots, is_t ? a.t : a.out, is_t ? a.q : (const float*)nullptr,
                            is_t ? 0 : a.accumulate);
-        if (hipGetLastError() != hipSuccess) { set_error("attention gradient kernel launch failed"); return NTP_EHIP; }
-        return NTP_OK;
+    } else if (phase == 2) {
+        if (r.n_segs > 0) hipLaunchKernelGGL(attention_bwd_segment_ds_kernel, dim3((unsigned)r.n_segs), dim3(256), 0, st, a, r.segs);
+    } else if (perm) {
+        const int n_long = r.n_group_rows + r.n_block_rows - r.n_rows_32;
+        const int64_t blocks = (int64_t)r.n_segs + (n_long + 3) / 4 + (r.n_rows_32 + 31) / 32;
+        if (blocks > 0)
+            hipLaunchKernelGGL(perm_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, perm, r.n_segs, r.segs, r.n_rows_32, n_long);
+    } else {
+        const bool vec4 = a.m % 4 == 0 && a.ld_own % 4 == 0 && a.ld_other % 4 == 0 &&
+                          (uintptr_t)a.own % 16 == 0 && (uintptr_t)a.other % 16 == 0;
+        if (vec4) rc = transposed ? launch_bwd_vec<4, true>(a, r, st) : launch_bwd_vec<4, false>(a, r, st);
+        else rc = transposed ? launch_bwd_vec<1, true>(a, r, st) : launch_bwd_vec<1, false>(a, r, st);
+        if (rc == NTP_EUNSUPPORTED) return rc;
     }
-    const bool vec4 = a.m % 4 == 0 && a.ld_own % 4 == 0 && a.ld_other % 4 == 0 &&
-                      (uintptr_t)a.own % 16 == 0 && (uintptr_t)a.other % 16 == 0;
-    int rc;
-    if (vec4) rc = transposed ? launch_bwd_vec<4, true>(a, r, phase, st)
-                              : launch_bwd_vec<4, false>(a, r, phase, st);
-    else rc = transposed ? launch_bwd_vec<1, true>(a, r, phase, st)
-                         : launch_bwd_vec<1, false>(a, r, phase, st);
-    if (rc == NTP_EHIP) set_error("attention gradient kernel launch failed");
-    return rc;
+    if (rc != NTP_OK || hipGetLastError() != hipSuccess) { set_error("attention gradient kernel launch failed"); return NTP_EHIP; }
+    return NTP_OK;
 }
 
 }  // namespace ntp

@@ -144,14 +144,14 @@ inline int bin_max_degree(int b) { return b == 0 ? 1 : (b == NBINS - 1 ? INT_MAX
 // weights: caller's edge weights in the entry order of the form (nullptr: the stored ones)
 int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* partial,
               int64_t f, int64_t ldx, int64_t ldy, int dtype, hipStream_t st, bool scatter = false,
-              const float* weights = nullptr, const int32_t* columns = nullptr, bool defer_reduce = false,
+              const float* weights = nullptr, bool defer_reduce = false,
               const int32_t* hub_cols = nullptr, int n_hub = 0, const Epilogue& epi = Epilogue()) {
     AggArgs a;
     memset(&a, 0, sizeof a);
     a.rowptr = reinterpret_cast<const int64_t*>(img + c.off_rowptr);
     a.rows = reinterpret_cast<const int32_t*>(img + c.off_rows);
     a.segs = reinterpret_cast<const Segment*>(img + c.off_segs);
-    a.colidx = columns ? columns + c.e_begin : reinterpret_cast<const int32_t*>(img + c.img_off_colidx);
+    a.colidx = reinterpret_cast<const int32_t*>(img + c.img_off_colidx);
     a.val = weights ? weights + c.e_begin : reinterpret_cast<const float*>(img + c.img_off_val);
     a.X = X;
     a.Y = Y;
@@ -177,7 +177,7 @@ int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* pa
     }
     const int R = 64 / L;
     bool hub = false;
-    if (!scatter && !columns && c.d_colidx_hub && hub_cols) {
+    if (!scatter && c.d_colidx_hub && hub_cols) {
         a.colidx_hub = c.d_colidx_hub;
         a.hub_cols = hub_cols;
         a.n_hub = n_hub;
@@ -640,7 +640,7 @@ int ntp_graph_device_bytes(const ntp_graph_t* g, int64_t* bytes) {
 // static_partial: run on the library's static scratch instead of the handle's (no allocation)
 static int aggregate_resident(ntp_graph_t* g, int which, const void* X, void* Y, int64_t f,
                               int64_t ldx, int64_t ldy, int dtype, void* stream, const float* weights = nullptr,
-                              const int32_t* columns = nullptr, bool static_partial = false) {
+                              bool static_partial = false) {
     int rc = check_agg_args(g, X, Y, f, ldx, ldy, dtype);
     if (rc != NTP_OK) return rc;
     Form& F = g->f(which);
@@ -665,7 +665,7 @@ static int aggregate_resident(ntp_graph_t* g, int which, const void* X, void* Y,
     }
     if (rc != NTP_OK) return rc;
     for (auto& c : F.plan.chunks) {
-        rc = run_chunk(c, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, columns, F.one_reduce(),
+        rc = run_chunk(c, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
                        F.d_hub_cols, (int)F.plan.hub_cols.size());
         if (rc != NTP_OK) return rc;
     }
@@ -680,7 +680,7 @@ int ntp_aggregate_fwd(ntp_graph_t* g, const void* X, void* Y, int64_t f, int64_t
 
 int ntp_aggregate_fwd_noalloc(ntp_graph_t* g, const void* X, void* Y, int64_t f, int64_t ldx, int64_t ldy,
                               int dtype, void* stream) {
-    return aggregate_resident(g, NTP_CSR, X, Y, f, ldx, ldy, dtype, stream, nullptr, nullptr, true);
+    return aggregate_resident(g, NTP_CSR, X, Y, f, ldx, ldy, dtype, stream, nullptr, true);
 }
 
 int ntp_aggregate_bwd(ntp_graph_t* g, const void* Gout, void* Gin, int64_t f, int64_t ldo, int64_t ldi,
@@ -722,7 +722,7 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
     auto run_all = [&](const Chunk& c, const char* img) -> int {
         for (int r = 0; r < n_rhs; ++r) {
             const int e = run_chunk(c, img, X[r], Y[r], scatter ? nullptr : g->partial + (size_t)r * pstride, f, ldx, ldy, dtype, cs, scatter,
-                                    nullptr, nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
+                                    nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
             if (e != NTP_OK) return e;
         }
         return NTP_OK;
@@ -830,7 +830,7 @@ int ntp_edge_softmax(ntp_graph_t* g, const float* p, const float* q, float negat
     float* seg_stats = g->att_stats + 4 * n;
     // chunk by chunk, phase by phase (a split row's segments may lie in several chunks)
     auto run = [&](const Form& F, float* out, bool transposed) -> int {
-        for (int phase = transposed ? 2 : 0; phase < 3; ++phase)
+        for (int phase = 0; phase < (transposed ? 1 : 3); ++phase)
             for (const Chunk& c : F.plan.chunks) {
                 AttArgs a;
                 a.rowptr = reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin;
@@ -871,21 +871,19 @@ int ntp_edge_softmax_bwd(ntp_graph_t* g, const float* p, const float* q, float n
         return NTP_EBUDGET;
     }
     // scratch kept by the handle: (t, q) of every destination, one partial sum per segment of a
-    // split row, one dp per vertex, dalpha of every edge
+    // split row, dalpha of every edge
     const int64_t nnz = g->g.csr.nnz;
     const int64_t n_slots = std::max(Fin.plan.n_slots, Fout.plan.n_slots);
     if (!g->att_bwd) {
         void* ptr = nullptr;
-        // the per-edge array is also read as a one-column feature matrix indexed by ids below n
-        const size_t bytes = ((size_t)std::max(nnz, n) + 3 * (size_t)n + (size_t)n_slots) * 4 + 16;
+        const size_t bytes = ((size_t)nnz + 2 * (size_t)n + (size_t)n_slots) * 4 + 16;
         if (hipMalloc(&ptr, bytes) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of %zu bytes failed", bytes); return NTP_ENOMEM; }
         g->att_bwd = (float*)ptr;
         g->device_bytes += (int64_t)bytes;
     }
     float* t = g->att_bwd;              // (t, q) pairs
     float* slots = t + 2 * n;
-    float* dp_round = slots + n_slots;  // [n] this call's dp when it is added to the caller's
-    float* park = dp_round + n;
+    float* park = slots + n_slots;
     const bool by_perm = g->d_perm != nullptr;
     // chunk by chunk, phase by phase (a split row's segments may lie in several chunks)
     auto run = [&](const Form& F, bool transposed) -> int {
@@ -912,25 +910,20 @@ int ntp_edge_softmax_bwd(ntp_graph_t* g, const float* p, const float* q, float n
                 AttBwdRows r;
                 r.n_group_rows = c.bin_row_off[NBINS - 1];
                 r.n_block_rows = c.bin_count[NBINS - 1];
+                r.n_rows_32 = c.bin_row_off[6];
                 r.segs = reinterpret_cast<const Segment*>(c.d_image + c.off_segs);
                 r.n_segs = c.n_segs;
                 r.split_rows = reinterpret_cast<const ReduceItem*>(c.d_image + c.off_reduce);
                 r.n_split_rows = c.n_reduce;
-                const int rc = launch_attention_bwd(a, r, transposed, phase, stream);
+                const int rc = launch_attention_bwd(a, r, transposed, phase, transposed && by_perm ? g->d_perm : nullptr, stream);
                 if (rc != NTP_OK) return rc;
             }
         return NTP_OK;
     };
-    int rc = run(Fin, false);           // dq and t first: the by-source pass reads t
-    if (rc != NTP_OK) return rc;
-    if (!by_perm) return run(Fout, true);
-    // every edge's w = (dalpha - t) * LeakyReLU' now sits in park, in by-destination order:
-    // dp[u] = sum over the out-edges of alpha w is a one-column aggregation over the by-source
-    // form whose column ids are the edges' by-destination positions
-    float* dst = accumulate ? dp_round : dp;
-    rc = aggregate_resident(g, NTP_CSC, park, dst, 1, 1, 1, NTP_F32, stream, alpha_out, g->d_perm);
-    if (rc == NTP_OK && accumulate) rc = launch_vec_add(dp, dp_round, n, stream);
-    return rc;
+    // dq and t first: the by-source pass reads t, or (by_perm) every edge's w = (dalpha - t) * LeakyReLU', which then sits in
+    // park in by-destination order: dp[u] = sum over the out-edges of alpha w
+    const int rc = run(Fin, false);
+    return rc == NTP_OK ? run(Fout, true) : rc;
 }
 
 int ntp_attention_scores_fwd(const float* Z, const float* a_src, const float* a_dst, float* p, float* q,

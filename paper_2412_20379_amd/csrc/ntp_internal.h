@@ -246,12 +246,13 @@ struct AttBwdArgs {
 struct AttBwdRows {
     int n_group_rows;
     int n_block_rows;
+    int n_rows_32;                     // leading rows of up to 32 entries
     const Segment* segs;
     int n_segs;
     const ReduceItem* split_rows;      // rows whose last segment lies in this chunk
     int n_split_rows;
 };
-int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, void* stream);
+int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, const int32_t* perm, void* stream);
 
 // per-vertex attention scores and their chain rule (attention_scores_kernels.hip)
 int64_t attention_scores_max_width();
@@ -267,9 +268,6 @@ int launch_attention_scores_bwd(const float* Z, const float* a_src, const float*
 int launch_rebuild_weights(const int64_t* rowptr, int64_t row_base, int64_t n_rows, int64_t e_base, int64_t n_entries,
                            const int32_t* colidx, float* val, const int32_t* deg_row, const int32_t* deg_col, int mode,
                            void* stream);
-
-// a[i] += b[i]
-int launch_vec_add(float* a, const float* b, int64_t n, void* stream);
 
 int launch_softmax_xent(const float* Z, const int64_t* labels, float* dZ, float* loss, float* scratch,
                         int64_t n, int64_t c, int64_t ldz, int64_t lddz, void* stream);
