@@ -46,6 +46,8 @@ struct ntp_graph {
     size_t stage_bytes = 0;
     hipEvent_t ev_ready[2] = {nullptr, nullptr};   // copy of the chunk finished
     hipEvent_t ev_free[2] = {nullptr, nullptr};    // kernels reading the buffer finished
+    hipStream_t copy2 = nullptr;                   // second copy stream: buffer 1's (buffer 0's is the caller's)
+    hipEvent_t ev_copy2[2] = {nullptr, nullptr};   // orders it after and before the caller's copy stream
     bool stage_used[2] = {false, false};
     int next_stage = 0;
     char* pinned_meta = nullptr;                    // metas of streamed chunks
@@ -111,22 +113,38 @@ void free_entries(HostSparse& m, bool pinned, bool val_pinned) {
     m.val = nullptr;
 }
 
-// with_val = false: the weights are rebuilt on the device after the copy (launch_rebuild_weights)
-int upload_chunk(const HostSparse& m, Chunk& c, char* dst, hipStream_t st, bool async, const char* meta_src, bool with_val = true) {
+// a resident chunk's image
+int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
     const size_t ne = (size_t)(c.e_end - c.e_begin);
-    if (async) {
-        HIP_TRY(hipMemcpyAsync(dst, meta_src, c.meta.size(), hipMemcpyHostToDevice, st));
-        if (ne) {
-            HIP_TRY(hipMemcpyAsync(dst + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice, st));
-            if (with_val) HIP_TRY(hipMemcpyAsync(dst + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice, st));
-        }
-    } else {
-        HIP_TRY(hipMemcpy(dst, meta_src, c.meta.size(), hipMemcpyHostToDevice));
-        if (ne) {
-            HIP_TRY(hipMemcpy(dst + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(dst + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice));
-        }
+    HIP_TRY(hipMemcpy(dst, c.meta.data(), c.meta.size(), hipMemcpyHostToDevice));
+    if (ne) {
+        HIP_TRY(hipMemcpy(dst + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice));
+        HIP_TRY(hipMemcpy(dst + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice));
     }
+    return NTP_OK;
+}
+
+// Chunk images of up to this many bytes are copied by a kernel on the compute stream (36 us on the link): with DMA copies,
+// events and a second stream a chunk costs 50-70 us whatever its size.
+constexpr int64_t SMALL_CHUNK_BYTES = 2 << 20;
+
+int64_t streamed_bytes(const Chunk& c, bool with_val) { return (int64_t)c.meta.size() + (c.e_end - c.e_begin) * (with_val ? 8 : 4); }
+
+// Enqueue the copy of a streamed chunk's row pointers and lists, or of all of it, by a kernel (everything it reads is pinned).
+// with_val = false: the weights are rebuilt on the device after the copy (launch_rebuild_weights).
+int stage_chunk(const HostSparse& m, const Chunk& c, char* dst, hipStream_t st, bool entries, bool with_val) {
+    const int64_t entry_bytes = entries ? (c.e_end - c.e_begin) * 4 : 0;
+    const void* src[3] = {c.h_meta_pinned, m.colidx + c.e_begin, m.val + c.e_begin};
+    void* to[3] = {dst, dst + c.img_off_colidx, dst + c.img_off_val};
+    const int64_t bytes[3] = {(int64_t)c.meta.size(), entry_bytes, with_val ? entry_bytes : 0};
+    return launch_stage_chunk(src, to, bytes, st);
+}
+// its entries by DMA
+int copy_entries(const HostSparse& m, const Chunk& c, char* dst, hipStream_t st, bool with_val) {
+    const size_t ne = (size_t)(c.e_end - c.e_begin);
+    if (ne == 0) return NTP_OK;
+    HIP_TRY(hipMemcpyAsync(dst + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice, st));
+    if (with_val) HIP_TRY(hipMemcpyAsync(dst + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice, st));
     return NTP_OK;
 }
 
@@ -316,7 +334,9 @@ void destroy(ntp_graph* G) {
         if (G->stage[k]) (void)hipFree(G->stage[k]);
         if (G->ev_ready[k]) (void)hipEventDestroy(G->ev_ready[k]);
         if (G->ev_free[k]) (void)hipEventDestroy(G->ev_free[k]);
+        if (G->ev_copy2[k]) (void)hipEventDestroy(G->ev_copy2[k]);
     }
+    if (G->copy2) (void)hipStreamDestroy(G->copy2);
     if (G->partial) (void)hipFree(G->partial);
     if (G->att_stats) (void)hipFree(G->att_stats);
     if (G->att_bwd) (void)hipFree(G->att_bwd);
@@ -411,10 +431,12 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                 G->stage[b] = (char*)p;
                 G->device_bytes += (int64_t)max_img;
                 if (hipEventCreateWithFlags(&G->ev_ready[b], hipEventDisableTiming) != hipSuccess ||
-                    hipEventCreateWithFlags(&G->ev_free[b], hipEventDisableTiming) != hipSuccess) {
+                    hipEventCreateWithFlags(&G->ev_free[b], hipEventDisableTiming) != hipSuccess ||
+                    hipEventCreateWithFlags(&G->ev_copy2[b], hipEventDisableTiming) != hipSuccess) {
                     set_error("hipEventCreate failed"); return NTP_EHIP;
                 }
             }
+            if (hipStreamCreateWithFlags(&G->copy2, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); set_error("hipStreamCreate failed"); return NTP_EHIP; }
             left = force_stream ? 0 : budget - (int64_t)(2 * max_img);
         }
         // residency: everything if it fits, else chunks in round-robin order over the forms
@@ -433,7 +455,7 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                     c.d_image = (char*)p;
                     G->device_bytes += (int64_t)c.img_bytes;
                     if (!fits) left -= (int64_t)c.img_bytes;
-                    rc = upload_chunk(*G->form[k].m, c, c.d_image, nullptr, false, c.meta.data());
+                    rc = upload_chunk(*G->form[k].m, c, c.d_image);
                     if (rc != NTP_OK) { return rc; }
                 } else {
                     pinned_meta_bytes += c.meta.size();
@@ -727,6 +749,19 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
         }
         return NTP_OK;
     };
+    const bool rebuild = g->streams_without_weights();
+    bool small = true;
+    for (auto& c : F.plan.chunks) small = small && (c.d_image || streamed_bytes(c, !rebuild) <= SMALL_CHUNK_BYTES);
+    // Large chunks: the entries of consecutive chunks go by DMA on two copy streams in turn (one per staging buffer), so
+    // that the 20-30 us it takes to start a copy pass while the other one is on the link; the rest of the image is copied by a
+    // kernel on the compute stream (four chunks of 4 M entries: 1.45 -> 1.32 ms a pass, the link alone 1.15).
+    // Small chunks: everything on the compute stream.
+    const bool dma = !F.all_resident && !small;
+    bool touched[2] = {false, false};
+    if (dma) {
+        HIP_TRY(hipEventRecord(g->ev_copy2[0], xs));
+        HIP_TRY(hipStreamWaitEvent(g->copy2, g->ev_copy2[0], 0));
+    }
     for (auto& c : F.plan.chunks) {
         if (c.d_image) {
             rc = run_all(c, c.d_image);
@@ -735,26 +770,43 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
         }
         const int b = g->next_stage;
         g->next_stage ^= 1;
-        // the buffer may still be read by the kernels of the chunk that used it last
-        if (g->stage_used[b]) HIP_TRY(hipStreamWaitEvent(xs, g->ev_free[b], 0));
-        const bool rebuild = g->streams_without_weights();
-        rc = upload_chunk(*F.m, c, g->stage[b], xs, true, c.h_meta_pinned, !rebuild);
+        char* img = g->stage[b];
+        // the buffer may still be read by the kernels of the chunk that used it last (of an earlier call: on any stream)
+        if (!touched[b] && g->stage_used[b]) HIP_TRY(hipStreamWaitEvent(cs, g->ev_free[b], 0));
+        if (dma) {
+            const hipStream_t ks = b == 0 ? xs : g->copy2;
+            if (g->stage_used[b]) HIP_TRY(hipStreamWaitEvent(ks, g->ev_free[b], 0));
+            rc = copy_entries(*F.m, c, img, ks, !rebuild);
+            if (rc != NTP_OK) return rc;
+            HIP_TRY(hipEventRecord(g->ev_ready[b], ks));
+        }
+        rc = stage_chunk(*F.m, c, img, cs, !dma, !rebuild);
         if (rc != NTP_OK) return rc;
-        HIP_TRY(hipEventRecord(g->ev_ready[b], xs));
-        HIP_TRY(hipStreamWaitEvent(cs, g->ev_ready[b], 0));
+        if (dma) HIP_TRY(hipStreamWaitEvent(cs, g->ev_ready[b], 0));
         if (rebuild) {
             const bool by_source = &F == &g->form[1];          // rows are sources: row degree = dout, column degree = din
-            char* img = g->stage[b];
             rc = launch_rebuild_weights(reinterpret_cast<const int64_t*>(img + c.off_rowptr), c.row_begin, c.row_end - c.row_begin,
                                         c.e_begin, c.e_end - c.e_begin, reinterpret_cast<const int32_t*>(img + c.img_off_colidx),
                                         reinterpret_cast<float*>(img + c.img_off_val), by_source ? g->d_dout : g->d_din,
                                         by_source ? g->d_din : g->d_dout, g->g.val_mode, cs);
             if (rc != NTP_OK) return rc;
         }
-        rc = run_all(c, g->stage[b]);
+        rc = run_all(c, img);
         if (rc != NTP_OK) return rc;
-        HIP_TRY(hipEventRecord(g->ev_free[b], cs));
-        g->stage_used[b] = true;
+        touched[b] = true;
+        if (dma) {
+            HIP_TRY(hipEventRecord(g->ev_free[b], cs));
+            g->stage_used[b] = true;
+        }
+    }
+    for (int b = 0; b < 2; ++b)
+        if (!dma && touched[b]) {
+            HIP_TRY(hipEventRecord(g->ev_free[b], cs));
+            g->stage_used[b] = true;
+        }
+    if (dma) {          // whoever waits for the caller's copy stream waits for all copies
+        HIP_TRY(hipEventRecord(g->ev_copy2[1], g->copy2));
+        HIP_TRY(hipStreamWaitEvent(xs, g->ev_copy2[1], 0));
     }
     if (!scatter && F.one_reduce())
         for (int r = 0; r < n_rhs; ++r) {

@@ -263,6 +263,10 @@ int launch_attention_scores_bwd(const float* Z, const float* a_src, const float*
                                 float* dZ, float* da_src, float* da_dst, int64_t n, int64_t m, int64_t ldz, int64_t lddz,
                                 float* scratch, void* stream);
 
+// copy up to three pieces (bytes a multiple of 4, 0: none) from pinned host memory; source and destination of a piece
+// agree modulo 16
+int launch_stage_chunk(const void* const src[3], void* const dst[3], const int64_t bytes[3], void* stream);
+
 // val[e] of a chunk's entries from the structure (VAL_GCN / VAL_ONES): rowptr is the chunk's slice
 // (global entry offsets), colidx / val its entry arrays, deg_row / deg_col indexed by vertex id
 int launch_rebuild_weights(const int64_t* rowptr, int64_t row_base, int64_t n_rows, int64_t e_base, int64_t n_entries,

@@ -66,9 +66,12 @@ struct ChunkBuilder {
         if (!segs.empty()) memcpy(c.meta.data() + c.off_segs, segs.data(), segs.size() * sizeof(Segment));
         if (!reduce.empty()) memcpy(c.meta.data() + c.off_reduce, reduce.data(), reduce.size() * sizeof(ReduceItem));
         const size_t ne = (size_t)(c.e_end - c.e_begin);
-        c.img_off_colidx = meta_bytes;
-        c.img_off_val = c.img_off_colidx + align_up(ne * 4, 256);
-        c.img_bytes = c.img_off_val + align_up(ne * 4, 256);
+        // the entry arrays keep the alignment modulo 16 that they have in the form's own arrays, so that a streamed
+        // chunk is copied in 16-byte vectors
+        const size_t shift = (size_t)(c.e_begin * 4) % 16;
+        c.img_off_colidx = meta_bytes + shift;
+        c.img_off_val = align_up(c.img_off_colidx + ne * 4, 256) + shift;
+        c.img_bytes = align_up(c.img_off_val + ne * 4, 256);
         plan.max_img_bytes = std::max(plan.max_img_bytes, c.img_bytes);
     }
 };
