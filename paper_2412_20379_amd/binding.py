@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 import numpy as np
@@ -42,16 +43,28 @@ def lib_path() -> str:
 _lib = None
 
 
+class _Unloaded:
+    """stands for the native module until the first call loads it"""
+
+    def __getattr__(self, name):
+        lib()
+        return getattr(_native, name)
+
+
+_native = _Unloaded()
+
+
 def lib():
     """Load libntp.so, building it first only when no built library exists."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     path = lib_path()
-    if not os.path.exists(path):
-        from . import build as _build
+    from . import build as _build
+    if not os.path.exists(path) or not os.path.exists(_build.NATIVE):
         _build.build()
     L = ctypes.CDLL(path)
+    _native = importlib.import_module("._native", __package__)
     vp, i64, i32, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_uint32
     L.ntp_graph_build.argtypes = [i64, i64, vp, vp, vp, u32, i64, i64, ctypes.POINTER(vp)]
     L.ntp_graph_info.argtypes = [vp, vp, vp, vp, vp, vp]
@@ -105,21 +118,15 @@ def _check(rc: int):
 
 def _ptr(x):
     """Device or host address of a torch tensor / numpy array / int / None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return ctypes.c_void_p(x)
+    if x is None or isinstance(x, int):
+        return x
     if isinstance(x, np.ndarray):
-        return ctypes.c_void_p(x.ctypes.data)
-    return ctypes.c_void_p(x.data_ptr())          # torch tensor
+        return x.ctypes.data
+    return x.data_ptr()                           # torch tensor
 
 
 def _stream(s):
-    if s is None:
-        return None
-    if isinstance(s, int):
-        return ctypes.c_void_p(s)
-    return ctypes.c_void_p(s.cuda_stream)          # torch.cuda.Stream
+    return s if s is None or isinstance(s, int) else s.cuda_stream          # torch.cuda.Stream
 
 
 class Graph:
@@ -127,11 +134,12 @@ class Graph:
 
     def __init__(self, handle):
         self.handle = handle
+        self.addr = handle.value          # the handle as an int, None once closed
 
     def close(self):
         if self.handle:
             lib().ntp_graph_free(self.handle)
-            self.handle = None
+            self.handle = self.addr = None
 
     def __del__(self):
         try:
@@ -211,35 +219,43 @@ def ntp_graph_free(g: Graph):
 
 
 def ntp_aggregate_fwd(g: Graph, X, Y, f_slice, ldx, ldy, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_aggregate_fwd(g.handle, _ptr(X), _ptr(Y), int(f_slice), int(ldx), int(ldy), int(dtype), _stream(stream)))
+    rc = _native.ntp_aggregate_fwd(g.addr, X, Y, f_slice, ldx, ldy, dtype, stream)
+    if rc:
+        _check(rc)
 
 
 NTP_NOALLOC_SCRATCH_BYTES = 8 << 20
 
 
 def ntp_aggregate_fwd_noalloc(g: Graph, X, Y, f_slice, ldx, ldy, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_aggregate_fwd_noalloc(g.handle, _ptr(X), _ptr(Y), int(f_slice), int(ldx), int(ldy), int(dtype), _stream(stream)))
+    rc = _native.ntp_aggregate_fwd_noalloc(g.addr, X, Y, f_slice, ldx, ldy, dtype, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_aggregate_bwd(g: Graph, Gout, Gin, f_slice, ldg_out, ldg_in, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_aggregate_bwd(g.handle, _ptr(Gout), _ptr(Gin), int(f_slice), int(ldg_out), int(ldg_in), int(dtype), _stream(stream)))
+    rc = _native.ntp_aggregate_bwd(g.addr, Gout, Gin, f_slice, ldg_out, ldg_in, dtype, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_edge_softmax(g: Graph, p, q, negative_slope, alpha_in, alpha_out=None, stream=None):
-    _check(lib().ntp_edge_softmax(g.handle, _ptr(p), _ptr(q), float(negative_slope), _ptr(alpha_in), _ptr(alpha_out),
-                                  _stream(stream)))
+    rc = _native.ntp_edge_softmax(g.addr, p, q, negative_slope, alpha_in, alpha_out, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_edge_softmax_bwd(g: Graph, p, q, negative_slope, alpha_in, alpha_out, Z, dY, m, ldz, lddy, dp, dq, accumulate=False,
                          stream=None):
-    _check(lib().ntp_edge_softmax_bwd(g.handle, _ptr(p), _ptr(q), float(negative_slope), _ptr(alpha_in), _ptr(alpha_out),
-                                      _ptr(Z), _ptr(dY), int(m), int(ldz), int(lddy), _ptr(dp), _ptr(dq), int(bool(accumulate)),
-                                      _stream(stream)))
+    rc = _native.ntp_edge_softmax_bwd(g.addr, p, q, negative_slope, alpha_in, alpha_out, Z, dY, m, ldz, lddy, dp, dq, 1 if accumulate else 0, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_attention_scores_fwd(Z, a_src, a_dst, p, q, n, m, ldz, stream=None):
-    _check(lib().ntp_attention_scores_fwd(_ptr(Z), _ptr(a_src), _ptr(a_dst), _ptr(p), _ptr(q), int(n), int(m), int(ldz),
-                                          _stream(stream)))
+    rc = _native.ntp_attention_scores_fwd(Z, a_src, a_dst, p, q, n, m, ldz, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_attention_scores_bwd_scratch_bytes(n, m) -> int:
@@ -247,26 +263,29 @@ def ntp_attention_scores_bwd_scratch_bytes(n, m) -> int:
 
 
 def ntp_attention_scores_bwd(Z, a_src, a_dst, dp, dq, dZ, da_src, da_dst, n, m, ldz, lddz, scratch, scratch_bytes, stream=None):
-    _check(lib().ntp_attention_scores_bwd(_ptr(Z), _ptr(a_src), _ptr(a_dst), _ptr(dp), _ptr(dq), _ptr(dZ), _ptr(da_src),
-                                          _ptr(da_dst), int(n), int(m), int(ldz), int(lddz), _ptr(scratch), int(scratch_bytes),
-                                          _stream(stream)))
+    rc = _native.ntp_attention_scores_bwd(Z, a_src, a_dst, dp, dq, dZ, da_src, da_dst, n, m, ldz, lddz, scratch, scratch_bytes, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_aggregate_weighted(g: Graph, direction, weights, X, Y, f_slice, ldx, ldy, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_aggregate_weighted(g.handle, int(direction), _ptr(weights), _ptr(X), _ptr(Y), int(f_slice),
-                                        int(ldx), int(ldy), int(dtype), _stream(stream)))
+    rc = _native.ntp_aggregate_weighted(g.addr, direction, weights, X, Y, f_slice, ldx, ldy, dtype, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_chunked_aggregate(g: Graph, direction, X, Y, f_slice, ldx, ldy, dtype=NTP_F32,
                           compute_stream=None, copy_stream=None):
-    _check(lib().ntp_chunked_aggregate(g.handle, int(direction), _ptr(X), _ptr(Y), int(f_slice), int(ldx), int(ldy),
-                                       int(dtype), _stream(compute_stream), _stream(copy_stream)))
+    rc = _native.ntp_chunked_aggregate(g.addr, direction, X, Y, f_slice, ldx, ldy, dtype, compute_stream, copy_stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_aggregate_act(g: Graph, direction, X, Y, f_slice, ldx, ldy, dtype=NTP_F32, act=NTP_ACT_RELU, M=None, ldm=0,
                       compute_stream=None, copy_stream=None):
-    _check(lib().ntp_aggregate_act(g.handle, int(direction), _ptr(X), _ptr(Y), int(f_slice), int(ldx), int(ldy), int(dtype),
-                                   int(act), _ptr(M), int(ldm), _stream(compute_stream), _stream(copy_stream)))
+    rc = _native.ntp_aggregate_act(g.addr, direction, X, Y, f_slice, ldx, ldy, dtype, act, M, ldm, compute_stream, copy_stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_chunked_aggregate_multi(g: Graph, direction, Xs, Ys, f_slice, ldx, ldy, dtype=NTP_F32,
@@ -281,7 +300,9 @@ def ntp_chunked_aggregate_multi(g: Graph, direction, Xs, Ys, f_slice, ldx, ldy, 
 
 
 def ntp_nn_fwd(A, W, H, n, k, m, act=NTP_ACT_NONE, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_nn_fwd(_ptr(A), _ptr(W), _ptr(H), int(n), int(k), int(m), int(act), int(dtype), _stream(stream)))
+    rc = _native.ntp_nn_fwd(A, W, H, n, k, m, act, dtype, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_nn_bwd_workspace_bytes(n, k, m) -> int:
@@ -290,8 +311,9 @@ def ntp_nn_bwd_workspace_bytes(n, k, m) -> int:
 
 def ntp_nn_bwd(A, W, H, dH, dA, dW, n, k, m, act=NTP_ACT_NONE, dtype=NTP_F32,
                workspace=None, workspace_bytes=0, stream=None):
-    _check(lib().ntp_nn_bwd(_ptr(A), _ptr(W), _ptr(H), _ptr(dH), _ptr(dA), _ptr(dW), int(n), int(k), int(m),
-                            int(act), int(dtype), _ptr(workspace), int(workspace_bytes), _stream(stream)))
+    rc = _native.ntp_nn_bwd(A, W, H, dH, dA, dW, n, k, m, act, dtype, workspace, workspace_bytes, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_softmax_xent_scratch_bytes(n) -> int:
@@ -299,13 +321,18 @@ def ntp_softmax_xent_scratch_bytes(n) -> int:
 
 
 def ntp_softmax_xent(Z, labels, dZ, loss, scratch, scratch_bytes, n, c, ldz, lddz, stream=None):
-    _check(lib().ntp_softmax_xent(_ptr(Z), _ptr(labels), _ptr(dZ), _ptr(loss), _ptr(scratch), int(scratch_bytes),
-                                  int(n), int(c), int(ldz), int(lddz), _stream(stream)))
+    rc = _native.ntp_softmax_xent(Z, labels, dZ, loss, scratch, scratch_bytes, n, c, ldz, lddz, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_relu_fwd(H, n, f, ld, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_relu_fwd(_ptr(H), int(n), int(f), int(ld), int(dtype), _stream(stream)))
+    rc = _native.ntp_relu_fwd(H, n, f, ld, dtype, stream)
+    if rc:
+        _check(rc)
 
 
 def ntp_relu_bwd(dH, H, dZ, n, f, ld, dtype=NTP_F32, stream=None):
-    _check(lib().ntp_relu_bwd(_ptr(dH), _ptr(H), _ptr(dZ), int(n), int(f), int(ld), int(dtype), _stream(stream)))
+    rc = _native.ntp_relu_bwd(dH, H, dZ, n, f, ld, dtype, stream)
+    if rc:
+        _check(rc)

@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -13,6 +14,9 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libntp.so")
 PROBE_SRC = os.path.join(CSRC, "line_rate_probe.hip")
 PROBE = os.path.join(PKG, "line_rate_probe")        # prints the chip's 128-byte line rates (L2 / Infinity Cache / HBM)
+
+NATIVE_SRC = os.path.join(CSRC, "py_native.cpp")
+NATIVE = os.path.join(PKG, "_native" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))       # Python entry to the enqueue calls
 
 SOURCES = ["graph_build.cpp", "plan.cpp", "ntp_api.hip", "agg_kernels.hip", "scatter_kernels.hip", "chunk_kernels.hip", "attention_kernels.hip", "attention_scores_kernels.hip", "loss_kernels.hip", "nn_kernels.hip", "nn_strip_kernels.hip", "nn_dw_kernels.hip"]
 HEADERS = [os.path.join(CSRC, "ntp_internal.h"), os.path.join(CSRC, "lane_util.h"), os.path.join(CSRC, "nn_util.h"), os.path.join(ROOT, "include", "ntp.h")]
@@ -66,6 +70,11 @@ def build(force: bool = False, verbose: bool = False) -> str:
         tmp = LIB + ".tmp%d" % os.getpid()
         run([hipcc, "-shared", "-fPIC", "-o", tmp] + objs + ["--offload-arch=gfx950", "-lpthread"])
         os.replace(tmp, LIB)
+    if force or _stale(NATIVE, [NATIVE_SRC, os.path.join(ROOT, "include", "ntp.h"), os.path.abspath(__file__)]):
+        tmp = NATIVE + ".tmp%d" % os.getpid()
+        run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + os.path.join(ROOT, "include"),
+             "-I" + sysconfig.get_paths()["include"], NATIVE_SRC, "-o", tmp, "-L" + PKG, "-lntp", "-Wl,-rpath,$ORIGIN"])
+        os.replace(tmp, NATIVE)
     # the stand-alone measurement aid (its own executable: it links nothing of the library)
     if force or _stale(PROBE, [PROBE_SRC]):
         tmp = PROBE + ".tmp%d" % os.getpid()
