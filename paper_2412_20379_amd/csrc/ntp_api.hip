@@ -98,7 +98,7 @@ int static_scratch(float** out) {
     return NTP_OK;
 }
 
-void* alloc_plain(size_t bytes, void*) { return malloc(bytes); }
+void* alloc_plain(size_t bytes, void*) { return alloc_large(bytes); }
 void* alloc_pinned(size_t bytes, void*) {
     void* p = nullptr;
     if (hipHostMalloc(&p, bytes, hipHostMallocDefault) != hipSuccess) return nullptr;
@@ -401,7 +401,7 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
         const int64_t nnz = G->g.csr.nnz;
         if (nnz > INT_MAX) { set_error("NTP_EDGE_PERM takes graphs of fewer than 2^31 stored entries"); return NTP_EUNSUPPORTED; }
         G->h_perm.resize((size_t)nnz);
-        build_edge_perm(G->g, G->h_perm.data());
+        if (!build_edge_perm(G->g, G->h_perm.data())) { set_error("out of host memory for the edge permutation"); return NTP_ENOMEM; }
     }
     for (int k = 0; k < n_forms; ++k) make_plan(*G->form[k].m, ce, &G->form[k].plan);
     for (int k = 0; k < n_forms; ++k)

@@ -71,7 +71,10 @@ int build_host_graph(int64_t n, int64_t n_edges, const int32_t* src, const int32
 
 // perm[p] (nnz entries, nnz < 2^31): where the edge at position p of the by-source form sits in
 // the by-destination form
-void build_edge_perm(const BuiltGraph& G, int32_t* perm);
+bool build_edge_perm(const BuiltGraph& G, int32_t* perm);       // false: out of host memory
+
+// malloc for arrays of many megabytes (free() releases them)
+void* alloc_large(size_t bytes);
 
 // ---------------------------------------------------------------------------------------
 // Plan: how the rows of one compressed form are mapped to wavefronts.

@@ -11,12 +11,10 @@ namespace ntp {
 
 namespace {
 
+// bin 0: d <= 1, bin b: 2^(b-1) < d <= 2^b, the last one everything above
 inline int bin_of(int64_t d) {
     if (d <= 1) return 0;
-    int b = 1;
-    int64_t hi = 2;
-    while (d > hi && b < NBINS - 1) { hi <<= 1; ++b; }
-    return b;
+    return std::min(NBINS - 1, 64 - __builtin_clzll((unsigned long long)(d - 1)));
 }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -24,23 +22,27 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 struct ChunkBuilder {
     const HostSparse& m;
     Plan& plan;
-    std::vector<int32_t> bin_rows[NBINS];
     std::vector<Segment> segs;
     std::vector<ReduceItem> reduce;
 
     void reset() {
-        for (auto& b : bin_rows) b.clear();
         segs.clear();
         reduce.clear();
     }
 
-    void finish(Chunk& c) {
+    // bins: the rows of the chunk that are not split are listed by bin (counted first, then written in place)
+    void finish(Chunk& c, bool bins) {
         const int64_t nrows = c.row_end - c.row_begin;
+        const int64_t* rp = m.rowptr.data();
+        if (bins)
+            for (int64_t v = c.row_begin; v < c.row_end; ++v) {
+                const int64_t d = rp[v + 1] - rp[v];
+                if (d <= plan.split_threshold) ++c.bin_count[bin_of(d)];
+            }
         size_t nbin = 0;
         for (int b = 0; b < NBINS; ++b) {
-            c.bin_count[b] = (int32_t)bin_rows[b].size();
             c.bin_row_off[b] = (int32_t)nbin;
-            nbin += bin_rows[b].size();
+            nbin += (size_t)c.bin_count[b];
         }
         c.n_segs = (int32_t)segs.size();
         c.n_reduce = (int32_t)reduce.size();
@@ -60,9 +62,15 @@ struct ChunkBuilder {
         const size_t meta_bytes = align_up(c.off_reduce + reduce.size() * sizeof(ReduceItem), 256);
         c.meta.assign(meta_bytes, 0);
         memcpy(c.meta.data() + c.off_rowptr, m.rowptr.data() + c.row_begin, (size_t)(nrows + 1) * 8);
-        for (int b = 0; b < NBINS; ++b)
-            if (!bin_rows[b].empty())
-                memcpy(c.meta.data() + c.off_rows + (size_t)c.bin_row_off[b] * 4, bin_rows[b].data(), bin_rows[b].size() * 4);
+        if (bins) {
+            int32_t* rows = reinterpret_cast<int32_t*>(c.meta.data() + c.off_rows);
+            int32_t* at[NBINS];
+            for (int b = 0; b < NBINS; ++b) at[b] = rows + c.bin_row_off[b];
+            for (int64_t v = c.row_begin; v < c.row_end; ++v) {
+                const int64_t d = rp[v + 1] - rp[v];
+                if (d <= plan.split_threshold) *at[bin_of(d)]++ = (int32_t)v;
+            }
+        }
         if (!segs.empty()) memcpy(c.meta.data() + c.off_segs, segs.data(), segs.size() * sizeof(Segment));
         if (!reduce.empty()) memcpy(c.meta.data() + c.off_reduce, reduce.data(), reduce.size() * sizeof(ReduceItem));
         const size_t ne = (size_t)(c.e_end - c.e_begin);
@@ -133,7 +141,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
     P.seg_len = seg;
     P.split_threshold = chunked ? std::min(2 * seg, chunk_edges) : 2 * seg;
 
-    ChunkBuilder cb{m, P, {}, {}, {}};
+    ChunkBuilder cb{m, P, {}, {}};
     int32_t next_slot = 0;
     int64_t r = 0;
     while (r < n) {
@@ -165,11 +173,9 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
                         cb.segs.push_back(Segment{e, (int32_t)l, (int32_t)v, next_slot++, 0});
                         e += l;
                     }
-                } else {
-                    cb.bin_rows[bin_of(d)].push_back((int32_t)v);
                 }
             }
-            cb.finish(c);
+            cb.finish(c, true);
             P.chunks.push_back(std::move(c));
         } else {
             // one row larger than a chunk: its segments are packed into chunks of their own
@@ -193,7 +199,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
                 }
                 c.e_end = e;
                 if (i == nseg) cb.reduce.push_back(ReduceItem{(int32_t)r, first_slot, (int32_t)nseg, 0});
-                cb.finish(c);
+                cb.finish(c, false);
                 P.chunks.push_back(std::move(c));
             }
         }
@@ -202,7 +208,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
     if (n == 0) {   // an empty graph still has one (empty) chunk
         Chunk c;
         cb.reset();
-        cb.finish(c);
+        cb.finish(c, true);
         P.chunks.push_back(std::move(c));
     }
     P.n_slots = next_slot;
