@@ -179,6 +179,7 @@ int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* pa
     a.partial = partial;
     a.row_base = c.row_begin;
     a.e_base = c.e_begin;
+    a.e_end = c.e_end;
     a.ldx = ldx;
     a.ldy = ldy;
     a.f = (int32_t)f;
@@ -204,14 +205,19 @@ int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* pa
 
     int ng = 0;
     int64_t waves = 0;
-    auto add_group = [&](int mode, int off, int count, int64_t nw) {
+    auto add_group = [&](int mode, int off, int count, int64_t nw, int per_wave = 1, int per_fetch = 1) {
         a.wave_start[ng] = (int32_t)waves;
         a.item_off[ng] = off;
         a.item_count[ng] = count;
         a.mode[ng] = mode;
+        a.per_wave[ng] = per_wave;
+        a.per_fetch[ng] = per_fetch;
         waves += nw;
         ++ng;
     };
+    // Gathers of the launch per 1/16 of the work of a wavefront slot (8192 on the chip): what one wavefront may take
+    // without the launch ending on a few late ones.
+    const double quantum = (double)(c.e_end - c.e_begin) * passes / (16.0 * 8192.0);
     const bool block_rows = !scatter && !hub && c.block_rows;      // split rows summed by one block each (see make_plan)
     a.split_rows = reinterpret_cast<const ReduceItem*>(img + c.off_reduce);
     // heaviest work first: split rows, then bins from long rows to short rows
@@ -220,10 +226,23 @@ int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* pa
     for (int b = NBINS - 1; b >= 0; --b) {
         const int cnt = c.bin_count[b];
         if (cnt == 0) continue;
-        // rows of up to 32 entries: one lane group per row (measured best for every group count)
-        const bool per_group = R > 1 && bin_max_degree(b) <= 32;
-        if (per_group) add_group(MODE_GROUP_PER_ROW, c.bin_row_off[b], cnt, (cnt + R - 1) / R);
-        else add_group(MODE_WAVE_PER_ROW, c.bin_row_off[b], cnt, cnt);
+        const int len = bin_max_degree(b);
+        // One lane group per row costs no reduction and one wavefront per R rows; it takes R times as long, so rows of
+        // more than 32 entries get it only in bf16 (whose reduction has twice the values) and in launches large enough
+        // (28.8 M entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us
+        // if they are, hence the rule; in fp32 it makes 1 % at best).
+        const bool per_group = R > 1 && (len <= 32 || (!scatter && dtype == NTP_BF16 && len <= 128 && (double)len * R <= 2 * quantum));
+        const int at_once = per_group ? R : 1;
+        const int items = (cnt + at_once - 1) / at_once;
+        // rows per wavefront: as many as the quantum allows, and two where one fetch of pairs covers two anyway
+        // (F = 256 on 2.5 M entries: 251 us with one, 228 with two, 247 with four)
+        int K = 1, S = 1;
+        if (!scatter && len <= 128) {
+            K = (int)std::min<double>(std::min(8, L), quantum / (len * at_once));
+            K = std::max(K, per_group && 2 * len <= 4 * L ? std::min(2, L) : 1);
+        }
+        while (per_group && 2 * S <= std::min(K, L) && 2 * S * len <= 4 * L) S *= 2;
+        add_group(per_group ? MODE_GROUP_PER_ROW : MODE_WAVE_PER_ROW, c.bin_row_off[b], cnt, (items + K - 1) / K, K, S);
     }
     if (waves > INT_MAX - 8) { set_error("chunk too large for one launch (%lld wavefronts)", (long long)waves); return NTP_EUNSUPPORTED; }
     a.wave_start[ng] = (int32_t)waves;

@@ -166,7 +166,7 @@ struct AggArgs {
     const void* M;             // epilogue mask source, rows indexed like Y (nullptr: the output itself)
     float* partial;            // [n_slots x fp] partial sums of split rows
     int64_t row_base;
-    int64_t e_base;
+    int64_t e_base, e_end;     // the chunk's entries
     int64_t ldx, ldy, ldm;
     int32_t epilogue;          // 1: an output element is kept where its mask element (M, or itself) is > 0, else stored as 0
     int32_t f;                 // slice width
@@ -178,6 +178,8 @@ struct AggArgs {
     int32_t item_off[NGROUPS];         // offset into rows[] (bins) or segs[] (segment group)
     int32_t item_count[NGROUPS];       // rows / segments in the group
     int32_t mode[NGROUPS];             // MODE_*
+    int32_t per_wave[NGROUPS];         // items (rows, or R rows at a time) a wavefront of a row group works through
+    int32_t per_fetch[NGROUPS];        // rows of a lane group whose entries one fetch brings (a power of two)
 };
 enum { MODE_GROUP_PER_ROW = 0, MODE_WAVE_PER_ROW = 1, MODE_SEGMENT = 2, MODE_BLOCK_PER_ROW = 3 };
 

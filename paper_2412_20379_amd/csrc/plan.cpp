@@ -19,6 +19,22 @@ inline int bin_of(int64_t d) {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Rows of one bin (ascending ids, lengths in (below, 2 * below]) ordered by length, longest first, inside windows of
+// SORT_WINDOW rows: lane groups that share a wavefront get rows of one length (mostly), and rows that are near in memory
+// stay near in the list (windows of 512 rows cost 2-5 % on short rows: fewer rows share a line of the row pointers).
+constexpr int SORT_WINDOW = 64;
+void sort_by_length(int32_t* rows, int64_t n, const int64_t* rp, int below) {
+    int32_t tmp[SORT_WINDOW];
+    for (int64_t w = 0; w < n; w += SORT_WINDOW) {
+        const int m = (int)std::min<int64_t>(SORT_WINDOW, n - w);
+        int at[64 + 1] = {0};               // at[k + 1]: rows of length 2 * below - k
+        for (int i = 0; i < m; ++i) ++at[2 * below - (rp[rows[w + i] + 1] - rp[rows[w + i]]) + 1];
+        for (int k = 1; k < below; ++k) at[k] += at[k - 1];
+        for (int i = 0; i < m; ++i) tmp[at[2 * below - (rp[rows[w + i] + 1] - rp[rows[w + i]])]++] = rows[w + i];
+        std::copy(tmp, tmp + m, rows + w);
+    }
+}
+
 struct ChunkBuilder {
     const HostSparse& m;
     Plan& plan;
@@ -70,6 +86,7 @@ struct ChunkBuilder {
                 const int64_t d = rp[v + 1] - rp[v];
                 if (d <= plan.split_threshold) *at[bin_of(d)]++ = (int32_t)v;
             }
+            for (int b = 2; b < NBINS - 1; ++b) sort_by_length(rows + c.bin_row_off[b], c.bin_count[b], rp, 1 << (b - 1));
         }
         if (!segs.empty()) memcpy(c.meta.data() + c.off_segs, segs.data(), segs.size() * sizeof(Segment));
         if (!reduce.empty()) memcpy(c.meta.data() + c.off_reduce, reduce.data(), reduce.size() * sizeof(ReduceItem));
