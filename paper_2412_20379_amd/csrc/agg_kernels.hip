@@ -150,6 +150,11 @@ template <int VEC> struct IoBf16 {
 constexpr int EPL = 4;      // entries (index, weight pairs) a lane fetches at a time
 typedef int Int4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float Float4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int IntL4 __attribute__((ext_vector_type(4)));
+typedef float FloatL4 __attribute__((ext_vector_type(4)));
+// words of LDS a wavefront stages its pairs in: 256 indices and weights, one 16-byte slot of padding per lane group (the
+// groups' slots would start in the same banks)
+constexpr int stage_words(int L, bool hub) { return 2 * (EPL * 64 + (hub ? 0 : 64 / L * EPL)); }
 typedef int64_t Long2 __attribute__((ext_vector_type(2), aligned(8)));
 
 // Sums over the two halves of the wavefront, and over the rows of 16 lanes of each half, of two values at once: the
@@ -184,13 +189,11 @@ __device__ __forceinline__ int64_t readlane_l(int64_t v, int lane) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Wavefronts per SIMD the register allocation must allow.  The line-wide shapes (8 lanes x 16 bytes) fit 7 (fp32) and 6
-// (bf16) per SIMD without spilling.  One more each spills 10 and 2 registers and costs 10-25 % in fp32; one less (forced
-// with LDS) costs 2-4 %.  The other shapes keep the compiler's choice.
+// Wavefronts per SIMD the register allocation must allow.  The line-wide shapes (8 lanes x 16 bytes) fit 6 per SIMD without
+// spilling; with 7 the fp32 one spills and is 2-4 % slower.  The other shapes keep the compiler's choice.
 template <class IO, int L, int NACC>
 constexpr int agg_min_waves() {
-    if (NACC == 1 && L == 8 && sizeof(typename IO::elem) * IO::kVec == 16) return sizeof(typename IO::elem) == 4 ? 7 : 6;
-    return 1;
+    return NACC == 1 && L == 8 && sizeof(typename IO::elem) * IO::kVec == 16 ? 6 : 1;
 }
 
 // ---- the aggregation kernels ----------------------------------------------------------
@@ -201,11 +204,12 @@ constexpr int HUB_SLOTS = 1024;       // lines of the LDS hub table (128 KB at 1
 // take their row from `table`; MODE_BLOCK_PER_ROW is not available then.
 template <class IO, int L, int NACC, bool HUB>
 __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const int pass,
-                                         const typename IO::elem* table, float (*quarter)[L * IO::kVec * NACC]) {
+                                         const typename IO::elem* table, float (*quarter)[L * IO::kVec * NACC], int* stage) {
     using T = typename IO::elem;
     constexpr int VEC = IO::kVec;
     constexpr int R = 64 / L;
     constexpr int PASS_W = L * VEC * NACC;
+    constexpr int STAGE = stage_words(L, HUB), GSTRIDE = EPL * L + (HUB ? 0 : EPL);
     // gathers in flight per lane: 1, 2 and 4 give the same throughput, 8 costs wavefronts
     constexpr int U = NACC == 4 || L == 2 ? 2 : 4;
 
@@ -218,7 +222,8 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     const int l = lane % L;
     const int colbase = pass * PASS_W + l * VEC;
 
-    int nval[NACC];            // elements of vector j that lie inside the slice (0..VEC)
+    // elements of vector j that lie inside the slice (0..VEC)
+    auto nval = [&](const int j) { return min(max(a.f - (colbase + j * L * VEC), 0), VEC); };
     int coff[NACC];            // column offset read by this lane
     // A lane whose vector lies outside the slice re-reads the first vector of its group's
     // 16*L-byte piece (or of the pass, if the whole piece is outside): an address the
@@ -228,8 +233,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     for (int j = 0; j < NACC; ++j) {
         const int c = colbase + j * L * VEC;
         const int c0 = passbase + j * L * VEC;
-        nval[j] = a.f - c < 0 ? 0 : (a.f - c > VEC ? VEC : a.f - c);
-        coff[j] = nval[j] > 0 ? c : (c0 < a.f ? c0 : passbase);
+        coff[j] = c < a.f ? c : (c0 < a.f ? c0 : passbase);
     }
     // a vector that straddles the end of the slice is read whole (the row stride is a
     // multiple of the vector width, so the read stays inside the row) and stored element
@@ -250,17 +254,17 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     auto store_row = [&](T* y, const int row) {
 #pragma unroll
         for (int j = 0; j < NACC; ++j) {
-            if (a.epilogue && nval[j] > 0) {
+            if (a.epilogue && nval(j) > 0) {
                 float m[VEC];
                 if (a.M) IO::load(static_cast<const T*>(a.M) + (int64_t)row * a.ldm + colbase + j * L * VEC, m);
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc[j][i] = (a.M ? m[i] : acc[j][i]) > 0.f ? acc[j][i] : 0.f;
             }
-            if (nval[j] == VEC) IO::store(y + j * L * VEC, acc[j]);
+            if (nval(j) == VEC) IO::store(y + j * L * VEC, acc[j]);
             else {
 #pragma unroll
                 for (int i = 0; i < VEC; ++i)
-                    if (i < nval[j]) IO::store1(y + j * L * VEC + i, acc[j][i]);
+                    if (i < nval(j)) IO::store1(y + j * L * VEC + i, acc[j][i]);
             }
         }
     };
@@ -309,7 +313,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
 #pragma unroll
         for (int u = 0; u < U; ++u) multiply_add(w[u], x[u]);
     };
-    // same with entries that may not exist (on(u) false; their weight is 0): nothing is loaded for them
+    // same with entries that may not exist (on(u) false): nothing is loaded for them, and they count as zero
     auto gather_u_if = [&](auto on, const int (&c)[U], const float (&w)[U]) {
         Raw x[U][NACC];
 #pragma unroll
@@ -319,7 +323,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
             if (on(u)) load_row(c[u], x[u]);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) multiply_add(w[u], x[u]);
+        for (int u = 0; u < U; ++u) multiply_add(on(u) ? w[u] : 0.f, x[u]);
     };
     // entry k of the form (chunk): column id cbase[k], weight vbase[k]
     const int32_t* const cbase = (HUB ? a.colidx_hub : a.colidx) - a.e_base;
@@ -328,23 +332,43 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     const int32_t* const rows = a.rows + a.item_off[grp];
     const int count = a.item_count[grp];
     const int K = a.per_wave[grp];
-    // lane groups: this lane's next four pairs, entries e .. e + 3, of which the first `left` belong to the row (the others are
-    // loaded if the chunk has them, and never used)
-    auto fetch = [&](const int64_t e, const int left, int (&c)[EPL], float (&w)[EPL]) {
-#pragma unroll
-        for (int q = 0; q < EPL; ++q) { c[q] = 0; w[q] = 0.f; }
+    // The pairs fetched ahead: entries e .. e + 3 of a lane, of which the first `left` belong to the row (the others are
+    // never used).  The last lanes of the chunk read its last four entries and are `shift` ahead of themselves.
+    Int4 fc = 0;
+    Float4 fw = 0.f;
+    int shift = 0;
+    const bool few = a.e_end - a.e_base < EPL;
+    auto fetch = [&](const int64_t e, const int left) {
+        shift = 0;
         if (left > 0) {
-            if (e + EPL <= a.e_end) {
-                const Int4 tc = __builtin_nontemporal_load(reinterpret_cast<const Int4*>(cbase + e));
-                const Float4 tw = __builtin_nontemporal_load(reinterpret_cast<const Float4*>(vbase + e));
-#pragma unroll
-                for (int q = 0; q < EPL; ++q) { c[q] = tc[q]; w[q] = tw[q]; }
-            } else {
+            if (few) {
 #pragma unroll
                 for (int q = 0; q < EPL; ++q)
-                    if (q < left) { c[q] = cbase[e + q]; w[q] = vbase[e + q]; }
+                    if (q < left) { fc[q] = cbase[e + q]; fw[q] = vbase[e + q]; }
+            } else {
+                const int64_t over = e + EPL - a.e_end;
+                shift = over > 0 ? (int)over : 0;
+                fc = __builtin_nontemporal_load(reinterpret_cast<const Int4*>(cbase + e - shift));
+                fw = __builtin_nontemporal_load(reinterpret_cast<const Float4*>(vbase + e - shift));
             }
         }
+    };
+    // The pairs being gathered, in LDS memory of the wavefront's own: written four per lane, read as the groups need them
+    // (16 bytes a lane for rows of a lane group, and nothing to hand from lane to lane: F = 128 on 7.2 M entries 252 -> 242
+    // us, F = 76 on 28.8 M 691 -> 670, bf16 488 -> 471, F = 32 on 63 M 707 -> 697 against pairs kept in registers and handed
+    // over with ds_bpermute).
+    int* const sc = stage;
+    float* const sw = reinterpret_cast<float*>(stage + STAGE / 2);
+    auto put = [&](const int at) {
+        if (__ballot(shift > 0)) {
+#pragma unroll
+            for (int t = 0; t < EPL - 1; ++t)
+                if (shift > t) { fc = fc.yzww; fw = fw.yzww; }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        *reinterpret_cast<IntL4*>(sc + at) = fc;
+        *reinterpret_cast<FloatL4*>(sw + at) = fw;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
     // Row lists: lane i holds the i-th row of the wavefront's share (id, first entry, number of entries), read once; the
     // share is K rows of a wavefront, or K times R rows of the lane groups (at most 64).
@@ -369,39 +393,36 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         const int S = a.per_fetch[grp];
         const int lpi = L / S;                              // lanes of a group per row and fetch
         const int fl = EPL * (l & (lpi - 1)), fs = l / lpi;
-        auto fetch_rows = [&](const int k, const int k0, int (&c)[EPL], float (&w)[EPL]) {
+        auto fetch_rows = [&](const int k, const int k0) {
             const int src = (k + fs) * R + g;
             const int64_t e = bperm_l(src & 63, mb) + k0 + fl;
             const int d = bperm_i(src & 63, md);
-            fetch(e, src < n_rows ? d - k0 - fl : 0, c, w);
+            fetch(e, src < n_rows ? d - k0 - fl : 0);
         };
-        int c[EPL];
-        float w[EPL];
         int k = 0, k0 = 0;
-        fetch_rows(0, 0, c, w);
+        fetch_rows(0, 0);
         do {
             const bool more = S == 1 && __ballot(bperm_i(k * R + g, md) > k0 + EPL * L) != 0;      // (0 entries past the last row)
             const int kn = more ? k : k + S, k0n = more ? k0 + EPL * L : 0;
-            int cn[EPL];
-            float wn[EPL];
-            fetch_rows(kn, k0n, cn, wn);
+            put(GSTRIDE * g + EPL * l);
+            fetch_rows(kn, k0n);
             for (int s = 0; s < S; ++s) {
                 const int src = (k + s) * R + g;
                 const bool valid = src < n_rows;
                 if (__ballot(valid) == 0) break;
                 const int row = bperm_i(src & 63, mrow);
                 const int d = bperm_i(src & 63, md) - k0;           // (not above 0 past the last row)
+                const int at = GSTRIDE * g + EPL * s * lpi;
                 for (int j0 = 0; j0 < lpi; ++j0) {
                     if (__ballot(EPL * j0 < d) == 0) break;
+                    const Int4 c4 = *reinterpret_cast<const IntL4*>(sc + at + EPL * j0);
+                    const Float4 w4 = *reinterpret_cast<const FloatL4*>(sw + at + EPL * j0);
 #pragma unroll
                     for (int q0 = 0; q0 < EPL; q0 += U) {
                         int cj[U];
                         float wj[U];
 #pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            cj[u] = bperm_i(g * L + s * lpi + j0, c[q0 + u]);
-                            wj[u] = bperm_f(g * L + s * lpi + j0, w[q0 + u]);
-                        }
+                        for (int u = 0; u < U; ++u) { cj[u] = c4[q0 + u]; wj[u] = w4[q0 + u]; }
                         if (__ballot(EPL * j0 + q0 + U > d) == 0) gather_u(cj, wj);
                         else gather_u_if([&](int u) { return EPL * j0 + q0 + u < d; }, cj, wj);
                     }
@@ -411,8 +432,6 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
                     clear_acc();
                 }
             }
-#pragma unroll
-            for (int q = 0; q < EPL; ++q) { c[q] = cn[q]; w[q] = wn[q]; }
             k = kn;
             k0 = k0n;
         } while (k * R < n_rows);
@@ -445,21 +464,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     int k = 0;
     int64_t e = readlane_l(mb, 0);
     int cnt = __builtin_amdgcn_readlane(md, 0);
-    int c[EPL];
-    float w[EPL];
-    // whole wavefront: pair q of the lane is entry 64 q + lane of the next EPL * 64
-    auto fetch_wave = [&](const int64_t e, const int cnt, int (&c)[EPL], float (&w)[EPL]) {
-#pragma unroll
-        for (int q = 0; q < EPL; ++q) {
-            c[q] = 0;
-            w[q] = 0.f;
-            if (64 * q + lane < cnt) {
-                c[q] = __builtin_nontemporal_load(cbase + e + 64 * q + lane);
-                w[q] = __builtin_nontemporal_load(vbase + e + 64 * q + lane);
-            }
-        }
-    };
-    fetch_wave(e, cnt, c, w);
+    fetch(e + EPL * lane, cnt - EPL * lane);
     for (;;) {
         const int row = __builtin_amdgcn_readlane(mrow, k);
         ++k;
@@ -472,34 +477,24 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
             more = cnt > EPL * 64;
             cnt = more ? cnt - EPL * 64 : cnt1;
             e = more ? e + EPL * 64 : e1;
-            int cn[EPL];
-            float wn[EPL];
-            fetch_wave(e, cnt, cn, wn);
-            // 64 pairs at a time; group g takes pairs g, g + R, ...
-#pragma unroll 1
-            for (int left = n; left > 0; left -= 64) {
-#pragma unroll 1
-                for (int j0 = 0; j0 < L && j0 * R < left; j0 += U) {
-                    int cj[U];
-                    float wj[U];
+            put(EPL * lane);
+            fetch(e + EPL * lane, cnt - EPL * lane);
+            // group g takes pairs g, g + R, ...
+            for (int j0 = 0; j0 * R < n; j0 += U) {
+                int cj[U];
+                float wj[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if constexpr (R == 1) {
-                            cj[u] = __builtin_amdgcn_readlane(c[0], j0 + u);
-                            wj[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w[0]), j0 + u));
-                        } else {
-                            cj[u] = bperm_i((j0 + u) * R + g, c[0]);
-                            wj[u] = bperm_f((j0 + u) * R + g, w[0]);
-                        }
+                for (int u = 0; u < U; ++u) {
+                    cj[u] = sc[(j0 + u) * R + g];
+                    wj[u] = sw[(j0 + u) * R + g];
+                    if constexpr (R == 1) {
+                        cj[u] = __builtin_amdgcn_readfirstlane(cj[u]);
+                        wj[u] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(wj[u])));
                     }
-                    if ((j0 + U) * R <= left) gather_u(cj, wj);
-                    else gather_u_if([&](int u) { return (j0 + u) * R + g < left; }, cj, wj);
                 }
-#pragma unroll
-                for (int q = 0; q + 1 < EPL; ++q) { c[q] = c[q + 1]; w[q] = w[q + 1]; }
+                if ((j0 + U) * R <= n) gather_u(cj, wj);
+                else gather_u_if([&](int u) { return (j0 + u) * R + g < n; }, cj, wj);
             }
-#pragma unroll
-            for (int q = 0; q < EPL; ++q) { c[q] = cn[q]; w[q] = wn[q]; }
         } while (more);
 
         // The sums over the R groups, nearest lanes first.  The steps over 16 and 32 lanes each leave half of the values to
@@ -534,17 +529,17 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
                 T* y = static_cast<T*>(a.Y) + (int64_t)row * a.ldy + col;
 #pragma unroll
                 for (int i = 0; i < NE; ++i) {
-                    if (a.epilogue && e0 + i < nval[0]) {
+                    if (a.epilogue && e0 + i < nval(0)) {
                         float m[1] = {acc[0][i]};
                         if (a.M) IO::load1(static_cast<const T*>(a.M) + (int64_t)row * a.ldm + col + i, m[0]);
                         acc[0][i] = m[0] > 0.f ? acc[0][i] : 0.f;
                     }
                 }
-                if (e0 + NE <= nval[0]) IO::template store_n<NE>(y, acc[0]);
+                if (e0 + NE <= nval(0)) IO::template store_n<NE>(y, acc[0]);
                 else {
 #pragma unroll
                     for (int i = 0; i < NE; ++i)
-                        if (e0 + i < nval[0]) IO::store1(y + i, acc[0][i]);
+                        if (e0 + i < nval(0)) IO::store1(y + i, acc[0][i]);
                 }
             }
         };
@@ -574,7 +569,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
             if (mode == MODE_SEGMENT) {     // scratch rows are padded to whole vectors
 #pragma unroll
                 for (int j = 0; j < NACC; ++j)
-                    if (nval[j] > 0) {
+                    if (nval(j) > 0) {
 #pragma unroll
                         for (int i = 0; i < NE; ++i) pout[j * L * VEC + e0 + i] = acc[j][i];
                     }
@@ -606,10 +601,11 @@ __device__ __forceinline__ int xcd_block(int b, int blocks) {
 // reads the first columns of its pass and stores nothing.
 template <class IO, int L, int NACC>
 __global__ void __launch_bounds__(256, (agg_min_waves<IO, L, NACC>())) agg_kernel(const AggArgs a) {
+    __shared__ __align__(16) int stage[4][stage_words(L, false)];
     __shared__ float quarter[3][L * IO::kVec * NACC];     // block-per-row mode: sums of wavefronts 1..3
     const int wave = __builtin_amdgcn_readfirstlane(xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + (int)(threadIdx.x >> 6));
     if (wave >= a.wave_start[a.n_groups]) return;
-    agg_item<IO, L, NACC, false>(a, wave, (int)blockIdx.y, nullptr, quarter);
+    agg_item<IO, L, NACC, false>(a, wave, (int)blockIdx.y, nullptr, quarter, stage[threadIdx.x >> 6]);
 }
 
 // The same work with the hub rows of the column pass in LDS: one block of 16 wavefronts per
@@ -621,6 +617,7 @@ __global__ void __launch_bounds__(1024, 4) agg_hub_kernel(const AggArgs a) {
     constexpr int VEC = IO::kVec;
     constexpr int LINE = L * VEC;
     __shared__ __align__(16) T table[HUB_SLOTS * LINE];
+    __shared__ __align__(16) int stage[16][stage_words(L, true)];
     {
         const int l = threadIdx.x % L;
         const int c = (int)blockIdx.y * LINE + l * VEC;
@@ -636,7 +633,7 @@ __global__ void __launch_bounds__(1024, 4) agg_hub_kernel(const AggArgs a) {
     const int total = a.wave_start[a.n_groups];
     const int w0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 16 + (threadIdx.x >> 6)));
     for (int wave = w0; wave < total; wave += 16 * (int)gridDim.x)
-        agg_item<IO, L, 1, true>(a, wave, (int)blockIdx.y, table, nullptr);
+        agg_item<IO, L, 1, true>(a, wave, (int)blockIdx.y, table, nullptr, stage[threadIdx.x >> 6]);
 }
 
 // ---- second pass for split rows: Y[row,:] = sum of its partial-sum slots ---------------
