@@ -147,11 +147,13 @@ struct RowStage {
             if constexpr (MASK) load_words<VB>(mA + off, x.m[j]);
         }
     }
-    // into LDS; elements beyond the row become zero
+    // into LDS, ordered after the reads of the step before and before the reads of this one; elements beyond the row
+    // become zero
     static __device__ __forceinline__ void stage(const StripArgs& g, Raw& x, int s, char* own, int lane) {
         const int vec = lane % LPR, row0 = lane / LPR;
         const bool tail = (s + 1) * KS > g.K;
         const int over = s * KS + vec * E + E - g.K;           // elements of this lane's vector beyond the row
+        lane_exchange_fence();
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int row = row0 + j * (VB / 2);
@@ -160,6 +162,7 @@ struct RowStage {
             const int byte = vec * VB;
             store_words<VB>(own + row * 128 + (((byte / 16) ^ (row & 7)) * 16 + byte % 16), x.a[j]);
         }
+        lane_exchange_fence();
     }
     // the pieces of this lane's eight elements of matrix step c
     static __device__ __forceinline__ void read(const char* own, int c, int lane, uint4 (&piece)[Pieces<T>::n]) {
@@ -435,7 +438,8 @@ __global__ void __launch_bounds__(512) strip_split_kernel(const StripArgs g) {
             mfma_pieces<1, 1, NP, NP>(a, b, acc);
         }
     }
-    // the sums of the wavefronts: element e of lane l at own[e * 64 + l]
+    // the sums of the wavefronts: element e of lane l at own[e * 64 + l], where other lanes have read their last step
+    lane_exchange_fence();
     float* mine = reinterpret_cast<float*>(own);
 #pragma unroll
     for (int e = 0; e < 16; ++e) mine[e * 64 + lane] = acc[0][0][e];

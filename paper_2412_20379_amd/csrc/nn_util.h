@@ -11,6 +11,11 @@ namespace ntp {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// Orders the LDS accesses of a wavefront whose lanes read what other lanes wrote.  The hardware keeps a wavefront's LDS
+// accesses in order; the compiler, which sees one lane's addresses and types, would be free to move them past each other.
+// No instruction comes of it.
+__device__ __forceinline__ void lane_exchange_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // pieces an element of type T is cut into for the bf16 matrix instructions
 template <class T> struct Pieces { static constexpr int n = 3; };
 template <> struct Pieces<unsigned short> { static constexpr int n = 1; };
