@@ -15,6 +15,8 @@
 // behind barriers, which this replaces (169,343 rows, fp32, without / with the ReLU mask): 256 x 256 0.147 / 0.185 -> 0.139 /
 // 0.161 ms, 128 x 256 0.085 / 0.108 -> 0.074 / 0.097, 256 x 64 0.065 / 0.149 -> 0.044 / 0.052, 256 x 40 0.061 / 0.132 -> 0.042 /
 // 0.046; 58,241 rows of 128 x 64 0.037 / 0.070 -> 0.020 / 0.023.
+// m <= 32 runs on the fp32 matrix instructions (the rule is in nn_kernels.hip), which bound it as much as memory does:
+// 256 x 16 0.042 ms against 0.037 with pieces and 0.044 in the fp32 tiles replaced (masked 0.042 / 0.040 / 0.050).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -46,9 +48,9 @@ __device__ __forceinline__ void load_vec(const T* p, T (&v)[VEC]) {
     __builtin_memcpy(v, p, sizeof(T) * VEC);
 }
 
-// the pieces of eight rows of one column block
-template <class T>
-__device__ __forceinline__ void cut_rows(const T (&x)[8], uint4 (&piece)[Pieces<T>::n]) {
+// the parts of eight rows of one column block
+template <class T, Core C>
+__device__ __forceinline__ void cut_rows(const T (&x)[8], uint4 (&piece)[Parts<T, C>::n]) {
     if constexpr (sizeof(T) == 2) {
         unsigned w[4];
 #pragma unroll
@@ -58,16 +60,16 @@ __device__ __forceinline__ void cut_rows(const T (&x)[8], uint4 (&piece)[Pieces<
         unsigned w[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) w[e] = __float_as_uint(x[e]);
-        cut_row8<T>(w, piece);
+        cut_row8<T, C>(w, piece);
     }
 }
 
 // A wavefront owns 64 columns of A x 32 * TN columns of dZ; the block's eight wavefronts are g.kt x g.mt such tiles x
 // row shares.
-template <class T, bool MASK, int VA, int VB, int TA, int TN>
+template <class T, Core C, bool MASK, int VA, int VB, int TA, int TN>
 __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     constexpr bool RING = TA * TN <= 4;        // two steps in flight (else one: the accumulators take the registers)
-    constexpr int NP = Pieces<T>::n;
+    constexpr int NP = Parts<T, C>::n;
     extern __shared__ float lds[];             // sums of the row shares
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -126,7 +128,7 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
         }
     };
     // multiply the rows held in x; left < 16: the rows from the left-th on count as zero.  A non-negative
-    // next is the row whose step x is refilled with (a whole one) before the matrix instructions.
+    // next is the row whose step x is refilled with (a whole one).
     auto use = [&](Raw& x, int left, int64_t next, auto whole) {
         constexpr bool WHOLE = decltype(whole)::value;
         uint4 pb[TN][NP];
@@ -139,7 +141,7 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
                 if constexpr (MASK) y[e] = elem_to_f32(x.mk[e][j / VB][j % VB]) > 0.f ? y[e] : (T)0;
                 if constexpr (!WHOLE) y[e] = 2 * e + h < left ? y[e] : (T)0;
             }
-            cut_rows<T>(y, pb[j]);
+            cut_rows<T, C>(y, pb[j]);
         }
         auto cut_a = [&](int i, uint4 (&pa)[NP]) {
             T y[8];
@@ -148,16 +150,21 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
                 y[e] = x.a[e][i / VA][i % VA];
                 if constexpr (!WHOLE) y[e] = 2 * e + h < left ? y[e] : (T)0;
             }
-            cut_rows<T>(y, pa);
+            cut_rows<T, C>(y, pa);
         };
         if constexpr (RING) {
             uint4 pa[TA][NP];
 #pragma unroll
             for (int i = 0; i < TA; ++i) cut_a(i, pa[i]);
-            if constexpr (WHOLE) {
+            // pieces leave x free before they are multiplied; floats are multiplied where they were loaded to (602 x 16 on
+            // 58,241 rows: 62.2 us, refilled before 64.4)
+            if constexpr (WHOLE && C == CORE_BF16) {
                 if (next + 16 <= r1) fetch(x, next, whole);
             }
-            mfma_pieces<TA, TN, NP, NP>(pa, pb, acc);
+            mfma_parts<C, TA, TN, NP>(pa, pb, acc);
+            if constexpr (WHOLE && C == CORE_F32) {
+                if (next + 16 <= r1) fetch(x, next, whole);
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < TA; ++i) {
@@ -166,7 +173,7 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
                 if constexpr (WHOLE) {
                     if (i == TA - 1 && next + 16 <= r1) fetch(x, next, whole);
                 }
-                mfma_pieces<1, TN, NP, NP>(pa, pb, reinterpret_cast<f32x16 (&)[1][TN]>(acc[i]));
+                mfma_parts<C, 1, TN, NP>(pa, pb, reinterpret_cast<f32x16 (&)[1][TN]>(acc[i]));
             }
         }
     };
@@ -236,10 +243,10 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     }
 }
 
-template <class T, bool MASK, int VA, int VB, int TA, int TN>
+template <class T, Core C, bool MASK, int VA, int VB, int TA, int TN>
 void launch_dw(const DwArgs& g, hipStream_t st) {
     constexpr int lds = 4 * TA * TN * 16 * 64 * 4;          // the upper half of the wavefronts' sums
-    auto kernel = dw_kernel<T, MASK, VA, VB, TA, TN>;
+    auto kernel = dw_kernel<T, C, MASK, VA, VB, TA, TN>;
     static bool allowed[64] = {};
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -256,20 +263,24 @@ int pow2_up(int64_t x, int most) {
 }
 
 // The shape of a wavefront tile and how the work is cut.
-//   m <= 32: 128 x 32;  k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);  else 128 x 64, whose operands
+//   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
+//   against 39.1 us);  k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);  else 128 x 64, whose operands
 //   are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343 rows 0.134 against 0.164 ms.
 // Blocks: about one per compute unit; two column tiles side by side where there are two (they share the rows of A through the
 // L1), the other wavefronts share out the rows.
-enum { DW_NARROW = 0, DW_SHORT = 1, DW_WIDE = 2 };
-int dw_shape(int64_t k, int64_t m) { return m <= 32 ? DW_NARROW : (k <= 64 ? DW_SHORT : DW_WIDE); }
+enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY };
+int dw_shape(int64_t k, int64_t m, bool fp32_core) {
+    if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
+    return fp32_core && k <= 32 ? DW_TINY : DW_NARROW;
+}
 
-DwArgs dw_plan(int64_t n, int64_t k, int64_t m) {
+DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core) {
     DwArgs g{};
     g.n = n; g.k = (int)k; g.m = (int)m;
-    const int shape = dw_shape(k, m);
-    const int ta = shape == DW_SHORT ? 2 : 4, tn = shape == DW_NARROW ? 1 : 2;
+    const int shape = dw_shape(k, m, fp32_core);
+    const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
     g.kt = shape == DW_NARROW && n <= 50000 ? pow2_up((k + 127) / 128, 4) : 1;        // short contraction: few rows per wavefront
-    g.mt = shape == DW_NARROW ? 1 : pow2_up((m + 63) / 64, shape == DW_SHORT ? 4 : 2);
+    g.mt = tn == 1 ? 1 : pow2_up((m + 63) / 64, shape == DW_SHORT ? 4 : 2);
     g.tiles_k = (int)((k + 32 * ta * g.kt - 1) / (32 * ta * g.kt));
     g.tiles_m = (int)((m + 32 * tn * g.mt - 1) / (32 * tn * g.mt));
     const int64_t shares = 8 / (g.kt * g.mt), tiles = (int64_t)g.tiles_k * g.tiles_m;
@@ -280,12 +291,15 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m) {
     return g;
 }
 
-template <class T>
+template <class T, Core C>
 void launch_dw_any(const DwArgs& g, hipStream_t st) {
-    switch (dw_shape(g.k, g.m)) {
-        case DW_NARROW: g.mask ? launch_dw<T, true, 4, 1, 4, 1>(g, st) : launch_dw<T, false, 4, 1, 4, 1>(g, st); break;
-        case DW_SHORT: g.mask ? launch_dw<T, true, 2, 2, 2, 2>(g, st) : launch_dw<T, false, 2, 2, 2, 2>(g, st); break;
-        default: g.mask ? launch_dw<T, true, 4, 2, 4, 2>(g, st) : launch_dw<T, false, 4, 2, 4, 2>(g, st); break;
+    switch (dw_shape(g.k, g.m, C == CORE_F32)) {
+        case DW_TINY:
+            if constexpr (C == CORE_F32) g.mask ? launch_dw<T, C, true, 1, 1, 1, 1>(g, st) : launch_dw<T, C, false, 1, 1, 1, 1>(g, st);
+            break;
+        case DW_NARROW: g.mask ? launch_dw<T, C, true, 4, 1, 4, 1>(g, st) : launch_dw<T, C, false, 4, 1, 4, 1>(g, st); break;
+        case DW_SHORT: g.mask ? launch_dw<T, C, true, 2, 2, 2, 2>(g, st) : launch_dw<T, C, false, 2, 2, 2, 2>(g, st); break;
+        default: g.mask ? launch_dw<T, C, true, 4, 2, 4, 2>(g, st) : launch_dw<T, C, false, 4, 2, 4, 2>(g, st); break;
     }
 }
 
@@ -294,14 +308,17 @@ void launch_dw_any(const DwArgs& g, hipStream_t st) {
 // every product whose A has a whole vector of four columns
 bool nn_dw_direct(int64_t n, int64_t k, int64_t) { return n > 0 && k >= 4; }
 
-int nn_dw_direct_splits(int64_t n, int64_t k, int64_t m) { return dw_plan(n, k, m).n_splits; }
+int nn_dw_direct_splits(int64_t n, int64_t k, int64_t m, bool fp32_core) { return dw_plan(n, k, m, fp32_core).n_splits; }
 
-// partial sums of every range of vertices to out [splits][k x m]
+// partial sums of every range of vertices to out [splits][k x m]; fp32_core: fp32 operands on the fp32 matrix instructions
 int launch_nn_dw_direct(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m,
-                        int dtype, void* stream) {
-    DwArgs g = dw_plan(n, k, m);
+                        int dtype, bool fp32_core, void* stream) {
+    DwArgs g = dw_plan(n, k, m, fp32_core);
     g.A = A; g.Z = dH; g.mask = mask; g.out = out;
-    dtype == NTP_BF16 ? launch_dw_any<unsigned short>(g, (hipStream_t)stream) : launch_dw_any<float>(g, (hipStream_t)stream);
+    const hipStream_t st = (hipStream_t)stream;
+    if (dtype == NTP_BF16) launch_dw_any<unsigned short, CORE_BF16>(g, st);
+    else if (fp32_core) launch_dw_any<float, CORE_F32>(g, st);
+    else launch_dw_any<float, CORE_BF16>(g, st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("transform kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
     return NTP_OK;

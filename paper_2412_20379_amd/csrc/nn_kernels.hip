@@ -5,8 +5,10 @@
 // bf16 pieces hi + mid + lo = x (exact: 3 x 8 significant bits, by truncation), and a product a*b is formed as the
 // six piece products of weight >= 2^-16 (hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi), each exact in the fp32
 // accumulator's input; the dropped pieces are below 2^-23 |a b|.  Six bf16 instructions cost 6 x 32 cycles per 32x32x16
-// block against 8 x 64 for fp32, and operands that are bf16 in memory need one piece only.  H and dA: nn_strip_kernels.hip;
-// dW: nn_dw_kernels.hip, partial sums to the caller's workspace, added in order here (deterministic, no atomics).
+// block against 8 x 64 for fp32, and operands that are bf16 in memory need one piece only.  fp32 products with a
+// contraction below 64 or an output of up to 32 columns run on the fp32 instructions (fp32_core below).  H and dA:
+// nn_strip_kernels.hip; dW: nn_dw_kernels.hip, partial sums to the caller's workspace, added in order here (deterministic,
+// no atomics).
 //
 // This file holds the dispatch and the plain fp32 form (v_mfma_f32_32x32x2_f32), which NTP_NN_CORE=fp32 selects for
 // comparison and which computes dW of matrices of fewer than four columns.  A block of 256 threads (4 wavefronts)
@@ -308,6 +310,15 @@ bool use_split_core() {
     return v;
 }
 
+// Are the products of an output of `cols` columns and a contraction of length k formed on the fp32 instructions?
+//   Contractions below 64: the cut's six of nine piece products lose up to 2^-21 |a b| of each product, which a sum of
+//   few terms shows (largest error over the sum of magnitudes at k = 1 4.2e-7 against 6.0e-8, at k = 4 3.0e-7 against
+//   1.7e-7; from k = 16 on the rounding of the sum is larger than either).
+//   Outputs of up to 32 columns: bound by reading A for the most part, so the exact products cost little (256 -> 16 on
+//   169,343 rows 33.6 -> 35.2 us, dW 256 x 16 37.5 -> 42.5).
+// In both an infinite operand gives an infinite result, where the cut gives inf - inf.
+bool fp32_core(int64_t k, int64_t cols) { return k < 64 || cols <= 32 || !use_split_core(); }
+
 template <class TA, class TB, class TC, bool AK, bool BKC, bool MA, bool MB, int BM, int BN, int WM, int WN>
 void launch_tiles(GemmArgs g, int n_splits, hipStream_t st) {
     g.tiles_m = (int)((g.Mdim + BM - 1) / BM);
@@ -373,7 +384,7 @@ template <class T> constexpr int DTYPE = sizeof(T) == 2 ? NTP_BF16 : NTP_F32;
 
 template <class T>
 int nn_fwd_t(const void* A, const void* W, void* H, int64_t n, int64_t k, int64_t m, int act, hipStream_t st) {
-    if (use_split_core()) return launch_nn_strip(A, nullptr, W, H, n, k, m, k, m, m, false, act == NTP_ACT_RELU, DTYPE<T>, st);
+    if (use_split_core()) return launch_nn_strip(A, nullptr, W, H, n, k, m, k, m, m, false, act == NTP_ACT_RELU, DTYPE<T>, fp32_core(k, m), st);
     GemmArgs g{};
     g.A = A; g.B = W; g.C = H;
     g.lda = k; g.ldb = m; g.ldc = m;
@@ -391,7 +402,7 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
     if (dA && n > 0) {
         // dA[n x k] = dZ[n x m] * W^T : contraction over m; W is read as (kk=m, j=k) = W[j*m + kk]
         if (use_split_core()) {
-            rc = launch_nn_strip(dH, relu ? H : nullptr, W, dA, n, m, k, m, m, k, true, false, DTYPE<T>, st);
+            rc = launch_nn_strip(dH, relu ? H : nullptr, W, dA, n, m, k, m, m, k, true, false, DTYPE<T>, fp32_core(m, k), st);
         } else {
         GemmArgs g{};
         g.A = dH; g.maskA = H; g.B = W; g.C = dA;
@@ -406,8 +417,9 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
     if (!dW) return NTP_OK;
     // dW[k x m] = A^T[k x n] * dZ[n x m] : contraction over the vertices, split over blocks
     if (use_split_core() && nn_dw_direct(n, k, m)) {
-        const int splits = nn_dw_direct_splits(n, k, m);
-        rc = launch_nn_dw_direct(A, dH, relu ? H : nullptr, splits > 1 ? (float*)ws : dW, n, k, m, DTYPE<T>, st);
+        const bool f32 = DTYPE<T> == NTP_F32 && fp32_core(n, m);
+        const int splits = nn_dw_direct_splits(n, k, m, f32);
+        rc = launch_nn_dw_direct(A, dH, relu ? H : nullptr, splits > 1 ? (float*)ws : dW, n, k, m, DTYPE<T>, f32, st);
         return rc != NTP_OK ? rc : sum_splits(ws, dW, k * m, splits, st);
     }
     const int S = dw_splits(n, k, m);
@@ -429,7 +441,7 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
 
 int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m) {
     int S = dw_splits(n, k, m);
-    if (nn_dw_direct(n, k, m)) S = std::max(S, nn_dw_direct_splits(n, k, m));
+    if (nn_dw_direct(n, k, m)) S = std::max({S, nn_dw_direct_splits(n, k, m, false), nn_dw_direct_splits(n, k, m, true)});
     return S > 1 ? (int64_t)S * k * m * 4 : 0;
 }
 

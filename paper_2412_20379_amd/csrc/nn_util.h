@@ -16,9 +16,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // No instruction comes of it.
 __device__ __forceinline__ void lane_exchange_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-// pieces an element of type T is cut into for the bf16 matrix instructions
-template <class T> struct Pieces { static constexpr int n = 3; };
-template <> struct Pieces<unsigned short> { static constexpr int n = 1; };
+// How products are formed.  CORE_BF16: on the bf16 matrix instructions, an fp32 operand cut into three bf16 pieces (a bf16
+// operand is one).  CORE_F32 (fp32 operands only): on the fp32 matrix instructions, whose products are exact and pass
+// infinities on.
+enum Core { CORE_BF16, CORE_F32 };
+
+// 16-byte parts in which a lane holds eight consecutive contraction indices of an operand: pieces, or four floats each
+template <class T, Core C> struct Parts { static constexpr int n = C == CORE_F32 ? 2 : 3; };
+template <> struct Parts<unsigned short, CORE_BF16> { static constexpr int n = 1; };
 
 // x = sum of NP bf16 values, each returned as an fp32 bit pattern whose low half is zero
 // (NP = 1: x is a bf16 value already)
@@ -66,11 +71,14 @@ __device__ __forceinline__ void zero_row8_from(unsigned (&w)[Row8<T>::words], in
         for (int e = 0; e < 4; ++e) w[e] = 2 * e + 1 < left ? w[e] : (2 * e < left ? w[e] & 0xffffu : 0u);
     }
 }
-// the bf16 pieces of the eight elements, each as the four dwords of a matrix operand
-template <class T>
-__device__ __forceinline__ void cut_row8(const unsigned (&w)[Row8<T>::words], uint4 (&piece)[Pieces<T>::n]) {
+// the parts of the eight elements (bf16 pieces: each the four dwords of a matrix operand)
+template <class T, Core C>
+__device__ __forceinline__ void cut_row8(const unsigned (&w)[Row8<T>::words], uint4 (&piece)[Parts<T, C>::n]) {
     if constexpr (sizeof(T) == 2) {
         piece[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    } else if constexpr (C == CORE_F32) {
+        piece[0] = make_uint4(w[0], w[1], w[2], w[3]);
+        piece[1] = make_uint4(w[4], w[5], w[6], w[7]);
     } else {
         unsigned x[8][3];
 #pragma unroll
@@ -82,23 +90,38 @@ __device__ __forceinline__ void cut_row8(const unsigned (&w)[Row8<T>::words], ui
     }
 }
 
-// acc[i][j] += a[i] b[j] for TM x TN blocks of 32x32x16 from the pieces of both operands: piece
-// products of weight 2^-8w, small ones first; consecutive instructions go to different accumulators
-template <int TM, int TN, int NPA, int NPB>
-__device__ __forceinline__ void mfma_pieces(const uint4 (&a)[TM][NPA], const uint4 (&b)[TN][NPB], f32x16 (&acc)[TM][TN]) {
+// acc[i][j] += a[i] b[j] for TM x TN blocks of 32x32x16 from the parts of both operands; consecutive instructions go to
+// different accumulators.
+// CORE_F32: v_mfma_f32_32x32x2_f32 takes one float per lane, contraction index lane / 32.  Its eight steps use the lane's
+// eight elements in order, i.e. the indices t and 8 + t of the block in step t: the same ones for both operands.
+// CORE_BF16: piece products of weight 2^-8w, small ones first.
+template <Core C, int TM, int TN, int NP>
+__device__ __forceinline__ void mfma_parts(const uint4 (&a)[TM][NP], const uint4 (&b)[TN][NP], f32x16 (&acc)[TM][TN]) {
+    if constexpr (C == CORE_F32) {
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-    for (int w = 2; w >= 0; --w)
-#pragma unroll
-        for (int pa = 0; pa <= w; ++pa)
+        for (int t = 0; t < 8; ++t)
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int pb = w - pa;
-                    if (pa < NPA && pb < NPB)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            __builtin_bit_cast(bf16x8, a[i][pa < NPA ? pa : 0]), __builtin_bit_cast(bf16x8, b[j][pb < NPB ? pb : 0]), acc[i][j], 0, 0, 0);
-                }
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, a[i][t / 4])[t % 4],
+                                                                     __builtin_bit_cast(f32x4, b[j][t / 4])[t % 4], acc[i][j], 0, 0, 0);
+    } else {
+#pragma unroll
+        for (int w = 2; w >= 0; --w)
+#pragma unroll
+            for (int pa = 0; pa <= w; ++pa)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const int pb = w - pa;
+                        if (pa < NP && pb < NP)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                __builtin_bit_cast(bf16x8, a[i][pa < NP ? pa : 0]), __builtin_bit_cast(bf16x8, b[j][pb < NP ? pb : 0]), acc[i][j], 0, 0, 0);
+                    }
+    }
 }
 
 }  // namespace ntp

@@ -289,12 +289,12 @@ int launch_nn_bwd(const void* A, const void* W, const void* H, const void* dH, v
 int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m);
 // C = act(A' B) with B resident in LDS (nn_strip_kernels.hip)
 int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int64_t n, int64_t K, int64_t N, int64_t lda,
-                    int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, void* stream);
+                    int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, bool fp32_core, void* stream);
 // dW = A^T dZ straight from memory (nn_dw_kernels.hip)
 bool nn_dw_direct(int64_t n, int64_t k, int64_t m);
-int nn_dw_direct_splits(int64_t n, int64_t k, int64_t m);
+int nn_dw_direct_splits(int64_t n, int64_t k, int64_t m, bool fp32_core);
 int launch_nn_dw_direct(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m,
-                        int dtype, void* stream);
+                        int dtype, bool fp32_core, void* stream);
 int launch_relu(const void* dH, const void* H, void* out, int64_t n, int64_t f, int64_t ld, int dtype,
                 bool backward, void* stream);
 

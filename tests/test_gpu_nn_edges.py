@@ -63,3 +63,66 @@ def test_transform_edges(n, k, m, dtype, act):
     dZ = dH * (got > 0) if act == ntp.NTP_ACT_RELU else dH
     assert_close(host(dA), rnd(dA_ref), _abs(dZ, W.T), tol, "dA")
     assert_close(dW.cpu().numpy(), dW_ref, _abs(A.T, dZ), TOL_F32 * (2 if bf16 else 1), "dW")
+
+
+# Products with a contraction below 64 or an output of up to 32 columns: fp32 arithmetic (exact products, infinities kept)
+def _fp32_products(contraction, cols):
+    return contraction < 64 or cols <= 32
+
+
+NARROW = [(1, 1, 1), (1000, 1, 40), (333, 2, 70), (1000, 4, 256), (777, 7, 65), (5000, 16, 33), (4097, 40, 256), (2500, 63, 129),
+          (5000, 256, 40), (2708, 1433, 16), (17000, 1433, 16), (20000, 602, 32), (33000, 130, 1), (50, 300, 200), (20000, 100, 7)]
+
+
+def _transform_fp32(A, W, dH):
+    """H, dA and dW of the library, no activation"""
+    import torch
+    (n, k), m = A.shape, W.shape[1]
+    At, Wt, dHt = (torch.from_numpy(x).to("cuda:0") for x in (A, W, dH))
+    H, dA, dW = (torch.full(s, 7.0, device="cuda:0") for s in ((n, m), (n, k), (k, m)))
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws = torch.empty(max(wsb, 4), dtype=torch.uint8, device="cuda:0")
+    ntp.ntp_nn_fwd(At, Wt, H, n, k, m)
+    ntp.ntp_nn_bwd(At, Wt, H, dHt, dA, dW, n, k, m, ntp.NTP_ACT_NONE, ntp.NTP_F32, ws, wsb)
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in (H, dA, dW)]
+
+
+@pytest.mark.parametrize("n,k,m", NARROW)
+def test_short_contractions_round_like_fp32(n, k, m):
+    """A sum of c exact products that rounds once per term is within c 2^-24 of the sum of magnitudes."""
+    print("nn fp32 products", n, k, m, file=sys.stderr, flush=True)
+    A = gen.normal_features(n, k, seed=n + k)
+    W = gen.glorot_weight(k, m, seed=m)
+    dH = gen.normal_features(n, m, seed=7, stream=6)
+    got = _transform_fp32(A, W, dH)
+    A, W, dH = (x.astype(np.float64) for x in (A, W, dH))
+    for name, g, a, b in (("H", got[0], A, W), ("dA", got[1], dH, W.T), ("dW", got[2], A.T, dH)):
+        c = a.shape[1]
+        if c < 64:
+            err = np.abs(g - a @ b) / (np.abs(a) @ np.abs(b))
+            assert err.max() <= c * 2.0 ** -24 * (1 + 1e-6), "%s: %.2e at contraction %d" % (name, err.max(), c)
+
+
+@pytest.mark.parametrize("n,k,m", NARROW)
+def test_infinities_pass_through_narrow_products(n, k, m):
+    """+-inf in an operand gives what fp32 (and fp64) arithmetic gives: inf, and NaN only where infinities cancel"""
+    print("nn infinities", n, k, m, file=sys.stderr, flush=True)
+    A = gen.normal_features(n, k, seed=n + k)
+    W = gen.glorot_weight(k, m, seed=m)
+    dH = gen.normal_features(n, m, seed=7, stream=6)
+    A[n // 2, k // 3] = np.inf
+    A[n - 1, k - 1] = -np.inf
+    dH[n // 3, m // 2] = -np.inf
+    W[k - 1, m - 1] = np.inf
+    got = _transform_fp32(A, W, dH)
+    A, W, dH = (x.astype(np.float64) for x in (A, W, dH))
+    for name, g, a, b in (("H", got[0], A, W), ("dA", got[1], dH, W.T), ("dW", got[2], A.T, dH)):
+        if not _fp32_products(a.shape[1], b.shape[1]):
+            continue
+        with np.errstate(invalid="ignore"):
+            want = a @ b
+        assert np.array_equal(np.isnan(g), np.isnan(want)), name
+        assert np.array_equal(np.isposinf(g), np.isposinf(want)) and np.array_equal(np.isneginf(g), np.isneginf(want)), name
+        fin = np.isfinite(want)
+        assert np.abs(g[fin] - want[fin]).max(initial=0.0) <= 1e-5 * max(1.0, np.abs(want[fin]).max(initial=0.0)), name
