@@ -126,3 +126,28 @@ def test_infinities_pass_through_narrow_products(n, k, m):
         assert np.array_equal(np.isposinf(g), np.isposinf(want)) and np.array_equal(np.isneginf(g), np.isneginf(want)), name
         fin = np.isfinite(want)
         assert np.abs(g[fin] - want[fin]).max(initial=0.0) <= 1e-5 * max(1.0, np.abs(want[fin]).max(initial=0.0)), name
+
+
+@pytest.mark.parametrize("n,k,m", [(640, 64, 33), (2000, 100, 47), (20000, 256, 128), (1100, 602, 64)])
+def test_a_product_formed_from_pieces_is_within_its_bound(n, k, m):
+    """Sums of a single product: what the cut leaves out of it (below 2^-21, always towards zero) and the roundings of the six
+    piece products on their way into the accumulator (the last and largest: 2^-24 of the sum, the others below 2^-7 of that)."""
+    print("nn piece products", n, k, m, file=sys.stderr, flush=True)
+    rng = gen.stream_rng(n + k + m, 78)
+    A = np.zeros((n, k), np.float32)
+    A[np.arange(n), np.arange(n) % k] = rng.uniform(1, 2, n)
+    W = rng.uniform(1, 2, (k, m)).astype(np.float32)
+    dH = np.zeros((n, m), np.float32)
+    dH[np.arange(n), np.arange(n) % m] = rng.uniform(1, 2, n)
+    H, dA, _ = _transform_fp32(A, W, dH)
+    first = (np.arange(n) < k)[:, None]                       # one row of A per row of dW
+    dH_all = rng.uniform(1, 2, (n, m)).astype(np.float32)
+    _, _, dW = _transform_fp32(A * first, W, dH_all)
+    A64, W64, dH64 = A.astype(np.float64), W.astype(np.float64), dH.astype(np.float64)
+    checks = [("H", H, A64 @ W64), ("dW", dW, (A64 * first).T @ dH_all.astype(np.float64))]
+    if m >= 64:
+        checks.append(("dA", dA, dH64 @ W64.T))
+    for name, got, want in checks:
+        short = 1 - got / want
+        print("   %s: left out of a product 2^%.2f at most" % (name, np.log2(short.max())), file=sys.stderr, flush=True)
+        assert short.max() <= 2.0 ** -21 + 1.1 * 2.0 ** -24 and short.min() >= -1.1 * 2.0 ** -24, name
