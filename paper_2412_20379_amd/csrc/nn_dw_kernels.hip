@@ -263,6 +263,8 @@ int pow2_up(int64_t x, int most) {
 }
 
 // The shape of a wavefront tile and how the work is cut.
+//   k < 4 (no whole vector of four columns of A): 32 x 32 read element by element, up to eight column tiles side by side
+//   (2 x 64 on 306,129 rows 0.025 ms against 0.111 in tiles through LDS, 3 x 256 0.077 against 0.186);
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //   against 39.1 us);  k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);  else 128 x 64, whose operands
 //   are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343 rows 0.134 against 0.164 ms.
@@ -270,6 +272,7 @@ int pow2_up(int64_t x, int most) {
 // L1), the other wavefronts share out the rows.
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY };
 int dw_shape(int64_t k, int64_t m, bool fp32_core) {
+    if (k < 4) return DW_TINY;
     if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
     return fp32_core && k <= 32 ? DW_TINY : DW_NARROW;
 }
@@ -280,12 +283,13 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core) {
     const int shape = dw_shape(k, m, fp32_core);
     const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
     g.kt = shape == DW_NARROW && n <= 50000 ? pow2_up((k + 127) / 128, 4) : 1;        // short contraction: few rows per wavefront
-    g.mt = tn == 1 ? 1 : pow2_up((m + 63) / 64, shape == DW_SHORT ? 4 : 2);
+    g.mt = shape == DW_NARROW ? 1 : pow2_up((m + 32 * tn - 1) / (32 * tn), shape == DW_TINY ? 8 : shape == DW_SHORT ? 4 : 2);
     g.tiles_k = (int)((k + 32 * ta * g.kt - 1) / (32 * ta * g.kt));
     g.tiles_m = (int)((m + 32 * tn * g.mt - 1) / (32 * tn * g.mt));
     const int64_t shares = 8 / (g.kt * g.mt), tiles = (int64_t)g.tiles_k * g.tiles_m;
     int64_t s = std::max<int64_t>(1, 256 / tiles);
     s = std::min(s, (n + 32 * shares - 1) / (32 * shares));        // at least two steps a wavefront
+    if (k < 4) s = std::min(s, std::max<int64_t>(1, n / 256));     // many column tiles: no more partial sums than rows pay for
     g.rows_per_split = ((n + s - 1) / s + 15) / 16 * 16;
     g.n_splits = (int)((n + g.rows_per_split - 1) / g.rows_per_split);
     return g;
@@ -295,7 +299,7 @@ template <class T, Core C>
 void launch_dw_any(const DwArgs& g, hipStream_t st) {
     switch (dw_shape(g.k, g.m, C == CORE_F32)) {
         case DW_TINY:
-            if constexpr (C == CORE_F32) g.mask ? launch_dw<T, C, true, 1, 1, 1, 1>(g, st) : launch_dw<T, C, false, 1, 1, 1, 1>(g, st);
+            if constexpr (sizeof(T) == 2 || C == CORE_F32) g.mask ? launch_dw<T, C, true, 1, 1, 1, 1>(g, st) : launch_dw<T, C, false, 1, 1, 1, 1>(g, st);
             break;
         case DW_NARROW: g.mask ? launch_dw<T, C, true, 4, 1, 4, 1>(g, st) : launch_dw<T, C, false, 4, 1, 4, 1>(g, st); break;
         case DW_SHORT: g.mask ? launch_dw<T, C, true, 2, 2, 2, 2>(g, st) : launch_dw<T, C, false, 2, 2, 2, 2>(g, st); break;
@@ -305,14 +309,14 @@ void launch_dw_any(const DwArgs& g, hipStream_t st) {
 
 }  // namespace
 
-// every product whose A has a whole vector of four columns
-bool nn_dw_direct(int64_t n, int64_t k, int64_t) { return n > 0 && k >= 4; }
+// fp32 operands with so few columns have a kernel on the fp32 instructions only (they are bound by reading dZ)
+bool nn_dw_fp32_only(int64_t k) { return k < 4; }
 
-int nn_dw_direct_splits(int64_t n, int64_t k, int64_t m, bool fp32_core) { return dw_plan(n, k, m, fp32_core).n_splits; }
+int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core) { return dw_plan(n, k, m, fp32_core).n_splits; }
 
 // partial sums of every range of vertices to out [splits][k x m]; fp32_core: fp32 operands on the fp32 matrix instructions
-int launch_nn_dw_direct(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m,
-                        int dtype, bool fp32_core, void* stream) {
+int launch_nn_dw(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m, int dtype,
+                 bool fp32_core, void* stream) {
     DwArgs g = dw_plan(n, k, m, fp32_core);
     g.A = A; g.Z = dH; g.mask = mask; g.out = out;
     const hipStream_t st = (hipStream_t)stream;

@@ -291,10 +291,10 @@ int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m);
 int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int64_t n, int64_t K, int64_t N, int64_t lda,
                     int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, bool fp32_core, void* stream);
 // dW = A^T dZ straight from memory (nn_dw_kernels.hip)
-bool nn_dw_direct(int64_t n, int64_t k, int64_t m);
-int nn_dw_direct_splits(int64_t n, int64_t k, int64_t m, bool fp32_core);
-int launch_nn_dw_direct(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m,
-                        int dtype, bool fp32_core, void* stream);
+bool nn_dw_fp32_only(int64_t k);
+int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core);
+int launch_nn_dw(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m, int dtype,
+                 bool fp32_core, void* stream);
 int launch_relu(const void* dH, const void* H, void* out, int64_t n, int64_t f, int64_t ld, int dtype,
                 bool backward, void* stream);
 

@@ -65,6 +65,14 @@ def test_transform_edges(n, k, m, dtype, act):
     assert_close(dW.cpu().numpy(), dW_ref, _abs(A.T, dZ), TOL_F32 * (2 if bf16 else 1), "dW")
 
 
+# dW of fewer than four columns of A: up to eight column tiles of dZ side by side, and more than one block of them
+@pytest.mark.parametrize("n,k,m", [(17, 3, 1), (33, 2, 300), (5000, 3, 256), (40001, 1, 40), (3000, 2, 1030), (300000, 3, 64)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
+def test_transform_few_columns(n, k, m, dtype, act):
+    test_transform_edges(n, k, m, dtype, act)
+
+
 # Products with a contraction below 64 or an output of up to 32 columns: fp32 arithmetic (exact products, infinities kept)
 def _fp32_products(contraction, cols):
     return contraction < 64 or cols <= 32
