@@ -1,6 +1,7 @@
-// Stand-alone driver for the host side of libntp (graph_build.cpp + plan.cpp): builds graphs
-// for every combination of the build flags, plans them with several chunk sizes and checks
-// the structural invariants of the result.  It links no device code, so it can be compiled
+// Stand-alone driver for the host side of libntp (graph_build.cpp, plan.cpp, chunk_schedule.h): builds
+// graphs for every combination of the build flags, plans them with several chunk sizes and checks
+// the structural invariants of the result; runs the streaming schedule on recorded streams, with
+// failures at every step, and checks the order of every access to the staging buffers.  It links no device code, so it can be compiled
 // with the host sanitizers (tests/test_host_sanitizers.py builds it with
 // -fsanitize=address,undefined and runs it); any invariant that fails, and anything a
 // sanitizer finds, ends the process with a non-zero status.
@@ -9,6 +10,7 @@
 #include <cstdlib>
 #include <vector>
 
+#include "chunk_schedule.h"
 #include "ntp_internal.h"
 
 using namespace ntp;
@@ -184,6 +186,96 @@ void build_and_plan(int64_t n, const std::vector<int32_t>& src, const std::vecto
     free_graph(G);
 }
 
+// ---- the streaming schedule on recorded streams -----------------------------------------------
+// A clock vector per stream: clock[s][t] = how much of stream t has run when the next operation of stream s runs.
+struct Recorder {
+    static constexpr int STREAMS = 8;
+    using Stream = int;
+    struct Event { int64_t at[STREAMS] = {0}; };
+    int64_t clock[STREAMS][STREAMS] = {{0}};
+    struct Access { int stream = -1; int64_t time = 0; };
+    struct Region { Access write, read; int holds = -1; } region[2][2];      // [buffer][0: entries, 1: row pointers and lists]
+    Access last_copy[STREAMS];
+    int compute = 0, fail_in = -1;           // fail_in: operations until one fails (negative: none does)
+    const char* what = "";
+
+    bool fails() { return fail_in >= 0 && fail_in-- == 0; }
+    bool before(const Access& a, int s) const { return a.stream < 0 || clock[s][a.stream] >= a.time; }
+    Access tick(int s) { ++clock[s][s]; return Access{s, clock[s][s]}; }
+    int record(Event& e, int s) {
+        if (fails()) return -1;
+        for (int t = 0; t < STREAMS; ++t) e.at[t] = clock[s][t];
+        return 0;
+    }
+    int wait(int s, const Event& e) {
+        if (fails()) return -1;
+        for (int t = 0; t < STREAMS; ++t) clock[s][t] = e.at[t] > clock[s][t] ? e.at[t] : clock[s][t];
+        return 0;
+    }
+    void write(int c, int b, int part, int s) {
+        Region& r = region[b][part];
+        CHECK(before(r.write, s) && before(r.read, s), "%s: buffer %d part %d is written on stream %d while in use", what, b, part, s);
+        r.write = tick(s);
+        r.holds = c;
+    }
+    int copy_entries(int c, int b, int s) {
+        if (fails()) return -1;
+        write(c, b, 0, s);
+        last_copy[s] = region[b][0].write;
+        return 0;
+    }
+    int copy_by_kernel(int c, int b, int s, bool entries) {
+        if (fails()) return -1;
+        write(c, b, 1, s);
+        if (entries) write(c, b, 0, s);
+        last_copy[s] = Access{s, clock[s][s]};
+        return 0;
+    }
+    int aggregate(int c, int b) {
+        if (fails()) return -1;
+        for (int part = 0; part < 2; ++part) {
+            Region& r = region[b][part];
+            CHECK(r.holds == c && before(r.write, compute), "%s: chunk %d is read before its copy", what, c);
+            r.read = tick(compute);
+        }
+        return 0;
+    }
+};
+
+void check_schedule() {
+    const int COPY2 = 7;
+    for (int first = 0; first < 3; ++first)
+        for (int fail = -1; fail < 60; ++fail) {
+            Recorder ops;
+            StageState<Recorder> state;
+            state.copy2 = COPY2;
+            Lcg rng{(uint64_t)(first * 1000 + fail + 2)};
+            char what[64];
+            snprintf(what, sizeof what, "path %d, failure at step %d", first, fail);
+            ops.what = what;
+            int chunk = 0;
+            for (int pass = 0; pass < 6; ++pass) {
+                // every pass on compute and copy streams of its own choice, without a wait in between
+                const int cs = (int)(rng.next() % 3), xs = 3 + (int)(rng.next() % 3);
+                const CopyPath path = (CopyPath)(pass == 0 ? first : rng.next() % 3);
+                ops.compute = cs;
+                for (auto& a : ops.last_copy) a = Recorder::Access();
+                ops.fail_in = pass == 0 ? fail : -1;
+                {
+                    StreamedPass<Recorder> p(ops, state, cs, xs, path);
+                    int rc = p.begin();
+                    for (int i = 0; i < 5 && rc == 0; ++i) rc = p.streamed(chunk++);
+                    ops.fail_in = -1;
+                    if (rc == 0) CHECK(p.end() == 0, "%s: the pass does not end", what);
+                }
+                for (int s : {xs, COPY2}) {
+                    CHECK(ops.before(ops.last_copy[s], xs), "%s: the copy stream does not stand behind the copies", what);
+                    CHECK(ops.before(ops.last_copy[s], cs), "%s: the compute stream does not stand behind the copies", what);
+                }
+            }
+        }
+}
+
 }  // namespace
 
 int main() {
@@ -263,6 +355,8 @@ int main() {
         const int32_t s[2] = {0, 9}, d[2] = {1, 2};
         CHECK(build_host_graph(3, 2, s, d, nullptr, NTP_DEDUP, alloc, &G) == NTP_EINVAL, "vertex id out of range accepted");
     }
+    // 5. the order of a streamed pass
+    check_schedule();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");
     return 0;

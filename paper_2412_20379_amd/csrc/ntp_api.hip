@@ -10,6 +10,7 @@
 #include <mutex>
 #include <new>
 
+#include "chunk_schedule.h"
 #include "ntp_internal.h"
 
 using namespace ntp;
@@ -35,6 +36,25 @@ struct Form {
     bool one_reduce() const { return d_all_reduce != nullptr; }
 };
 
+// What a pass of chunk_schedule.h does on HIP streams (defined below)
+struct ntp_graph;
+struct ChunkKernels;
+struct HipPass {
+    using Stream = hipStream_t;
+    using Event = hipEvent_t;
+    ntp_graph* g;
+    const HostSparse& m;
+    bool by_source;                // rows of the by-source form
+    bool with_val;                 // weights travel (else they are rebuilt on the device)
+    hipStream_t cs;                // compute stream
+    const ChunkKernels& kernels;
+    int record(hipEvent_t e, hipStream_t s) { HIP_TRY(hipEventRecord(e, s)); return NTP_OK; }
+    int wait(hipStream_t s, hipEvent_t e) { HIP_TRY(hipStreamWaitEvent(s, e, 0)); return NTP_OK; }
+    int copy_entries(const Chunk& c, int b, hipStream_t s);
+    int copy_by_kernel(const Chunk& c, int b, hipStream_t s, bool entries);
+    int aggregate(const Chunk& c, int b);
+};
+
 struct ntp_graph {
     BuiltGraph g;
     Form form[2];                  // NTP_CSR, NTP_CSC (unused when symmetric)
@@ -44,12 +64,7 @@ struct ntp_graph {
     // staging for streamed chunks
     char* stage[2] = {nullptr, nullptr};
     size_t stage_bytes = 0;
-    hipEvent_t ev_ready[2] = {nullptr, nullptr};   // copy of the chunk finished
-    hipEvent_t ev_free[2] = {nullptr, nullptr};    // kernels reading the buffer finished
-    hipStream_t copy2 = nullptr;                   // second copy stream: buffer 1's (buffer 0's is the caller's)
-    hipEvent_t ev_copy2[2] = {nullptr, nullptr};   // orders it after and before the caller's copy stream
-    bool stage_used[2] = {false, false};
-    int next_stage = 0;
+    StageState<HipPass> staged;                     // streams, events and the state of the two buffers
     char* pinned_meta = nullptr;                    // metas of streamed chunks
     // partial sums of split rows
     float* partial = nullptr;
@@ -124,29 +139,7 @@ int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
     return NTP_OK;
 }
 
-// Chunk images of up to this many bytes are copied by a kernel on the compute stream (36 us on the link): with DMA copies,
-// events and a second stream a chunk costs 50-70 us whatever its size.
-constexpr int64_t SMALL_CHUNK_BYTES = 2 << 20;
-
 int64_t streamed_bytes(const Chunk& c, bool with_val) { return (int64_t)c.meta.size() + (c.e_end - c.e_begin) * (with_val ? 8 : 4); }
-
-// Enqueue the copy of a streamed chunk's row pointers and lists, or of all of it, by a kernel (everything it reads is pinned).
-// with_val = false: the weights are rebuilt on the device after the copy (launch_rebuild_weights).
-int stage_chunk(const HostSparse& m, const Chunk& c, char* dst, hipStream_t st, bool entries, bool with_val) {
-    const int64_t entry_bytes = entries ? (c.e_end - c.e_begin) * 4 : 0;
-    const void* src[3] = {c.h_meta_pinned, m.colidx + c.e_begin, m.val + c.e_begin};
-    void* to[3] = {dst, dst + c.img_off_colidx, dst + c.img_off_val};
-    const int64_t bytes[3] = {(int64_t)c.meta.size(), entry_bytes, with_val ? entry_bytes : 0};
-    return launch_stage_chunk(src, to, bytes, st);
-}
-// its entries by DMA
-int copy_entries(const HostSparse& m, const Chunk& c, char* dst, hipStream_t st, bool with_val) {
-    const size_t ne = (size_t)(c.e_end - c.e_begin);
-    if (ne == 0) return NTP_OK;
-    HIP_TRY(hipMemcpyAsync(dst + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice, st));
-    if (with_val) HIP_TRY(hipMemcpyAsync(dst + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice, st));
-    return NTP_OK;
-}
 
 // what the aggregation does to an output element on its way out (AggArgs::epilogue)
 struct Epilogue {
@@ -351,11 +344,10 @@ void destroy(ntp_graph* G) {
         if (G->form[k].d_hub_cols) (void)hipFree(G->form[k].d_hub_cols);
         if (G->form[k].d_all_reduce) (void)hipFree(G->form[k].d_all_reduce);
         if (G->stage[k]) (void)hipFree(G->stage[k]);
-        if (G->ev_ready[k]) (void)hipEventDestroy(G->ev_ready[k]);
-        if (G->ev_free[k]) (void)hipEventDestroy(G->ev_free[k]);
-        if (G->ev_copy2[k]) (void)hipEventDestroy(G->ev_copy2[k]);
+        for (hipEvent_t e : {G->staged.ready[k], G->staged.free_[k], G->staged.join[k]})
+            if (e) (void)hipEventDestroy(e);
     }
-    if (G->copy2) (void)hipStreamDestroy(G->copy2);
+    if (G->staged.copy2) (void)hipStreamDestroy(G->staged.copy2);
     if (G->partial) (void)hipFree(G->partial);
     if (G->att_stats) (void)hipFree(G->att_stats);
     if (G->att_bwd) (void)hipFree(G->att_bwd);
@@ -369,6 +361,61 @@ void destroy(ntp_graph* G) {
 }
 
 }  // namespace
+
+// The aggregation of one chunk into every right-hand side
+struct ChunkKernels {
+    const Form& F;
+    int n_rhs;
+    const void* const* X;
+    void* const* Y;
+    bool scatter;
+    float* partial;
+    size_t partial_stride;
+    int64_t f, ldx, ldy;
+    int dtype;
+    hipStream_t cs;
+    const Epilogue& epi;
+    int operator()(const Chunk& c, const char* img) const {
+        for (int r = 0; r < n_rhs; ++r) {
+            const int e = run_chunk(c, img, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
+                                    scatter, nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
+            if (e != NTP_OK) return e;
+        }
+        return NTP_OK;
+    }
+};
+
+// its entries by DMA (everything a streamed chunk is copied from is pinned)
+int HipPass::copy_entries(const Chunk& c, int b, hipStream_t s) {
+    char* img = g->stage[b];
+    const size_t ne = (size_t)(c.e_end - c.e_begin);
+    if (ne == 0) return NTP_OK;
+    HIP_TRY(hipMemcpyAsync(img + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice, s));
+    if (with_val) HIP_TRY(hipMemcpyAsync(img + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice, s));
+    return NTP_OK;
+}
+
+// its row pointers and lists, or all of it, by a kernel
+int HipPass::copy_by_kernel(const Chunk& c, int b, hipStream_t s, bool entries) {
+    char* img = g->stage[b];
+    const int64_t entry_bytes = entries ? (c.e_end - c.e_begin) * 4 : 0;
+    const void* src[3] = {c.h_meta_pinned, m.colidx + c.e_begin, m.val + c.e_begin};
+    void* to[3] = {img, img + c.img_off_colidx, img + c.img_off_val};
+    const int64_t bytes[3] = {(int64_t)c.meta.size(), entry_bytes, with_val ? entry_bytes : 0};
+    return launch_stage_chunk(src, to, bytes, s);
+}
+
+int HipPass::aggregate(const Chunk& c, int b) {
+    char* img = g->stage[b];
+    if (!with_val) {          // row degree = dout and column degree = din where rows are sources
+        const int rc = launch_rebuild_weights(reinterpret_cast<const int64_t*>(img + c.off_rowptr), c.row_begin, c.row_end - c.row_begin,
+                                              c.e_begin, c.e_end - c.e_begin, reinterpret_cast<const int32_t*>(img + c.img_off_colidx),
+                                              reinterpret_cast<float*>(img + c.img_off_val), by_source ? g->d_dout : g->d_din,
+                                              by_source ? g->d_din : g->d_dout, g->g.val_mode, cs);
+        if (rc != NTP_OK) return rc;
+    }
+    return kernels(c, img);
+}
 
 extern "C" {
 
@@ -449,13 +496,10 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                 if (hipMalloc(&p, max_img) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of a %zu-byte staging buffer failed", max_img); return NTP_ENOMEM; }
                 G->stage[b] = (char*)p;
                 G->device_bytes += (int64_t)max_img;
-                if (hipEventCreateWithFlags(&G->ev_ready[b], hipEventDisableTiming) != hipSuccess ||
-                    hipEventCreateWithFlags(&G->ev_free[b], hipEventDisableTiming) != hipSuccess ||
-                    hipEventCreateWithFlags(&G->ev_copy2[b], hipEventDisableTiming) != hipSuccess) {
-                    set_error("hipEventCreate failed"); return NTP_EHIP;
-                }
+                for (hipEvent_t* e : {&G->staged.ready[b], &G->staged.free_[b], &G->staged.join[b]})
+                    if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) { set_error("hipEventCreate failed"); return NTP_EHIP; }
             }
-            if (hipStreamCreateWithFlags(&G->copy2, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); set_error("hipStreamCreate failed"); return NTP_EHIP; }
+            if (hipStreamCreateWithFlags(&G->staged.copy2, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); set_error("hipStreamCreate failed"); return NTP_EHIP; }
             left = force_stream ? 0 : budget - (int64_t)(2 * max_img);
         }
         // residency: everything if it fits, else chunks in round-robin order over the forms
@@ -760,73 +804,20 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
     if (rc != NTP_OK) return rc;
     const size_t pstride = scatter ? 0 : partial_floats(F, f);
     // every chunk is brought in once and applied to all right-hand sides before the next one
-    auto run_all = [&](const Chunk& c, const char* img) -> int {
-        for (int r = 0; r < n_rhs; ++r) {
-            const int e = run_chunk(c, img, X[r], Y[r], scatter ? nullptr : g->partial + (size_t)r * pstride, f, ldx, ldy, dtype, cs, scatter,
-                                    nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
-            if (e != NTP_OK) return e;
-        }
-        return NTP_OK;
-    };
-    const bool rebuild = g->streams_without_weights();
-    bool small = true;
-    for (auto& c : F.plan.chunks) small = small && (c.d_image || streamed_bytes(c, !rebuild) <= SMALL_CHUNK_BYTES);
-    // Large chunks: the entries of consecutive chunks go by DMA on two copy streams in turn (one per staging buffer), so
-    // that the 20-30 us it takes to start a copy pass while the other one is on the link; the rest of the image is copied by a
-    // kernel on the compute stream (four chunks of 4 M entries: 1.45 -> 1.32 ms a pass, the link alone 1.15).
-    // Small chunks: everything on the compute stream.
-    const bool dma = !F.all_resident && !small;
-    bool touched[2] = {false, false};
-    if (dma) {
-        HIP_TRY(hipEventRecord(g->ev_copy2[0], xs));
-        HIP_TRY(hipStreamWaitEvent(g->copy2, g->ev_copy2[0], 0));
-    }
+    const ChunkKernels run_all{F, n_rhs, X, Y, scatter, g->partial, pstride, f, ldx, ldy, dtype, cs, epi};
+    const bool with_val = !g->streams_without_weights();
+    int64_t largest = 0;
+    for (auto& c : F.plan.chunks)
+        if (!c.d_image) largest = std::max(largest, streamed_bytes(c, with_val));
+    HipPass ops{g, *F.m, &F == &g->form[1], with_val, cs, run_all};
+    StreamedPass<HipPass> pass(ops, g->staged, cs, xs, pick_copy_path(largest));
+    if (!F.all_resident) rc = pass.begin();
     for (auto& c : F.plan.chunks) {
-        if (c.d_image) {
-            rc = run_all(c, c.d_image);
-            if (rc != NTP_OK) return rc;
-            continue;
-        }
-        const int b = g->next_stage;
-        g->next_stage ^= 1;
-        char* img = g->stage[b];
-        // the buffer may still be read by the kernels of the chunk that used it last (of an earlier call: on any stream)
-        if (!touched[b] && g->stage_used[b]) HIP_TRY(hipStreamWaitEvent(cs, g->ev_free[b], 0));
-        if (dma) {
-            const hipStream_t ks = b == 0 ? xs : g->copy2;
-            if (g->stage_used[b]) HIP_TRY(hipStreamWaitEvent(ks, g->ev_free[b], 0));
-            rc = copy_entries(*F.m, c, img, ks, !rebuild);
-            if (rc != NTP_OK) return rc;
-            HIP_TRY(hipEventRecord(g->ev_ready[b], ks));
-        }
-        rc = stage_chunk(*F.m, c, img, cs, !dma, !rebuild);
         if (rc != NTP_OK) return rc;
-        if (dma) HIP_TRY(hipStreamWaitEvent(cs, g->ev_ready[b], 0));
-        if (rebuild) {
-            const bool by_source = &F == &g->form[1];          // rows are sources: row degree = dout, column degree = din
-            rc = launch_rebuild_weights(reinterpret_cast<const int64_t*>(img + c.off_rowptr), c.row_begin, c.row_end - c.row_begin,
-                                        c.e_begin, c.e_end - c.e_begin, reinterpret_cast<const int32_t*>(img + c.img_off_colidx),
-                                        reinterpret_cast<float*>(img + c.img_off_val), by_source ? g->d_dout : g->d_din,
-                                        by_source ? g->d_din : g->d_dout, g->g.val_mode, cs);
-            if (rc != NTP_OK) return rc;
-        }
-        rc = run_all(c, img);
-        if (rc != NTP_OK) return rc;
-        touched[b] = true;
-        if (dma) {
-            HIP_TRY(hipEventRecord(g->ev_free[b], cs));
-            g->stage_used[b] = true;
-        }
+        rc = c.d_image ? run_all(c, c.d_image) : pass.streamed(c);
     }
-    for (int b = 0; b < 2; ++b)
-        if (!dma && touched[b]) {
-            HIP_TRY(hipEventRecord(g->ev_free[b], cs));
-            g->stage_used[b] = true;
-        }
-    if (dma) {          // whoever waits for the caller's copy stream waits for all copies
-        HIP_TRY(hipEventRecord(g->ev_copy2[1], g->copy2));
-        HIP_TRY(hipStreamWaitEvent(xs, g->ev_copy2[1], 0));
-    }
+    if (rc == NTP_OK && !F.all_resident) rc = pass.end();
+    if (rc != NTP_OK) return rc;
     if (!scatter && F.one_reduce())
         for (int r = 0; r < n_rhs; ++r) {
             rc = reduce_all(F, g->partial + (size_t)r * pstride, Y[r], f, ldy, dtype, cs, epi);

@@ -233,3 +233,59 @@ def test_config5_shape_streams_under_a_budget():
     say("  oracle rows in %.0fs (%d entries)" % (time.time() - t0, m.nnz))
     got = got_fwd[torch.from_numpy(rows).to("cuda:0")].cpu().numpy()
     assert_close(got, ref, ref_abs, TOL_F32, "config 5 / 8 sampled rows")
+
+
+@pytest.mark.parametrize("case", ["directed", "symmetric", "caller weights", "under a budget"])
+@pytest.mark.parametrize("f,n_rhs", [(13, 1), (16, 3), (256, 1), (40, 8)])
+def test_large_streamed_chunks_equal_resident_ones(case, f, n_rhs):
+    """Chunks of several megabytes travel by DMA on two copy streams, their row pointers and lists on the compute stream or
+    behind them: the bits of the resident chunks in both directions, for several right-hand sides, with the activation, and
+    for passes that follow each other on other streams without the host waiting in between."""
+    import torch
+    n = 30000
+    src, dst = gen.directed_random_edges(n, 1_600_000, 43, hub=17, hub_in=20000, hub_out=9000)
+    flags = ntp.NTP_GCN_FLAGS if case == "symmetric" else ntp.NTP_DIRECTED_GCN_FLAGS
+    w = (gen.stream_rng(3, 8).random(src.size) + 0.5).astype(np.float32) if case == "caller weights" else None
+    ce = 600_000
+    resident = ntp.ntp_graph_build(n, src, dst, w, flags=flags, chunk_edges=ce)
+    if case == "under a budget":        # some chunks resident between streamed ones
+        streamed = ntp.ntp_graph_build(n, src, dst, w, flags=flags, chunk_edges=ce, device_budget_bytes=17 << 20)
+        res = ntp.ntp_graph_chunks(streamed)["resident"]
+        assert 0 < res.sum() < res.size
+    else:
+        streamed = ntp.ntp_graph_build(n, src, dst, w, flags=flags | ntp.NTP_FORCE_STREAM, chunk_edges=ce)
+    assert ntp.ntp_graph_stream_bytes(streamed) > 4 << 20
+    say("large chunks", case, f, n_rhs, "chunks", ntp.ntp_graph_info(streamed)["n_chunks"])
+    gen_t = torch.Generator(device="cuda:0")
+    gen_t.manual_seed(f)
+    ld = (f + 3) // 4 * 4
+    xs = [torch.randn(n, ld, device="cuda:0", generator=gen_t) for _ in range(n_rhs)]
+    mask = torch.randn(n, ld, device="cuda:0", generator=gen_t)
+    streams = [(torch.cuda.Stream(), torch.cuda.Stream()) for _ in range(3)]
+
+    def passes(g):
+        outs = []
+        before = torch.cuda.current_stream()
+        for i, (direction, act) in enumerate([(ntp.NTP_FWD, False), (ntp.NTP_BWD, False), (ntp.NTP_FWD, True), (ntp.NTP_BWD, True), (ntp.NTP_FWD, False)]):
+            cs, cp = streams[i % 3]
+            ys = [torch.full((n, ld), 7.0, device="cuda:0") for _ in range(n_rhs)]
+            cs.wait_stream(torch.cuda.current_stream())     # the fills
+            cs.wait_stream(before)                          # the scratch for split rows belongs to one pass at a time
+            if act:
+                M = mask if direction == ntp.NTP_BWD else None
+                ntp.ntp_aggregate_act(g, direction, xs[0], ys[0], f, ld, ld, ntp.NTP_F32, ntp.NTP_ACT_RELU, M, ld if M is not None else 0, cs, cp)
+                ys = ys[:1]
+            else:
+                ntp.ntp_chunked_aggregate_multi(g, direction, xs, ys, f, ld, ld, ntp.NTP_F32, cs, cp)
+            before = cs
+            outs += ys
+        torch.cuda.synchronize()
+        return outs
+
+    torch.cuda.synchronize()
+    want, got = passes(resident), passes(streamed)
+    for i, (a, b) in enumerate(zip(want, got)):
+        assert torch.equal(a[:, :f], b[:, :f]), "output %d" % i
+        assert torch.isfinite(a[:, :f]).all() and bool((b[:, f:] == 7.0).all())
+    resident.close()
+    streamed.close()
