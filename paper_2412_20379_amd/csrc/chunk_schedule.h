@@ -15,13 +15,26 @@ namespace ntp {
 // How the parts of a streamed chunk travel.
 //   COPY_ON_COMPUTE   everything by a kernel on the compute stream: no event, no second stream
 //   COPY_META_ON_COMPUTE  entries by DMA on two copy streams in turn (one per buffer; the 20-30 us it takes to start a copy pass
-//                     while the other one is on the link), row pointers and lists by a kernel on the compute stream (four
-//                     chunks of 4 M entries: 1.45 -> 1.32 ms a pass, the link alone 1.15)
+//                     while the other one is on the link), row pointers and lists by a kernel on the compute stream
 //   COPY_ON_COPY      the same with the row pointers and lists behind the entries on the copy stream
 enum CopyPath { COPY_ON_COMPUTE, COPY_META_ON_COMPUTE, COPY_ON_COPY };
 
-// Up to 2 MB (36 us on the link) a chunk with DMA copies, events and a second stream costs 50-70 us whatever its size.
-inline CopyPath pick_copy_path(int64_t largest) { return largest <= (2 << 20) ? COPY_ON_COMPUTE : COPY_META_ON_COMPUTE; }
+// The path for a pass whose streamed chunks have, on average, `bytes` to copy and `entries` entries to aggregate into n_rhs
+// right-hand sides of `lines` cache lines a row; largest: bytes of the largest one.
+//   Up to 3/4 MB a copy by DMA with its events and second stream (50-70 us a chunk whatever its size) costs more than it
+//   hides.  us a pass over 2.0 M entries, one right-hand side of 32 columns / eight, everything on the compute stream
+//   against entries by DMA: chunks of 0.1 M entries (0.5 MB) 846 / 1992 against 840 / 2193, 0.2 M 512 / 1099 against 455 / 1141,
+//   0.3 M 408 / 824 against 338 / 822, 0.4 M (1.8 MB) 341 / 660 against 266 / 621.
+//   Above, the link is the bound until the aggregation of a chunk takes about as long as its copy: then the row pointers
+//   and lists (a fifth of the bytes at 15 entries a row), copied on the compute stream, are time that the aggregation
+//   cannot have.  On the compute / copy stream: 4 chunks of 4 M entries F = 32 1268 / 1314, F = 128 1316 / 1376, F = 256 1539 /
+//   1469, 8 x 32 columns 1971 / 1821; 11 of 0.4 M F = 32 669 / 682, F = 128 862 / 803, F = 256 1096 / 1016, 8 x 32 1581 / 1543.
+//   Estimates: 56 GB/s on the link; 10 us a launch and 100 G lines/s in the aggregation.  The line lies at 0.7 of the copy.
+inline CopyPath pick_copy_path(double bytes, double largest, double entries, int64_t lines, int n_rhs) {
+    if (largest <= 768 * 1024) return COPY_ON_COMPUTE;
+    const double copy_us = bytes / 56e3, aggregate_us = n_rhs * (10.0 + entries * (double)lines * 1e-5);
+    return aggregate_us > 0.7 * copy_us ? COPY_ON_COPY : COPY_META_ON_COMPUTE;
+}
 
 template <class Ops> struct StageState {
     typename Ops::Event ready[2] = {}, free_[2] = {}, join[2] = {};

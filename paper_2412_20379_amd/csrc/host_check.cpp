@@ -274,6 +274,12 @@ void check_schedule() {
                 }
             }
         }
+    // the path: small chunks on the compute stream, larger ones by what bounds them
+    CHECK(pick_copy_path(700e3, 700e3, 150e3, 8, 8) == COPY_ON_COMPUTE, "small chunk");
+    CHECK(pick_copy_path(300e3, 900e3, 60e3, 1, 1) != COPY_ON_COMPUTE, "one larger chunk");
+    CHECK(pick_copy_path(17e6, 17e6, 4e6, 1, 1) == COPY_META_ON_COMPUTE, "4 M entries, F = 32: the link");
+    CHECK(pick_copy_path(17e6, 17e6, 4e6, 8, 1) == COPY_ON_COPY, "4 M entries, F = 256: the aggregation");
+    CHECK(pick_copy_path(17e6, 17e6, 4e6, 1, 8) == COPY_ON_COPY, "4 M entries, eight right-hand sides: the aggregation");
 }
 
 }  // namespace
