@@ -1,4 +1,7 @@
-"""ctypes binding of libntp.so: same names as include/ntp.h, argument marshalling only."""
+"""Python binding of libntp.so: same names as include/ntp.h, argument marshalling only.
+
+The calls that only enqueue work go through the extension module _native (csrc/py_native.cpp), or through ctypes where it could
+not be built; everything else goes through ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -43,6 +46,36 @@ def lib_path() -> str:
 _lib = None
 
 
+# the calls that only enqueue work, and how many of their last parameters are streams
+ENQUEUE_CALLS = {
+    "ntp_aggregate_fwd": 1, "ntp_aggregate_fwd_noalloc": 1, "ntp_aggregate_bwd": 1, "ntp_aggregate_weighted": 1,
+    "ntp_chunked_aggregate": 2, "ntp_aggregate_act": 2, "ntp_edge_softmax": 1, "ntp_edge_softmax_bwd": 1,
+    "ntp_attention_scores_fwd": 1, "ntp_attention_scores_bwd": 1, "ntp_nn_fwd": 1, "ntp_nn_bwd": 1, "ntp_softmax_xent": 1,
+    "ntp_relu_fwd": 1, "ntp_relu_bwd": 1,
+}
+
+
+class CtypesCalls:
+    """The functions of _native by way of ctypes: the same positional arguments, the status as the result."""
+
+    def __init__(self, L):
+        for name, streams in ENQUEUE_CALLS.items():
+            setattr(self, name, self._call(getattr(L, name), streams))
+
+    @staticmethod
+    def _call(fn, streams):
+        kinds = fn.argtypes
+        convert = [_ptr if k is ctypes.c_void_p else float if k is ctypes.c_float else int for k in kinds]
+        convert[len(kinds) - streams:] = [_stream] * streams
+
+        def call(*args):
+            if len(args) != len(kinds):
+                raise TypeError("%d arguments expected, %d given" % (len(kinds), len(args)))
+            return fn(*[c(a) for c, a in zip(convert, args)])
+
+        return call
+
+
 class _Unloaded:
     """stands for the native module until the first call loads it"""
 
@@ -61,10 +94,9 @@ def lib():
         return _lib
     path = lib_path()
     from . import build as _build
-    if not os.path.exists(path) or not os.path.exists(_build.NATIVE):
+    if not os.path.exists(path) or (not os.path.exists(_build.NATIVE) and _build.native_command("")):
         _build.build()
     L = ctypes.CDLL(path)
-    _native = importlib.import_module("._native", __package__)
     vp, i64, i32, u32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_uint32
     L.ntp_graph_build.argtypes = [i64, i64, vp, vp, vp, u32, i64, i64, ctypes.POINTER(vp)]
     L.ntp_graph_info.argtypes = [vp, vp, vp, vp, vp, vp]
@@ -103,6 +135,10 @@ def lib():
         if name not in ("ntp_graph_free", "ntp_last_error", "ntp_nn_bwd_workspace_bytes", "ntp_softmax_xent_scratch_bytes",
                         "ntp_attention_scores_bwd_scratch_bytes"):
             fn.restype = ctypes.c_int
+    try:
+        _native = importlib.import_module("._native", __package__)
+    except ImportError:
+        _native = CtypesCalls(L)
     _lib = L
     return L
 
@@ -117,11 +153,13 @@ def _check(rc: int):
 
 
 def _ptr(x):
-    """Device or host address of a torch tensor / numpy array / int / None."""
+    """Device or host address of a torch tensor / numpy array / ctypes pointer / int / None."""
     if x is None or isinstance(x, int):
         return x
     if isinstance(x, np.ndarray):
         return x.ctypes.data
+    if isinstance(x, ctypes.c_void_p):
+        return x.value
     return x.data_ptr()                           # torch tensor
 
 

@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -42,6 +43,17 @@ def _stale(out: str, deps) -> bool:
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def native_command(out: str):
+    """Compiler line of the Python entry module, or None where the interpreter's headers are missing (the binding then
+    marshals with ctypes)."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        return None
+    cxx = [shutil.which("g++")] if shutil.which("g++") else [_hipcc(), "-x", "c++"]
+    return cxx + ["-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + os.path.join(ROOT, "include"), "-I" + include, NATIVE_SRC,
+                  "-o", out, "-L" + PKG, "-lntp", "-Wl,-rpath,$ORIGIN"]
+
+
 def build(force: bool = False, verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     hipcc = _hipcc()
@@ -72,9 +84,12 @@ def build(force: bool = False, verbose: bool = False) -> str:
         os.replace(tmp, LIB)
     if force or _stale(NATIVE, [NATIVE_SRC, os.path.join(ROOT, "include", "ntp.h"), os.path.abspath(__file__)]):
         tmp = NATIVE + ".tmp%d" % os.getpid()
-        run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + os.path.join(ROOT, "include"),
-             "-I" + sysconfig.get_paths()["include"], NATIVE_SRC, "-o", tmp, "-L" + PKG, "-lntp", "-Wl,-rpath,$ORIGIN"])
-        os.replace(tmp, NATIVE)
+        cmd = native_command(tmp)
+        if cmd:
+            run(cmd)
+            os.replace(tmp, NATIVE)
+        elif verbose:
+            print("no Python.h: calls go through ctypes")
     # the stand-alone measurement aid (its own executable: it links nothing of the library)
     if force or _stale(PROBE, [PROBE_SRC]):
         tmp = PROBE + ".tmp%d" % os.getpid()
