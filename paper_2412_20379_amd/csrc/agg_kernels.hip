@@ -690,15 +690,6 @@ int launch_one(const AggArgs& a, int n_passes, hipStream_t st) {
     return NTP_OK;
 }
 
-int compute_units() {
-    static const int cus = [] {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        return n;
-    }();
-    return cus;
-}
-
 template <class IO, int L>
 int launch_hub(const AggArgs& a, int n_passes, hipStream_t st) {
     const int total = a.wave_start[a.n_groups];
@@ -833,6 +824,15 @@ int launch_reduce(const ReduceArgs& a, int dtype, void* stream) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("reduce kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
     return NTP_OK;
+}
+
+int compute_units() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        return n;
+    }();
+    return cus;
 }
 
 }  // namespace ntp

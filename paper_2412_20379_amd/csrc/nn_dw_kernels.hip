@@ -268,6 +268,9 @@ int pow2_up(int64_t x, int most) {
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //   against 39.1 us);  k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);  else 128 x 64, whose operands
 //   are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343 rows 0.134 against 0.164 ms.
+// m <= 32 and k > 256 take four row tiles side by side: whole rows of A from few blocks (us with one / four, 602 x 16 on 16,000
+// rows 27.3 / 22.5, 50,000 54.7 / 46.9, 200,000 195 / 162; 1433 x 16 on 30,000 75.2 / 70.5; 256 x 16 on 120,000 33.6 / 35.5, so
+// not there; 602 x 16 on 8,000 13.9 / 16.4: the few rows of a block are better shared out).
 // Blocks: about one per compute unit; two column tiles side by side where there are two (they share the rows of A through the
 // L1), the other wavefronts share out the rows.
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY };
@@ -282,12 +285,12 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core) {
     g.n = n; g.k = (int)k; g.m = (int)m;
     const int shape = dw_shape(k, m, fp32_core);
     const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
-    g.kt = shape == DW_NARROW && n <= 50000 ? pow2_up((k + 127) / 128, 4) : 1;        // short contraction: few rows per wavefront
+    g.kt = shape == DW_NARROW && k > 256 && n > 10000 ? 4 : 1;
     g.mt = shape == DW_NARROW ? 1 : pow2_up((m + 32 * tn - 1) / (32 * tn), shape == DW_TINY ? 8 : shape == DW_SHORT ? 4 : 2);
     g.tiles_k = (int)((k + 32 * ta * g.kt - 1) / (32 * ta * g.kt));
     g.tiles_m = (int)((m + 32 * tn * g.mt - 1) / (32 * tn * g.mt));
     const int64_t shares = 8 / (g.kt * g.mt), tiles = (int64_t)g.tiles_k * g.tiles_m;
-    int64_t s = std::max<int64_t>(1, 256 / tiles);
+    int64_t s = std::max<int64_t>(1, compute_units() / tiles);
     s = std::min(s, (n + 32 * shares - 1) / (32 * shares));        // at least two steps a wavefront
     if (k < 4) s = std::min(s, std::max<int64_t>(1, n / 256));     // many column tiles: no more partial sums than rows pay for
     g.rows_per_split = ((n + s - 1) / s + 15) / 16 * 16;

@@ -463,12 +463,15 @@ __global__ void __launch_bounds__(512) strip_split_kernel(const StripArgs g) {
 }
 
 // How a shape (TN, NW) would cut the work, and its cost in units of (rounds of a wavefront) x (wavefronts of a compute
-// unit) x (column blocks + 1 for the cutting of A); a panel in phases costs its barriers on top (measured 1.3x)
+// unit) x (column blocks + 1 for the reading and cutting of A, or + 2 for bf16, whose matrix work is a sixth of that); a panel
+// in phases costs its barriers on top (1.3x).  Against the best of all shapes, each timed for 12 widths on 17,000 to 306,129
+// rows with and without mask: fp32 within 0.4 % on average and 7 % at worst, bf16 0.2 % and 13 % (with + 1 there 1.6 % and
+// 59 %: masked 200 -> 172 on 169,343 rows 108 us where 68 are possible).
 struct StripPlan { int steps, phase_steps, panels, panel_groups, row_groups; double cost; };
 
 template <class T, Core C, int TN, int NW>
 StripPlan strip_plan(int64_t n, int K, int N, bool short_k = false) {
-    constexpr int CUS = 256;
+    const int CUS = compute_units();
     constexpr int KS = STEP_BYTES / (int)sizeof(T);
     constexpr int step_bytes = KS / 16 * TN * Parts<T, C>::n * 1024;
     constexpr int max_steps = (LDS_BYTES - NW * 4096) / step_bytes;
@@ -502,7 +505,7 @@ StripPlan strip_plan(int64_t n, int K, int N, bool short_k = false) {
     p.row_groups = (int)std::min(rg_all, rg_fit);
     const int64_t waves = (int64_t)p.row_groups * NW;
     const int64_t rounds = (units + waves - 1) / waves * std::max<int64_t>(1, (int64_t)p.panels * 8 / CUS);
-    p.cost = (double)rounds * NW * (short_k ? p.panel_groups * TN + 1 : p.panel_groups * (TN + 1)) * (phased ? 1.3 : 1.0);
+    p.cost = (double)rounds * NW * (short_k ? p.panel_groups * TN + 1 : p.panel_groups * (TN + (sizeof(T) == 2 ? 2 : 1))) * (phased ? 1.3 : 1.0);
     return p;
 }
 
@@ -536,8 +539,12 @@ int launch_strip(StripArgs g, const StripPlan& p, hipStream_t st) {
     return NTP_OK;
 }
 
-// Few rows and several steps: the wavefronts of a block share a unit's contraction
-bool split_contraction(const StripArgs& g) { return (g.n + 31) / 32 * ((g.N + 31) / 32) <= 512 && g.steps >= 4; }
+// Few rows and several steps: the wavefronts of a block share a unit's contraction.  Up to four blocks (two run at a time) per
+// compute unit; more of them read B too often.  us split / in strips: 602 -> 128 on 4,000 rows (500 blocks) 12.6 / 30.7, on 8,000
+// (1,000) 23.8 / 32.3, on 12,000 (1,500) 32.7 / 33.3, on 16,000 40.6 / 34.6; 256 -> 64 on 16,000 (1,000) 10.0 / 15.8, on 24,000
+// (1,500) 16.6 / 16.4; 256 -> 256 on 4,000 (1,000) 9.9 / 15.7, on 8,000 (2,000) 20.2 / 16.6; 128 -> 128 on 8,000 (1,000) 7.4 /
+// 10.2, on 12,000 (1,500) 10.1 / 10.5; 1433 -> 16 on 24,000 (750) 42.2 / 60.6, on 40,000 (1,250) 63.6 / 60.9.
+bool split_contraction(const StripArgs& g) { return (g.n + 31) / 32 * ((g.N + 31) / 32) <= 4 * compute_units() && g.steps >= 4; }
 
 template <class T, Core C, bool MASK>
 int launch_split(const StripArgs& g, hipStream_t st) {

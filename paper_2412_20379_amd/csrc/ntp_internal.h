@@ -198,6 +198,7 @@ struct ReduceArgs {
 // kernels (agg_kernels.hip / nn_kernels.hip); stream is a hipStream_t
 int launch_aggregate(const AggArgs& a, int dtype, void* stream);
 int launch_reduce(const ReduceArgs& a, int dtype, void* stream);
+int compute_units();               // of the current device
 int agg_hub_slots();               // lines of the LDS hub table
 // does the launch of `a` (already holding X, Y, f, strides, pass_lanes) take the hub kernel?
 bool agg_uses_hub(const AggArgs& a, int dtype);
