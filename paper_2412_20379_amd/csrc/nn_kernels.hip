@@ -2,15 +2,15 @@
 // gradients dW = A^T dZ, dA = dZ W^T with dZ = dH * 1[H > 0].
 //
 // The products run on the bf16 matrix instructions (v_mfma_f32_32x32x16_bf16): every fp32 operand element is cut into three
-// bf16 pieces hi + mid + lo = x (exact: 3 x 8 significant bits, by truncation), and a product a*b is formed as the
-// six piece products of weight >= 2^-16 (hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi), each exact in the fp32
-// accumulator's input.  Truncation leaves mid < 2^-7 |x| and lo < 2^-15 |x|, so the three products left out are below
-// 2^-21 |a b| together, which sums of 64 and more terms do not show: rms error over the sum of magnitudes at 64 / 256 / 602
-// terms 2.4e-8 / 2.4e-8 / 2.4e-8 (positive terms 0.9e-7 / 1.9e-7 / 3.3e-7) against 2.8e-8 (1.2e-7 / 2.2e-7 / 3.8e-7) of the
-// fp32 instructions, which round more often.  Six bf16 instructions cost 6 x 32 cycles per 32x32x16 block against 8 x 64 for fp32, and operands
-// that are bf16 in memory need one piece only.  fp32 products with a contraction below 64 or an output of up to 32 columns
-// run on the fp32 instructions (fp32_core below).  H and dA: nn_strip_kernels.hip; dW: nn_dw_kernels.hip, partial sums to
-// the caller's workspace, added in order here (deterministic, no atomics).
+// bf16 pieces hi + mid + lo = x (exact: 3 x 8 significant bits, by truncation), and a product a*b is formed as the six
+// piece products of weight >= 2^-16 (hi*hi, hi*mid, mid*hi, mid*mid, hi*lo, lo*hi), each exact in the fp32 accumulator's
+// input.  Truncation leaves mid < 2^-7 |x| and lo < 2^-15 |x|, so the three products left out are below 2^-21 |a b|
+// together, which sums of 64 and more terms do not show: rms error over the sum of magnitudes at 64 / 256 / 602 terms
+// 2.4e-8 / 2.4e-8 / 2.4e-8 (positive terms 0.9e-7 / 1.9e-7 / 3.3e-7) against 2.8e-8 (1.2e-7 / 2.2e-7 / 3.8e-7) of the fp32
+// instructions, which round more often.  Six bf16 instructions cost 6 x 32 cycles per 32x32x16 block against 8 x 64 for
+// fp32, and operands that are bf16 in memory need one piece only.  fp32 products with a contraction below 64 or an output
+// of up to 32 columns run on the fp32 instructions (fp32_core below).  H and dA: nn_strip_kernels.hip; dW:
+// nn_dw_kernels.hip, partial sums to the caller's workspace, added in order here (deterministic, no atomics).
 //
 // This file holds the dispatch, the sum over partial sums and the activation on its own.
 #include <hip/hip_runtime.h>

@@ -228,46 +228,46 @@ __device__ __forceinline__ void fill_panel(const StripArgs& g, uint4* lds, int c
 template <class T, int TN>
 __device__ __forceinline__ void store_unit(const StripArgs& g, const f32x16 (&acc)[1][TN], int u, int cb, int lane) {
     const int r = lane & 31, h = lane >> 5, N = g.N;
-                const bool relu = g.relu != 0;
-                const int64_t rbase = (int64_t)u * 32 + 4 * h;
-                const int64_t left64 = g.n - rbase;
-                const int rows_left = left64 > 32 ? 32 : (int)left64;
-                            const bool whole = (int64_t)(u + 1) * 32 <= g.n && cb + 32 * TN <= N;      // no tests needed
-                if (sizeof(T) == 2 && g.interleave) {
-                    T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + r * TN;
-                    const bool in = cb + r * TN < N;          // N is a multiple of TN
-    #pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        float v[TN];
-    #pragma unroll
-                        for (int j = 0; j < TN; ++j) v[j] = relu ? (acc[0][j][e] > 0.f ? acc[0][j][e] : 0.f) : acc[0][j][e];
-                        if (whole || (in && 8 * (e / 4) + (e % 4) < rows_left)) store_bf16<TN>(p, v, g.nt != 0);
-                        p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
-                    }
-                } else if (whole && g.nt) {
-    #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + j * 32 + r;
-    #pragma unroll
-                        for (int e = 0; e < 16; ++e) {
-                            const float v = acc[0][j][e];
-                            stream_elem(p, relu ? (v > 0.f ? v : 0.f) : v);
-                            p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
-                        }
-                    }
-                } else {
-    #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + j * 32 + r;
-                        const int lim = cb + j * 32 + r < N ? rows_left : 0;
-    #pragma unroll
-                        for (int e = 0; e < 16; ++e) {
-                            const float v = acc[0][j][e];
-                            if (8 * (e / 4) + (e % 4) < lim) store_elem(p, relu ? (v > 0.f ? v : 0.f) : v);
-                            p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
-                        }
-                    }
-                }
+    const bool relu = g.relu != 0;
+    const int64_t rbase = (int64_t)u * 32 + 4 * h;
+    const int64_t left64 = g.n - rbase;
+    const int rows_left = left64 > 32 ? 32 : (int)left64;
+    const bool whole = (int64_t)(u + 1) * 32 <= g.n && cb + 32 * TN <= N;      // no tests needed
+    if (sizeof(T) == 2 && g.interleave) {
+        T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + r * TN;
+        const bool in = cb + r * TN < N;          // N is a multiple of TN
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            float v[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) v[j] = relu ? (acc[0][j][e] > 0.f ? acc[0][j][e] : 0.f) : acc[0][j][e];
+            if (whole || (in && 8 * (e / 4) + (e % 4) < rows_left)) store_bf16<TN>(p, v, g.nt != 0);
+            p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+        }
+    } else if (whole && g.nt) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + j * 32 + r;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float v = acc[0][j][e];
+                stream_elem(p, relu ? (v > 0.f ? v : 0.f) : v);
+                p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            T* p = static_cast<T*>(g.C) + rbase * g.ldc + cb + j * 32 + r;
+            const int lim = cb + j * 32 + r < N ? rows_left : 0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float v = acc[0][j][e];
+                if (8 * (e / 4) + (e % 4) < lim) store_elem(p, relu ? (v > 0.f ? v : 0.f) : v);
+                p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+            }
+        }
+    }
 }
 
 // PHASED: the panel (one column group) does not fit in LDS; its contraction steps come in phases of
