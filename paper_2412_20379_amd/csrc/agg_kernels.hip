@@ -12,11 +12,14 @@
 //     partial sums to a scratch slot; reduce_kernel adds the slots of a row in order.
 // No atomics anywhere: the result is deterministic.
 //
-// What bounds it: lines that miss the L2 arrive at 53-56 G lines/s whatever the kernel does, lines that hit pass the
-// address unit of the compute unit (24 cycles per 64-lane 16-byte load, busy 85-92 % of this kernel's time).  In between
-// stands the latency of everything a gather depends on, because a wavefront's loads complete in order: a gather issued
-// after a load of (index, weight) pairs returns after it, at memory latency.  Hence few and wide loads in front of the
-// gathers:
+// What bounds it: lines that miss the L2 arrive at 53-56 G lines/s whatever the kernel does (63 M entries, F = 32:
+// 55.5). Where most lines hit, the kernel asks for 119-136 G lines/s (F = 128 on 7.2 M entries, three quarters of them
+// hits, 119; F = 76 on 28.8 M 136; all in the L2 132); bare loads of the same shape pass at 240-250, and at 146 with
+// ids and weights read beside them.  (The address unit of the compute unit reads busy for 86-91 % of these launches,
+// but that counts its waiting for the L1: 23 to 41 busy cycles per load, where the bare loads pass one every 20.)  In
+// between stands the latency of everything a gather depends on, because a wavefront's loads complete in order: a gather
+// issued after a load of (index, weight) pairs returns after it, at memory latency.  Hence few and wide loads in front
+// of the gathers:
 //   - row ids and row pointers of all rows of a wavefront are read at its start, one row per lane, and handed out through
 //     the cross-lane network;
 //   - 256 pairs are fetched at a time for a row of its own; a lane group fetches four consecutive pairs per lane: the whole
