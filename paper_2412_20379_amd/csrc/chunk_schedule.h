@@ -13,32 +13,39 @@
 namespace ntp {
 
 // How the parts of a streamed chunk travel.
-//   COPY_ON_COMPUTE   everything by a kernel on the compute stream: no event, no second stream
-//   COPY_META_ON_COMPUTE  entries by DMA on two copy streams in turn (one per buffer; the 20-30 us it takes to start a copy pass
-//                     while the other one is on the link), row pointers and lists by a kernel on the compute stream
-//   COPY_ON_COPY      the same with the row pointers and lists behind the entries on the copy stream
-enum CopyPath { COPY_ON_COMPUTE, COPY_META_ON_COMPUTE, COPY_ON_COPY };
+struct CopyPath {
+    bool dma;               // entries by DMA on a copy stream; else everything by a kernel on the compute stream (no event)
+    bool two_streams;       // the buffers have a copy stream each: the 20-60 us it takes to start a copy pass while the other
+                            // one is on the link; else the caller's copy stream takes all copies, one after the other
+    bool meta_on_compute;   // row pointers and lists by a kernel on the compute stream, else by one behind the entries
+};
 
 // The path for a pass whose streamed chunks have, on average, `bytes` to copy and `entries` entries to aggregate into n_rhs
-// right-hand sides of `lines` cache lines a row; largest: bytes of the largest one.
-//   Up to 3/4 MB a copy by DMA with its events and second stream (50-70 us a chunk whatever its size) costs more than it
-//   hides.  us a pass over 2.0 M entries, one right-hand side of 32 columns / eight, everything on the compute stream
-//   against entries by DMA: chunks of 0.1 M entries (0.5 MB) 846 / 1992 against 840 / 2193, 0.2 M 512 / 1099 against 455 / 1141,
-//   0.3 M 408 / 824 against 338 / 822, 0.4 M (1.8 MB) 341 / 660 against 266 / 621.
-//   Above, the link is the bound until the aggregation of a chunk takes about as long as its copy: then the row pointers
-//   and lists (a fifth of the bytes at 15 entries a row), copied on the compute stream, are time that the aggregation
-//   cannot have.  On the compute / copy stream: 4 chunks of 4 M entries F = 32 1268 / 1314, F = 128 1316 / 1376, F = 256 1539 /
-//   1469, 8 x 32 columns 1971 / 1821; 11 of 0.4 M F = 32 669 / 682, F = 128 862 / 803, F = 256 1096 / 1016, 8 x 32 1581 / 1543.
-//   Estimates: 56 GB/s on the link; 10 us a launch and 100 G lines/s in the aggregation.  The line lies at 0.7 of the copy.
+// right-hand sides of `lines` cache lines a row; largest: bytes of the largest one.  Estimates: 56 GB/s on the link; 10 us a
+// launch and 100 G lines/s in the aggregation.
+//   Up to 3/4 MB a copy by DMA with its events (50-70 us a chunk whatever its size) costs more than it hides.  us a pass over
+//   2.0 M entries, one right-hand side of 32 columns / eight, all on the compute stream against DMA: chunks of 0.1 M entries
+//   (0.5 MB) 846 / 1992 against 840 / 2193, 0.2 M 512 / 1099 against 455 / 1141, 0.3 M 408 / 824 against 338 / 822, 0.4 M (1.8 MB)
+//   341 / 660 against 266 / 621.
+//   Two copies at a time share the link and both arrive late, and the aggregation with them; its time then shows at the ends of
+//   a pass.  Hence one at a time where the aggregation is long (0.4 of the copy) and the start of a copy is short against it.
+//   us a pass from rest, two streams / one: 4 chunks of 16 M entries, 4 x 32 columns 6539 / 5642, F = 256 9171 / 7835;
+//   4 of 4 M F = 256 2063 / 1714; but pass after pass 8 of 2 M F = 128 1499 / 1630.
+//   The row pointers and lists (a fifth of the bytes at 15 entries a row) are copied on the compute stream until the
+//   aggregation cannot spare the time (0.7 of the copy).  On the compute / copy stream: 4 chunks of 4 M entries F = 32 1268 / 1314,
+//   F = 256 1511 / 1438, 8 x 32 columns 1852 / 1762; 11 of 0.4 M F = 32 669 / 682, F = 128 862 / 803, F = 256 1096 / 1016.
 inline CopyPath pick_copy_path(double bytes, double largest, double entries, int64_t lines, int n_rhs) {
-    if (largest <= 768 * 1024) return COPY_ON_COMPUTE;
     const double copy_us = bytes / 56e3, aggregate_us = n_rhs * (10.0 + entries * (double)lines * 1e-5);
-    return aggregate_us > 0.7 * copy_us ? COPY_ON_COPY : COPY_META_ON_COMPUTE;
+    CopyPath p;
+    p.dma = largest > 768 * 1024;
+    p.two_streams = p.dma && (aggregate_us < 0.4 * copy_us || copy_us < 200);
+    p.meta_on_compute = !p.dma || aggregate_us <= 0.7 * copy_us;
+    return p;
 }
 
 template <class Ops> struct StageState {
     typename Ops::Event ready[2] = {}, free_[2] = {}, join[2] = {};
-    typename Ops::Stream copy2 = {};        // buffer 1's copy stream (buffer 0's is the caller's)
+    typename Ops::Stream copy2 = {};        // buffer 1's copy stream where there are two (buffer 0's is the caller's)
     bool used[2] = {false, false};          // free_ has been recorded
     int next = 0;
 };
@@ -58,7 +65,7 @@ public:
 
     int begin() {
         open_ = true;
-        if (path_ == COPY_ON_COMPUTE) return 0;
+        if (!path_.two_streams) return 0;
         int rc = ops_.record(st_.join[0], xs_);        // the second copy stream starts where the caller's stands
         if (rc == 0) rc = ops_.wait(st_.copy2, st_.join[0]);
         forked_ = rc == 0;
@@ -67,32 +74,32 @@ public:
     template <class Chunk> int streamed(const Chunk& c) {
         const int b = st_.next;
         st_.next ^= 1;
-        const Stream ks = path_ == COPY_ON_COMPUTE ? cs_ : copy_stream(b);
+        const Stream ks = path_.dma ? copy_stream(b) : cs_;
         int rc = 0;
         // the buffer may still be read by the kernels of the chunk that used it last (of an earlier pass: on any stream)
         if (st_.used[b] && !touched_[b]) rc = ops_.wait(cs_, st_.free_[b]);
-        if (rc == 0 && st_.used[b] && path_ != COPY_ON_COMPUTE) rc = ops_.wait(ks, st_.free_[b]);
+        if (rc == 0 && st_.used[b] && path_.dma) rc = ops_.wait(ks, st_.free_[b]);
         if (rc != 0) return rc;
         touched_[b] = held_[b] = true;
-        if (path_ != COPY_ON_COMPUTE) {
+        if (path_.dma) {
             copying_[b] = true;
             rc = ops_.copy_entries(c, b, ks);
-            if (rc == 0 && path_ == COPY_ON_COPY) rc = ops_.copy_by_kernel(c, b, ks, false);
+            if (rc == 0 && !path_.meta_on_compute) rc = ops_.copy_by_kernel(c, b, ks, false);
             if (rc == 0) rc = ops_.record(st_.ready[b], ks);
         }
-        if (rc == 0 && path_ != COPY_ON_COPY) rc = ops_.copy_by_kernel(c, b, cs_, path_ == COPY_ON_COMPUTE);
-        if (rc == 0 && path_ != COPY_ON_COMPUTE) {
+        if (rc == 0 && path_.meta_on_compute) rc = ops_.copy_by_kernel(c, b, cs_, !path_.dma);
+        if (rc == 0 && path_.dma) {
             rc = ops_.wait(cs_, st_.ready[b]);
             if (rc == 0) copying_[b] = false;
         }
         if (rc == 0) rc = ops_.aggregate(c, b);
-        if (rc != 0 || path_ == COPY_ON_COMPUTE) return rc;
+        if (rc != 0 || !path_.dma) return rc;
         return release(b);
     }
     int end() { return close(); }
 
 private:
-    Stream copy_stream(int b) const { return b == 0 ? xs_ : st_.copy2; }
+    Stream copy_stream(int b) const { return b == 1 && path_.two_streams ? st_.copy2 : xs_; }
     int release(int b) {
         const int rc = ops_.record(st_.free_[b], cs_);
         if (rc == 0) { st_.used[b] = true; held_[b] = false; }

@@ -244,7 +244,8 @@ struct Recorder {
 
 void check_schedule() {
     const int COPY2 = 7;
-    for (int first = 0; first < 3; ++first)
+    const CopyPath paths[] = {{false, false, true}, {true, true, true}, {true, true, false}, {true, false, true}, {true, false, false}};
+    for (int first = 0; first < 5; ++first)
         for (int fail = -1; fail < 60; ++fail) {
             Recorder ops;
             StageState<Recorder> state;
@@ -257,7 +258,7 @@ void check_schedule() {
             for (int pass = 0; pass < 6; ++pass) {
                 // every pass on compute and copy streams of its own choice, without a wait in between
                 const int cs = (int)(rng.next() % 3), xs = 3 + (int)(rng.next() % 3);
-                const CopyPath path = (CopyPath)(pass == 0 ? first : rng.next() % 3);
+                const CopyPath path = paths[pass == 0 ? first : (int)(rng.next() % 5)];
                 ops.compute = cs;
                 for (auto& a : ops.last_copy) a = Recorder::Access();
                 ops.fail_in = pass == 0 ? fail : -1;
@@ -275,11 +276,14 @@ void check_schedule() {
             }
         }
     // the path: small chunks on the compute stream, larger ones by what bounds them
-    CHECK(pick_copy_path(700e3, 700e3, 150e3, 8, 8) == COPY_ON_COMPUTE, "small chunk");
-    CHECK(pick_copy_path(300e3, 900e3, 60e3, 1, 1) != COPY_ON_COMPUTE, "one larger chunk");
-    CHECK(pick_copy_path(17e6, 17e6, 4e6, 1, 1) == COPY_META_ON_COMPUTE, "4 M entries, F = 32: the link");
-    CHECK(pick_copy_path(17e6, 17e6, 4e6, 8, 1) == COPY_ON_COPY, "4 M entries, F = 256: the aggregation");
-    CHECK(pick_copy_path(17e6, 17e6, 4e6, 1, 8) == COPY_ON_COPY, "4 M entries, eight right-hand sides: the aggregation");
+    auto is = [](const CopyPath& p, bool dma, bool two, bool meta) { return p.dma == dma && p.two_streams == two && p.meta_on_compute == meta; };
+    CHECK(is(pick_copy_path(700e3, 700e3, 150e3, 8, 8), false, false, true), "small chunk");
+    CHECK(pick_copy_path(300e3, 900e3, 60e3, 1, 1).dma, "one larger chunk");
+    CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 1, 1), true, true, true), "4 M entries, F = 32: the link");
+    CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 4, 1), true, false, true), "4 M entries, F = 128: both");
+    CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 8, 1), true, false, false), "4 M entries, F = 256: the aggregation");
+    CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 1, 8), true, false, false), "4 M entries, eight right-hand sides: the aggregation");
+    CHECK(is(pick_copy_path(2e6, 2e6, 4e5, 8, 1), true, true, false), "0.4 M entries, F = 256: the aggregation, short copies");
 }
 
 }  // namespace
