@@ -264,13 +264,15 @@ int pow2_up(int64_t x, int most) {
 
 // The shape of a wavefront tile and how the work is cut.
 //   k < 4 (no whole vector of four columns of A): 32 x 32 read element by element, up to eight column tiles side by side
-//   (2 x 64 on 306,129 rows 0.025 ms against 0.111 in tiles through LDS, 3 x 256 0.077 against 0.186);
+//     (2 x 64 on 306,129 rows 0.025 ms against 0.111 in tiles through LDS, 3 x 256 0.077 against 0.186);
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
-//   against 39.1 us);  k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);  else 128 x 64, whose operands
-//   are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343 rows 0.134 against 0.164 ms.
-// m <= 32 and k > 256 take four row tiles side by side: whole rows of A from few blocks (us with one / four, 602 x 16 on 16,000
-// rows 27.3 / 22.5, 50,000 54.7 / 46.9, 200,000 195 / 162; 1433 x 16 on 30,000 75.2 / 70.5; 256 x 16 on 120,000 33.6 / 35.5, so
-// not there; 602 x 16 on 8,000 13.9 / 16.4: the few rows of a block are better shared out).
+//     against 39.1 us);
+//   k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
+//   else 128 x 64, whose operands are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343
+//     rows 0.134 against 0.164 ms.
+// m <= 32 and more than three row tiles of A take four of them side by side: whole rows of A from few blocks (us with one /
+// four, 602 x 16 on 16,000 rows 27.3 / 22.5, 50,000 54.7 / 46.9, 200,000 195 / 162; 1433 x 16 on 30,000 75.2 / 70.5; 256 x 16
+// on 120,000 33.6 / 35.5, so not there; 602 x 16 on 8,000 13.9 / 16.4: the few rows of a block are better shared out).
 // Blocks: about one per compute unit; two column tiles side by side where there are two (they share the rows of A through the
 // L1), the other wavefronts share out the rows.
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY };
@@ -285,7 +287,7 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core) {
     g.n = n; g.k = (int)k; g.m = (int)m;
     const int shape = dw_shape(k, m, fp32_core);
     const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
-    g.kt = shape == DW_NARROW && k > 256 && n > 10000 ? 4 : 1;
+    g.kt = shape == DW_NARROW && k > 384 && n > 10000 ? 4 : 1;
     g.mt = shape == DW_NARROW ? 1 : pow2_up((m + 32 * tn - 1) / (32 * tn), shape == DW_TINY ? 8 : shape == DW_SHORT ? 4 : 2);
     g.tiles_k = (int)((k + 32 * ta * g.kt - 1) / (32 * ta * g.kt));
     g.tiles_m = (int)((m + 32 * tn * g.mt - 1) / (32 * tn * g.mt));
