@@ -331,7 +331,7 @@ def step_bench(args, cfg, scale_down=1, agg_dtype="f32", copy_gbs=None, graph=No
     roofline_nn = dict(bound="mfma",
                        kernel=("strip_kernel, dw_kernel (fp32 products from bf16 pieces, 6 bf16 MFMA per product; "
                                "peak = 2500/6), all transform calls of a step"
-                               if split_core else "gemm_kernel (fp32 MFMA, all transform calls of a step)"),
+                               if split_core else "strip_kernel, dw_kernel (fp32 MFMA, all transform calls of a step)"),
                        achieved=nn_tflops, peak=nn_peak, unit="TFLOP/s (useful fp32 flops)",
                        frac=(nn_tflops / nn_peak) if nn_tflops else None,
                        frac_of_fp32_mfma_peak=(nn_tflops / FP32_MFMA_PEAK_TFLOPS) if nn_tflops else None, traffic=None)

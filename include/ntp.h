@@ -189,17 +189,17 @@ int ntp_aggregate_bwd(ntp_graph_t* g, const void* Gout, void* Gin,
  * graph built with another chunking the result agrees to rounding, not in every bit: rows too
  * long for one wavefront are summed in pieces whose length follows the chunk size.  For one
  * graph the result is the same whether a chunk is resident or streamed, and from call to call.
- * Resident chunks are aggregated in place; every other chunk is copied from pinned host
- * memory into one of two device staging buffers.  Chunks of more than 768 KB are copied by
- * DMA on copy_stream (and on a second stream of the handle in turn, where the link bounds the
- * call or the copies are short) while the previous chunk is aggregated on compute_stream; events
- * order them, and copy_stream ends behind all copies.  Their row pointers and lists are copied by
- * a kernel, on compute_stream where the link bounds the call, else behind the entries.  Smaller
- * chunks are copied by a kernel on compute_stream, which costs
- * less than a DMA copy and its events.  X and Y stay on the device for the whole call.  Works for fully resident graphs too.  On return all work is enqueued;
- * compute_stream has been made to wait for the copies it needs, and the staging buffers
- * are protected across calls by events.  copy_stream must differ from compute_stream
- * when any chunk is streamed (NTP_EINVAL otherwise).
+ * Resident chunks are aggregated in place; every other chunk is copied from pinned host memory
+ * into one of two device staging buffers.  Chunks of more than 768 KB are copied by DMA on
+ * copy_stream (and on a second stream of the handle in turn, where the link bounds the call or the
+ * copies are short) while the previous chunk is aggregated on compute_stream; events order them,
+ * and copy_stream ends behind all copies.  Their row pointers and lists are copied by a kernel, on
+ * compute_stream where the link bounds the call, else behind the entries.  Smaller chunks are
+ * copied by a kernel on compute_stream, which costs less than a DMA copy and its events.  X and Y
+ * stay on the device for the whole call.  Works for fully resident graphs too.  On return all work
+ * is enqueued; compute_stream has been made to wait for the copies it needs, and the staging
+ * buffers are protected across calls by events.  copy_stream must differ from compute_stream when
+ * any chunk is streamed (NTP_EINVAL otherwise).
  */
 int ntp_chunked_aggregate(ntp_graph_t* g, int direction, const void* X, void* Y,
                           int64_t f_slice, int64_t ldx, int64_t ldy, int dtype,

@@ -149,7 +149,7 @@ def test_relu_alone(n, f, ld, dtype):
 def test_wide_dynamic_range_keeps_fp32_accuracy(n, k, m):
     """Operands whose magnitudes span six decades: the transform (whose default core forms
     fp32 products from bf16 pieces) must stay at fp32-class accuracy, far inside the
-    tolerance: every piece product that matters at 2^-23 has to be there."""
+    tolerance: every piece product of weight 2^-16 and more has to be there."""
     import torch
     from gpu_util import dev_f32
     from helpers import rel_errors
