@@ -301,8 +301,8 @@ void* alloc_large(size_t bytes) {
 // How it works.  Every thread takes a slice of the edge list, counts and then writes its entries (row, neighbour) into
 // buckets of consecutive rows; a bucket is then sorted by row and neighbour while it sits in one core's cache.  Every edge
 // is read twice, whatever the number of threads.  (Threads that owned row ranges and each read the whole edge list, and a
-// stable_sort call per row, made the build of a 1.2 M-edge graph 27.3 ms on 16 threads; 6.4 with this, both with upload and
-// export of the arrays.)
+// stable_sort call per row, made the build of a 1.2 M-edge graph, with upload and export of the arrays, 26.2 ms on 16
+// threads; 6.9 with this.)
 int build_host_graph(int64_t n, int64_t n_edges, const int32_t* src, const int32_t* dst,
                      const float* edge_weight, uint32_t flags, EntryAllocator alloc,
                      BuiltGraph* out) {

@@ -10,11 +10,11 @@
 // wavefronts is a few neighbouring tiles x shares of the rows of one range of vertices; the shares are added through
 // LDS in a fixed order, the ranges by sum_splits_kernel: deterministic.
 //
-// Bound: memory for a narrow side (256 x 64 on 169,343 rows: 217 MB in 0.043 ms = 5.0 TB/s), the matrix pipe and the power
-// it takes otherwise (256 x 256: 0.139 ms, the matrix instructions alone about 0.09).  Against 128 x 128 tiles cut through LDS
-// behind barriers, which this replaces (169,343 rows, fp32, without / with the ReLU mask): 256 x 256 0.147 / 0.185 -> 0.139 /
-// 0.161 ms, 128 x 256 0.085 / 0.108 -> 0.074 / 0.097, 256 x 64 0.065 / 0.149 -> 0.044 / 0.052, 256 x 40 0.061 / 0.132 -> 0.042 /
-// 0.046; 58,241 rows of 128 x 64 0.037 / 0.070 -> 0.020 / 0.023.
+// Bound: memory for a narrow side (256 x 64 on 169,343 rows: 217 MB in 0.043 ms = 5.0 TB/s), the two pipes of the SIMD
+// otherwise (256 x 256: matrix instructions 49 % of the time, other vector instructions 40 %, half of them beside those).
+// Against 128 x 128 tiles cut through LDS behind barriers, which this replaces (169,343 rows, fp32, without / with the ReLU
+// mask): 256 x 256 0.147 / 0.185 -> 0.139 / 0.161 ms, 128 x 256 0.085 / 0.108 -> 0.074 / 0.097, 256 x 64 0.065 / 0.149 ->
+// 0.044 / 0.052, 256 x 40 0.061 / 0.132 -> 0.042 / 0.046; 58,241 rows of 128 x 64 0.037 / 0.070 -> 0.020 / 0.023.
 // m <= 32 runs on the fp32 matrix instructions (the rule is in nn_kernels.hip), which bound it as much as memory does:
 // 256 x 16 0.042 ms against 0.037 with pieces and 0.044 in the fp32 tiles replaced (masked 0.042 / 0.040 / 0.050).
 #include <hip/hip_runtime.h>

@@ -8,20 +8,20 @@
 // multiplied with the panel, 32 * TN columns at a time; the next two steps are in flight meanwhile.  Nobody waits for
 // another wavefront, so the cutting, loads and stores of one run under the matrix instructions of the others.
 // The blocks that work on the same rows (the panels of a row group) have ids that differ by 8, hence sit on one XCD, and
-// all but the first reader find the rows in its L2 (692 MB of re-reads at 17 TB/s measured alone).
+// all but the first reader find the rows in its L2 (256 -> 256 on 169,343 rows: 182 MB fetched for 173 MB of A).
 //
 // Bound.  Narrow outputs: memory (256 -> 40 on 169,343 rows: 200 MB in 0.040 ms = 5.0 TB/s, the rate of a large
-// copy).  256 -> 256: the matrix pipe at the clock that power allows (alone 0.067 ms at 2.3 GHz; together with
-// the cutting and LDS reads the chip drops to 1.8-2.0 GHz and 0.091 ms) plus 0.35 GB of traffic that
-// overlaps it only in part.  Against the 128 x 128 tiles of both operands cut through LDS behind barriers that this replaces
-// (169,343 rows, fp32): 256 -> 256 0.158 -> 0.136 ms, 128 -> 256 0.086 -> 0.077, 256 -> 40 0.048 -> 0.040, dA 256 -> 256
-// masked 0.183 -> 0.163; 602 -> 128 on 58,241 rows 0.086 -> 0.063 (bf16 0.112 -> 0.034); bf16 256 -> 256 0.080 -> 0.062, its
-// dA 0.061 -> 0.045 (masked 0.090 -> 0.061).
+// copy).  256 -> 256: the two pipes of the SIMD, at the 2.0 GHz that power leaves: 47 % of the time matrix instructions, 33 %
+// other vector instructions (the cutting), half of which run beside them.  Against the 128 x 128 tiles of both operands cut
+// through LDS behind barriers that this replaces (169,343 rows, fp32): 256 -> 256 0.158 -> 0.136 ms, 128 -> 256 0.086 -> 0.077,
+// 256 -> 40 0.048 -> 0.040, dA 256 -> 256 masked 0.183 -> 0.163; 602 -> 128 on 58,241 rows 0.086 -> 0.063 (bf16 0.112 -> 0.034);
+// bf16 256 -> 256 0.080 -> 0.062, its dA 0.061 -> 0.045 (masked 0.090 -> 0.061).  The three products of a masked 256 x 256 layer on
+// 306,129 rows together 0.89 -> 0.82 ms.
 //
 // Contractions below 64 and outputs of up to 32 columns keep B as floats and run on the fp32 matrix instructions, whose
-// products are exact (the rule is in nn_kernels.hip): their time adds to that of memory instead of hiding under it, dA
-// 40 -> 256 0.061 ms (masked 0.064) against 0.046 (0.050) with pieces and 0.069 (0.080) in the fp32 tiles replaced;
-// 256 -> 16 0.035 against 0.034 and 0.040; 1433 -> 16 on 60,000 rows 0.078 against 0.087 and 0.108.
+// products are exact (the rule is in nn_kernels.hip): no other vector instruction runs beside one, so their time adds to the
+// rest instead of hiding under it, dA 40 -> 256 0.061 ms (masked 0.064) against 0.046 (0.050) with pieces and 0.069 (0.080) in
+// the fp32 tiles replaced; 256 -> 16 0.035 against 0.034 and 0.040; 1433 -> 16 on 60,000 rows 0.078 against 0.087 and 0.108.
 // Reading A in operand layout straight from memory (a lane = a row) instead of through LDS costs 32 line look-ups per
 // instruction instead of 8: 256 -> 256 0.200 ms.
 #include <hip/hip_runtime.h>
