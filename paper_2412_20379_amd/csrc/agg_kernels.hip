@@ -351,8 +351,17 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
             } else {
                 const int64_t over = e + EPL - a.e_end;
                 shift = over > 0 ? (int)over : 0;
-                fc = __builtin_nontemporal_load(reinterpret_cast<const Int4*>(cbase + e - shift));
-                fw = __builtin_nontemporal_load(reinterpret_cast<const Float4*>(vbase + e - shift));
+                const Int4* pc = reinterpret_cast<const Int4*>(cbase + e - shift);
+                const Float4* pw = reinterpret_cast<const Float4*>(vbase + e - shift);
+                if (a.past_caches) {
+                    fc = __builtin_nontemporal_load(pc);
+                    fw = __builtin_nontemporal_load(pw);
+                    asm volatile("");          // keeps the compiler from making one plain load of the two kinds
+                } else {
+                    asm volatile("");
+                    fc = *pc;
+                    fw = *pw;
+                }
             }
         }
     };

@@ -152,8 +152,8 @@ inline int bin_max_degree(int b) { return b == 0 ? 1 : (b == NBINS - 1 ? INT_MAX
 
 // Enqueue the kernels of one chunk whose image lives at `img` on the device.
 // scatter: Y[colidx[k], :] += val[k] * X[row, :] instead of Y[row, :] = sum val[k] * X[colidx[k], :]
-// weights: caller's edge weights in the entry order of the form (nullptr: the stored ones)
-int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* partial,
+// weights: caller's edge weights in the entry order of the form (nullptr: the stored ones); n: rows of X
+int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y, float* partial,
               int64_t f, int64_t ldx, int64_t ldy, int dtype, hipStream_t st, bool scatter = false,
               const float* weights = nullptr, bool defer_reduce = false,
               const int32_t* hub_cols = nullptr, int n_hub = 0, const Epilogue& epi = Epilogue()) {
@@ -177,6 +177,13 @@ int run_chunk(const Chunk& c, const char* img, const void* X, void* Y, float* pa
     a.ldy = ldy;
     a.f = (int32_t)f;
     a.fp = (int32_t)((f + 7) / 8 * 8);
+    // Indices and weights from the Infinity Cache (256 MB, which non-temporal loads pass by) where they fit in it together with
+    // X: a wavefront's gathers wait behind its load of pairs, and that returns sooner.  us past the caches / through them:
+    // 2.5 M entries, F = 256 235 / 217 (F = 128 123 / 113, F = 40 67 / 60); 7.2 M, F = 128 245 / 214; 28.8 M, F = 76 in bf16 (230 MB
+    // and 30 MB of X) 496 / 470, in fp32 (230 + 45) 671 / 635.  Where they do not fit they only displace rows of X: 26 M
+    // entries of two forms (210 + 78) 311 / 318, 63 M (505 + 157) 686 / 706.
+    const int64_t es = dtype == NTP_BF16 ? 2 : 4, x_row = std::min(ldx * es, (f * es + 127) / 128 * 128);
+    a.past_caches = (c.e_end - c.e_begin) * 8 + n * x_row > 280000000;
 
     int L, nacc = 1, passes = 1;
     if (scatter) {
@@ -377,7 +384,7 @@ struct ChunkKernels {
     const Epilogue& epi;
     int operator()(const Chunk& c, const char* img) const {
         for (int r = 0; r < n_rhs; ++r) {
-            const int e = run_chunk(c, img, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
+            const int e = run_chunk(c, F.m->n, img, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
                                     scatter, nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
             if (e != NTP_OK) return e;
         }
@@ -750,7 +757,7 @@ static int aggregate_resident(ntp_graph_t* g, int which, const void* X, void* Y,
     }
     if (rc != NTP_OK) return rc;
     for (auto& c : F.plan.chunks) {
-        rc = run_chunk(c, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
+        rc = run_chunk(c, g->g.n, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
                        F.d_hub_cols, (int)F.plan.hub_cols.size());
         if (rc != NTP_OK) return rc;
     }
