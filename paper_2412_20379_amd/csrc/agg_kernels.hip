@@ -25,6 +25,8 @@
 //   - 256 pairs are fetched at a time for a row of its own; a lane group fetches four consecutive pairs per lane: the whole
 //     of R rows of up to 4 L entries, or of several times R shorter rows; the next fetch is issued before the gathers of
 //     this one;
+//   - resident chunks keep the entries of rows of up to 128 a second time, in the order in which wavefronts take them (slices and
+//     packed rows, ntp_internal.h), so that these loads are whole lines of a wavefront's own;
 //   - absent entries are masked out, not loaded (one lane group shares its wavefront with rows of the same length: the
 //     row lists are sorted by length inside small windows).
 // Measured (one call, before -> after): 2.5 M-entry R-MAT graph F = 256 258 -> 229 us, bf16 152 -> 119; 7.2 M-entry Zipf
@@ -217,10 +219,10 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     constexpr int U = NACC == 4 || L == 2 ? 2 : 4;
 
     const int lane = threadIdx.x & 63;
-    int grp = 0;
-    while (grp + 1 < a.n_groups && wave >= a.wave_start[grp + 1]) ++grp;
+    const int grp = agg_group_of(a, wave);
+    const AggGroup G = a.group[grp];
     const int item0 = wave - a.wave_start[grp];
-    const int mode = a.mode[grp];
+    const int mode = G.mode;
     const int g = lane / L;
     const int l = lane % L;
     const int colbase = pass * PASS_W + l * VEC;
@@ -329,18 +331,20 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         for (int u = 0; u < U; ++u) multiply_add(on(u) ? w[u] : 0.f, x[u]);
     };
     // entry k of the form (chunk): column id cbase[k], weight vbase[k]
-    const int32_t* const cbase = (HUB ? a.colidx_hub : a.colidx) - a.e_base;
-    const float* const vbase = a.val - a.e_base;
+    const bool packed = !HUB && G.packed;
+    const int32_t* const cbase = packed ? a.packed_colidx : (HUB ? a.colidx_hub : a.colidx) - a.e_base;
+    const float* const vbase = packed ? a.packed_val : a.val - a.e_base;
+    const int64_t e_end = packed ? a.packed_end : a.e_end;
     const int64_t* const rp = a.rowptr - a.row_base;
-    const int32_t* const rows = a.rows + a.item_off[grp];
-    const int count = a.item_count[grp];
-    const int K = a.per_wave[grp];
+    const int32_t* const rows = a.rows + G.item_off;
+    const int count = G.item_count;
+    const int K = G.per_wave;
     // The pairs fetched ahead: entries e .. e + 3 of a lane, of which the first `left` belong to the row (the others are
     // never used).  The last lanes of the chunk read its last four entries and are `shift` ahead of themselves.
     Int4 fc = 0;
     Float4 fw = 0.f;
     int shift = 0;
-    const bool few = a.e_end - a.e_base < EPL;
+    const bool few = !packed && a.e_end - a.e_base < EPL;
     auto fetch = [&](const int64_t e, const int left) {
         shift = 0;
         if (left > 0) {
@@ -349,7 +353,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
                 for (int q = 0; q < EPL; ++q)
                     if (q < left) { fc[q] = cbase[e + q]; fw[q] = vbase[e + q]; }
             } else {
-                const int64_t over = e + EPL - a.e_end;
+                const int64_t over = e + EPL - e_end;
                 shift = over > 0 ? (int)over : 0;
                 const Int4* pc = reinterpret_cast<const Int4*>(cbase + e - shift);
                 const Float4* pw = reinterpret_cast<const Float4*>(vbase + e - shift);
@@ -387,7 +391,13 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     int mrow = 0, md = 0;
     int64_t mb = 0;
     auto read_rows = [&](const int first, const int n) {
-        if (lane < n) {
+        if (lane >= n) return;
+        if (packed) {
+            const PackedRow p = a.packed_rows[G.item_off + first + lane];
+            mrow = p.row;
+            mb = p.e_begin;
+            md = p.len;
+        } else {
             mrow = rows[first + lane];
             const Long2 t = *reinterpret_cast<const Long2*>(rp + mrow);
             mb = t[0];
@@ -402,7 +412,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         const int first = item0 * K * R;
         const int n_rows = min(K * R, count - first);
         read_rows(first, n_rows);
-        const int S = a.per_fetch[grp];
+        const int S = G.per_fetch;
         const int lpi = L / S;                              // lanes of a group per row and fetch
         const int fl = EPL * (l & (lpi - 1)), fs = l / lpi;
         auto fetch_rows = [&](const int k, const int k0) {
@@ -450,20 +460,91 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         return;
     }
 
+    if (!HUB && R > 1 && mode == MODE_SLICE) {
+        // ---- one group of L lanes per row, entries from the slices ---------------------
+        // A fetch brings a lane four entries: S = L / chunks rows of each group (a row of more than L chunks takes several).
+        const int first = item0 * K * R;
+        const int n_rows = min(K * R, count - first);
+        int mbase = 0;                 // first chunk and number of chunks of the slice of row `lane`
+        if (lane < n_rows) {
+            mrow = rows[first + lane];
+            const int s = G.slice_off + (first + lane) / SLICE_ROWS;
+            mbase = a.slice_base[s];
+            md = a.slice_base[s + 1] - mbase;
+        }
+        const int chunks = G.slice_chunks, S = G.per_fetch;
+        const int lpi = L / S;                              // lanes of a group per row and fetch
+        const int fl = l & (lpi - 1), fs = l / lpi;
+        auto fetch_rows = [&](const int k, const int c0) {
+            const int src = (k + fs) * R + g;
+            const int base = bperm_i(src & 63, mbase), n = bperm_i(src & 63, md);
+            fc = -1;
+            if (src < n_rows && c0 + fl < n) {
+                const int64_t at = (int64_t)(base + c0 + fl) * (4 * SLICE_ROWS) + (first + src) % SLICE_ROWS * 4;
+                const Int4* pc = reinterpret_cast<const Int4*>(a.slice_colidx + at);
+                const Float4* pw = reinterpret_cast<const Float4*>(a.slice_val + at);
+                if (a.past_caches) {
+                    fc = __builtin_nontemporal_load(pc);
+                    fw = __builtin_nontemporal_load(pw);
+                    asm volatile("");          // (as in fetch)
+                } else {
+                    asm volatile("");
+                    fc = *pc;
+                    fw = *pw;
+                }
+            }
+        };
+        int k = 0, c0 = 0;
+        fetch_rows(0, 0);
+        do {
+            const bool more = c0 + lpi < chunks;
+            const int kn = more ? k : k + S, cn = more ? c0 + lpi : 0;
+            put(GSTRIDE * g + EPL * l);
+            if (kn * R < n_rows) fetch_rows(kn, cn);
+            for (int s = 0; s < S; ++s) {
+                const int src = (k + s) * R + g;
+                if ((k + s) * R >= n_rows) break;
+                const int row = bperm_i(src & 63, mrow);
+                const int at = GSTRIDE * g + EPL * s * lpi;
+                for (int j0 = 0; j0 < lpi; ++j0) {
+                    const Int4 c4 = *reinterpret_cast<const IntL4*>(sc + at + EPL * j0);
+                    if (__ballot(c4[0] >= 0) == 0) break;
+                    const Float4 w4 = *reinterpret_cast<const FloatL4*>(sw + at + EPL * j0);
+#pragma unroll
+                    for (int q0 = 0; q0 < EPL; q0 += U) {
+                        int cj[U];
+                        float wj[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) { cj[u] = c4[q0 + u]; wj[u] = w4[q0 + u]; }
+                        if (__ballot(cj[U - 1] < 0) == 0) gather_u(cj, wj);
+                        else gather_u_if([&](int u) { return cj[u] >= 0; }, cj, wj);
+                    }
+                }
+                if (!more) {
+                    if (src < n_rows) store_row(static_cast<T*>(a.Y) + (int64_t)row * a.ldy + colbase, row);
+                    clear_acc();
+                }
+            }
+            k = kn;
+            c0 = cn;
+        } while (k * R < n_rows);
+        return;
+    }
+
     // ---- one wavefront per row or per segment ------------------------------------------
     int n_items = 1;
     float* pout = nullptr;
     if (!HUB && mode == MODE_BLOCK_PER_ROW) {
         // the block's four wavefronts take a quarter of the row each; the group is the first of
         // the launch, so item0 / 4 is the block and item0 % 4 the wavefront inside it
-        mrow = a.split_rows[a.item_off[grp] + (item0 >> 2)].row;
+        mrow = a.split_rows[G.item_off + (item0 >> 2)].row;
         const int64_t b0 = rp[mrow];
         const int64_t d = rp[mrow + 1] - b0;
         const int q = item0 & 3;
         mb = b0 + d * q / 4;
         md = (int)(b0 + d * (q + 1) / 4 - mb);
     } else if (mode == MODE_SEGMENT) {
-        const Segment* sp = a.segs + a.item_off[grp] + item0;
+        const Segment* sp = a.segs + G.item_off + item0;
         mrow = sp->row;
         mb = sp->e_begin;
         md = sp->len;
@@ -594,6 +675,49 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     }
 }
 
+// eight threads per row
+__global__ void __launch_bounds__(256) fill_slices_kernel(const int32_t* __restrict__ rows, int64_t n_rows, const int32_t* __restrict__ base,
+                                                          const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+                                                          const float* __restrict__ val, int32_t* __restrict__ out_c, float* __restrict__ out_v) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = t / 64 * SLICE_ROWS + t % SLICE_ROWS;       // place in the list
+    if (t / 64 >= (n_rows + SLICE_ROWS - 1) / SLICE_ROWS) return;
+    int64_t b = 0;
+    int d = 0;
+    if (i < n_rows) {
+        b = rowptr[rows[i]];
+        d = (int)(rowptr[rows[i] + 1] - b);
+    }
+    const int c0 = base[t / 64], n = base[t / 64 + 1] - c0;
+    for (int chunk = (int)(t % 64 / SLICE_ROWS); chunk < n; chunk += 64 / SLICE_ROWS) {
+        IntL4 c;
+        FloatL4 w;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool in = 4 * chunk + q < d;
+            c[q] = in ? colidx[b + 4 * chunk + q] : -1;
+            w[q] = in ? val[b + 4 * chunk + q] : 0.f;
+        }
+        const int64_t at = (int64_t)(c0 + chunk) * SLICE_ROWS + t % SLICE_ROWS;
+        reinterpret_cast<IntL4*>(out_c)[at] = c;
+        reinterpret_cast<FloatL4*>(out_v)[at] = w;
+    }
+}
+
+// a wavefront per row
+__global__ void __launch_bounds__(256) fill_packed_kernel(const PackedRow* __restrict__ packed, int64_t n_rows, const int64_t* __restrict__ rowptr,
+                                                          const int32_t* __restrict__ colidx, const float* __restrict__ val,
+                                                          int32_t* __restrict__ out_c, float* __restrict__ out_v) {
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= n_rows) return;
+    const PackedRow p = packed[i];
+    const int64_t b = rowptr[p.row];
+    for (int k = threadIdx.x & 63; k < (p.len + 3) / 4 * 4; k += 64) {
+        out_c[p.e_begin + k] = k < p.len ? colidx[b + k] : 0;
+        out_v[p.e_begin + k] = k < p.len ? val[b + k] : 0.f;
+    }
+}
+
 // Blocks are dealt to the 8 XCDs in turn.  Runs of XCD_RUN consecutive blocks of work go to one XCD: rows that are near
 // in memory share lines of the row pointers and of the index and weight arrays, which are then fetched by one L2
 // (200 k rows of 8 entries: 80 -> 74 us; larger graphs 0.5-1 %).
@@ -616,7 +740,7 @@ __global__ void __launch_bounds__(256, (agg_min_waves<IO, L, NACC>())) agg_kerne
     __shared__ __align__(16) int stage[4][stage_words(L, false)];
     __shared__ float quarter[3][L * IO::kVec * NACC];     // block-per-row mode: sums of wavefronts 1..3
     const int wave = __builtin_amdgcn_readfirstlane(xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + (int)(threadIdx.x >> 6));
-    if (wave >= a.wave_start[a.n_groups]) return;
+    if (wave >= a.n_waves) return;
     agg_item<IO, L, NACC, false>(a, wave, (int)blockIdx.y, nullptr, quarter, stage[threadIdx.x >> 6]);
 }
 
@@ -642,7 +766,7 @@ __global__ void __launch_bounds__(1024, 4) agg_hub_kernel(const AggArgs a) {
         }
     }
     __syncthreads();
-    const int total = a.wave_start[a.n_groups];
+    const int total = a.n_waves;
     const int w0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 16 + (threadIdx.x >> 6)));
     for (int wave = w0; wave < total; wave += 16 * (int)gridDim.x)
         agg_item<IO, L, 1, true>(a, wave, (int)blockIdx.y, table, nullptr, stage[threadIdx.x >> 6]);
@@ -693,7 +817,7 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ReduceArgs a) {
 
 template <class IO, int L, int NACC>
 int launch_one(const AggArgs& a, int n_passes, hipStream_t st) {
-    const int total = a.wave_start[a.n_groups];
+    const int total = a.n_waves;
     if (total <= 0) return NTP_OK;
     dim3 grid((unsigned)((total + 3) / 4), (unsigned)n_passes);
     hipLaunchKernelGGL((agg_kernel<IO, L, NACC>), grid, dim3(256), 0, st, a);
@@ -704,7 +828,7 @@ int launch_one(const AggArgs& a, int n_passes, hipStream_t st) {
 
 template <class IO, int L>
 int launch_hub(const AggArgs& a, int n_passes, hipStream_t st) {
-    const int total = a.wave_start[a.n_groups];
+    const int total = a.n_waves;
     if (total <= 0) return NTP_OK;
     const int blocks = std::min(compute_units(), (total + 15) / 16);
     hipLaunchKernelGGL((agg_hub_kernel<IO, L>), dim3((unsigned)blocks, (unsigned)n_passes), dim3(1024), 0, st, a);
@@ -835,6 +959,27 @@ int launch_reduce(const ReduceArgs& a, int dtype, void* stream) {
     else hipLaunchKernelGGL(reduce_kernel<unsigned short>, grid, dim3(256), 0, st, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("reduce kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
+    return NTP_OK;
+}
+
+int launch_fill_slices(const int32_t* rows, int64_t n_rows, const int32_t* base, const int64_t* rowptr, const int32_t* colidx, const float* val,
+                       int32_t* out_colidx, float* out_val, void* stream) {
+    if (n_rows == 0) return NTP_OK;
+    const int64_t threads = (n_rows + SLICE_ROWS - 1) / SLICE_ROWS * 64;
+    hipLaunchKernelGGL(fill_slices_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, (hipStream_t)stream, rows, n_rows, base, rowptr,
+                       colidx, val, out_colidx, out_val);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("slice launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
+    return NTP_OK;
+}
+
+int launch_fill_packed(const PackedRow* packed, int64_t n_rows, const int64_t* rowptr, const int32_t* colidx, const float* val,
+                       int32_t* out_colidx, float* out_val, void* stream) {
+    if (n_rows == 0) return NTP_OK;
+    hipLaunchKernelGGL(fill_packed_kernel, dim3((unsigned)((n_rows + 3) / 4)), dim3(256), 0, (hipStream_t)stream, packed, n_rows, rowptr, colidx, val,
+                       out_colidx, out_val);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("packing launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
     return NTP_OK;
 }
 

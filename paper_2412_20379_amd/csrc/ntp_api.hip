@@ -139,6 +139,88 @@ int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
     return NTP_OK;
 }
 
+// The slices of a resident chunk, made on the device from its image.  In the form's own arrays a short row's pairs are a part of a
+// line of each, whose other rows are other wavefronts' (other bins, other XCDs), so every column pass fetched a line many times;
+// a wavefront's slices are whole lines of its own, and their address follows from the place in the list (no row pointers).  One
+// call: 2.5 M entries F = 256 215 -> 194 us, F = 40 60 -> 55, directed 26 M entries F = 13 312 -> 286, 63 M F = 32 686 -> 658.  (A form
+// of up to half a million entries is in the L2s whole: no copies.)
+int make_slices(ntp_graph* G, const HostSparse& m, Chunk& c) {
+    const int32_t* rows = reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows);
+    std::vector<int32_t> base;                 // one more per bin than it has slices: a slice's end is the next one's beginning
+    int32_t n_base = 0;
+    for (int b = 0; b < SLICE_BINS; ++b) {
+        c.slice_off[b] = n_base;
+        n_base += (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS + 1;
+    }
+    base.resize((size_t)n_base);               // chunks of each slice (0 between the bins), then their sums
+    parallel_for_threads(std::max(1, std::min(host_threads(), n_base / 4096)), [&](int t, int nt) {
+        for (int b = 0; b < SLICE_BINS; ++b) {
+            const int32_t* r = rows + c.bin_row_off[b];
+            const int64_t slices = (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS;
+            for (int64_t s = slices * t / nt; s < slices * (t + 1) / nt; ++s) {
+                int64_t most = 0;
+                for (int64_t j = s * SLICE_ROWS; j < std::min<int64_t>((s + 1) * SLICE_ROWS, c.bin_count[b]); ++j)
+                    most = std::max(most, m.rowptr[(size_t)r[j] + 1] - m.rowptr[(size_t)r[j]]);
+                base[(size_t)(c.slice_off[b] + s)] = (int32_t)((most + 3) / 4);
+            }
+        }
+    });
+    int64_t chunks = 0;
+    for (int32_t& x : base) {
+        const int32_t here = x;
+        x = (int32_t)chunks;
+        chunks += here;
+    }
+    if (chunks == 0 || chunks > INT_MAX) return NTP_OK;          // (no entries, or a chunk of 2^36 of them)
+    c.off_slice_val = (size_t)chunks * (4 * SLICE_ROWS) * 4;
+    c.off_slice_base = 2 * c.off_slice_val;
+    const size_t bytes = c.off_slice_base + base.size() * 4;
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of %zu bytes for the slices of short rows failed", bytes); return NTP_ENOMEM; }
+    c.d_slices = (char*)p;
+    G->device_bytes += (int64_t)bytes;
+    HIP_TRY(hipMemcpy(c.d_slices + c.off_slice_base, base.data(), base.size() * 4, hipMemcpyHostToDevice));
+    for (int b = 0; b < SLICE_BINS; ++b) {
+        const int rc = launch_fill_slices(reinterpret_cast<const int32_t*>(c.d_image + c.off_rows) + c.bin_row_off[b], c.bin_count[b],
+                                          reinterpret_cast<const int32_t*>(c.d_slices + c.off_slice_base) + c.slice_off[b],
+                                          reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin,
+                                          reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin,
+                                          reinterpret_cast<const float*>(c.d_image + c.img_off_val) - c.e_begin, reinterpret_cast<int32_t*>(c.d_slices),
+                                          reinterpret_cast<float*>(c.d_slices + c.off_slice_val), nullptr);
+        if (rc != NTP_OK) return rc;
+    }
+    return NTP_OK;
+}
+
+// The packed rows, likewise, where the form is at most half of the Infinity Cache: 12 M entries (98 MB), rows of about 41, F = 32 222 ->
+// 209 us, 7.2 M 215 -> 211; beyond, the copy displaces more than it saves (28.8 M, 230 MB: 478 -> 489 us) or makes 0 to 1 %.
+int make_packed(ntp_graph* G, const HostSparse& m, Chunk& c) {
+    if (m.nnz * 8 > (128ll << 20)) return NTP_OK;
+    const int32_t* rows = reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows);
+    std::vector<PackedRow> packed;
+    for (int b = SLICE_BINS; b < PACKED_BINS; ++b)
+        for (int32_t i = 0; i < c.bin_count[b]; ++i) {
+            const int32_t r = rows[c.bin_row_off[b] + i];
+            const int32_t len = (int32_t)(m.rowptr[(size_t)r + 1] - m.rowptr[(size_t)r]);
+            packed.push_back(PackedRow{c.n_packed, len, r});
+            c.n_packed += (len + 3) / 4 * 4;
+        }
+    if (packed.empty()) return NTP_OK;
+    c.off_packed_colidx = packed.size() * sizeof(PackedRow);
+    c.off_packed_val = c.off_packed_colidx + (size_t)c.n_packed * 4;
+    const size_t bytes = c.off_packed_val + (size_t)c.n_packed * 4;
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of %zu bytes for packed rows failed", bytes); return NTP_ENOMEM; }
+    c.d_packed = (char*)p;
+    G->device_bytes += (int64_t)bytes;
+    HIP_TRY(hipMemcpy(c.d_packed, packed.data(), c.off_packed_colidx, hipMemcpyHostToDevice));
+    return launch_fill_packed(reinterpret_cast<const PackedRow*>(c.d_packed), (int64_t)packed.size(),
+                              reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin,
+                              reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin,
+                              reinterpret_cast<const float*>(c.d_image + c.img_off_val) - c.e_begin,
+                              reinterpret_cast<int32_t*>(c.d_packed + c.off_packed_colidx), reinterpret_cast<float*>(c.d_packed + c.off_packed_val), nullptr);
+}
+
 int64_t streamed_bytes(const Chunk& c, bool with_val) { return (int64_t)c.meta.size() + (c.e_end - c.e_begin) * (with_val ? 8 : 4); }
 
 // what the aggregation does to an output element on its way out (AggArgs::epilogue)
@@ -207,11 +289,7 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     int64_t waves = 0;
     auto add_group = [&](int mode, int off, int count, int64_t nw, int per_wave = 1, int per_fetch = 1) {
         a.wave_start[ng] = (int32_t)waves;
-        a.item_off[ng] = off;
-        a.item_count[ng] = count;
-        a.mode[ng] = mode;
-        a.per_wave[ng] = per_wave;
-        a.per_fetch[ng] = per_fetch;
+        a.group[ng] = AggGroup{mode, off, count, per_wave, per_fetch, 0, 0, 0};
         waves += nw;
         ++ng;
     };
@@ -220,6 +298,8 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     const double quantum = (double)(c.e_end - c.e_begin) * passes / (16.0 * 8192.0);
     const bool block_rows = !scatter && !hub && c.block_rows;      // split rows summed by one block each (see make_plan)
     a.split_rows = reinterpret_cast<const ReduceItem*>(img + c.off_reduce);
+    const bool own_copies = !scatter && !hub && !weights && img == c.d_image;
+    const bool slices = own_copies && c.d_slices, packed = own_copies && c.d_packed;
     // heaviest work first: split rows, then bins from long rows to short rows
     if (block_rows) add_group(MODE_BLOCK_PER_ROW, 0, c.n_reduce, 4 * (int64_t)c.n_reduce);   // first: block-aligned
     else if (c.n_segs > 0) add_group(MODE_SEGMENT, 0, c.n_segs, c.n_segs);
@@ -231,7 +311,13 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
         // more than 32 entries get it only in bf16 (whose reduction has twice the values) and in launches large enough
         // (28.8 M entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us
         // if they are, hence the rule; in fp32 it makes 1 % at best).
-        const bool per_group = R > 1 && (len <= 32 || (!scatter && dtype == NTP_BF16 && len <= 128 && (double)len * R <= 2 * quantum));
+        // One lane group per row costs no reduction and one wavefront per R rows; it takes R times as long, so rows of
+        // more than 32 entries get it only in launches large enough, in bf16 (whose reduction has twice the values; 28.8 M
+        // entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us if they are,
+        // hence the rule) and where the columns take four passes and more, each with a reduction (2.5 M entries, F = 256 193 ->
+        // 185 us, F = 128 99 -> 94).  A narrower fp32 slice, whose rows are summed by wavefronts, would gain 3 % at best.
+        const bool per_group = R > 1 && (len <= 32 || (!scatter && len <= 128 && ((dtype == NTP_BF16 && (double)len * R <= 2 * quantum) ||
+                                                                                  (passes >= 4 && len <= 3.5 * quantum))));
         const int at_once = per_group ? R : 1;
         const int items = (cnt + at_once - 1) / at_once;
         // rows per wavefront: as many as the quantum allows, and two where one fetch of pairs covers two anyway
@@ -243,10 +329,26 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
         }
         while (per_group && 2 * S <= std::min(K, L) && 2 * S * len <= 4 * L) S *= 2;
         add_group(per_group ? MODE_GROUP_PER_ROW : MODE_WAVE_PER_ROW, c.bin_row_off[b], cnt, (items + K - 1) / K, K, S);
+        AggGroup& g = a.group[ng - 1];
+        if (slices && b < SLICE_BINS && per_group) {
+            g.mode = MODE_SLICE;
+            g.slice_off = c.slice_off[b];
+            g.slice_chunks = slice_chunks(b);
+        } else if (packed && b >= SLICE_BINS && b < PACKED_BINS) {
+            g.packed = 1;
+            g.item_off -= c.bin_row_off[SLICE_BINS];
+        }
     }
     if (waves > INT_MAX - 8) { set_error("chunk too large for one launch (%lld wavefronts)", (long long)waves); return NTP_EUNSUPPORTED; }
-    a.wave_start[ng] = (int32_t)waves;
-    a.n_groups = ng;
+    a.n_waves = (int32_t)waves;
+    for (int g = ng; g < NGROUPS; ++g) a.wave_start[g] = INT_MAX;
+    a.slice_colidx = reinterpret_cast<const int32_t*>(c.d_slices);
+    a.slice_val = reinterpret_cast<const float*>(c.d_slices + c.off_slice_val);
+    a.slice_base = reinterpret_cast<const int32_t*>(c.d_slices + c.off_slice_base);
+    a.packed_rows = reinterpret_cast<const PackedRow*>(c.d_packed);
+    a.packed_colidx = reinterpret_cast<const int32_t*>(c.d_packed + c.off_packed_colidx);
+    a.packed_val = reinterpret_cast<const float*>(c.d_packed + c.off_packed_val);
+    a.packed_end = c.n_packed;
     if (ng > 0) {
         const int rc = scatter ? launch_scatter(a, st) : launch_aggregate(a, dtype, st);
         if (rc != NTP_OK) return rc;
@@ -346,6 +448,10 @@ void destroy(ntp_graph* G) {
     for (int k = 0; k < 2; ++k) {
         for (auto& c : G->form[k].plan.chunks)
             if (c.d_image) (void)hipFree(c.d_image);
+        for (auto& c : G->form[k].plan.chunks)
+            if (c.d_slices) (void)hipFree(c.d_slices);
+        for (auto& c : G->form[k].plan.chunks)
+            if (c.d_packed) (void)hipFree(c.d_packed);
         for (auto& c : G->form[k].plan.chunks)
             if (c.d_colidx_hub) (void)hipFree(c.d_colidx_hub);
         if (G->form[k].d_hub_cols) (void)hipFree(G->form[k].d_hub_cols);
@@ -607,6 +713,14 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                 }
             }
         }
+        if (fits && budget == 0)
+            for (int k = 0; k < n_forms; ++k)
+                for (auto& c : G->form[k].plan.chunks) {
+                    if (G->form[k].m->nnz * 8 <= (4ll << 20)) continue;
+                    rc = make_slices(G, *G->form[k].m, c);
+                    if (rc == NTP_OK) rc = make_packed(G, *G->form[k].m, c);
+                    if (rc != NTP_OK) return rc;
+                }
         bool any_streamed = false;
         for (int k = 0; k < n_forms; ++k) any_streamed = any_streamed || !G->form[k].all_resident;
         if (any_streamed && G->g.val_mode == VAL_GCN && n > 0) {

@@ -87,6 +87,21 @@ void* alloc_large(size_t bytes);
 constexpr int NBINS = 9;             // d<=1, 2, 3-4, 5-8, 9-16, 17-32, 33-64, 65-128, >128
 constexpr int NGROUPS = NBINS + 1;   // + the segment group
 
+// Second copies of the entries of a resident chunk, in the order in which the aggregation takes them.
+// Rows of the first SLICE_BINS bins (a lane group each): eight rows that follow each other in the list of a bin make a slice, as
+// many times 8 x 4 entries as the longest of them needs, four consecutive entries of each row.  Column id -1: the row has no
+// such entry.  Rows of the bins from there to PACKED_BINS: one after the other in the order of the lists, each from a multiple
+// of four entries on (PackedRow).
+constexpr int SLICE_ROWS = 8;
+constexpr int SLICE_BINS = 6;        // rows of up to 32 entries
+constexpr int PACKED_BINS = 8;       // 33 to 128
+constexpr int slice_chunks(int bin) { return bin <= 2 ? 1 : 1 << (bin - 2); }      // most chunks of four entries of a row
+struct PackedRow {      // (device-visible, 16 bytes)
+    int64_t e_begin;    // in the packed entries
+    int32_t len;
+    int32_t row;
+};
+
 struct Segment {        // one piece of a split row (device-visible, 24 bytes)
     int64_t e_begin;    // first entry (global offset into colidx/val)
     int32_t len;        // number of entries
@@ -123,6 +138,12 @@ struct Chunk {
     // residency
     int32_t* d_colidx_hub = nullptr;           // resident chunks of a form with a hub table: hub-encoded column ids
     char* d_image = nullptr;                   // device image if resident
+    char* d_slices = nullptr;                  // slices of a resident chunk: column ids, weights, first chunk of each slice
+    size_t off_slice_val = 0, off_slice_base = 0;
+    int32_t slice_off[SLICE_BINS] = {0};       // first slice of each bin
+    char* d_packed = nullptr;                  // packed rows of a resident chunk: rows, column ids, weights
+    size_t off_packed_colidx = 0, off_packed_val = 0;
+    int64_t n_packed = 0;                      // packed entries
     char* h_meta_pinned = nullptr;             // pinned copy of meta for streaming
 };
 
@@ -150,6 +171,17 @@ void pick_hub_columns(const HostSparse& m, const HostSparse* transposed, int max
 void encode_hub_columns(const HostSparse& m, const std::vector<int32_t>& hub_cols, int64_t e_begin, int64_t e_end, int32_t* out);
 
 // ---------------------------------------------------------------------------------------
+// Rows of a bin, or the split rows or segments
+struct AggGroup {
+    int32_t mode;              // MODE_*
+    int32_t item_off;          // offset into rows[] or packed_rows[] (bins), segs[] or split_rows[]
+    int32_t item_count;        // rows / segments in the group
+    int32_t per_wave;          // items (rows, or R rows at a time) a wavefront of a row group works through
+    int32_t per_fetch;         // rows of a lane group whose entries one fetch brings (a power of two)
+    int32_t packed;            // 1: packed rows
+    int32_t slice_off;         // MODE_SLICE: first slice of the group
+    int32_t slice_chunks;      // MODE_SLICE: most chunks of a row
+};
 // Argument block of the aggregation kernel (passed by value).
 struct AggArgs {
     const int64_t* rowptr;     // chunk slice: rowptr[r - row_base]
@@ -174,15 +206,18 @@ struct AggArgs {
     int32_t pass_lanes;        // vectors per feature row and column pass (0: widest shape)
     int32_t past_caches;       // 1: indices and weights are read with non-temporal loads (see run_chunk)
     int32_t n_hub;             // hub columns (at most agg_hub_slots())
-    int32_t n_groups;          // entries used in the tables below
-    int32_t wave_start[NGROUPS + 1];   // first wavefront of each group; last = total
-    int32_t item_off[NGROUPS];         // offset into rows[] (bins) or segs[] (segment group)
-    int32_t item_count[NGROUPS];       // rows / segments in the group
-    int32_t mode[NGROUPS];             // MODE_*
-    int32_t per_wave[NGROUPS];         // items (rows, or R rows at a time) a wavefront of a row group works through
-    int32_t per_fetch[NGROUPS];        // rows of a lane group whose entries one fetch brings (a power of two)
+    int32_t n_waves;           // wavefronts of the launch
+    int32_t wave_start[NGROUPS];       // first wavefront of each group (INT_MAX beyond the last)
+    AggGroup group[NGROUPS];
+    const int32_t* slice_colidx;
+    const float* slice_val;
+    const int32_t* slice_base;         // first chunk (of 8 x 4 entries) of each slice
+    const PackedRow* packed_rows;
+    const int32_t* packed_colidx;
+    const float* packed_val;
+    int64_t packed_end;
 };
-enum { MODE_GROUP_PER_ROW = 0, MODE_WAVE_PER_ROW = 1, MODE_SEGMENT = 2, MODE_BLOCK_PER_ROW = 3 };
+enum { MODE_GROUP_PER_ROW = 0, MODE_WAVE_PER_ROW = 1, MODE_SEGMENT = 2, MODE_BLOCK_PER_ROW = 3, MODE_SLICE = 4 };      // MODE_SLICE: lane groups, from slices
 
 struct ReduceArgs {
     const ReduceItem* items;
@@ -198,7 +233,13 @@ struct ReduceArgs {
 
 // kernels (agg_kernels.hip / nn_kernels.hip); stream is a hipStream_t
 int launch_aggregate(const AggArgs& a, int dtype, void* stream);
+// the entries of packed rows, likewise; e_begin of a row: its place in out_colidx and out_val
+int launch_fill_packed(const PackedRow* packed, int64_t n_rows, const int64_t* rowptr, const int32_t* colidx, const float* val,
+                       int32_t* out_colidx, float* out_val, void* stream);
 int launch_reduce(const ReduceArgs& a, int dtype, void* stream);
+// the slices of the n_rows rows of a bin; base: first chunk of each of them; rowptr, colidx and val indexed globally
+int launch_fill_slices(const int32_t* rows, int64_t n_rows, const int32_t* base, const int64_t* rowptr, const int32_t* colidx, const float* val,
+                       int32_t* out_colidx, float* out_val, void* stream);
 int compute_units();               // of the current device
 int agg_hub_slots();               // lines of the LDS hub table
 // does the launch of `a` (already holding X, Y, f, strides, pass_lanes) take the hub kernel?

@@ -31,11 +31,11 @@ __global__ void __launch_bounds__(256) scatter_kernel(const AggArgs a) {
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    if (wave >= a.wave_start[a.n_groups]) return;
-    int grp = 0;
-    while (grp + 1 < a.n_groups && wave >= a.wave_start[grp + 1]) ++grp;
+    if (wave >= a.n_waves) return;
+    const int grp = agg_group_of(a, wave);
+    const AggGroup G = a.group[grp];
     const int item0 = wave - a.wave_start[grp];
-    const int mode = a.mode[grp];
+    const int mode = G.mode;
     const int g = lane / L;
     const int l = lane % L;
     const int colbase = (int)blockIdx.y * PASS_W + l;
@@ -60,12 +60,12 @@ __global__ void __launch_bounds__(256) scatter_kernel(const AggArgs a) {
 
     if (mode == MODE_GROUP_PER_ROW) {
         const int idx = item0 * R + g;
-        const bool valid = idx < a.item_count[grp];
+        const bool valid = idx < G.item_count;
         int row = 0;
         int64_t beg = a.e_base;
         int d = 0;
         if (valid) {
-            row = a.rows[a.item_off[grp] + idx];
+            row = a.rows[G.item_off + idx];
             beg = a.rowptr[row - a.row_base];
             d = (int)(a.rowptr[row - a.row_base + 1] - beg);
         }
@@ -93,12 +93,12 @@ __global__ void __launch_bounds__(256) scatter_kernel(const AggArgs a) {
     int row;
     int64_t beg, end;
     if (mode == MODE_SEGMENT) {
-        const Segment* sp = a.segs + a.item_off[grp] + item0;
+        const Segment* sp = a.segs + G.item_off + item0;
         row = __builtin_amdgcn_readfirstlane(sp->row);
         beg = uniform64(sp->e_begin);
         end = beg + __builtin_amdgcn_readfirstlane(sp->len);
     } else {
-        row = __builtin_amdgcn_readfirstlane(a.rows[a.item_off[grp] + item0]);
+        row = __builtin_amdgcn_readfirstlane(a.rows[G.item_off + item0]);
         beg = uniform64(a.rowptr[row - a.row_base]);
         end = uniform64(a.rowptr[row - a.row_base + 1]);
     }
@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(256) zero_rows_kernel(T* Y, int64_t n, int64_t
 
 template <int L, int NACC>
 int launch_scatter_one(const AggArgs& a, hipStream_t st) {
-    const int total = a.wave_start[a.n_groups];
+    const int total = a.n_waves;
     if (total <= 0) return NTP_OK;
     const int passes = (a.f + L * NACC - 1) / (L * NACC);
     dim3 grid((unsigned)((total + 3) / 4), (unsigned)passes);

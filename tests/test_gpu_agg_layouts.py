@@ -1,0 +1,84 @@
+"""The second copies of the topology that resident graphs keep for the aggregation (slices of short rows, packed rows) against the form's own
+arrays, which a call with caller weights reads, and against the oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import ntp_inputs as gen
+import paper_2412_20379_amd as ntp
+from helpers import assert_close, TOL_F32, TOL_BF16
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def graph_of_degrees(deg, seed):
+    """directed edges (with weights) into vertex v from deg[v] distinct vertices, in random order"""
+    rng = np.random.default_rng(seed)
+    n = deg.size
+    dst = np.repeat(np.arange(n), deg)
+    start = rng.integers(0, n, size=n)
+    step = 2 * rng.integers(0, n // 1000, size=n) + 1
+    k = np.arange(dst.size) - np.repeat(np.cumsum(deg) - deg, deg)
+    src = (start[dst] + k * step[dst]) % n          # distinct: n is a power of two, the step odd, deg[v] <= n
+    order = rng.permutation(dst.size)
+    w = rng.random(dst.size).astype(np.float32) + 0.25
+    return src[order].astype(np.int32), dst[order].astype(np.int32), w
+
+
+@pytest.fixture(scope="module")
+def slice_graphs():
+    """every row length from 0 to 140, in one of them so many rows that at 128 columns a lane group takes a row of up to 128 entries;
+    and short rows only"""
+    out = {}
+    for name, n, top in (("long", 1 << 13, 140), ("large", 1 << 15, 140), ("short", 1 << 18, 5)):      # (more than half a million entries)
+        deg = np.random.default_rng(n).integers(0, top + 1, size=n)
+        deg[-3:] = 0                            # the last rows of the list have no entries
+        src, dst, w = graph_of_degrees(deg, n)
+        g = ntp.ntp_graph_build(n, src, dst, edge_weight=w, flags=0)
+        og = oracle.build_graph(n, src, dst, 0, edge_weight=w)
+        out[name] = (g, og)
+    yield out
+    for g, _ in out.values():
+        g.close()
+
+
+@pytest.mark.parametrize("name", ["short", "long", "large"])
+@pytest.mark.parametrize("f,ld,dtype", [(5, 8, "f32"), (13, 16, "f32"), (32, 32, "f32"), (47, 48, "f32"), (100, 100, "f32"), (128, 128, "f32"),
+                                        (250, 250, "f32"), (300, 300, "f32"), (76, 128, "bf16"), (24, 24, "bf16"), (6, 6, "bf16")])
+def test_slices_give_the_bits_of_the_forms_own_arrays(slice_graphs, name, f, ld, dtype):
+    import torch
+    from gpu_util import dev_f32, dev_bf16_bits, host_bf16
+    g, og = slice_graphs[name]
+    if name == "short" and f > 128:
+        pytest.skip("no more of the same at a quarter of a gigabyte")
+    say("slices", name, f, ld, dtype)
+    n = og.n
+    x = gen.normal_features(n, f, seed=f)
+    x[17, :] = np.inf                           # reaches the rows that name it and no other
+    code = ntp.NTP_BF16 if dtype == "bf16" else ntp.NTP_F32
+    src = dev_bf16_bits(x)[0] if dtype == "bf16" else dev_f32(x)
+    X = torch.zeros(n, ld, dtype=src.dtype, device="cuda:0")
+    X[:, :f] = src
+    for direction, which, m in ((ntp.NTP_FWD, ntp.NTP_CSR, og.csr), (ntp.NTP_BWD, ntp.NTP_CSC, og.csc)):
+        own, got = torch.full_like(X, 3), torch.full_like(X, 5)
+        ntp.ntp_aggregate_weighted(g, direction, dev_f32(m.val), X, own, f, ld, ld, code)
+        (ntp.ntp_aggregate_fwd if direction == ntp.NTP_FWD else ntp.ntp_aggregate_bwd)(g, X, got, f, ld, ld, code)
+        torch.cuda.synchronize()
+        assert torch.equal(own[:, :f], got[:, :f])
+        assert bool((got[:, f:] == 5).all())
+        seen = np.isinf(host_bf16(got[:, :f].contiguous()) if dtype == "bf16" else got[:, :f].cpu().numpy()).any(axis=1)
+        rows = np.repeat(np.arange(n), np.diff(m.rowptr))
+        assert np.array_equal(np.flatnonzero(seen), np.unique(rows[m.colidx == 17]))
+        used = gen.bf16_bits_to_f32(gen.to_bf16_bits(x)) if dtype == "bf16" else x.copy()
+        used[17, :] = 0
+        ref, ref_abs = oracle.aggregate(m, used, with_abs=True)
+        y = host_bf16(got[:, :f].contiguous()) if dtype == "bf16" else got[:, :f].cpu().numpy()
+        keep = ~seen
+        assert_close(y[keep], (oracle.round_bf16(ref).astype(np.float64) if dtype == "bf16" else ref)[keep], ref_abs[keep],
+                     TOL_BF16 if dtype == "bf16" else TOL_F32, "slices")
