@@ -1,0 +1,237 @@
+// Dense transform with the small operand resident in registers: C[n x N] = act(A[n x K] B[K x N]) for tall fp32 A, 64 < K <= 256
+// and N of 193 to 256, products from bf16 pieces (H = act(A W), and dA = dZ W^T with the ReLU mask applied to dZ on its way in).
+//
+// The pieces of a 256 x 256 operand are 384 KB: more than the LDS of a compute unit, but not than its registers (512 KB).  One block of
+// eight wavefronts per compute unit, each with 32 columns of B: 12 matrix steps (144 registers a lane) in registers, up to four in LDS.
+// A unit of 32 rows is read once, as whole rows, cut once by the block and put into LDS in operand layout, from where all wavefronts
+// read it; the strips of nn_strip_kernels.hip, whose LDS holds 64 columns, read and cut it four times.  Half a row (KH matrix steps) is
+// multiplied while the next half is cut into the other buffer and the one two further is on its way: one barrier per half, and
+// nothing else is waited for (rows beyond the matrix are stored out of the range of a buffer resource, so no branch hides from the
+// compiler how many loads and stores are in flight).  Every element is summed in the strips' order: the same bits.
+//
+// Bound: the power of the matrix pipe.  256 -> 256 on 306,129 rows 254 -> 204 us (masked dA 283 -> 230), 1180 TFLOP/s of bf16
+// products, where a large bf16 matrix product of the library reaches 1117: the matrix pipe is busy 58 % of the cycles, at 1.7 GHz.
+// 169,343 rows: 256 -> 256 153 -> 125, dA 140 -> 122 (masked 159 -> 135), 128 -> 256 76 -> 63; 153,065 rows of 100 -> 256 61 -> 54.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "nn_util.h"
+#include "ntp_internal.h"
+
+namespace ntp {
+
+namespace {
+
+struct ResidentArgs {
+    const float* A;
+    const float* mask;     // like A (nullable): an element of A is used only where its mask element is > 0
+    const float* B;
+    float* C;
+    int64_t n, ldb;
+    int K, N;              // A and C are dense
+    int b_kcontig;         // B[kk][col] at B[col * ldb + kk] (else at B[kk * ldb + col])
+    int relu;
+    int nt;
+};
+
+// eight elements of B's column col from row k on, zero outside the matrix
+__device__ __forceinline__ void read_b8(const ResidentArgs& g, int k, int col, unsigned (&w)[8]) {
+    const int64_t sk = g.b_kcontig ? 1 : g.ldb, sc = g.b_kcontig ? g.ldb : 1;
+    const float* src = g.B + (int64_t)min(col, g.N - 1) * sc;
+    if (g.b_kcontig && k + 8 <= g.K) {
+        __builtin_memcpy(w, src + k, 32);
+        if (col >= g.N) zero_row8_from<float>(w, 0);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = __float_as_uint(src[(int64_t)min(k + e, g.K - 1) * sk]);
+    zero_row8_from<float>(w, col < g.N ? g.K - k : 0);
+}
+
+// The contraction in HALVES parts of KH matrix steps of 16 indices; KR steps of B in registers, the others in LDS.
+template <bool MASK, int KH, int HALVES, int KR>
+__global__ void __launch_bounds__(512, 2) resident_kernel(const ResidentArgs g) {
+    constexpr Core CORE = CORE_BF16;
+    constexpr int KC = KH * HALVES, Q = 2 * KH;
+    constexpr int PART = KH * 3 * 64;                  // 16-byte fragments of the pieces of a part of 32 rows
+    extern __shared__ uint4 lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int h = lane >> 5, r = lane & 31;
+    const int col = wave * 32 + r;
+    const int K = g.K, N = g.N;
+
+    // this wavefront's 32 columns of B
+    uint4 b[KR][1][3];
+    uint4* const bl = lds + 2 * PART + (wave * (KC - KR) * 3) * 64 + lane;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+        unsigned w[8];
+        read_b8(g, 16 * c + 8 * h, col, w);
+        uint4 p[3];
+        cut_row8<float, CORE>(w, p);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (c < KR) b[c < KR ? c : 0][0][q] = p[q];
+            else bl[((c - KR) * 3 + q) * 64] = p[q];
+        }
+    }
+
+    const int tiles = (int)((g.n + 31) / 32), step = (int)gridDim.x;
+    struct Raw { unsigned w[8], m[MASK ? 8 : 1]; };
+    // eight elements of a row of part `half` of tile t, by every thread of the first 64 KH
+    const int q = tid % Q, row = min(tid / Q, 31);
+    auto issue = [&](Raw& x, int t, int half) {
+        const int64_t at = min((int64_t)min(t, tiles - 1) * 32 + row, g.n - 1) * K + min(half * (16 * KH) + 8 * q, K - 8);
+        __builtin_memcpy(x.w, g.A + at, 32);
+        if constexpr (MASK) __builtin_memcpy(x.m, g.mask + at, 32);
+    };
+    uint4* const to = lds + (q / 2 * 3) * 64 + (((q & 1) * 32 + row) ^ (q & 15));
+    auto stage = [&](Raw& x, int buf, int half) {
+        if constexpr (MASK) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x.w[e] = __uint_as_float(x.m[e]) > 0.f ? x.w[e] : 0u;
+        }
+        if (half == HALVES - 1 && K != 16 * KC) {            // drop the elements that stand before the eight, zeros come in at the end
+            const int over = max(half * (16 * KH) + 8 * q - (K - 8), 0);
+#pragma unroll
+            for (int s = 4; s >= 1; s /= 2)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x.w[e] = over >= 8 ? 0u : (over & s) ? (e + s < 8 ? x.w[e + s < 8 ? e + s : 7] : 0u) : x.w[e];
+        }
+        uint4 p[3];
+        cut_row8<float, CORE>(x.w, p);
+        if (KH == 8 || tid < 64 * KH) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) to[buf * PART + k * 64] = p[k];
+        }
+    };
+    f32x16 acc[1][1];
+    // multiply part `half` from buffer buf while the part that follows comes into the other one from x, which is then refilled with
+    // part nh of tile nt
+    auto part = [&](int half, int buf, Raw& x, int sh, int nt, int nh) {
+        const uint4* src = lds + buf * PART;
+        auto read_a = [&](int c, uint4 (&a)[1][3]) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) a[0][k] = src[(c * 3 + k) * 64 + (lane ^ ((2 * c + h) & 15))];
+        };
+        uint4 a[2][1][3];
+        read_a(0, a[0]);
+#pragma unroll
+        for (int c = 0; c < KH; ++c) {
+            if (c + 1 < KH) read_a(c + 1, a[(c + 1) & 1]);
+            if (c == 1) {
+                stage(x, buf ^ 1, sh);
+                issue(x, nt, nh);
+            }
+            const int cc = half * KH + c;
+            if (cc < KR) {
+                mfma_parts<CORE, 1, 1, 3>(a[c & 1], b[cc < KR ? cc : 0], acc);
+            } else {
+                uint4 bb[1][3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) bb[0][k] = bl[((cc - KR) * 3 + k) * 64];
+                mfma_parts<CORE, 1, 1, 3>(a[c & 1], bb, acc);
+            }
+        }
+    };
+    auto clear = [&] {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
+    };
+    auto store = [&](int t) {
+        // element e: row 8 * (e / 4) + 4 * h + e % 4, column r; rows and columns beyond the matrix are out of the buffer's range
+        const int64_t row0 = (int64_t)t * 32;
+        const int left = (int)min(max(g.n - row0, (int64_t)0), (int64_t)32);
+        const auto out = __builtin_amdgcn_make_buffer_rsrc(g.C + row0 * N, 0, left * N * 4, 0x00020000);
+        const int off = col < N ? (4 * h * N + col) * 4 : 0x7fff0000;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            float v = acc[0][0][e];
+            if (g.relu) v = v > 0.f ? v : 0.f;
+            const int at = off + (8 * (e / 4) + e % 4) * N * 4;
+            if (g.nt) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, at, 0, 2);
+            else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, at, 0, 0);
+        }
+    };
+
+    Raw x0, x1;
+    int t = (int)blockIdx.x;
+    issue(x0, t, 0);
+    stage(x0, 0, 0);
+    if constexpr (HALVES == 2) {
+        issue(x1, t, 1);
+        issue(x0, t + step, 0);
+        __syncthreads();
+        for (; t < tiles; t += step) {
+            clear();
+            part(0, 0, x1, 1, t + step, 1);
+            __syncthreads();
+            part(1, 1, x0, 0, t + 2 * step, 0);
+            store(t);
+            __syncthreads();
+        }
+    } else {
+        issue(x1, t + step, 0);
+        issue(x0, t + 2 * step, 0);
+        __syncthreads();
+        for (; t < tiles; t += 2 * step) {
+            clear();
+            part(0, 0, x1, 0, t + 3 * step, 0);
+            store(t);
+            __syncthreads();
+            if (t + step >= tiles) break;
+            clear();
+            part(0, 1, x0, 0, t + 4 * step, 0);
+            store(t + step);
+            __syncthreads();
+        }
+    }
+}
+
+template <bool MASK, int KH, int HALVES>
+void launch(const ResidentArgs& g, hipStream_t st) {
+    constexpr int KC = KH * HALVES, KR = KC < 12 ? KC : 12;
+    constexpr int lds = (2 * KH + 8 * (KC - KR)) * 3 * 1024;
+    static bool allowed[64] = {};
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    auto kernel = resident_kernel<MASK, KH, HALVES, KR>;
+    if (dev >= 0 && dev < 64 && !allowed[dev])
+        allowed[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>((g.n + 31) / 32, compute_units())), dim3(512), lds, st, g);
+}
+
+template <bool MASK>
+void launch_k(const ResidentArgs& g, hipStream_t st) {
+    switch ((g.K + 15) / 16) {
+        case 5: return launch<MASK, 5, 1>(g, st);
+        case 6: return launch<MASK, 6, 1>(g, st);
+        case 7: return launch<MASK, 7, 1>(g, st);
+        case 8: return launch<MASK, 8, 1>(g, st);
+        case 9: case 10: return launch<MASK, 5, 2>(g, st);
+        case 11: case 12: return launch<MASK, 6, 2>(g, st);
+        case 13: case 14: return launch<MASK, 7, 2>(g, st);
+        default: return launch<MASK, 8, 2>(g, st);
+    }
+}
+
+}  // namespace
+
+// A block's B costs some 12 us (256 x 256) before its first rows: us in strips / here, 256 -> 256 (fwd, dA, masked dA) on 24,576 rows 26 26
+// 28 / 30 29 33, on 40,000 39 39 43 / 39 38 43, on 65,536 56 57 62 / 54 53 58; 128 -> 256 on 16,384 13 / 13, on 32,768 21.7 / 20.6.
+bool nn_resident_takes(int64_t n, int64_t K, int64_t N) { return K > 64 && K <= 256 && N > 192 && N <= 256 && n >= (K <= 128 ? 24576 : 40000); }
+
+int launch_nn_resident(const float* A, const float* mask, const float* B, float* C, int64_t n, int64_t K, int64_t N, int64_t ldb,
+                       bool b_kcontig, bool relu, bool nt, void* stream) {
+    ResidentArgs g{A, mask, B, C, n, ldb, (int)K, (int)N, b_kcontig, relu, nt};
+    const hipStream_t st = (hipStream_t)stream;
+    if (mask) launch_k<true>(g, st);
+    else launch_k<false>(g, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) { set_error("transform kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
+    return NTP_OK;
+}
+
+}  // namespace ntp

@@ -159,3 +159,34 @@ def test_a_product_formed_from_pieces_is_within_its_bound(n, k, m):
         short = 1 - got / want
         print("   %s: left out of a product 2^%.2f at most" % (name, np.log2(short.max())), file=sys.stderr, flush=True)
         assert short.max() <= 2.0 ** -21 + 1.1 * 2.0 ** -24 and short.min() >= -1.1 * 2.0 ** -24, name
+
+
+RESIDENT_ROWS = 40031          # more than the strips take, and no multiple of 32
+
+
+@pytest.mark.parametrize("k,m", [(65, 256), (80, 193), (97, 256), (112, 224), (113, 255), (128, 256), (129, 200), (161, 256), (193, 256), (208, 250),
+                                 (225, 193), (255, 255), (256, 256)])
+@pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
+def test_many_rows_give_the_bits_of_few(k, m, act):
+    """the kernel with the small operand in registers takes products of many rows: each row must come out as in a call of few rows (in
+    strips), in H and in dA, where dA is taken with the operand transposed"""
+    import torch
+    n, part = RESIDENT_ROWS, 10008
+    gen_ = torch.Generator(device="cuda:0").manual_seed(k * 1000 + m)
+    r = lambda *s: torch.randn(*s, generator=gen_, device="cuda:0")
+    st = torch.cuda.current_stream()
+    A, W = r(n, k), r(k, m)
+    H, few = torch.full((n + 1, m), 7.0, device="cuda:0"), torch.empty(n, m, device="cuda:0")
+    ntp.ntp_nn_fwd(A, W, H, n, k, m, act, ntp.NTP_F32, st)
+    for b in range(0, n, part):
+        e = min(b + part, n)
+        ntp.ntp_nn_fwd(A[b:e], W, few[b:e], e - b, k, m, act, ntp.NTP_F32, st)
+    assert torch.equal(H[:n], few) and bool((H[n] == 7.0).all())
+    # dA of a layer m -> k: contraction over k, m columns
+    Wt, dH, Hm = r(m, k), A, r(n, k)
+    dA = torch.full((n + 1, m), 7.0, device="cuda:0")
+    ntp.ntp_nn_bwd(H, Wt, Hm, dH, dA, None, n, m, k, act, ntp.NTP_F32, None, 0, st)
+    for b in range(0, n, part):
+        e = min(b + part, n)
+        ntp.ntp_nn_bwd(H[b:e], Wt, Hm[b:e], dH[b:e], few[b:e], None, e - b, m, k, act, ntp.NTP_F32, None, 0, st)
+    assert torch.equal(dA[:n], few) and bool((dA[n] == 7.0).all())
