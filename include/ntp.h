@@ -141,7 +141,8 @@ int ntp_graph_chunks(const ntp_graph_t* g, int which, int32_t* n_chunks,
  * is not resident its row pointers and row lists plus 4 bytes per entry (column ids), and 4 more
  * (weights) only when the graph was built with caller weights.  Without caller weights the weights
  * of a streamed chunk are rebuilt on the device from the degrees (bit-identical to the stored
- * ones), which halves the host-link traffic of the chunk schedule. */
+ * ones), which halves the host-link traffic of the chunk schedule, and where chunks hold 655,360
+ * entries and more their column ids travel in as few bits each as hold a vertex id (up to 28). */
 int ntp_graph_stream_bytes(const ntp_graph_t* g, int which, int64_t* bytes);
 
 /* Device bytes held by the handle (resident topology, staging buffers, scratch). */

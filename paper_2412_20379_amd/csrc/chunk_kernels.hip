@@ -14,6 +14,10 @@
 // (product of the two degrees, square root, reciprocal, one rounding to fp32), so the rebuilt
 // values are the stored ones bit for bit.  A block finds the rows of its 4096 entries in a copy of their row pointers in
 // LDS (4 M entries of a 306,128-vertex graph: 0.071 -> 0.037 ms).
+//
+// Column ids travel packed: a vertex id of a graph of 306,128 vertices takes 19 of 32 bits, and the link is what a cold pass
+// waits for (15.8 M entries in four chunks, forward and backward: 2.62 -> 1.70 ms).  The unpacking kernel is bound by memory (8 us
+// for 4 M ids).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -79,6 +83,23 @@ __global__ void __launch_bounds__(256) rebuild_weights_kernel(const int64_t* __r
     }
 }
 
+// four ids a thread
+__global__ void __launch_bounds__(256) unpack_ids_kernel(const uint32_t* __restrict__ packed, int bits, int64_t n, int32_t* __restrict__ ids) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n) return;
+    int32_t v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int64_t at = std::min(i + q, n - 1) * bits;
+        const uint64_t two = (uint64_t)packed[at >> 5] | (uint64_t)packed[(at >> 5) + 1] << 32;
+        v[q] = (int32_t)((uint32_t)(two >> (at & 31)) & ((1u << bits) - 1));
+    }
+    if (i + 4 <= n) __builtin_memcpy(ids + i, v, 16);
+    else
+        for (int q = 0; q < 3; ++q)
+            if (i + q < n) ids[i + q] = v[q];
+}
+
 // up to three pieces; source and destination of a piece have the same address modulo 16
 struct StageArgs { const char* src[3]; char* dst[3]; int64_t bytes[3]; };
 
@@ -115,6 +136,13 @@ int launch_stage_chunk(const void* const src[3], void* const dst[3], const int64
     const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(16, (total / 16 + 255) / 256));
     hipLaunchKernelGGL(stage_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, a);
     if (hipGetLastError() != hipSuccess) { set_error("chunk copy kernel launch failed"); return NTP_EHIP; }
+    return NTP_OK;
+}
+
+int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n, int32_t* ids, void* stream) {
+    if (n <= 0) return NTP_OK;
+    hipLaunchKernelGGL(unpack_ids_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, (hipStream_t)stream, packed, bits, n, ids);
+    if (hipGetLastError() != hipSuccess) { set_error("column id kernel launch failed"); return NTP_EHIP; }
     return NTP_OK;
 }
 

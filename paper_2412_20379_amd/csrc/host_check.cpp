@@ -288,7 +288,27 @@ void check_schedule() {
 
 }  // namespace
 
+// column ids of every width, also where several threads share the words
+static void check_pack_ids() {
+    Lcg rng{99};
+    for (int bits = 1; bits <= 28; ++bits)
+        for (int64_t n : {(int64_t)1, (int64_t)2, (int64_t)31, (int64_t)33, (int64_t)1000, (int64_t)300007}) {
+            std::vector<int32_t> ids((size_t)n);
+            for (auto& x : ids) x = (int32_t)(rng.next() & ((1u << bits) - 1));
+            std::vector<uint32_t> packed((size_t)packed_words(n, bits), 0xffffffffu);
+            pack_ids(ids.data(), n, bits, packed.data());
+            int64_t wrong = 0;
+            for (int64_t k = 0; k < n; ++k) {
+                const int64_t at = k * bits;
+                const uint64_t two = (uint64_t)packed[(size_t)(at >> 5)] | (uint64_t)packed[(size_t)(at >> 5) + 1] << 32;
+                wrong += (int32_t)((uint32_t)(two >> (at & 31)) & ((1u << bits) - 1)) != ids[(size_t)k];
+            }
+            CHECK(wrong == 0, "%" PRId64 " of %" PRId64 " ids of %d bits", wrong, n, bits);
+        }
+}
+
 int main() {
+    check_pack_ids();
     // 1. every flag combination, weighted and not, on random multigraphs with loops and repeats
     Lcg rng{12345};
     for (int64_t n : {(int64_t)0, (int64_t)1, (int64_t)2, (int64_t)57, (int64_t)900}) {

@@ -66,6 +66,8 @@ struct ntp_graph {
     size_t stage_bytes = 0;
     StageState<HipPass> staged;                     // streams, events and the state of the two buffers
     char* pinned_meta = nullptr;                    // metas of streamed chunks
+    char* pinned_ids = nullptr;                     // packed column ids of streamed chunks
+    int id_bits = 0;
     // partial sums of split rows
     float* partial = nullptr;
     size_t partial_bytes = 0;
@@ -221,7 +223,46 @@ int make_packed(ntp_graph* G, const HostSparse& m, Chunk& c) {
                               reinterpret_cast<int32_t*>(c.d_packed + c.off_packed_colidx), reinterpret_cast<float*>(c.d_packed + c.off_packed_val), nullptr);
 }
 
-int64_t streamed_bytes(const Chunk& c, bool with_val) { return (int64_t)c.meta.size() + (c.e_end - c.e_begin) * (with_val ? 8 : 4); }
+int64_t streamed_bytes(const Chunk& c, bool with_val) {
+    return (int64_t)c.meta.size() + (c.h_packed_ids ? c.packed_id_bytes : (c.e_end - c.e_begin) * (with_val ? 8 : 4));
+}
+
+// Streamed chunks of this many entries send their column ids packed (where the weights are rebuilt, so that their place is free).
+// us a pass (both directions) as they are / packed: chunks of 0.66 M entries, 16 bits 1220 / 980; 0.74 M, 20 bits 1855 / 1645; 0.89 M, 18
+// bits, F = 76 1380 / 1255; 4 M, 19 bits 2620 / 1704.  The unpacking kernel is a launch more a chunk (8 us for 4 M ids): short chunks,
+// whose copies are mostly their start (pick_copy_path), go as they are.
+constexpr int64_t PACK_ENTRIES = 5 << 17;
+
+// bits of a vertex id; packed: at most 28, so that the packed ids and a spare word fit in the place of the weights
+int bits_of_ids(int64_t n) { return n <= 2 ? 1 : 64 - __builtin_clzll((unsigned long long)(n - 1)); }
+
+int pack_streamed_ids(ntp_graph* G, int n_forms, bool all) {
+    const int bits = G->id_bits;
+    int64_t bytes = 0;
+    auto each = [&](auto&& f) {
+        for (int k = 0; k < n_forms; ++k) {
+            auto& chunks = G->form[k].plan.chunks;
+            int64_t most = 0;
+            for (auto& c : chunks) most = std::max(most, c.d_image ? 0 : c.e_end - c.e_begin);
+            if (!all && most < PACK_ENTRIES) continue;
+            for (auto& c : chunks)
+                if (!c.d_image && c.e_end > c.e_begin) f(*G->form[k].m, c);
+        }
+    };
+    // like the arrays, packed ids keep their place modulo 16 (16-byte copies)
+    each([&](const HostSparse&, Chunk& c) { c.packed_id_bytes = packed_words(c.e_end - c.e_begin, bits) * 4; bytes += (c.packed_id_bytes + 31) / 16 * 16; });
+    if (bytes == 0) return NTP_OK;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, (size_t)bytes, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); set_error("pinned allocation of %lld bytes failed", (long long)bytes); return NTP_ENOMEM; }
+    G->pinned_ids = (char*)p;
+    int64_t off = 0;
+    each([&](const HostSparse& m, Chunk& c) {
+        c.h_packed_ids = G->pinned_ids + off + c.img_off_val % 16;
+        off += (c.packed_id_bytes + 31) / 16 * 16;
+        pack_ids(m.colidx + c.e_begin, c.e_end - c.e_begin, bits, reinterpret_cast<uint32_t*>(c.h_packed_ids));
+    });
+    return NTP_OK;
+}
 
 // what the aggregation does to an output element on its way out (AggArgs::epilogue)
 struct Epilogue {
@@ -468,6 +509,7 @@ void destroy(ntp_graph* G) {
     if (G->d_din) (void)hipFree(G->d_din);
     if (G->d_dout && G->d_dout != G->d_din) (void)hipFree(G->d_dout);
     if (G->pinned_meta) (void)hipHostFree(G->pinned_meta);
+    if (G->pinned_ids) (void)hipHostFree(G->pinned_ids);
     free_entries(G->g.csr, G->pinned_entries, G->val_pinned);
     free_entries(G->g.csc, G->pinned_entries, G->val_pinned);
     delete G;
@@ -503,6 +545,10 @@ int HipPass::copy_entries(const Chunk& c, int b, hipStream_t s) {
     char* img = g->stage[b];
     const size_t ne = (size_t)(c.e_end - c.e_begin);
     if (ne == 0) return NTP_OK;
+    if (c.h_packed_ids) {
+        HIP_TRY(hipMemcpyAsync(img + c.img_off_val, c.h_packed_ids, (size_t)c.packed_id_bytes, hipMemcpyHostToDevice, s));
+        return NTP_OK;
+    }
     HIP_TRY(hipMemcpyAsync(img + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice, s));
     if (with_val) HIP_TRY(hipMemcpyAsync(img + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice, s));
     return NTP_OK;
@@ -514,12 +560,18 @@ int HipPass::copy_by_kernel(const Chunk& c, int b, hipStream_t s, bool entries) 
     const int64_t entry_bytes = entries ? (c.e_end - c.e_begin) * 4 : 0;
     const void* src[3] = {c.h_meta_pinned, m.colidx + c.e_begin, m.val + c.e_begin};
     void* to[3] = {img, img + c.img_off_colidx, img + c.img_off_val};
-    const int64_t bytes[3] = {(int64_t)c.meta.size(), entry_bytes, with_val ? entry_bytes : 0};
+    int64_t bytes[3] = {(int64_t)c.meta.size(), entry_bytes, with_val ? entry_bytes : 0};
+    if (c.h_packed_ids) { src[1] = c.h_packed_ids; to[1] = to[2]; bytes[1] = entries ? c.packed_id_bytes : 0; }
     return launch_stage_chunk(src, to, bytes, s);
 }
 
 int HipPass::aggregate(const Chunk& c, int b) {
     char* img = g->stage[b];
+    if (c.h_packed_ids) {
+        const int rc = launch_unpack_ids(reinterpret_cast<const uint32_t*>(img + c.img_off_val), g->id_bits, c.e_end - c.e_begin,
+                                         reinterpret_cast<int32_t*>(img + c.img_off_colidx), cs);
+        if (rc != NTP_OK) return rc;
+    }
     if (!with_val) {          // row degree = dout and column degree = din where rows are sources
         const int rc = launch_rebuild_weights(reinterpret_cast<const int64_t*>(img + c.off_rowptr), c.row_begin, c.row_end - c.row_begin,
                                               c.e_begin, c.e_end - c.e_begin, reinterpret_cast<const int32_t*>(img + c.img_off_colidx),
@@ -554,6 +606,11 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
     const bool force_stream = flags & NTP_FORCE_STREAM;
     // entries go to pinned memory whenever chunks may have to be streamed
     G->pinned_entries = !G->host_only && (budget > 0 || force_stream);
+    // streamed chunks whose column ids all travel packed (pack_streamed_ids): the ids themselves stay in ordinary memory
+    G->id_bits = bits_of_ids(n);
+    const bool pack_all = force_stream && !G->host_only && !edge_weight && G->id_bits <= 28 && n_edges >= PACK_ENTRIES &&
+                          (chunk_edges == 0 || chunk_edges >= PACK_ENTRIES);
+    if (pack_all) G->pinned_entries = false;
     G->val_pinned = G->pinned_entries && edge_weight != nullptr;
     EntryAllocator alloc{G->pinned_entries ? alloc_pinned : alloc_plain, nullptr, alloc_plain};
 
@@ -659,6 +716,11 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
             F.n_all_reduce = (int)all.size();
             G->device_bytes += (int64_t)bytes;
             if (hipMemcpy(p, all.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) { (void)hipGetLastError(); set_error("upload of the split rows failed"); return NTP_EHIP; }
+        }
+        const bool rebuilt = pinned_meta_bytes > 0 && !edge_weight && G->id_bits <= 28;
+        if (rebuilt) {
+            rc = pack_streamed_ids(G, n_forms, pack_all);
+            if (rc != NTP_OK) return rc;
         }
         if (pinned_meta_bytes) {
             void* p = nullptr;
@@ -828,11 +890,10 @@ int ntp_graph_stream_bytes(const ntp_graph_t* g, int which, int64_t* bytes) {
     if (!g || !bytes) { set_error("NULL argument"); return NTP_EINVAL; }
     if (which != NTP_CSR && which != NTP_CSC) { set_error("which must be NTP_CSR or NTP_CSC"); return NTP_EINVAL; }
     const Form& F = (which == NTP_CSC && g->scatter_bwd()) ? g->form[0] : g->f(which);
-    const int64_t per_entry = g->streams_without_weights() ? 4 : 8;
     int64_t total = 0;
     if (!g->host_only)
         for (const Chunk& c : F.plan.chunks)
-            if (!c.d_image) total += (int64_t)c.meta.size() + (c.e_end - c.e_begin) * per_entry;
+            if (!c.d_image) total += streamed_bytes(c, !g->streams_without_weights());
     *bytes = total;
     return NTP_OK;
 }

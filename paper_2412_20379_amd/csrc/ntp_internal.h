@@ -145,6 +145,8 @@ struct Chunk {
     size_t off_packed_colidx = 0, off_packed_val = 0;
     int64_t n_packed = 0;                      // packed entries
     char* h_meta_pinned = nullptr;             // pinned copy of meta for streaming
+    char* h_packed_ids = nullptr;              // pinned: the column ids in as few bits as hold a vertex id (nullptr: they travel as
+    int64_t packed_id_bytes = 0;               // they are); goes where the weights are rebuilt afterwards, unpacked from there
 };
 
 struct Plan {
@@ -314,6 +316,11 @@ int launch_attention_scores_bwd(const float* Z, const float* a_src, const float*
 // copy up to three pieces (bytes a multiple of 4, 0: none) from pinned host memory; source and destination of a piece
 // agree modulo 16
 int launch_stage_chunk(const void* const src[3], void* const dst[3], const int64_t bytes[3], void* stream);
+
+// Column ids of `bits` bits each, one after the other from the lowest bit of packed[0] on (which is followed by one spare word)
+void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed);
+inline int64_t packed_words(int64_t n, int bits) { return (n * bits + 31) / 32 + 1; }
+int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n, int32_t* ids, void* stream);
 
 // val[e] of a chunk's entries from the structure (VAL_GCN / VAL_ONES): rowptr is the chunk's slice
 // (global entry offsets), colidx / val its entry arrays, deg_row / deg_col indexed by vertex id

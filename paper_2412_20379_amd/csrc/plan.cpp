@@ -103,6 +103,29 @@ struct ChunkBuilder {
 
 }  // namespace
 
+void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed) {
+    const int64_t words = packed_words(n, bits);
+    const int T = std::max(1, std::min(host_threads(), (int)std::min<int64_t>(64, n / (1 << 16) + 1)));
+    parallel_for_threads(T, [&](int t, int nt) {        // a thread writes whole words: the ids that reach into them
+        const int64_t w0 = words * t / nt, w1 = words * (t + 1) / nt;
+        int64_t k = w0 * 32 / bits;
+        uint64_t buf = 0;
+        int have = 0;                                   // bits of buf that belong to word w on
+        int64_t skip = w0 * 32 - k * bits;              // leading bits of id k that belong to the word before
+        for (int64_t w = w0; w < w1; ++w) {
+            while (have < 32 && k < n) {
+                buf |= ((uint64_t)(uint32_t)ids[k] >> skip) << have;
+                have += bits - (int)skip;
+                skip = 0;
+                ++k;
+            }
+            packed[w] = (uint32_t)buf;
+            buf >>= 32;
+            have = std::max(0, have - 32);
+        }
+    });
+}
+
 void pick_hub_columns(const HostSparse& m, const HostSparse* transposed, int max_slots, int64_t min_count,
                       std::vector<int32_t>* hub_cols) {
     hub_cols->clear();

@@ -289,3 +289,44 @@ def test_large_streamed_chunks_equal_resident_ones(case, f, n_rhs):
         assert torch.isfinite(a[:, :f]).all() and bool((b[:, f:] == 7.0).all())
     resident.close()
     streamed.close()
+
+
+@pytest.mark.parametrize("case", ["directed", "symmetric", "ones", "budget", "all alike", "2 vertices more"])
+def test_packed_column_ids_equal_resident_ones(case):
+    """Chunks of 655,360 entries and more send their column ids in as few bits as hold a vertex id: the bits of the resident chunks, for
+    ids of 16 and 17 bits, beside resident chunks, and where hardly an edge of a long list is left"""
+    import torch
+    n = (1 << 16) + (2 if case == "2 vertices more" else 0)
+    rng = gen.stream_rng(11, 3)
+    m = 1_500_000
+    src, dst = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+    src[:4] = dst[4:8] = n - 1
+    if case == "all alike":
+        src[:], dst[:] = 5, n - 1
+    flags = {"symmetric": ntp.NTP_GCN_FLAGS, "ones": 0}.get(case, ntp.NTP_DIRECTED_GCN_FLAGS)
+    ce = 1 << 20
+    resident = ntp.ntp_graph_build(n, src, dst, flags=flags, chunk_edges=ce)
+    nnz = ntp.ntp_graph_info(resident)["nnz"]
+    if case == "budget":
+        streamed = ntp.ntp_graph_build(n, src, dst, flags=flags, chunk_edges=ce, device_budget_bytes=24 << 20)
+        res = ntp.ntp_graph_chunks(streamed)["resident"]
+        assert 0 < res.sum() < res.size or 0 < ntp.ntp_graph_chunks(streamed, ntp.NTP_CSC)["resident"].sum() < res.size
+    else:
+        streamed = ntp.ntp_graph_build(n, src, dst, flags=flags | ntp.NTP_FORCE_STREAM, chunk_edges=ce)
+        assert ntp.ntp_graph_stream_bytes(streamed) < 2.2 * nnz + 40 * n + 65536
+    say("packed ids", case, "nnz", nnz, "bytes a pass", ntp.ntp_graph_stream_bytes(streamed))
+    x = torch.randn(n, 32, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(1))
+    cs, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for direction in (ntp.NTP_FWD, ntp.NTP_BWD, ntp.NTP_FWD):
+        a, b = torch.full_like(x, 3), torch.full_like(x, 5)
+        torch.cuda.synchronize()
+        ntp.ntp_chunked_aggregate(resident, direction, x, a, 32, 32, 32, ntp.NTP_F32, cs, cp)
+        ntp.ntp_chunked_aggregate(streamed, direction, x, b, 32, 32, 32, ntp.NTP_F32, cs, cp)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
+    for which in (ntp.NTP_CSR, ntp.NTP_CSC):
+        for u, v in zip(ntp.ntp_graph_export(resident, which), ntp.ntp_graph_export(streamed, which)):
+            assert np.array_equal(u, v)
+    resident.close()
+    streamed.close()
