@@ -8,10 +8,11 @@
 // where both sides are that wide) and walks its rows 16 at a time: coalesced loads of the next rows are in
 // flight while the present ones are cut into bf16 pieces and multiplied; no barrier until the end.  A block of eight
 // wavefronts is a few neighbouring tiles x shares of the rows of one range of vertices; the shares are added through
-// LDS in a fixed order, the ranges by sum_splits_kernel: deterministic.
+// LDS in a fixed order, the ranges by sum_splits_kernel: deterministic.  Wide fp32 products of many rows go through LDS all the
+// same (dw_shared_kernel): there the cutting costs more than the transposition.
 //
 // Bound: memory for a narrow side (256 x 64 on 169,343 rows: 217 MB in 0.043 ms = 5.0 TB/s), the two pipes of the SIMD
-// otherwise (256 x 256: matrix instructions 49 % of the time, other vector instructions 40 %, half of them beside those).
+// otherwise (256 x 256 here: matrix instructions 49 % of the time, other vector instructions 40 %, half of them beside those).
 // Against 128 x 128 tiles cut through LDS behind barriers, which this replaces (169,343 rows, fp32, without / with the ReLU
 // mask): 256 x 256 0.147 / 0.185 -> 0.139 / 0.161 ms, 128 x 256 0.085 / 0.108 -> 0.074 / 0.097, 256 x 64 0.065 / 0.149 ->
 // 0.044 / 0.052, 256 x 40 0.061 / 0.132 -> 0.042 / 0.046; 58,241 rows of 128 x 64 0.037 / 0.070 -> 0.020 / 0.023.
@@ -243,6 +244,156 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     }
 }
 
+// Wide dW from shared pieces: the eight wavefronts of a block own 64 x 64 each of a tile of 32 BK x 32 BZ columns, and all of
+// them walk the same rows, 32 at a time.  Every 16 rows of a 32-column block of A or dZ (a fragment) are loaded and cut by one
+// wavefront and put into LDS in operand order, where those find it that need it; the pieces of the next 32 rows go into the
+// other half of the LDS while these are multiplied: one barrier per 32 rows, 144 KB.
+//
+// Bound: the matrix pipe at the clock that its power leaves, and beside it the loads.  In dw_kernel a wavefront cuts
+// six fragments for every eight blocks of products, here three for every eight (and masks a quarter as often): vector
+// instructions on 306,129 rows of 256 x 256 fall from 54 to 31 million.  dW of 169,343 rows of 256 x 256, without / with the
+// ReLU mask, 0.144 / 0.166 -> 0.133 / 0.132 ms; 306,129 rows 0.250 / 0.285 -> 0.229 / 0.235, of 200 x 172 0.234 / 0.270 ->
+// 0.211 / 0.209; 400,000 rows of 128 x 256 0.182 / 0.214 -> 0.168 / 0.191.
+// A sum runs through many more rows than in the shares of dw_kernel, so it is put away and begun anew every 128 rows: relative
+// error on those 169,343 rows 3.9e-7 against 6.7e-7 in dw_kernel (9.5e-7 without; 64 rows 4.2e-7 and 2 % slower).
+template <bool MASK, int BK, int BZ>
+__global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
+    constexpr int WZ = BZ / 2, F = BK + BZ;                             // fragments of 16 rows
+    constexpr int UNITS_A = 2 * BK / 8, UNITS = 2 * F / 8;              // fragments that a wavefront cuts per 32 rows
+    constexpr int FOLD_ROWS = 128;
+    static_assert(BK / 2 * WZ == 8 && BK % 4 == 0 && BZ % 4 == 0, "eight wavefronts");
+    extern __shared__ uint4 pieces[];          // [buffer][16 rows][fragment][piece][lane]
+    constexpr int BUF = 2 * F * 3 * 64;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane & 31, h = lane >> 5;
+    const int minor = g.tiles_k * g.tiles_m, id = (int)blockIdx.x;
+    const int split = id / (8 * minor) * 8 + id % 8, t = id / 8 % minor;
+    if (split >= g.n_splits) return;
+    const int k = g.k, m = g.m;
+    const int c0 = t % g.tiles_k * (32 * BK), z0 = t / g.tiles_k * (32 * BZ);
+    const int64_t r0 = split * g.rows_per_split, r1 = min(r0 + g.rows_per_split, g.n);
+    const int wk = wave / WZ, wz = wave % WZ;
+
+    f32x16 acc[2][2] = {}, total[2][2] = {};
+    auto fold = [&] {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                total[i][j] += acc[i][j];
+                acc[i][j] = f32x16{};
+            }
+    };
+
+    // Unit u of this wavefront: a fragment of A (u < UNITS_A) or of dZ.  Column r of it, rows 2 j + h of its 16, as loads from a
+    // buffer that ends with the range: rows beyond it read as zero, and the lanes compute no addresses.  Columns beyond the matrix
+    // re-read the last one (their sums are not stored).
+    struct Raw { float x[8], mk[8]; };
+    int off[UNITS];
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        const int f = u < UNITS_A ? (wave + 8 * u) % BK : (wave + 8 * (u - UNITS_A)) % BZ;
+        off[u] = u < UNITS_A ? 4 * (min(c0 + 32 * f + r, k - 1) + h * k) : 4 * (min(z0 + 32 * f + r, m - 1) + h * m);
+    }
+    auto rows16 = [&](const void* at, int64_t first, int pitch) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(at) + min(first, r1) * pitch), 0,
+                                                 (int)min(max(r1 - first, (int64_t)0), (int64_t)16) * pitch, 0x00020000);
+    };
+    auto issue = [&](Raw& x, int u, int64_t row0) {
+        const bool of_z = u >= UNITS_A;
+        const int64_t first = row0 + (of_z ? (wave + 8 * (u - UNITS_A)) / BZ : (wave + 8 * u) / BK) * 16;
+        const int pitch = 4 * (of_z ? m : k);
+        const auto buf = rows16(of_z ? g.Z : g.A, first, pitch);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x.x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off[u], 2 * j * pitch, 0));
+        if (MASK && of_z) {
+            const auto mbuf = rows16(g.mask, first, pitch);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x.mk[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mbuf, off[u], 2 * j * pitch, 0));
+        }
+    };
+    auto stage = [&](Raw& x, int u, int buf) {
+        const bool of_z = u >= UNITS_A;
+        if (MASK && of_z) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x.x[j] = x.mk[j] > 0.f ? x.x[j] : 0.f;
+        }
+        uint4 p[3];
+        cut_rows<float, CORE_BF16>(x.x, p);
+        const int q = of_z ? wave + 8 * (u - UNITS_A) : wave + 8 * u;
+        const int at = buf * BUF + (of_z ? q / BZ * F + BK + q % BZ : q / BK * F + q % BK) * 3 * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) pieces[at + i * 64] = p[i];
+    };
+    Raw x[UNITS];
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) issue(x[u], u, r0);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+        stage(x[u], u, 0);
+        issue(x[u], u, r0 + 32);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int64_t row = r0; row < r1;) {
+        for (const int64_t stop = min(row + FOLD_ROWS, r1); row < stop; row += 32, buf ^= 1) {
+            const uint4* src = pieces + buf * BUF + lane;
+            uint4 pa[2][1][3], pb[2][2][3];            // operands of this product and of the next one
+            auto read_a = [&](int p, uint4 (&a)[1][3]) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a[0][q] = src[((p / 2 * F + 2 * wk + p % 2) * 3 + q) * 64];
+            };
+            auto read_b = [&](int s, uint4 (&b)[2][3]) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) b[j][q] = src[((s * F + BK + 2 * wz + j) * 3 + q) * 64];
+            };
+            read_b(0, pb[0]);
+            read_a(0, pa[0]);
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {              // 16 rows p / 2, column block p % 2 of A
+                if (p < 3) read_a(p + 1, pa[(p + 1) & 1]);
+                if (p == 1) read_b(1, pb[1]);
+                if (p < UNITS) {
+                    stage(x[p < UNITS ? p : 0], p, buf ^ 1);
+                    issue(x[p < UNITS ? p : 0], p, row + 64);
+                }
+                mfma_parts<CORE_BF16, 1, 2, 3>(pa[p & 1], pb[p / 2], reinterpret_cast<f32x16 (&)[1][2]>(acc[p % 2]));
+            }
+            __syncthreads();
+        }
+        fold();
+    }
+    // element e of a 32x32 block: row 8 * (e / 4) + 4 * h + e % 4 of the A columns, column r of dZ's
+    float* out = g.out + (int64_t)split * k * m;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int col = z0 + 64 * wz + 32 * j + r;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int rowk = c0 + 64 * wk + 32 * i + 8 * (e / 4) + 4 * h + e % 4;
+                if (col < m && rowk < k) out[(int64_t)rowk * m + col] = total[i][j][e];
+            }
+        }
+}
+
+template <bool MASK, int BK, int BZ>
+void launch_dw_shared(const DwArgs& g, hipStream_t st) {
+    constexpr int lds = 2 * 2 * (BK + BZ) * 3 * 1024;
+    auto kernel = dw_shared_kernel<MASK, BK, BZ>;
+    static bool allowed[64] = {};
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    if (dev >= 0 && dev < 64 && !allowed[dev])
+        allowed[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
+    const int64_t blocks = (int64_t)(g.n_splits + 7) / 8 * 8 * g.tiles_k * g.tiles_m;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(512), lds, st, g);
+}
+
 template <class T, Core C, bool MASK, int VA, int VB, int TA, int TN>
 void launch_dw(const DwArgs& g, hipStream_t st) {
     constexpr int lds = 4 * TA * TN * 16 * 64 * 4;          // the upper half of the wavefronts' sums
@@ -268,6 +419,10 @@ int pow2_up(int64_t x, int most) {
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //     against 39.1 us);
 //   k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
+//   fp32 whose tiles of 128 x 128 pair up without padding and whose blocks get 512 rows or more: 256 x 128 (or 128 x 256) per
+//     block of dw_shared_kernel.  Below that the longer tail of a block eats the gain (256 x 256 on 50,000 rows 48.5 against
+//     49.7 us) and its sums, in fewer chains than those of the eight shares, are less exact; with a padded pair the padding
+//     does (300 x 300 on 100,000 rows 0.271 / 0.308 ms, 602 x 128 on 58,241 0.101 / 0.107);
 //   else 128 x 64, whose operands are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343
 //     rows 0.134 against 0.164 ms.
 // m <= 32 and more than three row tiles of A take four of them side by side: whole rows of A from few blocks (us with one /
@@ -275,17 +430,29 @@ int pow2_up(int64_t x, int most) {
 // on 120,000 33.6 / 35.5, so not there; 602 x 16 on 8,000 13.9 / 16.4: the few rows of a block are better shared out).
 // Blocks: about one per compute unit; two column tiles side by side where there are two (they share the rows of A through the
 // L1), the other wavefronts share out the rows.
-enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY };
-int dw_shape(int64_t k, int64_t m, bool fp32_core) {
+enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE };
+int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
+    const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
+    if (f32 && !fp32_core && k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 131072)
+        return tk % 2 == 0 ? DW_SHARED_TALL : DW_SHARED_WIDE;
     if (k < 4) return DW_TINY;
     if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
     return fp32_core && k <= 32 ? DW_TINY : DW_NARROW;
 }
 
-DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core) {
+DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
     DwArgs g{};
     g.n = n; g.k = (int)k; g.m = (int)m;
-    const int shape = dw_shape(k, m, fp32_core);
+    const int shape = dw_shape(n, k, m, fp32_core, f32);
+    if (shape == DW_SHARED_TALL || shape == DW_SHARED_WIDE) {
+        const int bk = shape == DW_SHARED_TALL ? 256 : 128, bz = 384 - bk;
+        g.tiles_k = (int)((k + bk - 1) / bk);
+        g.tiles_m = (int)((m + bz - 1) / bz);
+        int64_t s = std::max<int64_t>(1, compute_units() / ((int64_t)g.tiles_k * g.tiles_m));
+        g.rows_per_split = ((n + s - 1) / s + 31) / 32 * 32;
+        g.n_splits = (int)((n + g.rows_per_split - 1) / g.rows_per_split);
+        return g;
+    }
     const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
     g.kt = shape == DW_NARROW && k > 384 && n > 10000 ? 4 : 1;
     g.mt = shape == DW_NARROW ? 1 : pow2_up((m + 32 * tn - 1) / (32 * tn), shape == DW_TINY ? 8 : shape == DW_SHORT ? 4 : 2);
@@ -302,7 +469,9 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core) {
 
 template <class T, Core C>
 void launch_dw_any(const DwArgs& g, hipStream_t st) {
-    switch (dw_shape(g.k, g.m, C == CORE_F32)) {
+    switch (dw_shape(g.n, g.k, g.m, C == CORE_F32, sizeof(T) == 4)) {
+        case DW_SHARED_TALL: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, 8, 4>(g, st) : launch_dw_shared<false, 8, 4>(g, st); break;
+        case DW_SHARED_WIDE: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, 4, 8>(g, st) : launch_dw_shared<false, 4, 8>(g, st); break;
         case DW_TINY:
             if constexpr (sizeof(T) == 2 || C == CORE_F32) g.mask ? launch_dw<T, C, true, 1, 1, 1, 1>(g, st) : launch_dw<T, C, false, 1, 1, 1, 1>(g, st);
             break;
@@ -317,12 +486,12 @@ void launch_dw_any(const DwArgs& g, hipStream_t st) {
 // fp32 operands with so few columns have a kernel on the fp32 instructions only (they are bound by reading dZ)
 bool nn_dw_fp32_only(int64_t k) { return k < 4; }
 
-int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core) { return dw_plan(n, k, m, fp32_core).n_splits; }
+int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) { return dw_plan(n, k, m, fp32_core, f32).n_splits; }
 
 // partial sums of every range of vertices to out [splits][k x m]; fp32_core: fp32 operands on the fp32 matrix instructions
 int launch_nn_dw(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m, int dtype,
                  bool fp32_core, void* stream) {
-    DwArgs g = dw_plan(n, k, m, fp32_core);
+    DwArgs g = dw_plan(n, k, m, fp32_core, dtype == NTP_F32);
     g.A = A; g.Z = dH; g.mask = mask; g.out = out;
     const hipStream_t st = (hipStream_t)stream;
     if (dtype == NTP_BF16) launch_dw_any<unsigned short, CORE_BF16>(g, st);

@@ -26,7 +26,7 @@ namespace ntp {
 namespace {
 
 // out[i] = sum over the splits of part[s * stride + i].  A block owns 64 consecutive
-// elements; wavefront w adds the splits w, w+4, ... in ascending order and the four sums
+// elements; wavefront w adds the splits w, w+4, ..., eight at a time, and the four sums
 // are combined as (s0 + s1) + (s2 + s3): fixed order, deterministic.
 __global__ void __launch_bounds__(256) sum_splits_kernel(const float* __restrict__ part, float* __restrict__ out,
                                                          int64_t count, int64_t stride, int n_splits) {
@@ -38,12 +38,11 @@ __global__ void __launch_bounds__(256) sum_splits_kernel(const float* __restrict
     if (i < count) {
         const float* p = part + i;
         int k = w;
-        for (; k + 28 < n_splits; k += 32) {       // eight loads in flight, added in ascending order
+        for (; k + 28 < n_splits; k += 32) {       // eight loads in flight, added in pairs: fewer roundings at the size of the sum
             float t[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) t[j] = p[(int64_t)(k + 4 * j) * stride];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s += t[j];
+            s += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
         }
         for (; k + 12 < n_splits; k += 16) {
             const float t0 = p[(int64_t)k * stride], t1 = p[(int64_t)(k + 4) * stride];
@@ -121,7 +120,7 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
     if (!dW) return NTP_OK;
     // dW[k x m] = A^T[k x n] * dZ[n x m] : contraction over the vertices, split over blocks
     const bool f32 = DTYPE<T> == NTP_F32 && (fp32_core(n, m) || nn_dw_fp32_only(k));
-    const int splits = nn_dw_splits(n, k, m, f32);
+    const int splits = nn_dw_splits(n, k, m, f32, DTYPE<T> == NTP_F32);
     const int rc = launch_nn_dw(A, dH, mask, splits > 1 ? (float*)ws : dW, n, k, m, DTYPE<T>, f32, st);
     return rc != NTP_OK ? rc : sum_splits(ws, dW, k * m, splits, st);
 }
@@ -129,7 +128,7 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
 }  // namespace
 
 int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m) {
-    const int S = n > 0 ? std::max(nn_dw_splits(n, k, m, false), nn_dw_splits(n, k, m, true)) : 1;
+    const int S = n > 0 ? std::max({nn_dw_splits(n, k, m, false, false), nn_dw_splits(n, k, m, false, true), nn_dw_splits(n, k, m, true, true)}) : 1;
     return S > 1 ? (int64_t)S * k * m * 4 : 0;
 }
 

@@ -346,7 +346,7 @@ int launch_nn_resident(const float* A, const float* mask, const float* B, float*
                        bool b_kcontig, bool relu, bool nt, void* stream);
 // dW = A^T dZ straight from memory (nn_dw_kernels.hip)
 bool nn_dw_fp32_only(int64_t k);
-int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core);
+int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32);
 int launch_nn_dw(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m, int dtype,
                  bool fp32_core, void* stream);
 int launch_relu(const void* dH, const void* H, void* out, int64_t n, int64_t f, int64_t ld, int dtype,

@@ -190,3 +190,38 @@ def test_many_rows_give_the_bits_of_few(k, m, act):
         e = min(b + part, n)
         ntp.ntp_nn_bwd(H[b:e], Wt, Hm[b:e], dH[b:e], few[b:e], None, e - b, m, k, act, ntp.NTP_F32, None, 0, st)
     assert torch.equal(dA[:n], few) and bool((dA[n] == 7.0).all())
+
+
+# one to eight tiles of 256 x 128 or (k in an odd number of 128s) 128 x 256, just above the fewest rows that are taken: row counts of
+# no whole step, of a step, of one row in the last range
+@pytest.mark.parametrize("n,k,m", [(131073, 130, 70), (131072, 256, 128), (131104, 200, 65), (65553, 129, 200), (65600, 256, 256),
+                                   (131087, 65, 129), (131072, 128, 256), (133000, 97, 250), (43700, 384, 256), (65569, 300, 129),
+                                   (16385, 512, 512)])
+@pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
+def test_wide_weight_gradients_of_many_rows(n, k, m, act):
+    """Whole numbers whose sums all stay below 2^24 come out exactly, with rows of NaN after the last one; random operands within a
+    rounding per step of a chain of 128 rows (8 steps of 6 products), per chain and per range, on top of what the cut leaves out"""
+    import torch
+    gen_ = torch.Generator(device="cuda:0").manual_seed(n + k * 1000 + m)
+    st = torch.cuda.current_stream()
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws, dW = torch.empty(max(4, wsb), dtype=torch.uint8, device="cuda:0"), torch.full((k * m + 1,), 7.0, device="cuda:0")
+    for whole in (True, False):
+        full = lambda c: torch.full((n + 40, c), float("nan"), device="cuda:0")
+        A, dH, H = full(k), full(m), full(m)
+        for x in (A, dH, H):
+            if whole:
+                x[:n] = torch.randint(-8, 9, x[:n].shape, generator=gen_, device="cuda:0").float()
+            else:
+                x[:n] = torch.randn(x[:n].shape, generator=gen_, device="cuda:0")
+        ntp.ntp_nn_bwd(A, None, H, dH, None, dW, n, k, m, act, ntp.NTP_F32, ws, wsb, st)
+        A64, Z64 = A[:n].double(), dH[:n].double()
+        if act == ntp.NTP_ACT_RELU:
+            Z64 *= H[:n] > 0
+        got, want = dW[:k * m].view(k, m).double(), A64.T @ Z64
+        if whole:
+            assert torch.equal(got, want)
+        else:
+            roundings = 48 + n / 128 / 32 + 64
+            assert bool(((got - want).abs() <= (2.0 ** -21 + roundings * 2.0 ** -24) * (A64.abs().T @ Z64.abs())).all())
+        assert float(dW[k * m]) == 7.0
