@@ -74,6 +74,7 @@ template <int VEC> struct IoF32 {
     static constexpr int kVec = VEC;
     typedef float Raw __attribute__((ext_vector_type(VEC)));          // a loaded vector
     static __device__ __forceinline__ Raw load_raw(const float* p) { return *reinterpret_cast<const Raw*>(p); }
+    static __device__ __forceinline__ Raw load_once(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const Raw*>(p)); }
     static __device__ __forceinline__ void expand(const Raw& r, float (&v)[VEC]) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) v[i] = r[i];
@@ -118,6 +119,10 @@ template <int VEC> struct IoBf16 {
     static __device__ __forceinline__ Raw load_raw(const unsigned short* p) {
         if constexpr (VEC > 1) return *reinterpret_cast<const Raw*>(p);
         else { Raw r; r[0] = *p; return r; }
+    }
+    static __device__ __forceinline__ Raw load_once(const unsigned short* p) {
+        if constexpr (VEC > 1) return __builtin_nontemporal_load(reinterpret_cast<const Raw*>(p));
+        else { Raw r; r[0] = __builtin_nontemporal_load(p); return r; }
     }
     static __device__ __forceinline__ void expand(const Raw& r, float (&v)[VEC]) {
         if constexpr (VEC > 1) {
@@ -261,7 +266,16 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         for (int j = 0; j < NACC; ++j) {
             if (a.epilogue && nval(j) > 0) {
                 float m[VEC];
-                if (a.M) IO::load(static_cast<const T*>(a.M) + (int64_t)row * a.ldm + colbase + j * L * VEC, m);
+                if (a.M) {
+                    const T* pm = static_cast<const T*>(a.M) + (int64_t)row * a.ldm + colbase + j * L * VEC;
+                    if (a.mask_once) {
+                        IO::expand(IO::load_once(pm), m);
+                        asm volatile("");          // (as in fetch)
+                    } else {
+                        asm volatile("");
+                        IO::load(pm, m);
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc[j][i] = (a.M ? m[i] : acc[j][i]) > 0.f ? acc[j][i] : 0.f;
             }

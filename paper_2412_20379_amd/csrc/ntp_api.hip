@@ -307,6 +307,10 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     // entries of two forms (210 + 78) 311 / 318, 63 M (505 + 157) 686 / 706.
     const int64_t es = dtype == NTP_BF16 ? 2 : 4, x_row = std::min(ldx * es, (f * es + 127) / 128 * 128);
     a.past_caches = (c.e_end - c.e_begin) * 8 + n * x_row > 280000000;
+    // The mask is read once: past the caches where it would displace rows of X that are still to be gathered (us with M through / past
+    // the caches: 169,343 rows of 256, 173 + 173 MB, 235 / 216; 1,224,514 of 32, 157 + 157 MB, 687 / 681; of 13, 78 + 78 MB, 651 /
+    // 657; 169,343 rows of 128, 87 + 87 MB, 105 / 117 with an M that is still there from its last use).
+    a.mask_once = epi.M && n * x_row + (c.row_end - c.row_begin) * x_row > 256000000;
 
     int L, nacc = 1, passes = 1;
     if (scatter) {

@@ -206,6 +206,7 @@ struct AggArgs {
     int32_t f;                 // slice width
     int32_t fp;                // row stride of `partial` in floats: f rounded up to 8
     int32_t pass_lanes;        // vectors per feature row and column pass (0: widest shape)
+    int32_t mask_once;         // 1: M is read with non-temporal loads (see run_chunk)
     int32_t past_caches;       // 1: indices and weights are read with non-temporal loads (see run_chunk)
     int32_t n_hub;             // hub columns (at most agg_hub_slots())
     int32_t n_waves;           // wavefronts of the launch

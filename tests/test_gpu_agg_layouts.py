@@ -82,3 +82,23 @@ def test_slices_give_the_bits_of_the_forms_own_arrays(slice_graphs, name, f, ld,
         keep = ~seen
         assert_close(y[keep], (oracle.round_bf16(ref).astype(np.float64) if dtype == "bf16" else ref)[keep], ref_abs[keep],
                      TOL_BF16 if dtype == "bf16" else TOL_F32, "slices")
+
+
+@pytest.mark.parametrize("name,f,ld,dtype", [("short", 128, 128, "f32"), ("short", 121, 124, "f32"), ("large", 1000, 1000, "f32"), ("short", 250, 256, "bf16")])
+def test_a_mask_beside_rows_beyond_the_caches(slice_graphs, name, f, ld, dtype):
+    """X and the mask above 256 MB together (the mask is read past the caches): the unmasked result where the mask is above zero"""
+    import torch
+    g, og = slice_graphs[name]
+    say("mask", name, f, ld, dtype)
+    n, bf16 = og.n, dtype == "bf16"
+    rnd = lambda: torch.randn(n, ld, generator=torch.Generator(device="cuda:0").manual_seed(f), device="cuda:0").to(torch.bfloat16 if bf16 else torch.float32)
+    X, M = rnd(), rnd().roll(1, 0)
+    M[5] = float("nan")
+    M[6], M[7] = 0.0, -0.0
+    code = ntp.NTP_BF16 if bf16 else ntp.NTP_F32
+    for direction, plain in ((ntp.NTP_FWD, ntp.ntp_aggregate_fwd), (ntp.NTP_BWD, ntp.ntp_aggregate_bwd)):
+        want, got = torch.full_like(X, 7.0), torch.full_like(X, 7.0)
+        plain(g, X, want, f, ld, ld, code)
+        want[:, :f] = torch.where(M[:, :f] > 0, want[:, :f], torch.zeros_like(want[:, :f]))
+        ntp.ntp_aggregate_act(g, direction, X, got, f, ld, ld, code, ntp.NTP_ACT_RELU, M, ld)
+        assert torch.equal(got, want)
