@@ -41,6 +41,7 @@ struct DwArgs {
     int tiles_k, tiles_m;  // block tiles
     int n_splits;
     int64_t rows_per_split;    // multiple of 16
+    int per_xcd;               // ceil(splits x tiles / 8): no XCD gets a block more than the others, which would be its second round
 };
 
 // VEC consecutive elements in one load (element alignment is enough)
@@ -77,9 +78,9 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     const int r = lane & 31, h = lane >> 5;
     const int per_share = g.kt * g.mt, shares = 8 / per_share;
     const int tile = wave % per_share, share = wave / per_share;
-    // blocks of one range of vertices have ids that differ by 8: one XCD
+    // an XCD (blocks 8 apart) takes per_xcd pieces of work in a row: the tiles of one range of vertices are mostly on one
     const int minor = g.tiles_k * g.tiles_m, id = (int)blockIdx.x;
-    const int split = id / (8 * minor) * 8 + id % 8, t = id / 8 % minor;
+    const int j = id % 8 * g.per_xcd + id / 8, split = j / minor, t = j % minor;
     if (split >= g.n_splits) return;
     const int c0 = (t % g.tiles_k * g.kt + tile % g.kt) * (32 * TA), z0 = (t / g.tiles_k * g.mt + tile / g.kt) * (32 * TN);
     const int64_t r0 = split * g.rows_per_split, r1 = min(r0 + g.rows_per_split, g.n);
@@ -268,7 +269,7 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 31, h = lane >> 5;
     const int minor = g.tiles_k * g.tiles_m, id = (int)blockIdx.x;
-    const int split = id / (8 * minor) * 8 + id % 8, t = id / 8 % minor;
+    const int j = id % 8 * g.per_xcd + id / 8, split = j / minor, t = j % minor;
     if (split >= g.n_splits) return;
     const int k = g.k, m = g.m;
     const int c0 = t % g.tiles_k * (32 * BK), z0 = t / g.tiles_k * (32 * BZ);
@@ -390,8 +391,7 @@ void launch_dw_shared(const DwArgs& g, hipStream_t st) {
     (void)hipGetDevice(&dev);
     if (dev >= 0 && dev < 64 && !allowed[dev])
         allowed[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
-    const int64_t blocks = (int64_t)(g.n_splits + 7) / 8 * 8 * g.tiles_k * g.tiles_m;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(512), lds, st, g);
+    hipLaunchKernelGGL(kernel, dim3(8u * (unsigned)g.per_xcd), dim3(512), lds, st, g);
 }
 
 template <class T, Core C, bool MASK, int VA, int VB, int TA, int TN>
@@ -403,8 +403,7 @@ void launch_dw(const DwArgs& g, hipStream_t st) {
     (void)hipGetDevice(&dev);
     if (dev >= 0 && dev < 64 && !allowed[dev])
         allowed[dev] = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
-    const int64_t blocks = (int64_t)(g.n_splits + 7) / 8 * 8 * g.tiles_k * g.tiles_m;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(512), lds, st, g);
+    hipLaunchKernelGGL(kernel, dim3(8u * (unsigned)g.per_xcd), dim3(512), lds, st, g);
 }
 
 int pow2_up(int64_t x, int most) {
@@ -422,14 +421,17 @@ int pow2_up(int64_t x, int most) {
 //   fp32 whose tiles of 128 x 128 pair up without padding and whose blocks get 512 rows or more: 256 x 128 (or 128 x 256) per
 //     block of dw_shared_kernel.  Below that the longer tail of a block eats the gain (256 x 256 on 50,000 rows 48.5 against
 //     49.7 us) and its sums, in fewer chains than those of the eight shares, are less exact; with a padded pair the padding
-//     does (300 x 300 on 100,000 rows 0.271 / 0.308 ms, 602 x 128 on 58,241 0.101 / 0.107);
+//     does (300 x 300 on 100,000 rows 0.168 / 0.206 ms, 602 x 128 on 58,241 0.070 / 0.077);
 //   else 128 x 64, whose operands are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343
 //     rows 0.134 against 0.164 ms.
 // m <= 32 and more than three row tiles of A take four of them side by side: whole rows of A from few blocks (us with one /
 // four, 602 x 16 on 16,000 rows 27.3 / 22.5, 50,000 54.7 / 46.9, 200,000 195 / 162; 1433 x 16 on 30,000 75.2 / 70.5; 256 x 16
 // on 120,000 33.6 / 35.5, so not there; 602 x 16 on 8,000 13.9 / 16.4: the few rows of a block are better shared out).
-// Blocks: about one per compute unit; two column tiles side by side where there are two (they share the rows of A through the
-// L1), the other wavefronts share out the rows.
+// Blocks: one per compute unit and no more (a range's sums fill most of the LDS), the same number on each XCD: with whole ranges
+// dealt to the XCDs, three tiles of 85 ranges came to 33 blocks for the 32 compute units of some of them, a second round
+// (602 x 128 on 58,241 rows 0.101 -> 0.070 ms, 384 x 384 on 169,343 0.465 -> 0.295, 700 x 100 on 8,000 0.033 -> 0.023).
+// Two column tiles side by side where there are two (they share the rows of A through the L1), the other wavefronts share out
+// the rows.
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE };
 int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
     const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
@@ -451,6 +453,7 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
         int64_t s = std::max<int64_t>(1, compute_units() / ((int64_t)g.tiles_k * g.tiles_m));
         g.rows_per_split = ((n + s - 1) / s + 31) / 32 * 32;
         g.n_splits = (int)((n + g.rows_per_split - 1) / g.rows_per_split);
+        g.per_xcd = (int)(((int64_t)g.n_splits * g.tiles_k * g.tiles_m + 7) / 8);
         return g;
     }
     const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
@@ -464,6 +467,7 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
     if (k < 4) s = std::min(s, std::max<int64_t>(1, n / 256));     // many column tiles: no more partial sums than rows pay for
     g.rows_per_split = ((n + s - 1) / s + 15) / 16 * 16;
     g.n_splits = (int)((n + g.rows_per_split - 1) / g.rows_per_split);
+    g.per_xcd = (int)((g.n_splits * tiles + 7) / 8);
     return g;
 }
 

@@ -196,11 +196,14 @@ def test_many_rows_give_the_bits_of_few(k, m, act):
 # no whole step, of a step, of one row in the last range
 @pytest.mark.parametrize("n,k,m", [(131073, 130, 70), (131072, 256, 128), (131104, 200, 65), (65553, 129, 200), (65600, 256, 256),
                                    (131087, 65, 129), (131072, 128, 256), (133000, 97, 250), (43700, 384, 256), (65569, 300, 129),
-                                   (16385, 512, 512)])
+                                   (16385, 512, 512),
+                                   # below them; tiles that divide neither 32 nor 256, up to more than there are compute units
+                                   (3000, 602, 128), (5000, 300, 300), (2001, 1433, 64), (900, 700, 100), (500, 1433, 700), (300, 2600, 2100)])
 @pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
-def test_wide_weight_gradients_of_many_rows(n, k, m, act):
+def test_wide_weight_gradients(n, k, m, act):
     """Whole numbers whose sums all stay below 2^24 come out exactly, with rows of NaN after the last one; random operands within a
-    rounding per step of a chain of 128 rows (8 steps of 6 products), per chain and per range, on top of what the cut leaves out"""
+    rounding per step of a chain of 128 rows (8 steps of 6 products; up to as many in the shares of few rows), per chain and per range, on
+    top of what the cut leaves out"""
     import torch
     gen_ = torch.Generator(device="cuda:0").manual_seed(n + k * 1000 + m)
     st = torch.cuda.current_stream()
