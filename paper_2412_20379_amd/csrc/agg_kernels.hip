@@ -72,6 +72,7 @@ template <int VEC> struct IoF32 {
     static_assert(VEC == 1 || VEC == 2 || VEC == 4, "fp32 vectors of 1, 2 or 4 elements");
     using elem = float;
     static constexpr int kVec = VEC;
+    static constexpr bool kAny = false;
     typedef float Raw __attribute__((ext_vector_type(VEC)));          // a loaded vector
     static __device__ __forceinline__ Raw load_raw(const float* p) { return *reinterpret_cast<const Raw*>(p); }
     static __device__ __forceinline__ Raw load_once(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const Raw*>(p)); }
@@ -107,10 +108,31 @@ template <int VEC> struct IoF32 {
     }
 };
 
+// Four floats at any float's address.  A vector that would cross the end of the slice lies at its last four columns instead (two
+// lanes then form and store the same elements), so the slice is read and stored in whole vectors only.
+struct IoF32Any : IoF32<4> {
+    static constexpr bool kAny = true;
+    typedef float V4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float V2 __attribute__((ext_vector_type(2), aligned(4)));
+    static __device__ __forceinline__ Raw load_raw(const float* p) { return *reinterpret_cast<const V4*>(p); }
+    static __device__ __forceinline__ Raw load_once(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const V4*>(p)); }
+    static __device__ __forceinline__ void load(const float* p, float (&v)[4]) { expand(load_raw(p), v); }
+    static __device__ __forceinline__ void store(float* p, const float (&v)[4]) {
+        const V4 t = {v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<V4*>(p) = t;
+    }
+    template <int N> static __device__ __forceinline__ void store_n(float* p, const float (&v)[4]) {
+        static_assert(N <= 2, "one or two elements");
+        if constexpr (N == 2) { const V2 t = {v[0], v[1]}; *reinterpret_cast<V2*>(p) = t; }
+        else *p = v[0];
+    }
+};
+
 template <int VEC> struct IoBf16 {
     static_assert(VEC == 1 || VEC == 2 || VEC == 4 || VEC == 8, "bf16 vectors of 1, 2, 4 or 8 elements");
     using elem = unsigned short;
     static constexpr int kVec = VEC;
+    static constexpr bool kAny = false;
     static __device__ __forceinline__ void unpack(unsigned w, float& lo, float& hi) {
         lo = __uint_as_float(w << 16);
         hi = __uint_as_float(w & 0xffff0000u);
@@ -199,8 +221,9 @@ __device__ __forceinline__ int64_t readlane_l(int64_t v, int lane) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Wavefronts per SIMD the register allocation must allow.  The line-wide shapes (8 lanes x 16 bytes) fit 6 per SIMD without
-// spilling; with 7 the fp32 one spills and is 2-4 % slower.  The other shapes keep the compiler's choice.
+// Wavefronts per SIMD the register allocation must allow.  The line-wide shapes (8 lanes x 16 bytes) fit 6 per SIMD without spilling
+// (the fp32 one comes out at 7); with 8 both spill and are 15-40 % slower, with 7 the bf16 one, 6 % slower.  The other shapes keep the
+// compiler's choice.
 template <class IO, int L, int NACC>
 constexpr int agg_min_waves() {
     return NACC == 1 && L == 8 && sizeof(typename IO::elem) * IO::kVec == 16 ? 6 : 1;
@@ -230,7 +253,9 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     const int mode = G.mode;
     const int g = lane / L;
     const int l = lane % L;
-    const int colbase = pass * PASS_W + l * VEC;
+    const int passbase = IO::kAny ? min(pass * PASS_W, a.f - VEC) : pass * PASS_W;
+    int colbase = pass * PASS_W + l * VEC;
+    if constexpr (IO::kAny) colbase = colbase < a.f ? min(colbase, a.f - VEC) : colbase;
 
     // elements of vector j that lie inside the slice (0..VEC)
     auto nval = [&](const int j) { return min(max(a.f - (colbase + j * L * VEC), 0), VEC); };
@@ -238,7 +263,6 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     // A lane whose vector lies outside the slice re-reads the first vector of its group's
     // 16*L-byte piece (or of the pass, if the whole piece is outside): an address the
     // active lanes fetch anyway, so it adds no cache line to the gather.
-    const int passbase = pass * PASS_W;
 #pragma unroll
     for (int j = 0; j < NACC; ++j) {
         const int c = colbase + j * L * VEC;
@@ -862,10 +886,9 @@ int launch_by_shape(const AggArgs& a, int L, int nacc, int n_passes, hipStream_t
             case 32: return launch_one<IO, 32, 1>(a, n_passes, st);
             case 64: return launch_one<IO, 64, 1>(a, n_passes, st);
         }
-    } else if (L == 64 && nacc == 2) {
-        return launch_one<IO, 64, 2>(a, n_passes, st);
-    } else if (L == 64 && nacc == 4) {
-        return launch_one<IO, 64, 4>(a, n_passes, st);
+    } else if constexpr (!IO::kAny) {
+        if (L == 64 && nacc == 2) return launch_one<IO, 64, 2>(a, n_passes, st);
+        if (L == 64 && nacc == 4) return launch_one<IO, 64, 4>(a, n_passes, st);
     }
     set_error("no aggregation kernel for lanes=%d acc=%d", L, nacc);
     return NTP_EUNSUPPORTED;
@@ -925,6 +948,28 @@ int agg_pick_vec(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t l
     return vec;
 }
 
+// Lanes, vectors and passes of a launch.  fp32 rows that are not all at 16-byte addresses are read in vectors of four all the same
+// (IoF32Any): us with vectors of one or two / of four, 2.5 M entries F = 33 81 / 46, 47 83 / 56, 66 111 / 74, 101 123 / 107, 130 188 /
+// 143, 514 983 / 712; 7.2 M entries F = 602 2391 / 1705.  Not where that takes twice as many passes as vectors of two (512 columns) and
+// ends in one of few columns (2.5 M entries F = 258 359 / 415, 302 386 / 415), not for rows of a few columns (F = 6 26 / 30), and up to 256
+// columns of few entries stay with more lanes per row, which end sooner (66 k entries F = 47 5.2 / 6.6; 130 k 7.8 / 7.5; 0.2 M
+// 13.3 / 9.6).
+AggShape agg_shape_of(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t ldy, int dtype, const void* M, int64_t ldm, int pass_lanes,
+                      int64_t entries) {
+    AggShape s;
+    s.vec = agg_pick_vec(X, Y, f, ldx, ldy, dtype, M, ldm);
+    const int64_t passes = (f + 255) / 256;
+    const bool few_last = passes > 1 && f - (passes - 1) * 256 < 128 && (f + 511) / 512 * 2 <= passes;
+    s.any = dtype == NTP_F32 && f >= 8 && (entries >= 131072 || f > 256) && (s.vec == 1 || (s.vec == 2 && !few_last));
+    if (s.any) s.vec = 4;
+    agg_shape(f, s.vec, pass_lanes, &s.lanes, &s.n_acc, &s.passes);
+    if (s.any && s.n_acc > 1) {
+        s.passes = (int)passes;
+        s.n_acc = 1;
+    }
+    return s;
+}
+
 int agg_hub_slots() { return HUB_SLOTS; }
 
 // The hub kernel exists for rows walked in 16-byte vectors by 4 or 8 lanes (64- and 128-byte
@@ -940,9 +985,9 @@ bool agg_uses_hub(const AggArgs& a, int dtype) {
 
 int launch_aggregate(const AggArgs& a, int dtype, void* stream) {
     hipStream_t st = (hipStream_t)stream;
-    const int vec = agg_pick_vec(a.X, a.Y, a.f, a.ldx, a.ldy, dtype, a.M, a.ldm);
-    int L, nacc, passes;
-    agg_shape(a.f, vec, a.pass_lanes, &L, &nacc, &passes);
+    const AggShape s = agg_shape_of(a.X, a.Y, a.f, a.ldx, a.ldy, dtype, a.M, a.ldm, a.pass_lanes, a.e_end - a.e_base);
+    const int vec = s.vec, L = s.lanes, nacc = s.n_acc, passes = s.passes;
+    if (s.any) return launch_by_shape<IoF32Any>(a, L, nacc, passes, st);
     if (agg_uses_hub(a, dtype)) {
         if (dtype == NTP_F32) return L == 8 ? launch_hub<IoF32<4>, 8>(a, passes, st) : launch_hub<IoF32<4>, 4>(a, passes, st);
         return L == 8 ? launch_hub<IoBf16<8>, 8>(a, passes, st) : launch_hub<IoBf16<8>, 4>(a, passes, st);

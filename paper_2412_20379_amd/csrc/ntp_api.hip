@@ -316,10 +316,10 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     if (scatter) {
         L = scatter_lanes(f);
     } else {
-        const int vec = agg_pick_vec(X, Y, f, ldx, ldy, dtype, epi.M, epi.ldm);
         const int64_t rows = c.partial_row ? 1 : c.row_end - c.row_begin;
-        a.pass_lanes = agg_pick_pass_lanes(X, ldx, dtype, vec, (double)(c.e_end - c.e_begin) / (double)std::max<int64_t>(1, rows));
-        agg_shape(f, vec, a.pass_lanes, &L, &nacc, &passes);
+        a.pass_lanes = agg_pick_pass_lanes(X, ldx, dtype, agg_pick_vec(X, Y, f, ldx, ldy, dtype, epi.M, epi.ldm), (double)(c.e_end - c.e_begin) / (double)std::max<int64_t>(1, rows));
+        const AggShape s = agg_shape_of(X, Y, f, ldx, ldy, dtype, epi.M, epi.ldm, a.pass_lanes, a.e_end - a.e_base);
+        L = s.lanes; nacc = s.n_acc; passes = s.passes;
     }
     const int R = 64 / L;
     bool hub = false;
@@ -352,10 +352,6 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
         const int cnt = c.bin_count[b];
         if (cnt == 0) continue;
         const int len = bin_max_degree(b);
-        // One lane group per row costs no reduction and one wavefront per R rows; it takes R times as long, so rows of
-        // more than 32 entries get it only in bf16 (whose reduction has twice the values) and in launches large enough
-        // (28.8 M entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us
-        // if they are, hence the rule; in fp32 it makes 1 % at best).
         // One lane group per row costs no reduction and one wavefront per R rows; it takes R times as long, so rows of
         // more than 32 entries get it only in launches large enough, in bf16 (whose reduction has twice the values; 28.8 M
         // entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us if they are,

@@ -255,6 +255,9 @@ int launch_zero_rows(void* Y, int64_t n, int64_t f, int64_t ld, int dtype, void*
 // lanes per row chosen for (f, vec): exposed for tests of the host logic
 void agg_shape(int64_t f, int vec, int pass_lanes, int* lanes_per_row, int* n_acc, int* n_passes);
 int agg_pick_pass_lanes(const void* X, int64_t ldx, int dtype, int vec, double entries_per_row);
+struct AggShape { int vec, lanes, n_acc, passes; bool any; };      // any: four floats at any address (IoF32Any)
+AggShape agg_shape_of(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t ldy, int dtype, const void* M, int64_t ldm, int pass_lanes,
+                      int64_t entries);
 int agg_pick_vec(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t ldy, int dtype, const void* M = nullptr, int64_t ldm = 0);
 
 // edge attention weights (attention_kernels.hip)

@@ -102,3 +102,32 @@ def test_a_mask_beside_rows_beyond_the_caches(slice_graphs, name, f, ld, dtype):
         want[:, :f] = torch.where(M[:, :f] > 0, want[:, :f], torch.zeros_like(want[:, :f]))
         ntp.ntp_aggregate_act(g, direction, X, got, f, ld, ld, code, ntp.NTP_ACT_RELU, M, ld)
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("name", ["short", "long"])
+@pytest.mark.parametrize("f,ldx,ldy,at", [(8, 9, 8, 0), (10, 10, 10, 1), (13, 13, 13, 0), (33, 33, 36, 0), (47, 48, 47, 3), (66, 66, 66, 0), (101, 102, 103, 0),
+                                          (130, 131, 130, 0), (255, 255, 255, 0), (257, 257, 257, 0), (260, 260, 260, 2), (386, 386, 386, 0), (514, 514, 514, 0),
+                                          (602, 602, 602, 0), (32, 32, 32, 1), (128, 128, 128, 1)])
+def test_rows_at_any_address_give_the_bits_of_aligned_ones(slice_graphs, name, f, ldx, ldy, at):
+    """fp32 rows that start at any float (row strides, first elements), read in vectors of four of which the last lies at the row's end,
+    against rows padded to 16 bytes; whole and masked, and nothing beyond the slice is written"""
+    import torch
+    g, og = slice_graphs[name]
+    if name == "short" and f > 130:
+        pytest.skip("no more of the same at a quarter of a gigabyte")
+    say("any address", name, f, ldx, ldy, at)
+    n, ld = og.n, (f + 3) // 4 * 4
+    ld += 4 * (ld % 32 == 0)                    # (rows of whole lines are walked line by line, in another order)
+    gen_ = torch.Generator(device="cuda:0").manual_seed(f)
+    rows = lambda stride, first: torch.full((n * stride + first,), 7.0, device="cuda:0")[first:].view(n, stride)
+    Xa, Ma, Xu, Mu = rows(ld, 0), rows(ld, 0), rows(ldx, at), rows(ldx, at)
+    for a, u in ((Xa, Xu), (Ma, Mu)):
+        a[:, :f] = torch.randn(n, f, generator=gen_, device="cuda:0")
+        u[:, :f] = a[:, :f]
+    for masked in (False, True):
+        for direction in (ntp.NTP_FWD, ntp.NTP_BWD):
+            want, got = rows(ld, 0), rows(ldy, at)
+            act = ntp.NTP_ACT_RELU if masked else ntp.NTP_ACT_NONE
+            ntp.ntp_aggregate_act(g, direction, Xa, want, f, ld, ld, ntp.NTP_F32, act, Ma if masked else None, ld if masked else 0)
+            ntp.ntp_aggregate_act(g, direction, Xu, got, f, ldx, ldy, ntp.NTP_F32, act, Mu if masked else None, ldx if masked else 0)
+            assert torch.equal(want[:, :f], got[:, :f]) and bool((got[:, f:] == 7.0).all())
