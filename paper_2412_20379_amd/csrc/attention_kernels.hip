@@ -137,11 +137,8 @@ __device__ __forceinline__ void attention_segment_stats(const AttArgs& a, const 
     if (threadIdx.x == 0) seg_stats[sg.slot] = make_float2(m, (red[0] + red[1]) + (red[2] + red[3]));
 }
 
-// pass 2: one wavefront per split row combines its segments: maximum of the maxima, sums
-// rescaled to it and added in a fixed tree
-__global__ void __launch_bounds__(64) attention_combine_kernel(const AttArgs a, const ReduceItem* items, const float2* seg_stats) {
-    const int lane = threadIdx.x;
-    const ReduceItem it = items[blockIdx.x];
+// a wavefront combines the segments of a row: maximum of the maxima, sums rescaled to it and added in a fixed tree
+__device__ __forceinline__ float2 attention_combine(const ReduceItem& it, const float2* seg_stats, int lane) {
     const float2* st = seg_stats + it.first_slot;
     float m = -INFINITY;
     for (int k = lane; k < it.n_slots; k += 64) m = fmaxf(m, st[k].x);
@@ -149,15 +146,30 @@ __global__ void __launch_bounds__(64) attention_combine_kernel(const AttArgs a, 
     float s = 0.f;
     for (int k = lane; k < it.n_slots; k += 64) s += st[k].y * expf(st[k].x - m);
     s = group_sum<64>(s, lane);
-    if (lane == 0) reinterpret_cast<float4*>(a.st)[it.row] = make_float4(a.q[it.row], m, 1.f / s, 0.f);
+    return make_float2(m, 1.f / s);
+}
+// pass 2 of forms that have a row with segments in several chunks: one wavefront per split row
+__global__ void __launch_bounds__(64) attention_combine_kernel(const AttArgs a, const ReduceItem* items, const float2* seg_stats) {
+    const ReduceItem it = items[blockIdx.x];
+    const float2 t = attention_combine(it, seg_stats, threadIdx.x);
+    if (threadIdx.x == 0) reinterpret_cast<float4*>(a.st)[it.row] = make_float4(a.q[it.row], t.x, t.y, 0.f);
 }
 
-// pass 3 (by destination): parked scores -> weights
-__global__ void __launch_bounds__(256) attention_segment_write_kernel(const AttArgs a, const Segment* segs) {
+// pass 3 (by destination): parked scores -> weights.  items: pass 2 as well, by every wavefront of the row's segments for itself (a
+// launch less, 5 us)
+__global__ void __launch_bounds__(256) attention_segment_write_kernel(const AttArgs a, const Segment* segs, const ReduceItem* items, const float2* seg_stats) {
     const Segment sg = segs[blockIdx.x];
     float* out = a.alpha + sg.e_begin;
-    const float4 t = reinterpret_cast<const float4*>(a.st)[sg.row];
-    for (int k = threadIdx.x; k < sg.len; k += 256) out[k] = weight_of(out[k], t.y, t.z);
+    float2 t;
+    if (items) {
+        const ReduceItem it = items[sg.item];
+        t = attention_combine(it, seg_stats, threadIdx.x & 63);
+        if (sg.slot == it.first_slot && threadIdx.x == 0) reinterpret_cast<float4*>(a.st)[sg.row] = make_float4(a.q[sg.row], t.x, t.y, 0.f);
+    } else {
+        const float4 st = reinterpret_cast<const float4*>(a.st)[sg.row];
+        t = make_float2(st.y, st.z);
+    }
+    for (int k = threadIdx.x; k < sg.len; k += 256) out[k] = weight_of(out[k], t.x, t.y);
 }
 // by source: the element-wise form
 __device__ __forceinline__ void attention_segment_write_transposed(const AttArgs& a, const Segment& sg) {
@@ -381,25 +393,50 @@ __device__ __forceinline__ void attention_bwd_work(const AttBwdArgs& a, int bloc
     }
 }
 
-// blocks [0, n_segs): the segments of split rows; the next n_block_rows: rows of more than 128 entries; then the rest
+// out[row] = sum of the row's slots, in segment order
+__device__ __forceinline__ float slots_sum(const ReduceItem& it, const float* slots) {
+    float s = 0.f;
+    for (int j = 0; j < it.n_slots; ++j) s += slots[it.first_slot + j];
+    return s;
+}
+__device__ __forceinline__ void attention_combine_slots(const AttCombine& c, int block) {
+    const int i = block * 256 + threadIdx.x;
+    if (i >= c.n_items) return;
+    const ReduceItem it = c.items[i];
+    const float s = slots_sum(it, c.slots);
+    c.out[it.row] = c.accumulate ? c.out[it.row] + s : s;
+}
+
+// blocks [0, n_segs): the segments of split rows; the next n_block_rows: rows of more than 128 entries; then the rest, and at the
+// end (by source) what is left of dq
 template <int VEC, int NJ, int L, bool TRANSPOSED>
-__global__ void __launch_bounds__(256) attention_bwd_kernel(const AttBwdArgs a, int n_segs, const Segment* segs, int n_group_rows, int n_block_rows) {
+__global__ void __launch_bounds__(256) attention_bwd_kernel(const AttBwdArgs a, int n_segs, const Segment* segs, int n_group_rows, int n_block_rows,
+                                                            const AttCombine also, int also_first) {
     __shared__ float red[256 / L];
     const int b = (int)blockIdx.x;
+    if (TRANSPOSED && b >= also_first) { attention_combine_slots(also, b - also_first); return; }
     if (b < n_segs) attention_bwd_work<VEC, NJ, L, TRANSPOSED, WORK_SEG>(a, b, 0, 0, segs, red);
     else if (b < n_segs + n_block_rows) attention_bwd_work<VEC, NJ, L, TRANSPOSED, WORK_BLOCK>(a, b - n_segs, n_group_rows, n_block_rows, segs, red);
     else attention_bwd_work<VEC, NJ, L, TRANSPOSED, WORK_GROUP>(a, b - n_segs - n_block_rows, 0, n_group_rows, segs, red);
 }
 
-// by destination, after the slots of t were combined: ds of a segment's entries from the parked dalpha, partial dq to the slot
-__global__ void __launch_bounds__(256) attention_bwd_segment_ds_kernel(const AttBwdArgs a, const Segment* segs) {
+// by destination, after the slots of t: ds of a segment's entries from the parked dalpha, partial dq to its slot.  items: t is summed
+// here, by every block of the row for itself (a launch less); else it is in place
+__global__ void __launch_bounds__(256) attention_bwd_segment_ds_kernel(const AttBwdArgs a, const Segment* segs, const ReduceItem* items) {
     __shared__ float red[4];
     const Segment sg = segs[blockIdx.x];
     const int32_t* ci = a.colidx + sg.e_begin;
     const float* al = a.alpha + sg.e_begin;
     float* park = a.park + sg.e_begin;
-    const float t = a.t[2 * sg.row];
     const float qv = a.q[sg.row];
+    float t;
+    if (items) {
+        const ReduceItem it = items[sg.item];
+        t = slots_sum(it, a.slots);
+        if (sg.slot == it.first_slot && threadIdx.x == 0) reinterpret_cast<float2*>(a.t)[sg.row] = make_float2(t, qv);
+    } else {
+        t = a.t[2 * sg.row];
+    }
     float dqp = 0.f;
     for (int k = threadIdx.x; k < sg.len; k += 256) {
         const float wv = (park[k] - t) * (a.p[ci[k]] + qv > 0.f ? 1.f : a.slope);
@@ -407,7 +444,7 @@ __global__ void __launch_bounds__(256) attention_bwd_segment_ds_kernel(const Att
         dqp += al[k] * wv;
     }
     dqp = block_sum<64>(group_sum<64>(dqp, threadIdx.x & 63), red);
-    if (threadIdx.x == 0) a.slots[sg.slot] = dqp;
+    if (threadIdx.x == 0) a.dq_slots[sg.slot] = dqp;
 }
 
 // dp[u] = sum over the by-source entries k of row u of alpha[k] * w[perm[k]] (EDGE_PERM graphs: w of every edge sits in
@@ -444,10 +481,12 @@ __device__ __forceinline__ void perm_sum_rows(const AttBwdArgs& a, const int32_t
 }
 
 __global__ void __launch_bounds__(256) perm_sum_kernel(const AttBwdArgs a, const int32_t* perm, int n_segs, const Segment* segs,
-                                                       int n_short_rows, int n_long_rows) {
+                                                       int n_short_rows, int n_long_rows, const AttCombine also, int also_first) {
     __shared__ float red[4];
     const int b = (int)blockIdx.x, long_blocks = (n_long_rows + 3) / 4;
-    if (b < n_segs) {
+    if (b >= also_first) {
+        attention_combine_slots(also, b - also_first);
+    } else if (b < n_segs) {
         const Segment sg = segs[b];
         float s = 0.f;
         for (int k = threadIdx.x; k < sg.len; k += 256) s += a.alpha[sg.e_begin + k] * a.park[perm[sg.e_begin + k]];
@@ -460,26 +499,24 @@ __global__ void __launch_bounds__(256) perm_sum_kernel(const AttBwdArgs a, const
     }
 }
 
-// out[row] = sum of the row's slots, in segment order (added to out[row] when accumulate is set);
-// with q: the pair (sum, q[row]) at out[2 row]
-__global__ void __launch_bounds__(256) attention_bwd_combine_kernel(const ReduceItem* items, int n_items, const float* slots, float* out,
-                                                                    const float* q, int accumulate) {
+__global__ void __launch_bounds__(256) attention_bwd_combine_kernel(const AttCombine c) { attention_combine_slots(c, (int)blockIdx.x); }
+
+// (t, q) of the split rows of forms that have a row with segments in several chunks
+__global__ void __launch_bounds__(256) attention_bwd_combine_t_kernel(const ReduceItem* items, int n_items, const float* slots, float* t, const float* q) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n_items) return;
     const ReduceItem it = items[i];
-    float s = 0.f;
-    for (int j = 0; j < it.n_slots; ++j) s += slots[it.first_slot + j];
-    if (q) reinterpret_cast<float2*>(out)[it.row] = make_float2(s, q[it.row]);
-    else out[it.row] = accumulate ? out[it.row] + s : s;
+    reinterpret_cast<float2*>(t)[it.row] = make_float2(slots_sum(it, slots), q[it.row]);
 }
 
 template <int VEC, int NJ, int L, bool T>
 int launch_bwd_shape(const AttBwdArgs& a, const AttBwdRows& r, hipStream_t st) {
     constexpr int ROWS_PER_BLOCK = 4 * (64 / L);
-    const int64_t blocks = (int64_t)r.n_segs + r.n_block_rows + (r.n_group_rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
+    const int64_t rows = (int64_t)r.n_segs + r.n_block_rows + (r.n_group_rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
+    const int64_t blocks = rows + (r.also.n_items + 255) / 256;
     if (blocks == 0) return NTP_OK;
     hipLaunchKernelGGL((attention_bwd_kernel<VEC, NJ, L, T>), dim3((unsigned)blocks), dim3(256), 0, st, a, r.n_segs, r.segs,
-                       r.n_group_rows, r.n_block_rows);
+                       r.n_group_rows, r.n_block_rows, r.also, (int)rows);
     return hipGetLastError() == hipSuccess ? NTP_OK : NTP_EHIP;
 }
 
@@ -508,12 +545,13 @@ int launch_bwd_vec(const AttBwdArgs& a, const AttBwdRows& r, hipStream_t st) {
 //            by source: all weights
 //   phase 1: per-row combination of the segment statistics (by-destination pass only)
 //   phase 2: weights of the split rows' segments (by-destination pass only)
+// combined: no row's segments lie in several chunks, phase 2 does the work of phase 1 and that is left out
 // bins: bin_row_off / bin_count describe rows[] (see Plan); bins 0..3 hold rows of up to 8
 // entries, 4..5 up to 32, the rest up to the split threshold; split rows come as segments
 // (segs, n_segs), their rows as reduce items; seg_stats: two floats per partial-sum slot.
 int launch_attention(const AttArgs& a, const int32_t* bin_row_off, const int32_t* bin_count,
                      const Segment* segs, int n_segs, const ReduceItem* split_rows, int n_split_rows,
-                     float* seg_stats, bool transposed, int phase, void* stream) {
+                     float* seg_stats, bool transposed, int phase, bool combined, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     float2* ss = reinterpret_cast<float2*>(seg_stats);
     if (phase == 1) {
@@ -521,7 +559,7 @@ int launch_attention(const AttArgs& a, const int32_t* bin_row_off, const int32_t
             hipLaunchKernelGGL(attention_combine_kernel, dim3((unsigned)n_split_rows), dim3(64), 0, st, a, split_rows, ss);
     } else if (phase == 2) {
         if (!transposed && n_segs > 0)
-            hipLaunchKernelGGL(attention_segment_write_kernel, dim3((unsigned)n_segs), dim3(256), 0, st, a, segs);
+            hipLaunchKernelGGL(attention_segment_write_kernel, dim3((unsigned)n_segs), dim3(256), 0, st, a, segs, combined ? split_rows : nullptr, ss);
     } else {
         AttRanges r;
         r.segs = segs;
@@ -547,24 +585,29 @@ int launch_attention(const AttArgs& a, const int32_t* bin_row_off, const int32_t
 // By destination: phase 0 = whole rows (dq, t) and the first sweep of the segments (partial t),
 // 1 = t of the split rows from their slots, 2 = second sweep of the segments (partial dq),
 // 3 = dq of the split rows.  By source: phase 0 = whole rows and segments (partial dp), 1 = dp of
-// the split rows.  The caller runs each phase over every chunk before the next one.
+// the split rows.  The caller runs each phase over every chunk before the next one.  combined: phase 2 does the work of phase 1 by
+// destination, which is left out (as above); r.also: phase 0 by source does that of phase 3.  Each launch less is 5 us, the epoch of
+// 2.5 M entries 1,420 -> 1,400 us.
 // perm (by source only, nullable): the edge permutation, with w of every edge in a.park (see perm_sum_kernel).
-int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, const int32_t* perm, void* stream) {
+int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, bool combined, const int32_t* perm, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     int rc = NTP_OK;
     if (phase == 1 || phase == 3) {
         if (r.n_split_rows == 0) return NTP_OK;
-        const bool is_t = phase == 1 && !transposed;
-        hipLaunchKernelGGL(attention_bwd_combine_kernel, dim3((unsigned)((r.n_split_rows + 255) / 256)), dim3(256), 0, st,
-                           r.split_rows, r.n_split_rows, a.slots, is_t ? a.t : a.out, is_t ? a.q : (const float*)nullptr,
-                           is_t ? 0 : a.accumulate);
+        const dim3 blocks((unsigned)((r.n_split_rows + 255) / 256));
+        if (phase == 1 && !transposed)
+            hipLaunchKernelGGL(attention_bwd_combine_t_kernel, blocks, dim3(256), 0, st, r.split_rows, r.n_split_rows, a.slots, a.t, a.q);
+        else
+            hipLaunchKernelGGL(attention_bwd_combine_kernel, blocks, dim3(256), 0, st,
+                               AttCombine{r.split_rows, transposed ? a.slots : a.dq_slots, a.out, r.n_split_rows, a.accumulate});
     } else if (phase == 2) {
-        if (r.n_segs > 0) hipLaunchKernelGGL(attention_bwd_segment_ds_kernel, dim3((unsigned)r.n_segs), dim3(256), 0, st, a, r.segs);
+        if (r.n_segs > 0)
+            hipLaunchKernelGGL(attention_bwd_segment_ds_kernel, dim3((unsigned)r.n_segs), dim3(256), 0, st, a, r.segs, combined ? r.split_rows : nullptr);
     } else if (perm) {
         const int n_long = r.n_group_rows + r.n_block_rows - r.n_rows_32;
-        const int64_t blocks = (int64_t)r.n_segs + (n_long + 3) / 4 + (r.n_rows_32 + 31) / 32;
+        const int64_t rows = (int64_t)r.n_segs + (n_long + 3) / 4 + (r.n_rows_32 + 31) / 32, blocks = rows + (r.also.n_items + 255) / 256;
         if (blocks > 0)
-            hipLaunchKernelGGL(perm_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, perm, r.n_segs, r.segs, r.n_rows_32, n_long);
+            hipLaunchKernelGGL(perm_sum_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, perm, r.n_segs, r.segs, r.n_rows_32, n_long, r.also, (int)rows);
     } else {
         const bool vec4 = a.m % 4 == 0 && a.ld_own % 4 == 0 && a.ld_other % 4 == 0 &&
                           (uintptr_t)a.own % 16 == 0 && (uintptr_t)a.other % 16 == 0;

@@ -1083,8 +1083,10 @@ int ntp_edge_softmax(ntp_graph_t* g, const float* p, const float* q, float negat
     float* seg_stats = g->att_stats + 4 * n;
     // chunk by chunk, phase by phase (a split row's segments may lie in several chunks)
     auto run = [&](const Form& F, float* out, bool transposed) -> int {
+        const bool combined = !F.plan.has_partial_rows();         // phase 1 as part of phase 2
         for (int phase = 0; phase < (transposed ? 1 : 3); ++phase)
             for (const Chunk& c : F.plan.chunks) {
+                if (combined && phase == 1) continue;
                 AttArgs a;
                 a.rowptr = reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin;
                 a.colidx = reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin;
@@ -1096,7 +1098,7 @@ int ntp_edge_softmax(ntp_graph_t* g, const float* p, const float* q, float negat
                 const int rc = launch_attention(a, c.bin_row_off, c.bin_count,
                                                 reinterpret_cast<const Segment*>(c.d_image + c.off_segs), c.n_segs,
                                                 reinterpret_cast<const ReduceItem*>(c.d_image + c.off_reduce), c.n_reduce,
-                                                seg_stats, transposed, phase, stream);
+                                                seg_stats, transposed, phase, combined, stream);
                 if (rc != NTP_OK) return rc;
             }
         return NTP_OK;
@@ -1123,25 +1125,32 @@ int ntp_edge_softmax_bwd(ntp_graph_t* g, const float* p, const float* q, float n
         set_error("the attention gradient needs every chunk of the topology device-resident");
         return NTP_EBUDGET;
     }
-    // scratch kept by the handle: (t, q) of every destination, one partial sum per segment of a
+    // scratch kept by the handle: (t, q) of every destination, two partial sums per segment of a
     // split row, dalpha of every edge
     const int64_t nnz = g->g.csr.nnz;
     const int64_t n_slots = std::max(Fin.plan.n_slots, Fout.plan.n_slots);
     if (!g->att_bwd) {
         void* ptr = nullptr;
-        const size_t bytes = ((size_t)nnz + 2 * (size_t)n + (size_t)n_slots) * 4 + 16;
+        const size_t bytes = ((size_t)nnz + 2 * (size_t)n + 2 * (size_t)n_slots) * 4 + 16;
         if (hipMalloc(&ptr, bytes) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of %zu bytes failed", bytes); return NTP_ENOMEM; }
         g->att_bwd = (float*)ptr;
         g->device_bytes += (int64_t)bytes;
     }
     float* t = g->att_bwd;              // (t, q) pairs
     float* slots = t + 2 * n;
-    float* park = slots + n_slots;
+    float* dq_slots = slots + n_slots;
+    float* park = dq_slots + n_slots;
     const bool by_perm = g->d_perm != nullptr;
     // chunk by chunk, phase by phase (a split row's segments may lie in several chunks)
+    // t of split rows where their ds is formed (phase 1 in phase 2), and dq of theirs beside the by-source pass (phase 3 in its phase 0): two
+    // launches of 5 us less.  Not with a row whose segments lie in several chunks; the latter for one chunk and buffers apart only.
+    const bool combined = !Fin.plan.has_partial_rows();
+    const bool dq_later = combined && Fin.plan.chunks.size() == 1 && Fin.plan.chunks[0].n_reduce > 0 && 
+                          ((uintptr_t)(dp + n) <= (uintptr_t)dq || (uintptr_t)(dq + n) <= (uintptr_t)dp);
     auto run = [&](const Form& F, bool transposed) -> int {
         for (int phase = 0; phase < (transposed ? 2 : 4); ++phase)
             for (const Chunk& c : F.plan.chunks) {
+                if (!transposed && ((combined && phase == 1) || (dq_later && phase == 3))) continue;
                 AttBwdArgs a;
                 a.rowptr = reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin;
                 a.colidx = reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin;
@@ -1156,6 +1165,7 @@ int ntp_edge_softmax_bwd(ntp_graph_t* g, const float* p, const float* q, float n
                 a.park = park;
                 a.out = transposed ? dp : dq;
                 a.slots = slots;
+                a.dq_slots = dq_slots;
                 a.slope = negative_slope;
                 a.m = (int32_t)m;
                 a.accumulate = accumulate ? 1 : 0;
@@ -1168,7 +1178,12 @@ int ntp_edge_softmax_bwd(ntp_graph_t* g, const float* p, const float* q, float n
                 r.n_segs = c.n_segs;
                 r.split_rows = reinterpret_cast<const ReduceItem*>(c.d_image + c.off_reduce);
                 r.n_split_rows = c.n_reduce;
-                const int rc = launch_attention_bwd(a, r, transposed, phase, transposed && by_perm ? g->d_perm : nullptr, stream);
+                r.also = AttCombine{};
+                if (transposed && dq_later && phase == 0 && &c == F.plan.chunks.data()) {
+                    const Chunk& f = Fin.plan.chunks[0];
+                    r.also = AttCombine{reinterpret_cast<const ReduceItem*>(f.d_image + f.off_reduce), dq_slots, dq, f.n_reduce, accumulate ? 1 : 0};
+                }
+                const int rc = launch_attention_bwd(a, r, transposed, phase, combined, transposed && by_perm ? g->d_perm : nullptr, stream);
                 if (rc != NTP_OK) return rc;
             }
         return NTP_OK;

@@ -107,7 +107,7 @@ struct Segment {        // one piece of a split row (device-visible, 24 bytes)
     int32_t len;        // number of entries
     int32_t row;        // row the piece belongs to
     int32_t slot;       // partial-sum slot (global numbering within the form)
-    int32_t pad;
+    int32_t item;       // reduction item of the row in this chunk (-1: a row with segments in other chunks)
 };
 
 struct ReduceItem {     // a split row whose last segment lies in this chunk (16 bytes)
@@ -159,6 +159,11 @@ struct Plan {
     int64_t n_slots = 0;                       // partial-sum slots of the whole form
     size_t max_img_bytes = 0;                  // largest chunk image (staging buffer size)
     std::vector<Chunk> chunks;
+    bool has_partial_rows() const {            // a row with segments in several chunks?
+        for (const Chunk& c : chunks)
+            if (c.partial_row) return true;
+        return false;
+    }
 };
 
 // Build the plan of one compressed form.  chunk_edges <= 0: a single chunk.
@@ -274,7 +279,7 @@ struct AttArgs {
 };
 int launch_attention(const AttArgs& a, const int32_t* bin_row_off, const int32_t* bin_count,
                      const Segment* segs, int n_segs, const ReduceItem* split_rows, int n_split_rows,
-                     float* seg_stats, bool transposed, int phase, void* stream);
+                     float* seg_stats, bool transposed, int phase, bool combined, void* stream);
 
 struct AttBwdArgs {
     const int64_t* rowptr;     // indexed by the global row id
@@ -290,10 +295,18 @@ struct AttBwdArgs {
     float* park;               // [nnz] dalpha per entry (by-destination pass)
     float* out;                // dq (by destination) or dp (by source)
     float* slots;              // [n_slots] partial sums of the segments of split rows
+    float* dq_slots;           // by destination: those of dq
     float slope;
     int32_t m;                 // feature width
     int32_t accumulate;        // add to out instead of overwriting it
     int32_t keep_w;            // by destination: leave (dalpha - t) * LeakyReLU' of every entry in park
+};
+struct AttCombine {                    // out[row] = (out[row] +) sum of the row's slots, in segment order
+    const ReduceItem* items;
+    const float* slots;
+    float* out;
+    int n_items;
+    int accumulate;
 };
 // rows[0 .. n_group_rows): a lane group each; rows[n_group_rows .. + n_block_rows): a wavefront
 // each (the bin lists are stored by increasing entry count); split rows: a block per segment
@@ -305,8 +318,9 @@ struct AttBwdRows {
     int n_segs;
     const ReduceItem* split_rows;      // rows whose last segment lies in this chunk
     int n_split_rows;
+    AttCombine also;                   // by source: dq of the split rows of the other form (n_items 0: is there already)
 };
-int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, const int32_t* perm, void* stream);
+int launch_attention_bwd(const AttBwdArgs& a, const AttBwdRows& r, bool transposed, int phase, bool combined, const int32_t* perm, void* stream);
 
 // per-vertex attention scores and their chain rule (attention_scores_kernels.hip)
 int64_t attention_scores_max_width();

@@ -210,7 +210,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
                     c.max_split_len = (int32_t)std::max<int64_t>(c.max_split_len, std::min<int64_t>(d, INT32_MAX));
                     for (int64_t i = 0; i < nseg; ++i) {
                         const int64_t l = base + (i < extra ? 1 : 0);
-                        cb.segs.push_back(Segment{e, (int32_t)l, (int32_t)v, next_slot++, 0});
+                        cb.segs.push_back(Segment{e, (int32_t)l, (int32_t)v, next_slot++, (int32_t)cb.reduce.size() - 1});
                         e += l;
                     }
                 }
@@ -234,7 +234,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
                 while (i < nseg) {
                     const int64_t l = base + (i < extra ? 1 : 0);
                     if (used + l > chunk_edges && used > 0) break;
-                    cb.segs.push_back(Segment{e, (int32_t)l, (int32_t)r, next_slot++, 0});
+                    cb.segs.push_back(Segment{e, (int32_t)l, (int32_t)r, next_slot++, -1});
                     e += l; used += l; ++i;
                 }
                 c.e_end = e;

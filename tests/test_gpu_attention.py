@@ -453,6 +453,25 @@ def test_score_gradient_accumulates_over_calls(hub, hub_perm):
 
 
 
+def test_score_gradients_summed_in_one_buffer(hub, hub_perm):
+    """dp and dq may be the same accumulated buffer: it gains dq, then dp (the sums of split rows come last otherwise)"""
+    import torch
+    from gpu_util import dev_f32
+    for n, src, dst, g, og in (hub, hub_perm):
+        nnz, m = og.csr.nnz, 24
+        p, q = _scores(n, 33)
+        rng = gen.stream_rng(33, 79)
+        Z, dY = (dev_f32(rng.normal(size=(n, m)).astype(np.float32)) for _ in range(2))
+        a_in, a_out = _device_alpha(g, nnz, p, q, 0.2)
+        pd, qd = dev_f32(p), dev_f32(q)
+        dp, dq = torch.empty(n, device="cuda:0"), torch.empty(n, device="cuda:0")
+        ntp.ntp_edge_softmax_bwd(g, pd, qd, 0.2, a_in, a_out, Z, dY, m, m, m, dp, dq, False)
+        both = dev_f32(rng.normal(size=n).astype(np.float32))
+        want = (both + dq) + dp
+        ntp.ntp_edge_softmax_bwd(g, pd, qd, 0.2, a_in, a_out, Z, dY, m, m, m, both, both, True)
+        assert torch.equal(both, want)
+
+
 def test_two_heads_on_column_blocks(hub):
     """several attention heads = one call per head on its block of columns of a wider matrix
     (row strides, offset base pointers): each head's results equal those of a separate compact run"""
