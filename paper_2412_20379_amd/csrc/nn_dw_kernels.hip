@@ -41,6 +41,7 @@ struct DwArgs {
     int tiles_k, tiles_m;  // block tiles
     int n_splits;
     int64_t rows_per_split;    // multiple of 16
+    int shape;                 // see dw_shape
     int per_xcd;               // ceil(splits x tiles / 8): no XCD gets a block more than the others, which would be its second round
 };
 
@@ -433,19 +434,19 @@ int pow2_up(int64_t x, int most) {
 // Two column tiles side by side where there are two (they share the rows of A through the L1), the other wavefronts share out
 // the rows.
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE };
-int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
+int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
     const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
-    if (f32 && !fp32_core && k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 131072)
+    if (shared && !fp32_core && k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 131072)
         return tk % 2 == 0 ? DW_SHARED_TALL : DW_SHARED_WIDE;
     if (k < 4) return DW_TINY;
     if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
     return fp32_core && k <= 32 ? DW_TINY : DW_NARROW;
 }
 
-DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
+DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
     DwArgs g{};
     g.n = n; g.k = (int)k; g.m = (int)m;
-    const int shape = dw_shape(n, k, m, fp32_core, f32);
+    const int shape = g.shape = dw_shape(n, k, m, fp32_core, shared);
     if (shape == DW_SHARED_TALL || shape == DW_SHARED_WIDE) {
         const int bk = shape == DW_SHARED_TALL ? 256 : 128, bz = 384 - bk;
         g.tiles_k = (int)((k + bk - 1) / bk);
@@ -473,7 +474,7 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) {
 
 template <class T, Core C>
 void launch_dw_any(const DwArgs& g, hipStream_t st) {
-    switch (dw_shape(g.n, g.k, g.m, C == CORE_F32, sizeof(T) == 4)) {
+    switch (g.shape) {
         case DW_SHARED_TALL: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, 8, 4>(g, st) : launch_dw_shared<false, 8, 4>(g, st); break;
         case DW_SHARED_WIDE: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, 4, 8>(g, st) : launch_dw_shared<false, 4, 8>(g, st); break;
         case DW_TINY:
@@ -490,12 +491,13 @@ void launch_dw_any(const DwArgs& g, hipStream_t st) {
 // fp32 operands with so few columns have a kernel on the fp32 instructions only (they are bound by reading dZ)
 bool nn_dw_fp32_only(int64_t k) { return k < 4; }
 
-int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32) { return dw_plan(n, k, m, fp32_core, f32).n_splits; }
+int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) { return dw_plan(n, k, m, fp32_core, shared).n_splits; }
 
-// partial sums of every range of vertices to out [splits][k x m]; fp32_core: fp32 operands on the fp32 matrix instructions
+// partial sums of every range of vertices to out [splits][k x m]; fp32_core: fp32 operands on the fp32 matrix instructions; shared:
+// dw_shared_kernel may take them (fp32, and out holds its splits)
 int launch_nn_dw(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m, int dtype,
-                 bool fp32_core, void* stream) {
-    DwArgs g = dw_plan(n, k, m, fp32_core, dtype == NTP_F32);
+                 bool fp32_core, bool shared, void* stream) {
+    DwArgs g = dw_plan(n, k, m, fp32_core, shared);
     g.A = A; g.Z = dH; g.mask = mask; g.out = out;
     const hipStream_t st = (hipStream_t)stream;
     if (dtype == NTP_BF16) launch_dw_any<unsigned short, CORE_BF16>(g, st);

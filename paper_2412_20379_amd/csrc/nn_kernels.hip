@@ -111,7 +111,7 @@ int nn_fwd_t(const void* A, const void* W, void* H, int64_t n, int64_t k, int64_
 
 template <class T>
 int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* dA, float* dW,
-             int64_t n, int64_t k, int64_t m, int act, void* ws, hipStream_t st) {
+             int64_t n, int64_t k, int64_t m, int act, void* ws, int64_t ws_bytes, hipStream_t st) {
     const void* mask = act == NTP_ACT_RELU ? H : nullptr;
     if (dA) {       // dA[n x k] = dZ[n x m] * W^T : contraction over m; W is read as (kk=m, j=k) = W[j*m + kk]
         const int rc = launch_nn_strip(dH, mask, W, dA, n, m, k, m, m, k, true, false, DTYPE<T>, fp32_core(m, k), st);
@@ -120,15 +120,16 @@ int nn_bwd_t(const void* A, const void* W, const void* H, const void* dH, void* 
     if (!dW) return NTP_OK;
     // dW[k x m] = A^T[k x n] * dZ[n x m] : contraction over the vertices, split over blocks
     const bool f32 = DTYPE<T> == NTP_F32 && (fp32_core(n, m) || nn_dw_fp32_only(k));
-    const int splits = nn_dw_splits(n, k, m, f32, DTYPE<T> == NTP_F32);
-    const int rc = launch_nn_dw(A, dH, mask, splits > 1 ? (float*)ws : dW, n, k, m, DTYPE<T>, f32, st);
+    const bool shared = DTYPE<T> == NTP_F32 && ws && ws_bytes >= nn_bwd_workspace_bytes(n, k, m);
+    const int splits = nn_dw_splits(n, k, m, f32, shared);
+    const int rc = launch_nn_dw(A, dH, mask, splits > 1 ? (float*)ws : dW, n, k, m, DTYPE<T>, f32, shared, st);
     return rc != NTP_OK ? rc : sum_splits(ws, dW, k * m, splits, st);
 }
 
 }  // namespace
 
-int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m) {
-    const int S = n > 0 ? std::max({nn_dw_splits(n, k, m, false, false), nn_dw_splits(n, k, m, false, true), nn_dw_splits(n, k, m, true, true)}) : 1;
+int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m, bool shared) {
+    const int S = n > 0 ? std::max({nn_dw_splits(n, k, m, false, false), nn_dw_splits(n, k, m, false, shared), nn_dw_splits(n, k, m, true, false)}) : 1;
     return S > 1 ? (int64_t)S * k * m * 4 : 0;
 }
 
@@ -161,7 +162,7 @@ int launch_nn_fwd(const void* A, const void* W, void* H, int64_t n, int64_t k, i
 
 int launch_nn_bwd(const void* A, const void* W, const void* H, const void* dH, void* dA, float* dW,
                   int64_t n, int64_t k, int64_t m, int act, int dtype,
-                  void* workspace, int64_t, void* stream) {
+                  void* workspace, int64_t workspace_bytes, void* stream) {
     hipStream_t st = (hipStream_t)stream;
     if (n == 0) {   // nothing to contract over: dW = 0 (a fill kernel, not a memset node)
         if (!dW) return NTP_OK;
@@ -172,8 +173,8 @@ int launch_nn_bwd(const void* A, const void* W, const void* H, const void* dH, v
         if (e != hipSuccess) { set_error("fill launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
         return NTP_OK;
     }
-    return dtype == NTP_BF16 ? nn_bwd_t<unsigned short>(A, W, H, dH, dA, dW, n, k, m, act, workspace, st)
-                             : nn_bwd_t<float>(A, W, H, dH, dA, dW, n, k, m, act, workspace, st);
+    return dtype == NTP_BF16 ? nn_bwd_t<unsigned short>(A, W, H, dH, dA, dW, n, k, m, act, workspace, workspace_bytes, st)
+                             : nn_bwd_t<float>(A, W, H, dH, dA, dW, n, k, m, act, workspace, workspace_bytes, st);
 }
 
 }  // namespace ntp

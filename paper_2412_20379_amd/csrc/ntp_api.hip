@@ -1241,7 +1241,7 @@ int ntp_nn_bwd(const void* A, const void* W, const void* H, const void* dH, void
     if (n > 0 && (!A || !dH || (dA && !W) || (act == NTP_ACT_RELU && !H))) { set_error("NULL buffer"); return NTP_EINVAL; }
     if (act != NTP_ACT_NONE && act != NTP_ACT_RELU) { set_error("unknown activation %d", act); return NTP_EINVAL; }
     if (dtype != NTP_F32 && dtype != NTP_BF16) { set_error("unknown dtype %d", dtype); return NTP_EINVAL; }
-    if (dW && (workspace_bytes < nn_bwd_workspace_bytes(n, k, m) || (!workspace && nn_bwd_workspace_bytes(n, k, m) > 0))) {
+    if (dW && (workspace_bytes < nn_bwd_workspace_bytes(n, k, m, false) || (!workspace && nn_bwd_workspace_bytes(n, k, m, false) > 0))) {
         set_error("workspace too small: need %lld bytes", (long long)nn_bwd_workspace_bytes(n, k, m));
         return NTP_EINVAL;
     }

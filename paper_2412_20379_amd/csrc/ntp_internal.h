@@ -354,7 +354,7 @@ int launch_nn_fwd(const void* A, const void* W, void* H, int64_t n, int64_t k, i
 int launch_nn_bwd(const void* A, const void* W, const void* H, const void* dH, void* dA, float* dW,
                   int64_t n, int64_t k, int64_t m, int act, int dtype,
                   void* workspace, int64_t workspace_bytes, void* stream);
-int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m);
+int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m, bool shared = true);     // shared: with room for dw_shared_kernel, which is otherwise not taken
 // C = act(A' B) with B resident in LDS (nn_strip_kernels.hip)
 int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int64_t n, int64_t K, int64_t N, int64_t lda,
                     int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, bool fp32_core, void* stream);
@@ -364,9 +364,9 @@ int launch_nn_resident(const float* A, const float* mask, const float* B, float*
                        bool b_kcontig, bool relu, bool nt, void* stream);
 // dW = A^T dZ straight from memory (nn_dw_kernels.hip)
 bool nn_dw_fp32_only(int64_t k);
-int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core, bool f32);
+int nn_dw_splits(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared);
 int launch_nn_dw(const void* A, const void* dH, const void* mask, float* out, int64_t n, int64_t k, int64_t m, int dtype,
-                 bool fp32_core, void* stream);
+                 bool fp32_core, bool shared, void* stream);
 int launch_relu(const void* dH, const void* H, void* out, int64_t n, int64_t f, int64_t ld, int dtype,
                 bool backward, void* stream);
 

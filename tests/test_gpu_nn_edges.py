@@ -228,3 +228,17 @@ def test_wide_weight_gradients(n, k, m, act):
             roundings = 48 + n / 128 / 32 + 64
             assert bool(((got - want).abs() <= (2.0 ** -21 + roundings * 2.0 ** -24) * (A64.abs().T @ Z64.abs())).all())
         assert float(dW[k * m]) == 7.0
+
+
+def test_wide_weight_gradients_in_half_the_workspace():
+    """the shared kernel's twice as many ranges are an offer: half of the workspace that is asked for goes on being enough, a quarter not"""
+    import torch
+    n, k, m = 131072, 256, 256
+    gen_ = torch.Generator(device="cuda:0").manual_seed(3)
+    A, dH = (torch.randint(-8, 9, (n, 256), generator=gen_, device="cuda:0").float() for _ in range(2))
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws, dW = torch.empty(wsb // 2, dtype=torch.uint8, device="cuda:0"), torch.empty(k, m, device="cuda:0")
+    ntp.ntp_nn_bwd(A, None, None, dH, None, dW, n, k, m, ntp.NTP_ACT_NONE, ntp.NTP_F32, ws, wsb // 2, torch.cuda.current_stream())
+    assert torch.equal(dW.double(), A.double().T @ dH.double())
+    with pytest.raises(Exception, match="workspace too small"):
+        ntp.ntp_nn_bwd(A, None, None, dH, None, dW, n, k, m, ntp.NTP_ACT_NONE, ntp.NTP_F32, ws, wsb // 4)
