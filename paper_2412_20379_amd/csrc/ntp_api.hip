@@ -356,7 +356,8 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
         // more than 32 entries get it only in launches large enough, in bf16 (whose reduction has twice the values; 28.8 M
         // entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us if they are,
         // hence the rule) and where the columns take four passes and more, each with a reduction (2.5 M entries, F = 256 193 ->
-        // 185 us, F = 128 99 -> 94).  A narrower fp32 slice, whose rows are summed by wavefronts, would gain 3 % at best.
+        // 185 us, F = 128 99 -> 94; MODE_GROUP_LONG_ROW keeps the sums as exact as a wavefront's).  A narrower fp32 slice, whose rows are
+        // summed by wavefronts, would gain 3 % at best.
         const bool per_group = R > 1 && (len <= 32 || (!scatter && len <= 128 && ((dtype == NTP_BF16 && (double)len * R <= 2 * quantum) ||
                                                                                   (passes >= 4 && len <= 3.5 * quantum))));
         const int at_once = per_group ? R : 1;
@@ -369,7 +370,7 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
             K = std::max(K, per_group && 2 * len <= 4 * L ? std::min(2, L) : 1);
         }
         while (per_group && 2 * S <= std::min(K, L) && 2 * S * len <= 4 * L) S *= 2;
-        add_group(per_group ? MODE_GROUP_PER_ROW : MODE_WAVE_PER_ROW, c.bin_row_off[b], cnt, (items + K - 1) / K, K, S);
+        add_group(!per_group ? MODE_WAVE_PER_ROW : len > 32 && dtype == NTP_F32 ? MODE_GROUP_LONG_ROW : MODE_GROUP_PER_ROW, c.bin_row_off[b], cnt, (items + K - 1) / K, K, S);
         AggGroup& g = a.group[ng - 1];
         if (slices && b < SLICE_BINS && per_group) {
             g.mode = MODE_SLICE;

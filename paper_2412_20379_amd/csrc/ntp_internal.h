@@ -225,7 +225,8 @@ struct AggArgs {
     const float* packed_val;
     int64_t packed_end;
 };
-enum { MODE_GROUP_PER_ROW = 0, MODE_WAVE_PER_ROW = 1, MODE_SEGMENT = 2, MODE_BLOCK_PER_ROW = 3, MODE_SLICE = 4 };      // MODE_SLICE: lane groups, from slices
+enum { MODE_GROUP_PER_ROW = 0, MODE_WAVE_PER_ROW = 1, MODE_SEGMENT = 2, MODE_BLOCK_PER_ROW = 3, MODE_SLICE = 4,      // MODE_SLICE: lane groups, from slices
+       MODE_GROUP_LONG_ROW = 5 };      // lane groups, sums in parts
 
 struct ReduceArgs {
     const ReduceItem* items;

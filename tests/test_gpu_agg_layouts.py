@@ -84,6 +84,35 @@ def test_slices_give_the_bits_of_the_forms_own_arrays(slice_graphs, name, f, ld,
                      TOL_BF16 if dtype == "bf16" else TOL_F32, "slices")
 
 
+@pytest.mark.parametrize("f", [128, 256])
+@pytest.mark.parametrize("positive", [False, True])
+def test_a_wide_slice_is_summed_as_exactly_as_a_narrow_one(slice_graphs, f, positive):
+    """Rows of 33 to 128 entries: at 64 columns a wavefront's lane groups take a part of the row each, at 128 and more (four passes, in a
+    graph as large as this one) a lane group takes the row.  Chains of 8 with a total in 64 bits round less often than chains of an
+    eighth of 33 entries and a tree of three levels (error variance for signed terms, in units of a term's: 33 entries 178 / 184, 128
+    entries 704 / 1472), so the wide call's error against 64 bits is not the larger one"""
+    import torch
+    from gpu_util import dev_f32
+    g, og = slice_graphs["large"]
+    say("exactness", f, positive)
+    n = og.n
+    x = gen.normal_features(n, 64, seed=f)
+    x = np.abs(x) if positive else x
+    for direction, m in ((ntp.NTP_FWD, og.csr), (ntp.NTP_BWD, og.csc)):
+        ref, _ = oracle.aggregate(m, x, with_abs=True)
+        lens = np.diff(m.rowptr)
+        of = [(lens > lo) & (lens <= hi) for lo, hi in ((32, 48), (48, 64), (64, 96), (96, 128))]
+        error = []
+        for width in (64, f):
+            X = dev_f32(np.tile(x, (1, width // 64)))
+            Y = torch.empty_like(X)
+            (ntp.ntp_aggregate_fwd if direction == ntp.NTP_FWD else ntp.ntp_aggregate_bwd)(g, X, Y, width, width, width, ntp.NTP_F32)
+            d = Y[:, width - 64:].cpu().numpy().astype(np.float64) - ref
+            error.append([np.sqrt(np.mean(d[rows] ** 2)) for rows in of if rows.any()])
+        say("narrow", error[0], "wide", error[1])
+        assert np.all(np.array(error[1]) <= np.array(error[0]))
+
+
 @pytest.mark.parametrize("name,f,ld,dtype", [("short", 128, 128, "f32"), ("short", 121, 124, "f32"), ("large", 1000, 1000, "f32"), ("short", 250, 256, "bf16")])
 def test_a_mask_beside_rows_beyond_the_caches(slice_graphs, name, f, ld, dtype):
     """X and the mask above 256 MB together (the mask is read past the caches): the unmasked result where the mask is above zero"""
