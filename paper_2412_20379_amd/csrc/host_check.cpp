@@ -1,4 +1,4 @@
-// Stand-alone driver for the host side of libntp (graph_build.cpp, plan.cpp, chunk_schedule.h): builds
+// Stand-alone driver for the host side of libntp (graph_build.cpp, plan.cpp, chunk_schedule.h, row_copies.h): builds
 // graphs for every combination of the build flags, plans them with several chunk sizes and checks
 // the structural invariants of the result; runs the streaming schedule on recorded streams, with
 // failures at every step, and checks the order of every access to the staging buffers.  It links no device code, so it can be compiled
@@ -8,10 +8,12 @@
 #include <cinttypes>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "chunk_schedule.h"
 #include "ntp_internal.h"
+#include "row_copies.h"
 
 using namespace ntp;
 
@@ -114,6 +116,95 @@ void check_plan(const HostSparse& m, const Plan& P, int64_t chunk_edges, const c
     CHECK(slots == P.n_slots, "%s: %" PRId64 " slots, plan says %" PRId64, what, slots, P.n_slots);
     for (int64_t v = 0; v < n; ++v)
         CHECK(covered[v] == m.rowptr[v + 1] - m.rowptr[v], "%s: row %" PRId64 " covered %" PRId64 " of %" PRId64, what, v, covered[v], m.rowptr[v + 1] - m.rowptr[v]);
+}
+
+// The second copies of a chunk in host memory, with a call that fails.
+struct HostCopies {
+    const HostSparse& m;
+    int fail_at;                   // this call (0: none) fails
+    int calls = 0, alive = 0;
+    bool fails() { return ++calls == fail_at; }
+    char* alloc(size_t bytes) {
+        if (fails()) return nullptr;
+        ++alive;
+        return (char*)malloc(bytes);
+    }
+    void release(char* p) { --alive; free(p); }
+    int upload(char* p, const void* src, size_t bytes) {
+        if (fails()) return NTP_EHIP;
+        memcpy(p, src, bytes);
+        return NTP_OK;
+    }
+    const int32_t* rows(const Chunk& c) const { return reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows); }
+    int fill_slices(const Chunk& c, const RowCopies& l, char* p, int b) {
+        if (fails()) return NTP_EHIP;
+        const int32_t* base = reinterpret_cast<const int32_t*>(p + l.off_slice_base) + l.slice_off[b];
+        int32_t* col = reinterpret_cast<int32_t*>(p);
+        float* val = reinterpret_cast<float*>(p + l.off_slice_val);
+        for (int64_t i = 0; i < (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS * SLICE_ROWS; ++i) {
+            const int32_t v = i < c.bin_count[b] ? rows(c)[c.bin_row_off[b] + i] : -1;
+            const int64_t e = v < 0 ? 0 : m.rowptr[v], d = v < 0 ? 0 : m.rowptr[v + 1] - e;
+            const int64_t s = i / SLICE_ROWS;
+            CHECK((base[s + 1] - base[s]) * 4 >= d, "slice of %d chunks for a row of %" PRId64, base[s + 1] - base[s], d);
+            CHECK(base[s + 1] - base[s] <= slice_chunks(b), "slice of %d chunks in bin %d", base[s + 1] - base[s], b);
+            for (int64_t k = 0; k < (base[s + 1] - base[s]) * 4; ++k) {
+                const int64_t at = ((base[s] + k / 4) * SLICE_ROWS + i % SLICE_ROWS) * 4 + k % 4;
+                col[at] = k < d ? m.colidx[e + k] : -1;
+                val[at] = k < d ? m.val[e + k] : 0.f;
+            }
+        }
+        return NTP_OK;
+    }
+    int fill_packed(const Chunk& c, const RowCopies& l, char* p) {
+        if (fails()) return NTP_EHIP;
+        const PackedRow* r = reinterpret_cast<const PackedRow*>(p + l.off_packed_rows);
+        for (int64_t i = 0; i < l.packed_rows; ++i) {
+            CHECK(r[i].row == rows(c)[c.bin_row_off[SLICE_BINS] + i] && r[i].len == m.rowptr[r[i].row + 1] - m.rowptr[r[i].row], "packed row %" PRId64, i);
+            CHECK(r[i].e_begin % 4 == 0 && r[i].e_begin + r[i].len <= l.n_packed, "packed entries of row %" PRId64, i);
+            memcpy(p + l.off_packed_colidx + r[i].e_begin * 4, m.colidx + m.rowptr[r[i].row], (size_t)r[i].len * 4);
+            memcpy(p + l.off_packed_val + r[i].e_begin * 4, m.val + m.rowptr[r[i].row], (size_t)r[i].len * 4);
+        }
+        return NTP_OK;
+    }
+};
+
+// they hold every entry of the rows they are made for; no memory for them is no error, and nothing stays behind a failure
+void check_row_copies() {
+    const int64_t n = 4099;
+    std::vector<int32_t> src, dst;
+    Lcg rng{7};
+    for (int32_t v = 0; v < n; ++v)
+        for (uint32_t d = v < 64 ? 0 : v < 900 ? 1 : rng.next() % 150; d > 0; --d) { src.push_back((int32_t)(rng.next() % n)); dst.push_back(v); }
+    BuiltGraph G;
+    EntryAllocator alloc{alloc_plain, nullptr, alloc_plain};
+    if (build_host_graph(n, (int64_t)src.size(), src.data(), dst.data(), nullptr, 0, alloc, &G) != NTP_OK) { CHECK(false, "copies: %s", last_error()); return; }
+    for (int64_t ce : {(int64_t)0, (int64_t)50000})
+        for (int fail_at = 0; fail_at <= 9; ++fail_at) {       // alloc, upload, a fill for each bin, packed rows
+            Plan P;
+            make_plan(G.csr, ce, &P);
+            for (Chunk& c : P.chunks) {
+                HostCopies ops{G.csr, fail_at};
+                const int rc = make_row_copies(ops, G.csr, c);
+                CHECK(rc == (fail_at >= 2 ? NTP_EHIP : NTP_OK), "copies: status %d with call %d failing", rc, fail_at);
+                CHECK((c.d_copies != nullptr) == (fail_at == 0) && ops.alive == (fail_at == 0), "copies: %d kept with call %d failing", ops.alive, fail_at);
+                CHECK(fail_at == 0 || (!c.copies.slices && c.copies.packed_rows == 0), "copies: a layout without memory");
+                if (!c.d_copies) continue;
+                const RowCopies& l = c.copies;
+                int64_t held = 0, rows = 0;
+                for (int b = 0; b < SLICE_BINS; ++b) rows += c.bin_count[b];
+                const int32_t* col = reinterpret_cast<const int32_t*>(c.d_copies);
+                for (size_t k = 0; k < l.off_slice_val / 4; ++k) held += col[k] >= 0;
+                for (int b = 0; b < SLICE_BINS; ++b)
+                    for (int32_t i = 0; i < c.bin_count[b]; ++i) {
+                        const int32_t v = reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows)[c.bin_row_off[b] + i];
+                        held -= G.csr.rowptr[v + 1] - G.csr.rowptr[v];
+                    }
+                CHECK(l.slices && rows > 0 && held == 0, "copies: slices hold %" PRId64 " entries too many", held);
+                CHECK(l.packed_rows == c.bin_count[6] + c.bin_count[7], "copies: %" PRId64 " packed rows", l.packed_rows);
+                ops.release(c.d_copies);
+            }
+        }
+    free_graph(G);
 }
 
 // hub columns: the most gathered ones, most first, none below the bound; the encoded ids decode back
@@ -387,6 +478,8 @@ int main() {
     }
     // 5. the order of a streamed pass
     check_schedule();
+    // 6. the second copies of short rows
+    check_row_copies();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");
     return 0;

@@ -12,6 +12,7 @@
 
 #include "chunk_schedule.h"
 #include "ntp_internal.h"
+#include "row_copies.h"
 
 using namespace ntp;
 
@@ -141,87 +142,35 @@ int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
     return NTP_OK;
 }
 
-// The slices of a resident chunk, made on the device from its image.  In the form's own arrays a short row's pairs are a part of a
-// line of each, whose other rows are other wavefronts' (other bins, other XCDs), so every column pass fetched a line many times;
-// a wavefront's slices are whole lines of its own, and their address follows from the place in the list (no row pointers).  One
-// call: 2.5 M entries F = 256 215 -> 194 us, F = 40 60 -> 55, directed 26 M entries F = 13 312 -> 286, 63 M F = 32 686 -> 658.  (A form
-// of up to half a million entries is in the L2s whole: no copies.)
-int make_slices(ntp_graph* G, const HostSparse& m, Chunk& c) {
-    const int32_t* rows = reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows);
-    std::vector<int32_t> base;                 // one more per bin than it has slices: a slice's end is the next one's beginning
-    int32_t n_base = 0;
-    for (int b = 0; b < SLICE_BINS; ++b) {
-        c.slice_off[b] = n_base;
-        n_base += (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS + 1;
+// What make_row_copies does on the device
+struct HipCopies {
+    ntp_graph* G;
+    char* alloc(size_t bytes) {
+        void* p = nullptr;
+        if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+        G->device_bytes += (int64_t)bytes;
+        taken = bytes;
+        return (char*)p;
     }
-    base.resize((size_t)n_base);               // chunks of each slice (0 between the bins), then their sums
-    parallel_for_threads(std::max(1, std::min(host_threads(), n_base / 4096)), [&](int t, int nt) {
-        for (int b = 0; b < SLICE_BINS; ++b) {
-            const int32_t* r = rows + c.bin_row_off[b];
-            const int64_t slices = (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS;
-            for (int64_t s = slices * t / nt; s < slices * (t + 1) / nt; ++s) {
-                int64_t most = 0;
-                for (int64_t j = s * SLICE_ROWS; j < std::min<int64_t>((s + 1) * SLICE_ROWS, c.bin_count[b]); ++j)
-                    most = std::max(most, m.rowptr[(size_t)r[j] + 1] - m.rowptr[(size_t)r[j]]);
-                base[(size_t)(c.slice_off[b] + s)] = (int32_t)((most + 3) / 4);
-            }
-        }
-    });
-    int64_t chunks = 0;
-    for (int32_t& x : base) {
-        const int32_t here = x;
-        x = (int32_t)chunks;
-        chunks += here;
+    void release(char* p) {
+        (void)hipFree(p);
+        G->device_bytes -= (int64_t)taken;
     }
-    if (chunks == 0 || chunks > INT_MAX) return NTP_OK;          // (no entries, or a chunk of 2^36 of them)
-    c.off_slice_val = (size_t)chunks * (4 * SLICE_ROWS) * 4;
-    c.off_slice_base = 2 * c.off_slice_val;
-    const size_t bytes = c.off_slice_base + base.size() * 4;
-    void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of %zu bytes for the slices of short rows failed", bytes); return NTP_ENOMEM; }
-    c.d_slices = (char*)p;
-    G->device_bytes += (int64_t)bytes;
-    HIP_TRY(hipMemcpy(c.d_slices + c.off_slice_base, base.data(), base.size() * 4, hipMemcpyHostToDevice));
-    for (int b = 0; b < SLICE_BINS; ++b) {
-        const int rc = launch_fill_slices(reinterpret_cast<const int32_t*>(c.d_image + c.off_rows) + c.bin_row_off[b], c.bin_count[b],
-                                          reinterpret_cast<const int32_t*>(c.d_slices + c.off_slice_base) + c.slice_off[b],
-                                          reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin,
-                                          reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin,
-                                          reinterpret_cast<const float*>(c.d_image + c.img_off_val) - c.e_begin, reinterpret_cast<int32_t*>(c.d_slices),
-                                          reinterpret_cast<float*>(c.d_slices + c.off_slice_val), nullptr);
-        if (rc != NTP_OK) return rc;
+    int upload(char* p, const void* src, size_t bytes) { HIP_TRY(hipMemcpy(p, src, bytes, hipMemcpyHostToDevice)); return NTP_OK; }
+    int fill_slices(const Chunk& c, const RowCopies& l, char* p, int b) {
+        return launch_fill_slices(reinterpret_cast<const int32_t*>(c.d_image + c.off_rows) + c.bin_row_off[b], c.bin_count[b],
+                                  reinterpret_cast<const int32_t*>(p + l.off_slice_base) + l.slice_off[b], rowptr(c), colidx(c), val(c),
+                                  reinterpret_cast<int32_t*>(p), reinterpret_cast<float*>(p + l.off_slice_val), nullptr);
     }
-    return NTP_OK;
-}
-
-// The packed rows, likewise, where the form is at most half of the Infinity Cache: 12 M entries (98 MB), rows of about 41, F = 32 222 ->
-// 209 us, 7.2 M 215 -> 211; beyond, the copy displaces more than it saves (28.8 M, 230 MB: 478 -> 489 us) or makes 0 to 1 %.
-int make_packed(ntp_graph* G, const HostSparse& m, Chunk& c) {
-    if (m.nnz * 8 > (128ll << 20)) return NTP_OK;
-    const int32_t* rows = reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows);
-    std::vector<PackedRow> packed;
-    for (int b = SLICE_BINS; b < PACKED_BINS; ++b)
-        for (int32_t i = 0; i < c.bin_count[b]; ++i) {
-            const int32_t r = rows[c.bin_row_off[b] + i];
-            const int32_t len = (int32_t)(m.rowptr[(size_t)r + 1] - m.rowptr[(size_t)r]);
-            packed.push_back(PackedRow{c.n_packed, len, r});
-            c.n_packed += (len + 3) / 4 * 4;
-        }
-    if (packed.empty()) return NTP_OK;
-    c.off_packed_colidx = packed.size() * sizeof(PackedRow);
-    c.off_packed_val = c.off_packed_colidx + (size_t)c.n_packed * 4;
-    const size_t bytes = c.off_packed_val + (size_t)c.n_packed * 4;
-    void* p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of %zu bytes for packed rows failed", bytes); return NTP_ENOMEM; }
-    c.d_packed = (char*)p;
-    G->device_bytes += (int64_t)bytes;
-    HIP_TRY(hipMemcpy(c.d_packed, packed.data(), c.off_packed_colidx, hipMemcpyHostToDevice));
-    return launch_fill_packed(reinterpret_cast<const PackedRow*>(c.d_packed), (int64_t)packed.size(),
-                              reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin,
-                              reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin,
-                              reinterpret_cast<const float*>(c.d_image + c.img_off_val) - c.e_begin,
-                              reinterpret_cast<int32_t*>(c.d_packed + c.off_packed_colidx), reinterpret_cast<float*>(c.d_packed + c.off_packed_val), nullptr);
-}
+    int fill_packed(const Chunk& c, const RowCopies& l, char* p) {
+        return launch_fill_packed(reinterpret_cast<const PackedRow*>(p + l.off_packed_rows), l.packed_rows, rowptr(c), colidx(c), val(c),
+                                  reinterpret_cast<int32_t*>(p + l.off_packed_colidx), reinterpret_cast<float*>(p + l.off_packed_val), nullptr);
+    }
+    size_t taken = 0;
+    static const int64_t* rowptr(const Chunk& c) { return reinterpret_cast<const int64_t*>(c.d_image + c.off_rowptr) - c.row_begin; }
+    static const int32_t* colidx(const Chunk& c) { return reinterpret_cast<const int32_t*>(c.d_image + c.img_off_colidx) - c.e_begin; }
+    static const float* val(const Chunk& c) { return reinterpret_cast<const float*>(c.d_image + c.img_off_val) - c.e_begin; }
+};
 
 int64_t streamed_bytes(const Chunk& c, bool with_val) {
     return (int64_t)c.meta.size() + (c.h_packed_ids ? c.packed_id_bytes : (c.e_end - c.e_begin) * (with_val ? 8 : 4));
@@ -343,8 +292,9 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     const double quantum = (double)(c.e_end - c.e_begin) * passes / (16.0 * 8192.0);
     const bool block_rows = !scatter && !hub && c.block_rows;      // split rows summed by one block each (see make_plan)
     a.split_rows = reinterpret_cast<const ReduceItem*>(img + c.off_reduce);
-    const bool own_copies = !scatter && !hub && !weights && img == c.d_image;
-    const bool slices = own_copies && c.d_slices, packed = own_copies && c.d_packed;
+    const bool own_copies = c.d_copies && !scatter && !hub && !weights;
+    const RowCopies& copies = c.copies;
+    const bool slices = own_copies && copies.slices, packed = own_copies && copies.packed_rows > 0;
     // heaviest work first: split rows, then bins from long rows to short rows
     if (block_rows) add_group(MODE_BLOCK_PER_ROW, 0, c.n_reduce, 4 * (int64_t)c.n_reduce);   // first: block-aligned
     else if (c.n_segs > 0) add_group(MODE_SEGMENT, 0, c.n_segs, c.n_segs);
@@ -374,7 +324,7 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
         AggGroup& g = a.group[ng - 1];
         if (slices && b < SLICE_BINS && per_group) {
             g.mode = MODE_SLICE;
-            g.slice_off = c.slice_off[b];
+            g.slice_off = copies.slice_off[b];
             g.slice_chunks = slice_chunks(b);
         } else if (packed && b >= SLICE_BINS && b < PACKED_BINS) {
             g.packed = 1;
@@ -384,13 +334,13 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     if (waves > INT_MAX - 8) { set_error("chunk too large for one launch (%lld wavefronts)", (long long)waves); return NTP_EUNSUPPORTED; }
     a.n_waves = (int32_t)waves;
     for (int g = ng; g < NGROUPS; ++g) a.wave_start[g] = INT_MAX;
-    a.slice_colidx = reinterpret_cast<const int32_t*>(c.d_slices);
-    a.slice_val = reinterpret_cast<const float*>(c.d_slices + c.off_slice_val);
-    a.slice_base = reinterpret_cast<const int32_t*>(c.d_slices + c.off_slice_base);
-    a.packed_rows = reinterpret_cast<const PackedRow*>(c.d_packed);
-    a.packed_colidx = reinterpret_cast<const int32_t*>(c.d_packed + c.off_packed_colidx);
-    a.packed_val = reinterpret_cast<const float*>(c.d_packed + c.off_packed_val);
-    a.packed_end = c.n_packed;
+    a.slice_colidx = reinterpret_cast<const int32_t*>(c.d_copies);
+    a.slice_val = reinterpret_cast<const float*>(c.d_copies + copies.off_slice_val);
+    a.slice_base = reinterpret_cast<const int32_t*>(c.d_copies + copies.off_slice_base);
+    a.packed_rows = reinterpret_cast<const PackedRow*>(c.d_copies + copies.off_packed_rows);
+    a.packed_colidx = reinterpret_cast<const int32_t*>(c.d_copies + copies.off_packed_colidx);
+    a.packed_val = reinterpret_cast<const float*>(c.d_copies + copies.off_packed_val);
+    a.packed_end = copies.n_packed;
     if (ng > 0) {
         const int rc = scatter ? launch_scatter(a, st) : launch_aggregate(a, dtype, st);
         if (rc != NTP_OK) return rc;
@@ -491,9 +441,7 @@ void destroy(ntp_graph* G) {
         for (auto& c : G->form[k].plan.chunks)
             if (c.d_image) (void)hipFree(c.d_image);
         for (auto& c : G->form[k].plan.chunks)
-            if (c.d_slices) (void)hipFree(c.d_slices);
-        for (auto& c : G->form[k].plan.chunks)
-            if (c.d_packed) (void)hipFree(c.d_packed);
+            if (c.d_copies) (void)hipFree(c.d_copies);
         for (auto& c : G->form[k].plan.chunks)
             if (c.d_colidx_hub) (void)hipFree(c.d_colidx_hub);
         if (G->form[k].d_hub_cols) (void)hipFree(G->form[k].d_hub_cols);
@@ -776,14 +724,6 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                 }
             }
         }
-        if (fits && budget == 0)
-            for (int k = 0; k < n_forms; ++k)
-                for (auto& c : G->form[k].plan.chunks) {
-                    if (G->form[k].m->nnz * 8 <= (4ll << 20)) continue;
-                    rc = make_slices(G, *G->form[k].m, c);
-                    if (rc == NTP_OK) rc = make_packed(G, *G->form[k].m, c);
-                    if (rc != NTP_OK) return rc;
-                }
         bool any_streamed = false;
         for (int k = 0; k < n_forms; ++k) any_streamed = any_streamed || !G->form[k].all_resident;
         if (any_streamed && G->g.val_mode == VAL_GCN && n > 0) {
@@ -808,8 +748,6 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
             G->device_bytes += (int64_t)bytes;
             if (hipMemcpy(G->d_perm, G->h_perm.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) { (void)hipGetLastError(); set_error("upload of the edge permutation failed"); return NTP_EHIP; }
         }
-        const hipError_t se = hipDeviceSynchronize();
-        if (se != hipSuccess) { set_error("hipDeviceSynchronize failed: %s", hipGetErrorString(se)); return NTP_EHIP; }
         // partial sums of split rows: allocated here for slices of up to 256 columns, so that only a
         // call with a wider slice ever allocates (and synchronises) inside an aggregation
         for (int k = 0; k < n_forms; ++k)
@@ -820,6 +758,18 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
         float* unused = nullptr;            // resolve the static scratch of this device at set-up
         rc = static_scratch(&unused);
         if (rc != NTP_OK) return rc;
+        // Second copies last: they take nothing that the graph needs.  (A form of up to half a million entries is in the L2s whole: none.)
+        if (fits && budget == 0) {
+            HipCopies ops{G};
+            for (int k = 0; k < n_forms; ++k)
+                for (auto& c : G->form[k].plan.chunks) {
+                    if (G->form[k].m->nnz * 8 <= (4ll << 20)) continue;
+                    rc = make_row_copies(ops, *G->form[k].m, c);
+                    if (rc != NTP_OK) return rc;
+                }
+        }
+        const hipError_t se = hipDeviceSynchronize();
+        if (se != hipSuccess) { set_error("hipDeviceSynchronize failed: %s", hipGetErrorString(se)); return NTP_EHIP; }
     }
     *out = guard.release();
     return NTP_OK;

@@ -101,6 +101,15 @@ struct PackedRow {      // (device-visible, 16 bytes)
     int32_t len;
     int32_t row;
 };
+struct RowCopies {      // layout in device memory: column ids and weights of the slices, of the packed rows, lists (PackedRow[], base[])
+    bool slices = false;
+    size_t off_slice_val = 0, off_slice_base = 0;
+    int32_t slice_off[SLICE_BINS] = {0};       // first slice of each bin in base[], the first chunk of each slice
+    int64_t packed_rows = 0, n_packed = 0;     // packed rows (0: none) and their entries
+    size_t off_packed_colidx = 0, off_packed_val = 0, off_packed_rows = 0;
+    size_t off_lists = 0;
+    size_t bytes = 0;                          // 0: there is nothing to copy
+};
 
 struct Segment {        // one piece of a split row (device-visible, 24 bytes)
     int64_t e_begin;    // first entry (global offset into colidx/val)
@@ -138,12 +147,8 @@ struct Chunk {
     // residency
     int32_t* d_colidx_hub = nullptr;           // resident chunks of a form with a hub table: hub-encoded column ids
     char* d_image = nullptr;                   // device image if resident
-    char* d_slices = nullptr;                  // slices of a resident chunk: column ids, weights, first chunk of each slice
-    size_t off_slice_val = 0, off_slice_base = 0;
-    int32_t slice_off[SLICE_BINS] = {0};       // first slice of each bin
-    char* d_packed = nullptr;                  // packed rows of a resident chunk: rows, column ids, weights
-    size_t off_packed_colidx = 0, off_packed_val = 0;
-    int64_t n_packed = 0;                      // packed entries
+    char* d_copies = nullptr;                  // second copies of a resident chunk (nullptr: none)
+    RowCopies copies;
     char* h_meta_pinned = nullptr;             // pinned copy of meta for streaming
     char* h_packed_ids = nullptr;              // pinned: the column ids in as few bits as hold a vertex id (nullptr: they travel as
     int64_t packed_id_bytes = 0;               // they are); goes where the weights are rebuilt afterwards, unpacked from there
@@ -168,6 +173,9 @@ struct Plan {
 
 // Build the plan of one compressed form.  chunk_edges <= 0: a single chunk.
 void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan);
+
+// The second copies of a chunk and the lists that go with them (host copy)
+void plan_row_copies(const HostSparse& m, const Chunk& c, RowCopies* layout, std::vector<char>* lists);
 
 // The hub columns of a form: the up to max_slots columns with most entries, most first (ties by
 // id), among those with at least min_count entries.  transposed (nullable): the other compressed

@@ -23,6 +23,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // SORT_WINDOW rows: lane groups that share a wavefront get rows of one length (mostly), and rows that are near in memory
 // stay near in the list (windows of 512 rows cost 2-5 % on short rows: fewer rows share a line of the row pointers).
 constexpr int SORT_WINDOW = 64;
+static_assert(SORT_WINDOW % SLICE_ROWS == 0, "a slice's rows lie in one window");
 void sort_by_length(int32_t* rows, int64_t n, const int64_t* rp, int below) {
     int32_t tmp[SORT_WINDOW];
     for (int64_t w = 0; w < n; w += SORT_WINDOW) {
@@ -124,6 +125,65 @@ void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed) {
             have = std::max(0, have - 32);
         }
     });
+}
+
+// In the form's own arrays a short row's pairs are a part of a line of each, whose other rows are other wavefronts' (other bins, other
+// XCDs), so every column pass fetched a line many times; a wavefront's slices are whole lines of its own, and their address follows
+// from the place in the list (no row pointers).  One call: 2.5 M entries F = 256 215 -> 194 us, F = 40 60 -> 55, directed 26 M
+// entries F = 13 312 -> 286, 63 M F = 32 686 -> 658.
+// Packed rows, where the form is at most half of the Infinity Cache: 12 M entries (98 MB), rows of about 41, F = 32 222 ->
+// 209 us, 7.2 M 215 -> 211; beyond, the copy displaces more than it saves (28.8 M, 230 MB: 478 -> 489 us) or makes 0 to 1 %.
+void plan_row_copies(const HostSparse& m, const Chunk& c, RowCopies* layout, std::vector<char>* lists) {
+    RowCopies& L = *layout;
+    L = RowCopies();
+    lists->clear();
+    const int32_t* rows = reinterpret_cast<const int32_t*>(c.meta.data() + c.off_rows);
+    const int64_t* rp = m.rowptr.data();
+    int64_t n_base = 0, n_packed_rows = 0;
+    for (int b = 0; b < SLICE_BINS; ++b) {                     // one more per bin than it has slices: a slice's end is the next one's beginning
+        L.slice_off[b] = (int32_t)n_base;
+        n_base += (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS + 1;
+    }
+    if (m.nnz * 8 <= (128ll << 20))
+        for (int b = SLICE_BINS; b < PACKED_BINS; ++b) n_packed_rows += c.bin_count[b];
+    const size_t packed_bytes = (size_t)n_packed_rows * sizeof(PackedRow);
+    lists->resize(packed_bytes + (size_t)n_base * 4);
+    PackedRow* packed = reinterpret_cast<PackedRow*>(lists->data());
+    int32_t* base = reinterpret_cast<int32_t*>(lists->data() + packed_bytes);      // chunks of each slice (0 between the bins), then their sums
+    parallel_for_threads(std::max(1, (int)std::min<int64_t>(host_threads(), n_base / 65536)), [&](int t, int nt) {
+        for (int b = 0; b < SLICE_BINS; ++b) {
+            const int32_t* r = rows + c.bin_row_off[b];
+            const int64_t slices = (c.bin_count[b] + SLICE_ROWS - 1) / SLICE_ROWS;
+            for (int64_t s = slices * t / nt; s < slices * (t + 1) / nt; ++s) {
+                int64_t most = 0;                              // (its first row's, but for rows of no or one entry: sort_by_length)
+                const int64_t end = std::min<int64_t>(s * SLICE_ROWS + (b == 0 ? SLICE_ROWS : 1), c.bin_count[b]);
+                for (int64_t j = s * SLICE_ROWS; j < end; ++j) most = std::max(most, rp[(size_t)r[j] + 1] - rp[(size_t)r[j]]);
+                base[L.slice_off[b] + s] = (int32_t)((most + 3) / 4);
+            }
+        }
+    });
+    int64_t chunks = 0;
+    for (int64_t i = 0; i < n_base; ++i) {
+        const int32_t here = base[i];
+        base[i] = (int32_t)chunks;
+        chunks += here;
+        if (chunks > INT_MAX) return;                          // (a chunk of 2^36 entries)
+    }
+    for (int64_t i = 0; i < n_packed_rows; ++i) {
+        const int32_t r = rows[c.bin_row_off[SLICE_BINS] + i];
+        const int32_t len = (int32_t)(rp[(size_t)r + 1] - rp[(size_t)r]);
+        packed[i] = PackedRow{L.n_packed, len, r};
+        L.n_packed += (len + 3) / 4 * 4;
+    }
+    L.slices = chunks > 0;
+    L.packed_rows = n_packed_rows;
+    const size_t slice_bytes = (size_t)chunks * (4 * SLICE_ROWS) * 4;
+    L.off_slice_val = slice_bytes;
+    L.off_packed_colidx = 2 * slice_bytes;
+    L.off_packed_val = L.off_packed_colidx + (size_t)L.n_packed * 4;
+    L.off_lists = L.off_packed_rows = L.off_packed_val + (size_t)L.n_packed * 4;      // (all of them multiples of 16)
+    L.off_slice_base = L.off_lists + packed_bytes;
+    if (L.slices || L.packed_rows > 0) L.bytes = L.off_lists + lists->size();
 }
 
 void pick_hub_columns(const HostSparse& m, const HostSparse* transposed, int max_slots, int64_t min_count,
