@@ -106,6 +106,15 @@ typedef struct ntp_graph ntp_graph_t;
  * 0 = unlimited.  Chunks that fit stay resident from build time on; the others are
  * streamed from pinned host memory by ntp_chunked_aggregate.
  *
+ * Without a budget, a form of more than 524,288 entries is held a second time in part: the entries
+ * of rows of up to 32 in the order in which the aggregation reads them (32 bytes for every four
+ * entries of a row begun, times the longest of eight rows; at most 20 bytes an entry, else not at
+ * all), and, in forms of up to 16.8 M entries, those of rows of 33 to 128 (8 bytes an entry).  Such
+ * a handle takes about twice the device memory of its entries (2.5 M entries, 15 a row: 45 MB for 22).
+ * These copies are made last, take at most an eighth of the memory that is then free, and are left
+ * out where they do not fit; results are the same bits with and without them.  A budget keeps a
+ * handle without copies.
+ *
  * The input arrays are copied; *out is owned by the library until ntp_graph_free.
  * Errors: NTP_EINVAL (bad ids/sizes/flags), NTP_ENOMEM, NTP_EHIP, NTP_EBUDGET.
  */
@@ -145,7 +154,7 @@ int ntp_graph_chunks(const ntp_graph_t* g, int which, int32_t* n_chunks,
  * entries and more their column ids travel in as few bits each as hold a vertex id (up to 28). */
 int ntp_graph_stream_bytes(const ntp_graph_t* g, int which, int64_t* bytes);
 
-/* Device bytes held by the handle (resident topology, staging buffers, scratch). */
+/* Device bytes held by the handle (resident topology and its second copies, staging buffers, scratch). */
 int ntp_graph_device_bytes(const ntp_graph_t* g, int64_t* bytes);
 
 /*

@@ -205,6 +205,20 @@ void check_row_copies() {
             }
         }
     free_graph(G);
+    // rows of one entry: slices would take 32 bytes for 8, and are not made; of two entries (16 for 32) they are
+    for (int d : {1, 2}) {
+        HostSparse m;
+        m.n = 1000;
+        for (int64_t v = 0; v <= m.n; ++v) m.rowptr.push_back(v * d);
+        m.nnz = m.n * d;
+        Plan P;
+        make_plan(m, 0, &P);
+        RowCopies l;
+        std::vector<char> lists;
+        plan_row_copies(m, P.chunks[0], &l, &lists);
+        CHECK(l.slices == (d == 2) && (l.bytes > 0) == (d == 2), "copies: rows of %d entries, %zu bytes", d, l.bytes);
+        CHECK(l.off_lists <= (size_t)m.nnz * 20, "copies: %zu bytes for %" PRId64 " entries", l.off_lists, m.nnz);
+    }
 }
 
 // hub columns: the most gathered ones, most first, none below the bound; the encoded ids decode back

@@ -142,19 +142,28 @@ int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
     return NTP_OK;
 }
 
-// What make_row_copies does on the device
+// What make_row_copies does on the device.  A handle's copies take an eighth of what is free at most: the rest is for the caller's matrices.
 struct HipCopies {
     ntp_graph* G;
+    int64_t left = -1;         // bytes that may be taken yet (-1: not asked for)
     char* alloc(size_t bytes) {
         void* p = nullptr;
+        if (left < 0) {
+            size_t free_bytes = 0, all = 0;
+            if (hipMemGetInfo(&free_bytes, &all) != hipSuccess) { (void)hipGetLastError(); free_bytes = 0; }
+            left = (int64_t)(free_bytes / 8);
+        }
+        if ((int64_t)bytes > left) return nullptr;
         if (hipMalloc(&p, bytes) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
         G->device_bytes += (int64_t)bytes;
+        left -= (int64_t)bytes;
         taken = bytes;
         return (char*)p;
     }
     void release(char* p) {
         (void)hipFree(p);
         G->device_bytes -= (int64_t)taken;
+        left += (int64_t)taken;
     }
     int upload(char* p, const void* src, size_t bytes) { HIP_TRY(hipMemcpy(p, src, bytes, hipMemcpyHostToDevice)); return NTP_OK; }
     int fill_slices(const Chunk& c, const RowCopies& l, char* p, int b) {

@@ -131,6 +131,9 @@ void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed) {
 // XCDs), so every column pass fetched a line many times; a wavefront's slices are whole lines of its own, and their address follows
 // from the place in the list (no row pointers).  One call: 2.5 M entries F = 256 215 -> 194 us, F = 40 60 -> 55, directed 26 M
 // entries F = 13 312 -> 286, 63 M F = 32 686 -> 658.
+// A row begun takes 32 bytes per four entries of the longest row of its slice, so slices are 1.1 to 1.4 times the entries' 8 bytes each at
+// 4 to 16 entries a row, 2.1 times at 2 (1 M vertices F = 32 70 -> 63 us, F = 128 281 -> 253), and 4 times at rows of one entry, where they
+// gain little (49 -> 45) or, where such rows follow each other, lose (F = 4 22 -> 24, F = 64 88 -> 90): not above two and a half times.
 // Packed rows, where the form is at most half of the Infinity Cache: 12 M entries (98 MB), rows of about 41, F = 32 222 ->
 // 209 us, 7.2 M 215 -> 211; beyond, the copy displaces more than it saves (28.8 M, 230 MB: 478 -> 489 us) or makes 0 to 1 %.
 void plan_row_copies(const HostSparse& m, const Chunk& c, RowCopies* layout, std::vector<char>* lists) {
@@ -175,6 +178,7 @@ void plan_row_copies(const HostSparse& m, const Chunk& c, RowCopies* layout, std
         packed[i] = PackedRow{L.n_packed, len, r};
         L.n_packed += (len + 3) / 4 * 4;
     }
+    if (chunks * SLICE_ROWS * 32 * 2 > (c.e_end - c.e_begin) * 8 * 5) chunks = 0;
     L.slices = chunks > 0;
     L.packed_rows = n_packed_rows;
     const size_t slice_bytes = (size_t)chunks * (4 * SLICE_ROWS) * 4;
