@@ -148,7 +148,7 @@ __device__ __forceinline__ float2 attention_combine(const ReduceItem& it, const 
     s = group_sum<64>(s, lane);
     return make_float2(m, 1.f / s);
 }
-// pass 2 of forms that have a row with segments in several chunks: one wavefront per split row
+// pass 2 where the segments do not do it: one wavefront per split row
 __global__ void __launch_bounds__(64) attention_combine_kernel(const AttArgs a, const ReduceItem* items, const float2* seg_stats) {
     const ReduceItem it = items[blockIdx.x];
     const float2 t = attention_combine(it, seg_stats, threadIdx.x);
@@ -501,7 +501,7 @@ __global__ void __launch_bounds__(256) perm_sum_kernel(const AttBwdArgs a, const
 
 __global__ void __launch_bounds__(256) attention_bwd_combine_kernel(const AttCombine c) { attention_combine_slots(c, (int)blockIdx.x); }
 
-// (t, q) of the split rows of forms that have a row with segments in several chunks
+// (t, q) of the split rows where the segments do not sum t
 __global__ void __launch_bounds__(256) attention_bwd_combine_t_kernel(const ReduceItem* items, int n_items, const float* slots, float* t, const float* q) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n_items) return;
@@ -545,7 +545,7 @@ int launch_bwd_vec(const AttBwdArgs& a, const AttBwdRows& r, hipStream_t st) {
 //            by source: all weights
 //   phase 1: per-row combination of the segment statistics (by-destination pass only)
 //   phase 2: weights of the split rows' segments (by-destination pass only)
-// combined: no row's segments lie in several chunks, phase 2 does the work of phase 1 and that is left out
+// combined: phase 2 does the work of phase 1 and that is left out (Plan::segments_combine)
 // bins: bin_row_off / bin_count describe rows[] (see Plan); bins 0..3 hold rows of up to 8
 // entries, 4..5 up to 32, the rest up to the split threshold; split rows come as segments
 // (segs, n_segs), their rows as reduce items; seg_stats: two floats per partial-sum slot.

@@ -65,7 +65,7 @@ void check_form(const HostSparse& m, int64_t n, bool strictly, const char* what)
 void check_plan(const HostSparse& m, const Plan& P, int64_t chunk_edges, const char* what) {
     const int64_t n = m.n;
     std::vector<int64_t> covered(n > 0 ? n : 0, 0);      // entries of each row accounted for
-    int64_t e_next = 0, slots = 0;
+    int64_t e_next = 0, slots = 0, slot_reads = 0;
     CHECK(!P.chunks.empty(), "%s: no chunk", what);
     for (const Chunk& c : P.chunks) {
         CHECK(c.e_begin == e_next, "%s: chunk starts at %" PRId64 ", expected %" PRId64, what, c.e_begin, e_next);
@@ -108,12 +108,14 @@ void check_plan(const HostSparse& m, const Plan& P, int64_t chunk_edges, const c
             const int64_t d = m.rowptr[it.row + 1] - m.rowptr[it.row];
             CHECK(d > P.split_threshold || c.partial_row, "%s: short row split", what);
             CHECK(it.first_slot >= 0 && it.first_slot + it.n_slots <= slots, "%s: reduce item slots", what);
+            slot_reads += (int64_t)it.n_slots * it.n_slots;
         }
         CHECK(c.img_bytes >= c.img_off_val && c.img_off_val >= c.img_off_colidx && c.img_off_colidx >= c.meta.size(), "%s: image layout", what);
         CHECK(c.img_bytes <= P.max_img_bytes, "%s: image larger than the staging size", what);
     }
     CHECK(e_next == m.nnz, "%s: chunks end at %" PRId64 " of %" PRId64, what, e_next, m.nnz);
     CHECK(slots == P.n_slots, "%s: %" PRId64 " slots, plan says %" PRId64, what, slots, P.n_slots);
+    CHECK(slot_reads == P.slot_reads, "%s: %" PRId64 " slot reads, plan says %" PRId64, what, slot_reads, P.slot_reads);
     for (int64_t v = 0; v < n; ++v)
         CHECK(covered[v] == m.rowptr[v + 1] - m.rowptr[v], "%s: row %" PRId64 " covered %" PRId64 " of %" PRId64, what, v, covered[v], m.rowptr[v + 1] - m.rowptr[v]);
 }
@@ -218,6 +220,22 @@ void check_row_copies() {
         plan_row_copies(m, P.chunks[0], &l, &lists);
         CHECK(l.slices == (d == 2) && (l.bytes > 0) == (d == 2), "copies: rows of %d entries, %zu bytes", d, l.bytes);
         CHECK(l.off_lists <= (size_t)m.nnz * 20, "copies: %zu bytes for %" PRId64 " entries", l.off_lists, m.nnz);
+    }
+}
+
+// segments combine their row's slots where that is little work: not a row of a thousand segments, nor many rows
+void check_segments_combine() {
+    struct Case { int64_t rows, entries, chunk_edges; bool combine; };
+    for (const Case& t : {Case{1, 600, 0, true}, Case{1, 512 * 256, 0, true}, Case{1, 1024 * 256, 0, false}, Case{1, 1 << 22, 0, false}, Case{250, 32 * 256, 0, true},
+                          Case{1000, 32 * 256, 0, false}, Case{4000, 3 * 256, 0, false}, Case{1, 600, 300, false}, Case{1, 1, 0, true}}) {
+        HostSparse m;
+        m.n = t.rows;
+        for (int64_t v = 0; v <= m.n; ++v) m.rowptr.push_back(v * t.entries);
+        m.nnz = m.n * t.entries;
+        Plan P;
+        make_plan(m, t.chunk_edges, &P);
+        check_plan(m, P, t.chunk_edges, "rows of one length");
+        CHECK(P.segments_combine() == t.combine, "%" PRId64 " rows of %" PRId64 " entries: %" PRId64 " slots, %" PRId64 " reads", t.rows, t.entries, P.n_slots, P.slot_reads);
     }
 }
 
@@ -494,6 +512,8 @@ int main() {
     check_schedule();
     // 6. the second copies of short rows
     check_row_copies();
+    // 7. who combines the slots of split rows
+    check_segments_combine();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");
     return 0;

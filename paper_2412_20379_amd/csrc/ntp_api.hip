@@ -1043,7 +1043,7 @@ int ntp_edge_softmax(ntp_graph_t* g, const float* p, const float* q, float negat
     float* seg_stats = g->att_stats + 4 * n;
     // chunk by chunk, phase by phase (a split row's segments may lie in several chunks)
     auto run = [&](const Form& F, float* out, bool transposed) -> int {
-        const bool combined = !F.plan.has_partial_rows();         // phase 1 as part of phase 2
+        const bool combined = F.plan.segments_combine();         // phase 1 as part of phase 2
         for (int phase = 0; phase < (transposed ? 1 : 3); ++phase)
             for (const Chunk& c : F.plan.chunks) {
                 if (combined && phase == 1) continue;
@@ -1104,8 +1104,8 @@ int ntp_edge_softmax_bwd(ntp_graph_t* g, const float* p, const float* q, float n
     // chunk by chunk, phase by phase (a split row's segments may lie in several chunks)
     // t of split rows where their ds is formed (phase 1 in phase 2), and dq of theirs beside the by-source pass (phase 3 in its phase 0): two
     // launches of 5 us less.  Not with a row whose segments lie in several chunks; the latter for one chunk and buffers apart only.
-    const bool combined = !Fin.plan.has_partial_rows();
-    const bool dq_later = combined && Fin.plan.chunks.size() == 1 && Fin.plan.chunks[0].n_reduce > 0 && 
+    const bool combined = Fin.plan.segments_combine();
+    const bool dq_later = !Fin.plan.has_partial_rows() && Fin.plan.chunks.size() == 1 && Fin.plan.chunks[0].n_reduce > 0 &&
                           ((uintptr_t)(dp + n) <= (uintptr_t)dq || (uintptr_t)(dq + n) <= (uintptr_t)dp);
     auto run = [&](const Form& F, bool transposed) -> int {
         for (int phase = 0; phase < (transposed ? 2 : 4); ++phase)

@@ -162,6 +162,7 @@ struct Plan {
     int64_t split_threshold = 0;
     int64_t chunk_edges = 0;
     int64_t n_slots = 0;                       // partial-sum slots of the whole form
+    int64_t slot_reads = 0;                    // slots that all segments read if each reads those of its row: sum of the rows' squares
     size_t max_img_bytes = 0;                  // largest chunk image (staging buffer size)
     std::vector<Chunk> chunks;
     bool has_partial_rows() const {            // a row with segments in several chunks?
@@ -169,6 +170,12 @@ struct Plan {
             if (c.partial_row) return true;
         return false;
     }
+    // Should every segment of a split row combine the row's slots for itself (a launch less, 5 us), rather than one wavefront or
+    // thread per row in a launch of its own?  Its work grows with the square of a row's segments, and with more segments than the chip holds
+    // blocks each round pays it.  us of the attention weights / of their gradient, in a launch of its own and by the segments: one row
+    // of 512 segments 18.3 / 88 and 17.0 / 68, of 1,024 29.2 / 167 and 30.2 / 136, of 4,096 101 / 626 and 141 / 929; 250 rows of 32 48.4 /
+    // 70.3 and 48.8 / 65.0, 1,000 of 32 93 / 230 and 102 / 240, 64 of 128 61 / 82 and 63 / 95.
+    bool segments_combine() const { return !has_partial_rows() && n_slots <= 8192 && slot_reads <= (1 << 19); }
 };
 
 // Build the plan of one compressed form.  chunk_edges <= 0: a single chunk.

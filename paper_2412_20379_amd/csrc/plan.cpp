@@ -271,6 +271,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
                     const int64_t base = d / nseg, extra = d % nseg;
                     int64_t e = m.rowptr[v];
                     cb.reduce.push_back(ReduceItem{(int32_t)v, next_slot, (int32_t)nseg, 0});
+                    P.slot_reads += nseg * nseg;
                     c.max_split_len = (int32_t)std::max<int64_t>(c.max_split_len, std::min<int64_t>(d, INT32_MAX));
                     for (int64_t i = 0; i < nseg; ++i) {
                         const int64_t l = base + (i < extra ? 1 : 0);
@@ -287,6 +288,7 @@ void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan) {
             const int64_t nseg = (d + seg - 1) / seg;
             const int64_t base = d / nseg, extra = d % nseg;
             const int32_t first_slot = next_slot;
+            P.slot_reads += nseg * nseg;
             int64_t e = e0;
             int64_t i = 0;
             while (i < nseg) {

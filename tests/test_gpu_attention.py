@@ -280,6 +280,20 @@ def test_score_gradient_widths(hub, m):
     _score_grad_case(g, og, m, 0.2, 40 + m, "hub graph")
 
 
+@pytest.mark.parametrize("segments", [700, 730, 1100])
+@pytest.mark.parametrize("flags", [0, ntp.NTP_EDGE_PERM])
+def test_a_row_of_many_segments(segments, flags):
+    """a star: up to 724 segments combine their row's partial sums themselves, more leave it to a launch in between"""
+    n = 256 * segments + 1
+    src, dst = np.arange(1, n, dtype=np.int32), np.zeros(n - 1, np.int32)
+    og = oracle.build_graph(n, src, dst, 0)
+    g = ntp.ntp_graph_build(n, src, dst, flags=flags)
+    p, q = _scores(n, segments)
+    _check_alpha(og, *_device_alpha(g, og.csr.nnz, p, q, 0.2), p, q, 0.2, "star of %d segments" % segments)
+    _score_grad_case(g, og, 8, 0.2, segments, "star")
+    g.close()
+
+
 @pytest.mark.parametrize("slope", [0.0, 1.0])
 def test_score_gradient_slopes(hub, slope):
     n, src, dst, g, og = hub
