@@ -239,6 +239,18 @@ void check_segments_combine() {
     }
 }
 
+// rows of more than 32 entries to lane groups: in fp32 up to 64, where X and the entries are cached and the launch gathers X often enough
+void check_lane_groups() {
+    struct Case { int len, R, passes, dtype; int64_t entries, n; bool cached, groups; };
+    for (const Case& t : {Case{32, 8, 1, NTP_F32, 10, 100000, false, true}, Case{64, 8, 4, NTP_F32, 2501829, 169343, true, true}, Case{64, 8, 3, NTP_F32, 2501829, 169343, true, false},
+                          Case{64, 1, 4, NTP_F32, 2501829, 169343, true, false}, Case{128, 8, 4, NTP_F32, 2501829, 169343, true, false}, Case{128, 8, 8, NTP_F32, 6055034, 60000, true, false},
+                          Case{64, 8, 8, NTP_F32, 15769774, 306128, false, false}, Case{64, 8, 8, NTP_F32, 1000000, 200000, true, false}, Case{64, 8, 4, NTP_F32, 400000, 20000, true, false},
+                          Case{64, 8, 16, NTP_F32, 400000, 20000, true, true}, Case{128, 6, 2, NTP_BF16, 28800000, 232965, false, true}, Case{128, 8, 1, NTP_BF16, 2501829, 169343, true, false},
+                          Case{64, 8, 4, NTP_BF16, 2501829, 169343, true, true}, Case{1 << 30, 8, 16, NTP_BF16, 1 << 30, 1000, true, false}})
+        CHECK(agg_lane_groups(t.len, t.R, t.passes, t.dtype, t.entries, t.n, t.cached) == t.groups, "rows of %d, %d a wavefront, %d passes, %" PRId64 " entries, %" PRId64 " rows of X",
+              t.len, t.R, t.passes, t.entries, t.n);
+}
+
 // hub columns: the most gathered ones, most first, none below the bound; the encoded ids decode back
 void check_hubs(const HostSparse& m, const HostSparse* transposed, const char* what) {
     std::vector<int64_t> count((size_t)m.n, 0);
@@ -514,6 +526,8 @@ int main() {
     check_row_copies();
     // 7. who combines the slots of split rows
     check_segments_combine();
+    // 8. which rows a lane group sums
+    check_lane_groups();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");
     return 0;

@@ -233,8 +233,8 @@ inline int bin_max_degree(int b) { return b == 0 ? 1 : (b == NBINS - 1 ? INT_MAX
 
 // Enqueue the kernels of one chunk whose image lives at `img` on the device.
 // scatter: Y[colidx[k], :] += val[k] * X[row, :] instead of Y[row, :] = sum val[k] * X[colidx[k], :]
-// weights: caller's edge weights in the entry order of the form (nullptr: the stored ones); n: rows of X
-int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y, float* partial,
+// weights: caller's edge weights in the entry order of the form m (nullptr: the stored ones)
+int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const void* X, void* Y, float* partial,
               int64_t f, int64_t ldx, int64_t ldy, int dtype, hipStream_t st, bool scatter = false,
               const float* weights = nullptr, bool defer_reduce = false,
               const int32_t* hub_cols = nullptr, int n_hub = 0, const Epilogue& epi = Epilogue()) {
@@ -264,11 +264,11 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
     // and 30 MB of X) 496 / 470, in fp32 (230 + 45) 671 / 635.  Where they do not fit they only displace rows of X: 26 M
     // entries of two forms (210 + 78) 311 / 318, 63 M (505 + 157) 686 / 706.
     const int64_t es = dtype == NTP_BF16 ? 2 : 4, x_row = std::min(ldx * es, (f * es + 127) / 128 * 128);
-    a.past_caches = (c.e_end - c.e_begin) * 8 + n * x_row > 280000000;
+    a.past_caches = (c.e_end - c.e_begin) * 8 + m.n * x_row > 280000000;
     // The mask is read once: past the caches where it would displace rows of X that are still to be gathered (us with M through / past
     // the caches: 169,343 rows of 256, 173 + 173 MB, 235 / 216; 1,224,514 of 32, 157 + 157 MB, 687 / 681; of 13, 78 + 78 MB, 651 /
     // 657; 169,343 rows of 128, 87 + 87 MB, 105 / 117 with an M that is still there from its last use).
-    a.mask_once = epi.M && n * x_row + (c.row_end - c.row_begin) * x_row > 256000000;
+    a.mask_once = epi.M && m.n * x_row + (c.row_end - c.row_begin) * x_row > 256000000;
 
     int L, nacc = 1, passes = 1;
     if (scatter) {
@@ -311,14 +311,8 @@ int run_chunk(const Chunk& c, int64_t n, const char* img, const void* X, void* Y
         const int cnt = c.bin_count[b];
         if (cnt == 0) continue;
         const int len = bin_max_degree(b);
-        // One lane group per row costs no reduction and one wavefront per R rows; it takes R times as long, so rows of
-        // more than 32 entries get it only in launches large enough, in bf16 (whose reduction has twice the values; 28.8 M
-        // entries, F = 76: 607 -> 571 us with rows of up to 128 entries in it; 2.5 M entries, F = 40: 65 -> 75 us if they are,
-        // hence the rule) and where the columns take four passes and more, each with a reduction (2.5 M entries, F = 256 193 ->
-        // 185 us, F = 128 99 -> 94; MODE_GROUP_LONG_ROW keeps the sums as exact as a wavefront's).  A narrower fp32 slice, whose rows are
-        // summed by wavefronts, would gain 3 % at best.
-        const bool per_group = R > 1 && (len <= 32 || (!scatter && len <= 128 && ((dtype == NTP_BF16 && (double)len * R <= 2 * quantum) ||
-                                                                                  (passes >= 4 && len <= 3.5 * quantum))));
+        // (the form's entries: streamed chunks are summed in the order of resident ones)
+        const bool per_group = scatter ? R > 1 && len <= 32 : agg_lane_groups(len, R, passes, dtype, c.e_end - c.e_begin, m.n, m.nnz * 8 + m.n * x_row <= 280000000);
         const int at_once = per_group ? R : 1;
         const int items = (cnt + at_once - 1) / at_once;
         // rows per wavefront: as many as the quantum allows, and two where one fetch of pairs covers two anyway
@@ -490,7 +484,7 @@ struct ChunkKernels {
     const Epilogue& epi;
     int operator()(const Chunk& c, const char* img) const {
         for (int r = 0; r < n_rhs; ++r) {
-            const int e = run_chunk(c, F.m->n, img, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
+            const int e = run_chunk(c, *F.m, img, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
                                     scatter, nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
             if (e != NTP_OK) return e;
         }
@@ -892,7 +886,7 @@ static int aggregate_resident(ntp_graph_t* g, int which, const void* X, void* Y,
     }
     if (rc != NTP_OK) return rc;
     for (auto& c : F.plan.chunks) {
-        rc = run_chunk(c, g->g.n, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
+        rc = run_chunk(c, *F.m, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
                        F.d_hub_cols, (int)F.plan.hub_cols.size());
         if (rc != NTP_OK) return rc;
     }

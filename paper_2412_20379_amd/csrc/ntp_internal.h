@@ -279,6 +279,9 @@ int agg_pick_pass_lanes(const void* X, int64_t ldx, int dtype, int vec, double e
 struct AggShape { int vec, lanes, n_acc, passes; bool any; };      // any: four floats at any address (IoF32Any)
 AggShape agg_shape_of(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t ldy, int dtype, const void* M, int64_t ldm, int pass_lanes,
                       int64_t entries);
+// Do rows of up to `len` entries get a lane group each (R rows per wavefront), rather than a wavefront?  entries: of the launch; n: rows of X;
+// cached: X and the form's entries fit in the Infinity Cache together
+bool agg_lane_groups(int len, int R, int passes, int dtype, int64_t entries, int64_t n, bool cached);
 int agg_pick_vec(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t ldy, int dtype, const void* M = nullptr, int64_t ldm = 0);
 
 // edge attention weights (attention_kernels.hip)

@@ -190,6 +190,26 @@ void plan_row_copies(const HostSparse& m, const Chunk& c, RowCopies* layout, std
     if (L.slices || L.packed_rows > 0) L.bytes = L.off_lists + lists->size();
 }
 
+// One lane group per row costs no reduction and one wavefront per R rows; it takes R times as long.  Hence rows of more than 32 entries
+// in bf16 (whose reduction has twice the values) in large launches: 28.8 M entries, F = 76, 607 -> 571 us with rows of up to 128 entries in
+// it, 2.5 M entries, F = 40, 65 -> 75.
+// And rows of 33 to 64 where the columns take four passes and more, each with a reduction, and the gathers are not what is waited for: X
+// and the entries fit in the Infinity Cache and a row of X is gathered ten times a launch.  us, a wavefront / a lane group per row:
+// uniform graphs of 41 entries a row, 20,000 vertices F = 128 41 / 29, F = 512 142 / 91, 60,000 F = 256 225 / 210, 200,000 F = 256
+// 1136 / 1116; skewed ones of 2.1 M entries F = 256 113 / 108, 2.5 M F = 128 101 / 95, F = 256 180 / 183, 7.2 M F = 128 202 / 190.  Not
+// otherwise: 306,128 vertices of 51 entries F = 256 2301 / 2336, 200,000 of 41 F = 512 2300 / 2339, in chunks of a million entries 2279 /
+// 2455, skewed 116,482 in such chunks F = 256 1025 / 1053.  Rows of 65 to 128 end the launch late and leave less of the reduction to save: 60,000 vertices of 100 entries F = 256 495 /
+// 553, in chunks of a million entries F = 512 1141 / 1494; 2.1 M entries F = 256 108 / 114; 2.5 M F = 256 183 / 178.
+// (A narrower fp32 slice would gain 3 % at best.  MODE_GROUP_LONG_ROW keeps the sums as exact as a wavefront's.)
+bool agg_lane_groups(int len, int R, int passes, int dtype, int64_t entries, int64_t n, bool cached) {
+    if (R == 1 || len > 128) return false;
+    if (len <= 32) return true;
+    // gathers of the launch per 1/16 of the work of a wavefront slot (8192 on the chip)
+    const double quantum = (double)entries * passes / (16.0 * 8192.0);
+    if (dtype == NTP_BF16 && (double)len * R <= 2 * quantum) return true;
+    return len <= 64 && passes >= 4 && len <= 3.5 * quantum && cached && entries >= 10 * n;
+}
+
 void pick_hub_columns(const HostSparse& m, const HostSparse* transposed, int max_slots, int64_t min_count,
                       std::vector<int32_t>* hub_cols) {
     hub_cols->clear();

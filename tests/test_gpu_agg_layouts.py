@@ -87,10 +87,10 @@ def test_slices_give_the_bits_of_the_forms_own_arrays(slice_graphs, name, f, ld,
 @pytest.mark.parametrize("f", [128, 256])
 @pytest.mark.parametrize("positive", [False, True])
 def test_a_wide_slice_is_summed_as_exactly_as_a_narrow_one(slice_graphs, f, positive):
-    """Rows of 33 to 128 entries: at 64 columns a wavefront's lane groups take a part of the row each, at 128 and more (four passes, in a
+    """Rows of 33 to 64 entries: at 64 columns a wavefront's lane groups take a part of the row each, at 128 and more (four passes, in a
     graph as large as this one) a lane group takes the row.  Chains of 8 with a total in 64 bits round less often than chains of an
-    eighth of 33 entries and a tree of three levels (error variance for signed terms, in units of a term's: 33 entries 178 / 184, 128
-    entries 704 / 1472), so the wide call's error against 64 bits is not the larger one"""
+    eighth of 33 entries and a tree of three levels (error variance for signed terms, in units of a term's: 33 entries 178 / 184), so the
+    wide call's error against 64 bits is not the larger one.  Rows of 65 to 128 are summed alike"""
     import torch
     from gpu_util import dev_f32
     g, og = slice_graphs["large"]
