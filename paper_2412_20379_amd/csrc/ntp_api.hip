@@ -262,9 +262,13 @@ int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const void* 
     // X: a wavefront's gathers wait behind its load of pairs, and that returns sooner.  us past the caches / through them:
     // 2.5 M entries, F = 256 235 / 217 (F = 128 123 / 113, F = 40 67 / 60); 7.2 M, F = 128 245 / 214; 28.8 M, F = 76 in bf16 (230 MB
     // and 30 MB of X) 496 / 470, in fp32 (230 + 45) 671 / 635.  Where they do not fit they only displace rows of X: 26 M
-    // entries of two forms (210 + 78) 311 / 318, 63 M (505 + 157) 686 / 706.
+    // entries of two forms (210 + 78) 311 / 318, 63 M (505 + 157) 686 / 706.  All resident entries count, whatever the chunks (50 M in chunks
+    // of a million, F = 32 1271 / 1304, F = 64 2289 / 2333); of a streamed form the chunk at hand.  (Through them loses up to 4 % where
+    // long rows of one length hardly hit anyway: 60,000 vertices of 100 entries F = 64 118 / 122, F = 512 1081 / 1127; but skewed
+    // 58,241 of 123 F = 128 223 / 190.)
     const int64_t es = dtype == NTP_BF16 ? 2 : 4, x_row = std::min(ldx * es, (f * es + 127) / 128 * 128);
-    a.past_caches = (c.e_end - c.e_begin) * 8 + m.n * x_row > 280000000;
+    const bool resident = img == c.d_image;
+    a.past_caches = (resident ? m.nnz : c.e_end - c.e_begin) * 8 + m.n * x_row > 280000000;
     // The mask is read once: past the caches where it would displace rows of X that are still to be gathered (us with M through / past
     // the caches: 169,343 rows of 256, 173 + 173 MB, 235 / 216; 1,224,514 of 32, 157 + 157 MB, 687 / 681; of 13, 78 + 78 MB, 651 /
     // 657; 169,343 rows of 128, 87 + 87 MB, 105 / 117 with an M that is still there from its last use).
