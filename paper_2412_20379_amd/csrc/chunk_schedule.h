@@ -34,12 +34,19 @@ struct CopyPath {
 //   The row pointers and lists (a fifth of the bytes at 15 entries a row) are copied on the compute stream until the
 //   aggregation cannot spare the time (0.7 of the copy).  On the compute / copy stream: 4 chunks of 4 M entries F = 32 1268 / 1314,
 //   F = 256 1511 / 1438, 8 x 32 columns 1852 / 1762; 11 of 0.4 M F = 32 669 / 682, F = 128 862 / 803, F = 256 1096 / 1016.
-inline CopyPath pick_copy_path(double bytes, double largest, double entries, int64_t lines, int n_rhs) {
+//   Packed ids (`packed`) are a half to seven eighths of the bytes, and kernels that unpack them and rebuild the weights stand before the
+//   aggregation: by these bounds two copies at a time and row pointers on the compute stream would hold up a pass that the aggregation
+//   already bounds.  From three lines a row on: one copy at a time, the row pointers behind it.  us for both directions, ids as they are /
+//   packed by these bounds / packed and so: 4 chunks of 4 M entries of 306,128 vertices F = 76 2840 / 2819 / 2448, F = 128 3019 / 3049 / 2852,
+//   of 200,000 F = 160 3175 / 3460 / 3198; 16 of 1 M of 1 M vertices F = 76 4045 / 4004 / 3504; 23 of 0.7 M of 306,128 F = 128 4373 / 4498 /
+//   4372.  Fewer lines stay with the bounds: 4 of 4 M of 306,128 F = 32 2769 / 1789 / 1948, of 200,000 F = 64 2869 / 1815 / 1940.
+inline CopyPath pick_copy_path(double bytes, double largest, double entries, int64_t lines, int n_rhs, bool packed = false) {
     const double copy_us = bytes / 56e3, aggregate_us = n_rhs * (10.0 + entries * (double)lines * 1e-5);
     CopyPath p;
     p.dma = largest > 768 * 1024;
     p.two_streams = p.dma && (aggregate_us < 0.4 * copy_us || copy_us < 200);
     p.meta_on_compute = !p.dma || aggregate_us <= 0.7 * copy_us;
+    if (packed && p.dma && n_rhs * lines > 2) p.two_streams = p.meta_on_compute = false;
     return p;
 }
 

@@ -419,6 +419,10 @@ void check_schedule() {
     CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 8, 1), true, false, false), "4 M entries, F = 256: the aggregation");
     CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 1, 8), true, false, false), "4 M entries, eight right-hand sides: the aggregation");
     CHECK(is(pick_copy_path(2e6, 2e6, 4e5, 8, 1), true, true, false), "0.4 M entries, F = 256: the aggregation, short copies");
+    CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 1, 1, true), true, true, true), "4 M packed entries, F = 32: the link");
+    CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 3, 1, true), true, false, false), "4 M packed entries, F = 76: the aggregation");
+    CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 1, 4, true), true, false, false), "4 M packed entries, four right-hand sides: the aggregation");
+    CHECK(is(pick_copy_path(700e3, 700e3, 3e5, 3, 1, true), false, false, true), "small packed chunk");
 }
 
 }  // namespace

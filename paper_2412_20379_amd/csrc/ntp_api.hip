@@ -947,19 +947,21 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
     const ChunkKernels run_all{F, n_rhs, X, Y, scatter, g->partial, pstride, f, ldx, ldy, dtype, cs, epi};
     const bool with_val = !g->streams_without_weights();
     int64_t streamed = 0, bytes = 0, largest = 0, entries = 0;
+    bool packed = false;
     for (auto& c : F.plan.chunks)
         if (!c.d_image) {
             const int64_t size = streamed_bytes(c, with_val);
             ++streamed;
             bytes += size;
             largest = std::max(largest, size);
+            packed = packed || c.h_packed_ids;
             entries += c.e_end - c.e_begin;
         }
     const double each = 1.0 / (double)std::max<int64_t>(1, streamed);
     // the scatter's atomics take about sixteen times as long as the gather of a line
     const int64_t lines = (f * (dtype == NTP_BF16 ? 2 : 4) + 127) / 128 * (scatter ? 16 : 1);
     HipPass ops{g, *F.m, &F == &g->form[1], with_val, cs, run_all};
-    StreamedPass<HipPass> pass(ops, g->staged, cs, xs, pick_copy_path(bytes * each, (double)largest, entries * each, lines, n_rhs));
+    StreamedPass<HipPass> pass(ops, g->staged, cs, xs, pick_copy_path(bytes * each, (double)largest, entries * each, lines, n_rhs, packed));
     if (!F.all_resident) rc = pass.begin();
     for (auto& c : F.plan.chunks) {
         if (rc != NTP_OK) return rc;
