@@ -150,8 +150,10 @@ int ntp_graph_chunks(const ntp_graph_t* g, int which, int32_t* n_chunks,
  * is not resident its row pointers and row lists plus 4 bytes per entry (column ids), and 4 more
  * (weights) only when the graph was built with caller weights.  Without caller weights the weights
  * of a streamed chunk are rebuilt on the device from the degrees (bit-identical to the stored
- * ones), which halves the host-link traffic of the chunk schedule, and where chunks hold 655,360
- * entries and more their column ids travel in as few bits each as hold a vertex id (up to 28). */
+ * ones), which halves the host-link traffic of the chunk schedule, and where chunks are cut
+ * at 655,360 entries and more (a graph of 1,310,720 and more that NTP_FORCE_STREAM has the library
+ * cut: in any case) their column ids travel in as few bits each as hold a vertex id (up to 28).
+ * The packed ids are what is pinned then; the ids stay in ordinary host memory beside them. */
 int ntp_graph_stream_bytes(const ntp_graph_t* g, int which, int64_t* bytes);
 
 /* Device bytes held by the handle (resident topology and its second copies, staging buffers, scratch). */

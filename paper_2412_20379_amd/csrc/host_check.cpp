@@ -427,6 +427,22 @@ void check_schedule() {
 
 }  // namespace
 
+// packed where the chunks that will be cut are long enough, by their stored entries and not by the caller's list
+static void check_packs_ids() {
+    struct Case { StreamRequest r; int64_t nnz; bool packs; };
+    const int64_t n = 60000;
+    for (const Case& t : {Case{{n, 0, 655360, 1, true, false}, 655360, true}, Case{{n, 0, 655360, 1, true, false}, 655359, false}, Case{{n, 0, 655359, 1, true, false}, 4000000, false},
+                          Case{{n, 0, 4000000, 2, true, true}, 8000000, false}, Case{{1 << 28, 0, 4000000, 1, true, false}, 8000000, true}, Case{{(1 << 28) + 1, 0, 4000000, 1, true, false}, 8000000, false},
+                          Case{{n, 0, 0, 1, true, false}, 1310720, true}, Case{{n, 0, 0, 2, true, false}, 1310719, false},
+                          Case{{n, 52500000, 0, 1, false, false}, 8000000, true}, Case{{n, 52000000, 0, 1, false, false}, 8000000, false}, Case{{n, 52500000, 0, 1, true, false}, 8000000, true},
+                          Case{{n, 24 << 20, 1 << 20, 2, false, false}, 1500000, true}}) {
+        CHECK(packs_ids(t.r, t.nnz) == t.packs, "packed ids: %" PRId64 " entries, chunks of %" PRId64 ", budget %" PRId64, t.nnz, t.r.chunk_edges, t.r.budget);
+        const int64_t ce = pick_chunk_edges(t.r, t.nnz);
+        CHECK(t.r.chunk_edges > 0 ? ce == t.r.chunk_edges : ce > 0 && (t.r.budget == 0 || ce * 20 * 4 <= t.r.budget), "chunks of %" PRId64 " entries", ce);
+    }
+    CHECK(pick_chunk_edges({n, 0, 0, 1, false, false}, 8000000) == 0 && pick_chunk_edges({n, 65000000, 0, 1, false, false}, 8000000) == 0, "one chunk where everything fits");
+}
+
 // column ids of every width, also where several threads share the words
 static void check_pack_ids() {
     Lcg rng{99};
@@ -448,6 +464,7 @@ static void check_pack_ids() {
 
 int main() {
     check_pack_ids();
+    check_packs_ids();
     // 1. every flag combination, weighted and not, on random multigraphs with loops and repeats
     Lcg rng{12345};
     for (int64_t n : {(int64_t)0, (int64_t)1, (int64_t)2, (int64_t)57, (int64_t)900}) {

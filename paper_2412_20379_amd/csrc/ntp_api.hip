@@ -69,6 +69,7 @@ struct ntp_graph {
     char* pinned_meta = nullptr;                    // metas of streamed chunks
     char* pinned_ids = nullptr;                     // packed column ids of streamed chunks
     int id_bits = 0;
+    bool pack_ids = false;         // streamed chunks send packed column ids
     // partial sums of split rows
     float* partial = nullptr;
     size_t partial_bytes = 0;
@@ -185,30 +186,16 @@ int64_t streamed_bytes(const Chunk& c, bool with_val) {
     return (int64_t)c.meta.size() + (c.h_packed_ids ? c.packed_id_bytes : (c.e_end - c.e_begin) * (with_val ? 8 : 4));
 }
 
-// Streamed chunks of this many entries send their column ids packed (where the weights are rebuilt, so that their place is free).
-// us a pass (both directions) as they are / packed: chunks of 0.66 M entries, 16 bits 1220 / 980; 0.74 M, 20 bits 1855 / 1645; 0.89 M, 18
-// bits, F = 76 1380 / 1255; 4 M, 19 bits 2620 / 1704.  The unpacking kernel is a launch more a chunk (8 us for 4 M ids): short chunks,
-// whose copies are mostly their start (pick_copy_path), go as they are.
-constexpr int64_t PACK_ENTRIES = 5 << 17;
-
-// bits of a vertex id; packed: at most 28, so that the packed ids and a spare word fit in the place of the weights
-int bits_of_ids(int64_t n) { return n <= 2 ? 1 : 64 - __builtin_clzll((unsigned long long)(n - 1)); }
-
-int pack_streamed_ids(ntp_graph* G, int n_forms, bool all) {
-    const int bits = G->id_bits;
+// Column ids of the streamed chunks in as few bits as hold a vertex id (packs_ids)
+int pack_streamed_ids(ntp_graph* G, int n_forms) {
     int64_t bytes = 0;
     auto each = [&](auto&& f) {
-        for (int k = 0; k < n_forms; ++k) {
-            auto& chunks = G->form[k].plan.chunks;
-            int64_t most = 0;
-            for (auto& c : chunks) most = std::max(most, c.d_image ? 0 : c.e_end - c.e_begin);
-            if (!all && most < PACK_ENTRIES) continue;
-            for (auto& c : chunks)
+        for (int k = 0; k < n_forms; ++k)
+            for (auto& c : G->form[k].plan.chunks)
                 if (!c.d_image && c.e_end > c.e_begin) f(*G->form[k].m, c);
-        }
     };
     // like the arrays, packed ids keep their place modulo 16 (16-byte copies)
-    each([&](const HostSparse&, Chunk& c) { c.packed_id_bytes = packed_words(c.e_end - c.e_begin, bits) * 4; bytes += (c.packed_id_bytes + 31) / 16 * 16; });
+    each([&](const HostSparse&, Chunk& c) { c.packed_id_bytes = packed_words(c.e_end - c.e_begin, G->id_bits) * 4; bytes += (c.packed_id_bytes + 31) / 16 * 16; });
     if (bytes == 0) return NTP_OK;
     void* p = nullptr;
     if (hipHostMalloc(&p, (size_t)bytes, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); set_error("pinned allocation of %lld bytes failed", (long long)bytes); return NTP_ENOMEM; }
@@ -217,10 +204,29 @@ int pack_streamed_ids(ntp_graph* G, int n_forms, bool all) {
     each([&](const HostSparse& m, Chunk& c) {
         c.h_packed_ids = G->pinned_ids + off + c.img_off_val % 16;
         off += (c.packed_id_bytes + 31) / 16 * 16;
-        pack_ids(m.colidx + c.e_begin, c.e_end - c.e_begin, bits, reinterpret_cast<uint32_t*>(c.h_packed_ids));
+        pack_ids(m.colidx + c.e_begin, c.e_end - c.e_begin, G->id_bits, reinterpret_cast<uint32_t*>(c.h_packed_ids));
     });
     return NTP_OK;
 }
+
+// Where the entries of a graph live, decided when their number is known: in pinned memory if they may be copied from there, which packed
+// ids are not (they have pinned memory of their own).
+struct EntryMemory {
+    ntp_graph* G;
+    const StreamRequest& request;
+    bool may_stream;
+    bool decided = false;
+    static void* alloc(size_t bytes, void* ctx) {
+        EntryMemory& e = *static_cast<EntryMemory*>(ctx);
+        if (!e.decided) {
+            e.decided = true;
+            e.G->pack_ids = e.may_stream && packs_ids(e.request, (int64_t)(bytes / 4));
+            e.G->pinned_entries = e.may_stream && !e.G->pack_ids;
+            e.G->val_pinned = e.G->pinned_entries && e.request.weighted;
+        }
+        return e.G->pinned_entries ? alloc_pinned(bytes, nullptr) : alloc_plain(bytes, nullptr);
+    }
+};
 
 // what the aggregation does to an output element on its way out (AggArgs::epilogue)
 struct Epilogue {
@@ -560,15 +566,11 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
     std::unique_ptr<ntp_graph, void (*)(ntp_graph*)> guard(G, destroy);   // frees everything on any early return
     G->host_only = flags & NTP_HOST_ONLY;
     const bool force_stream = flags & NTP_FORCE_STREAM;
-    // entries go to pinned memory whenever chunks may have to be streamed
-    G->pinned_entries = !G->host_only && (budget > 0 || force_stream);
-    // streamed chunks whose column ids all travel packed (pack_streamed_ids): the ids themselves stay in ordinary memory
+    const bool weighted = edge_weight != nullptr;
+    StreamRequest request{n, budget, chunk_edges, (flags & NTP_SCATTER_BWD) || ((flags & NTP_SYMMETRISE) && !weighted) ? 1 : 2, force_stream, weighted};
     G->id_bits = bits_of_ids(n);
-    const bool pack_all = force_stream && !G->host_only && !edge_weight && G->id_bits <= 28 && n_edges >= PACK_ENTRIES &&
-                          (chunk_edges == 0 || chunk_edges >= PACK_ENTRIES);
-    if (pack_all) G->pinned_entries = false;
-    G->val_pinned = G->pinned_entries && edge_weight != nullptr;
-    EntryAllocator alloc{G->pinned_entries ? alloc_pinned : alloc_plain, nullptr, alloc_plain};
+    EntryMemory memory{G, request, !G->host_only && (budget > 0 || force_stream)};
+    EntryAllocator alloc{EntryMemory::alloc, &memory, alloc_plain};
 
     int rc = build_host_graph(n, n_edges, src, dst, edge_weight, flags, alloc, &G->g);
     if (rc != NTP_OK) { return rc; }
@@ -578,17 +580,8 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
     G->form[0].m = &G->g.csr;
     G->form[1].m = n_forms == 1 ? &G->g.csr : &G->g.csc;
 
-    // chunk size: caller's, else one chunk if everything fits, else half of what the
-    // budget leaves per staging buffer
-    int64_t ce = chunk_edges;
-    if (ce == 0 && (budget > 0 || force_stream)) {
-        int64_t need = 0;
-        for (int k = 0; k < n_forms; ++k) need += G->form[k].m->nnz * 8 + (n + 1) * 12 + 4096;
-        if (force_stream || need > budget) {
-            const int64_t per_buf = (budget > 0 ? budget : need) / 4;    // two buffers use half
-            ce = std::max<int64_t>(1024, std::min<int64_t>((per_buf - 4096) / 20, INT_MAX / 2));
-        }
-    }
+    request.n_forms = n_forms;            // (one also where the two came out alike)
+    const int64_t ce = pick_chunk_edges(request, G->g.csr.nnz);
     if (flags & NTP_EDGE_PERM) {
         const int64_t nnz = G->g.csr.nnz;
         if (nnz > INT_MAX) { set_error("NTP_EDGE_PERM takes graphs of fewer than 2^31 stored entries"); return NTP_EUNSUPPORTED; }
@@ -673,9 +666,8 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
             G->device_bytes += (int64_t)bytes;
             if (hipMemcpy(p, all.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) { (void)hipGetLastError(); set_error("upload of the split rows failed"); return NTP_EHIP; }
         }
-        const bool rebuilt = pinned_meta_bytes > 0 && !edge_weight && G->id_bits <= 28;
-        if (rebuilt) {
-            rc = pack_streamed_ids(G, n_forms, pack_all);
+        if (G->pack_ids && pinned_meta_bytes > 0) {
+            rc = pack_streamed_ids(G, n_forms);
             if (rc != NTP_OK) return rc;
         }
         if (pinned_meta_bytes) {

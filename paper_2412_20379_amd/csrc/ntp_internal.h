@@ -178,6 +178,16 @@ struct Plan {
     bool segments_combine() const { return !has_partial_rows() && n_slots <= 8192 && slot_reads <= (1 << 19); }
 };
 
+// What a build call asks for that says how its chunks are cut and travel
+struct StreamRequest {
+    int64_t n, budget, chunk_edges;    // chunk_edges 0: the library chooses
+    int n_forms;
+    bool force_stream, weighted;
+};
+int64_t pick_chunk_edges(const StreamRequest& r, int64_t nnz);      // 0: a single chunk
+int bits_of_ids(int64_t n);                                         // bits of a vertex id
+bool packs_ids(const StreamRequest& r, int64_t nnz);                // do streamed chunks send packed column ids?
+
 // Build the plan of one compressed form.  chunk_edges <= 0: a single chunk.
 void make_plan(const HostSparse& m, int64_t chunk_edges, Plan* plan);
 

@@ -104,6 +104,33 @@ struct ChunkBuilder {
 
 }  // namespace
 
+// the caller's chunk size, else one chunk if everything fits, else half of what the budget leaves per staging buffer
+int64_t pick_chunk_edges(const StreamRequest& r, int64_t nnz) {
+    if (r.chunk_edges != 0 || (r.budget == 0 && !r.force_stream)) return r.chunk_edges;
+    const int64_t need = r.n_forms * (nnz * 8 + (r.n + 1) * 12 + 4096);
+    if (!r.force_stream && need <= r.budget) return 0;
+    const int64_t per_buf = (r.budget > 0 ? r.budget : need) / 4;    // two buffers use half
+    return std::max<int64_t>(1024, std::min<int64_t>((per_buf - 4096) / 20, INT_MAX / 2));
+}
+
+int bits_of_ids(int64_t n) { return n <= 2 ? 1 : 64 - __builtin_clzll((unsigned long long)(n - 1)); }
+
+// Packed ids are a half to seven eighths of the bytes on the link and cost a kernel a chunk (8 us for 4 M ids); they go where the weights are
+// rebuilt afterwards, where ids of up to 28 bits and a spare word fit.  us a pass (both directions) as they are / packed:
+//   chunks of 4 M entries, F = 32: 19 bits 2620 / 1704, 22 2612 / 2062, 24 2582 / 2233, 26 2607 / 2359, 28 2619 / 2462; of 1 M, F = 32 (F = 76): 20 bits
+//   2899 / 2400 (3509 / 3288), 24 2909 / 2543 (3519 / 3529), 28 2889 / 2709 (3554 / 3586); of 0.66 M, F = 32 (F = 128): 20 bits 3526 / 3019
+//   (4518 / 4563), 28 3517 / 3227 (4467 / 4589), 16 bits 1220 / 980.
+// Shorter chunks, whose copies are mostly their start (pick_copy_path), gain and lose: of 0.27 M, 20 bits, F = 32 6004 / 6336, F = 76
+// 9908 / 7722; of 0.34 M 5035 / 4997 and 8554 / 8292.  A streamed graph that the library cuts, in five chunks a form or ten, gains earlier: one form of
+// 1.46 M entries 16 bits 916 / 848, 24 bits 914 / 895, of 3.06 M 1493 / 1001 and 1502 / 1476; two forms of 1.56 M 493 / 480 and 499 / 505; not two of
+// 0.76 M, 466 / 477 and 461 / 489.
+bool packs_ids(const StreamRequest& r, int64_t nnz) {
+    if (r.weighted || bits_of_ids(r.n) > 28) return false;
+    if (r.force_stream && r.budget == 0 && r.chunk_edges == 0) return nnz >= 10 << 17;
+    const int64_t ce = pick_chunk_edges(r, nnz);
+    return (ce > 0 ? std::min(ce, nnz) : nnz) >= 5 << 17;
+}
+
 void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed) {
     const int64_t words = packed_words(n, bits);
     const int T = std::max(1, std::min(host_threads(), (int)std::min<int64_t>(64, n / (1 << 16) + 1)));

@@ -330,3 +330,37 @@ def test_packed_column_ids_equal_resident_ones(case):
             assert np.array_equal(u, v)
     resident.close()
     streamed.close()
+
+
+@pytest.mark.parametrize("n_edges,chunk,budget,forms,packed", [(700_000, 655_360, 0, 2, True), (700_000, 655_359, 0, 2, False), (1_320_000, 0, 0, 2, True), (1_300_000, 0, 0, 2, False),
+                                                              (660_000, 0, 0, 1, True), (700_000, 0, 0, 0, False), (3_000_000, 0, 52_500_000, 2, True), (3_000_000, 0, 52_000_000, 2, False)])
+def test_ids_are_packed_by_the_chunks_that_are_cut(n_edges, chunk, budget, forms, packed):
+    """by the caller's chunk size, by the one that a budget leaves, and of a streamed graph cut by the library by its stored entries (forms 0: a list
+    of edges of which every other one is a repetition); the bits of a resident graph in such chunks either way"""
+    import torch
+    n = 60000
+    rng = gen.stream_rng(n_edges, 5)
+    if forms == 0:
+        key = np.tile(np.unique(rng.integers(0, n * n, n_edges // 2)), 2)
+    else:
+        key = np.unique(rng.integers(0, n * n, n_edges))
+    src, dst = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    flags = ntp.NTP_GCN_FLAGS if forms == 1 else ntp.NTP_DEDUP
+    g = ntp.ntp_graph_build(n, src, dst, flags=flags | ntp.NTP_FORCE_STREAM, chunk_edges=chunk, device_budget_bytes=budget)
+    nnz, ch = ntp.ntp_graph_info(g)["nnz"], ntp.ntp_graph_chunks(g)
+    sent = ntp.ntp_graph_stream_bytes(g)
+    say("packed?", n_edges, chunk, budget, forms, "nnz", nnz, "chunks", len(ch["resident"]), "bytes", sent)
+    assert not ch["resident"].any()
+    assert ((sent - 12 * n) / nnz < 3) == packed          # (16 bits or 32; 12 bytes a row)
+    x = torch.randn(n, 8, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(2))
+    cs, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    whole = ntp.ntp_graph_build(n, src, dst, flags=flags, chunk_edges=int(np.max(ch["entry_end"] - ch["entry_begin"])) if chunk == 0 else chunk)
+    for direction in (ntp.NTP_FWD, ntp.NTP_BWD):
+        a, b = torch.full_like(x, 3), torch.full_like(x, 5)
+        torch.cuda.synchronize()
+        ntp.ntp_chunked_aggregate(whole, direction, x, a, 8, 8, 8, ntp.NTP_F32, cs, cp)
+        ntp.ntp_chunked_aggregate(g, direction, x, b, 8, 8, 8, ntp.NTP_F32, cs, cp)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)                # (no row is long enough to be split)
+    whole.close()
+    g.close()
