@@ -112,8 +112,8 @@ typedef struct ntp_graph ntp_graph_t;
  * all), and, in forms of up to 16.8 M entries, those of rows of 33 to 128 (8 bytes an entry).  Such
  * a handle takes about twice the device memory of its entries (2.5 M entries, 15 a row: 45 MB for 22).
  * These copies are made last, take at most an eighth of the memory that is then free, and are left
- * out where they do not fit; results are the same bits with and without them.  A budget keeps a
- * handle without copies.
+ * out where they do not fit; results are the same bits with and without them.  Calls with weights of
+ * the caller's do not read them; a budget, or NTP_EDGE_PERM (attention), keeps a handle without.
  *
  * The input arrays are copied; *out is owned by the library until ntp_graph_free.
  * Errors: NTP_EINVAL (bad ids/sizes/flags), NTP_ENOMEM, NTP_EHIP, NTP_EBUDGET.

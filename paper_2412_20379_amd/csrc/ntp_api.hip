@@ -757,8 +757,10 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
         float* unused = nullptr;            // resolve the static scratch of this device at set-up
         rc = static_scratch(&unused);
         if (rc != NTP_OK) return rc;
-        // Second copies last: they take nothing that the graph needs.  (A form of up to half a million entries is in the L2s whole: none.)
-        if (fits && budget == 0) {
+        // Second copies last: they take nothing that the graph needs.  Not in a graph built for the attention gradient, whose aggregations bring
+        // weights of their own and do not read them (2.5 M entries: 23 MB).  (A form of up to half a million entries is in the L2s whole:
+        // none.  With a hub table they serve the widths that do not take it.)
+        if (fits && budget == 0 && !G->d_perm) {
             HipCopies ops{G};
             for (int k = 0; k < n_forms; ++k)
                 for (auto& c : G->form[k].plan.chunks) {

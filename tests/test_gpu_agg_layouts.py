@@ -160,3 +160,27 @@ def test_rows_at_any_address_give_the_bits_of_aligned_ones(slice_graphs, name, f
             ntp.ntp_aggregate_act(g, direction, Xa, want, f, ld, ld, ntp.NTP_F32, act, Ma if masked else None, ld if masked else 0)
             ntp.ntp_aggregate_act(g, direction, Xu, got, f, ldx, ldy, ntp.NTP_F32, act, Mu if masked else None, ldx if masked else 0)
             assert torch.equal(want[:, :f], got[:, :f]) and bool((got[:, f:] == 7.0).all())
+
+
+def test_no_second_copies_where_no_call_reads_them():
+    """graphs for the attention gradient hold no second copies of their short rows: not their bytes (32 per four entries of a row begun), and
+    the bits of a graph that does"""
+    import torch
+    n = 1 << 17
+    src, dst, w = graph_of_degrees(np.random.default_rng(5).integers(0, 13, size=n), 5)
+    X = torch.randn(n, 32, generator=torch.Generator(device="cuda:0").manual_seed(1), device="cuda:0")
+    bytes_of, out = [], []
+    for flags in (0, ntp.NTP_EDGE_PERM):
+        g = ntp.ntp_graph_build(n, src, dst, edge_weight=w, flags=flags)
+        bytes_of.append(ntp.ntp_graph_device_bytes(g))
+        out.append(torch.full((n, 32), 7.0, device="cuda:0"))
+        ntp.ntp_aggregate_fwd(g, X, out[-1], 32, 32, 32, ntp.NTP_F32)
+        torch.cuda.synchronize()
+        g.close()
+    nnz = src.size
+    say("bytes", bytes_of, "entries", nnz)
+    assert nnz > 1 << 19
+    own = 2 * (8 * nnz + 12 * n)                                # both forms
+    assert bytes_of[0] > own + 2 * 8 * nnz                      # a copy takes at least an entry's eight bytes
+    assert bytes_of[1] < own + 4 * nnz + (1 << 20)              # the permutation
+    assert torch.equal(out[0], out[1])
