@@ -451,7 +451,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         // tree of a wavefront's rows do, so a chain ends after 8 entries and its sum goes to a total in 64 bits, rounded once at the end.
         // Error against 64 bits, rows of 33 to 128 entries, rms over the rms of the sums, signed / positive terms: one chain 1.7e-7 /
         // 1.45e-7, wavefronts 7.9e-8 / 4.4e-8, chains of 8 5.9e-8 / 3.0e-8, in the same time (72 registers still).
-        constexpr bool TOTALS = sizeof(T) == 4 && NACC == 1;
+        constexpr bool TOTALS = sizeof(T) == 4 && NACC == 1 && L == 8 && VEC == 4 && !IO::kAny;          // (agg_lane_groups)
         const bool totals = TOTALS && mode == MODE_GROUP_LONG_ROW;
         double total[TOTALS ? VEC : 1] = {};
         const int first = item0 * K * R;

@@ -234,7 +234,7 @@ bool agg_lane_groups(int len, int R, int passes, int dtype, int64_t entries, int
     // gathers of the launch per 1/16 of the work of a wavefront slot (8192 on the chip)
     const double quantum = (double)entries * passes / (16.0 * 8192.0);
     if (dtype == NTP_BF16 && (double)len * R <= 2 * quantum) return true;
-    return len <= 64 && passes >= 4 && len <= 3.5 * quantum && cached && entries >= 10 * n;
+    return len <= 64 && R == 8 && passes >= 4 && len <= 3.5 * quantum && cached && entries >= 10 * n;
 }
 
 void pick_hub_columns(const HostSparse& m, const HostSparse* transposed, int max_slots, int64_t min_count,
