@@ -234,8 +234,10 @@ constexpr int HUB_SLOTS = 1024;       // lines of the LDS hub table (128 KB at 1
 
 // One wavefront's unit of work (item `wave` of the launch: some rows, some times R short rows, a segment, or a
 // quarter of a block-per-row row) in column pass `pass`.  HUB: entries whose column id is negative
-// take their row from `table`; MODE_BLOCK_PER_ROW is not available then.
-template <class IO, int L, int NACC, bool HUB>
+// take their row from `table`; MODE_BLOCK_PER_ROW is not available then.  PLAIN: without the code of second copies, of loads past
+// the caches and of long rows in lane groups (AggArgs::plain), which launches of a few microseconds on small graphs would wait for (28,343
+// vertices of 7 entries F = 64 9.8 / 9.5 us, 100,000 of 5 F = 32 13.9 / 13.5).
+template <class IO, int L, int NACC, bool HUB, bool PLAIN>
 __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const int pass,
                                          const typename IO::elem* table, float (*quarter)[L * IO::kVec * NACC], int* stage) {
     using T = typename IO::elem;
@@ -250,7 +252,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
     const int grp = agg_group_of(a, wave);
     const AggGroup G = a.group[grp];
     const int item0 = wave - a.wave_start[grp];
-    const int mode = G.mode;
+    const int mode = (int)G.mode;
     const int g = lane / L;
     const int l = lane % L;
     const int passbase = IO::kAny ? min(pass * PASS_W, a.f - VEC) : pass * PASS_W;
@@ -292,7 +294,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
                 float m[VEC];
                 if (a.M) {
                     const T* pm = static_cast<const T*>(a.M) + (int64_t)row * a.ldm + colbase + j * L * VEC;
-                    if (a.mask_once) {
+                    if (!PLAIN && a.mask_once) {
                         IO::expand(IO::load_once(pm), m);
                         asm volatile("");          // (as in fetch)
                     } else {
@@ -369,14 +371,14 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         for (int u = 0; u < U; ++u) multiply_add(on(u) ? w[u] : 0.f, x[u]);
     };
     // entry k of the form (chunk): column id cbase[k], weight vbase[k]
-    const bool packed = !HUB && G.packed;
+    const bool packed = !HUB && !PLAIN && G.packed;
     const int32_t* const cbase = packed ? a.packed_colidx : (HUB ? a.colidx_hub : a.colidx) - a.e_base;
     const float* const vbase = packed ? a.packed_val : a.val - a.e_base;
     const int64_t e_end = packed ? a.packed_end : a.e_end;
     const int64_t* const rp = a.rowptr - a.row_base;
     const int32_t* const rows = a.rows + G.item_off;
     const int count = G.item_count;
-    const int K = G.per_wave;
+    const int K = (int)G.per_wave;
     // The pairs fetched ahead: entries e .. e + 3 of a lane, of which the first `left` belong to the row (the others are
     // never used).  The last lanes of the chunk read its last four entries and are `shift` ahead of themselves.
     Int4 fc = 0;
@@ -395,7 +397,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
                 shift = over > 0 ? (int)over : 0;
                 const Int4* pc = reinterpret_cast<const Int4*>(cbase + e - shift);
                 const Float4* pw = reinterpret_cast<const Float4*>(vbase + e - shift);
-                if (a.past_caches) {
+                if (!PLAIN && a.past_caches) {
                     fc = __builtin_nontemporal_load(pc);
                     fw = __builtin_nontemporal_load(pw);
                     asm volatile("");          // keeps the compiler from making one plain load of the two kinds
@@ -443,7 +445,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         }
     };
 
-    if (R > 1 && (mode == MODE_GROUP_PER_ROW || mode == MODE_GROUP_LONG_ROW)) {
+    if (R > 1 && (mode == MODE_GROUP_PER_ROW || (!PLAIN && mode == MODE_GROUP_LONG_ROW))) {
         // ---- one group of L lanes per row --------------------------------------------
         // A fetch covers per_fetch rows of each group, L / per_fetch lanes each (rows too long for that: one row and
         // EPL * L pairs at a time).
@@ -451,13 +453,13 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         // tree of a wavefront's rows do, so a chain ends after 8 entries and its sum goes to a total in 64 bits, rounded once at the end.
         // Error against 64 bits, rows of 33 to 128 entries, rms over the rms of the sums, signed / positive terms: one chain 1.7e-7 /
         // 1.45e-7, wavefronts 7.9e-8 / 4.4e-8, chains of 8 5.9e-8 / 3.0e-8, in the same time (72 registers still).
-        constexpr bool TOTALS = sizeof(T) == 4 && NACC == 1 && L == 8 && VEC == 4 && !IO::kAny;          // (agg_lane_groups)
+        constexpr bool TOTALS = sizeof(T) == 4 && NACC == 1 && L == 8 && VEC == 4 && !IO::kAny && !PLAIN;          // (agg_lane_groups)
         const bool totals = TOTALS && mode == MODE_GROUP_LONG_ROW;
         double total[TOTALS ? VEC : 1] = {};
         const int first = item0 * K * R;
         const int n_rows = min(K * R, count - first);
         read_rows(first, n_rows);
-        const int S = G.per_fetch;
+        const int S = (int)G.per_fetch;
         const int lpi = L / S;                              // lanes of a group per row and fetch
         const int fl = EPL * (l & (lpi - 1)), fs = l / lpi;
         auto fetch_rows = [&](const int k, const int k0) {
@@ -515,7 +517,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
         return;
     }
 
-    if (!HUB && R > 1 && mode == MODE_SLICE) {
+    if (!HUB && !PLAIN && R > 1 && mode == MODE_SLICE) {
         // ---- one group of L lanes per row, entries from the slices ---------------------
         // A fetch brings a lane four entries: S = L / chunks rows of each group (a row of more than L chunks takes several).
         const int first = item0 * K * R;
@@ -527,7 +529,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
             mbase = a.slice_base[s];
             md = a.slice_base[s + 1] - mbase;
         }
-        const int chunks = G.slice_chunks, S = G.per_fetch;
+        const int chunks = (int)G.slice_chunks, S = (int)G.per_fetch;
         const int lpi = L / S;                              // lanes of a group per row and fetch
         const int fl = l & (lpi - 1), fs = l / lpi;
         auto fetch_rows = [&](const int k, const int c0) {
@@ -538,7 +540,7 @@ __device__ __forceinline__ void agg_item(const AggArgs& a, const int wave, const
                 const int64_t at = (int64_t)(base + c0 + fl) * (4 * SLICE_ROWS) + (first + src) % SLICE_ROWS * 4;
                 const Int4* pc = reinterpret_cast<const Int4*>(a.slice_colidx + at);
                 const Float4* pw = reinterpret_cast<const Float4*>(a.slice_val + at);
-                if (a.past_caches) {
+                if (!PLAIN && a.past_caches) {
                     fc = __builtin_nontemporal_load(pc);
                     fw = __builtin_nontemporal_load(pw);
                     asm volatile("");          // (as in fetch)
@@ -790,13 +792,13 @@ __device__ __forceinline__ int xcd_block(int b, int blocks) {
 // Gathers are issued U at a time with no branch between them, so that U neighbour rows are in flight per lane before the
 // first multiply-add waits; only the last ones of a row are masked one by one.  A lane whose columns lie beyond the slice
 // reads the first columns of its pass and stores nothing.
-template <class IO, int L, int NACC>
+template <class IO, int L, int NACC, bool PLAIN>
 __global__ void __launch_bounds__(256, (agg_min_waves<IO, L, NACC>())) agg_kernel(const AggArgs a) {
     __shared__ __align__(16) int stage[4][stage_words(L, false)];
     __shared__ float quarter[3][L * IO::kVec * NACC];     // block-per-row mode: sums of wavefronts 1..3
     const int wave = __builtin_amdgcn_readfirstlane(xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + (int)(threadIdx.x >> 6));
     if (wave >= a.n_waves) return;
-    agg_item<IO, L, NACC, false>(a, wave, (int)blockIdx.y, nullptr, quarter, stage[threadIdx.x >> 6]);
+    agg_item<IO, L, NACC, false, PLAIN>(a, wave, (int)blockIdx.y, nullptr, quarter, stage[threadIdx.x >> 6]);
 }
 
 // The same work with the hub rows of the column pass in LDS: one block of 16 wavefronts per
@@ -824,7 +826,7 @@ __global__ void __launch_bounds__(1024, 4) agg_hub_kernel(const AggArgs a) {
     const int total = a.n_waves;
     const int w0 = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 16 + (threadIdx.x >> 6)));
     for (int wave = w0; wave < total; wave += 16 * (int)gridDim.x)
-        agg_item<IO, L, 1, true>(a, wave, (int)blockIdx.y, table, nullptr, stage[threadIdx.x >> 6]);
+        agg_item<IO, L, 1, true, false>(a, wave, (int)blockIdx.y, table, nullptr, stage[threadIdx.x >> 6]);
 }
 
 // ---- second pass for split rows: Y[row,:] = sum of its partial-sum slots ---------------
@@ -875,7 +877,8 @@ int launch_one(const AggArgs& a, int n_passes, hipStream_t st) {
     const int total = a.n_waves;
     if (total <= 0) return NTP_OK;
     dim3 grid((unsigned)((total + 3) / 4), (unsigned)n_passes);
-    hipLaunchKernelGGL((agg_kernel<IO, L, NACC>), grid, dim3(256), 0, st, a);
+    if (a.plain) hipLaunchKernelGGL((agg_kernel<IO, L, NACC, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((agg_kernel<IO, L, NACC, false>), grid, dim3(256), 0, st, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("aggregation kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
     return NTP_OK;

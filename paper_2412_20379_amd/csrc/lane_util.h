@@ -51,12 +51,11 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// The group of an AggArgs that wavefront `wave` belongs to: the whole table is read at once, not one entry after the other
-// (0.4 us of a launch with nine groups).
+// The group of an AggArgs that wavefront `wave` belongs to.  One entry after the other: most wavefronts are in the first ones (28,343
+// vertices of 7 entries F = 64 9.45 us where the whole table is compared, 9.35 so; 100,000 of 5 F = 32 13.4 / 13.1).
 template <class Args> __device__ __forceinline__ int agg_group_of(const Args& a, int wave) {
     int g = 0;
-#pragma unroll
-    for (int i = 1; i < (int)(sizeof a.wave_start / sizeof a.wave_start[0]); ++i) g += wave >= a.wave_start[i] ? 1 : 0;
+    while (g + 1 < (int)(sizeof a.wave_start / sizeof a.wave_start[0]) && wave >= a.wave_start[g + 1]) ++g;
     return g;
 }
 

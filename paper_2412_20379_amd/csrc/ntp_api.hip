@@ -302,7 +302,7 @@ int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const void* 
     int64_t waves = 0;
     auto add_group = [&](int mode, int off, int count, int64_t nw, int per_wave = 1, int per_fetch = 1) {
         a.wave_start[ng] = (int32_t)waves;
-        a.group[ng] = AggGroup{mode, off, count, per_wave, per_fetch, 0, 0, 0};
+        a.group[ng] = AggGroup{off, count, 0, (uint32_t)mode, 0, (uint32_t)per_wave, (uint32_t)per_fetch, 0};
         waves += nw;
         ++ng;
     };
@@ -346,6 +346,8 @@ int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const void* 
     }
     if (waves > INT_MAX - 8) { set_error("chunk too large for one launch (%lld wavefronts)", (long long)waves); return NTP_EUNSUPPORTED; }
     a.n_waves = (int32_t)waves;
+    a.plain = !a.past_caches && !a.mask_once;
+    for (int g = 0; g < ng; ++g) a.plain = a.plain && a.group[g].mode != MODE_SLICE && a.group[g].mode != MODE_GROUP_LONG_ROW && !a.group[g].packed;
     for (int g = ng; g < NGROUPS; ++g) a.wave_start[g] = INT_MAX;
     a.slice_colidx = reinterpret_cast<const int32_t*>(c.d_copies);
     a.slice_val = reinterpret_cast<const float*>(c.d_copies + copies.off_slice_val);

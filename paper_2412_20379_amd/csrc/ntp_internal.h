@@ -204,15 +204,15 @@ void encode_hub_columns(const HostSparse& m, const std::vector<int32_t>& hub_col
 
 // ---------------------------------------------------------------------------------------
 // Rows of a bin, or the split rows or segments
-struct AggGroup {
-    int32_t mode;              // MODE_*
+struct AggGroup {              // (16 bytes: one scalar load, and the argument block stays short for calls of a few microseconds)
     int32_t item_off;          // offset into rows[] or packed_rows[] (bins), segs[] or split_rows[]
     int32_t item_count;        // rows / segments in the group
-    int32_t per_wave;          // items (rows, or R rows at a time) a wavefront of a row group works through
-    int32_t per_fetch;         // rows of a lane group whose entries one fetch brings (a power of two)
-    int32_t packed;            // 1: packed rows
     int32_t slice_off;         // MODE_SLICE: first slice of the group
-    int32_t slice_chunks;      // MODE_SLICE: most chunks of a row
+    uint32_t mode : 4;         // MODE_*
+    uint32_t packed : 1;       // packed rows
+    uint32_t per_wave : 8;     // items (rows, or R rows at a time) a wavefront of a row group works through
+    uint32_t per_fetch : 8;    // rows of a lane group whose entries one fetch brings (a power of two)
+    uint32_t slice_chunks : 8; // MODE_SLICE: most chunks of a row
 };
 // Argument block of the aggregation kernel (passed by value).
 struct AggArgs {
@@ -238,6 +238,7 @@ struct AggArgs {
     int32_t pass_lanes;        // vectors per feature row and column pass (0: widest shape)
     int32_t mask_once;         // 1: M is read with non-temporal loads (see run_chunk)
     int32_t past_caches;       // 1: indices and weights are read with non-temporal loads (see run_chunk)
+    int32_t plain;             // 1: no second copies, nothing past the caches, no long rows in lane groups
     int32_t n_hub;             // hub columns (at most agg_hub_slots())
     int32_t n_waves;           // wavefronts of the launch
     int32_t wave_start[NGROUPS];       // first wavefront of each group (INT_MAX beyond the last)

@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(256) scatter_kernel(const AggArgs a) {
     const int grp = agg_group_of(a, wave);
     const AggGroup G = a.group[grp];
     const int item0 = wave - a.wave_start[grp];
-    const int mode = G.mode;
+    const int mode = (int)G.mode;
     const int g = lane / L;
     const int l = lane % L;
     const int colbase = (int)blockIdx.y * PASS_W + l;
