@@ -219,9 +219,12 @@ void launch_k(const ResidentArgs& g, hipStream_t st) {
 
 }  // namespace
 
-// A block's B costs some 12 us (256 x 256) before its first rows: us in strips / here, 256 -> 256 (fwd, dA, masked dA) on 24,576 rows 26 26
-// 28 / 30 29 33, on 40,000 39 39 43 / 39 38 43, on 65,536 56 57 62 / 54 53 58; 128 -> 256 on 16,384 13 / 13, on 32,768 21.7 / 20.6.
-bool nn_resident_takes(int64_t n, int64_t K, int64_t N) { return K > 64 && K <= 256 && N > 192 && N <= 256 && n >= (K <= 128 ? 24576 : 40000); }
+// A block's B costs some 12 us (256 x 256) before its first rows, and a block more or less per compute unit shows: the strips take 40,961 to
+// 49,152 rows in the time that they take 40,960 in.  us in strips / here, 256 -> 256 (fwd, dA, masked dA) on 40,000 rows 38 38 42 / 38 37 43, 41,000
+// 39 39 43 / 41 40 45, 49,152 43 43 47 / 43 42 48, 49,200 48 47 53 / 45 45 50, 65,536 57 56 62 / 52 51 58; 200 -> 256 on 41,000 34 34 40 / 38 37 37,
+// 49,200 42 42 49 / 42 41 42, 58,000 46 46 52 / 47 46 46; 128 -> 256 on 24,576 16.7 16.3 18.2 / 17.2 16.7 17.9, 27,000 19.1 18.5 19.7 / 18.9 18.5
+// 19.9, 32,800 23.9 23.3 25.9 / 20.6 20.2 22.1; 100 -> 200 on 24,576 15.2 15.1 18.0 / 15.8 15.3 15.9, 24,600 16.6 16.4 18.5 / 15.6 15.4 16.5.
+bool nn_resident_takes(int64_t n, int64_t K, int64_t N) { return K > 64 && K <= 256 && N > 192 && N <= 256 && n > (K <= 128 ? 24576 : 49152); }
 
 int launch_nn_resident(const float* A, const float* mask, const float* B, float* C, int64_t n, int64_t K, int64_t N, int64_t ldb,
                        bool b_kcontig, bool relu, bool nt, void* stream) {
