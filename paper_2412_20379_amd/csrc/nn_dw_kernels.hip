@@ -79,9 +79,10 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     const int r = lane & 31, h = lane >> 5;
     const int per_share = g.kt * g.mt, shares = 8 / per_share;
     const int tile = wave % per_share, share = wave / per_share;
-    // an XCD (blocks 8 apart) takes per_xcd pieces of work in a row: the tiles of one range of vertices are mostly on one
+    // an XCD (blocks 8 apart) takes per_xcd pieces of work in a row: the tiles of one range of vertices are mostly on one.  Ranges of one
+    // tile are dealt in turn (29,112 rows of 64 x 128 16.9 us in a row, 16.2 in turn)
     const int minor = g.tiles_k * g.tiles_m, id = (int)blockIdx.x;
-    const int j = id % 8 * g.per_xcd + id / 8, split = j / minor, t = j % minor;
+    const int j = minor == 1 ? id : id % 8 * g.per_xcd + id / 8, split = j / minor, t = j % minor;
     if (split >= g.n_splits) return;
     const int c0 = (t % g.tiles_k * g.kt + tile % g.kt) * (32 * TA), z0 = (t / g.tiles_k * g.mt + tile / g.kt) * (32 * TN);
     const int64_t r0 = split * g.rows_per_split, r1 = min(r0 + g.rows_per_split, g.n);
