@@ -973,7 +973,8 @@ int agg_pick_vec(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t l
 // 143, 514 983 / 712; 7.2 M entries F = 602 2391 / 1705.  Not where that takes twice as many passes as vectors of two (512 columns) and
 // ends in one of few columns (2.5 M entries F = 258 359 / 415, 302 386 / 415), not for rows of a few columns (F = 6 26 / 30), and up to 256
 // columns of few entries stay with more lanes per row, which end sooner (66 k entries F = 47 5.2 / 6.6; 130 k 7.8 / 7.5; 0.2 M
-// 13.3 / 9.6).
+// 13.3 / 9.6).  Above 256 whatever the entries: 5 k F = 602 6.2 / 5.9, 13 k F = 257 6.0 / 5.9, F = 602 9.2 / 7.4, F = 1433 15.5 / 15.3 (rows of X not
+// read before 16.4 / 16.2), 120 k F = 514 48.9 / 37.1, F = 1001 60.2 / 59.7.
 AggShape agg_shape_of(const void* X, const void* Y, int64_t f, int64_t ldx, int64_t ldy, int dtype, const void* M, int64_t ldm, int pass_lanes,
                       int64_t entries) {
     AggShape s;
