@@ -33,7 +33,7 @@ def graph_of_degrees(deg, seed):
 
 @pytest.fixture(scope="module")
 def slice_graphs():
-    """every row length from 0 to 140, in one of them so many rows that at 128 columns a lane group takes a row of up to 128 entries;
+    """every row length from 0 to 140, in one of them so many rows that at 128 columns a lane group takes a row of up to 64 entries;
     and short rows only"""
     out = {}
     for name, n, top in (("long", 1 << 13, 140), ("large", 1 << 15, 140), ("short", 1 << 18, 5)):      # (more than half a million entries)
