@@ -4,8 +4,11 @@
 #include "ntp_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include <cstring>
+#include <thread>
+#include <utility>
 
 namespace ntp {
 
@@ -24,17 +27,38 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // stay near in the list (windows of 512 rows cost 2-5 % on short rows: fewer rows share a line of the row pointers).
 constexpr int SORT_WINDOW = 64;
 static_assert(SORT_WINDOW % SLICE_ROWS == 0, "a slice's rows lie in one window");
-void sort_by_length(int32_t* rows, int64_t n, const int64_t* rp, int below) {
+void sort_window(int32_t* rows, int m, const int64_t* rp, int below) {
     int32_t tmp[SORT_WINDOW];
-    for (int64_t w = 0; w < n; w += SORT_WINDOW) {
-        const int m = (int)std::min<int64_t>(SORT_WINDOW, n - w);
-        int at[64 + 1] = {0};               // at[k + 1]: rows of length 2 * below - k
-        for (int i = 0; i < m; ++i) ++at[2 * below - (rp[rows[w + i] + 1] - rp[rows[w + i]]) + 1];
-        for (int k = 1; k < below; ++k) at[k] += at[k - 1];
-        for (int i = 0; i < m; ++i) tmp[at[2 * below - (rp[rows[w + i] + 1] - rp[rows[w + i]])]++] = rows[w + i];
-        std::copy(tmp, tmp + m, rows + w);
+    int key[SORT_WINDOW];               // of length 2 * below - key
+    int at[64 + 1] = {0};
+    for (int i = 0; i < m; ++i) {
+        const int64_t* p = rp + rows[i];
+        key[i] = 2 * below - (int)(p[1] - p[0]);
+        ++at[key[i] + 1];
     }
+    for (int k = 1; k < below; ++k) at[k] += at[k - 1];
+    for (int i = 0; i < m; ++i) tmp[at[key[i]]++] = rows[i];
+    std::copy(tmp, tmp + m, rows);
 }
+
+// All threads of a parallel_for_threads call meet here.
+class Meeting {
+public:
+    explicit Meeting(int n) : n_(n) {}
+    void wait() {
+        const int turn = turn_.load(std::memory_order_acquire);
+        if (here_.fetch_add(1, std::memory_order_acq_rel) + 1 == n_) {
+            here_.store(0, std::memory_order_relaxed);
+            turn_.store(turn + 1, std::memory_order_release);
+        } else {
+            while (turn_.load(std::memory_order_acquire) == turn) std::this_thread::yield();
+        }
+    }
+
+private:
+    const int n_;
+    std::atomic<int> here_{0}, turn_{0};
+};
 
 struct ChunkBuilder {
     const HostSparse& m;
@@ -51,14 +75,45 @@ struct ChunkBuilder {
     void finish(Chunk& c, bool bins) {
         const int64_t nrows = c.row_end - c.row_begin;
         const int64_t* rp = m.rowptr.data();
-        if (bins)
-            for (int64_t v = c.row_begin; v < c.row_end; ++v) {
+        // Threads take consecutive rows, count them by bin, list them and sort the windows: 169,343 rows 1.34 ms on one, 0.48 on five
+        const int T = bins ? (int)std::max<int64_t>(1, std::min<int64_t>(host_threads(), nrows / 32768)) : 1;
+        std::vector<int32_t> counts((size_t)T * NBINS, 0);
+        Meeting meeting(T);
+        auto rows_of = [&](int t) { return c.row_begin + nrows * t / T; };
+        auto count_bins = [&](int t) {
+            int32_t count[NBINS] = {0};
+            for (int64_t v = rows_of(t), end = rows_of(t + 1); v < end; ++v) {
                 const int64_t d = rp[v + 1] - rp[v];
-                if (d <= plan.split_threshold) ++c.bin_count[bin_of(d)];
+                if (d <= plan.split_threshold) ++count[bin_of(d)];
             }
+            std::copy(count, count + NBINS, counts.begin() + (std::ptrdiff_t)t * NBINS);
+        };
+        auto list_rows = [&](int t) {          // counts: the first place of every thread in every bin
+            int32_t* const rows = reinterpret_cast<int32_t*>(c.meta.data() + c.off_rows);
+            int32_t* at[NBINS];
+            for (int b = 0; b < NBINS; ++b) at[b] = rows + counts[(size_t)t * NBINS + b];
+            const int64_t first = rows_of(t), end = rows_of(t + 1);
+            memcpy(c.meta.data() + c.off_rowptr + (size_t)(first - c.row_begin) * 8, rp + first, (size_t)(end - first) * 8);
+            for (int64_t v = first; v < end; ++v) {
+                const int64_t d = rp[v + 1] - rp[v];
+                if (d <= plan.split_threshold) *at[bin_of(d)]++ = (int32_t)v;
+            }
+            meeting.wait();
+            for (int b = 2; b < NBINS - 1; ++b) {
+                const int64_t windows = (c.bin_count[b] + SORT_WINDOW - 1) / SORT_WINDOW;
+                for (int64_t w = windows * t / T; w < windows * (t + 1) / T; ++w)
+                    sort_window(rows + c.bin_row_off[b] + w * SORT_WINDOW, (int)std::min<int64_t>(SORT_WINDOW, c.bin_count[b] - w * SORT_WINDOW), rp, 1 << (b - 1));
+            }
+        };
+        if (T == 1 && bins) count_bins(0);
+        if (T > 1) parallel_for_threads(T, [&](int t, int) { count_bins(t); });
+        for (int b = 0; b < NBINS; ++b)
+            for (int t = 0; t < T; ++t) c.bin_count[b] += counts[(size_t)t * NBINS + b];
         size_t nbin = 0;
         for (int b = 0; b < NBINS; ++b) {
             c.bin_row_off[b] = (int32_t)nbin;
+            int32_t at = (int32_t)nbin;
+            for (int t = 0; t < T; ++t) at += std::exchange(counts[(size_t)t * NBINS + b], at);
             nbin += (size_t)c.bin_count[b];
         }
         c.n_segs = (int32_t)segs.size();
@@ -78,17 +133,10 @@ struct ChunkBuilder {
         c.off_reduce = align_up(c.off_segs + segs.size() * sizeof(Segment), 16);
         const size_t meta_bytes = align_up(c.off_reduce + reduce.size() * sizeof(ReduceItem), 256);
         c.meta.assign(meta_bytes, 0);
-        memcpy(c.meta.data() + c.off_rowptr, m.rowptr.data() + c.row_begin, (size_t)(nrows + 1) * 8);
-        if (bins) {
-            int32_t* rows = reinterpret_cast<int32_t*>(c.meta.data() + c.off_rows);
-            int32_t* at[NBINS];
-            for (int b = 0; b < NBINS; ++b) at[b] = rows + c.bin_row_off[b];
-            for (int64_t v = c.row_begin; v < c.row_end; ++v) {
-                const int64_t d = rp[v + 1] - rp[v];
-                if (d <= plan.split_threshold) *at[bin_of(d)]++ = (int32_t)v;
-            }
-            for (int b = 2; b < NBINS - 1; ++b) sort_by_length(rows + c.bin_row_off[b], c.bin_count[b], rp, 1 << (b - 1));
-        }
+        memcpy(c.meta.data() + c.off_rowptr + (size_t)nrows * 8, rp + c.row_end, 8);
+        if (T > 1) parallel_for_threads(T, [&](int t, int) { list_rows(t); });
+        else if (bins) list_rows(0);
+        else memcpy(c.meta.data() + c.off_rowptr, rp + c.row_begin, (size_t)nrows * 8);
         if (!segs.empty()) memcpy(c.meta.data() + c.off_segs, segs.data(), segs.size() * sizeof(Segment));
         if (!reduce.empty()) memcpy(c.meta.data() + c.off_reduce, reduce.data(), reduce.size() * sizeof(ReduceItem));
         const size_t ne = (size_t)(c.e_end - c.e_begin);
