@@ -132,6 +132,53 @@ void free_entries(HostSparse& m, bool pinned, bool val_pinned) {
     m.val = nullptr;
 }
 
+// a resident chunk's image from column ids that are on the device, weights made there as for streamed chunks
+int fill_chunk(const DeviceForms& forms, int k, int val_mode, const Chunk& c, char* dst) {
+    const size_t ne = (size_t)(c.e_end - c.e_begin);
+    HIP_TRY(hipMemcpy(dst, c.meta.data(), c.meta.size(), hipMemcpyHostToDevice));
+    if (!ne) return NTP_OK;
+    HIP_TRY(hipMemcpyAsync(dst + c.img_off_colidx, forms.colidx[k] + c.e_begin, ne * 4, hipMemcpyDeviceToDevice, nullptr));
+    return launch_rebuild_weights(reinterpret_cast<const int64_t*>(dst + c.off_rowptr), c.row_begin, c.row_end - c.row_begin, c.e_begin, (int64_t)ne,
+                                  reinterpret_cast<const int32_t*>(dst + c.img_off_colidx), reinterpret_cast<float*>(dst + c.img_off_val),
+                                  forms.degree[k], forms.degree[1 - k], val_mode, nullptr);
+}
+
+// A stream for copies to the host that are independent of everything else, one per device (creating and destroying one takes 0.3 ms)
+hipError_t export_stream(hipStream_t* out) {
+    constexpr int MAX_DEVICES = 64;
+    static std::mutex mu;
+    static hipStream_t streams[MAX_DEVICES] = {nullptr};
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= MAX_DEVICES) return hipErrorInvalidDevice;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!streams[dev]) e = hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking);
+    *out = streams[dev];
+    return e;
+}
+
+// a form's entries from the images of its chunks (a graph built on the device has no others); also while a stream is being captured
+int read_entries(const Form& F, int32_t* colidx, float* val) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+    hipStream_t st = nullptr;
+    hipError_t e = export_stream(&st);
+    const bool begun = e == hipSuccess;
+    for (const Chunk& c : F.plan.chunks) {
+        const size_t bytes = (size_t)(c.e_end - c.e_begin) * 4;
+        if (bytes && colidx && e == hipSuccess) e = hipMemcpyAsync(colidx + c.e_begin, c.d_image + c.img_off_colidx, bytes, hipMemcpyDeviceToHost, st);
+        if (bytes && val && e == hipSuccess) e = hipMemcpyAsync(val + c.e_begin, c.d_image + c.img_off_val, bytes, hipMemcpyDeviceToHost, st);
+    }
+    if (begun) {
+        const hipError_t done = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = done;
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    HIP_TRY(e);
+    return NTP_OK;
+}
+
 // a resident chunk's image
 int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
     const size_t ne = (size_t)(c.e_end - c.e_begin);
@@ -574,7 +621,16 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
     EntryMemory memory{G, request, !G->host_only && (budget > 0 || force_stream)};
     EntryAllocator alloc{EntryMemory::alloc, &memory, alloc_plain};
 
-    int rc = build_host_graph(n, n_edges, src, dst, edge_weight, flags, alloc, &G->g);
+    const char* hub_env = getenv("NTP_AGG_HUB");
+    const bool hub_tables = hub_env && hub_env[0] == '1';
+    // on the device where nothing asks for the entries on the host
+    DeviceForms forms;
+    bool on_device = !G->host_only && !force_stream && budget == 0 && !weighted && !(flags & NTP_EDGE_PERM) && !hub_tables && device_build_takes(n, n_edges, flags);
+    int rc = on_device ? build_device_forms(n, n_edges, src, dst, flags, &G->g, &forms) : DEVICE_BUILD_NO_MEMORY;
+    if (rc == DEVICE_BUILD_NO_MEMORY) {
+        on_device = false;
+        rc = build_host_graph(n, n_edges, src, dst, edge_weight, flags, alloc, &G->g);
+    }
     if (rc != NTP_OK) { return rc; }
     if (G->g.symmetric && G->g.csc.colidx) { free_entries(G->g.csc, G->pinned_entries, G->val_pinned); G->g.csc = HostSparse(); }
 
@@ -639,7 +695,7 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                     c.d_image = (char*)p;
                     G->device_bytes += (int64_t)c.img_bytes;
                     if (!fits) left -= (int64_t)c.img_bytes;
-                    rc = upload_chunk(*G->form[k].m, c, c.d_image);
+                    rc = on_device ? fill_chunk(forms, k, G->g.val_mode, c, c.d_image) : upload_chunk(*G->form[k].m, c, c.d_image);
                     if (rc != NTP_OK) { return rc; }
                 } else {
                     pinned_meta_bytes += c.meta.size();
@@ -691,8 +747,7 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
         // array names them.  A column is worth a slot when it is gathered more often than the table is
         // filled (once per compute unit and column pass): NTP_AGG_HUB_MIN_COUNT overrides the bound,
         // NTP_AGG_HUB_SLOTS the number of slots.
-        const char* hub_env = getenv("NTP_AGG_HUB");
-        if (fits && n > 0 && hub_env && hub_env[0] == '1') {
+        if (fits && n > 0 && hub_tables) {
             int64_t min_count = 256;
             if (const char* e = getenv("NTP_AGG_HUB_MIN_COUNT")) min_count = std::max<int64_t>(1, atoll(e));
             int64_t extra = 0;
@@ -749,6 +804,7 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
             G->device_bytes += (int64_t)bytes;
             if (hipMemcpy(G->d_perm, G->h_perm.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) { (void)hipGetLastError(); set_error("upload of the edge permutation failed"); return NTP_EHIP; }
         }
+        forms.release();
         // partial sums of split rows: allocated here for slices of up to 256 columns, so that only a
         // call with a wider slice ever allocates (and synchronises) inside an aggregation
         for (int k = 0; k < n_forms; ++k)
@@ -811,6 +867,7 @@ int ntp_graph_export(const ntp_graph_t* g, int which, int64_t* rowptr, int32_t* 
     if (which == NTP_CSC && g->scatter_bwd()) { set_error("graph was built with NTP_SCATTER_BWD: no by-source form is stored"); return NTP_EUNSUPPORTED; }
     const HostSparse& m = *g->f(which).m;
     if (rowptr) memcpy(rowptr, m.rowptr.data(), (size_t)(m.n + 1) * 8);
+    if (m.nnz && !m.colidx) return read_entries(g->f(which), colidx, val);
     if (colidx && m.nnz) memcpy(colidx, m.colidx, (size_t)m.nnz * 4);
     if (val && m.nnz) memcpy(val, m.val, (size_t)m.nnz * 4);
     return NTP_OK;

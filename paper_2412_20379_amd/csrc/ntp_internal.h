@@ -69,6 +69,21 @@ int build_host_graph(int64_t n, int64_t n_edges, const int32_t* src, const int32
                      const float* edge_weight, uint32_t flags, EntryAllocator alloc,
                      BuiltGraph* out);
 
+// The same on the device, for graphs without caller weights that stay there (graph_device.hip).  The host gets the row pointers (csc empty when
+// symmetric); column ids and degrees wait on the device.
+struct DeviceForms {
+    int32_t* colidx[2] = {nullptr, nullptr};        // by destination, by source
+    int32_t* degree[2] = {nullptr, nullptr};        // row lengths of both forms
+    char* arena = nullptr;                          // the memory of all of it
+    void release();
+    DeviceForms() = default;
+    DeviceForms(const DeviceForms&) = delete;
+    ~DeviceForms() { release(); }
+};
+enum { DEVICE_BUILD_NO_MEMORY = 1 };                // (no error: the host builds)
+bool device_build_takes(int64_t n, int64_t n_edges, uint32_t flags);
+int build_device_forms(int64_t n, int64_t n_edges, const int32_t* src, const int32_t* dst, uint32_t flags, BuiltGraph* g, DeviceForms* out);
+
 // perm[p] (nnz entries, nnz < 2^31): where the edge at position p of the by-source form sits in
 // the by-destination form
 bool build_edge_perm(const BuiltGraph& G, int32_t* perm);       // false: out of host memory

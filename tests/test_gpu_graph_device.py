@@ -1,0 +1,83 @@
+"""Graphs built on the device against those that the host's threads build (NTP_HOST_ONLY): the same arrays bit for bit, for every combination of
+the flags, around the tile of 4,096 keys, the digit widths and the widths of a vertex id, with repeated edges, self loops and hubs."""
+import itertools
+
+import numpy as np
+import pytest
+
+import paper_2412_20379_amd as ntp
+
+pytestmark = pytest.mark.gpu
+
+FLAGS = [ntp.NTP_SYMMETRISE, ntp.NTP_DEDUP, ntp.NTP_ADD_SELF_LOOPS, ntp.NTP_NORM_GCN_SYM]
+
+
+def _edges(n, m, kind, seed):
+    rng = np.random.default_rng(seed)
+    if kind == "skewed":
+        return (n * rng.random(m) ** 4).astype(np.int32), (n * rng.random(m) ** 3).astype(np.int32)
+    src, dst = (rng.integers(0, n, m).astype(np.int32) for _ in range(2))
+    if kind == "hub":
+        dst[rng.random(m) < 0.5] = 7
+    if kind == "both ways":            # a directed edge list that is its own transpose
+        src, dst = np.concatenate([src, dst]), np.concatenate([dst, src])
+    return src, dst
+
+
+def _same(g, h, which):
+    for a, b in zip(ntp.ntp_graph_export(g, which), ntp.ntp_graph_export(h, which)):
+        assert a.dtype == b.dtype and np.array_equal(a.view(np.uint8), b.view(np.uint8))
+    cg, ch = ntp.ntp_graph_chunks(g, which), ntp.ntp_graph_chunks(h, which)
+    assert all(np.array_equal(cg[k], ch[k]) for k in cg if k != "resident") and cg["resident"].all()
+
+
+# 24,576 edges are the fewest that the device takes; 2 vertices: one bit an id; 65,536 and 65,537: 16 and 17 bits; many vertices: rows without entries
+@pytest.mark.parametrize("n,m,kind", [(2, 24576, "even"), (300, 70001, "even"), (5000, 40960, "hub"), (65536, 24577, "even"), (65537, 90000, "skewed"),
+                                      (700001, 24576, "even"), (20000, 30000, "both ways")])
+def test_device_build_gives_the_host_builds_arrays(n, m, kind):
+    src, dst = _edges(n, m, kind, n + m)
+    for used in itertools.product([0, 1], repeat=4):
+        flags = sum(f for f, u in zip(FLAGS, used) if u)
+        for more, chunk in ((0, 0), (ntp.NTP_SCATTER_BWD, 0), (0, 20000)):
+            g = ntp.ntp_graph_build(n, src, dst, flags=flags | more, chunk_edges=chunk)
+            h = ntp.ntp_graph_build(n, src, dst, flags=flags | more | ntp.NTP_HOST_ONLY, chunk_edges=chunk)
+            info = ntp.ntp_graph_info(g)
+            assert info == ntp.ntp_graph_info(h)
+            _same(g, h, ntp.NTP_CSR)
+            if not more or info["is_symmetric"]:
+                _same(g, h, ntp.NTP_CSC)
+            g.close()
+            h.close()
+
+
+def test_device_build_refuses_ids_outside_the_graph():
+    n = 5000
+    src, dst = _edges(n, 40000, "even", 1)
+    for where, bad in ((src, n), (dst, -1), (src, np.iinfo(np.int32).min)):
+        good, where[31234] = where[31234], bad
+        with pytest.raises(Exception, match="edge 31234 has a vertex id outside"):
+            ntp.ntp_graph_build(n, src, dst)
+        where[31234] = good
+    ntp.ntp_graph_build(n, src, dst).close()
+
+
+def test_export_while_a_stream_is_captured():
+    import torch
+    src, dst = _edges(3000, 30000, "even", 2)
+    g = ntp.ntp_graph_build(3000, src, dst)
+    want = ntp.ntp_graph_export(g, ntp.NTP_CSR)
+    x, y = torch.randn(3000, 32, device="cuda:0"), torch.empty(3000, 32, device="cuda:0")
+    ntp.ntp_aggregate_fwd(g, x, y, 32, 32, 32)
+    torch.cuda.synchronize()
+    eager = y.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ntp.ntp_aggregate_fwd(g, x, y, 32, 32, 32, ntp.NTP_F32, torch.cuda.current_stream())
+        got = ntp.ntp_graph_export(g, ntp.NTP_CSR)
+    assert all(np.array_equal(a, b) for a, b in zip(got, want))
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, eager)
+    g.close()
