@@ -15,9 +15,11 @@
 // values are the stored ones bit for bit.  A block finds the rows of its 4096 entries in a copy of their row pointers in
 // LDS (4 M entries of a 306,128-vertex graph: 0.071 -> 0.037 ms).
 //
-// Column ids travel packed: a vertex id of a graph of 306,128 vertices takes 19 of 32 bits, and the link is what a cold pass
-// waits for (15.8 M entries in four chunks, forward and backward: 2.62 -> 1.70 ms).  The unpacking kernel is bound by memory (8 us
-// for 4 M ids).
+// Column ids travel packed, as the link is what a cold pass waits for: 15.8 M entries of 306,128 vertices in four chunks, forward and
+// backward, 2.62 ms as they are, 1.70 in the 19 bits of a vertex id, 1.24 as Elias-Fano parts of the ascending rows (12.7 bits: a row of d
+// neighbours among n vertices needs log2(n / d) + 1.5 bits an id at least, and many entries are in long rows).  Blocks of 256 entries, by entries and not by rows: each its
+// own number of low bits, so that hubs and short rows both come out near what they need, and a wavefront a block (of 128, 512 and 1,024 entries 12.8, 12.9 and
+// 13.2 bits).  The unpacking kernel takes 15.5 us for 4 M ids, 8 in plain bits; its chain of loads bounds it, and it runs beside the next copy.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -83,21 +85,69 @@ __global__ void __launch_bounds__(256) rebuild_weights_kernel(const int64_t* __r
     }
 }
 
-// four ids a thread
-__global__ void __launch_bounds__(256) unpack_ids_kernel(const uint32_t* __restrict__ packed, int bits, int64_t n, int32_t* __restrict__ ids) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n) return;
-    int32_t v[4];
+// A wavefront a block of PACK_BLOCK entries, four a lane.  The ones of the bit string are found 16 places a lane, behind a scan over the words'
+// counts, and leave their entry's high part in LDS; nothing is waited for but the block's own words.
+__global__ void __launch_bounds__(256) unpack_ids_kernel(const uint32_t* __restrict__ packed, int bits, int64_t n_cols, double per_col, int64_t n,
+                                                         int32_t* __restrict__ ids) {
+    static_assert(PACK_BLOCK == 256, "four entries a lane");
+    __shared__ __align__(8) uint16_t high_lds[4][PACK_BLOCK];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t block = (int64_t)blockIdx.x * 4 + wave;
+    if (block * PACK_BLOCK >= n) return;
+    const int len = (int)std::min<int64_t>(PACK_BLOCK, n - block * PACK_BLOCK);
+    const uint32_t begin = packed[block], end = packed[block + 1];
+    const uint32_t* w = packed + begin;
+    const uint32_t first = w[0];
+    const int l = (int)w[1];
+    w += 2;
+    const bool plain = l == PACK_PLAIN;
+    const int lb = plain ? bits : l;
+    const int n_low = (len * lb + 31) / 32, n_high = (int)(end - begin) - 2 - n_low;      // n_high <= (len + 2 len + 1 + 31) / 32 < 32
+    const uint32_t* low = w + n_high;
+    const int i0 = lane * 4;
+    uint32_t v[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int64_t at = std::min(i + q, n - 1) * bits;
-        const uint64_t two = (uint64_t)packed[at >> 5] | (uint64_t)packed[(at >> 5) + 1] << 32;
-        v[q] = (int32_t)((uint32_t)(two >> (at & 31)) & ((1u << bits) - 1));
+        const int at = std::min(i0 + q, len - 1) * lb;
+        const uint64_t two = (uint64_t)low[at >> 5] | (uint64_t)low[(at >> 5) + 1] << 32;
+        v[q] = (uint32_t)(two >> (at & 31)) & ((1u << lb) - 1);
     }
-    if (i + 4 <= n) __builtin_memcpy(ids + i, v, 16);
+    if (!plain) {
+        uint16_t* const high = high_lds[wave];
+        const uint32_t word = lane < n_high ? w[lane] : 0u;
+        int before = __popc(word);                        // ones up to this word's end, then up to its start
+        for (int d = 1; d < 32; d *= 2) {
+            const int x = __shfl_up(before, d);
+            before += lane >= d ? x : 0;
+        }
+        before -= __popc(word);
+        const uint32_t mine = __shfl(word, lane / 2);
+        int rank = __shfl(before, lane / 2);
+        uint32_t ones = mine;
+        if (lane & 1) { rank += __popc(mine & 0xffffu); ones &= 0xffff0000u; }
+        else ones &= 0xffffu;
+        while (ones) {
+            const int at = (lane / 2) * 32 + __ffs(ones) - 1;
+            if (rank < PACK_BLOCK) high[rank] = (uint16_t)(at - rank);
+            ++rank;
+            ones &= ones - 1;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // the lanes read what other lanes wrote (in order in the hardware)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t z = ((int64_t)high[i0 + q] << l) + v[q] + first;       // less than (PACK_BLOCK + 1) * n_cols
+            int64_t id = z - (int64_t)((double)z * per_col) * n_cols;            // the quotient to within one
+            id += id < 0 ? n_cols : 0;
+            id -= id >= n_cols ? n_cols : 0;
+            v[q] = (uint32_t)id;
+        }
+    }
+    int32_t* const out = ids + block * PACK_BLOCK + i0;
+    if (i0 + 4 <= len) __builtin_memcpy(out, v, 16);
     else
+#pragma unroll
         for (int q = 0; q < 3; ++q)
-            if (i + q < n) ids[i + q] = v[q];
+            if (i0 + q < len) out[q] = (int32_t)v[q];
 }
 
 // up to three pieces; source and destination of a piece have the same address modulo 16
@@ -139,9 +189,11 @@ int launch_stage_chunk(const void* const src[3], void* const dst[3], const int64
     return NTP_OK;
 }
 
-int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n, int32_t* ids, void* stream) {
+int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n_cols, int64_t n, int32_t* ids, void* stream) {
     if (n <= 0) return NTP_OK;
-    hipLaunchKernelGGL(unpack_ids_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, (hipStream_t)stream, packed, bits, n, ids);
+    const int64_t blocks = (n + PACK_BLOCK - 1) / PACK_BLOCK;
+    hipLaunchKernelGGL(unpack_ids_kernel, dim3((unsigned)((blocks + 3) / 4)), dim3(256), 0, (hipStream_t)stream, packed, bits, n_cols,
+                       1.0 / (double)std::max<int64_t>(1, n_cols), n, ids);
     if (hipGetLastError() != hipSuccess) { set_error("column id kernel launch failed"); return NTP_EHIP; }
     return NTP_OK;
 }

@@ -11,6 +11,8 @@
 #include <cstring>
 #include <vector>
 
+#include <algorithm>
+
 #include "chunk_schedule.h"
 #include "ntp_internal.h"
 #include "row_copies.h"
@@ -443,23 +445,64 @@ static void check_packs_ids() {
     CHECK(pick_chunk_edges({n, 0, 0, 1, false, false}, 8000000) == 0 && pick_chunk_edges({n, 65000000, 0, 1, false, false}, 8000000) == 0, "one chunk where everything fits");
 }
 
-// column ids of every width, also where several threads share the words
+// packed column ids against a reader of one entry at a time: rows of every length (none, long ones), repeated ids, blocks as they are and in
+// parts, chunks that begin and end inside rows, several threads
 static void check_pack_ids() {
     Lcg rng{99};
+    int64_t plain = 0, parts = 0;
     for (int bits = 1; bits <= 28; ++bits)
-        for (int64_t n : {(int64_t)1, (int64_t)2, (int64_t)31, (int64_t)33, (int64_t)1000, (int64_t)300007}) {
-            std::vector<int32_t> ids((size_t)n);
-            for (auto& x : ids) x = (int32_t)(rng.next() & ((1u << bits) - 1));
-            std::vector<uint32_t> packed((size_t)packed_words(n, bits), 0xffffffffu);
-            pack_ids(ids.data(), n, bits, packed.data());
-            int64_t wrong = 0;
-            for (int64_t k = 0; k < n; ++k) {
-                const int64_t at = k * bits;
-                const uint64_t two = (uint64_t)packed[(size_t)(at >> 5)] | (uint64_t)packed[(size_t)(at >> 5) + 1] << 32;
-                wrong += (int32_t)((uint32_t)(two >> (at & 31)) & ((1u << bits) - 1)) != ids[(size_t)k];
+        for (int64_t nnz : {(int64_t)1, (int64_t)2, (int64_t)48, (int64_t)60, (int64_t)255, (int64_t)257, (int64_t)1000, (int64_t)300007}) {
+            const int64_t n = ((int64_t)1 << bits) - (bits > 2 ? 1 : 0), rows = std::min<int64_t>(n, 5000);
+            HostSparse m;
+            m.n = n;
+            m.nnz = nnz;
+            m.rowptr.assign((size_t)rows + 1, 0);
+            for (int64_t i = 0; i < nnz; ++i) {
+                const int64_t r = (int64_t)(rng.next() % (uint64_t)rows);
+                ++m.rowptr[(size_t)(rng.next() % 3 == 0 ? r * r / rows : r % std::max<int64_t>(1, rows / 50)) + 1];
             }
-            CHECK(wrong == 0, "%" PRId64 " of %" PRId64 " ids of %d bits", wrong, n, bits);
+            for (int64_t r = 0; r < rows; ++r) m.rowptr[(size_t)r + 1] += m.rowptr[(size_t)r];
+            std::vector<int32_t> ids((size_t)nnz);
+            for (int64_t r = 0; r < rows; ++r) {
+                const int64_t span = rng.next() % 2 ? n : std::max<int64_t>(1, n >> 4);
+                for (int64_t e = m.rowptr[(size_t)r]; e < m.rowptr[(size_t)r + 1]; ++e) ids[(size_t)e] = (int32_t)(rng.next() % (uint64_t)span);
+                std::sort(ids.begin() + m.rowptr[(size_t)r], ids.begin() + m.rowptr[(size_t)r + 1]);
+                if (m.rowptr[(size_t)r + 1] > m.rowptr[(size_t)r] && r % 7 == 0) ids[(size_t)m.rowptr[(size_t)r + 1] - 1] = (int32_t)(n - 1);
+            }
+            m.colidx = ids.data();
+            for (int64_t e_begin : {(int64_t)0, nnz / 3}) {
+                const int64_t e_end = e_begin == 0 ? nnz : nnz - nnz / 5, count = e_end - e_begin;
+                std::vector<uint32_t> offsets;
+                const int64_t words = plan_packed_ids(m, e_begin, e_end, bits, &offsets);
+                for (int64_t shift : {0, 4, 8, 12})       // the weights' part of a chunk's image takes them
+                    CHECK(shift + words * 4 <= (shift + count * 4 + 255) / 256 * 256, "%" PRId64 " words for %" PRId64 " ids", words, count);
+                CHECK(words <= (count * bits + 31) / 32 + 4 * ((count + 255) / 256) + 3, "%" PRId64 " words for %" PRId64 " ids of %d bits", words, count, bits);
+                std::vector<uint32_t> packed((size_t)words, 0xffffffffu);
+                pack_ids(m, e_begin, e_end, bits, offsets, packed.data());
+                int64_t wrong = 0;
+                for (int64_t b = 0; b * PACK_BLOCK < count; ++b) {
+                    const int64_t len = std::min<int64_t>(PACK_BLOCK, count - b * PACK_BLOCK);
+                    const uint32_t* w = packed.data() + packed[(size_t)b] + 2;
+                    const int l = (int)w[-1], lb = l == PACK_PLAIN ? bits : l;
+                    const int64_t low_words = (len * lb + 31) / 32, high_words = (int64_t)packed[(size_t)b + 1] - packed[(size_t)b] - 2 - low_words;
+                    (l == PACK_PLAIN ? plain : parts) += 1;
+                    CHECK(high_words >= 0 && high_words < 32 && packed[(size_t)b + 1] < words, "block %" PRId64 ": %" PRId64 " words of high parts", b, high_words);
+                    for (int64_t i = 0, at = 0; i < len; ++i, ++at) {
+                        const int64_t p = i * lb;
+                        const uint32_t* low = w + high_words + (p >> 5);
+                        const uint64_t two = (uint64_t)low[0] | (uint64_t)low[1] << 32;
+                        int64_t id = (int64_t)((uint32_t)(two >> (p & 31)) & (uint32_t)(((uint64_t)1 << lb) - 1));
+                        if (l != PACK_PLAIN) {
+                            while (at < high_words * 32 && !(w[at >> 5] >> (at & 31) & 1)) ++at;
+                            id = (((at - i) << l) + id + (int64_t)w[-2]) % n;
+                        }
+                        wrong += id != ids[(size_t)(e_begin + b * PACK_BLOCK + i)];
+                    }
+                }
+                CHECK(wrong == 0, "%" PRId64 " of %" PRId64 " ids of %d bits", wrong, count, bits);
+            }
         }
+    CHECK(plain > 1000 && parts > 1000, "blocks %" PRId64 " as they are, %" PRId64 " in parts", plain, parts);
 }
 
 int main() {

@@ -233,25 +233,31 @@ int64_t streamed_bytes(const Chunk& c, bool with_val) {
     return (int64_t)c.meta.size() + (c.h_packed_ids ? c.packed_id_bytes : (c.e_end - c.e_begin) * (with_val ? 8 : 4));
 }
 
-// Column ids of the streamed chunks in as few bits as hold a vertex id (packs_ids)
+// Packed column ids of the streamed chunks (packs_ids)
 int pack_streamed_ids(ntp_graph* G, int n_forms) {
     int64_t bytes = 0;
+    std::vector<std::vector<uint32_t>> offsets;
     auto each = [&](auto&& f) {
         for (int k = 0; k < n_forms; ++k)
             for (auto& c : G->form[k].plan.chunks)
                 if (!c.d_image && c.e_end > c.e_begin) f(*G->form[k].m, c);
     };
     // like the arrays, packed ids keep their place modulo 16 (16-byte copies)
-    each([&](const HostSparse&, Chunk& c) { c.packed_id_bytes = packed_words(c.e_end - c.e_begin, G->id_bits) * 4; bytes += (c.packed_id_bytes + 31) / 16 * 16; });
+    each([&](const HostSparse& m, Chunk& c) {
+        offsets.emplace_back();
+        c.packed_id_bytes = plan_packed_ids(m, c.e_begin, c.e_end, G->id_bits, &offsets.back()) * 4;
+        bytes += (c.packed_id_bytes + 31) / 16 * 16;
+    });
     if (bytes == 0) return NTP_OK;
     void* p = nullptr;
     if (hipHostMalloc(&p, (size_t)bytes, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); set_error("pinned allocation of %lld bytes failed", (long long)bytes); return NTP_ENOMEM; }
     G->pinned_ids = (char*)p;
     int64_t off = 0;
+    size_t k = 0;
     each([&](const HostSparse& m, Chunk& c) {
         c.h_packed_ids = G->pinned_ids + off + c.img_off_val % 16;
         off += (c.packed_id_bytes + 31) / 16 * 16;
-        pack_ids(m.colidx + c.e_begin, c.e_end - c.e_begin, G->id_bits, reinterpret_cast<uint32_t*>(c.h_packed_ids));
+        pack_ids(m, c.e_begin, c.e_end, G->id_bits, offsets[k++], reinterpret_cast<uint32_t*>(c.h_packed_ids));
     });
     return NTP_OK;
 }
@@ -579,7 +585,7 @@ int HipPass::copy_by_kernel(const Chunk& c, int b, hipStream_t s, bool entries) 
 int HipPass::aggregate(const Chunk& c, int b) {
     char* img = g->stage[b];
     if (c.h_packed_ids) {
-        const int rc = launch_unpack_ids(reinterpret_cast<const uint32_t*>(img + c.img_off_val), g->id_bits, c.e_end - c.e_begin,
+        const int rc = launch_unpack_ids(reinterpret_cast<const uint32_t*>(img + c.img_off_val), g->id_bits, g->g.n, c.e_end - c.e_begin,
                                          reinterpret_cast<int32_t*>(img + c.img_off_colidx), cs);
         if (rc != NTP_OK) return rc;
     }

@@ -165,8 +165,8 @@ struct Chunk {
     char* d_copies = nullptr;                  // second copies of a resident chunk (nullptr: none)
     RowCopies copies;
     char* h_meta_pinned = nullptr;             // pinned copy of meta for streaming
-    char* h_packed_ids = nullptr;              // pinned: the column ids in as few bits as hold a vertex id (nullptr: they travel as
-    int64_t packed_id_bytes = 0;               // they are); goes where the weights are rebuilt afterwards, unpacked from there
+    char* h_packed_ids = nullptr;              // pinned: the column ids packed (nullptr: they travel as they are); goes where the weights
+    int64_t packed_id_bytes = 0;               // are rebuilt afterwards, unpacked from there
 };
 
 struct Plan {
@@ -380,10 +380,14 @@ int launch_attention_scores_bwd(const float* Z, const float* a_src, const float*
 // agree modulo 16
 int launch_stage_chunk(const void* const src[3], void* const dst[3], const int64_t bytes[3], void* stream);
 
-// Column ids of `bits` bits each, one after the other from the lowest bit of packed[0] on (which is followed by one spare word)
-void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed);
-inline int64_t packed_words(int64_t n, int bits) { return (n * bits + 31) / 32 + 1; }
-int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n, int32_t* ids, void* stream);
+// The column ids of the entries [e_begin, e_end) of a form, packed: blocks of PACK_BLOCK entries, offset (in words) of each and of the end in front.
+// A block: the first entry's id; l; then for l < PACK_PLAIN the ascending sequence z (plan.cpp) as Elias-Fano parts: entry i's high part z >> l as a
+// one at place (z >> l) + i of a bit string, in whole words; its l low bits, one entry after the other from a whole word on.  PACK_PLAIN: the ids, `bits`
+// bits each.  Two spare words follow the last block.
+constexpr int PACK_BLOCK = 256, PACK_PLAIN = 32;
+int64_t plan_packed_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, std::vector<uint32_t>* offsets);      // words in all
+void pack_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, const std::vector<uint32_t>& offsets, uint32_t* packed);
+int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n_cols, int64_t n, int32_t* ids, void* stream);
 
 // val[e] of a chunk's entries from the structure (VAL_GCN / VAL_ONES): rowptr is the chunk's slice
 // (global entry offsets), colidx / val its entry arrays, deg_row / deg_col indexed by vertex id

@@ -163,8 +163,9 @@ int64_t pick_chunk_edges(const StreamRequest& r, int64_t nnz) {
 
 int bits_of_ids(int64_t n) { return n <= 2 ? 1 : 64 - __builtin_clzll((unsigned long long)(n - 1)); }
 
-// Packed ids are a half to seven eighths of the bytes on the link and cost a kernel a chunk (8 us for 4 M ids); they go where the weights are
-// rebuilt afterwards, where ids of up to 28 bits and a spare word fit.  us a pass (both directions) as they are / packed:
+// Packed ids are a third to seven eighths of the bytes on the link and cost a kernel a chunk (15 us for 4 M ids); they go where the weights are
+// rebuilt afterwards, where ids of up to 28 bits and what a block has in front fit.  us a pass (both directions) as they are / packed, measured with every id in
+// the bits of a vertex id, which is the most that a block takes; 15.8 M entries of 306,128 vertices take 12.7 bits of 19:
 //   chunks of 4 M entries, F = 32: 19 bits 2620 / 1704, 22 2612 / 2062, 24 2582 / 2233, 26 2607 / 2359, 28 2619 / 2462; of 1 M, F = 32 (F = 76): 20 bits
 //   2899 / 2400 (3509 / 3288), 24 2909 / 2543 (3519 / 3529), 28 2889 / 2709 (3554 / 3586); of 0.66 M, F = 32 (F = 128): 20 bits 3526 / 3019
 //   (4518 / 4563), 28 3517 / 3227 (4467 / 4589), 16 bits 1220 / 980.
@@ -179,26 +180,116 @@ bool packs_ids(const StreamRequest& r, int64_t nnz) {
     return (ce > 0 ? std::min(ce, nnz) : nnz) >= 5 << 17;
 }
 
-void pack_ids(const int32_t* ids, int64_t n, int bits, uint32_t* packed) {
-    const int64_t words = packed_words(n, bits);
-    const int T = std::max(1, std::min(host_threads(), (int)std::min<int64_t>(64, n / (1 << 16) + 1)));
-    parallel_for_threads(T, [&](int t, int nt) {        // a thread writes whole words: the ids that reach into them
-        const int64_t w0 = words * t / nt, w1 = words * (t + 1) / nt;
-        int64_t k = w0 * 32 / bits;
-        uint64_t buf = 0;
-        int have = 0;                                   // bits of buf that belong to word w on
-        int64_t skip = w0 * 32 - k * bits;              // leading bits of id k that belong to the word before
-        for (int64_t w = w0; w < w1; ++w) {
-            while (have < 32 && k < n) {
-                buf |= ((uint64_t)(uint32_t)ids[k] >> skip) << have;
-                have += bits - (int)skip;
-                skip = 0;
-                ++k;
-            }
-            packed[w] = (uint32_t)buf;
-            buf >>= 32;
-            have = std::max(0, have - 32);
+namespace {
+
+// Blocks of PACK_BLOCK entries of a chunk, in order.  A block's sequence z, ascending because the rows are: the column id plus n for every row that
+// has begun since the block's first entry, less that entry's id.
+struct PackBlocks {
+    const HostSparse& m;
+    int64_t e_begin, e_end;
+    int bits;
+    int64_t count() const { return (e_end - e_begin + PACK_BLOCK - 1) / PACK_BLOCK; }
+    // f(block, entries, first entry, row of the first entry) for the blocks [b0, b1)
+    template <class F> void each(int64_t b0, int64_t b1, F&& f) const {
+        if (b0 >= b1) return;
+        int64_t r = std::upper_bound(m.rowptr.begin(), m.rowptr.end(), e_begin + b0 * PACK_BLOCK) - m.rowptr.begin() - 1;
+        for (int64_t b = b0; b < b1; ++b) {
+            const int64_t e = e_begin + b * PACK_BLOCK, len = std::min<int64_t>(PACK_BLOCK, e_end - e);
+            while (m.rowptr[(size_t)r + 1] <= e) ++r;
+            f(b, (int)len, e, r);
         }
+    }
+    int64_t last(int len, int64_t e, int64_t r) const {        // z of the block's last entry
+        int64_t z = (int64_t)m.colidx[e + len - 1] - m.colidx[e];
+        for (int64_t start = m.rowptr[(size_t)r + 1]; start < e + len; start = m.rowptr[(size_t)r + 1]) {
+            z += m.n;
+            do ++r; while (m.rowptr[(size_t)r + 1] <= start);
+        }
+        return z;
+    }
+    // Low bits that leave the fewest in all: one more costs an entry each and halves what the high parts take.  At least `bits` of them: the ids
+    // as they are take less.
+    int low_bits(int len, int64_t last) const {
+        int l = 0;
+        while ((last >> (l + 1)) > len) ++l;
+        return 2 + high_words(len, last, l) + low_words(len, l) < low_words(len, bits) ? l : PACK_PLAIN;
+    }
+    static int64_t high_words(int len, int64_t last, int l) { return (len + (last >> l) + 31) / 32; }
+    static int64_t low_words(int len, int l) { return ((int64_t)len * l + 31) / 32; }
+};
+
+// bits one value after the other into whole words
+struct BitWriter {
+    uint32_t* w;
+    uint64_t buf = 0;
+    int have = 0;
+    void put(uint32_t v, int bits) {                 // 0 < bits <= 28; a word is written again and again until it is full: no branch to be guessed
+        buf |= (uint64_t)v << have;
+        have += bits;
+        *w = (uint32_t)buf;
+        w += have >> 5;
+        buf >>= have & 32;
+        have &= 31;
+    }
+    void end() { if (have > 0) *w = (uint32_t)buf; }
+};
+
+int pack_threads(int64_t blocks) { return std::max(1, std::min(host_threads(), (int)std::min<int64_t>(64, blocks / 256 + 1))); }
+
+}  // namespace
+
+int64_t plan_packed_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, std::vector<uint32_t>* offsets) {
+    const PackBlocks blocks{m, e_begin, e_end, bits};
+    const int64_t nb = blocks.count();
+    offsets->assign((size_t)nb + 1, 0);
+    parallel_for_threads(pack_threads(nb), [&](int t, int nt) {
+        blocks.each(nb * t / nt, nb * (t + 1) / nt, [&](int64_t b, int len, int64_t e, int64_t r) {
+            const int64_t last = blocks.last(len, e, r);
+            const int l = blocks.low_bits(len, last);
+            (*offsets)[(size_t)b + 1] = (uint32_t)(l == PACK_PLAIN ? 2 + blocks.low_words(len, bits) : 2 + blocks.high_words(len, last, l) + blocks.low_words(len, l));
+        });
+    });
+    uint32_t at = (uint32_t)nb + 1;
+    for (auto& o : *offsets) o = at += o;
+    return (int64_t)at + 2;
+}
+
+void pack_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, const std::vector<uint32_t>& offsets, uint32_t* packed) {
+    const PackBlocks blocks{m, e_begin, e_end, bits};
+    const int64_t nb = blocks.count();
+    std::copy(offsets.begin(), offsets.end(), packed);
+    packed[offsets.back()] = packed[offsets.back() + 1] = 0;
+    parallel_for_threads(pack_threads(nb), [&](int t, int nt) {        // a block is whole words of its own
+        blocks.each(nb * t / nt, nb * (t + 1) / nt, [&](int64_t b, int len, int64_t e, int64_t r) {
+            uint32_t* w = packed + offsets[(size_t)b];
+            const int32_t* const ids = m.colidx + e;
+            const int64_t last = blocks.last(len, e, r);
+            const int l = blocks.low_bits(len, last);
+            *w++ = (uint32_t)ids[0];
+            *w++ = (uint32_t)l;
+            if (l == PACK_PLAIN) {
+                BitWriter out{w};
+                for (int i = 0; i < len; ++i) out.put((uint32_t)ids[i], bits);
+                out.end();
+                return;
+            }
+            const int64_t high_words = blocks.high_words(len, last, l);
+            std::fill(w, w + high_words, 0u);
+            BitWriter low{w + high_words};
+            const uint32_t mask = ((uint32_t)1 << l) - 1;
+            int64_t base = -(int64_t)ids[0];
+            for (int i = 0;;) {                       // up to the end of the row
+                for (const int end = (int)std::min<int64_t>(len, m.rowptr[(size_t)r + 1] - e); i < end; ++i) {
+                    const int64_t z = base + ids[i], at = (z >> l) + i;
+                    w[at >> 5] |= 1u << (at & 31);
+                    if (l > 0) low.put((uint32_t)z & mask, l);
+                }
+                if (i == len) break;
+                base += m.n;
+                do ++r; while (m.rowptr[(size_t)r + 1] <= e + i);
+            }
+            low.end();
+        });
     });
 }
 

@@ -332,6 +332,31 @@ def test_packed_column_ids_equal_resident_ones(case):
     streamed.close()
 
 
+@pytest.mark.parametrize("n,m,hub,chunk", [(3_000_001, 900_000, 0, 700_001), (70_000, 1_400_001, 0, 655_361), (1_500_007, 1_500_000, 1_400_000, 660_000), (700, 1_500_000, 0, 655_617),
+                                           (1_000_003, 2_000_000, 300_000, 900_007)])
+def test_packed_blocks_of_every_kind(n, m, hub, chunk):
+    """ids as they are where most rows are empty or short, in parts where rows are long (no low bits where rows repeat every neighbour), rows over
+    several blocks and chunks, a last block and chunk of a few entries: the bits of the resident chunks"""
+    import torch
+    rng = gen.stream_rng(n, 7)
+    src, dst = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+    dst[:hub] = n // 2                                     # a row of `hub` entries
+    resident = ntp.ntp_graph_build(n, src, dst, flags=0, chunk_edges=chunk)
+    streamed = ntp.ntp_graph_build(n, src, dst, flags=ntp.NTP_FORCE_STREAM, chunk_edges=chunk)
+    say("packed blocks", n, m, "hub", hub, "chunks", len(ntp.ntp_graph_chunks(streamed)["resident"]), "bytes a pass", ntp.ntp_graph_stream_bytes(streamed))
+    x = torch.randn(n, 4, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(3))
+    cs, cp = torch.cuda.Stream(), torch.cuda.Stream()
+    for direction in (ntp.NTP_FWD, ntp.NTP_BWD):
+        a, b = torch.full_like(x, 3), torch.full_like(x, 5)
+        torch.cuda.synchronize()
+        ntp.ntp_chunked_aggregate(resident, direction, x, a, 4, 4, 4, ntp.NTP_F32, cs, cp)
+        ntp.ntp_chunked_aggregate(streamed, direction, x, b, 4, 4, 4, ntp.NTP_F32, cs, cp)
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
+    resident.close()
+    streamed.close()
+
+
 @pytest.mark.parametrize("n_edges,chunk,budget,forms,packed", [(700_000, 655_360, 0, 2, True), (700_000, 655_359, 0, 2, False), (1_320_000, 0, 0, 2, True), (1_300_000, 0, 0, 2, False),
                                                               (660_000, 0, 0, 1, True), (700_000, 0, 0, 0, False), (3_000_000, 0, 52_500_000, 2, True), (3_000_000, 0, 52_000_000, 2, False)])
 def test_ids_are_packed_by_the_chunks_that_are_cut(n_edges, chunk, budget, forms, packed):
