@@ -16,7 +16,7 @@
 // LDS (4 M entries of a 306,128-vertex graph: 0.071 -> 0.037 ms).
 //
 // Column ids travel packed, as the link is what a cold pass waits for: 15.8 M entries of 306,128 vertices in four chunks, forward and
-// backward, 2.62 ms as they are, 1.70 in the 19 bits of a vertex id, 1.24 as Elias-Fano parts of the ascending rows (12.7 bits: a row of d
+// backward, 2.62 ms as they are, 1.70 in the 19 bits of a vertex id, 1.25 as Elias-Fano parts of the ascending rows (12.7 bits: a row of d
 // neighbours among n vertices needs log2(n / d) + 1.5 bits an id at least, and many entries are in long rows).  Blocks of 256 entries, by entries and not by rows: each its
 // own number of low bits, so that hubs and short rows both come out near what they need, and a wavefront a block (of 128, 512 and 1,024 entries 12.8, 12.9 and
 // 13.2 bits).  The unpacking kernel takes 15.5 us for 4 M ids, 8 in plain bits; its chain of loads bounds it, and it runs beside the next copy.

@@ -2,7 +2,9 @@
 // what holds when a pass ends early.  Host logic only; the streams, the copies and the kernels are those of Ops
 // (ntp_api.hip: HIP; host_check.cpp: a recorder that checks every access to a staging buffer against the order).
 //
-// Two staging buffers alternate.  Whoever writes a buffer waits for its readers (event free_), the readers wait for the
+// Staging buffers take turns: two that hold a chunk's arrays as the kernels read them, or, where ids travel packed, up to MAX_BUFFERS that hold what
+// came over the link (row pointers, lists, packed ids), with one place for the unpacked entries, which belongs to the compute stream alone.
+// Whoever writes a buffer waits for its readers (event free_), the readers wait for the
 // copy (event ready).  At the end of a pass, completed or not, every buffer that it touched has its free_ event recorded
 // behind all copies into it and all kernels on it, and the caller's copy stream stands behind the second one: the next
 // pass may come on other streams.
@@ -18,6 +20,7 @@ struct CopyPath {
     bool two_streams;       // the buffers have a copy stream each: the 20-60 us it takes to start a copy pass while the other
                             // one is on the link; else the caller's copy stream takes all copies, one after the other
     bool meta_on_compute;   // row pointers and lists by a kernel on the compute stream, else by one behind the entries
+    bool whole = false;     // row pointers, lists and packed ids lie side by side: one copy takes them all
 };
 
 // The path for a pass whose streamed chunks have, on average, `bytes` to copy and `entries` entries to aggregate into n_rhs
@@ -34,27 +37,32 @@ struct CopyPath {
 //   The row pointers and lists (a fifth of the bytes at 15 entries a row) are copied on the compute stream until the
 //   aggregation cannot spare the time (0.7 of the copy).  On the compute / copy stream: 4 chunks of 4 M entries F = 32 1268 / 1314,
 //   F = 256 1511 / 1438, 8 x 32 columns 1852 / 1762; 11 of 0.4 M F = 32 669 / 682, F = 128 862 / 803, F = 256 1096 / 1016.
-//   Packed ids (`packed`) are a half to seven eighths of the bytes, and kernels that unpack them and rebuild the weights stand before the
-//   aggregation: by these bounds two copies at a time and row pointers on the compute stream would hold up a pass that the aggregation
-//   already bounds.  From three lines a row on: one copy at a time, the row pointers behind it.  us for both directions, ids as they are /
-//   packed by these bounds / packed and so: 4 chunks of 4 M entries of 306,128 vertices F = 76 2840 / 2819 / 2448, F = 128 3019 / 3049 / 2852,
-//   of 200,000 F = 160 3175 / 3460 / 3198; 16 of 1 M of 1 M vertices F = 76 4045 / 4004 / 3504; 23 of 0.7 M of 306,128 F = 128 4373 / 4498 /
-//   4372.  Fewer lines stay with the bounds: 4 of 4 M of 306,128 F = 32 2769 / 1789 / 1948, of 200,000 F = 64 2869 / 1815 / 1940.
+//   Packed ids (`packed`) come with their row pointers and lists in one copy, one copy at a time: the buffers that it goes to hold nothing else, so
+//   there are more of them than two and copies run ahead of the kernels.  us for both directions, two images with the row pointers copied by a kernel and two
+//   copy streams while the link is the bound / these buffers with two copy streams / with one: 15.8 M entries of 306,128 vertices, chunks of 4 M F = 32
+//   1291 / 1300 / 1263, F = 76 1474 / 1625 / 1478, F = 128 1766 / 2360 / 1773; of 1 M F = 32 3062 / 2793 / 1904, F = 76 2460 / 2528 / 2460; of 0.66 M
+//   F = 32 3984 / 3701 / 2556; 15 M entries of 1 M vertices in chunks of 2 M F = 32 3181 / 2722 / 2024, F = 128 3582 / 3733 / 3599; 5.1 M of 70,000 in
+//   chunks of 1.3 M F = 16 764 / 658 / 508.  By a kernel of 16 blocks on the copy stream instead of by DMA 1555 (chunks of 4 M), 2470 (1 M): what runs
+//   beside it waits behind its loads.
 inline CopyPath pick_copy_path(double bytes, double largest, double entries, int64_t lines, int n_rhs, bool packed = false) {
     const double copy_us = bytes / 56e3, aggregate_us = n_rhs * (10.0 + entries * (double)lines * 1e-5);
     CopyPath p;
     p.dma = largest > 768 * 1024;
     p.two_streams = p.dma && (aggregate_us < 0.4 * copy_us || copy_us < 200);
     p.meta_on_compute = !p.dma || aggregate_us <= 0.7 * copy_us;
-    if (packed && p.dma && n_rhs * lines > 2) p.two_streams = p.meta_on_compute = false;
+    p.whole = packed;
+    if (packed && p.dma) p.two_streams = p.meta_on_compute = false;
     return p;
 }
 
+constexpr int MAX_BUFFERS = 4;
+
 template <class Ops> struct StageState {
-    typename Ops::Event ready[2] = {}, free_[2] = {}, join[2] = {};
-    typename Ops::Stream copy2 = {};        // buffer 1's copy stream where there are two (buffer 0's is the caller's)
-    bool used[2] = {false, false};          // free_ has been recorded
-    int next = 0;
+    typename Ops::Event ready[MAX_BUFFERS] = {}, free_[MAX_BUFFERS] = {}, join[2] = {};
+    typename Ops::Stream copy2 = {};        // every other copy's stream where there are two (the others': the caller's)
+    bool used[MAX_BUFFERS] = {};            // free_ has been recorded
+    int buffers = 2, next = 0, turn = 0;
+    int last = -1;                          // the buffer whose kernels used the unpacked entries last
 };
 
 // Calls of Ops (0: done, else a status that ends the pass):
@@ -80,33 +88,40 @@ public:
     }
     template <class Chunk> int streamed(const Chunk& c) {
         const int b = st_.next;
-        st_.next ^= 1;
-        const Stream ks = path_.dma ? copy_stream(b) : cs_;
+        st_.next = (b + 1) % st_.buffers;
+        st_.turn ^= 1;
+        const Stream ks = on_[b] = !path_.dma ? cs_ : st_.turn == 0 && path_.two_streams ? st_.copy2 : xs_;
         int rc = 0;
         // the buffer may still be read by the kernels of the chunk that used it last (of an earlier pass: on any stream)
         if (st_.used[b] && !touched_[b]) rc = ops_.wait(cs_, st_.free_[b]);
         if (rc == 0 && st_.used[b] && path_.dma) rc = ops_.wait(ks, st_.free_[b]);
+        if (rc == 0 && path_.whole && !entered_) {       // the unpacked entries: kernels of an earlier pass, on any stream
+            if (st_.last >= 0 && st_.used[st_.last]) rc = ops_.wait(cs_, st_.free_[st_.last]);
+            entered_ = rc == 0;
+        }
         if (rc != 0) return rc;
         touched_[b] = held_[b] = true;
         if (path_.dma) {
             copying_[b] = true;
             rc = ops_.copy_entries(c, b, ks);
-            if (rc == 0 && !path_.meta_on_compute) rc = ops_.copy_by_kernel(c, b, ks, false);
+            if (rc == 0 && !path_.meta_on_compute && !path_.whole) rc = ops_.copy_by_kernel(c, b, ks, false);
             if (rc == 0) rc = ops_.record(st_.ready[b], ks);
         }
-        if (rc == 0 && path_.meta_on_compute) rc = ops_.copy_by_kernel(c, b, cs_, !path_.dma);
+        if (rc == 0 && path_.meta_on_compute && !(path_.whole && path_.dma)) rc = ops_.copy_by_kernel(c, b, cs_, !path_.dma);
         if (rc == 0 && path_.dma) {
             rc = ops_.wait(cs_, st_.ready[b]);
             if (rc == 0) copying_[b] = false;
         }
-        if (rc == 0) rc = ops_.aggregate(c, b);
+        if (rc == 0) {
+            st_.last = b;
+            rc = ops_.aggregate(c, b);
+        }
         if (rc != 0 || !path_.dma) return rc;
         return release(b);
     }
     int end() { return close(); }
 
 private:
-    Stream copy_stream(int b) const { return b == 1 && path_.two_streams ? st_.copy2 : xs_; }
     int release(int b) {
         const int rc = ops_.record(st_.free_[b], cs_);
         if (rc == 0) { st_.used[b] = true; held_[b] = false; }
@@ -117,8 +132,8 @@ private:
         open_ = false;
         int rc = 0;
         auto also = [&](int r) { if (rc == 0) rc = r; return r == 0; };
-        for (int b = 0; b < 2; ++b) {
-            if (copying_[b] && also(ops_.record(st_.ready[b], copy_stream(b)))) also(ops_.wait(cs_, st_.ready[b]));
+        for (int b = 0; b < MAX_BUFFERS; ++b) {
+            if (copying_[b] && also(ops_.record(st_.ready[b], on_[b]))) also(ops_.wait(cs_, st_.ready[b]));
             copying_[b] = false;
             if (held_[b]) also(release(b));
         }
@@ -132,10 +147,11 @@ private:
     StageState<Ops>& st_;
     const Stream cs_, xs_;
     const CopyPath path_;
-    bool open_ = false, forked_ = false;
-    bool touched_[2] = {false, false};      // the compute stream has waited for the buffer's earlier readers
-    bool copying_[2] = {false, false};      // a copy is enqueued that the compute stream does not wait for yet
-    bool held_[2] = {false, false};         // used since free_ was recorded last
+    bool open_ = false, forked_ = false, entered_ = false;
+    Stream on_[MAX_BUFFERS] = {};           // of the buffer's copy
+    bool touched_[MAX_BUFFERS] = {};        // the compute stream has waited for the buffer's earlier readers
+    bool copying_[MAX_BUFFERS] = {};        // a copy is enqueued that the compute stream does not wait for yet
+    bool held_[MAX_BUFFERS] = {};           // used since free_ was recorded last
 };
 
 }  // namespace ntp

@@ -331,8 +331,9 @@ struct Recorder {
     struct Event { int64_t at[STREAMS] = {0}; };
     int64_t clock[STREAMS][STREAMS] = {{0}};
     struct Access { int stream = -1; int64_t time = 0; };
-    struct Region { Access write, read; int holds = -1; } region[2][2];      // [buffer][0: entries, 1: row pointers and lists]
-    Access last_copy[STREAMS];
+    struct Region { Access write, read; int holds = -1; } region[MAX_BUFFERS][2];      // [buffer][0: entries, 1: row pointers and lists]
+    Access last_copy[STREAMS], unpacked;     // unpacked: the last use of the unpacked entries
+    bool whole = false;
     int compute = 0, fail_in = -1;           // fail_in: operations until one fails (negative: none does)
     const char* what = "";
 
@@ -358,7 +359,8 @@ struct Recorder {
     int copy_entries(int c, int b, int s) {
         if (fails()) return -1;
         write(c, b, 0, s);
-        last_copy[s] = region[b][0].write;
+        if (whole) write(c, b, 1, s);
+        last_copy[s] = Access{s, clock[s][s]};
         return 0;
     }
     int copy_by_kernel(int c, int b, int s, bool entries) {
@@ -369,6 +371,10 @@ struct Recorder {
         return 0;
     }
     int aggregate(int c, int b) {
+        if (whole) {
+            CHECK(before(unpacked, compute), "%s: chunk %d is unpacked while other entries are in use", what, c);
+            unpacked = tick(compute);
+        }
         if (fails()) return -1;
         for (int part = 0; part < 2; ++part) {
             Region& r = region[b][part];
@@ -382,11 +388,13 @@ struct Recorder {
 void check_schedule() {
     const int COPY2 = 7;
     const CopyPath paths[] = {{false, false, true}, {true, true, true}, {true, true, false}, {true, false, true}, {true, false, false}};
-    for (int first = 0; first < 5; ++first)
+    for (int first = 0; first < 20; ++first)               // five paths, two images or one to four buffers for packed chunks
         for (int fail = -1; fail < 60; ++fail) {
             Recorder ops;
             StageState<Recorder> state;
             state.copy2 = COPY2;
+            ops.whole = first >= 5;
+            state.buffers = first < 5 ? 2 : first < 10 ? 4 : first < 15 ? 3 : 1 + fail % 2 * (fail > 0);
             Lcg rng{(uint64_t)(first * 1000 + fail + 2)};
             char what[64];
             snprintf(what, sizeof what, "path %d, failure at step %d", first, fail);
@@ -395,7 +403,8 @@ void check_schedule() {
             for (int pass = 0; pass < 6; ++pass) {
                 // every pass on compute and copy streams of its own choice, without a wait in between
                 const int cs = (int)(rng.next() % 3), xs = 3 + (int)(rng.next() % 3);
-                const CopyPath path = paths[pass == 0 ? first : (int)(rng.next() % 5)];
+                CopyPath path = paths[pass == 0 ? first % 5 : (int)(rng.next() % 5)];
+                path.whole = ops.whole;
                 ops.compute = cs;
                 for (auto& a : ops.last_copy) a = Recorder::Access();
                 ops.fail_in = pass == 0 ? fail : -1;
@@ -421,10 +430,11 @@ void check_schedule() {
     CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 8, 1), true, false, false), "4 M entries, F = 256: the aggregation");
     CHECK(is(pick_copy_path(17e6, 17e6, 4e6, 1, 8), true, false, false), "4 M entries, eight right-hand sides: the aggregation");
     CHECK(is(pick_copy_path(2e6, 2e6, 4e5, 8, 1), true, true, false), "0.4 M entries, F = 256: the aggregation, short copies");
-    CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 1, 1, true), true, true, true), "4 M packed entries, F = 32: the link");
+    CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 1, 1, true), true, false, false), "4 M packed entries, F = 32: one copy each");
     CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 3, 1, true), true, false, false), "4 M packed entries, F = 76: the aggregation");
     CHECK(is(pick_copy_path(10.4e6, 10.4e6, 4e6, 1, 4, true), true, false, false), "4 M packed entries, four right-hand sides: the aggregation");
     CHECK(is(pick_copy_path(700e3, 700e3, 3e5, 3, 1, true), false, false, true), "small packed chunk");
+    CHECK(pick_copy_path(700e3, 700e3, 3e5, 3, 1, true).whole && !pick_copy_path(17e6, 17e6, 4e6, 1, 1).whole, "packed ids with their row pointers");
 }
 
 }  // namespace

@@ -63,11 +63,12 @@ struct ntp_graph {
     bool pinned_entries = false;
     bool val_pinned = false;       // the weights are in pinned memory too (caller weights on a graph that may stream)
     // staging for streamed chunks
-    char* stage[2] = {nullptr, nullptr};
-    size_t stage_bytes = 0;
+    char* stage_memory = nullptr;                   // two images of the largest chunk, or, where ids travel packed, its entries and, behind them, the
+    char* stage[MAX_BUFFERS] = {};                  // staging buffers (row pointers, lists and packed ids of a chunk)
+    char* stage_entries = nullptr;
     StageState<HipPass> staged;                     // streams, events and the state of the two buffers
     char* pinned_meta = nullptr;                    // metas of streamed chunks
-    char* pinned_ids = nullptr;                     // packed column ids of streamed chunks
+    char* pinned_ids = nullptr;                     // row pointers, lists and packed column ids of streamed chunks
     int id_bits = 0;
     bool pack_ids = false;         // streamed chunks send packed column ids
     // partial sums of split rows
@@ -233,20 +234,24 @@ int64_t streamed_bytes(const Chunk& c, bool with_val) {
     return (int64_t)c.meta.size() + (c.h_packed_ids ? c.packed_id_bytes : (c.e_end - c.e_begin) * (with_val ? 8 : 4));
 }
 
-// Packed column ids of the streamed chunks (packs_ids)
-int pack_streamed_ids(ntp_graph* G, int n_forms) {
+// What the streamed chunks send where ids are packed (packs_ids): row pointers and lists, packed ids behind them.  The staging memory, two images, is
+// cut into the entries of the largest chunk and as many buffers for that as fit.
+int pack_streamed_ids(ntp_graph* G, int n_forms, size_t stage_bytes) {
     int64_t bytes = 0;
+    size_t most = 0, entries = 0;
     std::vector<std::vector<uint32_t>> offsets;
     auto each = [&](auto&& f) {
         for (int k = 0; k < n_forms; ++k)
             for (auto& c : G->form[k].plan.chunks)
-                if (!c.d_image && c.e_end > c.e_begin) f(*G->form[k].m, c);
+                if (!c.d_image) f(*G->form[k].m, c);
     };
-    // like the arrays, packed ids keep their place modulo 16 (16-byte copies)
     each([&](const HostSparse& m, Chunk& c) {
         offsets.emplace_back();
-        c.packed_id_bytes = plan_packed_ids(m, c.e_begin, c.e_end, G->id_bits, &offsets.back()) * 4;
-        bytes += (c.packed_id_bytes + 31) / 16 * 16;
+        if (c.e_end > c.e_begin) c.packed_id_bytes = plan_packed_ids(m, c.e_begin, c.e_end, G->id_bits, &offsets.back()) * 4;
+        const size_t size = (c.meta.size() + (size_t)c.packed_id_bytes + 255) / 256 * 256;
+        bytes += (int64_t)size;
+        most = std::max(most, size);
+        entries = std::max(entries, c.img_bytes - c.entries_base());
     });
     if (bytes == 0) return NTP_OK;
     void* p = nullptr;
@@ -255,10 +260,19 @@ int pack_streamed_ids(ntp_graph* G, int n_forms) {
     int64_t off = 0;
     size_t k = 0;
     each([&](const HostSparse& m, Chunk& c) {
-        c.h_packed_ids = G->pinned_ids + off + c.img_off_val % 16;
-        off += (c.packed_id_bytes + 31) / 16 * 16;
-        pack_ids(m, c.e_begin, c.e_end, G->id_bits, offsets[k++], reinterpret_cast<uint32_t*>(c.h_packed_ids));
+        c.h_meta_pinned = G->pinned_ids + off;
+        memcpy(c.h_meta_pinned, c.meta.data(), c.meta.size());
+        if (c.packed_id_bytes > 0) {
+            c.h_packed_ids = c.h_meta_pinned + c.meta.size();
+            pack_ids(m, c.e_begin, c.e_end, G->id_bits, offsets[k], reinterpret_cast<uint32_t*>(c.h_packed_ids));
+        }
+        ++k;
+        off += (int64_t)((c.meta.size() + (size_t)c.packed_id_bytes + 255) / 256 * 256);
     });
+    // (packed ids take less than the 8 bytes of an entry's id and weight twice over: two buffers fit unless another chunk has by far the most rows)
+    G->stage_entries = G->stage_memory;
+    G->staged.buffers = (int)std::min<size_t>(MAX_BUFFERS, (2 * stage_bytes - entries) / most);
+    for (int b = 0; b < G->staged.buffers; ++b) G->stage[b] = G->stage_memory + entries + (size_t)b * most;
     return NTP_OK;
 }
 
@@ -293,7 +307,8 @@ inline int bin_max_degree(int b) { return b == 0 ? 1 : (b == NBINS - 1 ? INT_MAX
 // Enqueue the kernels of one chunk whose image lives at `img` on the device.
 // scatter: Y[colidx[k], :] += val[k] * X[row, :] instead of Y[row, :] = sum val[k] * X[colidx[k], :]
 // weights: caller's edge weights in the entry order of the form m (nullptr: the stored ones)
-int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const void* X, void* Y, float* partial,
+// entries: where the chunk's entries lie, less their place in an image (its image, unless they were unpacked elsewhere)
+int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const char* entries, const void* X, void* Y, float* partial,
               int64_t f, int64_t ldx, int64_t ldy, int dtype, hipStream_t st, bool scatter = false,
               const float* weights = nullptr, bool defer_reduce = false,
               const int32_t* hub_cols = nullptr, int n_hub = 0, const Epilogue& epi = Epilogue()) {
@@ -302,8 +317,8 @@ int run_chunk(const Chunk& c, const HostSparse& m, const char* img, const void* 
     a.rowptr = reinterpret_cast<const int64_t*>(img + c.off_rowptr);
     a.rows = reinterpret_cast<const int32_t*>(img + c.off_rows);
     a.segs = reinterpret_cast<const Segment*>(img + c.off_segs);
-    a.colidx = reinterpret_cast<const int32_t*>(img + c.img_off_colidx);
-    a.val = weights ? weights + c.e_begin : reinterpret_cast<const float*>(img + c.img_off_val);
+    a.colidx = reinterpret_cast<const int32_t*>(entries + c.img_off_colidx);
+    a.val = weights ? weights + c.e_begin : reinterpret_cast<const float*>(entries + c.img_off_val);
     a.X = X;
     a.Y = Y;
     a.M = epi.M;
@@ -514,10 +529,12 @@ void destroy(ntp_graph* G) {
             if (c.d_colidx_hub) (void)hipFree(c.d_colidx_hub);
         if (G->form[k].d_hub_cols) (void)hipFree(G->form[k].d_hub_cols);
         if (G->form[k].d_all_reduce) (void)hipFree(G->form[k].d_all_reduce);
-        if (G->stage[k]) (void)hipFree(G->stage[k]);
-        for (hipEvent_t e : {G->staged.ready[k], G->staged.free_[k], G->staged.join[k]})
-            if (e) (void)hipEventDestroy(e);
+        if (G->staged.join[k]) (void)hipEventDestroy(G->staged.join[k]);
     }
+    if (G->stage_memory) (void)hipFree(G->stage_memory);
+    for (int b = 0; b < MAX_BUFFERS; ++b)
+        for (hipEvent_t e : {G->staged.ready[b], G->staged.free_[b]})
+            if (e) (void)hipEventDestroy(e);
     if (G->staged.copy2) (void)hipStreamDestroy(G->staged.copy2);
     if (G->partial) (void)hipFree(G->partial);
     if (G->att_stats) (void)hipFree(G->att_stats);
@@ -547,9 +564,9 @@ struct ChunkKernels {
     int dtype;
     hipStream_t cs;
     const Epilogue& epi;
-    int operator()(const Chunk& c, const char* img) const {
+    int operator()(const Chunk& c, const char* img, const char* entries) const {
         for (int r = 0; r < n_rhs; ++r) {
-            const int e = run_chunk(c, *F.m, img, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
+            const int e = run_chunk(c, *F.m, img, entries, X[r], Y[r], scatter ? nullptr : partial + (size_t)r * partial_stride, f, ldx, ldy, dtype, cs,
                                     scatter, nullptr, F.one_reduce(), F.d_hub_cols, (int)F.plan.hub_cols.size(), epi);
             if (e != NTP_OK) return e;
         }
@@ -557,15 +574,15 @@ struct ChunkKernels {
     }
 };
 
-// its entries by DMA (everything a streamed chunk is copied from is pinned)
+// by DMA its entries, or all that it sends where ids are packed (everything a streamed chunk is copied from is pinned)
 int HipPass::copy_entries(const Chunk& c, int b, hipStream_t s) {
     char* img = g->stage[b];
-    const size_t ne = (size_t)(c.e_end - c.e_begin);
-    if (ne == 0) return NTP_OK;
-    if (c.h_packed_ids) {
-        HIP_TRY(hipMemcpyAsync(img + c.img_off_val, c.h_packed_ids, (size_t)c.packed_id_bytes, hipMemcpyHostToDevice, s));
+    if (g->stage_entries) {
+        HIP_TRY(hipMemcpyAsync(img, c.h_meta_pinned, c.meta.size() + (size_t)c.packed_id_bytes, hipMemcpyHostToDevice, s));
         return NTP_OK;
     }
+    const size_t ne = (size_t)(c.e_end - c.e_begin);
+    if (ne == 0) return NTP_OK;
     HIP_TRY(hipMemcpyAsync(img + c.img_off_colidx, m.colidx + c.e_begin, ne * 4, hipMemcpyHostToDevice, s));
     if (with_val) HIP_TRY(hipMemcpyAsync(img + c.img_off_val, m.val + c.e_begin, ne * 4, hipMemcpyHostToDevice, s));
     return NTP_OK;
@@ -578,25 +595,25 @@ int HipPass::copy_by_kernel(const Chunk& c, int b, hipStream_t s, bool entries) 
     const void* src[3] = {c.h_meta_pinned, m.colidx + c.e_begin, m.val + c.e_begin};
     void* to[3] = {img, img + c.img_off_colidx, img + c.img_off_val};
     int64_t bytes[3] = {(int64_t)c.meta.size(), entry_bytes, with_val ? entry_bytes : 0};
-    if (c.h_packed_ids) { src[1] = c.h_packed_ids; to[1] = to[2]; bytes[1] = entries ? c.packed_id_bytes : 0; }
+    if (g->stage_entries) { bytes[0] += c.packed_id_bytes; bytes[1] = 0; }
     return launch_stage_chunk(src, to, bytes, s);
 }
 
 int HipPass::aggregate(const Chunk& c, int b) {
-    char* img = g->stage[b];
+    char* const img = g->stage[b];
+    char* const to = g->stage_entries ? g->stage_entries - c.entries_base() : img;
+    int32_t* const colidx = reinterpret_cast<int32_t*>(to + c.img_off_colidx);
     if (c.h_packed_ids) {
-        const int rc = launch_unpack_ids(reinterpret_cast<const uint32_t*>(img + c.img_off_val), g->id_bits, g->g.n, c.e_end - c.e_begin,
-                                         reinterpret_cast<int32_t*>(img + c.img_off_colidx), cs);
+        const int rc = launch_unpack_ids(reinterpret_cast<const uint32_t*>(img + c.meta.size()), g->id_bits, g->g.n, c.e_end - c.e_begin, colidx, cs);
         if (rc != NTP_OK) return rc;
     }
     if (!with_val) {          // row degree = dout and column degree = din where rows are sources
         const int rc = launch_rebuild_weights(reinterpret_cast<const int64_t*>(img + c.off_rowptr), c.row_begin, c.row_end - c.row_begin,
-                                              c.e_begin, c.e_end - c.e_begin, reinterpret_cast<const int32_t*>(img + c.img_off_colidx),
-                                              reinterpret_cast<float*>(img + c.img_off_val), by_source ? g->d_dout : g->d_din,
-                                              by_source ? g->d_din : g->d_dout, g->g.val_mode, cs);
+                                              c.e_begin, c.e_end - c.e_begin, colidx, reinterpret_cast<float*>(to + c.img_off_val),
+                                              by_source ? g->d_dout : g->d_din, by_source ? g->d_din : g->d_dout, g->g.val_mode, cs);
         if (rc != NTP_OK) return rc;
     }
-    return kernels(c, img);
+    return kernels(c, img, to);
 }
 
 extern "C" {
@@ -673,15 +690,15 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
                 set_error("device budget %lld cannot hold two staging buffers of %zu bytes", (long long)budget, max_img);
                 return NTP_EBUDGET;
             }
-            G->stage_bytes = max_img;
-            for (int b = 0; b < 2; ++b) {
-                void* p = nullptr;
-                if (hipMalloc(&p, max_img) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of a %zu-byte staging buffer failed", max_img); return NTP_ENOMEM; }
-                G->stage[b] = (char*)p;
-                G->device_bytes += (int64_t)max_img;
-                for (hipEvent_t* e : {&G->staged.ready[b], &G->staged.free_[b], &G->staged.join[b]})
-                    if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) { set_error("hipEventCreate failed"); return NTP_EHIP; }
-            }
+            void* p = nullptr;
+            if (hipMalloc(&p, 2 * max_img) != hipSuccess) { (void)hipGetLastError(); set_error("device allocation of two staging buffers of %zu bytes failed", max_img); return NTP_ENOMEM; }
+            G->stage_memory = (char*)p;
+            for (int b = 0; b < 2; ++b) G->stage[b] = G->stage_memory + (size_t)b * max_img;
+            G->device_bytes += (int64_t)(2 * max_img);
+            std::vector<hipEvent_t*> events = {&G->staged.join[0], &G->staged.join[1]};
+            for (int b = 0; b < MAX_BUFFERS; ++b) events.insert(events.end(), {&G->staged.ready[b], &G->staged.free_[b]});
+            for (hipEvent_t* e : events)
+                if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) { set_error("hipEventCreate failed"); return NTP_EHIP; }
             if (hipStreamCreateWithFlags(&G->staged.copy2, hipStreamNonBlocking) != hipSuccess) { (void)hipGetLastError(); set_error("hipStreamCreate failed"); return NTP_EHIP; }
             left = force_stream ? 0 : budget - (int64_t)(2 * max_img);
         }
@@ -731,10 +748,9 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
             if (hipMemcpy(p, all.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) { (void)hipGetLastError(); set_error("upload of the split rows failed"); return NTP_EHIP; }
         }
         if (G->pack_ids && pinned_meta_bytes > 0) {
-            rc = pack_streamed_ids(G, n_forms);
+            rc = pack_streamed_ids(G, n_forms, max_img);
             if (rc != NTP_OK) return rc;
-        }
-        if (pinned_meta_bytes) {
+        } else if (pinned_meta_bytes) {
             void* p = nullptr;
             if (hipHostMalloc(&p, pinned_meta_bytes, hipHostMallocDefault) != hipSuccess) { (void)hipGetLastError(); set_error("pinned allocation of %zu bytes failed", pinned_meta_bytes); return NTP_ENOMEM; }
             G->pinned_meta = (char*)p;
@@ -949,7 +965,7 @@ static int aggregate_resident(ntp_graph_t* g, int which, const void* X, void* Y,
     }
     if (rc != NTP_OK) return rc;
     for (auto& c : F.plan.chunks) {
-        rc = run_chunk(c, *F.m, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
+        rc = run_chunk(c, *F.m, c.d_image, c.d_image, X, Y, partial, f, ldx, ldy, dtype, (hipStream_t)stream, scatter, weights, F.one_reduce(),
                        F.d_hub_cols, (int)F.plan.hub_cols.size());
         if (rc != NTP_OK) return rc;
     }
@@ -1006,14 +1022,13 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
     const ChunkKernels run_all{F, n_rhs, X, Y, scatter, g->partial, pstride, f, ldx, ldy, dtype, cs, epi};
     const bool with_val = !g->streams_without_weights();
     int64_t streamed = 0, bytes = 0, largest = 0, entries = 0;
-    bool packed = false;
+    const bool packed = g->stage_entries != nullptr;
     for (auto& c : F.plan.chunks)
         if (!c.d_image) {
             const int64_t size = streamed_bytes(c, with_val);
             ++streamed;
             bytes += size;
             largest = std::max(largest, size);
-            packed = packed || c.h_packed_ids;
             entries += c.e_end - c.e_begin;
         }
     const double each = 1.0 / (double)std::max<int64_t>(1, streamed);
@@ -1024,7 +1039,7 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
     if (!F.all_resident) rc = pass.begin();
     for (auto& c : F.plan.chunks) {
         if (rc != NTP_OK) return rc;
-        rc = c.d_image ? run_all(c, c.d_image) : pass.streamed(c);
+        rc = c.d_image ? run_all(c, c.d_image, c.d_image) : pass.streamed(c);
     }
     if (rc == NTP_OK && !F.all_resident) rc = pass.end();
     if (rc != NTP_OK) return rc;

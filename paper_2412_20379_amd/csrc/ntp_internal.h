@@ -159,14 +159,15 @@ struct Chunk {
     bool block_rows = false;                   // split rows are summed by one block each (no segments, no partial sums)
     // device image layout: [meta | colidx | val], each part 256-byte aligned
     size_t img_off_colidx = 0, img_off_val = 0, img_bytes = 0;
+    size_t entries_base() const { return img_off_colidx / 256 * 256; }       // from there on the image holds entries only
     // residency
     int32_t* d_colidx_hub = nullptr;           // resident chunks of a form with a hub table: hub-encoded column ids
     char* d_image = nullptr;                   // device image if resident
     char* d_copies = nullptr;                  // second copies of a resident chunk (nullptr: none)
     RowCopies copies;
     char* h_meta_pinned = nullptr;             // pinned copy of meta for streaming
-    char* h_packed_ids = nullptr;              // pinned: the column ids packed (nullptr: they travel as they are); goes where the weights
-    int64_t packed_id_bytes = 0;               // are rebuilt afterwards, unpacked from there
+    char* h_packed_ids = nullptr;              // pinned, behind h_meta_pinned: the column ids packed (nullptr: they travel as they are)
+    int64_t packed_id_bytes = 0;
 };
 
 struct Plan {

@@ -234,7 +234,8 @@ struct BitWriter {
     void end() { if (have > 0) *w = (uint32_t)buf; }
 };
 
-int pack_threads(int64_t blocks) { return std::max(1, std::min(host_threads(), (int)std::min<int64_t>(64, blocks / 256 + 1))); }
+// (a thread costs some 20 us: a block 0.07 us to plan, 0.6 to pack)
+int pack_threads(int64_t blocks, int64_t each) { return std::max(1, std::min(host_threads(), (int)std::min<int64_t>(64, blocks / each + 1))); }
 
 }  // namespace
 
@@ -242,7 +243,7 @@ int64_t plan_packed_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int
     const PackBlocks blocks{m, e_begin, e_end, bits};
     const int64_t nb = blocks.count();
     offsets->assign((size_t)nb + 1, 0);
-    parallel_for_threads(pack_threads(nb), [&](int t, int nt) {
+    parallel_for_threads(pack_threads(nb, 4096), [&](int t, int nt) {
         blocks.each(nb * t / nt, nb * (t + 1) / nt, [&](int64_t b, int len, int64_t e, int64_t r) {
             const int64_t last = blocks.last(len, e, r);
             const int l = blocks.low_bits(len, last);
@@ -259,7 +260,7 @@ void pack_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, con
     const int64_t nb = blocks.count();
     std::copy(offsets.begin(), offsets.end(), packed);
     packed[offsets.back()] = packed[offsets.back() + 1] = 0;
-    parallel_for_threads(pack_threads(nb), [&](int t, int nt) {        // a block is whole words of its own
+    parallel_for_threads(pack_threads(nb, 1024), [&](int t, int nt) {        // a block is whole words of its own
         blocks.each(nb * t / nt, nb * (t + 1) / nt, [&](int64_t b, int len, int64_t e, int64_t r) {
             uint32_t* w = packed + offsets[(size_t)b];
             const int32_t* const ids = m.colidx + e;

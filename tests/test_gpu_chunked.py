@@ -357,6 +357,37 @@ def test_packed_blocks_of_every_kind(n, m, hub, chunk):
     streamed.close()
 
 
+@pytest.mark.parametrize("chunk,budget", [(700_000, 0), (1_500_000, 0), (700_000, 16 << 20), (700_000, 26 << 20)])
+def test_packed_chunks_pass_after_pass(chunk, budget):
+    """copies run ahead of the kernels, over the ends of passes too: passes on other streams, both directions and several right-hand sides without a
+    wait in between, each the bits of the resident chunks"""
+    import torch
+    n, f = 40_000, 16
+    rng = gen.stream_rng(17, 2)
+    src, dst = rng.integers(0, n, 3_000_000).astype(np.int32), rng.integers(0, n, 3_000_000).astype(np.int32)
+    flags = ntp.NTP_DIRECTED_GCN_FLAGS
+    resident = ntp.ntp_graph_build(n, src, dst, flags=flags, chunk_edges=chunk)
+    streamed = ntp.ntp_graph_build(n, src, dst, flags=flags | (0 if budget else ntp.NTP_FORCE_STREAM), chunk_edges=chunk, device_budget_bytes=budget)
+    assert not ntp.ntp_graph_chunks(streamed)["resident"].all()
+    say("pass after pass", chunk, budget, "bytes", ntp.ntp_graph_stream_bytes(streamed), "resident", int(ntp.ntp_graph_chunks(streamed)["resident"].sum()))
+    xs = [torch.randn(n, f, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(i)) for i in range(8)]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    torch.cuda.synchronize()
+    outs = []
+    for g in (resident, streamed):
+        ys = [torch.full_like(x, 9) for x in xs]
+        torch.cuda.synchronize()
+        for i, x in enumerate(xs):
+            cs, cp = streams[i % 2], streams[2 + i // 2 % 2]
+            ntp.ntp_chunked_aggregate(g, ntp.NTP_FWD if i % 3 else ntp.NTP_BWD, x, ys[i], f, f, f, ntp.NTP_F32, cs, cp)
+        torch.cuda.synchronize()
+        outs.append(ys)
+    for i, (a, b) in enumerate(zip(*outs)):
+        assert torch.equal(a, b), i
+    resident.close()
+    streamed.close()
+
+
 @pytest.mark.parametrize("n_edges,chunk,budget,forms,packed", [(700_000, 655_360, 0, 2, True), (700_000, 655_359, 0, 2, False), (1_320_000, 0, 0, 2, True), (1_300_000, 0, 0, 2, False),
                                                               (660_000, 0, 0, 1, True), (700_000, 0, 0, 0, False), (3_000_000, 0, 52_500_000, 2, True), (3_000_000, 0, 52_000_000, 2, False)])
 def test_ids_are_packed_by_the_chunks_that_are_cut(n_edges, chunk, budget, forms, packed):
