@@ -415,15 +415,16 @@ __global__ void __launch_bounds__(64 * NW, NW / 4) strip_short_kernel(const Stri
     }
 }
 
-// Few rows: the eight wavefronts of a block share one unit of 32 rows and one column group of 32, wavefront w
-// taking steps w, w + 8, ... of the contraction; B comes straight from memory.  The eight sums are
-// added through LDS in a fixed order.
-template <class T, Core C, bool MASK, int VB>
-__global__ void __launch_bounds__(512) strip_split_kernel(const StripArgs g) {
+// Few rows: the NW wavefronts of a block share one unit of 32 rows and one column group of 32, wavefront w
+// taking steps w, w + NW, ... of the contraction; B comes straight from memory.  Their sums are
+// added through LDS in a fixed order.  Bound: the loads of a wavefront's steps, one after the other, so sixteen of them where a compute unit has
+// one block.
+template <class T, Core C, bool MASK, int VB, int NW>
+__global__ void __launch_bounds__(64 * NW) strip_split_kernel(const StripArgs g) {
     constexpr int NP = Parts<T, C>::n;
     using Rows = RowStage<T, C, MASK, VB>;
     constexpr int KS = Rows::KS;
-    __shared__ uint4 lds[8 * 256];
+    __shared__ uint4 lds[NW * 256];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 31, h = lane >> 5;
@@ -434,9 +435,9 @@ __global__ void __launch_bounds__(512) strip_split_kernel(const StripArgs g) {
     for (int e = 0; e < 16; ++e) acc[0][0][e] = 0.f;
     typename Rows::Raw x;
     if (wave < g.steps) Rows::issue(g, x, u, wave, lane);
-    for (int s = wave; s < g.steps; s += 8) {
+    for (int s = wave; s < g.steps; s += NW) {
         Rows::stage(g, x, s, own, lane);
-        if (s + 8 < g.steps) Rows::issue(g, x, u, s + 8, lane);
+        if (s + NW < g.steps) Rows::issue(g, x, u, s + NW, lane);
 #pragma unroll
         for (int c = 0; c < KS / 16; ++c) {
             uint4 a[1][NP], b[1][NP];
@@ -452,10 +453,10 @@ __global__ void __launch_bounds__(512) strip_split_kernel(const StripArgs g) {
     for (int e = 0; e < 16; ++e) mine[e * 64 + lane] = acc[0][0][e];
     __syncthreads();
     const float* all = reinterpret_cast<const float*>(lds);
-    for (int i = threadIdx.x; i < 1024; i += 512) {
+    for (int i = threadIdx.x; i < 1024; i += 64 * NW) {
         float v = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) v += all[w * 1024 + i];
+        for (int w = 0; w < NW; ++w) v += all[w * 1024 + i];
         const int e = i >> 6, l = i & 63;
         const int64_t row = (int64_t)u * 32 + 8 * (e / 4) + 4 * (l >> 5) + e % 4;
         const int col = gr * 32 + (l & 31);
@@ -546,12 +547,16 @@ int launch_strip(StripArgs g, const StripPlan& p, hipStream_t st) {
 // (1,000) 23.8 / 32.3, on 12,000 (1,500) 32.7 / 33.3, on 16,000 40.6 / 34.6; 256 -> 64 on 16,000 (1,000) 10.0 / 15.8, on 24,000
 // (1,500) 16.6 / 16.4; 256 -> 256 on 4,000 (1,000) 9.9 / 15.7, on 8,000 (2,000) 20.2 / 16.6; 128 -> 128 on 8,000 (1,000) 7.4 /
 // 10.2, on 12,000 (1,500) 10.1 / 10.5; 1433 -> 16 on 24,000 (750) 42.2 / 60.6, on 40,000 (1,250) 63.6 / 60.9.
+// Sixteen wavefronts a block instead of eight where compute units have one block or none and there are two steps or more for each: us 8 / 16,
+// 1433 -> 16 on 2,708 rows 14.9 / 14.2 (bf16 9.6 / 8.4), 1433 -> 64 on 4,000 17.7 / 16.5 (10.1 / 8.6), 4000 -> 32 on 1,000 33.9 / 32.0 (19.3 / 16.4);
+// of 19 steps 602 -> 16 on 1,000 7.1 / 7.3, on 8,000 8.1 / 8.4.
 bool split_contraction(const StripArgs& g) { return (g.n + 31) / 32 * ((g.N + 31) / 32) <= 4 * compute_units() && g.steps >= 4; }
 
 template <class T, Core C, bool MASK>
 int launch_split(const StripArgs& g, hipStream_t st) {
     const int64_t blocks = (g.n + 31) / 32 * ((g.N + 31) / 32);
-    hipLaunchKernelGGL((strip_split_kernel<T, C, MASK, 16>), dim3((unsigned)blocks), dim3(512), 0, st, g);
+    if (blocks <= compute_units() && g.steps > 32) hipLaunchKernelGGL((strip_split_kernel<T, C, MASK, 16, 16>), dim3((unsigned)blocks), dim3(1024), 0, st, g);
+    else hipLaunchKernelGGL((strip_split_kernel<T, C, MASK, 16, 8>), dim3((unsigned)blocks), dim3(512), 0, st, g);
     return NTP_OK;
 }
 

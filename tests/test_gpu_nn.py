@@ -67,6 +67,27 @@ def test_nn_bwd_fp32(n, k, m, act, need_dA):
         assert_close(dA.cpu().numpy(), dA_ref, _abs_scale(dZ, W.T), TOL_F32, "dA %s" % ((n, k, m),))
 
 
+@pytest.mark.parametrize("n,k,m", [(1, 1025, 1), (33, 1057, 16), (2700, 1500, 33), (600, 2049, 128), (8192, 1100, 32), (8193, 1100, 32), (70, 4100, 41)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_long_contractions_of_few_rows(n, k, m, dtype):
+    """sixteen wavefronts share a unit's contraction (fp32 above 1,024 indices, bf16 above 2,048), eight where there are more units than compute units"""
+    import torch
+    from gpu_util import dev_bf16_bits, host_bf16, dev_f32
+    say("long contraction", n, k, m, dtype)
+    A, W = gen.normal_features(n, k, seed=n + 1), gen.glorot_weight(k, m, seed=m)
+    if dtype == "f32":
+        H = torch.full((n, m), float("nan"), device="cuda:0")
+        ntp.ntp_nn_fwd(dev_f32(A), dev_f32(W), H, n, k, m, ntp.NTP_ACT_RELU)
+        got, tol = H.cpu().numpy(), TOL_F32
+    else:
+        (Ab, A), (Wb, W) = dev_bf16_bits(A), dev_bf16_bits(W)
+        H = torch.empty(n, m, dtype=torch.int16, device="cuda:0")
+        ntp.ntp_nn_fwd(Ab, Wb, H, n, k, m, ntp.NTP_ACT_RELU, ntp.NTP_BF16)
+        got, tol = host_bf16(H), TOL_BF16
+    torch.cuda.synchronize()
+    assert_close(got, ogcn.nn_fwd(A, W, ntp.NTP_ACT_RELU), _abs_scale(A, W), tol, "nn_fwd %s" % ((n, k, m),))
+
+
 @pytest.mark.parametrize("n,k,m", [(300, 16, 8), (1000, 128, 256), (2049, 100, 48), (1500, 604, 128)])
 def test_nn_bf16(n, k, m):
     import torch
