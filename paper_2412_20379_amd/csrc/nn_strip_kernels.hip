@@ -20,9 +20,14 @@
 // bf16 256 -> 256 0.080 -> 0.062, its dA 0.061 -> 0.045 (masked 0.090 -> 0.061).  The three products of a masked 256 x 256 layer on
 // 306,129 rows together 0.89 -> 0.82 ms.
 //
+// Results are stored through a buffer resource that ends with the matrix, so rows and columns beyond it need no test: no vector instruction but
+// one addition a store (before, comparisons, masks and 64-bit addresses: seven), which counts where nothing hides it.  us before / now: dA 40 -> 256 on
+// 169,343 rows 63.2 / 54.8 (masked 64.7 / 58.0), 47 -> 256 on 153,065 53.9 / 47.8, 128 -> 602 on 58,241 64.0 / 58.9, 128 -> 128 on 306,129 77.9 /
+// 70.5, 64 -> 300 on 20,000 13.4 / 12.1; forward 47 -> 172 on 306,129 91.8 / 84.6, 41 -> 128 on 58,241 16.4 / 14.4.
+//
 // Contractions below 64 and outputs of up to 32 columns keep B as floats and run on the fp32 matrix instructions, whose
 // products are exact (the rule is in nn_kernels.hip): no other vector instruction runs beside one, so their time adds to the
-// rest instead of hiding under it, dA 40 -> 256 0.061 ms (masked 0.064) against 0.046 (0.050) with pieces and 0.069 (0.080) in
+// rest instead of hiding under it, dA 40 -> 256 0.055 ms (masked 0.058; 0.061 and 0.064 before those stores) against 0.046 (0.050) with pieces and 0.069 (0.080) in
 // the fp32 tiles replaced; 256 -> 16 0.035 against 0.034 and 0.040; 1433 -> 16 on 60,000 rows 0.078 against 0.087 and 0.108.
 // Reading A in operand layout straight from memory (a lane = a row) instead of through LDS costs 32 line look-ups per
 // instruction instead of 8: 256 -> 256 0.200 ms.
@@ -225,6 +230,7 @@ __device__ __forceinline__ void fill_panel(const StripArgs& g, uint4* lds, int c
     }
 }
 
+constexpr int64_t MAX_BUFFER_PITCH = 1 << 23;    // 32 rows in 31 bits
 // a unit's 32 rows x 32 * TN columns from column cb on: element e of a 32x32 accumulator sits at row
 // 8*(e/4) + 4*(lane/32) + e%4, column lane%32
 template <class T, int TN>
@@ -245,6 +251,23 @@ __device__ __forceinline__ void store_unit(const StripArgs& g, const f32x16 (&ac
             for (int j = 0; j < TN; ++j) v[j] = relu ? (acc[0][j][e] > 0.f ? acc[0][j][e] : 0.f) : acc[0][j][e];
             if (whole || (in && 8 * (e / 4) + (e % 4) < rows_left)) store_bf16<TN>(p, v, g.nt != 0);
             p += (e % 4 == 3) ? 5 * g.ldc : g.ldc;
+        }
+    } else if (sizeof(T) == 4 && g.ldc <= MAX_BUFFER_PITCH) {
+        const int64_t row0 = (int64_t)u * 32;
+        const int pitch = (int)g.ldc * 4, rows = (int)min(g.n - row0, (int64_t)32);
+        const auto out = __builtin_amdgcn_make_buffer_rsrc(static_cast<T*>(g.C) + row0 * g.ldc, 0, rows * pitch, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int col = cb + j * 32 + r, off = col < N ? 4 * h * pitch + 4 * col : 0x7fff0000;
+            auto put = [&](auto&& store) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float v = acc[0][j][e];
+                    store(__float_as_uint(relu ? (v > 0.f ? v : 0.f) : v), (8 * (e / 4) + e % 4) * pitch);
+                }
+            };
+            if (g.nt) put([&](unsigned v, int at) { __builtin_amdgcn_raw_buffer_store_b32(v, out, off + at, 0, 2); });
+            else put([&](unsigned v, int at) { __builtin_amdgcn_raw_buffer_store_b32(v, out, off + at, 0, 0); });
         }
     } else if (whole && g.nt) {
 #pragma unroll

@@ -88,6 +88,29 @@ def test_long_contractions_of_few_rows(n, k, m, dtype):
     assert_close(got, ogcn.nn_fwd(A, W, ntp.NTP_ACT_RELU), _abs_scale(A, W), tol, "nn_fwd %s" % ((n, k, m),))
 
 
+@pytest.mark.parametrize("n,k,m", [(1, 64, 47), (31, 70, 33), (33, 40, 100), (32, 65, 257), (4097, 100, 65), (8225, 47, 172), (20001, 300, 41), (5000, 20, 31)])
+def test_nothing_is_stored_beyond_the_output(n, k, m):
+    """the last rows and columns of H and dA, and what lies around them"""
+    import torch
+    from gpu_util import dev_f32
+    say("stores", n, k, m)
+    A, W = gen.normal_features(n, k, seed=n), gen.glorot_weight(k, m, seed=m)
+    G = gen.normal_features(n, m, seed=n + 1)
+    pad = 70 * max(k, m)
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws = torch.empty(max(wsb, 4), dtype=torch.uint8, device="cuda:0")
+    for out_m, ref, scale, run in (
+            (m, ogcn.nn_fwd(A, W, ntp.NTP_ACT_NONE), _abs_scale(A, W), lambda C: ntp.ntp_nn_fwd(dev_f32(A), dev_f32(W), C, n, k, m, ntp.NTP_ACT_NONE)),
+            (k, G.astype(np.float64) @ W.astype(np.float64).T, _abs_scale(G, W.T),
+             lambda C: ntp.ntp_nn_bwd(dev_f32(A), dev_f32(W), dev_f32(G), dev_f32(G), C, None, n, k, m, ntp.NTP_ACT_NONE, ntp.NTP_F32, ws, wsb))):
+        whole = torch.full((pad + n * out_m + pad,), 12345.0, device="cuda:0")
+        C = whole[pad:pad + n * out_m].view(n, out_m)
+        run(C)
+        torch.cuda.synchronize()
+        assert_close(C.cpu().numpy(), ref, scale, TOL_F32, "stores %s" % ((n, k, m),))
+        assert bool((whole[:pad] == 12345.0).all()) and bool((whole[pad + n * out_m:] == 12345.0).all())
+
+
 @pytest.mark.parametrize("n,k,m", [(300, 16, 8), (1000, 128, 256), (2049, 100, 48), (1500, 604, 128)])
 def test_nn_bf16(n, k, m):
     import torch
