@@ -842,15 +842,17 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ReduceArgs a) {
     {
         const int col = (int)blockIdx.y * 64 + lane;        // one block per split row and 64 columns
         float s = 0.f;
+        T mask = T();
         if (col < a.f) {
+            if (w == 0 && a.epilogue && a.M) mask = static_cast<const T*>(a.M)[(int64_t)it.row * a.ldm + col];
             const float* p = a.partial + (int64_t)it.first_slot * a.fp + col;
-            int k = w;
-            for (; k + 12 < it.n_slots; k += 16) {
-                const float t0 = p[(int64_t)k * a.fp], t1 = p[(int64_t)(k + 4) * a.fp];
-                const float t2 = p[(int64_t)(k + 8) * a.fp], t3 = p[(int64_t)(k + 12) * a.fp];
-                s += t0; s += t1; s += t2; s += t3;
+            for (int k = w; k < it.n_slots; k += 32) {        // eight slots in flight, those beyond the last one count as zero
+                float t[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) t[j] = p[(int64_t)min(k + 4 * j, it.n_slots - 1) * a.fp];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) s += k + 4 * j < it.n_slots ? t[j] : 0.f;
             }
-            for (; k < it.n_slots; k += 4) s += p[(int64_t)k * a.fp];
         }
         part[w][lane] = s;
         __syncthreads();
@@ -859,9 +861,8 @@ __global__ void __launch_bounds__(256) reduce_kernel(const ReduceArgs a) {
             if (a.epilogue) {        // the aggregation's epilogue for rows summed here
                 float m = r;
                 if (a.M) {
-                    const T mv = static_cast<const T*>(a.M)[(int64_t)it.row * a.ldm + col];
-                    if constexpr (sizeof(T) == 4) m = mv;
-                    else m = __uint_as_float((unsigned)mv << 16);
+                    if constexpr (sizeof(T) == 4) m = mask;
+                    else m = __uint_as_float((unsigned)mask << 16);
                 }
                 r = m > 0.f ? r : 0.f;
             }

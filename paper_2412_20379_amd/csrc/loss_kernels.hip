@@ -104,14 +104,19 @@ __global__ void __launch_bounds__(256) xent_partial_kernel(const float* __restri
 __global__ void __launch_bounds__(256) xent_final_kernel(const float* __restrict__ partial, int count, float* __restrict__ loss, float inv_n) {
     __shared__ float red[256];
     float s = 0.f;
-    for (int i = threadIdx.x; i < count; i += 256) s += partial[i];
+    for (int i = threadIdx.x; i < count; i += 8 * 256) {       // eight in flight, those beyond the last one count as zero
+        float t[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t[j] = partial[min(i + 256 * j, count - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += i + 256 * j < count ? t[j] : 0.f;
+    }
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss[0] = red[0] * inv_n;
+    if (threadIdx.x >= 64) return;
+    s = (red[threadIdx.x] + red[threadIdx.x + 128]) + (red[threadIdx.x + 64] + red[threadIdx.x + 192]);
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w);
+    if (threadIdx.x == 0) loss[0] = s * inv_n;
 }
 
 // returns the number of blocks (= partial sums written to block_loss)

@@ -27,7 +27,8 @@ namespace {
 
 // out[i] = sum over the splits of part[s * stride + i].  A block owns 64 consecutive
 // elements; wavefront w adds the splits w, w+4, ..., eight at a time, and the four sums
-// are combined as (s0 + s1) + (s2 + s3): fixed order, deterministic.
+// are combined as (s0 + s1) + (s2 + s3): fixed order, deterministic.  Bound for few elements: the loads, one batch after the other
+// (sixteen in flight and no serial remainder: 128 splits of 128 x 256 7.0 -> 6.4 us, 11 of 1433 x 16 4.0 -> 3.3).
 __global__ void __launch_bounds__(256) sum_splits_kernel(const float* __restrict__ part, float* __restrict__ out,
                                                          int64_t count, int64_t stride, int n_splits) {
     __shared__ float tmp[4][64];
@@ -38,18 +39,25 @@ __global__ void __launch_bounds__(256) sum_splits_kernel(const float* __restrict
     if (i < count) {
         const float* p = part + i;
         int k = w;
-        for (; k + 28 < n_splits; k += 32) {       // eight loads in flight, added in pairs: fewer roundings at the size of the sum
+        auto eight = [](const float* t) { return ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7])); };
+        for (; k + 60 < n_splits; k += 64) {       // sixteen loads in flight, added in pairs: fewer roundings at the size of the sum
+            float t[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) t[j] = p[(int64_t)(k + 4 * j) * stride];
+            s += eight(t);
+            s += eight(t + 8);
+        }
+        for (; k < n_splits; k += 32) {            // eight; those beyond the last one count as zero
             float t[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) t[j] = p[(int64_t)(k + 4 * j) * stride];
-            s += ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+            for (int j = 0; j < 8; ++j) t[j] = p[(int64_t)min(k + 4 * j, n_splits - 1) * stride];
+            if (k + 28 < n_splits) {
+                s += eight(t);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) s += k + 4 * j < n_splits ? t[j] : 0.f;
+            }
         }
-        for (; k + 12 < n_splits; k += 16) {
-            const float t0 = p[(int64_t)k * stride], t1 = p[(int64_t)(k + 4) * stride];
-            const float t2 = p[(int64_t)(k + 8) * stride], t3 = p[(int64_t)(k + 12) * stride];
-            s += t0; s += t1; s += t2; s += t3;
-        }
-        for (; k < n_splits; k += 4) s += p[(int64_t)k * stride];
     }
     tmp[w][lane] = s;
     __syncthreads();
