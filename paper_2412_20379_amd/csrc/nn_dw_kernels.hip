@@ -72,6 +72,11 @@ __device__ __forceinline__ void cut_rows(const T (&x)[8], uint4 (&piece)[Parts<T
 template <class T, Core C, bool MASK, int VA, int VB, int TA, int TN>
 __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     constexpr bool RING = TA * TN <= 4;        // two steps in flight (else one: the accumulators take the registers)
+    // Tiles of 64 x 64 refill a register set on every step, past the end with the last whole one again, and ahead of the products: behind a branch
+    // the compiler loses count of what is in flight and waits for all of it.  us before / now, fp32 (bf16): 47 x 256 on 306,129 rows 99 / 94 (38.5 /
+    // 36.1), 41 x 128 on 58,241 19.7 / 18.3 (15.8 / 14.2), 64 x 64 on 169,343 25.8 / 23.9, masked 31.5 / 29.5.  Tiles of 128 x 32 gain nothing, and those
+    // with one step in flight wait for it in either form (masked 128 x 64 9 % slower so).
+    constexpr bool REFILL = RING && C == CORE_BF16 && TA == 2;
     constexpr int NP = Parts<T, C>::n;
     extern __shared__ float lds[];             // sums of the row shares
     const int lane = threadIdx.x & 63;
@@ -162,7 +167,10 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
             for (int i = 0; i < TA; ++i) cut_a(i, pa[i]);
             // pieces leave x free before they are multiplied; floats are multiplied where they were loaded to (602 x 16 on
             // 58,241 rows: 62.2 us, refilled before 64.4)
-            if constexpr (WHOLE && C == CORE_BF16) {
+            if constexpr (WHOLE && REFILL) {
+                fetch(x, min(next, r1 - 16), whole);          // (a whole step is being multiplied: r1 - 16 >= r0)
+                asm volatile("" ::: "memory");
+            } else if constexpr (WHOLE && C == CORE_BF16) {
                 if (next + 16 <= r1) fetch(x, next, whole);
             }
             mfma_parts<C, TA, TN, NP>(pa, pb, acc);

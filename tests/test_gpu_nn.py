@@ -88,6 +88,23 @@ def test_long_contractions_of_few_rows(n, k, m, dtype):
     assert_close(got, ogcn.nn_fwd(A, W, ntp.NTP_ACT_RELU), _abs_scale(A, W), tol, "nn_fwd %s" % ((n, k, m),))
 
 
+@pytest.mark.parametrize("n", [15, 16, 17, 32, 33, 63, 127, 128, 145, 8191, 8209, 41000])
+@pytest.mark.parametrize("k,m", [(4, 33), (64, 47), (41, 128), (63, 300)])
+def test_dw_of_few_steps(n, k, m):
+    """weight gradients of up to 64 columns of A: no whole step of 16 rows in a wavefront's share, one, two, and whole and partial ones"""
+    import torch
+    from gpu_util import dev_f32
+    say("dw steps", n, k, m)
+    A, G, H = (gen.normal_features(n, c, seed=n + c, stream=i) for i, c in enumerate((k, m, m)))
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws = torch.empty(max(wsb, 4), dtype=torch.uint8, device="cuda:0")
+    for act, dZ in ((ntp.NTP_ACT_NONE, G), (ntp.NTP_ACT_RELU, G * (H > 0))):
+        dW = torch.full((k, m), float("nan"), device="cuda:0")
+        ntp.ntp_nn_bwd(dev_f32(A), None, dev_f32(H), dev_f32(G), None, dW, n, k, m, act, ntp.NTP_F32, ws, wsb)
+        torch.cuda.synchronize()
+        assert_close(dW.cpu().numpy(), A.astype(np.float64).T @ dZ.astype(np.float64), _abs_scale(A.T, dZ), TOL_F32, "dW %s" % ((n, k, m),))
+
+
 @pytest.mark.parametrize("n,k,m", [(1, 64, 47), (31, 70, 33), (33, 40, 100), (32, 65, 257), (4097, 100, 65), (8225, 47, 172), (20001, 300, 41), (5000, 20, 31)])
 def test_nothing_is_stored_beyond_the_output(n, k, m):
     """the last rows and columns of H and dA, and what lies around them"""
