@@ -334,6 +334,7 @@ struct Recorder {
     struct Region { Access write, read; int holds = -1; } region[MAX_BUFFERS][2];      // [buffer][0: entries, 1: row pointers and lists]
     Access last_copy[STREAMS], unpacked;     // unpacked: the last use of the unpacked entries
     bool whole = false;
+    int enqueued = 0, done = 0, ahead = 0, total = 0;        // copies by DMA, chunks aggregated; copies that may be ahead (0: none by DMA), chunks of the pass
     int compute = 0, fail_in = -1;           // fail_in: operations until one fails (negative: none does)
     const char* what = "";
 
@@ -358,6 +359,7 @@ struct Recorder {
     }
     int copy_entries(int c, int b, int s) {
         if (fails()) return -1;
+        ++enqueued;
         write(c, b, 0, s);
         if (whole) write(c, b, 1, s);
         last_copy[s] = Access{s, clock[s][s]};
@@ -371,6 +373,8 @@ struct Recorder {
         return 0;
     }
     int aggregate(int c, int b) {
+        CHECK(ahead == 0 || enqueued == std::min(total, done + ahead), "%s: %d of %d copies are enqueued before the kernels of chunk %d", what, enqueued, total, c);
+        ++done;
         if (whole) {
             CHECK(before(unpacked, compute), "%s: chunk %d is unpacked while other entries are in use", what, c);
             unpacked = tick(compute);
@@ -411,7 +415,12 @@ void check_schedule() {
                 {
                     StreamedPass<Recorder> p(ops, state, cs, xs, path);
                     int rc = p.begin();
-                    for (int i = 0; i < 5 && rc == 0; ++i) rc = p.streamed(chunk++);
+                    std::vector<int> chunks;
+                    for (int i = 0; i < 9; ++i) chunks.push_back(rng.next() % 4 == 0 ? -1 - i : chunk++);       // negative: resident
+                    ops.enqueued = ops.done = 0;
+                    ops.ahead = path.dma ? std::min(state.buffers, 2) : 0;
+                    ops.total = (int)std::count_if(chunks.begin(), chunks.end(), [](int c) { return c >= 0; });
+                    if (rc == 0) rc = p.run(chunks, [](int c) { return c < 0; }, [&](int) { return ops.fails() ? -1 : 0; });
                     ops.fail_in = -1;
                     if (rc == 0) CHECK(p.end() == 0, "%s: the pass does not end", what);
                 }

@@ -1037,10 +1037,7 @@ static int chunked_multi(ntp_graph_t* g, int direction, int32_t n_rhs,
     HipPass ops{g, *F.m, &F == &g->form[1], with_val, cs, run_all};
     StreamedPass<HipPass> pass(ops, g->staged, cs, xs, pick_copy_path(bytes * each, (double)largest, entries * each, lines, n_rhs, packed));
     if (!F.all_resident) rc = pass.begin();
-    for (auto& c : F.plan.chunks) {
-        if (rc != NTP_OK) return rc;
-        rc = c.d_image ? run_all(c, c.d_image, c.d_image) : pass.streamed(c);
-    }
+    if (rc == NTP_OK) rc = pass.run(F.plan.chunks, [](const Chunk& c) { return c.d_image != nullptr; }, [&](const Chunk& c) { return run_all(c, c.d_image, c.d_image); });
     if (rc == NTP_OK && !F.all_resident) rc = pass.end();
     if (rc != NTP_OK) return rc;
     if (!scatter && F.one_reduce())
