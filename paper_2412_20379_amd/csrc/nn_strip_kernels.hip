@@ -258,7 +258,8 @@ __device__ __forceinline__ void store_unit(const StripArgs& g, const f32x16 (&ac
         const auto out = __builtin_amdgcn_make_buffer_rsrc(static_cast<T*>(g.C) + row0 * g.ldc, 0, rows * pitch, 0x00020000);
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            const int col = cb + j * 32 + r, off = col < N ? 4 * h * pitch + 4 * col : 0x7fff0000;
+            const int col = cb + j * 32 + r;
+            const unsigned off = col < N ? 4 * h * pitch + 4 * col : 0x7fff0000;       // (unsigned: the sums below pass 2^31 there)
             auto put = [&](auto&& store) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
