@@ -211,13 +211,21 @@ __global__ void __launch_bounds__(256) write_entries_kernel(const u64* __restric
     }
 }
 
+// Row lengths and the longest.  Bound by the additions to one address, so there is one a block and few blocks: 169,343 rows 33 -> 6 us with one a wavefront
+// of 64 rows before.
 __global__ void __launch_bounds__(256) degrees_kernel(const int64_t* __restrict__ rowptr, int64_t n, int32_t* __restrict__ deg, int32_t* __restrict__ most) {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int d = v < n ? (int)(rowptr[v + 1] - rowptr[v]) : 0;
-    if (v < n) deg[v] = d;
+    __shared__ int32_t longest[4];
+    int m = 0;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256) {
+        const int d = (int)(rowptr[v + 1] - rowptr[v]);
+        deg[v] = d;
+        m = max(m, d);
+    }
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) d = max(d, __shfl_xor(d, off));
-    if ((threadIdx.x & 63) == 0) atomicMax(most, d);
+    for (int off = 32; off >= 1; off >>= 1) m = max(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) longest[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax(most, max(max(longest[0], longest[1]), max(longest[2], longest[3])));
 }
 
 __global__ void __launch_bounds__(256) column_counts_kernel(const int32_t* __restrict__ colidx, int64_t nnz, int32_t* __restrict__ counts) {
@@ -318,7 +326,7 @@ int build_device_forms(int64_t n, int64_t n_edges, const int32_t* src, const int
     hipLaunchKernelGGL(count_entries_kernel, dim3((unsigned)tiles), dim3(256), 0, nullptr, a, raw, keep, kept);
     hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(256), 0, nullptr, kept, (int)tiles, &d_result->total);
     hipLaunchKernelGGL(write_entries_kernel, dim3((unsigned)tiles), dim3(256), 0, nullptr, a, raw, n, keep, kept, &d_result->total, rowptr[0], out->colidx[0], want_csc ? b : nullptr);
-    hipLaunchKernelGGL(degrees_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, nullptr, rowptr[0], n, out->degree[0], &d_result->most[0]);
+    hipLaunchKernelGGL(degrees_kernel, dim3(std::min(blocks_for(n, 256), 256u)), dim3(256), 0, nullptr, rowptr[0], n, out->degree[0], &d_result->most[0]);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpy(&result, d_result, sizeof result, hipMemcpyDeviceToHost));
     if (result.bad != ~0ull) {
@@ -349,7 +357,7 @@ int build_device_forms(int64_t n, int64_t n_edges, const int32_t* src, const int
         } else {
             hipLaunchKernelGGL(zero_kernel, dim3(few_blocks(2 * n)), dim3(256), 0, nullptr, reinterpret_cast<int32_t*>(rowptr[1]), 2 * (n + 1));
         }
-        hipLaunchKernelGGL(degrees_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, nullptr, rowptr[1], n, out->degree[1], &d_result->most[1]);
+        hipLaunchKernelGGL(degrees_kernel, dim3(std::min(blocks_for(n, 256), 256u)), dim3(256), 0, nullptr, rowptr[1], n, out->degree[1], &d_result->most[1]);
         // the same structure has the same weights
         hipLaunchKernelGGL(compare_kernel, dim3(few_blocks(nnz)), dim3(256), 0, nullptr, out->colidx[0], out->colidx[1], nnz, &d_result->differ);
         hipLaunchKernelGGL(compare_kernel, dim3(few_blocks(n)), dim3(256), 0, nullptr, out->degree[0], out->degree[1], n, &d_result->differ);
