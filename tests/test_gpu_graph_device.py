@@ -24,6 +24,10 @@ def _edges(n, m, kind, seed):
         src, dst = src // 2, n - 1 - dst // 2
     if kind == "hub":
         dst[rng.random(m) < 0.5] = 7
+    if kind == "one source":
+        src[:] = n // 3
+    if kind == "source hub":
+        src[rng.random(m) < 0.3] = n - 1
     if kind == "both ways":            # a directed edge list that is its own transpose
         src, dst = np.concatenate([src, dst]), np.concatenate([dst, src])
     return src, dst
@@ -38,7 +42,8 @@ def _same(g, h, which):
 
 # 24,576 edges are the fewest that the device takes; 2 vertices: one bit an id; 65,536 and 65,537: 16 and 17 bits; many vertices: rows without entries
 @pytest.mark.parametrize("n,m,kind", [(2, 24576, "even"), (300, 70001, "even"), (5000, 40960, "hub"), (65536, 24577, "even"), (65537, 90000, "skewed"),
-                                      (700001, 24576, "even"), (20000, 30000, "both ways"), (300001, 24576, "low ids"), (100001, 30000, "bipartite")])
+                                      (700001, 24576, "even"), (20000, 30000, "both ways"), (300001, 24576, "low ids"), (100001, 30000, "bipartite"),
+                                      (5000, 40960, "source hub"), (70001, 24577, "one source")])
 def test_device_build_gives_the_host_builds_arrays(n, m, kind):
     src, dst = _edges(n, m, kind, n + m)
     for used in itertools.product([0, 1], repeat=4):
@@ -83,6 +88,14 @@ def test_long_runs_of_empty_rows_take_no_longer(kind, flags):
     n, m = 5_000_000, 100_000
     even, runs = (_build_seconds(n, *_edges(n, m, k, 3), flags) for k in ("even", kind))
     assert runs <= 2 * even, (runs, even)
+
+
+def test_many_edges_of_one_source_take_no_longer():
+    """out-degrees without the form by source: a fifth more time than with the sources spread out at most, and what a test's clock needs (15 times where
+    every edge was an addition to memory)"""
+    n, m = 100_000, 4_000_000
+    even, one = (_build_seconds(n, *_edges(n, m, k, 3), ntp.NTP_SCATTER_BWD) for k in ("even", "one source"))
+    assert one <= 1.2 * even + 2e-3, (one, even)
 
 
 def test_export_while_a_stream_is_captured():
