@@ -130,7 +130,11 @@ int ntp_graph_info(const ntp_graph_t* g, int64_t* n_vertices, int64_t* nnz,
                    int32_t* n_chunks, int32_t* is_symmetric, int64_t* max_degree);
 
 /* Copy one compressed form to host arrays (rowptr[n+1] int64, colidx[nnz] int32,
- * val[nnz] fp32), for bit-exact comparison.  Any of the three may be NULL. */
+ * val[nnz] fp32), for bit-exact comparison.  Any of the three may be NULL.
+ * Graphs without a budget, NTP_FORCE_STREAM, NTP_HOST_ONLY, NTP_EDGE_PERM or caller weights may have
+ * their colidx and val on the device only: the call then copies them from there, whichever device is
+ * current and also while a stream is being captured, waits for these copies alone, and returns
+ * NTP_EHIP where the device no longer answers. */
 int ntp_graph_export(const ntp_graph_t* g, int which,
                      int64_t* rowptr, int32_t* colidx, float* val);
 

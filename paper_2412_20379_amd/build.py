@@ -20,7 +20,7 @@ NATIVE_SRC = os.path.join(CSRC, "py_native.cpp")
 NATIVE = os.path.join(PKG, "_native" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))       # Python entry to the enqueue calls
 
 SOURCES = ["graph_build.cpp", "graph_device.hip", "plan.cpp", "ntp_api.hip", "agg_kernels.hip", "scatter_kernels.hip", "chunk_kernels.hip", "attention_kernels.hip", "attention_scores_kernels.hip", "loss_kernels.hip", "nn_kernels.hip", "nn_strip_kernels.hip", "nn_resident_kernels.hip", "nn_dw_kernels.hip"]
-HEADERS = [os.path.join(CSRC, "ntp_internal.h"), os.path.join(CSRC, "lane_util.h"), os.path.join(CSRC, "nn_util.h"), os.path.join(CSRC, "chunk_schedule.h"), os.path.join(CSRC, "row_copies.h"), os.path.join(ROOT, "include", "ntp.h")]
+HEADERS = [os.path.join(CSRC, "ntp_internal.h"), os.path.join(CSRC, "lane_util.h"), os.path.join(CSRC, "nn_util.h"), os.path.join(CSRC, "chunk_schedule.h"), os.path.join(CSRC, "row_copies.h"), os.path.join(CSRC, "entry_export.h"), os.path.join(ROOT, "include", "ntp.h")]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
           "-ffp-contract=off", "-Wall", "-Wno-unused-function"]

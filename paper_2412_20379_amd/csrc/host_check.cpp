@@ -1,4 +1,4 @@
-// Stand-alone driver for the host side of libntp (graph_build.cpp, plan.cpp, chunk_schedule.h, row_copies.h): builds
+// Stand-alone driver for the host side of libntp (graph_build.cpp, plan.cpp, chunk_schedule.h, row_copies.h, entry_export.h): builds
 // graphs for every combination of the build flags, plans them with several chunk sizes and checks
 // the structural invariants of the result; runs the streaming schedule on recorded streams, with
 // failures at every step, and checks the order of every access to the staging buffers.  It links no device code, so it can be compiled
@@ -14,6 +14,7 @@
 #include <algorithm>
 
 #include "chunk_schedule.h"
+#include "entry_export.h"
 #include "ntp_internal.h"
 #include "row_copies.h"
 
@@ -223,6 +224,66 @@ void check_row_copies() {
         CHECK(l.slices == (d == 2) && (l.bytes > 0) == (d == 2), "copies: rows of %d entries, %zu bytes", d, l.bytes);
         CHECK(l.off_lists <= (size_t)m.nnz * 20, "copies: %zu bytes for %" PRId64 " entries", l.off_lists, m.nnz);
     }
+}
+
+// Entries read back from chunks' images: with the graph's device current during the copies, the caller's and its capture mode afterwards, and
+// every copy waited for, whichever call fails
+struct HostExport {
+    int device = 0, fail_in = -1, enqueued = 0;
+    bool relaxed = false, mode_failed = false, set_failed = false;
+    std::vector<std::pair<void*, std::pair<const void*, size_t>>> pending;
+    bool fails() { return fail_in >= 0 && fail_in-- == 0; }
+    int exchange_capture_mode() { if (fails()) { mode_failed = true; return -1; } relaxed = !relaxed; return 0; }
+    int current_device(int* d) { if (fails()) return -1; *d = device; return 0; }
+    int set_device(int d) { if (fails()) { set_failed = true; return -1; } device = d; return 0; }
+    int begin() { return fails() ? -1 : 0; }
+    int copy(void* dst, const void* src, size_t bytes) {
+        CHECK(relaxed && device == 3, "export: a copy with device %d current, capture mode %d", device, (int)relaxed);
+        if (fails()) return -1;
+        pending.push_back({dst, {src, bytes}});
+        return 0;
+    }
+    int finish() {
+        const bool f = fails();
+        for (auto& p : pending) memcpy(p.first, p.second.first, p.second.second);
+        pending.clear();
+        return f ? -1 : 0;
+    }
+};
+
+void check_export() {
+    HostSparse m;
+    m.n = 40;
+    for (int64_t v = 0; v <= m.n; ++v) m.rowptr.push_back(v * 7);
+    m.nnz = 7 * m.n;
+    Plan P;
+    make_plan(m, 50, &P);
+    std::vector<std::vector<char>> images;
+    for (Chunk& c : P.chunks) {
+        images.emplace_back(c.img_bytes);
+        c.d_image = images.back().data();
+        for (int64_t e = c.e_begin; e < c.e_end; ++e) {
+            reinterpret_cast<int32_t*>(c.d_image + c.img_off_colidx)[e - c.e_begin] = (int32_t)(3 * e + 1);
+            reinterpret_cast<float*>(c.d_image + c.img_off_val)[e - c.e_begin] = (float)e / 2;
+        }
+    }
+    CHECK(P.chunks.size() > 3, "export: %zu chunks", P.chunks.size());
+    for (int current : {3, 0, 5})
+        for (int parts = 0; parts < 4; ++parts)
+            for (int fail = -1; fail < 24; ++fail) {
+                HostExport ops;
+                ops.device = current;
+                ops.fail_in = fail;
+                std::vector<int32_t> colidx((size_t)m.nnz, -7);
+                std::vector<float> val((size_t)m.nnz, -7.f);
+                const int rc = read_entries(ops, 3, P.chunks, parts & 1 ? colidx.data() : nullptr, parts & 2 ? val.data() : nullptr);
+                const bool failed = fail >= 0 && ops.fail_in < 0;
+                CHECK((rc != 0) == failed, "export: status %d, failure at call %d", rc, fail);
+                CHECK(ops.pending.empty(), "export: copies nobody waited for");
+                CHECK((ops.set_failed || ops.device == current) && (ops.mode_failed || !ops.relaxed), "export: device %d instead of %d current afterwards", ops.device, current);
+                for (int64_t e = 0; e < m.nnz && !failed; ++e)
+                    CHECK(colidx[(size_t)e] == (parts & 1 ? (int32_t)(3 * e + 1) : -7) && val[(size_t)e] == (parts & 2 ? (float)e / 2 : -7.f), "export: entry %" PRId64, e);
+            }
 }
 
 // segments combine their row's slots where that is little work: not a row of a thousand segments, nor many rows
@@ -611,6 +672,8 @@ int main() {
     check_segments_combine();
     // 8. which rows a lane group sums
     check_lane_groups();
+    // 9. entries read back from the device
+    check_export();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");
     return 0;

@@ -11,6 +11,7 @@
 #include <new>
 
 #include "chunk_schedule.h"
+#include "entry_export.h"
 #include "ntp_internal.h"
 #include "row_copies.h"
 
@@ -60,13 +61,14 @@ struct ntp_graph {
     BuiltGraph g;
     Form form[2];                  // NTP_CSR, NTP_CSC (unused when symmetric)
     bool host_only = false;
+    int device = -1;               // where it was built
     bool pinned_entries = false;
     bool val_pinned = false;       // the weights are in pinned memory too (caller weights on a graph that may stream)
     // staging for streamed chunks
     char* stage_memory = nullptr;                   // two images of the largest chunk, or, where ids travel packed, its entries and, behind them, the
     char* stage[MAX_BUFFERS] = {};                  // staging buffers (row pointers, lists and packed ids of a chunk)
     char* stage_entries = nullptr;
-    StageState<HipPass> staged;                     // streams, events and the state of the two buffers
+    StageState<HipPass> staged;                     // streams, events and the state of the buffers
     char* pinned_meta = nullptr;                    // metas of streamed chunks
     char* pinned_ids = nullptr;                     // row pointers, lists and packed column ids of streamed chunks
     int id_bits = 0;
@@ -145,40 +147,29 @@ int fill_chunk(const DeviceForms& forms, int k, int val_mode, const Chunk& c, ch
 }
 
 // A stream for copies to the host that are independent of everything else, one per device (creating and destroying one takes 0.3 ms)
-hipError_t export_stream(hipStream_t* out) {
+int export_stream(int dev, hipStream_t* out) {
     constexpr int MAX_DEVICES = 64;
     static std::mutex mu;
     static hipStream_t streams[MAX_DEVICES] = {nullptr};
-    int dev = -1;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= MAX_DEVICES) return hipErrorInvalidDevice;
+    if (dev < 0 || dev >= MAX_DEVICES) { set_error("device ordinal %d outside 0..%d", dev, MAX_DEVICES - 1); return NTP_EUNSUPPORTED; }
     std::lock_guard<std::mutex> lock(mu);
-    if (!streams[dev]) e = hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking);
+    if (!streams[dev]) HIP_TRY(hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking));
     *out = streams[dev];
-    return e;
-}
-
-// a form's entries from the images of its chunks (a graph built on the device has no others); also while a stream is being captured
-int read_entries(const Form& F, int32_t* colidx, float* val) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
-    hipStream_t st = nullptr;
-    hipError_t e = export_stream(&st);
-    const bool begun = e == hipSuccess;
-    for (const Chunk& c : F.plan.chunks) {
-        const size_t bytes = (size_t)(c.e_end - c.e_begin) * 4;
-        if (bytes && colidx && e == hipSuccess) e = hipMemcpyAsync(colidx + c.e_begin, c.d_image + c.img_off_colidx, bytes, hipMemcpyDeviceToHost, st);
-        if (bytes && val && e == hipSuccess) e = hipMemcpyAsync(val + c.e_begin, c.d_image + c.img_off_val, bytes, hipMemcpyDeviceToHost, st);
-    }
-    if (begun) {
-        const hipError_t done = hipStreamSynchronize(st);
-        if (e == hipSuccess) e = done;
-    }
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    HIP_TRY(e);
     return NTP_OK;
 }
+
+// What read_entries does on the device
+struct HipExport {
+    int device;
+    hipStream_t st = nullptr;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    int exchange_capture_mode() { HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode)); return NTP_OK; }
+    int current_device(int* d) { HIP_TRY(hipGetDevice(d)); return NTP_OK; }
+    int set_device(int d) { HIP_TRY(hipSetDevice(d)); return NTP_OK; }
+    int begin() { return export_stream(device, &st); }
+    int copy(void* dst, const void* src, size_t bytes) { HIP_TRY(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st)); return NTP_OK; }
+    int finish() { HIP_TRY(hipStreamSynchronize(st)); return NTP_OK; }
+};
 
 // a resident chunk's image
 int upload_chunk(const HostSparse& m, const Chunk& c, char* dst) {
@@ -637,6 +628,7 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
     if (!G) { set_error("out of host memory"); return NTP_ENOMEM; }
     std::unique_ptr<ntp_graph, void (*)(ntp_graph*)> guard(G, destroy);   // frees everything on any early return
     G->host_only = flags & NTP_HOST_ONLY;
+    if (!G->host_only) HIP_TRY(hipGetDevice(&G->device));
     const bool force_stream = flags & NTP_FORCE_STREAM;
     const bool weighted = edge_weight != nullptr;
     StreamRequest request{n, budget, chunk_edges, (flags & NTP_SCATTER_BWD) || ((flags & NTP_SYMMETRISE) && !weighted) ? 1 : 2, force_stream, weighted};
@@ -889,7 +881,10 @@ int ntp_graph_export(const ntp_graph_t* g, int which, int64_t* rowptr, int32_t* 
     if (which == NTP_CSC && g->scatter_bwd()) { set_error("graph was built with NTP_SCATTER_BWD: no by-source form is stored"); return NTP_EUNSUPPORTED; }
     const HostSparse& m = *g->f(which).m;
     if (rowptr) memcpy(rowptr, m.rowptr.data(), (size_t)(m.n + 1) * 8);
-    if (m.nnz && !m.colidx) return read_entries(g->f(which), colidx, val);
+    if (m.nnz && !m.colidx) {
+        HipExport ops{g->device};
+        return read_entries(ops, g->device, g->f(which).plan.chunks, colidx, val);
+    }
     if (colidx && m.nnz) memcpy(colidx, m.colidx, (size_t)m.nnz * 4);
     if (val && m.nnz) memcpy(val, m.val, (size_t)m.nnz * 4);
     return NTP_OK;
