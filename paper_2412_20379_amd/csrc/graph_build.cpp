@@ -490,4 +490,23 @@ bool build_edge_perm(const BuiltGraph& G, int32_t* perm) {
     return transpose_order<int32_t>(W, R, colptr, counts.data(), [&](int64_t p, int64_t e, int32_t) { perm[p] = (int32_t)e; });
 }
 
+BuildArena plan_build_arena(int64_t n, int64_t n_edges, uint32_t flags) {
+    const bool symmetrise = flags & NTP_SYMMETRISE, want_csc = !symmetrise && !(flags & NTP_SCATTER_BWD);
+    BuildArena a;
+    a.raw = n_edges * (symmetrise ? 2 : 1) + (flags & NTP_ADD_SELF_LOOPS ? n : 0);
+    a.row_pointers = want_csc ? 2 : 1;
+    a.degrees = symmetrise ? 1 : 2;
+    const size_t tiles = (size_t)((a.raw + BUILD_TILE - 1) / BUILD_TILE), radix = (size_t)1 << BUILD_RADIX_BITS;
+    auto take = [&](size_t bytes) { const size_t at = a.bytes; a.bytes += (bytes + 255) / 256 * 256; return at; };
+    for (size_t& k : a.keys) k = take((size_t)a.raw * 8);
+    if (want_csc) a.colidx = take((size_t)a.raw * 4);
+    for (int k = 0; k < a.row_pointers; ++k) a.rowptr[k] = take((size_t)(n + 1) * 8);
+    for (int k = 0; k < a.degrees; ++k) a.degree[k] = take((size_t)n * 4);
+    a.counts = take(tiles * radix * 4);
+    a.totals = take(radix * 4);
+    a.kept = take(tiles * 4);
+    a.result = take(BUILD_RESULT_BYTES);
+    return a;
+}
+
 }  // namespace ntp

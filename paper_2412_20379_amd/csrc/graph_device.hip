@@ -20,8 +20,8 @@ namespace ntp {
 
 namespace {
 
-constexpr int RADIX_BITS = 9, RADIX = 1 << RADIX_BITS;
-constexpr int ITEMS = 16, TILE = 256 * ITEMS;
+constexpr int RADIX_BITS = BUILD_RADIX_BITS, RADIX = 1 << RADIX_BITS;
+constexpr int TILE = BUILD_TILE, ITEMS = TILE / 256;
 typedef unsigned long long u64;
 
 __global__ void __launch_bounds__(256) make_keys_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t edges, int64_t n, int bits,
@@ -331,35 +331,24 @@ int build_device_forms(int64_t n, int64_t n_edges, const int32_t* src, const int
     const bool symmetrise = flags & NTP_SYMMETRISE, dedup = flags & NTP_DEDUP, loops = flags & NTP_ADD_SELF_LOOPS;
     const bool want_csc = !symmetrise && !(flags & NTP_SCATTER_BWD);
     const int bits = bits_of_ids(n);
-    const int64_t raw = n_edges * (symmetrise ? 2 : 1) + (loops ? n : 0);
+    const BuildArena arena = plan_build_arena(n, n_edges, flags);
+    const int64_t raw = arena.raw;
     const int64_t tiles = (raw + TILE - 1) / TILE;
 
-    // One piece of device memory: keys twice, row pointers and degrees of both forms, counts.  The edges, and the column ids of the form that is made
-    // last, lie in keys that are not in use.
-    size_t at = 0;
-    auto take = [&](size_t bytes) { const size_t o = at; at += (bytes + 255) / 256 * 256; return o; };
-    const size_t o_a = take((size_t)raw * 8), o_b = take((size_t)raw * 8), o_col = take(want_csc ? (size_t)raw * 4 : 0);
-    size_t o_ptr[2], o_deg[2];
-    for (int k = 0; k < 2; ++k) {
-        o_ptr[k] = take((size_t)(n + 1) * 8);
-        o_deg[k] = take((size_t)n * 4);
-    }
-    const size_t o_counts = take((size_t)tiles * RADIX * 4), o_totals = take(RADIX * 4), o_kept = take((size_t)tiles * 4), o_result = take(64);
-    // (what is left holds the graph: 8 bytes an entry and 12 a row, where this takes 16 and 24)
+    // (an arena's size is left for the graph, which takes less in one chunk)
     size_t free_bytes = 0, all_bytes = 0;
     void* p = nullptr;
-    if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || free_bytes / 2 < at || hipMalloc(&p, at) != hipSuccess) { (void)hipGetLastError(); return DEVICE_BUILD_NO_MEMORY; }
+    if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess || free_bytes / 2 < arena.bytes || hipMalloc(&p, arena.bytes) != hipSuccess) { (void)hipGetLastError(); return DEVICE_BUILD_NO_MEMORY; }
     char* const base = out->arena = static_cast<char*>(p);
-    u64 *a = reinterpret_cast<u64*>(base + o_a), *b = reinterpret_cast<u64*>(base + o_b);
+    u64 *a = reinterpret_cast<u64*>(base + arena.keys[0]), *b = reinterpret_cast<u64*>(base + arena.keys[1]);
     int32_t *d_src = reinterpret_cast<int32_t*>(b), *d_dst = d_src + n_edges;
-    int32_t *counts = reinterpret_cast<int32_t*>(base + o_counts), *totals = reinterpret_cast<int32_t*>(base + o_totals), *kept = reinterpret_cast<int32_t*>(base + o_kept);
+    int32_t *counts = reinterpret_cast<int32_t*>(base + arena.counts), *totals = reinterpret_cast<int32_t*>(base + arena.totals), *kept = reinterpret_cast<int32_t*>(base + arena.kept);
     struct Result { u64 bad, differ; int32_t total, most[2], pad; };
-    Result* const d_result = reinterpret_cast<Result*>(base + o_result);
-    int64_t* rowptr[2];
-    for (int k = 0; k < 2; ++k) {
-        rowptr[k] = reinterpret_cast<int64_t*>(base + o_ptr[k]);
-        out->degree[k] = reinterpret_cast<int32_t*>(base + o_deg[k]);
-    }
+    Result* const d_result = reinterpret_cast<Result*>(base + arena.result);
+    static_assert(sizeof(Result) <= BUILD_RESULT_BYTES, "the arena holds it");
+    int64_t* rowptr[2] = {nullptr, nullptr};
+    for (int k = 0; k < arena.row_pointers; ++k) rowptr[k] = reinterpret_cast<int64_t*>(base + arena.rowptr[k]);
+    for (int k = 0; k < arena.degrees; ++k) out->degree[k] = reinterpret_cast<int32_t*>(base + arena.degree[k]);
     Result result{~0ull, ~0ull, 0, {0, 0}, 0};
     HIP_TRY(hipMemcpy(d_result, &result, sizeof result, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(d_src, src, (size_t)n_edges * 4, hipMemcpyHostToDevice));
@@ -367,7 +356,7 @@ int build_device_forms(int64_t n, int64_t n_edges, const int32_t* src, const int
     hipLaunchKernelGGL(make_keys_kernel, dim3(blocks_for(n_edges + (loops ? n : 0), 256)), dim3(256), 0, nullptr, d_src, d_dst, n_edges, n, bits, symmetrise, loops, a, &d_result->bad);
     sort_keys(&a, &b, raw, 0, 2 * bits, counts, totals);
     const Keep keep{dedup, loops, bits};
-    out->colidx[0] = want_csc ? reinterpret_cast<int32_t*>(base + o_col) : reinterpret_cast<int32_t*>(b);
+    out->colidx[0] = want_csc ? reinterpret_cast<int32_t*>(base + arena.colidx) : reinterpret_cast<int32_t*>(b);
     write_form(a, raw, n, keep, kept, &d_result->total, rowptr[0], out->colidx[0], want_csc ? b : nullptr);
     hipLaunchKernelGGL(degrees_kernel, dim3(std::min(blocks_for(n, 256), 256u)), dim3(256), 0, nullptr, rowptr[0], n, out->degree[0], &d_result->most[0]);
     HIP_TRY(hipGetLastError());

@@ -226,6 +226,41 @@ void check_row_copies() {
     }
 }
 
+// The memory of a build on the device: parts that do not overlap, nothing that its graph does not need, and no less than the graph's images take, as
+// that is how much is left for them
+void check_build_arena() {
+    for (int64_t n : {(int64_t)2, (int64_t)300, (int64_t)100003})
+        for (int64_t m : {(int64_t)24576, (int64_t)700001})
+            for (uint32_t flags : {0u, (uint32_t)NTP_SYMMETRISE, (uint32_t)NTP_SCATTER_BWD, (uint32_t)(NTP_SYMMETRISE | NTP_SCATTER_BWD), (uint32_t)NTP_ADD_SELF_LOOPS,
+                                   (uint32_t)(NTP_SYMMETRISE | NTP_ADD_SELF_LOOPS)}) {
+                const BuildArena a = plan_build_arena(n, m, flags);
+                const bool symmetrise = flags & NTP_SYMMETRISE, by_source = !symmetrise && !(flags & NTP_SCATTER_BWD);
+                const size_t raw = (size_t)(m * (symmetrise ? 2 : 1) + (flags & NTP_ADD_SELF_LOOPS ? n : 0)), tiles = (raw + 4095) / 4096, N = (size_t)n;
+                CHECK(a.raw == (int64_t)raw && a.row_pointers == (by_source ? 2 : 1) && a.degrees == (symmetrise ? 1 : 2), "arena: forms");
+                std::vector<std::pair<size_t, size_t>> parts = {{a.keys[0], raw * 8}, {a.keys[1], raw * 8}, {a.rowptr[0], (N + 1) * 8}, {a.degree[0], N * 4},
+                                                               {a.counts, tiles * 512 * 4}, {a.totals, 512 * 4}, {a.kept, tiles * 4}, {a.result, (size_t)BUILD_RESULT_BYTES}};
+                if (by_source) { parts.push_back({a.colidx, raw * 4}); parts.push_back({a.rowptr[1], (N + 1) * 8}); }
+                if (!symmetrise) parts.push_back({a.degree[1], N * 4});
+                std::sort(parts.begin(), parts.end());
+                size_t end = 0;
+                for (auto& p : parts) {
+                    CHECK(p.first % 256 == 0 && p.first >= end && p.first < end + 256, "arena: a part at %zu behind %zu", p.first, end);
+                    end = p.first + p.second;
+                }
+                CHECK(a.bytes >= end && a.bytes < end + 256, "arena: %zu bytes for %zu", a.bytes, end);
+                HostSparse form;                          // all entries in one row, or as even as they go
+                form.n = n;
+                for (bool one_row : {false, true}) {
+                    form.rowptr.clear();
+                    for (int64_t v = 0; v <= n; ++v) form.rowptr.push_back(one_row ? (v > 0) * (int64_t)raw : v * (int64_t)raw / n);
+                    form.nnz = (int64_t)raw;
+                    Plan P;
+                    make_plan(form, 0, &P);
+                    CHECK((by_source ? 2 : 1) * P.max_img_bytes <= a.bytes, "arena: %zu bytes, images of %zu", a.bytes, P.max_img_bytes);
+                }
+            }
+}
+
 // Entries read back from chunks' images: with the graph's device current during the copies, the caller's and its capture mode afterwards, and
 // every copy waited for, whichever call fails
 struct HostExport {
@@ -672,7 +707,9 @@ int main() {
     check_segments_combine();
     // 8. which rows a lane group sums
     check_lane_groups();
-    // 9. entries read back from the device
+    // 9. the memory of a build on the device
+    check_build_arena();
+    // 10. entries read back from the device
     check_export();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");

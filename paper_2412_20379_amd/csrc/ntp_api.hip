@@ -613,7 +613,9 @@ const char* ntp_last_error(void) { return last_error(); }
 
 static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, const int32_t* dst,
                             const float* edge_weight, uint32_t flags, int64_t budget, int64_t chunk_edges,
-                            ntp_graph_t** out) {
+                            bool* on_the_device, ntp_graph_t** out) {
+    const bool may_use_device = *on_the_device;
+    *on_the_device = false;
     if (!out) { set_error("out is NULL"); return NTP_EINVAL; }
     *out = nullptr;
     if (n < 0 || n > INT_MAX - 1) { set_error("n_vertices %lld out of range", (long long)n); return NTP_EINVAL; }
@@ -640,12 +642,13 @@ static int graph_build_impl(int64_t n, int64_t n_edges, const int32_t* src, cons
     const bool hub_tables = hub_env && hub_env[0] == '1';
     // on the device where nothing asks for the entries on the host
     DeviceForms forms;
-    bool on_device = !G->host_only && !force_stream && budget == 0 && !weighted && !(flags & NTP_EDGE_PERM) && !hub_tables && device_build_takes(n, n_edges, flags);
+    bool on_device = may_use_device && !G->host_only && !force_stream && budget == 0 && !weighted && !(flags & NTP_EDGE_PERM) && !hub_tables && device_build_takes(n, n_edges, flags);
     int rc = on_device ? build_device_forms(n, n_edges, src, dst, flags, &G->g, &forms) : DEVICE_BUILD_NO_MEMORY;
     if (rc == DEVICE_BUILD_NO_MEMORY) {
         on_device = false;
         rc = build_host_graph(n, n_edges, src, dst, edge_weight, flags, alloc, &G->g);
     }
+    *on_the_device = on_device;
     if (rc != NTP_OK) { return rc; }
     if (G->g.symmetric && G->g.csc.colidx) { free_entries(G->g.csc, G->pinned_entries, G->val_pinned); G->g.csc = HostSparse(); }
 
@@ -852,7 +855,14 @@ int ntp_graph_build(int64_t n, int64_t n_edges, const int32_t* src, const int32_
                     const float* edge_weight, uint32_t flags, int64_t budget, int64_t chunk_edges,
                     ntp_graph_t** out) {
     try {       // no C++ exception may cross the C boundary
-        return graph_build_impl(n, n_edges, src, dst, edge_weight, flags, budget, chunk_edges, out);
+        // a build on the device holds memory until the images are made: where they lack it (many small chunks) the host's threads build once more
+        bool on_device = true;
+        int rc = graph_build_impl(n, n_edges, src, dst, edge_weight, flags, budget, chunk_edges, &on_device, out);
+        if (rc == NTP_ENOMEM && on_device) {
+            on_device = false;
+            rc = graph_build_impl(n, n_edges, src, dst, edge_weight, flags, budget, chunk_edges, &on_device, out);
+        }
+        return rc;
     } catch (const std::bad_alloc&) {
         set_error("out of host memory while building the graph");
         if (out) *out = nullptr;

@@ -80,6 +80,16 @@ struct DeviceForms {
     DeviceForms(const DeviceForms&) = delete;
     ~DeviceForms() { release(); }
 };
+// Its device memory: keys twice, what both forms need of column ids, row pointers and degrees, counts.  The edges, and the column ids of the form that
+// is made last, lie in keys that are not in use.  Bytes an entry (input edges, reversed copies and self loops) and a row, about: 16.5 and 12 symmetrised,
+// 20.5 and 24 with a form by source, 16.5 and 16 with its row lengths only.
+constexpr int BUILD_RADIX_BITS = 9, BUILD_TILE = 4096, BUILD_RESULT_BYTES = 64;
+struct BuildArena {
+    int64_t raw = 0;                                // keys
+    int row_pointers = 1, degrees = 1;              // forms that have them
+    size_t keys[2] = {0, 0}, colidx = 0, rowptr[2] = {0, 0}, degree[2] = {0, 0}, counts = 0, totals = 0, kept = 0, result = 0, bytes = 0;
+};
+BuildArena plan_build_arena(int64_t n, int64_t n_edges, uint32_t flags);
 enum { DEVICE_BUILD_NO_MEMORY = 1 };                // (no error: the host builds)
 bool device_build_takes(int64_t n, int64_t n_edges, uint32_t flags);
 int build_device_forms(int64_t n, int64_t n_edges, const int32_t* src, const int32_t* dst, uint32_t flags, BuiltGraph* g, DeviceForms* out);
