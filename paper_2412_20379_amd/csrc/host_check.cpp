@@ -587,13 +587,13 @@ static void check_pack_ids() {
             m.colidx = ids.data();
             for (int64_t e_begin : {(int64_t)0, nnz / 3}) {
                 const int64_t e_end = e_begin == 0 ? nnz : nnz - nnz / 5, count = e_end - e_begin;
-                std::vector<uint32_t> offsets;
-                const int64_t words = plan_packed_ids(m, e_begin, e_end, bits, &offsets);
+                PackedIds plan;
+                const int64_t words = plan_packed_ids(m, e_begin, e_end, bits, &plan);
                 for (int64_t shift : {0, 4, 8, 12})       // the weights' part of a chunk's image takes them
                     CHECK(shift + words * 4 <= (shift + count * 4 + 255) / 256 * 256, "%" PRId64 " words for %" PRId64 " ids", words, count);
                 CHECK(words <= (count * bits + 31) / 32 + 4 * ((count + 255) / 256) + 3, "%" PRId64 " words for %" PRId64 " ids of %d bits", words, count, bits);
                 std::vector<uint32_t> packed((size_t)words, 0xffffffffu);
-                pack_ids(m, e_begin, e_end, bits, offsets, packed.data());
+                pack_ids(m, e_begin, e_end, bits, plan, packed.data());
                 int64_t wrong = 0;
                 for (int64_t b = 0; b * PACK_BLOCK < count; ++b) {
                     const int64_t len = std::min<int64_t>(PACK_BLOCK, count - b * PACK_BLOCK);

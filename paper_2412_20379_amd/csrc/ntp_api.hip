@@ -230,15 +230,15 @@ int64_t streamed_bytes(const Chunk& c, bool with_val) {
 int pack_streamed_ids(ntp_graph* G, int n_forms, size_t stage_bytes) {
     int64_t bytes = 0;
     size_t most = 0, entries = 0;
-    std::vector<std::vector<uint32_t>> offsets;
+    std::vector<PackedIds> plans;
     auto each = [&](auto&& f) {
         for (int k = 0; k < n_forms; ++k)
             for (auto& c : G->form[k].plan.chunks)
                 if (!c.d_image) f(*G->form[k].m, c);
     };
     each([&](const HostSparse& m, Chunk& c) {
-        offsets.emplace_back();
-        if (c.e_end > c.e_begin) c.packed_id_bytes = plan_packed_ids(m, c.e_begin, c.e_end, G->id_bits, &offsets.back()) * 4;
+        plans.emplace_back();
+        if (c.e_end > c.e_begin) c.packed_id_bytes = plan_packed_ids(m, c.e_begin, c.e_end, G->id_bits, &plans.back()) * 4;
         const size_t size = (c.meta.size() + (size_t)c.packed_id_bytes + 255) / 256 * 256;
         bytes += (int64_t)size;
         most = std::max(most, size);
@@ -255,7 +255,7 @@ int pack_streamed_ids(ntp_graph* G, int n_forms, size_t stage_bytes) {
         memcpy(c.h_meta_pinned, c.meta.data(), c.meta.size());
         if (c.packed_id_bytes > 0) {
             c.h_packed_ids = c.h_meta_pinned + c.meta.size();
-            pack_ids(m, c.e_begin, c.e_end, G->id_bits, offsets[k], reinterpret_cast<uint32_t*>(c.h_packed_ids));
+            pack_ids(m, c.e_begin, c.e_end, G->id_bits, plans[k], reinterpret_cast<uint32_t*>(c.h_packed_ids));
         }
         ++k;
         off += (int64_t)((c.meta.size() + (size_t)c.packed_id_bytes + 255) / 256 * 256);

@@ -396,8 +396,12 @@ int launch_stage_chunk(const void* const src[3], void* const dst[3], const int64
 // one at place (z >> l) + i of a bit string, in whole words; its l low bits, one entry after the other from a whole word on.  PACK_PLAIN: the ids, `bits`
 // bits each.  Two spare words follow the last block.
 constexpr int PACK_BLOCK = 256, PACK_PLAIN = 32;
-int64_t plan_packed_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, std::vector<uint32_t>* offsets);      // words in all
-void pack_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, const std::vector<uint32_t>& offsets, uint32_t* packed);
+struct PackedIds {
+    std::vector<uint32_t> offsets;       // of each block and of the end
+    std::vector<uint8_t> low_bits;       // l of each block
+};
+int64_t plan_packed_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, PackedIds* plan);      // words in all
+void pack_ids(const HostSparse& m, int64_t e_begin, int64_t e_end, int bits, const PackedIds& plan, uint32_t* packed);
 int launch_unpack_ids(const uint32_t* packed, int bits, int64_t n_cols, int64_t n, int32_t* ids, void* stream);
 
 // val[e] of a chunk's entries from the structure (VAL_GCN / VAL_ONES): rowptr is the chunk's slice
