@@ -571,15 +571,28 @@ int launch_strip(StripArgs g, const StripPlan& p, hipStream_t st) {
 // (1,000) 23.8 / 32.3, on 12,000 (1,500) 32.7 / 33.3, on 16,000 40.6 / 34.6; 256 -> 64 on 16,000 (1,000) 10.0 / 15.8, on 24,000
 // (1,500) 16.6 / 16.4; 256 -> 256 on 4,000 (1,000) 9.9 / 15.7, on 8,000 (2,000) 20.2 / 16.6; 128 -> 128 on 8,000 (1,000) 7.4 /
 // 10.2, on 12,000 (1,500) 10.1 / 10.5; 1433 -> 16 on 24,000 (750) 42.2 / 60.6, on 40,000 (1,250) 63.6 / 60.9.
-// Sixteen wavefronts a block instead of eight where compute units have one block or none and there are two steps or more for each: us 8 / 16,
-// 1433 -> 16 on 2,708 rows 14.9 / 14.2 (bf16 9.6 / 8.4), 1433 -> 64 on 4,000 17.7 / 16.5 (10.1 / 8.6), 4000 -> 32 on 1,000 33.9 / 32.0 (19.3 / 16.4);
-// of 19 steps 602 -> 16 on 1,000 7.1 / 7.3, on 8,000 8.1 / 8.4.
 bool split_contraction(const StripArgs& g) { return (g.n + 31) / 32 * ((g.N + 31) / 32) <= 4 * compute_units() && g.steps >= 4; }
+
+// Sixteen wavefronts a block instead of eight where compute units have one block or none: the loads of a wavefront's steps, one after the other, are
+// what takes the time.  us 8 / 16 wavefronts:
+//   B by columns (forward): from 768 indices on.  fp32 640 -> 32 on 1,000 rows 6.8 / 7.0, 768 8.0 / 7.7, 1024 10.1 / 9.8, 1433 14.2 / 13.6, 4000 34.0 / 32.2; 1433 -> 16 on
+//   2,708 14.4 / 13.8; 768 -> 64 on 4,000 7.7 / 7.1; 768 -> 32 on 8,000 8.5 / 8.2.  bf16 512 -> 32 on 1,000 4.5 / 4.4, 768 5.6 / 5.3, 1433 9.3 / 8.0;
+//   1433 -> 16 on 2,708 9.2 / 8.0; 1433 -> 64 on 4,000 9.9 / 8.3.
+//   B by rows (dA): its vectors are loaded whole, and more wavefronts mostly meet each other's lines.  bf16 with a mask gains all the same (dA 768 -> 32 on 1,000 rows
+//   4.8 / 4.2, 1433 -> 16 on 2,708 10.8 / 10.4, 2048 -> 32 on 8,000 19.2 / 15.8), without one past 2,048 indices (2048 -> 64 on 2,700 8.2 / 9.9, 2600 10.4 /
+//   9.5; 3000 -> 16 on 2,708 8.7 / 7.1).  fp32 with a mask does not (1433 -> 16 on 2,708 13.2 / 14.1 and on 8,000 rows of 32 20.0 / 21.7; 2600 -> 32 on 6,600
+//   29.3 / 31.4), without one where most compute units have a block (1433 -> 16 on 2,708 11.6 / 12.6, 2048 14.2 / 15.8; 2048 -> 64 on 4,000 18.9 / 17.0,
+//   2048 -> 32 on 8,000 22.7 / 20.7, 1433 15.7 / 15.2).
+bool sixteen_wavefronts(const StripArgs& g, int64_t blocks, bool mask, bool bf16) {
+    if (blocks > compute_units()) return false;
+    if (!g.b_kcontig || (bf16 && mask)) return g.K > 736;
+    return !mask && g.steps > 32 && (bf16 || 2 * blocks > compute_units());
+}
 
 template <class T, Core C, bool MASK>
 int launch_split(const StripArgs& g, hipStream_t st) {
     const int64_t blocks = (g.n + 31) / 32 * ((g.N + 31) / 32);
-    if (blocks <= compute_units() && g.steps > 32) hipLaunchKernelGGL((strip_split_kernel<T, C, MASK, 16, 16>), dim3((unsigned)blocks), dim3(1024), 0, st, g);
+    if (sixteen_wavefronts(g, blocks, MASK, sizeof(T) == 2)) hipLaunchKernelGGL((strip_split_kernel<T, C, MASK, 16, 16>), dim3((unsigned)blocks), dim3(1024), 0, st, g);
     else hipLaunchKernelGGL((strip_split_kernel<T, C, MASK, 16, 8>), dim3((unsigned)blocks), dim3(512), 0, st, g);
     return NTP_OK;
 }

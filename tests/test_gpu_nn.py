@@ -67,10 +67,11 @@ def test_nn_bwd_fp32(n, k, m, act, need_dA):
         assert_close(dA.cpu().numpy(), dA_ref, _abs_scale(dZ, W.T), TOL_F32, "dA %s" % ((n, k, m),))
 
 
-@pytest.mark.parametrize("n,k,m", [(1, 1025, 1), (33, 1057, 16), (2700, 1500, 33), (600, 2049, 128), (8192, 1100, 32), (8193, 1100, 32), (70, 4100, 41)])
+@pytest.mark.parametrize("n,k,m", [(1, 1025, 1), (33, 1057, 16), (2700, 1500, 33), (600, 2049, 128), (8192, 1100, 32), (8193, 1100, 32), (70, 4100, 41),
+                                   (500, 736, 40), (500, 737, 40)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_long_contractions_of_few_rows(n, k, m, dtype):
-    """sixteen wavefronts share a unit's contraction (fp32 above 1,024 indices, bf16 above 2,048), eight where there are more units than compute units"""
+    """sixteen wavefronts share a unit's contraction above 736 indices, eight where there are more units than compute units"""
     import torch
     from gpu_util import dev_bf16_bits, host_bf16, dev_f32
     say("long contraction", n, k, m, dtype)
@@ -86,6 +87,32 @@ def test_long_contractions_of_few_rows(n, k, m, dtype):
         got, tol = host_bf16(H), TOL_BF16
     torch.cuda.synchronize()
     assert_close(got, ogcn.nn_fwd(A, W, ntp.NTP_ACT_RELU), _abs_scale(A, W), tol, "nn_fwd %s" % ((n, k, m),))
+
+
+@pytest.mark.parametrize("n,k,m", [(33, 16, 1057), (500, 40, 736), (500, 40, 737), (2700, 16, 1433), (4097, 32, 1100), (8192, 32, 1100), (8193, 32, 1100), (600, 64, 2049)])
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_long_contractions_of_few_rows_backwards(n, k, m, relu, dtype):
+    """dA = dZ W^T: sixteen wavefronts in bf16 with a mask above 736 indices, without one above 2,048; in fp32 without a mask above 1,024 where more than
+    half the compute units have a unit"""
+    import torch
+    from gpu_util import dev_bf16_bits, host_bf16, dev_f32
+    say("long contraction back", n, k, m, relu, dtype)
+    A, G, H = (gen.normal_features(n, c, seed=n + c, stream=i) for i, c in enumerate((k, m, m)))
+    W = gen.glorot_weight(k, m, seed=m)
+    act = ntp.NTP_ACT_RELU if relu else ntp.NTP_ACT_NONE
+    if dtype == "f32":
+        dA = torch.full((n, k), float("nan"), device="cuda:0")
+        ntp.ntp_nn_bwd(dev_f32(A), dev_f32(W), dev_f32(H), dev_f32(G), dA, None, n, k, m, act)
+        got, tol = dA.cpu().numpy(), TOL_F32
+    else:
+        (Ab, A), (Wb, W), (Gb, G), (Hb, H) = (dev_bf16_bits(x) for x in (A, W, G, H))
+        dA = torch.empty(n, k, dtype=torch.int16, device="cuda:0")
+        ntp.ntp_nn_bwd(Ab, Wb, Hb, Gb, dA, None, n, k, m, act, ntp.NTP_BF16)
+        got, tol = host_bf16(dA), TOL_BF16
+    torch.cuda.synchronize()
+    dZ = np.where(H > 0, G, 0) if relu else G
+    assert_close(got, dZ.astype(np.float64) @ W.astype(np.float64).T, _abs_scale(dZ, W.T), tol, "dA %s" % ((n, k, m),))
 
 
 @pytest.mark.parametrize("n", [15, 16, 17, 32, 33, 63, 127, 128, 145, 8191, 8209, 41000])
