@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <string>
 #include <vector>
 
 #include <algorithm>
@@ -319,6 +320,43 @@ void check_export() {
                 for (int64_t e = 0; e < m.nnz && !failed; ++e)
                     CHECK(colidx[(size_t)e] == (parts & 1 ? (int32_t)(3 * e + 1) : -7) && val[(size_t)e] == (parts & 2 ? (float)e / 2 : -7.f), "export: entry %" PRId64, e);
             }
+}
+
+// Row lists that several threads make: every chunk byte for byte what one thread makes of it, with a thread for each 32,768 rows of a chunk
+void check_threaded_lists() {
+    const char* const before = getenv("NTP_HOST_THREADS");
+    const std::string threads = before ? before : "";
+    Lcg rng{4242};
+    for (int64_t rows : {(int64_t)65535, (int64_t)65536, (int64_t)65537, (int64_t)300007}) {
+        HostSparse m;
+        m.n = rows;
+        m.rowptr.push_back(0);
+        for (int64_t v = 0; v < rows; ++v) {            // empty ones, every bin, split ones, and a long run of empty rows
+            const uint64_t r = rng.next();
+            const int64_t d = v > rows / 3 && v < rows / 2 ? 0 : r % 977 == 0 ? 600 + (int64_t)(r >> 12) % 3000 : r % 41 == 0 ? 129 + (int64_t)(r >> 12) % 300 : (int64_t)((r >> 12) % (1ull << (r >> 30) % 8));
+            m.rowptr.push_back(m.rowptr.back() + d);
+        }
+        m.nnz = m.rowptr.back();
+        for (int64_t ce : {(int64_t)0, m.nnz / 2 + 1000, m.nnz / 7}) {
+            std::vector<Plan> plans;
+            for (const char* n : {"1", "2", "5", "13"}) {
+                setenv("NTP_HOST_THREADS", n, 1);
+                plans.emplace_back();
+                make_plan(m, ce, &plans.back());
+            }
+            check_plan(m, plans[0], ce, "row lists of one thread");
+            for (const Plan& P : plans) {
+                CHECK(P.chunks.size() == plans[0].chunks.size(), "row lists: %zu chunks", P.chunks.size());
+                for (size_t i = 0; i < P.chunks.size() && i < plans[0].chunks.size(); ++i) {
+                    const Chunk &a = P.chunks[i], &b = plans[0].chunks[i];
+                    CHECK(a.meta == b.meta && std::equal(a.bin_count, a.bin_count + NBINS, b.bin_count) && std::equal(a.bin_row_off, a.bin_row_off + NBINS, b.bin_row_off),
+                          "row lists: chunk %zu of %" PRId64 " rows", i, a.row_end - a.row_begin);
+                }
+            }
+        }
+    }
+    if (before) setenv("NTP_HOST_THREADS", threads.c_str(), 1);
+    else unsetenv("NTP_HOST_THREADS");
 }
 
 // segments combine their row's slots where that is little work: not a row of a thousand segments, nor many rows
@@ -709,7 +747,9 @@ int main() {
     check_lane_groups();
     // 9. the memory of a build on the device
     check_build_arena();
-    // 10. entries read back from the device
+    // 10. row lists made by several threads
+    check_threaded_lists();
+    // 11. entries read back from the device
     check_export();
     if (failures) { fprintf(stderr, "%d checks failed\n", failures); return 1; }
     printf("host checks passed\n");

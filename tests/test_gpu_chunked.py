@@ -293,8 +293,8 @@ def test_large_streamed_chunks_equal_resident_ones(case, f, n_rhs):
 
 @pytest.mark.parametrize("case", ["directed", "symmetric", "ones", "budget", "all alike", "2 vertices more"])
 def test_packed_column_ids_equal_resident_ones(case):
-    """Chunks of 655,360 entries and more send their column ids in as few bits as hold a vertex id: the bits of the resident chunks, for
-    ids of 16 and 17 bits, beside resident chunks, and where hardly an edge of a long list is left"""
+    """Chunks of 655,360 entries and more send their column ids packed: the bits of the resident chunks, for ids of 16 and 17 bits, beside
+    resident chunks, and where hardly an edge of a long list is left"""
     import torch
     n = (1 << 16) + (2 if case == "2 vertices more" else 0)
     rng = gen.stream_rng(11, 3)
@@ -332,11 +332,14 @@ def test_packed_column_ids_equal_resident_ones(case):
     streamed.close()
 
 
-@pytest.mark.parametrize("n,m,hub,chunk", [(3_000_001, 900_000, 0, 700_001), (70_000, 1_400_001, 0, 655_361), (1_500_007, 1_500_000, 1_400_000, 660_000), (700, 1_500_000, 0, 655_617),
-                                           (1_000_003, 2_000_000, 300_000, 900_007)])
-def test_packed_blocks_of_every_kind(n, m, hub, chunk):
+# bits: what an id takes in its block (as it is the bits of a vertex id; in a row of d among n vertices log2(n / d) + 1.5 and up to half a bit where that
+# is no whole number; no low bits: one and n / d), 0.4 in front of the block, and in rows that are split 0.8 for their pieces
+@pytest.mark.parametrize("n,m,hub,chunk,bits", [(3_000_001, 900_000, 0, 700_001, 22.5), (70_000, 1_400_001, 0, 655_361, 14.5), (1_500_007, 1_500_000, 1_400_000, 660_000, 4.7),
+                                                (700, 1_500_000, 0, 655_617, 2.8), (1_000_003, 2_000_000, 300_000, 900_007, 18.3)])
+def test_packed_blocks_of_every_kind(n, m, hub, chunk, bits):
     """ids as they are where most rows are empty or short, in parts where rows are long (no low bits where rows repeat every neighbour), rows over
-    several blocks and chunks, a last block and chunk of a few entries: the bits of the resident chunks"""
+    several blocks and chunks, a last block and chunk of a few entries: the bits of the resident chunks, and no more of them on the link than each kind
+    of block takes (as they are, the ids of the second to the last graph would take 17, 21, 10 and 20)"""
     import torch
     rng = gen.stream_rng(n, 7)
     src, dst = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
@@ -344,6 +347,7 @@ def test_packed_blocks_of_every_kind(n, m, hub, chunk):
     resident = ntp.ntp_graph_build(n, src, dst, flags=0, chunk_edges=chunk)
     streamed = ntp.ntp_graph_build(n, src, dst, flags=ntp.NTP_FORCE_STREAM, chunk_edges=chunk)
     say("packed blocks", n, m, "hub", hub, "chunks", len(ntp.ntp_graph_chunks(streamed)["resident"]), "bytes a pass", ntp.ntp_graph_stream_bytes(streamed))
+    assert (ntp.ntp_graph_stream_bytes(streamed) - 12 * n) * 8 <= bits * m          # (12 bytes a row: pointer and place in its list)
     x = torch.randn(n, 4, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(3))
     cs, cp = torch.cuda.Stream(), torch.cuda.Stream()
     for direction in (ntp.NTP_FWD, ntp.NTP_BWD):
@@ -359,8 +363,8 @@ def test_packed_blocks_of_every_kind(n, m, hub, chunk):
 
 @pytest.mark.parametrize("chunk,budget", [(700_000, 0), (1_500_000, 0), (700_000, 16 << 20), (700_000, 26 << 20)])
 def test_packed_chunks_pass_after_pass(chunk, budget):
-    """copies run ahead of the kernels, over the ends of passes too: passes on other streams, both directions and several right-hand sides without a
-    wait in between, each the bits of the resident chunks"""
+    """a copy runs ahead of the kernels, over the ends of passes too: passes on other streams, both directions and several right-hand sides without a
+    wait in between, each the bits of the resident chunks; copies by DMA, which those of 768 KB and less are not"""
     import torch
     n, f = 40_000, 16
     rng = gen.stream_rng(17, 2)
@@ -369,19 +373,24 @@ def test_packed_chunks_pass_after_pass(chunk, budget):
     resident = ntp.ntp_graph_build(n, src, dst, flags=flags, chunk_edges=chunk)
     streamed = ntp.ntp_graph_build(n, src, dst, flags=flags | (0 if budget else ntp.NTP_FORCE_STREAM), chunk_edges=chunk, device_budget_bytes=budget)
     assert not ntp.ntp_graph_chunks(streamed)["resident"].all()
+    for which in (ntp.NTP_CSR, ntp.NTP_CSC):
+        assert ntp.ntp_graph_stream_bytes(streamed, which) > 768 * 1024 * int((ntp.ntp_graph_chunks(streamed, which)["resident"] == 0).sum())
     say("pass after pass", chunk, budget, "bytes", ntp.ntp_graph_stream_bytes(streamed), "resident", int(ntp.ntp_graph_chunks(streamed)["resident"].sum()))
     xs = [torch.randn(n, f, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(i)) for i in range(8)]
     streams = [torch.cuda.Stream() for _ in range(4)]
     torch.cuda.synchronize()
     outs = []
     for g in (resident, streamed):
-        ys = [torch.full_like(x, 9) for x in xs]
+        ys, more = [torch.full_like(x, 9) for x in xs], [torch.full_like(x, 9) for x in xs[:2]]
         torch.cuda.synchronize()
         for i, x in enumerate(xs):
             cs, cp = streams[i % 2], streams[2 + i // 2 % 2]
-            ntp.ntp_chunked_aggregate(g, ntp.NTP_FWD if i % 3 else ntp.NTP_BWD, x, ys[i], f, f, f, ntp.NTP_F32, cs, cp)
+            if i % 4 == 3:
+                ntp.ntp_chunked_aggregate_multi(g, ntp.NTP_FWD if i % 3 else ntp.NTP_BWD, [x, xs[0]], [ys[i], more[i // 4]], f, f, f, ntp.NTP_F32, cs, cp)
+            else:
+                ntp.ntp_chunked_aggregate(g, ntp.NTP_FWD if i % 3 else ntp.NTP_BWD, x, ys[i], f, f, f, ntp.NTP_F32, cs, cp)
         torch.cuda.synchronize()
-        outs.append(ys)
+        outs.append(ys + more)
     for i, (a, b) in enumerate(zip(*outs)):
         assert torch.equal(a, b), i
     resident.close()

@@ -40,10 +40,10 @@ def _same(g, h, which):
     assert all(np.array_equal(cg[k], ch[k]) for k in cg if k != "resident") and cg["resident"].all()
 
 
-# 24,576 edges are the fewest that the device takes; 2 vertices: one bit an id; 65,536 and 65,537: 16 and 17 bits; many vertices: rows without entries
+# 1,100,003 keys: more tiles than threads add up at once; 24,576 edges are the fewest that the device takes; 2 vertices: one bit an id; 65,536 and 65,537: 16 and 17 bits; many vertices: rows without entries
 @pytest.mark.parametrize("n,m,kind", [(2, 24576, "even"), (300, 70001, "even"), (5000, 40960, "hub"), (65536, 24577, "even"), (65537, 90000, "skewed"),
                                       (700001, 24576, "even"), (20000, 30000, "both ways"), (300001, 24576, "low ids"), (100001, 30000, "bipartite"),
-                                      (5000, 40960, "source hub"), (70001, 24577, "one source")])
+                                      (5000, 40960, "source hub"), (70001, 24577, "one source"), (30000, 1100003, "skewed")])
 def test_device_build_gives_the_host_builds_arrays(n, m, kind):
     src, dst = _edges(n, m, kind, n + m)
     for used in itertools.product([0, 1], repeat=4):
