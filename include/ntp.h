@@ -156,8 +156,10 @@ int ntp_graph_chunks(const ntp_graph_t* g, int which, int32_t* n_chunks,
  * of a streamed chunk are rebuilt on the device from the degrees (bit-identical to the stored
  * ones), which halves the host-link traffic of the chunk schedule, and where chunks are cut
  * at 655,360 entries and more (a graph of 1,310,720 and more that NTP_FORCE_STREAM has the library
- * cut: in any case) their column ids travel in as few bits each as hold a vertex id (up to 28).
- * The packed ids are what is pinned then; the ids stay in ordinary host memory beside them. */
+ * cut: in any case; ids of up to 28 bits) their column ids travel packed: in blocks of 256 entries,
+ * each in as few bits as hold a vertex id, or in fewer where its rows are long (about
+ * log2(n / d) + 1.5 bits for a neighbour in a row of d).  Row pointers, lists and packed ids of the
+ * streamed chunks are what is pinned then; the ids stay in ordinary host memory beside them. */
 int ntp_graph_stream_bytes(const ntp_graph_t* g, int which, int64_t* bytes);
 
 /* Device bytes held by the handle (resident topology and its second copies, staging buffers, scratch). */

@@ -39,7 +39,7 @@ struct CopyPath {
 //   aggregation cannot spare the time (0.7 of the copy).  On the compute / copy stream: 4 chunks of 4 M entries F = 32 1268 / 1314,
 //   F = 256 1511 / 1438, 8 x 32 columns 1852 / 1762; 11 of 0.4 M F = 32 669 / 682, F = 128 862 / 803, F = 256 1096 / 1016.
 //   Packed ids (`packed`) come with their row pointers and lists in one copy, one copy at a time: the buffers that it goes to hold nothing else, so
-//   there are more of them than two and copies run ahead of the kernels.  us for both directions, two images with the row pointers copied by a kernel and two
+//   there are more of them than two, and the next copy runs ahead of the kernels.  us for both directions, two images with the row pointers copied by a kernel and two
 //   copy streams while the link is the bound / these buffers with two copy streams / with one: 15.8 M entries of 306,128 vertices, chunks of 4 M F = 32
 //   1291 / 1300 / 1263, F = 76 1474 / 1625 / 1478, F = 128 1766 / 2360 / 1773; of 1 M F = 32 3062 / 2793 / 1904, F = 76 2460 / 2528 / 2460; of 0.66 M
 //   F = 32 3984 / 3701 / 2556; 15 M entries of 1 M vertices in chunks of 2 M F = 32 3181 / 2722 / 2024, F = 128 3582 / 3733 / 3599; 5.1 M of 70,000 in

@@ -7,7 +7,7 @@
 // that runs of equal digits are written side by side.  Dropping repeated keys, row pointers and column ids follow in one sweep.  The form by source is
 // the same entries, already in order of their destination, after the passes over the source's bits alone.
 //
-// Bound: what surrounds it.  1.2 M edges symmetrised with self loops (2.5 M keys of 36 bits, four passes): the edges come in in 0.34 ms, keys,
+// Bound: what surrounds it.  1.2 M edges symmetrised with self loops (2.5 M keys of 36 bits, four passes), 1.7 ms in all: the edges come in in 0.34, keys,
 // sorting and arrays take 0.19, row pointers go back in 0.13, allocation and release of 45 MB take 0.5, the plan of the rows on the host 0.5; the
 // threads' build took 3.9 and the upload of its arrays 0.8.
 #include <hip/hip_runtime.h>
@@ -315,7 +315,9 @@ void write_form(const u64* keys, int64_t count, int64_t n, Keep keep, int32_t* k
 
 // Where graphs are built on the device rather than by the host's threads (16 of them): build, export of the arrays and release in us, host / device.
 // 2,000 vertices 10,000 edges 253 / 396, 5,000 of 30,000 527 / 319, 10,000 of 100,000 1396 / 488, 50,000 of 300,000 2687 / 1795 (directed 3518 /
-// 1555), 169,343 of 1.2 M 7500 / 3390, 1 M of 1 M 15845 / 8252 (directed 32155 / 12792), 200,000 of 4 M 18921 / 10853 (23500 / 9480).
+// 1555), 169,343 of 1.2 M 7500 / 3390, 1 M of 1 M 15845 / 8252 (directed 32155 / 12792), 200,000 of 4 M 18921 / 10853 (23500 / 9480).  Few edges among many
+// vertices, without the export: 200,000 of 24,576 2360 / 1530, 1 M of 24,576 6440 / 3620 (without self loops and with a form by source 8770 / 6580), 20 M of 24,576 196,000 /
+// 108,000 (317,000 / 209,000), and 5 M of 100,000 among the first 100 ids 82,000 / 54,000.
 // Keys are counted in 32 bits.
 bool device_build_takes(int64_t n, int64_t n_edges, uint32_t flags) {
     const int64_t raw = n_edges * (flags & NTP_SYMMETRISE ? 2 : 1) + (flags & NTP_ADD_SELF_LOOPS ? n : 0);
