@@ -52,6 +52,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "lane_util.h"
 #include "ntp_internal.h"
@@ -785,20 +786,41 @@ __device__ __forceinline__ int xcd_block(int b, int blocks) {
     return s0 + (b & 7) * XCD_RUN + ((b - s0) >> 3);
 }
 
+// The column passes of a launch, one after the other over all XCDs (blockIdx.y), or dealt to the XCDs: every XCD then gathers from the one or two
+// column passes that are its own, whose lines come into its L2 once, where otherwise every XCD loads those of every pass again.  That counts
+// where an XCD's share of a pass, an eighth of its entries, finds few lines a second time: us in turn / dealt, 128 columns (4 passes)
+// 30,000 entries of 8,000 vertices (R-MAT) 8.4 / 8.0, 240,000 of 15,000 16.8 / 11.8, 384,000 of 24,000 (Zipf) 22.3 / 19.1, 768,000 of 48,000 33 / 31; 256
+// columns (8 passes) 75,000 of 15,000 (Zipf) 17.9 / 11.0, 240,000 of 15,000 25 / 19, 384,000 of 24,000 35 / 32; 1433 columns (6 passes) 384,000 of
+// 24,000 230 / 178.  With more entries the lines are found in either way, and an XCD whose lines all lie at one place of a power of two of bytes does
+// not use all of its L2's channels (8 passes, row stride 1 KB, 3.6 M entries of 24,000 179 / 211; stride 1152 bytes 174 / 168): line between 0.98 M and 1.46 M
+// entries at 4 passes (915,000 31.8 / 30.7, 1.46 M 44.1 / 45.1), between 0.49 M (33 / 30) and 0.65 M (37.6 / 38.5) at 8.
+// Eight times n_passes consecutive ids are eight blocks of every pass; XCD id % 8 takes n_passes of them in a row.
+constexpr int64_t DEALT_ENTRIES = 3500000;      // entries x passes
+__device__ __forceinline__ int dealt_block(int id, int n_passes, int& pass) {
+    const int period = id / (8 * n_passes), in = id - period * (8 * n_passes);
+    const int i = n_passes * (in & 7) + (in >> 3);
+    pass = i >> 3;
+    return period * 8 + (i & 7);
+}
+
 // L lanes per feature row, NACC vectors per lane (columns l*VEC + j*L*VEC), 4 wavefronts
-// per block, every wavefront an independent unit of work.  blockIdx.y walks column passes
-// when the slice is wider than L*VEC*NACC.
+// per block, every wavefront an independent unit of work.  A slice wider than L*VEC*NACC is walked in column passes: DEALT, n_passes of them
+// dealt to the XCDs; else blockIdx.y.  (A kernel of its own: the test alone cost launches of 20 us 2 %.)
 //
 // Gathers are issued U at a time with no branch between them, so that U neighbour rows are in flight per lane before the
 // first multiply-add waits; only the last ones of a row are masked one by one.  A lane whose columns lie beyond the slice
 // reads the first columns of its pass and stores nothing.
-template <class IO, int L, int NACC, bool PLAIN>
-__global__ void __launch_bounds__(256, (agg_min_waves<IO, L, NACC>())) agg_kernel(const AggArgs a) {
+template <class IO, int L, int NACC, bool PLAIN, bool DEALT>
+__global__ void __launch_bounds__(256, (agg_min_waves<IO, L, NACC>())) agg_kernel(const AggArgs a, const int n_passes) {
     __shared__ __align__(16) int stage[4][stage_words(L, false)];
     __shared__ float quarter[3][L * IO::kVec * NACC];     // block-per-row mode: sums of wavefronts 1..3
-    const int wave = __builtin_amdgcn_readfirstlane(xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + (int)(threadIdx.x >> 6));
+    int pass = (int)blockIdx.y;
+    int block;
+    if constexpr (DEALT) block = dealt_block((int)blockIdx.x, n_passes, pass);
+    else block = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int wave = __builtin_amdgcn_readfirstlane(block * 4 + (int)(threadIdx.x >> 6));
     if (wave >= a.n_waves) return;
-    agg_item<IO, L, NACC, false, PLAIN>(a, wave, (int)blockIdx.y, nullptr, quarter, stage[threadIdx.x >> 6]);
+    agg_item<IO, L, NACC, false, PLAIN>(a, wave, pass, nullptr, quarter, stage[threadIdx.x >> 6]);
 }
 
 // The same work with the hub rows of the column pass in LDS: one block of 16 wavefronts per
@@ -877,9 +899,17 @@ template <class IO, int L, int NACC>
 int launch_one(const AggArgs& a, int n_passes, hipStream_t st) {
     const int total = a.n_waves;
     if (total <= 0) return NTP_OK;
-    dim3 grid((unsigned)((total + 3) / 4), (unsigned)n_passes);
-    if (a.plain) hipLaunchKernelGGL((agg_kernel<IO, L, NACC, true>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((agg_kernel<IO, L, NACC, false>), grid, dim3(256), 0, st, a);
+    const unsigned blocks = (unsigned)((total + 3) / 4);
+    auto launch = [&](auto dealt) {
+        constexpr bool DEALT = decltype(dealt)::value;
+        const dim3 grid(DEALT ? (blocks + 7) / 8 * 8 * n_passes : blocks, DEALT ? 1u : (unsigned)n_passes);
+        if (a.plain) hipLaunchKernelGGL((agg_kernel<IO, L, NACC, true, DEALT>), grid, dim3(256), 0, st, a, n_passes);
+        else hipLaunchKernelGGL((agg_kernel<IO, L, NACC, false, DEALT>), grid, dim3(256), 0, st, a, n_passes);
+    };
+    // only the widest shape and that of a cache line have passes, unless NTP_AGG_PASS_LANES asks for them
+    constexpr bool may = L == 64 || (L == 8 && sizeof(typename IO::elem) * IO::kVec == 16);
+    if (may && n_passes > 1 && (a.e_end - a.e_base) * n_passes <= DEALT_ENTRIES) launch(std::bool_constant<may>{});
+    else launch(std::false_type{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("aggregation kernel launch failed: %s", hipGetErrorString(e)); return NTP_EHIP; }
     return NTP_OK;

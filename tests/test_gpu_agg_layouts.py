@@ -184,3 +184,28 @@ def test_no_second_copies_where_no_call_reads_them():
     assert bytes_of[0] > own + 2 * 8 * nnz                      # a copy takes at least an entry's eight bytes
     assert bytes_of[1] < own + 4 * nnz + (1 << 20)              # the permutation
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n,m", [(40, 60), (300, 2000), (3000, 7000), (5000, 190_000), (6000, 250_000)])
+@pytest.mark.parametrize("f,ld,dtype", [(64, 64, "f32"), (70, 96, "f32"), (160, 160, "f32"), (256, 256, "f32"), (270, 288, "f32"), (602, 602, "f32"), (300, 320, "bf16")])
+def test_column_passes_on_their_own_xcds(n, m, f, ld, dtype):
+    """launches of few entries and passes deal the passes to the XCDs: numbers of passes that divide 8 and that do not, numbers of blocks that
+    are no multiple of 8, entries on both sides of the line; 128-byte passes against calls of one pass, bit for bit"""
+    import torch
+    from gpu_util import check_agg, dev_f32
+    src, dst = gen.directed_random_edges(n, m, seed=n, hub=1, hub_in=n // 2, hub_out=n // 3)
+    og = oracle.build_graph(n, src, dst, oracle.DIRECTED_GCN_FLAGS)
+    g = ntp.ntp_graph_build(n, src, dst, flags=ntp.NTP_DIRECTED_GCN_FLAGS)
+    say("passes", n, m, f, ld, dtype)
+    x = gen.normal_features(n, f, seed=f)
+    for direction in ("fwd", "bwd"):
+        got = check_agg(g, og, x, direction, dtype, "passes of %d columns %s" % (f, direction), ld_in=ld, ld_out=ld)
+        if dtype == "f32" and ld % 32 == 0:
+            X = torch.zeros(n, ld, device="cuda:0")
+            X[:, :f] = dev_f32(x)
+            Y = torch.empty_like(X)
+            for c in range(0, f - 31, 32):
+                (ntp.ntp_aggregate_fwd if direction == "fwd" else ntp.ntp_aggregate_bwd)(g, X[:, c:], Y[:, c:], 32, ld, ld)
+            torch.cuda.synchronize()
+            assert np.array_equal(Y[:, :f // 32 * 32].cpu().numpy(), got[:, :f // 32 * 32])
+    g.close()
