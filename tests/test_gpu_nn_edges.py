@@ -192,6 +192,39 @@ def test_many_rows_give_the_bits_of_few(k, m, act):
     assert torch.equal(dA[:n], few) and bool((dA[n] == 7.0).all())
 
 
+# products from fp16 pieces: the fewest rows that are taken so, a tile more, and rows that are no whole tile of 32 or 64
+@pytest.mark.parametrize("n,k,m", [(57345, 65, 65), (57376, 80, 128), (57409, 97, 66), (57377, 128, 127), (98305, 129, 128), (98400, 250, 100), (57345, 256, 129),
+                                   (57377, 161, 192), (60001, 112, 256), (57408, 208, 224), (65536, 256, 256), (58000, 225, 255)])
+@pytest.mark.parametrize("direction", ["forward", "dA", "masked dA"])
+def test_products_from_fp16_pieces(n, k, m, direction):
+    """H, and dA of a layer m -> k, of operands whose rows and columns differ by 30 decades and within those by six.  Bound: an operand is held to
+    2^-23 of its size (2^-52 of its row's largest), the product left out is below 2^-22, and the two sums round once a term at most.  Rows with a
+    NaN or an infinity keep to themselves."""
+    import torch
+    print("nn fp16 pieces", n, k, m, direction, file=sys.stderr, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(n + 1000 * k + m)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda:0")
+    u = lambda d, *s: torch.pow(10., d * (2 * torch.rand(*s, generator=g, device="cuda:0") - 1))
+    A, W = r(n, k) * u(3, n, k) * u(15, n, 1), r(k, m) * u(3, k, m) * u(15, 1, m)
+    W[:, m // 2] = 0
+    A[n - 1], A[32], A[9] = float("nan"), 0., 1e-39
+    A[31, k - 1] = float("inf")
+    out = torch.full((n + 1, m), 7.0, device="cuda:0")
+    if direction == "forward":
+        ntp.ntp_nn_fwd(A, W, out, n, k, m, ntp.NTP_ACT_NONE)
+        used = A
+    else:
+        mask, act = r(n, k), ntp.NTP_ACT_RELU if direction == "masked dA" else ntp.NTP_ACT_NONE
+        ntp.ntp_nn_bwd(out, W.T.contiguous(), mask, A, out, None, n, m, k, act, ntp.NTP_F32, None, 0, torch.cuda.current_stream())
+        used = torch.where(mask > 0, A, 0.) if act == ntp.NTP_ACT_RELU else A
+    assert bool((out[n] == 7.0).all())
+    plain = torch.isfinite(used).all(1)
+    got, a, w = out[:n][plain].double(), used[plain].double(), W.double()
+    rest = a.abs().amax(1, keepdim=True) * w.abs().sum(0) + a.abs().sum(1, keepdim=True) * w.abs().amax(0)
+    bound = (2.0 ** -21 + k * 2.0 ** -24) * (a.abs() @ w.abs()) + 2.0 ** -51 * rest + 2.0 ** -148
+    assert bool(((got - a @ w).abs() <= bound).all())
+
+
 # one to eight tiles of 256 x 128 or (k in an odd number of 128s) 128 x 256, just above the fewest rows that are taken: row counts of
 # no whole step, of a step, of one row in the last range
 @pytest.mark.parametrize("n,k,m", [(131073, 130, 70), (131072, 256, 128), (131104, 200, 65), (65553, 129, 200), (65600, 256, 256),
