@@ -9,7 +9,7 @@
 // flight while the present ones are cut into bf16 pieces and multiplied; no barrier until the end.  A block of eight
 // wavefronts is a few neighbouring tiles x shares of the rows of one range of vertices; the shares are added through
 // LDS in a fixed order, the ranges by sum_splits_kernel: deterministic.  Wide fp32 products of many rows go through LDS all the
-// same (dw_shared_kernel): there the cutting costs more than the transposition.
+// same (dw_shared_kernel, with fp16 pieces): there the cutting costs more than the transposition.
 //
 // Bound: memory for a narrow side (256 x 64 on 169,343 rows: 217 MB in 0.043 ms = 5.0 TB/s), the two pipes of the SIMD
 // otherwise (256 x 256 here: matrix instructions 49 % of the time, other vector instructions 40 %, half of them beside those).
@@ -255,26 +255,28 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
     }
 }
 
-// Wide dW from shared pieces: the eight wavefronts of a block own 64 x 64 each of a tile of 32 BK x 32 BZ columns, and all of
-// them walk the same rows, 32 at a time.  Every 16 rows of a 32-column block of A or dZ (a fragment) are loaded and cut by one
-// wavefront and put into LDS in operand order, where those find it that need it; the pieces of the next 32 rows go into the
-// other half of the LDS while these are multiplied: one barrier per 32 rows, 144 KB.
+// Wide dW from shared pieces: the eight wavefronts of a block own 64 x 64 each of a tile of 256 x 128 columns of A and dZ (TALL, or 128 x 256),
+// and all of them walk the same rows, 32 at a time.  Every column is loaded and cut (into two fp16 pieces, nn_util.h, one accumulator) by one
+// wavefront, which finds its scale, and put into LDS in operand order, where those find it that need it; the pieces of the next
+// 32 rows go into the other half of the LDS while these are multiplied: one barrier per 32 rows, 101 KB.  A scale is that of the largest
+// element so far with two bits to spare; where one changes, all sums are brought to it (in the first rows, and seldom after them: a block of
+// normal numbers once in all).
 //
-// Bound: the matrix pipe at the clock that its power leaves, and beside it the loads.  In dw_kernel a wavefront cuts
-// six fragments for every eight blocks of products, here three for every eight (and masks a quarter as often): vector
-// instructions on 306,129 rows of 256 x 256 fall from 54 to 31 million.  dW of 169,343 rows of 256 x 256, without / with the
-// ReLU mask, 0.144 / 0.166 -> 0.133 / 0.132 ms; 306,129 rows 0.250 / 0.285 -> 0.229 / 0.235, of 200 x 172 0.234 / 0.270 ->
-// 0.211 / 0.209; 400,000 rows of 128 x 256 0.182 / 0.214 -> 0.168 / 0.191.
+// Bound: the loads, of which the registers hold one step ahead (48 KB a compute unit, masked 64): 627 MB for 256 x 256 on 306,129 rows in 168 us.  us
+// with three bf16 pieces, where the matrix pipe was the bound, / here, without and with the ReLU mask: 306,129 rows of 256 x 256 225 242 / 168
+// 206 (940 MB: 4.6 TB/s), 169,343 129 140 / 104 122, of 128 x 256 73 95 / 59 93, 200 x 172 on 200,000 133 144 / 112 126.  No branch stands between the
+// products of a step (with two, where scales and flags were stored by some lanes, 185 us), and reads issued in groups between them by order
+// of the compiler's scheduling barriers lose 7-9 %.
 // A sum runs through many more rows than in the shares of dw_kernel, so it is put away and begun anew every 128 rows: relative
-// error on those 169,343 rows 3.9e-7 against 6.7e-7 in dw_kernel (9.5e-7 without; 64 rows 4.2e-7 and 2 % slower).
-template <bool MASK, int BK, int BZ>
+// error on 169,343 rows of 256 x 256 3.2e-7 (bf16 pieces 3.9e-7, dw_kernel 6.7e-7), on 306,129 3.9e-7 (4.8e-7), on a million 6.7e-7 (8.3e-7).
+template <bool MASK, bool TALL>
 __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
-    constexpr int WZ = BZ / 2, F = BK + BZ;                             // fragments of 16 rows
-    constexpr int UNITS_A = 2 * BK / 8, UNITS = 2 * F / 8;              // fragments that a wavefront cuts per 32 rows
+    constexpr int BK = TALL ? 8 : 4, BZ = 12 - BK, WZ = BZ / 2, F = BK + BZ;          // F: fragments of 16 rows
     constexpr int FOLD_ROWS = 128;
-    static_assert(BK / 2 * WZ == 8 && BK % 4 == 0 && BZ % 4 == 0, "eight wavefronts");
     extern __shared__ uint4 pieces[];          // [buffer][16 rows][fragment][piece][lane]
-    constexpr int BUF = 2 * F * 3 * 64;
+    constexpr int BUF = 2 * F * 2 * 64;
+    int* const scales = reinterpret_cast<int*>(pieces + 2 * BUF);          // [3][columns of A, columns of dZ]
+    int* const changed = scales + 3 * 32 * F;                              // [3][wavefront]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 31, h = lane >> 5;
@@ -297,105 +299,158 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
             }
     };
 
-    // Unit u of this wavefront: a fragment of A (u < UNITS_A) or of dZ.  Column r of it, rows 2 j + h of its 16, as loads from a
-    // buffer that ends with the range: rows beyond it read as zero, and the lanes compute no addresses.  Columns beyond the matrix
-    // re-read the last one (their sums are not stored).
-    struct Raw { float x[8], mk[8]; };
-    int off[UNITS];
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-        const int f = u < UNITS_A ? (wave + 8 * u) % BK : (wave + 8 * (u - UNITS_A)) % BZ;
-        off[u] = u < UNITS_A ? 4 * (min(c0 + 32 * f + r, k - 1) + h * k) : 4 * (min(z0 + 32 * f + r, m - 1) + h * m);
-    }
-    auto rows16 = [&](const void* at, int64_t first, int pitch) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(at) + min(first, r1) * pitch), 0,
-                                                 (int)min(max(r1 - first, (int64_t)0), (int64_t)16) * pitch, 0x00020000);
+    // Units of this wavefront, 32 rows x 48 columns.  0, 1: the 32 columns of a block of the wider operand, rows 2 j + h of its upper and lower 16;
+    // 2: sixteen columns of the other one, rows 2 j + h of its upper (lanes below 32) and lower 16, h = lane / 16 % 2.  So all of a
+    // column is this wavefront's, and with it its scale.  Loads from a buffer that ends with the range: rows beyond it read as zero, and the
+    // lanes compute no addresses.  Columns beyond the matrix re-read the last one (their sums are not stored).
+    struct Raw { unsigned x[8], mk[8]; };
+    const int wide_pitch = TALL ? k : m, narrow_pitch = TALL ? m : k;
+    const int wide_col = 32 * wave + r, narrow_col = 16 * wave + (lane & 15);
+    const int wide_off = 4 * (min((TALL ? c0 : z0) + wide_col, wide_pitch - 1) + h * wide_pitch);
+    const int narrow_off = 4 * (min((TALL ? z0 : c0) + narrow_col, narrow_pitch - 1) + ((lane >> 4 & 1) + 16 * h) * narrow_pitch);
+    auto rows = [&](const void* at, int64_t first, int count, int pitch) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(at) + min(first, r1) * (4 * pitch)), 0,
+                                                 (int)min(max(r1 - first, (int64_t)0), (int64_t)count) * (4 * pitch), 0x00020000);
     };
+    auto of_z = [](int u) { return u < 2 ? !TALL : TALL; };
     auto issue = [&](Raw& x, int u, int64_t row0) {
-        const bool of_z = u >= UNITS_A;
-        const int64_t first = row0 + (of_z ? (wave + 8 * (u - UNITS_A)) / BZ : (wave + 8 * u) / BK) * 16;
-        const int pitch = 4 * (of_z ? m : k);
-        const auto buf = rows16(of_z ? g.Z : g.A, first, pitch);
+        const int pitch = u < 2 ? wide_pitch : narrow_pitch, off = u < 2 ? wide_off : narrow_off;
+        const int64_t first = u == 1 ? row0 + 16 : row0;
+        const auto buf = rows(of_z(u) ? g.Z : g.A, first, u < 2 ? 16 : 32, pitch);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x.x[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, off[u], 2 * j * pitch, 0));
-        if (MASK && of_z) {
-            const auto mbuf = rows16(g.mask, first, pitch);
+        for (int j = 0; j < 8; ++j) x.x[j] = __builtin_amdgcn_raw_buffer_load_b32(buf, off, 8 * j * pitch, 0);
+        if (MASK && of_z(u)) {
+            const auto mbuf = rows(g.mask, first, u < 2 ? 16 : 32, pitch);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x.mk[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mbuf, off[u], 2 * j * pitch, 0));
+            for (int j = 0; j < 8; ++j) x.mk[j] = __builtin_amdgcn_raw_buffer_load_b32(mbuf, off, 8 * j * pitch, 0);
         }
     };
-    auto stage = [&](Raw& x, int u, int buf) {
-        const bool of_z = u >= UNITS_A;
-        if (MASK && of_z) {
+    auto mask_unit = [&](Raw& x, int u) {
+        if (MASK && of_z(u)) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) x.x[j] = x.mk[j] > 0.f ? x.x[j] : 0.f;
+            for (int j = 0; j < 8; ++j) x.x[j] = __uint_as_float(x.mk[j]) > 0.f ? x.x[j] : 0u;
         }
-        uint4 p[3];
-        cut_rows<float, CORE_BF16>(x.x, p);
-        const int q = of_z ? wave + 8 * (u - UNITS_A) : wave + 8 * u;
-        const int at = buf * BUF + (of_z ? q / BZ * F + BK + q % BZ : q / BK * F + q % BK) * 3 * 64 + lane;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) pieces[at + i * 64] = p[i];
     };
-    Raw x[UNITS];
+    // The scales of this wavefront's columns, as for the largest element up to now with two bits to spare, so that they seldom change; a column of
+    // zeros so far has none yet (the largest scale).
+    int wide_scale = 243, narrow_scale = 243;
+    auto adapt = [](int& scale, float largest) {
+        const int need = f16_scale(largest);
+        const bool over = scale > need;
+        scale = over ? max(need - 2, 0) : scale;
+        return __ballot(over) != 0 ? 1 : 0;
+    };
+    auto put = [&](const Raw& x, int u, int scale, int buf) {
+        uint4 p[2];
+        cut_f16<1>(x.x, scale, p);
+        const int frag = u < 2 ? u * F + (TALL ? wave : BK + wave) : h * F + (TALL ? BK + wave / 2 : wave / 2);
+        const int slot = u < 2 ? lane : (lane >> 4 & 1) * 32 + (wave & 1) * 16 + (lane & 15);
+        const int at = buf * BUF + frag * 2 * 64 + slot;
+        pieces[at] = p[0];
+        pieces[at + 64] = p[1];
+    };
+    Raw x[3];
+    int changes = 0;
+    // unit u of the rows that follow into buffer buf, its columns' scales into table `table`
+    auto stage = [&](int u, int buf, int table) {
+        if (u == 0) {
+            mask_unit(x[0], 0);
+            mask_unit(x[1], 1);
+            changes = adapt(wide_scale, max_of_halves(largest8(x[1].x, largest8(x[0].x, 0.f))));
+            scales[table * 32 * F + (TALL ? 0 : 32 * BK) + wide_col] = wide_scale;
+        } else if (u == 2) {
+            mask_unit(x[2], 2);
+            const float half = max_of_halves(largest8(x[2].x, 0.f));
+            const auto quarters = __builtin_amdgcn_permlane16_swap(__float_as_uint(half), __float_as_uint(half), false, false);
+            changes |= adapt(narrow_scale, __uint_as_float(max(quarters[0], quarters[1])));
+            scales[table * 32 * F + (TALL ? 32 * BK : 0) + narrow_col] = narrow_scale;
+            changed[table * 8 + wave] = changes;            // (all lanes the same: no branch cuts the products off from what runs beside them)
+        }
+        put(x[u], u, u < 2 ? wide_scale : narrow_scale, buf);
+    };
+    // sums to the scales of table `to`
+    auto rescale = [&](int from, int to) {
+        const int* a = scales + from * 32 * F;
+        const int* b = scales + to * 32 * F;
+        int dz[2];
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) issue(x[u], u, r0);
+        for (int j = 0; j < 2; ++j) dz[j] = b[32 * BK + 64 * wz + 32 * j + r] - a[32 * BK + 64 * wz + 32 * j + r];
 #pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-        stage(x[u], u, 0);
-        issue(x[u], u, r0 + 32);
-    }
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int ac = 64 * wk + 32 * i + 8 * (e / 4) + 4 * h + e % 4, da = b[ac] - a[ac];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    acc[i][j][e] = ldexpf(acc[i][j][e], dz[j] + da);
+                    total[i][j][e] = ldexpf(total[i][j][e], dz[j] + da);
+                }
+                if (e % 4 == 3) asm volatile("" ::: "memory");          // (four rows' scales in registers at a time)
+            }
+    };
+#pragma unroll
+    for (int u = 0; u < 3; ++u) issue(x[u], u, r0);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) stage(u, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) issue(x[u], u, r0 + 32);
     __syncthreads();
-    int buf = 0;
+    int buf = 0, table = 0;
     for (int64_t row = r0; row < r1;) {
         for (const int64_t stop = min(row + FOLD_ROWS, r1); row < stop; row += 32, buf ^= 1) {
+            const int next = table == 2 ? 0 : table + 1;
             const uint4* src = pieces + buf * BUF + lane;
-            uint4 pa[2][1][3], pb[2][2][3];            // operands of this product and of the next one
-            auto read_a = [&](int p, uint4 (&a)[1][3]) {
+            uint4 pa[2][2], pb[2][2][2];               // operands of this product and of the next one
+            auto read_a = [&](int p, uint4 (&a)[2]) {
 #pragma unroll
-                for (int q = 0; q < 3; ++q) a[0][q] = src[((p / 2 * F + 2 * wk + p % 2) * 3 + q) * 64];
+                for (int q = 0; q < 2; ++q) a[q] = src[((p / 2 * F + 2 * wk + p % 2) * 2 + q) * 64];
             };
-            auto read_b = [&](int s, uint4 (&b)[2][3]) {
+            auto read_b = [&](int s, uint4 (&b)[2][2]) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) b[j][q] = src[((s * F + BK + 2 * wz + j) * 3 + q) * 64];
+                    for (int q = 0; q < 2; ++q) b[j][q] = src[((s * F + BK + 2 * wz + j) * 2 + q) * 64];
             };
+            const int4 any0 = *reinterpret_cast<const int4*>(changed + table * 8), any1 = *reinterpret_cast<const int4*>(changed + table * 8 + 4);
+            if (row > r0 && __builtin_amdgcn_readfirstlane(any0.x | any0.y | any0.z | any0.w | any1.x | any1.y | any1.z | any1.w))
+                rescale(table == 0 ? 2 : table - 1, table);
             read_b(0, pb[0]);
             read_a(0, pa[0]);
 #pragma unroll
             for (int p = 0; p < 4; ++p) {              // 16 rows p / 2, column block p % 2 of A
                 if (p < 3) read_a(p + 1, pa[(p + 1) & 1]);
                 if (p == 1) read_b(1, pb[1]);
-                if (p < UNITS) {
-                    stage(x[p < UNITS ? p : 0], p, buf ^ 1);
-                    issue(x[p < UNITS ? p : 0], p, row + 64);
+                if (p < 3) {
+                    stage(p, buf ^ 1, next);
+                    issue(x[p], p, row + 64);
                 }
-                mfma_parts<CORE_BF16, 1, 2, 3>(pa[p & 1], pb[p / 2], reinterpret_cast<f32x16 (&)[1][2]>(acc[p % 2]));
+                mfma_f16<2>(pa[p & 1], pb[p / 2], acc[p % 2]);
             }
+            table = next;
             __syncthreads();
         }
         fold();
     }
-    // element e of a 32x32 block: row 8 * (e / 4) + 4 * h + e % 4 of the A columns, column r of dZ's
+    // element e of a 32x32 block: row 8 * (e / 4) + 4 * h + e % 4 of the A columns, column r of dZ's; the scales are those of the last rows multiplied
+    const int* last = scales + (table == 0 ? 2 : table - 1) * 32 * F;
     float* out = g.out + (int64_t)split * k * m;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const int col = z0 + 64 * wz + 32 * j + r;
+            const int zc = 64 * wz + 32 * j + r, col = z0 + zc;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int rowk = c0 + 64 * wk + 32 * i + 8 * (e / 4) + 4 * h + e % 4;
-                if (col < m && rowk < k) out[(int64_t)rowk * m + col] = total[i][j][e];
+                const int ac = 64 * wk + 32 * i + 8 * (e / 4) + 4 * h + e % 4, rowk = c0 + ac;
+                if (col < m && rowk < k) out[(int64_t)rowk * m + col] = ldexpf(total[i][j][e], 254 - last[ac] - last[32 * BK + zc]);
             }
         }
 }
 
-template <bool MASK, int BK, int BZ>
+template <bool MASK, bool TALL>
 void launch_dw_shared(const DwArgs& g, hipStream_t st) {
-    constexpr int lds = 2 * 2 * (BK + BZ) * 3 * 1024;
-    auto kernel = dw_shared_kernel<MASK, BK, BZ>;
+    constexpr int F = 12, lds = 2 * 2 * F * 2 * 1024 + 3 * (32 * F + 8) * 4;
+    auto kernel = dw_shared_kernel<MASK, TALL>;
     static bool allowed[64] = {};
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -428,10 +483,11 @@ int pow2_up(int64_t x, int most) {
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //     against 39.1 us);
 //   k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
-//   fp32 whose tiles of 128 x 128 pair up without padding and whose blocks get 512 rows or more: 256 x 128 (or 128 x 256) per
-//     block of dw_shared_kernel.  Below that the longer tail of a block eats the gain (256 x 256 on 50,000 rows 48.5 against
-//     49.7 us) and its sums, in fewer chains than those of the eight shares, are less exact; with a padded pair the padding
-//     does (300 x 300 on 100,000 rows 0.168 / 0.206 ms, 602 x 128 on 58,241 0.070 / 0.077);
+//   fp32 whose tiles of 128 x 128 pair up without padding and whose blocks get 192 rows or more: 256 x 128 (or 128 x 256) per
+//     block of dw_shared_kernel (us in dw_kernel / here, without and with the ReLU mask: 256 x 256 on 24,576 rows 31.2 34.3 / 28.4 29.9, 49,152 46.6
+//     53.1 / 39.4 41.7, 128 x 256 on 65,536 36.6 42.2 / 32.9 40.5, 256 x 128 36.4 40.7 / 33.1 35.6).  Below that the longer tail of a block eats the
+//     gain (256 x 256 on 16,384 25.2 26.9 / 24.9 25.9, 128 x 256 on 32,768 25.7 28.6 / 25.5 29.9); with a padded pair the padding
+//     does (300 x 300 on 100,000 rows 0.168 / 0.206 ms, 602 x 128 on 58,241 0.070 / 0.077, both with bf16 pieces);
 //   else 128 x 64, whose operands are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343
 //     rows 0.134 against 0.164 ms.
 // m <= 32 and more than three row tiles of A take four of them side by side: whole rows of A from few blocks (us with one /
@@ -445,7 +501,7 @@ int pow2_up(int64_t x, int most) {
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE };
 int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
     const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
-    if (shared && !fp32_core && k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 131072)
+    if (shared && !fp32_core && k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 49152)
         return tk % 2 == 0 ? DW_SHARED_TALL : DW_SHARED_WIDE;
     if (k < 4) return DW_TINY;
     if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
@@ -484,8 +540,8 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
 template <class T, Core C>
 void launch_dw_any(const DwArgs& g, hipStream_t st) {
     switch (g.shape) {
-        case DW_SHARED_TALL: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, 8, 4>(g, st) : launch_dw_shared<false, 8, 4>(g, st); break;
-        case DW_SHARED_WIDE: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, 4, 8>(g, st) : launch_dw_shared<false, 4, 8>(g, st); break;
+        case DW_SHARED_TALL: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, true>(g, st) : launch_dw_shared<false, true>(g, st); break;
+        case DW_SHARED_WIDE: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, false>(g, st) : launch_dw_shared<false, false>(g, st); break;
         case DW_TINY:
             if constexpr (sizeof(T) == 2 || C == CORE_F32) g.mask ? launch_dw<T, C, true, 1, 1, 1, 1>(g, st) : launch_dw<T, C, false, 1, 1, 1, 1>(g, st);
             break;

@@ -294,7 +294,7 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
 #pragma unroll
         for (int s = 0; s < SEGS; ++s) {
             uint4 p[2];
-            cut_f16(w[s], scale, p);
+            cut_f16<2048>(w[s], scale, p);
             if (KC == 8 * SEGS || q + 16 * s < 2 * KC) {
                 to[s][buf * PART + i * GROUP] = p[0];
                 to[s][buf * PART + i * GROUP + 64] = p[1];
@@ -323,7 +323,7 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
         for (int c = 0; c < KC; ++c) m = largest8(w[c], m);
         col_scale = f16_scale(max_of_halves(m));
 #pragma unroll
-        for (int c = 0; c < KC; ++c) cut_f16(w[c], col_scale, b[c][0]);
+        for (int c = 0; c < KC; ++c) cut_f16<2048>(w[c], col_scale, b[c][0]);
     }
 
     f32x16 sums[2][1];

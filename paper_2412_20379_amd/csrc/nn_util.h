@@ -50,13 +50,17 @@ __device__ __forceinline__ unsigned pack_pair(unsigned even, unsigned odd) {
 // largest, below that to 2^-52 of the largest.  A product is hi hi + (hi lo + lo hi) / 2048, the two sums in accumulators of their own; the
 // product left out, lo lo, is below 2^-22 |a b|, of either sign.  Three matrix instructions a block where three bf16 pieces take six.
 // Scales go with a row or column of the result, so they are taken out of the sums again exactly.  An infinity gives NaN (inf - inf).
+// Without the factor of 2048 all three products go to one accumulator; what is held is then 2^-40 of the largest where that is more.
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // scale of numbers of which m is the largest magnitude, as a biased exponent; (up to 243: times 2048 it is still a float)
 __device__ __forceinline__ int f16_scale(float m) { return min(268 - (int)((__float_as_uint(m) >> 23) & 255), 243); }
+// LIFT: 2048, or 1 (see below)
+template <int LIFT>
 __device__ __forceinline__ void cut_f16(const unsigned (&w)[8], int scale, uint4 (&piece)[2]) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-    const float s = __uint_as_float((unsigned)scale << 23), s2 = __uint_as_float((unsigned)(scale + 11) << 23);
+    const float s = __uint_as_float((unsigned)scale << 23);
+    const float lift = LIFT, s2 = LIFT == 1 ? s : s * lift;
     unsigned hi[4], lo[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -64,7 +68,7 @@ __device__ __forceinline__ void cut_f16(const unsigned (&w)[8], int scale, uint4
         hi[e] = __builtin_bit_cast(unsigned, f16x2{(_Float16)(x * s), (_Float16)(y * s)});
         asm("" : "+v"(hi[e]));          // (else each half is rounded once more by itself)
         const f16x2 h = __builtin_bit_cast(f16x2, hi[e]);
-        const float rx = __builtin_fmaf((float)h[0], -2048.f, x * s2), ry = __builtin_fmaf((float)h[1], -2048.f, y * s2);
+        const float rx = __builtin_fmaf((float)h[0], -lift, x * s2), ry = __builtin_fmaf((float)h[1], -lift, y * s2);
         lo[e] = __builtin_bit_cast(unsigned, f16x2{(_Float16)rx, (_Float16)ry});
     }
     piece[0] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
@@ -91,6 +95,15 @@ __device__ __forceinline__ void mfma_f16(const uint4 (&a)[2], const uint4 (&b)[T
     for (int j = 0; j < TN; ++j) mul(a[0], b[j][0], sums[0][j]);
 #pragma unroll
     for (int j = 0; j < TN; ++j) mul(a[0], b[j][1], sums[1][j]);
+}
+// the same of pieces without the factor: acc[j] += hi hi + hi lo + lo hi
+template <int TN>
+__device__ __forceinline__ void mfma_f16(const uint4 (&a)[2], const uint4 (&b)[TN][2], f32x16 (&acc)[TN]) {
+#pragma unroll
+    for (int p = 2; p >= 0; --p)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[p == 2]), __builtin_bit_cast(f16x8, b[j][p == 1]), acc[j], 0, 0, 0);
 }
 // an element of the product from its two sums; scales: those of its row and column added
 __device__ __forceinline__ float f16_result(float hh, float cross, int scales) { return ldexpf(__builtin_fmaf(cross, 1.f / 2048.f, hh), 254 - scales); }

@@ -225,7 +225,7 @@ def test_products_from_fp16_pieces(n, k, m, direction):
     assert bool(((got - a @ w).abs() <= bound).all())
 
 
-# one to eight tiles of 256 x 128 or (k in an odd number of 128s) 128 x 256, just above the fewest rows that are taken: row counts of
+# one to eight tiles of 256 x 128 or (k in an odd number of 128s) 128 x 256: row counts of
 # no whole step, of a step, of one row in the last range
 @pytest.mark.parametrize("n,k,m", [(131073, 130, 70), (131072, 256, 128), (131104, 200, 65), (65553, 129, 200), (65600, 256, 256),
                                    (131087, 65, 129), (131072, 128, 256), (133000, 97, 250), (43700, 384, 256), (65569, 300, 129),
@@ -261,6 +261,45 @@ def test_wide_weight_gradients(n, k, m, act):
             roundings = 48 + n / 128 / 32 + 64
             assert bool(((got - want).abs() <= (2.0 ** -21 + roundings * 2.0 ** -24) * (A64.abs().T @ Z64.abs())).all())
         assert float(dW[k * m]) == 7.0
+
+
+# the fewest rows of one and of two pairs of tiles (256 x 128, 128 x 256, and odd sizes in them), rows of no whole step
+@pytest.mark.parametrize("n,k,m", [(49152, 130, 128), (49185, 256, 65), (49999, 70, 129), (24576, 256, 256), (24609, 200, 256), (70001, 128, 200), (66000, 256, 129)])
+@pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
+def test_wide_weight_gradients_of_uneven_columns(n, k, m, act):
+    """Columns that differ by 24 decades, begin with zeros, stay tiny for some rows and then grow by up to six decades, hold one element only, or a
+    NaN or an infinity (theirs alone): within the bound of test_wide_weight_gradients, of which the cut is 2^-21, and 2^-40 of a column's largest"""
+    import torch
+    print("nn uneven columns", n, k, m, act, file=sys.stderr, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(n + 1000 * k + m)
+
+    def operand(c):
+        x = torch.randn(n, c, generator=g, device="cuda:0") * torch.pow(10., 12 * (2 * torch.rand(1, c, generator=g, device="cuda:0") - 1))
+        row = torch.arange(n, device="cuda:0")[:, None]
+        start = torch.randint(0, 700, (1, c), generator=g, device="cuda:0")
+        kind = torch.arange(c, device="cuda:0") % 5
+        x = torch.where((kind == 1) & (row < start), 0., x)
+        x = torch.where(kind == 2, x * torch.pow(10., 6 * (row / n) - 3), x)
+        x = torch.where((kind == 3) & (row < start), x * 1e-5, x)
+        x[:, 4] = 0
+        x[n // 2, 4] = 1e-30
+        return x
+
+    A, dH, H = operand(k), operand(m), torch.randn(n, m, generator=g, device="cuda:0")
+    A[n // 3, 5], A[n - 1, 6], H[n // 3] = float("nan"), float("inf"), 1.
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    ws, dW = torch.empty(wsb, dtype=torch.uint8, device="cuda:0"), torch.empty(k, m, device="cuda:0")
+    ntp.ntp_nn_bwd(A, None, H, dH, None, dW, n, k, m, act, ntp.NTP_F32, ws, wsb, torch.cuda.current_stream())
+    A64, Z64 = A.double(), dH.double()
+    if act == ntp.NTP_ACT_RELU:
+        Z64 = torch.where(H > 0, Z64, 0.)
+    plain = [c for c in range(k) if c not in (5, 6)]
+    got, A64 = dW.double()[plain], A64[:, plain]
+    rest = A64.abs().amax(0)[:, None] * Z64.abs().sum(0) + A64.abs().sum(0)[:, None] * Z64.abs().amax(0)
+    bound = (2.0 ** -21 + (24 + n / 128 / 32 + 64) * 2.0 ** -24) * (A64.abs().T @ Z64.abs()) + 2.0 ** -40 * rest + 2.0 ** -140          # (as many roundings of numbers below 2^-126 as there are ranges)
+    over = (got - A64.T @ Z64).abs() / bound
+    assert float(over.max()) <= 1, divmod(int(over.argmax()), m)
+    assert not bool(torch.isfinite(dW[5]).any())
 
 
 def test_wide_weight_gradients_in_half_the_workspace():
