@@ -262,11 +262,12 @@ __global__ void __launch_bounds__(512, 2) dw_kernel(const DwArgs g) {
 // element so far with two bits to spare; where one changes, all sums are brought to it (in the first rows, and seldom after them: a block of
 // normal numbers once in all).
 //
-// Bound: the loads, of which the registers hold one step ahead (48 KB a compute unit, masked 64): 627 MB for 256 x 256 on 306,129 rows in 168 us.  us
-// with three bf16 pieces, where the matrix pipe was the bound, / here, without and with the ReLU mask: 306,129 rows of 256 x 256 225 242 / 168
-// 206 (940 MB: 4.6 TB/s), 169,343 129 140 / 104 122, of 128 x 256 73 95 / 59 93, 200 x 172 on 200,000 133 144 / 112 126.  No branch stands between the
-// products of a step (with two, where scales and flags were stored by some lanes, 185 us), and reads issued in groups between them by order
-// of the compiler's scheduling barriers lose 7-9 %.
+// Bound: the loads, of which the registers hold one step ahead (48 KB a compute unit, masked 64): 627 MB for 256 x 256 on 306,129 rows in 165 us.  us
+// with three bf16 pieces, where the matrix pipe was the bound, / here, without and with the ReLU mask: 306,129 rows of 256 x 256 225 238 / 165
+// 198 (940 MB: 4.7 TB/s), 169,343 129 138 / 98 116, of 128 x 256 73 95 / 58 93, 200 x 172 on 200,000 133 144 / 112 126.  No branch stands between the
+// products of a step (with two, where scales and flags were stored by some lanes, 306,129 rows 185 us), and the first of them come before the wait
+// for the loads (after it 172).  A second step ahead does not fit the registers (spilled: 560); sums brought to the total's scale
+// every 128 rows instead of both at a change 177.
 // A sum runs through many more rows than in the shares of dw_kernel, so it is put away and begun anew every 128 rows: relative
 // error on 169,343 rows of 256 x 256 3.2e-7 (bf16 pieces 3.9e-7, dw_kernel 6.7e-7), on 306,129 3.9e-7 (4.8e-7), on a million 6.7e-7 (8.3e-7).
 template <bool MASK, bool TALL>
@@ -412,19 +413,21 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
                     for (int q = 0; q < 2; ++q) b[j][q] = src[((s * F + BK + 2 * wz + j) * 2 + q) * 64];
             };
             const int4 any0 = *reinterpret_cast<const int4*>(changed + table * 8), any1 = *reinterpret_cast<const int4*>(changed + table * 8 + 4);
-            if (row > r0 && __builtin_amdgcn_readfirstlane(any0.x | any0.y | any0.z | any0.w | any1.x | any1.y | any1.z | any1.w))
-                rescale(table == 0 ? 2 : table - 1, table);
             read_b(0, pb[0]);
             read_a(0, pa[0]);
+            if (row > r0 && __builtin_amdgcn_readfirstlane(any0.x | any0.y | any0.z | any0.w | any1.x | any1.y | any1.z | any1.w))
+                rescale(table == 0 ? 2 : table - 1, table);
 #pragma unroll
             for (int p = 0; p < 4; ++p) {              // 16 rows p / 2, column block p % 2 of A
                 if (p < 3) read_a(p + 1, pa[(p + 1) & 1]);
                 if (p == 1) read_b(1, pb[1]);
+                mfma_f16<2>(pa[p & 1], pb[p / 2], acc[p % 2]);
+                // the rows that follow are waited for under products, not before the first
+                if (p == 0) __builtin_amdgcn_sched_barrier(0);
                 if (p < 3) {
                     stage(p, buf ^ 1, next);
                     issue(x[p], p, row + 64);
                 }
-                mfma_f16<2>(pa[p & 1], pb[p / 2], acc[p % 2]);
             }
             table = next;
             __syncthreads();

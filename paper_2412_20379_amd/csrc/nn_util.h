@@ -60,7 +60,9 @@ template <int LIFT>
 __device__ __forceinline__ void cut_f16(const unsigned (&w)[8], int scale, uint4 (&piece)[2]) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     const float s = __uint_as_float((unsigned)scale << 23);
-    const float lift = LIFT, s2 = LIFT == 1 ? s : s * lift;
+    float lift = LIFT;
+    const float s2 = LIFT == 1 ? s : s * lift;
+    if constexpr (LIFT == 1) asm("" : "+s"(lift));          // (keeps the subtraction one instruction: a mixed multiply-add)
     unsigned hi[4], lo[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
