@@ -486,11 +486,12 @@ int pow2_up(int64_t x, int most) {
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //     against 39.1 us);
 //   k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
-//   fp32 whose tiles of 128 x 128 pair up without padding and whose blocks get 192 rows or more: 256 x 128 (or 128 x 256) per
-//     block of dw_shared_kernel (us in dw_kernel / here, without and with the ReLU mask: 256 x 256 on 24,576 rows 31.2 34.3 / 28.4 29.9, 49,152 46.6
-//     53.1 / 39.4 41.7, 128 x 256 on 65,536 36.6 42.2 / 32.9 40.5, 256 x 128 36.4 40.7 / 33.1 35.6).  Below that the longer tail of a block eats the
-//     gain (256 x 256 on 16,384 25.2 26.9 / 24.9 25.9, 128 x 256 on 32,768 25.7 28.6 / 25.5 29.9); with a padded pair the padding
-//     does (300 x 300 on 100,000 rows 0.168 / 0.206 ms, 602 x 128 on 58,241 0.070 / 0.077, both with bf16 pieces);
+//   fp32 whose tiles of 128 x 128 pair up, of an odd number of them all but the last (padding of a third or less), and whose blocks get 192
+//     rows or more: 256 x 128 (or 128 x 256) per block of dw_shared_kernel (us in dw_kernel / here, without and with the ReLU mask: 256 x 256 on
+//     24,576 rows 31.2 34.3 / 28.4 29.9, 49,152 46.6 53.1 / 39.4 41.7, 128 x 256 on 65,536 36.6 42.2 / 32.9 40.5, 256 x 128 36.4 40.7 / 33.1 35.6; with
+//     a padded pair 602 x 128 on 58,241 63.5 70.8 / 55.7 58.1, 300 x 128 42.8 48.5 / 40.7 43.0, 300 x 300 on 20,000 40.9 45.2 / 39.2 39.3 and on
+//     100,000 155 189 / 138 161).  Below that the longer tail of a block eats the gain (256 x 256 on 16,384 25.2 26.9 / 24.9 25.9, 128 x 256 on 32,768
+//     25.7 28.6 / 25.5 29.9); a padded pair on the side of dZ reads its mask for nothing (128 x 300 on 100,000 62.8 78.2 / 58.2 85.0);
 //   else 128 x 64, whose operands are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343
 //     rows 0.134 against 0.164 ms.
 // m <= 32 and more than three row tiles of A take four of them side by side: whole rows of A from few blocks (us with one /
@@ -504,8 +505,9 @@ int pow2_up(int64_t x, int most) {
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE };
 int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
     const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
-    if (shared && !fp32_core && k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 49152)
-        return tk % 2 == 0 ? DW_SHARED_TALL : DW_SHARED_WIDE;
+    const bool tall = tk % 2 == 0 || (tm % 2 != 0 && tk > 1 && tk >= tm), wide = !tall && tm % 2 == 0;
+    if (shared && !fp32_core && k > 64 && m > 64 && (tall || wide) && n * (tall ? (tk + 1) / 2 * tm : tk * (tm / 2)) >= 49152)
+        return tall ? DW_SHARED_TALL : DW_SHARED_WIDE;
     if (k < 4) return DW_TINY;
     if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
     return fp32_core && k <= 32 ? DW_TINY : DW_NARROW;

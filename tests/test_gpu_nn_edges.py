@@ -263,8 +263,9 @@ def test_wide_weight_gradients(n, k, m, act):
         assert float(dW[k * m]) == 7.0
 
 
-# the fewest rows of one and of two pairs of tiles (256 x 128, 128 x 256, and odd sizes in them), rows of no whole step
-@pytest.mark.parametrize("n,k,m", [(49152, 130, 128), (49185, 256, 65), (49999, 70, 129), (24576, 256, 256), (24609, 200, 256), (70001, 128, 200), (66000, 256, 129)])
+# the fewest rows of one and of two pairs of tiles (256 x 128, 128 x 256, and odd sizes in them), an odd number of tiles, rows of no whole step
+@pytest.mark.parametrize("n,k,m", [(49152, 130, 128), (49185, 256, 65), (49999, 70, 129), (24576, 256, 256), (24609, 200, 256), (70001, 128, 200), (66000, 256, 129),
+                                   (24577, 257, 100), (16400, 602, 128), (12300, 300, 300)])
 @pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
 def test_wide_weight_gradients_of_uneven_columns(n, k, m, act):
     """Columns that differ by 24 decades, begin with zeros, stay tiny for some rows and then grow by up to six decades, hold one element only, or a
