@@ -42,6 +42,7 @@ struct DwArgs {
     int n_splits;
     int64_t rows_per_split;    // multiple of 16
     int shape;                 // see dw_shape
+    int swap, f16;             // dw_own_kernel: the wide operand is dZ (kt: wavefronts side by side in its columns); fp16 pieces
     int per_xcd;               // ceil(splits x tiles / 8): no XCD gets a block more than the others, which would be its second round
 };
 
@@ -450,6 +451,268 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
         }
 }
 
+// dW from pieces of which one operand's stay with their wavefront.  A wavefront owns 32 columns of the wide operand (W: A, or with SWAP dZ), loads and
+// cuts them and multiplies them from its registers; of the other one (V) a tile has 64 columns, which the block cuts once and hands out through
+// LDS.  A step is 64 rows; KW wavefronts stand side by side in the columns of W, and the 8 / KW shares of the block take a share of a step's rows
+// each.  Against dw_kernel: no sums of eight row shares at the end (of up to four), and so few registers for them that a block's first rows are all in
+// flight at once.  The products of the first pieces have an accumulator of their own and the small ones another: one rounding of the large sum
+// per 16 rows instead of six.  F16: two fp16 pieces an operand (nn_util.h), with the scales of dw_shared_kernel, but the first rows' are found before any
+// product; half the products, for many rows.
+//
+// Bound: latency for few rows (a block a compute unit of a few steps: loads, cut, products, partial sums), memory for many (256 x 40 on 169,343 rows 200
+// MB in 41 us, with sum_splits_kernel; from bf16 pieces 49).  Relative error against 64 bits, dw_kernel / here: 128 x 64 on 1,000 rows 1.18e-7 / 0.93e-7, 256 x 47 on
+// 2,708 1.34e-7 / 1.06e-7, 256 x 256 on 10,000 1.71e-7 / 1.18e-7; from fp16 pieces 256 x 47 on 40,961 2.61e-7 / 1.46e-7, on 306,129 5.8e-7 / 1.75e-7.  A second
+// step of W in flight changes nothing; tiles of 128 columns of V leave the masked ones no registers.
+template <bool MASK, bool SWAP, int KW, bool F16>
+__global__ void __launch_bounds__(512, 2) dw_own_kernel(const DwArgs g) {
+    constexpr int SHARES = 8 / KW, GROUPS = 4 / SHARES;          // 16-row groups of a step that are a wavefront's
+    constexpr int NP = F16 ? 2 : 3, FOLD_ROWS = 128;
+    extern __shared__ uint4 pieces[];          // [buffer][16 rows][32 columns of V][piece][lane]
+    constexpr int BUF = 4 * 2 * NP * 64;
+    int* const scales = reinterpret_cast<int*>(pieces + 2 * BUF);          // (F16) [3][columns of V]
+    int* const changed = scales + 3 * 64;                                  // [3][wavefront]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane & 31, h = lane >> 5;
+    const int minor = g.tiles_k * g.tiles_m, id = (int)blockIdx.x;
+    const int job = minor == 1 ? id : id % 8 * g.per_xcd + id / 8, split = job / minor, t = job % minor;          // (as in dw_kernel)
+    if (split >= g.n_splits) return;
+    const int k = g.k, m = g.m;
+    const int w0 = (SWAP ? t / g.tiles_k : t % g.tiles_k) * (32 * KW), v0 = (SWAP ? t % g.tiles_k : t / g.tiles_k) * 64;
+    const int64_t r0 = split * g.rows_per_split, r1 = min(r0 + g.rows_per_split, g.n);
+    const int share = wave / KW, wcol = 32 * (wave % KW) + r;
+
+    f32x16 acc[2][2] = {}, total[2] = {};          // acc: of the first pieces, and of the others; two blocks of 32 columns of V
+
+    // Rows 16 q + 8 h + j, j < 8, of this lane's column of W; rows 8 * (lane / 8) + j of its column of V.  Loads from a buffer that ends with the
+    // range: rows beyond it read as zero, and the lanes compute no addresses.  Columns beyond the matrix re-read the last one (their sums are
+    // not stored).
+    struct Raw { unsigned x[8], mk[8]; };
+    const int wp = SWAP ? m : k, vp = SWAP ? k : m;
+    const int vcol = 8 * wave + (lane & 7), vrow = lane & ~7;
+    const int w_off = 4 * (min(w0 + wcol, wp - 1) + (8 * h + 16 * GROUPS * share) * wp);
+    const int v_off = 4 * (min(v0 + vcol, vp - 1) + vrow * vp);
+    auto load = [&](unsigned (&x)[8], const void* at, int64_t row0, int pitch, int off, int first) {
+        const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(static_cast<const char*>(at) + min(row0, r1) * (4 * pitch)), 0,
+                                                           (int)min(max(r1 - row0, (int64_t)0), (int64_t)64) * (4 * pitch), 0x00020000);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b32(buf, off, (first + j) * (4 * pitch), 0);
+    };
+    Raw w[GROUPS], v;
+    auto issue_w = [&](int q, int64_t row0) {
+        load(w[q].x, SWAP ? g.Z : g.A, row0, wp, w_off, 16 * q);
+        if constexpr (MASK && SWAP) load(w[q].mk, g.mask, row0, wp, w_off, 16 * q);
+    };
+    auto issue_v = [&](int64_t row0) {
+        load(v.x, SWAP ? g.A : g.Z, row0, vp, v_off, 0);
+        if constexpr (MASK && !SWAP) load(v.mk, g.mask, row0, vp, v_off, 0);
+    };
+    auto mask_unit = [](Raw& x) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x.x[j] = __uint_as_float(x.mk[j]) > 0.f ? x.x[j] : 0u;
+    };
+    int w_scale = F16_SCALE_MAX, v_scale = F16_SCALE_MAX;
+    auto adapt = [](int& scale, float largest) {
+        const int need = f16_scale(largest);
+        const bool over = scale > need;
+        scale = over ? max(need - 2, 0) : scale;
+        return __ballot(over) != 0;
+    };
+    auto cut = [](const unsigned (&x)[8], int scale, uint4 (&piece)[NP]) {
+        if constexpr (F16) cut_f16<2048>(x, scale, piece);
+        else cut_row8<float, CORE_BF16>(x, piece);
+    };
+    // the rows of V that follow into buffer buf, their columns' scales into table `table`
+    auto stage_v = [&](int buf, int table) {
+        if constexpr (MASK && !SWAP) mask_unit(v);
+        if constexpr (F16) {
+            unsigned y = __float_as_uint(max_of_halves(largest8(v.x, 0.f)));          // of the eight lanes that hold the column
+            const auto quarters = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+            y = max(quarters[0], quarters[1]);
+            y = max(y, (unsigned)__builtin_amdgcn_update_dpp(0, (int)y, 0x128, 0xf, 0xf, true));          // row_ror:8
+            changed[table * 8 + wave] = adapt(v_scale, __uint_as_float(y));
+            scales[table * 64 + vcol] = v_scale;
+        }
+        uint4 p[NP];
+        cut(v.x, v_scale, p);
+        const int at = buf * BUF + ((vrow / 16 * 2 + vcol / 32) * NP) * 64 + (vrow / 8 & 1) * 32 + (vcol & 31);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) pieces[at + i * 64] = p[i];
+    };
+    // sums to other scales: d, of the operand whose columns are the lanes of a block, or of one of its rows
+    auto scale_element = [&](int b, int e, int d) {
+        acc[0][b][e] = ldexpf(acc[0][b][e], d);
+        acc[1][b][e] = ldexpf(acc[1][b][e], d);
+        total[b][e] = ldexpf(total[b][e], d);
+    };
+    auto rescale_lanes = [&](int b, int d) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) scale_element(b, e, d);
+    };
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q) issue_w(q, r0);
+    issue_v(r0);
+    stage_v(0, 0);
+    issue_v(r0 + 64);
+    if constexpr (F16) {
+        float largest = 0.f;
+#pragma unroll
+        for (int q = 0; q < GROUPS; ++q) {
+            if constexpr (MASK && SWAP) mask_unit(w[q]);
+            largest = largest8(w[q].x, largest);
+        }
+        adapt(w_scale, max_of_halves(largest));
+    }
+    __syncthreads();
+    int buf = 0, table = 0;
+    // multiply the 64 rows of which those of W are in w, which is refilled, while the next ones of V come into the other buffer
+    auto step = [&](int64_t row) {
+        const int next = table == 2 ? 0 : table + 1;
+        const uint4* src = pieces + buf * BUF + lane;
+        if constexpr (F16) {
+            const int4 any0 = *reinterpret_cast<const int4*>(changed + table * 8), any1 = *reinterpret_cast<const int4*>(changed + table * 8 + 4);
+            if (row > r0 && __builtin_amdgcn_readfirstlane(any0.x | any0.y | any0.z | any0.w | any1.x | any1.y | any1.z | any1.w)) {
+                const int* from = scales + (table == 0 ? 2 : table - 1) * 64;
+                const int* to = scales + table * 64;
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    if constexpr (SWAP) {
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int c = 32 * b + 8 * (e / 4) + 4 * h + e % 4;
+                            scale_element(b, e, to[c] - from[c]);
+                        }
+                    } else {
+                        rescale_lanes(b, to[32 * b + r] - from[32 * b + r]);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < GROUPS; ++q) {
+            uint4 pv[2][NP], pw[NP];
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int i = 0; i < NP; ++i) pv[b][i] = src[(((GROUPS * share + q) * 2 + b) * NP + i) * 64];
+            if constexpr (MASK && SWAP) mask_unit(w[q]);
+            if constexpr (F16) {
+                const int before = w_scale;
+                if (adapt(w_scale, max_of_halves(largest8(w[q].x, 0.f)))) {
+                    const int d = w_scale - before;
+                    if constexpr (SWAP) {
+                        rescale_lanes(0, d);
+                        rescale_lanes(1, d);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const int de = __shfl(d, 8 * (e / 4) + 4 * h + e % 4);
+                            scale_element(0, e, de);
+                            scale_element(1, e, de);
+                        }
+                    }
+                }
+            }
+            cut(w[q].x, w_scale, pw);
+            issue_w(q, row + 64);
+            auto mul = [&](int i, int j, f32x16 (&s)[2]) {          // pieces i of W and j of V
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    const uint4 x = SWAP ? pv[b][j] : pw[i], y = SWAP ? pw[i] : pv[b][j];
+                    if constexpr (F16) s[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), s[b], 0, 0, 0);
+                    else s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), s[b], 0, 0, 0);
+                }
+            };
+            if constexpr (F16) {
+                mul(1, 0, acc[1]);
+                mul(0, 0, acc[0]);
+                mul(0, 1, acc[1]);
+            } else {
+                mul(NP - 1, 0, acc[1]);
+                mul(0, 0, acc[0]);
+                mul(1, 1, acc[1]);
+                mul(0, NP - 1, acc[1]);
+                mul(1, 0, acc[1]);
+                mul(0, 1, acc[1]);
+            }
+            if (q == GROUPS - 1) {
+                stage_v(buf ^ 1, next);
+                issue_v(row + 128);
+            }
+        }
+        table = next;
+        buf ^= 1;
+        __syncthreads();
+    };
+    static_assert(FOLD_ROWS == 128, "two steps");
+    for (int64_t row = r0; row < r1; row += FOLD_ROWS) {
+        step(row);
+        if (row + 64 < r1) step(row + 64);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) total[b][e] += F16 ? f16_sum(acc[0][b][e], acc[1][b][e]) : acc[0][b][e] + acc[1][b][e];
+            acc[0][b] = acc[1][b] = f32x16{};
+        }
+    }
+    if constexpr (F16) {          // without the scales (those of V: of the last rows multiplied)
+        const int* last = scales + (table == 0 ? 2 : table - 1) * 64;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int row = 8 * (e / 4) + 4 * h + e % 4;
+            const int of_row = SWAP ? 0 : __shfl(w_scale, row);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) total[b][e] = f16_result(total[b][e], SWAP ? w_scale + last[32 * b + row] : last[32 * b + r] + of_row);
+        }
+        if constexpr (SHARES > 1) __syncthreads();          // (the sums may lie where the scales were)
+    }
+    if constexpr (SHARES > 1) {          // (the pieces are read: the last step ended with a barrier)
+        float* const sums = reinterpret_cast<float*>(pieces) + 2048 * (wave % KW) + lane;
+        constexpr int SHARE = 2048 * KW;
+        if (share > 0) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sums[(share - 1) * SHARE + (b * 16 + e) * 64] = total[b][e];
+        }
+        __syncthreads();
+        if (share > 0) return;
+#pragma unroll
+        for (int s = 0; s < SHARES - 1; ++s)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) total[b][e] += sums[s * SHARE + (b * 16 + e) * 64];
+    }
+    // element e of a 32 x 32 block: row 8 * (e / 4) + 4 * h + e % 4, a column of A; column r, of dZ
+    float* out = g.out + (int64_t)split * k * m;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int row = 8 * (e / 4) + 4 * h + e % 4;
+            const int kc = SWAP ? v0 + 32 * b + row : w0 + 32 * (wave % KW) + row, mc = SWAP ? w0 + wcol : v0 + 32 * b + r;
+            if (kc < k && mc < m) out[(int64_t)kc * m + mc] = total[b][e];
+        }
+}
+
+template <bool MASK, bool SWAP, int KW>
+void launch_dw_own(const DwArgs& g, hipStream_t st) {
+    constexpr int lds = 2 * 4 * 2 * 3 * 1024;
+    static_assert((8 / KW - 1) * KW * 8192 <= lds && 2 * 4 * 2 * 2 * 1024 + 3 * (64 + 8) * 4 <= lds, "the sums of the other shares, and two pieces with their scales");
+    if (g.f16) hipLaunchKernelGGL((dw_own_kernel<MASK, SWAP, KW, true>), dim3(8u * (unsigned)g.per_xcd), dim3(512), lds, st, g);
+    else hipLaunchKernelGGL((dw_own_kernel<MASK, SWAP, KW, false>), dim3(8u * (unsigned)g.per_xcd), dim3(512), lds, st, g);
+}
+
+template <bool MASK>
+void launch_dw_own_any(const DwArgs& g, hipStream_t st) {
+    switch (g.kt) {
+        case 8: return g.swap ? launch_dw_own<MASK, true, 8>(g, st) : launch_dw_own<MASK, false, 8>(g, st);
+        case 4: return g.swap ? launch_dw_own<MASK, true, 4>(g, st) : launch_dw_own<MASK, false, 4>(g, st);
+        default: return g.swap ? launch_dw_own<MASK, true, 2>(g, st) : launch_dw_own<MASK, false, 2>(g, st);
+    }
+}
+
 template <bool MASK, bool TALL>
 void launch_dw_shared(const DwArgs& g, hipStream_t st) {
     constexpr int F = 12, lds = 2 * 2 * F * 2 * 1024 + 3 * (32 * F + 8) * 4;
@@ -485,7 +748,16 @@ int pow2_up(int64_t x, int most) {
 //     (2 x 64 on 306,129 rows 0.025 ms against 0.111 in tiles through LDS, 3 x 256 0.077 against 0.186);
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //     against 39.1 us);
-//   k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
+//   fp32 with m > 32 in dw_own_kernel, 256 x 64 (or 64 x 256 for k <= 64): always for m <= 64, else while the tiles, each of which reads its columns of A
+//     again, are few against the rows.  From fp16 pieces from F16_ROWS on, as in dw_shared_kernel: in a sum of few products each one's error shows, which of
+//     fp16 pieces is up to 2^-21 to either side, of bf16 pieces to one.  us in the shapes below / there, without and with the ReLU mask: 256 x 47 on 1,000 rows
+//     15.0 15.9 / 9.2 10.0, 24,000 18.0 18.8 / 15.7 16.7, 41,000 21.6 23.4 / 18.7 20.2, 200,000 47.6 56.4 / 46.2 52.9; 128 x 40 on 24,000 16.7 17.5 / 12.7 13.1; 64 x 47 on
+//     3,000 11.7 14.0 / 8.4 9.1; 602 x 64 on 41,000 32.1 35.6 / 29.1 31.7; 128 x 128 on 10,000 17.4 17.9 / 12.1 13.1, 200,000 48.2 65.4 / 43.7 61.5.  256 x 256 on
+//     10,000 24.4 22.0 / 20.5 19.9, 24,000 29.8 32.4 / 27.7 29.5, 41,000 33.9 36.1 / 33.8 38.0; 300 x 256 (eight tiles) on 10,000 25.2 24.9 / 24.6 23.9, 24,000 30.2
+//     33.8 / 40.6 42.7; 602 x 128 (six) on 10,000 22.7 23.9 / 21.1 22.5, 24,000 30.7 32.0 / 35.1 36.8; 200 x 172 (three) on 41,000 30.9 32.9 / 27.2 31.5, 100,000 54.0 56.5 / 50.1
+//     57.4; 128 x 256 (four of half the size) on 60,000 30.8 38.6 / 30.0 37.2, 100,000 40.2 53.5 / 44.3 61.7.  k <= 64: 41 x 128 on 100,000 22.3 28.4 / 19.4 26.9,
+//     200,000 30.9 43.5 / 28.6 44.8; 64 x 256 54.7 94.3 / 49.2 88.6; 16 x 47 on 41,000 13.1 15.2 / 11.7 12.3, 200,000 20.5 25.0 / 22.0 25.1;
+//   else k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
 //   fp32 whose tiles of 128 x 128 pair up, of an odd number of them all but the last (padding of a third or less), and whose blocks get 192
 //     rows or more: 256 x 128 (or 128 x 256) per block of dw_shared_kernel (us in dw_kernel / here, without and with the ReLU mask: 256 x 256 on
 //     24,576 rows 31.2 34.3 / 28.4 29.9, 49,152 46.6 53.1 / 39.4 41.7, 128 x 256 on 65,536 36.6 42.2 / 32.9 40.5, 256 x 128 36.4 40.7 / 33.1 35.6; with
@@ -502,9 +774,13 @@ int pow2_up(int64_t x, int most) {
 // (602 x 128 on 58,241 rows 0.101 -> 0.070 ms, 384 x 384 on 169,343 0.465 -> 0.295, 700 x 100 on 8,000 0.033 -> 0.023).
 // Two column tiles side by side where there are two (they share the rows of A through the L1), the other wavefronts share out
 // the rows.
-enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE };
+constexpr int64_t F16_ROWS = 24576;
+enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE, DW_OWN };
 int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
     const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
+    const int64_t own_tiles = (k + 255) / 256 * ((m + 63) / 64), most = k <= 128 ? 262144 : n < F16_ROWS ? 98304 : 131072;
+    const bool own = k <= 64 ? m > 128 || n <= 131072 : m <= 64 || (k <= 128 && m <= 128) || n * own_tiles <= most;
+    if (shared && !fp32_core && k >= 4 && m > 32 && own) return DW_OWN;
     const bool tall = tk % 2 == 0 || (tm % 2 != 0 && tk > 1 && tk >= tm), wide = !tall && tm % 2 == 0;
     if (shared && !fp32_core && k > 64 && m > 64 && (tall || wide) && n * (tall ? (tk + 1) / 2 * tm : tk * (tm / 2)) >= 49152)
         return tall ? DW_SHARED_TALL : DW_SHARED_WIDE;
@@ -527,6 +803,20 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
         g.per_xcd = (int)(((int64_t)g.n_splits * g.tiles_k * g.tiles_m + 7) / 8);
         return g;
     }
+    if (shape == DW_OWN) {
+        g.f16 = n >= F16_ROWS;
+        g.swap = k <= 32 || (k <= 64 && m > 64);
+        const int64_t wide = g.swap ? m : k, narrow = g.swap ? k : m;
+        g.kt = wide <= 64 ? 2 : wide <= 128 ? 4 : 8;
+        const int tw = (int)((wide + 32 * g.kt - 1) / (32 * g.kt)), tv = (int)((narrow + 63) / 64);
+        g.tiles_k = g.swap ? tv : tw;
+        g.tiles_m = g.swap ? tw : tv;
+        const int64_t s = std::min(std::max<int64_t>(1, compute_units() / (tw * tv)), (n + 63) / 64);
+        g.rows_per_split = ((n + s - 1) / s + 63) / 64 * 64;
+        g.n_splits = (int)((n + g.rows_per_split - 1) / g.rows_per_split);
+        g.per_xcd = (int)(((int64_t)g.n_splits * tw * tv + 7) / 8);
+        return g;
+    }
     const int ta = shape == DW_TINY ? 1 : shape == DW_SHORT ? 2 : 4, tn = shape == DW_TINY || shape == DW_NARROW ? 1 : 2;
     g.kt = shape == DW_NARROW && k > 384 && n > 10000 ? 4 : 1;
     g.mt = shape == DW_NARROW ? 1 : pow2_up((m + 32 * tn - 1) / (32 * tn), shape == DW_TINY ? 8 : shape == DW_SHORT ? 4 : 2);
@@ -547,6 +837,7 @@ void launch_dw_any(const DwArgs& g, hipStream_t st) {
     switch (g.shape) {
         case DW_SHARED_TALL: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, true>(g, st) : launch_dw_shared<false, true>(g, st); break;
         case DW_SHARED_WIDE: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_shared<true, false>(g, st) : launch_dw_shared<false, false>(g, st); break;
+        case DW_OWN: if constexpr (sizeof(T) == 4 && C == CORE_BF16) g.mask ? launch_dw_own_any<true>(g, st) : launch_dw_own_any<false>(g, st); break;
         case DW_TINY:
             if constexpr (sizeof(T) == 2 || C == CORE_F32) g.mask ? launch_dw<T, C, true, 1, 1, 1, 1>(g, st) : launch_dw<T, C, false, 1, 1, 1, 1>(g, st);
             break;

@@ -362,7 +362,7 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
             const int scales[4] = {rs.x, rs.y, rs.z, rs.w};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float v = f16_result(sums[0][0][4 * e4 + i], sums[1][0][4 * e4 + i], scales[i] + col_scale);
+                const float v = f16_result(f16_sum(sums[0][0][4 * e4 + i], sums[1][0][4 * e4 + i]), scales[i] + col_scale);
                 __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, off + (8 * e4 + i) * N * 4, 0, NT ? 2 : 0);
             }
         }

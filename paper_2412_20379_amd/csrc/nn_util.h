@@ -54,7 +54,8 @@ __device__ __forceinline__ unsigned pack_pair(unsigned even, unsigned odd) {
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // scale of numbers of which m is the largest magnitude, as a biased exponent; (up to 243: times 2048 it is still a float)
-__device__ __forceinline__ int f16_scale(float m) { return min(268 - (int)((__float_as_uint(m) >> 23) & 255), 243); }
+constexpr int F16_SCALE_MAX = 243;
+__device__ __forceinline__ int f16_scale(float m) { return min(268 - (int)((__float_as_uint(m) >> 23) & 255), F16_SCALE_MAX); }
 // LIFT: 2048, or 1 (see below)
 template <int LIFT>
 __device__ __forceinline__ void cut_f16(const unsigned (&w)[8], int scale, uint4 (&piece)[2]) {
@@ -107,8 +108,9 @@ __device__ __forceinline__ void mfma_f16(const uint4 (&a)[2], const uint4 (&b)[T
         for (int j = 0; j < TN; ++j)
             acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a[p == 2]), __builtin_bit_cast(f16x8, b[j][p == 1]), acc[j], 0, 0, 0);
 }
-// an element of the product from its two sums; scales: those of its row and column added
-__device__ __forceinline__ float f16_result(float hh, float cross, int scales) { return ldexpf(__builtin_fmaf(cross, 1.f / 2048.f, hh), 254 - scales); }
+// an element of the product from its two sums, and without its scales (those of its row and column added)
+__device__ __forceinline__ float f16_sum(float hh, float cross) { return __builtin_fmaf(cross, 1.f / 2048.f, hh); }
+__device__ __forceinline__ float f16_result(float sum, int scales) { return ldexpf(sum, 254 - scales); }
 
 __device__ __forceinline__ float elem_to_f32(float v) { return v; }
 __device__ __forceinline__ float elem_to_f32(unsigned short v) { return __uint_as_float((unsigned)v << 16); }

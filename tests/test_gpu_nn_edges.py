@@ -303,6 +303,19 @@ def test_wide_weight_gradients_of_uneven_columns(n, k, m, act):
     assert not bool(torch.isfinite(dW[5]).any())
 
 
+# one wavefront, two, four and eight side by side in the wide operand, which is A or (k <= 32, or 64 < m) dZ; a step of 64 rows and the rows around it,
+# two steps, a range's last row; bf16 pieces, and fp16 pieces from 24,576 rows on; tiles that end within a wavefront's columns, and the most rows that are taken so
+@pytest.mark.parametrize("n,k,m", [(1, 64, 33), (63, 40, 64), (64, 128, 47), (65, 256, 64), (129, 225, 41), (700, 33, 65), (2708, 16, 47), (3001, 7, 129), (16449, 64, 256),
+                                   (41001, 100, 256), (16384, 257, 66), (24575, 100, 47), (24576, 16, 47), (24577, 64, 40), (40961, 100, 47), (24640, 130, 200), (131072, 41, 128), (131073, 41, 128), (32768, 256, 256),
+                                   (5003, 1433, 40), (200003, 65, 64)])
+@pytest.mark.parametrize("act", [ntp.NTP_ACT_NONE, ntp.NTP_ACT_RELU])
+def test_weight_gradients_of_owned_columns(n, k, m, act):
+    """whole numbers exactly, random ones and uneven columns within the bounds of the two tests above"""
+    test_wide_weight_gradients(n, k, m, act)
+    if n > 2000 and k > 6:
+        test_wide_weight_gradients_of_uneven_columns(n, k, m, act)
+
+
 def test_wide_weight_gradients_in_half_the_workspace():
     """the shared kernel's twice as many ranges are an offer: half of the workspace that is asked for goes on being enough, a quarter not"""
     import torch
