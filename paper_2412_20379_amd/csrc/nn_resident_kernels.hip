@@ -21,6 +21,8 @@
 // 121 -> 85.  A block spends some 12 us on B before its first rows; with one tile of 256 x 256 in flight a compute unit (32 KB, all that the
 // registers leave) they arrive at 2 TB/s in each direction.  Relative error against 64 bits 1.30e-7 where the bf16 pieces have 2.42e-7 (256 terms;
 // 128 1.01e-7 / 1.71e-7; 100 1.04e-7 / 1.58e-7), largest error over the results' rms 1.4e-6 / 3.1e-6.
+// With a mask it can leave that as bits for the kernel of dW (nn_mask_rows): eight columns of 32 rows are 32 bytes, put together in LDS beside the
+// pieces (masked dA 256 -> 256 on 306,129 rows 179 -> 182 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,6 +44,8 @@ struct ResidentArgs {
     int b_kcontig;         // B[kk][col] at B[col * ldb + kk] (else at B[kk * ldb + col])
     int relu;
     int nt;
+    unsigned char* bits;   // (nullable) resident_f16_kernel with a mask: bit c % 8 of bits[c / 8 * bits_rows + row] says whether mask[row][c] > 0
+    int bits_rows;         // rows rounded up to whole tiles, see nn_mask_rows
 };
 
 // eight elements of B's column col from row k on, zero outside the matrix
@@ -246,6 +250,7 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
     constexpr int GROUP = KC * 2 * 64, PART = RG * GROUP;         // 16-byte fragments of the pieces of 32 rows, and of a tile
     extern __shared__ uint4 lds[];
     int* const row_scale = reinterpret_cast<int*>(lds + 2 * PART);
+    unsigned char* const row_bits = reinterpret_cast<unsigned char*>(row_scale + 2 * RG * 32);          // (MASK: RG is 1) [buffer][eight columns][row]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = lane >> 5, r = lane & 31;
@@ -277,9 +282,14 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
         float m = 0.f;
 #pragma unroll
         for (int s = 0; s < SEGS; ++s) {
+            unsigned bits = 0;
             if constexpr (MASK) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) w[s][e] = __uint_as_float(mask[s][e]) > 0.f ? w[s][e] : 0u;
+                for (int e = 0; e < 8; ++e) {
+                    const bool on = __uint_as_float(mask[s][e]) > 0.f;
+                    w[s][e] = on ? w[s][e] : 0u;
+                    bits |= on ? 1u << e : 0u;
+                }
             }
             if (s == SEGS - 1 && K != 16 * KC) {            // drop the elements that stand before the eight, zeros come in at the end
                 const int over = max(8 * (q + 16 * s) - (K - 8), 0);
@@ -287,6 +297,10 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
                 for (int d = 4; d >= 1; d /= 2)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) w[s][e] = over >= 8 ? 0u : (over & d) ? (e + d < 8 ? w[s][e + d < 8 ? e + d : 7] : 0u) : w[s][e];
+                bits >>= min(over, 8);
+            }
+            if constexpr (MASK) {
+                if (KC == 8 * SEGS || q + 16 * s < 2 * KC) row_bits[(buf * 32 + q + 16 * s) * 32 + row] = (unsigned char)bits;
             }
             m = largest8(w[s], m);
         }
@@ -353,6 +367,13 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
         // element e: row 8 * (e / 4) + 4 * h + e % 4, column r; rows and columns beyond the matrix are out of the buffer's range
         const int64_t row0 = ((int64_t)t * RG + group) * 32;
         const int left = (int)min(max(g.n - row0, (int64_t)0), (int64_t)32);
+        if constexpr (MASK) {          // the bits of four times eight columns, from eight lanes
+            const auto out_bits = __builtin_amdgcn_make_buffer_rsrc(g.bits + row0, 0, g.bits ? (K + 7) / 8 * g.bits_rows - (int)row0 : 0, 0x00020000);
+            const int eight = 4 * wave + (lane >> 1 & 3), half = 16 * (lane & 1);
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            const u32x4 v = *reinterpret_cast<const u32x4*>(row_bits + (buf * 32 + eight) * 32 + half);
+            __builtin_amdgcn_raw_buffer_store_b128(v, out_bits, lane < 8 && eight < (K + 7) / 8 ? eight * g.bits_rows + half : 0x7fff0000, 0, 0);
+        }
         const auto out = __builtin_amdgcn_make_buffer_rsrc(g.C + min(row0, g.n) * N, 0, left * N * 4, 0x00020000);
         unsigned off = col < N ? (4 * h * N + col) * 4 : 0x7fff0000;
         asm("" : "+v"(off));            // (not sixteen offsets kept in registers from tile to tile)
@@ -375,7 +396,7 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
     {
         const auto nowhere = __builtin_amdgcn_make_buffer_rsrc(g.C, 0, 0, 0x00020000);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) __builtin_amdgcn_raw_buffer_store_b32(0u, nowhere, 64 * e, 0, 0);
+        for (int e = 0; e < 16 + MASK; ++e) __builtin_amdgcn_raw_buffer_store_b32(0u, nowhere, 64 * e, 0, 0);
     }
     __syncthreads();
     for (int buf = 0; t < tiles; t += step, buf ^= 1) {
@@ -389,7 +410,7 @@ __global__ void __launch_bounds__(512, 2) resident_f16_kernel(const ResidentArgs
 
 template <bool MASK, bool NT, int KC, int RG>
 void launch_f16_nt(const ResidentArgs& g, hipStream_t st) {
-    constexpr int lds = 2 * RG * (KC * 2 * 1024 + 128);
+    constexpr int lds = 2 * RG * (KC * 2 * 1024 + 128) + (MASK ? 2 * 32 * 32 : 0);
     static bool allowed[64] = {};
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -444,11 +465,13 @@ static bool f16_takes(int64_t n, int64_t K, int64_t N, bool relu) {
     return !relu && K > 64 && K <= 256 && N > 64 && N <= 256 && n > (N <= 128 && K > 128 ? 98304 : 57344);
 }
 
+bool nn_resident_writes_bits(int64_t n, int64_t K, int64_t N) { return f16_takes(n, K, N, false) && n <= NN_MASK_MOST_ROWS; }
+
 bool nn_resident_takes(int64_t n, int64_t K, int64_t N, bool relu) { return bf16_takes(n, K, N) || f16_takes(n, K, N, relu); }
 
 int launch_nn_resident(const float* A, const float* mask, const float* B, float* C, int64_t n, int64_t K, int64_t N, int64_t ldb,
-                       bool b_kcontig, bool relu, bool nt, void* stream) {
-    ResidentArgs g{A, mask, B, C, n, ldb, (int)K, (int)N, b_kcontig, relu, nt};
+                       bool b_kcontig, bool relu, bool nt, unsigned char* bits, void* stream) {
+    ResidentArgs g{A, mask, B, C, n, ldb, (int)K, (int)N, b_kcontig, relu, nt, bits, (int)nn_mask_rows(n)};
     const hipStream_t st = (hipStream_t)stream;
     if (f16_takes(n, K, N, relu)) {
         if (mask) launch_f16_k<true>(g, nt, st);

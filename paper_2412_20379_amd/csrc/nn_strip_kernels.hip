@@ -683,7 +683,7 @@ int launch_bf16(StripArgs g, hipStream_t st) {
 // B[col * ldb + kk]; n, K, N >= 1.  fp32_core: fp32 operands on the fp32 matrix instructions
 // (K < 64 or N <= 32: always).
 int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int64_t n, int64_t K, int64_t N, int64_t lda,
-                    int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, bool fp32_core, void* stream) {
+                    int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, bool fp32_core, void* stream, unsigned char* bits) {
     StripArgs g{};
     g.A = A; g.mask = mask; g.B = B; g.C = C;
     g.n = n; g.K = (int)K; g.N = (int)N;
@@ -693,7 +693,7 @@ int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int
     if (dtype == NTP_F32 && !fp32_core && nn_resident_takes(n, K, N, relu) && lda == K && ldc == N) {
         const bool nt = ldc * 4 % 128 == 0 && (uintptr_t)C % 128 == 0 && n * ldc * 4 > CACHE_BYTES;
         return launch_nn_resident(static_cast<const float*>(A), static_cast<const float*>(mask), static_cast<const float*>(B), static_cast<float*>(C),
-                                  n, K, N, ldb, b_kcontig, relu, nt, stream);
+                                  n, K, N, ldb, b_kcontig, relu, nt, bits, stream);
     }
     const int rc = dtype == NTP_BF16 ? launch_bf16(g, st) : launch_f32(g, fp32_core, st);
     const hipError_t e = hipGetLastError();

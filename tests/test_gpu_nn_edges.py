@@ -328,3 +328,33 @@ def test_wide_weight_gradients_in_half_the_workspace():
     assert torch.equal(dW.double(), A.double().T @ dH.double())
     with pytest.raises(Exception, match="workspace too small"):
         ntp.ntp_nn_bwd(A, None, None, dH, None, dW, n, k, m, ntp.NTP_ACT_NONE, ntp.NTP_F32, ws, wsb // 4)
+
+
+# the fewest rows, rows of no whole tile or step, columns of dZ in no whole eights; dW's blocks of 256 x 128, 128 x 256, and of owned columns
+@pytest.mark.parametrize("n,k,m", [(57345, 256, 256), (57377, 200, 65), (98350, 100, 250), (98333, 128, 129), (70001, 129, 71), (98305, 128, 200), (98311, 65, 140), (60001, 97, 128), (58241, 256, 101)])
+def test_gradients_that_share_the_mask_as_bits(n, k, m):
+    """dW beside dA, whose kernel leaves the mask as bits, has the bits that it has alone, from H, and in a workspace without room for the mask"""
+    import torch
+    print("nn mask bits", n, k, m, file=sys.stderr, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(n + k)
+    A, dH, W = (torch.randn(s, generator=g, device="cuda:0") for s in ((n, k), (n, m), (k, m)))
+    H = torch.randn(n, m, generator=g, device="cuda:0").clamp(min=0)
+    H[::7, ::3] = float("nan")
+    H[1::11, 2::5] = -0.0
+    H[2::13, 1::3] = float("inf")
+    H[3::17] = 1e-45
+    H[5::64, m - 1] = 1.
+    wsb = ntp.ntp_nn_bwd_workspace_bytes(n, k, m)
+    mask_bytes = (m + 7) // 8 * ((n + 63) // 64 * 64) + 64
+    st = torch.cuda.current_stream()
+    got = []
+    for alone, size in ((True, wsb), (False, wsb), (False, wsb - 1), (False, wsb - mask_bytes)):
+        ws = torch.full((size + 256,), 0xff, dtype=torch.uint8, device="cuda:0")
+        dA, dW = torch.empty(n, k, device="cuda:0"), torch.empty(k, m, device="cuda:0")
+        ntp.ntp_nn_bwd(A, None if alone else W, H, dH, None if alone else dA, dW, n, k, m, ntp.NTP_ACT_RELU, ntp.NTP_F32, ws, size, st)
+        assert bool((ws[size:] == 0xff).all())
+        got.append((dA, dW))
+    for dA, dW in got[1:]:
+        assert torch.equal(dW, got[0][1]) and torch.equal(dA, got[1][0])
+    want = A.double().T @ torch.where(H > 0, dH.double(), 0.)
+    assert float((got[0][1] - want).norm() / want.norm()) < 1e-6
