@@ -225,6 +225,41 @@ def test_products_from_fp16_pieces(n, k, m, direction):
     assert bool(((got - a @ w).abs() <= bound).all())
 
 
+# behind a ReLU: the fewest rows and columns, rows of no whole tile, up to more blocks of near zeros than a thread block lists (64 tiles)
+@pytest.mark.parametrize("n,k,m", [(163841, 65, 241), (163872, 97, 225), (163873, 128, 226), (163841, 129, 193), (164001, 161, 200), (170001, 112, 256), (163900, 208, 224),
+                                   (200000, 256, 256), (163841, 225, 255), (540001, 66, 256)])
+@pytest.mark.parametrize("kind", ["normal", "cancelling"])
+def test_a_relu_keeps_the_same_of_many_rows_as_of_few(n, k, m, kind):
+    """normal: one mask, and both within the bound of a product from pieces; among them zero and NaN rows, zero columns and whole numbers.  cancelling: rows
+    whose products cancel but for a few parts in 10^7, whose every block is formed again in the strips' way: the same bits"""
+    import torch
+    print("nn relu of many rows", n, k, m, kind, file=sys.stderr, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(n + 1000 * k + m)
+    st, R = torch.cuda.current_stream(), ntp.NTP_ACT_RELU
+    A, W = torch.randn(n, k, generator=g, device="cuda:0"), torch.randn(k, m, generator=g, device="cuda:0")
+    if kind == "cancelling":
+        half = k // 2
+        W[half:2 * half], W[2 * half:] = W[:half], 0.
+        A[:, half:2 * half] = -A[:, :half] * (1 + 2.0 ** -22 * torch.randn(n, half, generator=g, device="cuda:0"))
+    else:
+        A[100:140], A[77], A[n - 1] = 0., float("nan"), A[n - 1].round()
+        W[:, m // 2], W[:, 1] = 0., W[:, 1].round()
+        A[200:232, k // 2:] = 0
+    H, few, part = torch.full((n + 1, m), 7.0, device="cuda:0"), torch.empty(n, m, device="cuda:0"), n // (n // 20000) + 1          # (parts as long as each other)
+    ntp.ntp_nn_fwd(A, W, H, n, k, m, R, ntp.NTP_F32, st)
+    for b in range(0, n, part):
+        e = min(b + part, n)
+        ntp.ntp_nn_fwd(A[b:e], W, few[b:e], e - b, k, m, R, ntp.NTP_F32, st)
+    assert bool((H[n] == 7.0).all())
+    if kind == "cancelling":
+        assert torch.equal(H[:n], few)
+    else:
+        assert torch.equal(H[:n] > 0, few > 0) and not bool(H[77].any())
+        for b in range(0, n, part):
+            a, w = A[b:b + part].nan_to_num().double(), W.double()
+            assert bool(((H[b:min(b + part, n)].double() - (a @ w).clamp(min=0)).abs() <= (2.0 ** -21 + k * 2.0 ** -24) * (a.abs() @ w.abs())).all())
+
+
 # one to eight tiles of 256 x 128 or (k in an odd number of 128s) 128 x 256: row counts of
 # no whole step, of a step, of one row in the last range
 @pytest.mark.parametrize("n,k,m", [(131073, 130, 70), (131072, 256, 128), (131104, 200, 65), (65553, 129, 200), (65600, 256, 256),
