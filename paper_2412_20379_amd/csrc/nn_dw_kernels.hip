@@ -279,7 +279,7 @@ __device__ __forceinline__ void load_bits(unsigned (&x)[N], const DwArgs& g, int
 __device__ __forceinline__ unsigned bit_mask(unsigned x, int b) { return (unsigned)((int)(x << (31 - b)) >> 31); }
 
 // Wide dW from shared pieces: the eight wavefronts of a block own 64 x 64 each of a tile of 256 x 128 columns of A and dZ (TALL, or 128 x 256),
-// and all of them walk the same rows, 32 at a time.  Every column is loaded and cut (into two fp16 pieces, nn_util.h, one accumulator) by one
+// and all of them walk the same rows, 32 at a time.  Every column is loaded and cut (F16: into two fp16 pieces, nn_util.h, one accumulator) by one
 // wavefront, which finds its scale, and put into LDS in operand order, where those find it that need it; the pieces of the next
 // 32 rows go into the other half of the LDS while these are multiplied: one barrier per 32 rows, 101 KB.  A scale is that of the largest
 // element so far with two bits to spare; where one changes, all sums are brought to it (in the first rows, and seldom after them: a block of
@@ -287,19 +287,19 @@ __device__ __forceinline__ unsigned bit_mask(unsigned x, int b) { return (unsign
 //
 // Bound: the loads, of which the registers hold one step ahead (48 KB a compute unit, masked 64): 627 MB for 256 x 256 on 306,129 rows in 165 us.  us
 // with three bf16 pieces, where the matrix pipe was the bound, / here, without and with the ReLU mask: 306,129 rows of 256 x 256 225 238 / 165
-// 198 (940 MB: 4.7 TB/s; with the mask as bits 172), 169,343 129 138 / 98 116, of 128 x 256 73 95 / 58 93, 200 x 172 on 200,000 133 144 / 112 126.  No branch stands between the
+// 198 (940 MB: 4.7 TB/s; with the mask as bits 172), 169,343 129 138 / 98 116, of 128 x 256 73 95 / 58 93.  No branch stands between the
 // products of a step (with two, where scales and flags were stored by some lanes, 306,129 rows 185 us), and the first of them come before the wait
 // for the loads (after it 172).  A second step ahead does not fit the registers (spilled: 560); sums brought to the total's scale
 // every 128 rows instead of both at a change 177.
 // A sum runs through many more rows than in the shares of dw_kernel, so it is put away and begun anew every 128 rows: relative
 // error on 169,343 rows of 256 x 256 3.2e-7 (bf16 pieces 3.9e-7, dw_kernel 6.7e-7), on 306,129 3.9e-7 (4.8e-7), on a million 6.7e-7 (8.3e-7).
-template <Mask MASK, bool TALL>
+template <Mask MASK, bool TALL, bool F16>
 __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
     constexpr int BK = TALL ? 8 : 4, BZ = 12 - BK, WZ = BZ / 2, F = BK + BZ;          // F: fragments of 16 rows
-    constexpr int FOLD_ROWS = 128;
+    constexpr int NP = F16 ? 2 : 3, FOLD_ROWS = 128;
     extern __shared__ uint4 pieces[];          // [buffer][16 rows][fragment][piece][lane]
-    constexpr int BUF = 2 * F * 2 * 64;
-    int* const scales = reinterpret_cast<int*>(pieces + 2 * BUF);          // [3][columns of A, columns of dZ]
+    constexpr int BUF = 2 * F * NP * 64;
+    int* const scales = reinterpret_cast<int*>(pieces + 2 * BUF);          // (F16) [3][columns of A, columns of dZ]
     int* const changed = scales + 3 * 32 * F;                              // [3][wavefront]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -373,13 +373,14 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
         return __ballot(over) != 0 ? 1 : 0;
     };
     auto put = [&](const Raw& x, int u, int scale, int buf) {
-        uint4 p[2];
-        cut_f16<1>(x.x, scale, p);
+        uint4 p[NP];
+        if constexpr (F16) cut_f16<1>(x.x, scale, p);
+        else cut_row8<float, CORE_BF16>(x.x, p);
         const int frag = u < 2 ? u * F + (TALL ? wave : BK + wave) : h * F + (TALL ? BK + wave / 2 : wave / 2);
         const int slot = u < 2 ? lane : (lane >> 4 & 1) * 32 + (wave & 1) * 16 + (lane & 15);
-        const int at = buf * BUF + frag * 2 * 64 + slot;
-        pieces[at] = p[0];
-        pieces[at + 64] = p[1];
+        const int at = buf * BUF + frag * NP * 64 + slot;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) pieces[at + i * 64] = p[i];
     };
     Raw x[3];
     int changes = 0;
@@ -388,15 +389,19 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
         if (u == 0) {
             mask_unit(x[0], 0);
             mask_unit(x[1], 1);
-            changes = adapt(wide_scale, max_of_halves(largest8(x[1].x, largest8(x[0].x, 0.f))));
-            scales[table * 32 * F + (TALL ? 0 : 32 * BK) + wide_col] = wide_scale;
+            if constexpr (F16) {
+                changes = adapt(wide_scale, max_of_halves(largest8(x[1].x, largest8(x[0].x, 0.f))));
+                scales[table * 32 * F + (TALL ? 0 : 32 * BK) + wide_col] = wide_scale;
+            }
         } else if (u == 2) {
             mask_unit(x[2], 2);
-            const float half = max_of_halves(largest8(x[2].x, 0.f));
-            const auto quarters = __builtin_amdgcn_permlane16_swap(__float_as_uint(half), __float_as_uint(half), false, false);
-            changes |= adapt(narrow_scale, __uint_as_float(max(quarters[0], quarters[1])));
-            scales[table * 32 * F + (TALL ? 32 * BK : 0) + narrow_col] = narrow_scale;
-            changed[table * 8 + wave] = changes;            // (all lanes the same: no branch cuts the products off from what runs beside them)
+            if constexpr (F16) {
+                const float half = max_of_halves(largest8(x[2].x, 0.f));
+                const auto quarters = __builtin_amdgcn_permlane16_swap(__float_as_uint(half), __float_as_uint(half), false, false);
+                changes |= adapt(narrow_scale, __uint_as_float(max(quarters[0], quarters[1])));
+                scales[table * 32 * F + (TALL ? 32 * BK : 0) + narrow_col] = narrow_scale;
+                changed[table * 8 + wave] = changes;            // (all lanes the same: no branch cuts the products off from what runs beside them)
+            }
         }
         put(x[u], u, u < 2 ? wide_scale : narrow_scale, buf);
     };
@@ -432,27 +437,34 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
         for (const int64_t stop = min(row + FOLD_ROWS, r1); row < stop; row += 32, buf ^= 1) {
             const int next = table == 2 ? 0 : table + 1;
             const uint4* src = pieces + buf * BUF + lane;
-            uint4 pa[2][2], pb[2][2][2];               // operands of this product and of the next one
-            auto read_a = [&](int p, uint4 (&a)[2]) {
+            uint4 pa[2][1][NP], pb[2][2][NP];               // operands of this product and of the next one
+            auto read_a = [&](int p, uint4 (&a)[1][NP]) {
 #pragma unroll
-                for (int q = 0; q < 2; ++q) a[q] = src[((p / 2 * F + 2 * wk + p % 2) * 2 + q) * 64];
+                for (int q = 0; q < NP; ++q) a[0][q] = src[((p / 2 * F + 2 * wk + p % 2) * NP + q) * 64];
             };
-            auto read_b = [&](int s, uint4 (&b)[2][2]) {
+            auto read_b = [&](int s, uint4 (&b)[2][NP]) {
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
 #pragma unroll
-                    for (int q = 0; q < 2; ++q) b[j][q] = src[((s * F + BK + 2 * wz + j) * 2 + q) * 64];
+                    for (int q = 0; q < NP; ++q) b[j][q] = src[((s * F + BK + 2 * wz + j) * NP + q) * 64];
             };
-            const int4 any0 = *reinterpret_cast<const int4*>(changed + table * 8), any1 = *reinterpret_cast<const int4*>(changed + table * 8 + 4);
+            int4 any0 = {}, any1 = {};
+            if constexpr (F16) {
+                any0 = *reinterpret_cast<const int4*>(changed + table * 8);
+                any1 = *reinterpret_cast<const int4*>(changed + table * 8 + 4);
+            }
             read_b(0, pb[0]);
             read_a(0, pa[0]);
-            if (row > r0 && __builtin_amdgcn_readfirstlane(any0.x | any0.y | any0.z | any0.w | any1.x | any1.y | any1.z | any1.w))
-                rescale(table == 0 ? 2 : table - 1, table);
+            if constexpr (F16) {
+                if (row > r0 && __builtin_amdgcn_readfirstlane(any0.x | any0.y | any0.z | any0.w | any1.x | any1.y | any1.z | any1.w))
+                    rescale(table == 0 ? 2 : table - 1, table);
+            }
 #pragma unroll
             for (int p = 0; p < 4; ++p) {              // 16 rows p / 2, column block p % 2 of A
                 if (p < 3) read_a(p + 1, pa[(p + 1) & 1]);
                 if (p == 1) read_b(1, pb[1]);
-                mfma_f16<2>(pa[p & 1], pb[p / 2], acc[p % 2]);
+                if constexpr (F16) mfma_f16<2>(pa[p & 1][0], pb[p / 2], acc[p % 2]);
+                else mfma_parts<CORE_BF16, 1, 2, NP>(pa[p & 1], pb[p / 2], reinterpret_cast<f32x16 (&)[1][2]>(acc[p % 2]));
                 // the rows that follow are waited for under products, not before the first
                 if (p == 0) __builtin_amdgcn_sched_barrier(0);
                 if (p < 3) {
@@ -476,7 +488,7 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int ac = 64 * wk + 32 * i + 8 * (e / 4) + 4 * h + e % 4, rowk = c0 + ac;
-                if (col < m && rowk < k) out[(int64_t)rowk * m + col] = ldexpf(total[i][j][e], 254 - last[ac] - last[32 * BK + zc]);
+                if (col < m && rowk < k) out[(int64_t)rowk * m + col] = F16 ? ldexpf(total[i][j][e], 254 - last[ac] - last[32 * BK + zc]) : total[i][j][e];
             }
         }
 }
@@ -489,9 +501,9 @@ __global__ void __launch_bounds__(512, 2) dw_shared_kernel(const DwArgs g) {
 // per 16 rows instead of six.  F16: two fp16 pieces an operand (nn_util.h), with the scales of dw_shared_kernel, but the first rows' are found before any
 // product; half the products, for many rows.
 //
-// Bound: latency for few rows (a block a compute unit of a few steps: loads, cut, products, partial sums), memory for many (256 x 40 on 169,343 rows 200
-// MB in 41 us, with sum_splits_kernel; from bf16 pieces 49).  Relative error against 64 bits, dw_kernel / here: 128 x 64 on 1,000 rows 1.18e-7 / 0.93e-7, 256 x 47 on
-// 2,708 1.34e-7 / 1.06e-7, 256 x 256 on 10,000 1.71e-7 / 1.18e-7; from fp16 pieces 256 x 47 on 40,961 2.61e-7 / 1.46e-7, on 306,129 5.8e-7 / 1.75e-7.  A second
+// Bound: latency for few rows (a block a compute unit of a few steps: loads, cut, products, partial sums), memory for many (128 x 64 on 306,129 rows 235 MB
+// in 45 us, with sum_splits_kernel).  Relative error against 64 bits, dw_kernel / here: 128 x 64 on 1,000 rows 1.18e-7 / 0.93e-7, 256 x 47 on
+// 2,708 1.34e-7 / 1.06e-7, 256 x 256 on 10,000 1.71e-7 / 1.18e-7.  A second
 // step of W in flight changes nothing; tiles of 128 columns of V leave the masked ones no registers.
 template <Mask MASK, bool SWAP, int KW, bool F16>
 __global__ void __launch_bounds__(512, 2) dw_own_kernel(const DwArgs g) {
@@ -755,10 +767,10 @@ void launch_dw_own_any(const DwArgs& g, hipStream_t st) {
     }
 }
 
-template <Mask MASK, bool TALL>
+template <Mask MASK, bool TALL, bool F16>
 void launch_dw_shared(const DwArgs& g, hipStream_t st) {
-    constexpr int F = 12, lds = 2 * 2 * F * 2 * 1024 + 3 * (32 * F + 8) * 4;
-    auto kernel = dw_shared_kernel<MASK, TALL>;
+    constexpr int F = 12, lds = F16 ? 2 * 2 * F * 2 * 1024 + 3 * (32 * F + 8) * 4 : 2 * 2 * F * 3 * 1024;
+    auto kernel = dw_shared_kernel<MASK, TALL, F16>;
     static bool allowed[64] = {};
     int dev = 0;
     (void)hipGetDevice(&dev);
@@ -767,10 +779,12 @@ void launch_dw_shared(const DwArgs& g, hipStream_t st) {
     hipLaunchKernelGGL(kernel, dim3(8u * (unsigned)g.per_xcd), dim3(512), lds, st, g);
 }
 
-template <bool TALL>
-void launch_dw_shared_any(const DwArgs& g, hipStream_t st) {
-    g.bits ? launch_dw_shared<BITS, TALL>(g, st) : g.mask ? launch_dw_shared<FLOATS, TALL>(g, st) : launch_dw_shared<NONE, TALL>(g, st);
+template <bool TALL, bool F16>
+void launch_dw_shared_mask(const DwArgs& g, hipStream_t st) {
+    g.bits ? launch_dw_shared<BITS, TALL, F16>(g, st) : g.mask ? launch_dw_shared<FLOATS, TALL, F16>(g, st) : launch_dw_shared<NONE, TALL, F16>(g, st);
 }
+template <bool TALL>
+void launch_dw_shared_any(const DwArgs& g, hipStream_t st) { g.f16 ? launch_dw_shared_mask<TALL, true>(g, st) : launch_dw_shared_mask<TALL, false>(g, st); }
 
 template <class T, Core C, bool MASK, int VA, int VB, int TA, int TN>
 void launch_dw(const DwArgs& g, hipStream_t st) {
@@ -795,20 +809,18 @@ int pow2_up(int64_t x, int most) {
 //     (2 x 64 on 306,129 rows 0.025 ms against 0.111 in tiles through LDS, 3 x 256 0.077 against 0.186);
 //   m <= 32: 128 x 32, on the fp32 instructions 32 x 32 for k <= 32 (padding is dear there: 16 x 16 on 300,000 rows 17.4
 //     against 39.1 us);
-//   fp32 with m > 32 in dw_own_kernel, 256 x 64 (or 64 x 256 for k <= 64): always for m <= 64, else while the tiles, each of which reads its columns of A
-//     again, are few against the rows.  From fp16 pieces from F16_ROWS on, as in dw_shared_kernel: in a sum of few products each one's error shows, which of
-//     fp16 pieces is up to 2^-21 to either side, of bf16 pieces to one.  us in the shapes below / there, without and with the ReLU mask: 256 x 47 on 1,000 rows
-//     15.0 15.9 / 9.2 10.0, 24,000 18.0 18.8 / 15.7 16.7, 41,000 21.6 23.4 / 18.7 20.2, 200,000 47.6 56.4 / 46.2 52.9; 128 x 40 on 24,000 16.7 17.5 / 12.7 13.1; 64 x 47 on
-//     3,000 11.7 14.0 / 8.4 9.1; 602 x 64 on 41,000 32.1 35.6 / 29.1 31.7; 128 x 128 on 10,000 17.4 17.9 / 12.1 13.1, 200,000 48.2 65.4 / 43.7 61.5.  256 x 256 on
-//     10,000 24.4 22.0 / 20.5 19.9, 24,000 29.8 32.4 / 27.7 29.5, 41,000 33.9 36.1 / 33.8 38.0; 300 x 256 (eight tiles) on 10,000 25.2 24.9 / 24.6 23.9, 24,000 30.2
-//     33.8 / 40.6 42.7; 602 x 128 (six) on 10,000 22.7 23.9 / 21.1 22.5, 24,000 30.7 32.0 / 35.1 36.8; 200 x 172 (three) on 41,000 30.9 32.9 / 27.2 31.5, 100,000 54.0 56.5 / 50.1
-//     57.4; 128 x 256 (four of half the size) on 60,000 30.8 38.6 / 30.0 37.2, 100,000 40.2 53.5 / 44.3 61.7.  k <= 64: 41 x 128 on 100,000 22.3 28.4 / 19.4 26.9,
-//     200,000 30.9 43.5 / 28.6 44.8; 64 x 256 54.7 94.3 / 49.2 88.6; 16 x 47 on 41,000 13.1 15.2 / 11.7 12.3, 200,000 20.5 25.0 / 22.0 25.1;
+//   fp32 with m > 32 in dw_own_kernel, 256 x 64 (or 64 x 256 for k <= 64), while the tiles, each of which reads its columns of A again, are few against the
+//     rows.  From fp16 pieces from F16_ROWS rows (in a sum of few products each one's error shows, which of fp16 pieces is up to 2^-21 to either side, of bf16
+//     pieces to one) and F16_COLUMNS columns on; fewer columns of as many rows have a rule and figures of their own (at F16_COLUMNS).  us in the shapes below /
+//     there, without and with the ReLU mask: 256 x 47 on 1,000 rows 15.0 15.9 / 9.2 10.0, 24,000 18.0 18.8 / 15.7 16.7; 128 x 40 on 24,000 16.7 17.5 / 12.7 13.1; 64 x 47 on
+//     3,000 11.7 14.0 / 8.4 9.1; 128 x 128 on 10,000 17.4 17.9 / 12.1 13.1; 256 x 256 on 10,000 24.4 22.0 / 20.5 19.9, 24,000 29.8 32.4 / 27.7 29.5, 41,000 33.9 36.1 / 33.8
+//     38.0; 300 x 256 (eight tiles) on 10,000 25.2 24.9 / 24.6 23.9, 24,000 30.2 33.8 / 40.6 42.7; 602 x 128 (six) on 10,000 22.7 23.9 / 21.1 22.5, 24,000 30.7 32.0 / 35.1
+//     36.8; 128 x 256 (four of half the size) on 60,000 30.8 38.6 / 30.0 37.2, 100,000 40.2 53.5 / 44.3 61.7; 64 x 256 on 200,000 54.7 94.3 / 49.2 88.6;
 //   else k <= 64 < m: 64 x 64 (a 128-column tile would be mostly padding);
 //   fp32 whose tiles of 128 x 128 pair up, of an odd number of them all but the last (padding of a third or less), and whose blocks get 192
-//     rows or more: 256 x 128 (or 128 x 256) per block of dw_shared_kernel (us in dw_kernel / here, without and with the ReLU mask: 256 x 256 on
-//     24,576 rows 31.2 34.3 / 28.4 29.9, 49,152 46.6 53.1 / 39.4 41.7, 128 x 256 on 65,536 36.6 42.2 / 32.9 40.5, 256 x 128 36.4 40.7 / 33.1 35.6; with
-//     a padded pair 602 x 128 on 58,241 63.5 70.8 / 55.7 58.1, 300 x 128 42.8 48.5 / 40.7 43.0, 300 x 300 on 20,000 40.9 45.2 / 39.2 39.3 and on
+//     rows or more: 256 x 128 (or 128 x 256) per block of dw_shared_kernel, from F16_COLUMNS columns on (us in dw_kernel / here, without and with the ReLU mask: 256 x 256 on
+//     24,576 rows 31.2 34.3 / 28.4 29.9, 49,152 46.6 53.1 / 39.4 41.7, 128 x 256 on 65,536 36.6 42.2 / 32.9 40.5; with
+//     a padded pair 300 x 300 on 20,000 40.9 45.2 / 39.2 39.3 and on
 //     100,000 155 189 / 138 161).  Below that the longer tail of a block eats the gain (256 x 256 on 16,384 25.2 26.9 / 24.9 25.9, 128 x 256 on 32,768
 //     25.7 28.6 / 25.5 29.9); a padded pair on the side of dZ reads its mask for nothing (128 x 300 on 100,000 62.8 78.2 / 58.2 85.0);
 //   else 128 x 64, whose operands are cut into pieces for 48 matrix instructions instead of 24 a step: 256 x 256 on 169,343
@@ -821,15 +833,30 @@ int pow2_up(int64_t x, int most) {
 // (602 x 128 on 58,241 rows 0.101 -> 0.070 ms, 384 x 384 on 169,343 0.465 -> 0.295, 700 x 100 on 8,000 0.033 -> 0.023).
 // Two column tiles side by side where there are two (they share the rows of A through the L1), the other wavefronts share out
 // the rows.
-constexpr int64_t F16_ROWS = 24576;
+// fp16 pieces only from F16_COLUMNS columns of dZ on: the gradient of a softmax is one large element a row among small ones that hardly differ, and the
+// matrix instruction drops bits of the small products of 22 bits beside a large one, to the same side in all rows, where the products of bf16 pieces have 16: what
+// the sums over all rows cancel to shows it.  Relative error of an untrained output layer's dW (its input all positive), bf16 / fp16 pieces: 256 x 47 on 162,500 rows
+// 0.8e-6 / 1.3e-6, 256 x 172 0.9e-6 / 1.8e-6, 128 x 128 0.8e-6 / 1.9e-6; in a worker's share 256 -> 40 1.1e-7 / 4.3e-7, 256 -> 172 1.6e-7 / 6.2e-7.  Hidden layers, 128 and
+// 256 columns: 0.7e-7 to 3.4e-7 / 0.5e-7 to 2.7e-7.  us in the shapes below / in dw_own_kernel, from bf16 pieces, without and with the ReLU mask: 256 x 47 on 24,600
+// rows 18.4 19.6 / 16.6 17.4, 41,000 21.3 22.9 / 20.3 22.1, 100,000 31.5 33.2 / 30.8 35.4, 306,129 78 88 / 82 96; 128 x 41 on 58,241 19.3 21.2 / 16.3 18.1, 128 x 64 on 306,129 46.6
+// 59.8 / 44.3 57.4; 64 x 47 on 41,000 13.8 15.7 / 11.7 12.7; 41 x 128 on 100,000 22.2 28.4 / 20.5 27.5, 200,000 30.9 43.2 / 31.1 43.5; 128 x 128 on 100,000 31.4 35.7 / 30.5 34.5,
+// 306,129 77 98 / 83 102; 256 x 128 on 60,000 33.9 37.2 / 32.1 34.5, 200,000 86 96 / 88 105; 200 x 172 on 100,000 68.8 69.8 / 61.0 67.7, 306,129 rows of 256 x 172 211 225 / 198 233;
+// 602 x 64 on 41,000 31.6 34.1 / 32.7 34.6, 602 x 128 on 58,241 61 68 / 70 73.
+constexpr int64_t F16_ROWS = 24576, F16_COLUMNS = 193;
 enum { DW_NARROW, DW_SHORT, DW_WIDE, DW_TINY, DW_SHARED_TALL, DW_SHARED_WIDE, DW_OWN };
 int dw_shape(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
     const int64_t tk = (k + 127) / 128, tm = (m + 127) / 128;
+    const bool pieces = shared && !fp32_core && k >= 4 && m > 32;
+    if (pieces && n >= F16_ROWS && m < F16_COLUMNS) {          // bf16 pieces
+        if (k <= 64 ? n <= 131072 : k <= 128 ? m <= 64 || n <= 98304 : k <= 256 && (m > 128 || n <= 65536)) return DW_OWN;
+        if (k > 64 && m > 64 && (tk % 2 == 0 || tm % 2 == 0) && n * ((tk * tm + 1) / 2) >= 131072) return tk % 2 == 0 ? DW_SHARED_TALL : DW_SHARED_WIDE;
+        return k <= 64 ? DW_SHORT : DW_WIDE;
+    }
     const int64_t own_tiles = (k + 255) / 256 * ((m + 63) / 64), most = k <= 128 ? 262144 : n < F16_ROWS ? 98304 : 131072;
     const bool own = k <= 64 ? m > 128 || n <= 131072 : m <= 64 || (k <= 128 && m <= 128) || n * own_tiles <= most;
-    if (shared && !fp32_core && k >= 4 && m > 32 && own) return DW_OWN;
+    if (pieces && own) return DW_OWN;
     const bool tall = tk % 2 == 0 || (tm % 2 != 0 && tk > 1 && tk >= tm), wide = !tall && tm % 2 == 0;
-    if (shared && !fp32_core && k > 64 && m > 64 && (tall || wide) && n * (tall ? (tk + 1) / 2 * tm : tk * (tm / 2)) >= 49152)
+    if (pieces && k > 64 && m > 64 && (tall || wide) && n * (tall ? (tk + 1) / 2 * tm : tk * (tm / 2)) >= 49152)
         return tall ? DW_SHARED_TALL : DW_SHARED_WIDE;
     if (k < 4) return DW_TINY;
     if (m > 32) return k <= 64 ? DW_SHORT : DW_WIDE;
@@ -844,6 +871,7 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
         const int bk = shape == DW_SHARED_TALL ? 256 : 128, bz = 384 - bk;
         g.tiles_k = (int)((k + bk - 1) / bk);
         g.tiles_m = (int)((m + bz - 1) / bz);
+        g.f16 = m >= F16_COLUMNS;
         int64_t s = std::max<int64_t>(1, compute_units() / ((int64_t)g.tiles_k * g.tiles_m));
         g.rows_per_split = ((n + s - 1) / s + 31) / 32 * 32;
         g.n_splits = (int)((n + g.rows_per_split - 1) / g.rows_per_split);
@@ -851,7 +879,7 @@ DwArgs dw_plan(int64_t n, int64_t k, int64_t m, bool fp32_core, bool shared) {
         return g;
     }
     if (shape == DW_OWN) {
-        g.f16 = n >= F16_ROWS;
+        g.f16 = n >= F16_ROWS && m >= F16_COLUMNS;
         g.swap = k <= 32 || (k <= 64 && m > 64);
         const int64_t wide = g.swap ? m : k, narrow = g.swap ? k : m;
         g.kt = wide <= 64 ? 2 : wide <= 128 ? 4 : 8;

@@ -366,7 +366,7 @@ def test_wide_weight_gradients_in_half_the_workspace():
 
 
 # the fewest rows, rows of no whole tile or step, columns of dZ in no whole eights; dW's blocks of 256 x 128, 128 x 256, and of owned columns
-@pytest.mark.parametrize("n,k,m", [(57345, 256, 256), (57377, 200, 65), (98350, 100, 250), (98333, 128, 129), (70001, 129, 71), (98305, 128, 200), (98311, 65, 140), (60001, 97, 128), (58241, 256, 101)])
+@pytest.mark.parametrize("n,k,m", [(57345, 256, 256), (57377, 200, 65), (98350, 100, 250), (131100, 128, 129), (65500, 129, 71), (98305, 128, 200), (131081, 65, 140), (60001, 97, 128), (58241, 256, 101)])
 def test_gradients_that_share_the_mask_as_bits(n, k, m):
     """dW beside dA, whose kernel leaves the mask as bits, has the bits that it has alone, from H, and in a workspace without room for the mask"""
     import torch
