@@ -417,7 +417,7 @@ def step_bench(args, cfg, scale_down=1, agg_dtype="f32", copy_gbs=None, graph=No
     # arithmetic type of the step: fp32 storage and accumulation; the transforms form every fp32
     # product from three bf16 pieces per operand on the bf16 matrix instructions (as accurate as fp32
     # arithmetic; narrow products use the fp32 matrix instructions)
-    dtype_full = "bf16 (fp32 accumulate)" if share_bf16 else ("f32 (transform: 3x bf16-split MFMA)" if split_core else "f32")
+    dtype_full = "bf16 (fp32 accumulate)" if share_bf16 else ("f32 (transform: bf16 or fp16 pieces on MFMA)" if split_core else "f32")
     out = {
         "metric": "aggregation GEPS (stored entries x F_slice / s) over the step; epoch ms in ms_per_step",
         "value": geps, "unit": "GEPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,

@@ -9,7 +9,7 @@
 // flight while the present ones are cut into bf16 pieces and multiplied; no barrier until the end.  A block of eight
 // wavefronts is a few neighbouring tiles x shares of the rows of one range of vertices; the shares are added through
 // LDS in a fixed order, the ranges by sum_splits_kernel: deterministic.  Wide fp32 products of many rows go through LDS all the
-// same (dw_shared_kernel, with fp16 pieces): there the cutting costs more than the transposition.
+// same (dw_shared_kernel, of wide dZ with fp16 pieces): there the cutting costs more than the transposition.
 //
 // Bound: memory for a narrow side (256 x 64 on 169,343 rows: 217 MB in 0.043 ms = 5.0 TB/s), the two pipes of the SIMD
 // otherwise (256 x 256 here: matrix instructions 49 % of the time, other vector instructions 40 %, half of them beside those).

@@ -8,7 +8,8 @@
 // together, which sums of 64 and more terms do not show: rms error over the sum of magnitudes at 64 / 256 / 602 terms
 // 2.4e-8 / 2.4e-8 / 2.4e-8 (positive terms 0.9e-7 / 1.9e-7 / 3.3e-7) against 2.8e-8 (1.2e-7 / 2.2e-7 / 3.8e-7) of the fp32
 // instructions, which round more often.  Six bf16 instructions cost 6 x 32 cycles per 32x32x16 block against 8 x 64 for
-// fp32, and operands that are bf16 in memory need one piece only.  fp32 products with a contraction below 64 or an output
+// fp32, and operands that are bf16 in memory need one piece only.  (Products of many rows are formed from two fp16 pieces:
+// nn_util.h.)  fp32 products with a contraction below 64 or an output
 // of up to 32 columns run on the fp32 instructions (fp32_core below).  H and dA: nn_strip_kernels.hip; dW:
 // nn_dw_kernels.hip, partial sums to the caller's workspace, added in order here (deterministic, no atomics).
 //
