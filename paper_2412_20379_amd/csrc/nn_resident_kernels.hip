@@ -535,20 +535,24 @@ static bool bf16_takes(int64_t n, int64_t K, int64_t N) { return K > 64 && K <= 
 // 163,900 rows 128 -> 256 60 / 50, 129 -> 193 70 / 64, 256 -> 193 107 / 84, 169,343 256 -> 256 128 / 96, 200,000 65 -> 256 63 / 56, 100 -> 225 66 / 63, 128 -> 225 79 / 68,
 // 306,129 100 -> 256 95 / 76, 256 -> 256 221 / 160, a million 665 / 480.  Narrower ones stay (200,000 rows 65 -> 225 51 / 57, 100 -> 200 53 / 57, 128 -> 200 68 / 67,
 // 256 -> 192 130 / 131).  Where the sums of all blocks cancel to a few parts in 10^7, 306,129 rows of 256 -> 256 take 209 / 755.
-static bool f16_takes(int64_t n, int64_t K, int64_t N, bool relu) {
+// dA of 129 to 192 columns of dZ keeps the bf16 pieces: that of a softmax over 172 classes is summed over rows whose parts nearly cancel, and weight gradients of
+// the layers below came out 1.1e-5 from before, more than sums of the same numbers in another order differ by, though nearer to 64 bits (sums of dA that
+// cancel so 9.7e-6 from bf16 pieces, 3.6e-6 from fp16).
+static bool f16_takes(int64_t n, int64_t K, int64_t N, bool relu, bool backward) {
+    if (backward && K > 128 && K <= 192) return false;
     if (relu) return K > 64 && K <= 256 && N > (K <= 96 ? 240 : K <= 128 ? 224 : 192) && N <= 256 && n > 163840;
     return K > 64 && K <= 256 && N > 64 && N <= 256 && n > (N <= 128 && K > 128 ? 98304 : 57344);
 }
 
-bool nn_resident_writes_bits(int64_t n, int64_t K, int64_t N) { return f16_takes(n, K, N, false) && n <= NN_MASK_MOST_ROWS; }
+bool nn_resident_writes_bits(int64_t n, int64_t K, int64_t N) { return f16_takes(n, K, N, false, true) && n <= NN_MASK_MOST_ROWS; }
 
-bool nn_resident_takes(int64_t n, int64_t K, int64_t N, bool relu) { return bf16_takes(n, K, N) || f16_takes(n, K, N, relu); }
+bool nn_resident_takes(int64_t n, int64_t K, int64_t N, bool relu, bool backward) { return bf16_takes(n, K, N) || f16_takes(n, K, N, relu, backward); }
 
 int launch_nn_resident(const float* A, const float* mask, const float* B, float* C, int64_t n, int64_t K, int64_t N, int64_t ldb,
                        bool b_kcontig, bool relu, bool nt, unsigned char* bits, void* stream) {
     ResidentArgs g{A, mask, B, C, n, ldb, (int)K, (int)N, b_kcontig, relu, nt, bits, (int)nn_mask_rows(n)};
     const hipStream_t st = (hipStream_t)stream;
-    if (f16_takes(n, K, N, relu)) {
+    if (f16_takes(n, K, N, relu, b_kcontig)) {
         if (mask) launch_f16_k<true, false>(g, nt, st);
         else if (relu) launch_f16_k<false, true>(g, nt, st);
         else launch_f16_k<false, false>(g, nt, st);

@@ -690,7 +690,7 @@ int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.b_kcontig = b_kcontig; g.relu = relu;
     const hipStream_t st = (hipStream_t)stream;
-    if (dtype == NTP_F32 && !fp32_core && nn_resident_takes(n, K, N, relu) && lda == K && ldc == N) {
+    if (dtype == NTP_F32 && !fp32_core && nn_resident_takes(n, K, N, relu, b_kcontig) && lda == K && ldc == N) {
         const bool nt = ldc * 4 % 128 == 0 && (uintptr_t)C % 128 == 0 && n * ldc * 4 > CACHE_BYTES;
         return launch_nn_resident(static_cast<const float*>(A), static_cast<const float*>(mask), static_cast<const float*>(B), static_cast<float*>(C),
                                   n, K, N, ldb, b_kcontig, relu, nt, bits, stream);

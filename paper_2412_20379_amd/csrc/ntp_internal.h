@@ -423,7 +423,7 @@ int64_t nn_bwd_workspace_bytes(int64_t n, int64_t k, int64_t m, bool shared = tr
 int launch_nn_strip(const void* A, const void* mask, const void* B, void* C, int64_t n, int64_t K, int64_t N, int64_t lda,
                     int64_t ldb, int64_t ldc, bool b_kcontig, bool relu, int dtype, bool fp32_core, void* stream, unsigned char* bits = nullptr);
 // the same with B resident in registers (nn_resident_kernels.hip): fp32 from bf16 or fp16 pieces, dense A and C
-bool nn_resident_takes(int64_t n, int64_t K, int64_t N, bool relu);
+bool nn_resident_takes(int64_t n, int64_t K, int64_t N, bool relu, bool backward);
 int launch_nn_resident(const float* A, const float* mask, const float* B, float* C, int64_t n, int64_t K, int64_t N, int64_t ldb,
                        bool b_kcontig, bool relu, bool nt, unsigned char* bits, void* stream);
 // A ReLU mask as bits, from the kernel of dA to that of dW: bit c % 8 of bits[c / 8 * nn_mask_rows(n) + row] is mask[row][c] > 0.  Both kernels address it
